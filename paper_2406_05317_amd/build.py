@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblococo.so")
 
-SOURCES = ["api.cpp", "generic_kernels.hip", "compress_mfma.hip", "attn_mfma.hip", "attn_decode.hip",
+SOURCES = ["api.cpp", "generic_kernels.hip", "scan_small.hip", "compress_mfma.hip", "attn_mfma.hip", "attn_decode.hip",
            "backward_generic.hip", "tiled_mfma.hip", "peaks.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

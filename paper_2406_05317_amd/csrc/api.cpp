@@ -62,11 +62,11 @@ lococo_status hip_fail(hipError_t e, const char* what) {
 // ---- optional per-kernel timing with HIP events (lococo_timing_begin / _end)
 enum KernelId { K_ATTN_GENERIC, K_FILL, K_CONV_GENERIC, K_NORM_GENERIC, K_MIX_GENERIC,
                 K_REPACK, K_COMPRESS_MFMA, K_ATTN_MFMA, K_ATTN_DECODE, K_ATTN_COLSUM, K_CONV_MFMA, K_MIX_MFMA,
-                K_COUNT };
+                K_COMPRESS_SMALL, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"attn_generic", "fill", "conv_logits_generic",
                                            "normalise_generic", "mix_generic", "repack_filters",
                                            "compress_mfma", "attn_mfma", "attn_decode", "attn_colsum",
-                                           "conv_logits_mfma", "mix_mfma"};
+                                           "conv_logits_mfma", "mix_mfma", "compress_small"};
 struct TimedLaunch { int id; hipEvent_t start, stop; };
 std::mutex g_timing_mu;
 bool g_timing_on = false;
@@ -268,6 +268,11 @@ size_t history_ws_bytes(const lococo_config* c, Path path, int32_t B, int64_t n_
   return step_ws_bytes(c, path, B) + stats_bytes(c, L) + 2 * (size_t)n_compress * align_up(state_bytes(c), 256);
 }
 
+// Whether the schedules that run the attention of many blocks in one launch exist for this shape
+bool batched_attention(const lococo_config* c, Path path, int32_t B) {
+  return path != PATH_GENERIC || attn_rows_fits(c->M + B);
+}
+
 // Polls a waiting workgroup makes before it gives up on its chain (each poll sleeps ~128 cycles and
 // reads the counter from the L2: roughly a microsecond, so the default bounds a wait to a few
 // seconds).  The tests force the give-up path from the host with a limit of -1.
@@ -441,7 +446,8 @@ lococo_status enqueue_attn(const lococo_config* c, Path path, const StepArgs& a,
     return LOCOCO_OK;
   }
   KTimer t(K_ATTN_GENERIC, s);
-  HIP_TRY(launch_attn_generic(c->dtype, a, s), "attention launch");
+  if (attn_rows_fits(a.m + a.Bn)) HIP_TRY(launch_attn_rows(c->dtype, attn_args_one_block(a), c->head_dim, a.colsum, s), "attention launch");
+  else HIP_TRY(launch_attn_generic(c->dtype, a, s), "attention launch");
   return LOCOCO_OK;
 }
 
@@ -471,6 +477,11 @@ lococo_status enqueue_compress(const lococo_config* c, Path path, StepArgs a, vo
     HIP_TRY(launch_compress_mfma(a, ws, filter_banks(c), cu_count(), (char*)ws + filter_ws_bytes(c), partials_of(c, ws, B),
                                  prelogits_of(c, ws, B), B, s),
             "compress launch");
+    return LOCOCO_OK;
+  }
+  if (path == PATH_GENERIC && small_step_fits(a.M + B, a.M, a.d, a.k_width, a.conv_in)) {
+    KTimer t(K_COMPRESS_SMALL, s);
+    HIP_TRY(launch_compress_small(c->dtype, a, a.M + B, 1, B, a.Bn, a.new_k, a.new_v, 0, 0, 1, s), "compress launch");
     return LOCOCO_OK;
   }
   const bool unfused = path == PATH_MFMA_UNFUSED;
@@ -740,7 +751,7 @@ lococo_status lococo_workspace_bytes(const lococo_config* cfg, int64_t L, int32_
   if ((st = resolve_path(cfg, B, &path))) return st;
   const int64_t n_blocks = (L + B - 1) / B;
   if (history < 0) return fail(LOCOCO_EINVAL, "history must be >= 0");
-  if (history == 0 || path == PATH_GENERIC || n_blocks == 0)
+  if (history == 0 || !batched_attention(cfg, path, B) || n_blocks == 0)
     *out = step_ws_bytes(cfg, path, B);
   else if (history == 1 || history >= n_blocks)
     *out = history_ws_bytes(cfg, path, B, n_blocks, L);             // every block may compress
@@ -861,7 +872,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
   // window of G blocks, the extra one being the state the window starts from); memory then stays
   // independent of the sequence length, as in the step-by-step schedule.
   int64_t window = 0, ring = 0;
-  if (path != PATH_GENERIC && any_compress && workspace) {
+  if (batched_attention(cfg, path, B) && any_compress && workspace) {
     if (ws_bytes >= history_ws_bytes(cfg, path, B, n_compress, L)) {
       window = n;
       ring = n_compress;
@@ -886,6 +897,8 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       StepArgs probe = make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true);
       one_launch = scan_fits_one_launch(cfg, probe);
     }
+    const bool small_scan = path == PATH_GENERIC && small_step_fits(cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in) &&
+                            small_scan_one_launch(cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
     for (int64_t w0 = 0; w0 < n; w0 += window) {
       const int64_t w1 = std::min<int64_t>(n, w0 + window);
@@ -943,6 +956,13 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
             break;
           }
         }
+        if (small_scan) {                // one workgroup per chain walks the rest of the window
+          KTimer t(K_COMPRESS_SMALL, s);
+          HIP_TRY(launch_compress_small(cfg->dtype, a, cfg->M + B, (int)(w1 - bi), B, L - sg.start, hist_k, hist_v, hist_stride,
+                                        (int)(c_done % ring), (int)ring, s), "compress scan launch");
+          c_done += w1 - bi;
+          break;
+        }
         a.new_k = slot_k(c_done);
         a.new_v = slot_v(c_done);
         if ((st = enqueue_compress(cfg, path, a, workspace, B, s))) return st;
@@ -974,11 +994,14 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
         t.n_fill = (int32_t)std::min<int64_t>(fills, w_batched - w0);
         t.n_seg = (int32_t)(w_batched - w0);
         t.stats = cache->attn_colsum ? win_stats : nullptr;
-        {
+        if (path == PATH_GENERIC) {
+          KTimer kt(K_ATTN_GENERIC, s);
+          HIP_TRY(launch_attn_rows(cfg->dtype, t, cfg->head_dim, cache->attn_colsum, s), "attention launch");
+        } else {
           KTimer kt(K_ATTN_MFMA, s);
           HIP_TRY(launch_attn_mfma(t, s), "attention launch");
         }
-        if (cache->attn_colsum) {           // sums over blocks commute: one launch for all of the window's
+        if (cache->attn_colsum && path != PATH_GENERIC) {   // sums over blocks commute: one launch for all of the window's
           KTimer kt(K_ATTN_COLSUM, s);
           HIP_TRY(launch_attn_colsum_mfma(t, cache->attn_colsum, s), "attention column-sum launch");
         }

@@ -154,6 +154,19 @@ hipError_t launch_mix_generic(int dtype, const StepArgs& a, const float* w, int 
 // normalisation); protected rows of the new cache <- the old rows (after the mix)
 hipError_t launch_protect_logits_generic(const StepArgs& a, float* logits, hipStream_t s);
 hipError_t launch_protect_rows_generic(int dtype, const StepArgs& a, hipStream_t s);
+// ---- small scans of the shape-agnostic path (scan_small.hip): Eq. 5, 6 and 4 of a step in one kernel
+// T: the largest m + Bn of the call
+bool small_step_fits(int T, int M, int d, int k, int conv_in);
+// whether all steps of a scan fit one launch of one workgroup per chain
+bool small_scan_one_launch(int T, int M, int d, int k, int conv_in);
+// n_steps consecutive compress steps (n_steps > 1 only where small_scan_one_launch), step 0 described by `a`, step s
+// taking the block s*B tokens further on (fewer where tokens_left runs out) and writing state (slot0 + s) % ring
+hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_steps, int B, int64_t tokens_left, void* out_k,
+                                 void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s);
+// attention of the blocks of a window, a wave per query row; T: M + B
+bool attn_rows_fits(int T);
+hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s);
+
 // largest T = m + Bn the generic attention kernel can hold in LDS
 int generic_attn_max_T();
 
