@@ -355,7 +355,8 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  * w.r.t. that block's resulting state.  The call runs the cache recurrence once more block by
  * block (the fill branch or steps 4-5), keeping the state every block starts from in the workspace, then walks the
  * blocks backwards through lococo_segment_step_backward; gradients therefore match that entry
- * point's composed by hand, launch for launch.
+ * point's composed by hand (on the MFMA kernels the attention of many blocks runs in one launch ahead of the walk, a
+ * window of them at a time, so the workspace does not grow faster with L than the kept states).
  *   seq: q, k, v of the L tokens as in the forward (o is not read); cache0: the state the scan
  *   starts from (not modified; its attn_colsum is neither read nor written).
  *   Gradients are fp32 device arrays, contiguous:
@@ -365,7 +366,7 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *          [batch, n_kv_heads, M, d] (rows that were not live in cache0 are zero); all overwritten;
  *     acc  d_conv_w, d_conv_b: ADDED to, as in the step (d_conv_b may be NULL).
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
- *   states per block (storage type) plus one step's worth of everything else.
+ *   states per block (storage type), one step's worth of everything else and at most 1 GiB for the window.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */
 LOCOCO_API lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg, int64_t L, int32_t B,
                                                                   size_t* out);

@@ -1048,6 +1048,26 @@ namespace {
 bool bwd_on_mfma(const lococo_config* c) {
   return c->impl != LOCOCO_IMPL_GENERIC && bwd_mfma_supports(c->dtype, c->head_dim, c->conv_in, c->conv_width);
 }
+bool bwd_attn_has_mfma(const lococo_config* c) {
+  const char* why;
+  return c->impl != LOCOCO_IMPL_GENERIC && attn_mfma_supports(c->dtype, c->head_dim, &why);
+}
+// the attention of the backward pass runs on its own MFMA kernels (bwd_attn_mfma.hip) where a block's rows can be
+// addressed with 32-bit offsets
+bool bwd_attn_on_mfma(const lococo_config* c, const lococo_qkvo* x, int32_t B) {
+  if (!bwd_attn_has_mfma(c)) return false;
+  const int64_t lim = 0x7fff0000;
+  for (const lococo_tensor* t : {&x->q, &x->k, &x->v})
+    if (((int64_t)B * t->stride_t + c->head_dim) * 2 >= lim) return false;
+  return (int64_t)c->M * c->head_dim * 2 < lim && (int64_t)B * c->head_dim * 4 < lim;
+}
+// scratch of those kernels for `rows` query rows per head: dO as two bf16 halves, three floats of row statistics
+size_t bwd_attn_hl_bytes(const lococo_config* c, int64_t rows) {
+  return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * c->head_dim * 4, 256);
+}
+size_t bwd_attn_stat_bytes(const lococo_config* c, int64_t rows) {
+  return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * 3 * sizeof(float), 256);
+}
 struct BwdLayout { size_t p, ds, w, n, dw, mf, total; };
 BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   const size_t T = (size_t)len + B;
@@ -1055,9 +1075,9 @@ BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   const bool compress = len + B > c->M;
   const size_t mat = compress ? (size_t)c->batch * c->n_kv_heads * c->M * T * sizeof(float) : 0;
   BwdLayout l;
-  l.p = 0;
-  l.ds = align_up(rows, 256);
-  l.w = l.ds + align_up(rows, 256);
+  l.p = 0;                                     // attention rows, or dO as two halves; then their gradient, or the statistics
+  l.ds = std::max(align_up(rows, 256), bwd_attn_hl_bytes(c, B));
+  l.w = l.ds + std::max(align_up(rows, 256), bwd_attn_stat_bytes(c, B));
   l.n = l.w + align_up(mat, 256);
   l.dw = l.n + align_up(mat, 256);
   l.mf = l.dw + align_up(mat, 256);
@@ -1065,6 +1085,44 @@ BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   if (compress && bwd_on_mfma(c))
     l.total += bwd_mfma_layout(c->batch, c->n_kv_heads, c->M, (int)T, c->conv_width, c->conv_in, filter_banks(c)).total;
   return l;
+}
+// The attention of the blocks of `t` (see BwdAttnArgs; the gradient arrays hold `rows` query / block rows per head from
+// the first token of the window on)
+lococo_status enqueue_bwd_attn(const lococo_config* c, BwdAttnArgs t, int64_t rows, char* hl, char* stats, hipStream_t s) {
+  t.q_sh = t.k_sh = rows * c->head_dim;
+  t.q_sb = t.q_sh * c->n_q_heads;
+  t.k_sb = t.k_sh * c->n_kv_heads;
+  t.do_hl = (uint16_t*)hl;
+  t.stats = (float*)stats;
+  HIP_TRY(launch_bwd_attn_mfma(t, s), "attention backward launches");
+  return LOCOCO_OK;
+}
+
+// Everything of a step's backward pass but (where g.attn_done) its attention.  `g`: all but the workspace filled in.
+lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool compress, const BwdLayout& l, char* ws, hipStream_t s) {
+  g.ws_p = (float*)(ws + l.p);
+  g.ws_ds = (float*)(ws + l.ds);
+  g.ws_w = (float*)(ws + l.w);
+  g.ws_n = (float*)(ws + l.n);
+  g.ws_dw = (float*)(ws + l.dw);
+  g.ws_mfma = compress && bwd_on_mfma(cfg) ? ws + l.mf : nullptr;
+  g.banks = filter_banks(cfg);
+  g.gemms_mfma = cfg->impl != LOCOCO_IMPL_GENERIC && cfg->dtype == LOCOCO_BF16 ? 1 : 0;
+  if (compress) {
+    // recompute Eq. 5 and Eq. 6 of the forward step: raw logits and normalised rows
+    if (g.ws_mfma) {
+      HIP_TRY(launch_pack_filters_per_tap(g.st, g.banks, g.ws_mfma, s), "filter packing launch");
+      HIP_TRY(launch_conv_logits_mfma(g.st, g.ws_mfma, g.ws_w, s), "conv launch");
+    } else {
+      HIP_TRY(launch_conv_logits_generic(cfg->dtype, g.st, g.ws_w, s), "conv launch");
+    }
+    if (g.st.protect) HIP_TRY(launch_protect_logits_generic(g.st, g.ws_w, s), "protect launch");
+    const size_t mat = (size_t)cfg->batch * cfg->n_kv_heads * cfg->M * ((size_t)g.st.m + g.st.Bn) * sizeof(float);
+    HIP_TRY(hipMemcpyAsync(g.ws_n, g.ws_w, mat, hipMemcpyDeviceToDevice, s), "copying the logits");
+    HIP_TRY(launch_normalise_generic(g.st, g.ws_n, s), "normalise launch");
+  }
+  HIP_TRY(launch_step_backward_generic(cfg->dtype, g, compress, s), "backward launches");
+  return LOCOCO_OK;
 }
 }  // namespace
 
@@ -1105,7 +1163,7 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
   hipStream_t s = (hipStream_t)stream;
   lococo_qkvo x = *blk;
   x.o = x.q;                                  // not read; keeps make_args' view arithmetic defined
-  BwdArgs g;
+  BwdArgs g{};
   g.st = make_args(cfg, &x, 0, B, cache_before, conv_w, conv_b, true);
   g.d_o = d_o;
   g.d_new_k = d_new_k;
@@ -1117,31 +1175,20 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
   g.d_cache_v = d_cache_v;
   g.d_conv_w = d_conv_w;
   g.d_conv_b = d_conv_b;
-  char* ws = (char*)workspace;
-  g.ws_p = (float*)(ws + l.p);
-  g.ws_ds = (float*)(ws + l.ds);
-  g.ws_w = (float*)(ws + l.w);
-  g.ws_n = (float*)(ws + l.n);
-  g.ws_dw = (float*)(ws + l.dw);
-  g.ws_mfma = compress && bwd_on_mfma(cfg) ? ws + l.mf : nullptr;
-  g.banks = filter_banks(cfg);
-  g.gemms_mfma = cfg->impl != LOCOCO_IMPL_GENERIC && cfg->dtype == LOCOCO_BF16 ? 1 : 0;
-  if (compress) {
-    // recompute Eq. 5 and Eq. 6 of the forward step: raw logits and normalised rows
-    if (g.ws_mfma) {
-      HIP_TRY(launch_pack_filters_per_tap(g.st, g.banks, g.ws_mfma, s), "filter packing launch");
-      HIP_TRY(launch_conv_logits_mfma(g.st, g.ws_mfma, g.ws_w, s), "conv launch");
-    } else {
-      HIP_TRY(launch_conv_logits_generic(cfg->dtype, g.st, g.ws_w, s), "conv launch");
-    }
-    if (g.st.protect) HIP_TRY(launch_protect_logits_generic(g.st, g.ws_w, s), "protect launch");
-    const size_t mat = (size_t)cfg->batch * cfg->n_kv_heads * cfg->M * ((size_t)cache_before->len + B) *
-                       sizeof(float);
-    HIP_TRY(hipMemcpyAsync(g.ws_n, g.ws_w, mat, hipMemcpyDeviceToDevice, s), "copying the logits");
-    HIP_TRY(launch_normalise_generic(g.st, g.ws_n, s), "normalise launch");
+  g.q_chain = g.kv_chain = (int64_t)B * cfg->head_dim;
+  if (bwd_attn_on_mfma(cfg, blk, B)) {
+    BwdAttnArgs t{};
+    t.a = attn_args_one_block(g.st);
+    t.d_o = d_o;
+    t.d_q = d_q;
+    t.d_k = d_k;
+    t.d_v = d_v;
+    t.d_ck = d_cache_k;
+    t.d_cv = d_cache_v;
+    if ((st = enqueue_bwd_attn(cfg, t, B, (char*)workspace + l.p, (char*)workspace + l.ds, s))) return st;
+    g.attn_done = 1;
   }
-  HIP_TRY(launch_step_backward_generic(cfg->dtype, g, compress, s), "backward launches");
-  return LOCOCO_OK;
+  return enqueue_step_backward(cfg, g, compress, l, (char*)workspace, s);
 }
 
 lococo_status lococo_mix_from_logits(const lococo_config* cfg, const lococo_qkvo* blk, int32_t B,
@@ -1182,15 +1229,20 @@ namespace {
 struct SeqBwdLayout {
   size_t cache[4];        // ping-pong buffers of the recomputed forward: k0, k1, v0, v1 (storage type)
   size_t states_k, states_v, state;   // the state BEFORE every block: n_blocks slots of `state` bytes each
-  size_t o_blk;           // attention output of one block of the recomputed forward (storage type; discarded)
   size_t fwd_ws, fwd_ws_bytes;        // step workspace of the recomputed forward
-  size_t d_o, d_q, d_k, d_v;          // one block of gradients, contiguous fp32
+  int64_t window;         // blocks whose attention runs in one launch (see lococo_sequence_backward)
+  size_t d_ck, d_cv, slot;            // gradients w.r.t. the state before each of them, fp32, `slot` bytes each
+  size_t hl, stats;       // scratch of those launches
   size_t g[2][2];         // gradient w.r.t. the cache state, ping-pong: [which][k, v], fp32 [chains, M, d]
   size_t step_ws;         // workspace of one backward step
   size_t total;
 };
+// What the window of the attention may take: enough blocks to fill the device many times over at any shape, whatever the
+// length of the sequence.
+constexpr size_t kBwdWindowBytes = (size_t)1 << 30;
+
 lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBwdLayout* out) {
-  SeqBwdLayout l;
+  SeqBwdLayout l{};
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
   const size_t chains = (size_t)c->batch * c->n_kv_heads, es = esize(c->dtype);
@@ -1199,18 +1251,22 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBw
   for (int i = 0; i < 4; ++i) l.cache[i] = take(l.state);
   l.states_k = take((size_t)n * l.state);
   l.states_v = take((size_t)n * l.state);
-  l.o_blk = take((size_t)c->batch * c->n_q_heads * B * c->head_dim * es);
   Path path;
   lococo_status st = resolve_path(c, B, &path);
   if (st) return st;
   l.fwd_ws_bytes = step_ws_bytes(c, path, B);
   l.fwd_ws = take(l.fwd_ws_bytes);
-  l.d_o = take((size_t)c->batch * c->n_q_heads * B * c->head_dim * sizeof(float));
-  l.d_q = take((size_t)c->batch * c->n_q_heads * B * c->head_dim * sizeof(float));
-  l.d_k = take(chains * B * c->head_dim * sizeof(float));
-  l.d_v = take(chains * B * c->head_dim * sizeof(float));
+  l.slot = align_up(chains * c->M * c->head_dim * sizeof(float), 256);
+  if (bwd_attn_has_mfma(c)) {
+    const size_t per_block = 2 * l.slot + bwd_attn_hl_bytes(c, B) + bwd_attn_stat_bytes(c, B);
+    l.window = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(kBwdWindowBytes / per_block)));
+    l.d_ck = take((size_t)l.window * l.slot);
+    l.d_cv = take((size_t)l.window * l.slot);
+    l.hl = take(bwd_attn_hl_bytes(c, l.window * (int64_t)B));
+    l.stats = take(bwd_attn_stat_bytes(c, l.window * (int64_t)B));
+  }
   for (int w = 0; w < 2; ++w)
-    for (int kv = 0; kv < 2; ++kv) l.g[w][kv] = take(chains * c->M * c->head_dim * sizeof(float));
+    for (int kv = 0; kv < 2; ++kv) l.g[w][kv] = take(l.slot);
   size_t step = 0;                    // a step's workspace grows with the occupancy: the full cache bounds all
   if ((st = lococo_backward_workspace_bytes(c, B, c->M, &step))) return st;
   l.step_ws = take(step);
@@ -1291,10 +1347,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
     if (i + 1 == n) break;                                   // the last block's own update is not needed
     lococo_qkvo blk = *seq;
     for (lococo_tensor* t : {&blk.q, &blk.k, &blk.v}) t->p = (char*)t->p + (size_t)(sg.start * t->stride_t) * es;
-    blk.o.p = ws + l.o_blk;                                  // (never written)
-    blk.o.stride_t = (int64_t)d;
-    blk.o.stride_h = (int64_t)sg.len * (int64_t)d;
-    blk.o.stride_b = (int64_t)cfg->n_q_heads * blk.o.stride_h;
+    blk.o = blk.q;                                           // (never written)
     const StepArgs a = make_args(cfg, &blk, 0, sg.len, &fc, conv_w, conv_b, true);
     if (sg.branch == 1 && path != PATH_GENERIC && !filters_ready) {
       if ((st = enqueue_repack(cfg, path, a, ws + l.fwd_ws, s))) return st;
@@ -1305,46 +1358,91 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
     fc = next;
   }
 
-  // ---- reverse walk.  g[w] = gradient w.r.t. the state AFTER the block at hand.
-  int w = 0;
+  // ---- reverse walk.  (gk, gv) = gradient w.r.t. the state AFTER the block at hand.  Step 3 of a block needs nothing
+  // of the walk, only the states: on the MFMA kernels the attention of a window of blocks runs in one launch ahead of
+  // the walk through it and leaves its share of the gradient w.r.t. each block's starting state in a slot of its own,
+  // to which the step then adds.
   const size_t gbytes = chains * cfg->M * d * sizeof(float);
-  for (int kv = 0; kv < 2; ++kv) {
-    const float* src = kv ? d_final_v : d_final_k;
-    if (src) HIP_TRY(hipMemcpyAsync(ws + l.g[w][kv], src, gbytes, hipMemcpyDeviceToDevice, s), "copying the final gradient");
-    else HIP_TRY(launch_zero_fill(ws + l.g[w][kv], gbytes, s), "clearing the final gradient");
+  const float* gk = d_final_k;
+  const float* gv = d_final_v;
+  if (!gk) { gk = (const float*)(ws + l.g[0][0]); HIP_TRY(launch_zero_fill(ws + l.g[0][0], gbytes, s), "clearing the final gradient"); }
+  if (!gv) { gv = (const float*)(ws + l.g[0][1]); HIP_TRY(launch_zero_fill(ws + l.g[0][1], gbytes, s), "clearing the final gradient"); }
+  const bool batched = l.window > 0 && bwd_attn_on_mfma(cfg, seq, B);
+  const int64_t G = batched ? l.window : n;
+  int w = 1;
+  for (int64_t w1 = n; w1 > 0;) {
+    const int64_t w0 = std::max<int64_t>(0, w1 - G);
+    if (batched) {
+      const lococo_seg& first = plan[(size_t)w0];
+      int64_t fills = 0;                       // fill blocks at the head of the window: their states are prefixes of the last one's
+      while (w0 + fills < w1 - 1 && plan[(size_t)(w0 + fills)].branch == 0) ++fills;
+      lococo_cache at = fc;
+      at.k[0] = ws + l.states_k + (size_t)(w0 + fills) * l.state;
+      at.v[0] = ws + l.states_v + (size_t)(w0 + fills) * l.state;
+      at.cur = 0;
+      at.len = first.len_before;
+      lococo_qkvo blk = *seq;
+      blk.o = blk.q;
+      BwdAttnArgs t{};
+      t.a = attn_args_one_block(make_args(cfg, &blk, first.start, B, &at, conv_w, conv_b, true));
+      t.a.L = std::min<int64_t>(L - first.start, (w1 - w0) * (int64_t)B);
+      t.a.n_seg = (int32_t)(w1 - w0);
+      t.a.n_fill = (int32_t)fills;
+      t.a.hist_k = ws + l.states_k + (size_t)(w0 + fills + 1) * l.state;
+      t.a.hist_v = ws + l.states_v + (size_t)(w0 + fills + 1) * l.state;
+      t.a.hist_stride = (int64_t)(l.state / es);
+      t.a.hist_ring = (int32_t)(w1 - w0);      // (slots in order, never wrapped)
+      t.d_o = d_o + first.start * (int64_t)d;
+      t.d_q = d_q + first.start * (int64_t)d;
+      t.d_k = d_k + first.start * (int64_t)d;
+      t.d_v = d_v + first.start * (int64_t)d;
+      t.d_ck = (float*)(ws + l.d_ck);
+      t.d_cv = (float*)(ws + l.d_cv);
+      if ((st = enqueue_bwd_attn(cfg, t, L, ws + l.hl, ws + l.stats, s))) return st;
+    }
+    for (int64_t i = w1 - 1; i >= w0; --i) {
+      const lococo_seg& sg = plan[(size_t)i];
+      lococo_cache before = fc;
+      before.k[0] = ws + l.states_k + (size_t)i * l.state;
+      before.v[0] = ws + l.states_v + (size_t)i * l.state;
+      before.cur = 0;
+      before.len = sg.len_before;
+      lococo_qkvo blk = *seq;
+      blk.o = blk.q;
+      BwdArgs g{};
+      g.st = make_args(cfg, &blk, sg.start, sg.len, &before, conv_w, conv_b, true);
+      g.d_o = d_o + sg.start * (int64_t)d;
+      g.d_new_k = gk;
+      g.d_new_v = gv;
+      g.d_q = d_q + sg.start * (int64_t)d;
+      g.d_k = d_k + sg.start * (int64_t)d;
+      g.d_v = d_v + sg.start * (int64_t)d;
+      g.q_chain = g.kv_chain = L * (int64_t)d;
+      if (batched) {
+        g.d_cache_k = (float*)(ws + l.d_ck + (size_t)(i - w0) * l.slot);
+        g.d_cache_v = (float*)(ws + l.d_cv + (size_t)(i - w0) * l.slot);
+        g.attn_done = 1;
+      } else {
+        g.d_cache_k = i == 0 ? d_cache0_k : (float*)(ws + l.g[w][0]);
+        g.d_cache_v = i == 0 ? d_cache0_v : (float*)(ws + l.g[w][1]);
+        w ^= 1;
+      }
+      g.d_conv_w = d_conv_w;
+      g.d_conv_b = d_conv_b;
+      if ((st = enqueue_step_backward(cfg, g, sg.branch == 1, bwd_layout(cfg, sg.len, sg.len_before), ws + l.step_ws, s))) return st;
+      gk = g.d_cache_k;
+      gv = g.d_cache_v;
+    }
+    if (batched) {                             // the slots are written again by the next window
+      float* ok = w0 == 0 ? d_cache0_k : (float*)(ws + l.g[w][0]);
+      float* ov = w0 == 0 ? d_cache0_v : (float*)(ws + l.g[w][1]);
+      HIP_TRY(launch_copy_pair(ok, gk, ov, gv, gbytes, s), "handing on the gradient of a state");
+      gk = ok;
+      gv = ov;
+      w ^= 1;
+    }
+    w1 = w0;
   }
-  for (int64_t i = n - 1; i >= 0; --i) {
-    const lococo_seg& sg = plan[(size_t)i];
-    const size_t Bn = (size_t)sg.len;
-    lococo_qkvo blk = *seq;
-    for (lococo_tensor* t : {&blk.q, &blk.k, &blk.v}) t->p = (char*)t->p + (size_t)(sg.start * t->stride_t) * es;
-    lococo_cache before = fc;
-    before.k[0] = ws + l.states_k + (size_t)i * l.state;
-    before.v[0] = ws + l.states_v + (size_t)i * l.state;
-    before.k[1] = ws + l.cache[1];
-    before.v[1] = ws + l.cache[3];
-    before.cur = 0;
-    before.len = sg.len_before;
-    // the block's slice of d_o as a contiguous array; its slices of d_q, d_k, d_v go back the same way
-    const size_t row = Bn * d * sizeof(float), pitch = (size_t)L * d * sizeof(float);
-    HIP_TRY(hipMemcpy2DAsync(ws + l.d_o, row, (const char*)d_o + (size_t)sg.start * d * sizeof(float), pitch, row,
-                             (size_t)cfg->batch * cfg->n_q_heads, hipMemcpyDeviceToDevice, s), "slicing d_o");
-    if ((st = lococo_segment_step_backward(cfg, &blk, sg.len, conv_w, conv_b, &before, (const float*)(ws + l.d_o),
-                                           (const float*)(ws + l.g[w][0]), (const float*)(ws + l.g[w][1]),
-                                           (float*)(ws + l.d_q), (float*)(ws + l.d_k), (float*)(ws + l.d_v),
-                                           (float*)(ws + l.g[w ^ 1][0]), (float*)(ws + l.g[w ^ 1][1]), d_conv_w, d_conv_b,
-                                           ws + l.step_ws, l.total - l.step_ws, s)))
-      return st;
-    HIP_TRY(hipMemcpy2DAsync((char*)d_q + (size_t)sg.start * d * sizeof(float), pitch, ws + l.d_q, row, row,
-                             (size_t)cfg->batch * cfg->n_q_heads, hipMemcpyDeviceToDevice, s), "placing d_q");
-    HIP_TRY(hipMemcpy2DAsync((char*)d_k + (size_t)sg.start * d * sizeof(float), pitch, ws + l.d_k, row, row, chains,
-                             hipMemcpyDeviceToDevice, s), "placing d_k");
-    HIP_TRY(hipMemcpy2DAsync((char*)d_v + (size_t)sg.start * d * sizeof(float), pitch, ws + l.d_v, row, row, chains,
-                             hipMemcpyDeviceToDevice, s), "placing d_v");
-    w ^= 1;
-  }
-  HIP_TRY(hipMemcpyAsync(d_cache0_k, ws + l.g[w][0], gbytes, hipMemcpyDeviceToDevice, s), "returning the gradient of the first state");
-  HIP_TRY(hipMemcpyAsync(d_cache0_v, ws + l.g[w][1], gbytes, hipMemcpyDeviceToDevice, s), "returning the gradient of the first state");
   return LOCOCO_OK;
 }
 

@@ -67,10 +67,10 @@ __device__ __forceinline__ const T* cat_row(const void* cache, const View& blk, 
   return (const T*)blk.p + b * blk.sb + hkv * blk.sh + (int64_t)(j - m) * blk.st;
 }
 // where the gradient of row j of [cache ; block] lives
-__device__ __forceinline__ float* grad_row(float* d_cache, float* d_blk, int M, int d, int m, int Bn, int ch,
+__device__ __forceinline__ float* grad_row(float* d_cache, float* d_blk, int M, int d, int m, int64_t kv_chain, int ch,
                                            int j) {
   if (j < m) return d_cache + ((int64_t)ch * M + j) * d;
-  return d_blk + ((int64_t)ch * Bn + (j - m)) * d;
+  return d_blk + ch * kv_chain + (int64_t)(j - m) * d;
 }
 __device__ __forceinline__ bool slot_protected(const StepArgs& a, int ch, int i) {
   return a.protect && i < a.m && ((a.protect[(int64_t)ch * a.protect_stride + (i >> 5)] >> (i & 31)) & 1u);
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_scores_k(BwdArgs g) {
   const int hq = blockIdx.z % a.Hq, b = blockIdx.z / a.Hq, hkv = hq / a.group;
   if (j0 > a.m + r0 + kAT - 1) return;             // the whole tile lies after its queries
   const int tr = threadIdx.x / 16, tj = threadIdx.x % 16;
-  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn;
+  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, q0 = ((int64_t)b * a.Hq + hq) * g.q_chain;
   float accs[4][4], accp[4][4];
 #pragma unroll
   for (int ii = 0; ii < 4; ++ii)
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_scores_k(BwdArgs g) {
       if (cc < d) {
         if (r0 + x < a.Bn) {
           qv = to_f(((const T*)a.q.p + b * a.q.sb + hq * a.q.sh + (int64_t)(r0 + x) * a.q.st)[cc]);
-          ov = g.d_o[(row0 + r0 + x) * d + cc];
+          ov = g.d_o[q0 + (int64_t)(r0 + x) * d + cc];
         }
         if (j0 + x < Tn) {
           kv = to_f(cat_row<T>(a.cache_k, a.k, a.M, d, a.m, b, hkv, a.Hkv, j0 + x)[cc]);
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_dq_k(BwdArgs g) {
   const int c0 = blockIdx.x * kAT, r0 = blockIdx.y * kAT;
   const int hq = blockIdx.z % a.Hq, b = blockIdx.z / a.Hq, hkv = hq / a.group;
   const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;
-  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn;
+  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, q0 = ((int64_t)b * a.Hq + hq) * g.q_chain;
   const int jend = min(Tn, a.m + r0 + kAT);        // nothing to add after the tile's last query
   float acc[4][4];
 #pragma unroll
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_dq_k(BwdArgs g) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = c0 + tc * 4 + q;
-      if (c < d) g.d_q[(row0 + r) * d + c] = acc[ii][q];
+      if (c < d) g.d_q[q0 + (int64_t)r * d + c] = acc[ii][q];
     }
   }
 }
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_cols_k(BwdArgs g) {
     for (int q = 0; q < 4; ++q) acck[jj][q] = accv[jj][q] = 0.f;
   for (int hh = 0; hh < a.group; ++hh) {
     const int hq = hkv * a.group + hh;
-    const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn;
+    const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, q0 = ((int64_t)b * a.Hq + hq) * g.q_chain;
     for (int rc = rbeg; rc < a.Bn; rc += kAK) {
       __syncthreads();
       for (int e = threadIdx.x; e < kAK * kAT; e += kThreads) {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_cols_k(BwdArgs g) {
         Ps[rr][x] = in ? g.ws_p[(row0 + r) * Tn + j0 + x] : 0.f;
         const bool inc = r < a.Bn && c0 + x < d;
         Qs[rr][x] = inc ? to_f(((const T*)a.q.p + b * a.q.sb + hq * a.q.sh + (int64_t)r * a.q.st)[c0 + x]) : 0.f;
-        Os[rr][x] = inc ? g.d_o[(row0 + r) * d + c0 + x] : 0.f;
+        Os[rr][x] = inc ? g.d_o[q0 + (int64_t)r * d + c0 + x] : 0.f;
       }
       __syncthreads();
 #pragma unroll
@@ -280,8 +280,8 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_cols_k(BwdArgs g) {
   for (int jj = 0; jj < 4; ++jj) {
     const int j = j0 + tj * 4 + jj;
     if (j >= Tn) continue;
-    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, a.Bn, ch, j);
-    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, a.Bn, ch, j);
+    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, g.kv_chain, ch, j);
+    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, g.kv_chain, ch, j);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = c0 + tc * 4 + q;
@@ -312,8 +312,8 @@ __global__ __launch_bounds__(kThreads) void bwd_fill_k(BwdArgs g) {
        e += (int64_t)gridDim.x * kThreads) {
     const int j = (int)(e / a.d), c = (int)(e % a.d);
     const int64_t at = ((int64_t)ch * a.M + j) * a.d + c;
-    grad_row(g.d_cache_k, g.d_k, a.M, a.d, a.m, a.Bn, ch, j)[c] += g.d_new_k[at];
-    grad_row(g.d_cache_v, g.d_v, a.M, a.d, a.m, a.Bn, ch, j)[c] += g.d_new_v[at];
+    grad_row(g.d_cache_k, g.d_k, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_k[at];
+    grad_row(g.d_cache_v, g.d_v, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_v[at];
   }
 }
 
@@ -457,8 +457,8 @@ __global__ __launch_bounds__(kThreads) void bwd_mix_cols_k(BwdArgs g) {
   for (int jj = 0; jj < 4; ++jj) {
     const int j = j0 + tj * 4 + jj;
     if (j >= Tn) continue;
-    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, a.Bn, ch, j);
-    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, a.Bn, ch, j);
+    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, g.kv_chain, ch, j);
+    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, g.kv_chain, ch, j);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = c0 + tc * 4 + q;
@@ -597,8 +597,8 @@ __global__ __launch_bounds__(kThreads) void bwd_conv_x_k(BwdArgs g) {
   for (int jj = 0; jj < 4; ++jj) {
     const int j = j0 + tj * 4 + jj;
     if (j >= Tn) continue;
-    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, a.Bn, ch, j);
-    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, a.Bn, ch, j);
+    float* dk = grad_row(g.d_cache_k, g.d_k, a.M, d, a.m, g.kv_chain, ch, j);
+    float* dv = grad_row(g.d_cache_v, g.d_v, a.M, d, a.m, g.kv_chain, ch, j);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = c0 + tc * 4 + q;
@@ -616,19 +616,21 @@ hipError_t run(const BwdArgs& g, bool compress, hipStream_t s) {
   const bool conv_mfma = g.ws_mfma != nullptr;
   const bool mfma = g.gemms_mfma && bwd_gemms_mfma_fit(g);
   hipError_t e = hipSuccess;
-  if (mfma) e = launch_bwd_attn_scores_mfma(g, s);
-  else
-    hipLaunchKernelGGL(bwd_attn_scores_k<T>, dim3((Tn + kAT - 1) / kAT, (a.Bn + kAT - 1) / kAT, a.batch * a.Hq),
-                       dim3(kThreads), 0, s, g);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bwd_attn_rows_k, dim3(a.Bn, a.Hq, a.batch), dim3(kThreads), 0, s, g);
-  if (mfma) {
-    if ((e = launch_bwd_attn_grads_mfma(g, s)) != hipSuccess) return e;
-  } else {
-    hipLaunchKernelGGL(bwd_attn_dq_k<T>, dim3((a.d + kAT - 1) / kAT, (a.Bn + kAT - 1) / kAT, a.batch * a.Hq),
-                       dim3(kThreads), 0, s, g);
-    hipLaunchKernelGGL(bwd_attn_cols_k<T>, dim3((a.d + kAT - 1) / kAT, (Tn + kAT - 1) / kAT, chains),
-                       dim3(kThreads), 0, s, g);
+  if (!g.attn_done) {
+    if (mfma) e = launch_bwd_attn_scores_mfma(g, s);
+    else
+      hipLaunchKernelGGL(bwd_attn_scores_k<T>, dim3((Tn + kAT - 1) / kAT, (a.Bn + kAT - 1) / kAT, a.batch * a.Hq),
+                         dim3(kThreads), 0, s, g);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(bwd_attn_rows_k, dim3(a.Bn, a.Hq, a.batch), dim3(kThreads), 0, s, g);
+    if (mfma) {
+      if ((e = launch_bwd_attn_grads_mfma(g, s)) != hipSuccess) return e;
+    } else {
+      hipLaunchKernelGGL(bwd_attn_dq_k<T>, dim3((a.d + kAT - 1) / kAT, (a.Bn + kAT - 1) / kAT, a.batch * a.Hq),
+                         dim3(kThreads), 0, s, g);
+      hipLaunchKernelGGL(bwd_attn_cols_k<T>, dim3((a.d + kAT - 1) / kAT, (Tn + kAT - 1) / kAT, chains),
+                         dim3(kThreads), 0, s, g);
+    }
   }
   if (a.m < a.M) hipLaunchKernelGGL(bwd_zero_dead_rows_k, dim3(64, chains), dim3(kThreads), 0, s, g);
   if (!compress) {

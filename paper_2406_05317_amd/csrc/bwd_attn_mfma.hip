@@ -1,0 +1,406 @@
+// Backward of the attention of every block of a window (Alg. 2 step 3), two kernels, bf16 MFMA, head_dim 128.
+//
+// Nothing of size queries x keys goes through memory: both kernels recompute the score tiles.
+//   bwd_attn_q_k    a workgroup per 128 query rows: one walk over the keys for the row statistics (softmax reference,
+//                   1 / row sum) and D = sum_j P dP, a second one for dq = dS Yk.  Leaves dO as two bf16 halves and the
+//                   statistics for
+//   bwd_attn_kv_k   a workgroup per 128 keys of [cache ; block]: dYk = dS^T q and dYv = P^T dO over the rows of all
+//                   heads of the group.
+// The fp32 operands (dO, P, dS) enter the matrix products as two bf16 halves (16 bits kept): S 1, dP 2, dq 2, dYk 2,
+// dYv 3 products; with the recomputation 15 products per (query, key) pair of 128 columns.
+// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.0 ms for the whole sequence (1.7 + 3.2) against 20.0 ms as
+// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.28 against
+// 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
+// between the products (matrix pipe 45 % busy in the first kernel, 27 % in the second).
+// D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.
+#include "lococo_internal.h"
+#include "mfma_util.h"
+
+namespace lococo {
+namespace {
+
+constexpr int kD = 128;
+constexpr int kTile = 64 * kD * 2;            // bytes of a tile of 64 rows
+
+struct Seg {
+  const uint16_t* ck; const uint16_t* cv;     // the chain's cache rows
+  int64_t start;                              // first token of the block (in the window)
+  int m, Bn;
+};
+__device__ __forceinline__ Seg segment(const AttnArgs& a, int n, int chain) {
+  Seg s;
+  s.start = (int64_t)n * a.B;
+  s.Bn = (int)(a.L - s.start < a.B ? a.L - s.start : a.B);
+  const bool base = n <= a.n_fill;
+  s.m = base ? a.len0 + n * a.B : a.M;
+  const int64_t slot = base ? 0 : (int64_t)((a.hist_first + n - a.n_fill - 1) % a.hist_ring) * a.hist_stride;
+  s.ck = (const uint16_t*)(base ? a.cache_k : a.hist_k) + slot + (int64_t)chain * a.M * kD;
+  s.cv = (const uint16_t*)(base ? a.cache_v : a.hist_v) + slot + (int64_t)chain * a.M * kD;
+  return s;
+}
+__device__ __forceinline__ u32x4 rows_rsrc(const void* p, int n, int64_t st_bytes) {
+  return make_rsrc(p, n > 0 ? (uint32_t)((n - 1) * st_bytes + 256) : 0u);
+}
+
+// requests rows row0 .. row0 + 63 of 256 bytes (st bytes apart in memory, `off` bytes into each) into the tile at lds;
+// W waves share the 16 instructions
+template <int W>
+__device__ __forceinline__ void request_tile(const u32x4& rsrc, uint32_t st, uint32_t row0, uint32_t lds, int w, int l) {
+#pragma unroll
+  for (int i = 0; i < 16 / W; ++i) {
+    const int r4 = w * (16 / W) + i, r = r4 * 4 + (l >> 4);
+    load_to_lds(rsrc, lds + r4 * 1024, (row0 + r) * st + (((l & 15) ^ swz(r)) << 4));
+  }
+}
+
+__global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const AttnArgs& a = g.a;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  const int qt = item % a.qtiles, hq = (item / a.qtiles) % a.Hq, b = (item / a.qtiles / a.Hq) % a.batch;
+  const int n = item / a.qtiles / a.Hq / a.batch, hkv = hq / a.group, chain = b * a.Hkv + hkv, q0 = qt * 128;
+  const Seg s = segment(a, n, chain);
+  if (q0 >= s.Bn) return;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
+  const int wq0 = q0 + 32 * w, qrow = wq0 + l31;
+  const u32x4 rck = rows_rsrc(s.ck, s.m, 256), rcv = rows_rsrc(s.cv, s.m, 256);
+  const u32x4 rbk = rows_rsrc((const uint16_t*)a.k.p + b * a.k.sb + hkv * a.k.sh + s.start * a.k.st, s.Bn, a.k.st * 2);
+  const u32x4 rbv = rows_rsrc((const uint16_t*)a.v.p + b * a.v.sb + hkv * a.v.sh + s.start * a.v.st, s.Bn, a.v.st * 2);
+  const int NTc = (s.m + 63) / 64, NT = NTc + (min(s.Bn, q0 + 128) + 63) / 64;
+  // tile t of the walk into buffer pair t % 2 (the walk is made twice: tile t % NT)
+  auto request = [&](int t) {
+    if (t >= 2 * NT) return;
+    const uint32_t lds = lds0 + (t & 1) * 2 * kTile;
+    const int tt = t < NT ? t : t - NT;
+    if (tt < NTc) {
+      request_tile<4>(rck, 256, tt * 64, lds, w, l);
+      request_tile<4>(rcv, 256, tt * 64, lds + kTile, w, l);
+    } else {
+      request_tile<4>(rbk, (uint32_t)(a.k.st * 2), (tt - NTc) * 64, lds, w, l);
+      request_tile<4>(rbv, (uint32_t)(a.v.st * 2), (tt - NTc) * 64, lds + kTile, w, l);
+    }
+  };
+  request(0);
+
+  // ---- this lane's query and output-gradient row as operand fragments; dO also goes to memory as two halves
+  const int row = min(qrow, s.Bn - 1);
+  const bool live = qrow < s.Bn;
+  bf16x8 fq[8], foh[8], fol[8];
+  {
+    const uint16_t* qp = (const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + (s.start + row) * a.q.st + lh * 8;
+    const float* op = g.d_o + b * g.q_sb + hq * g.q_sh + (s.start + row) * kD + lh * 8;
+    uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start + row) * (2 * kD) + lh * 8;
+    f32x4 o0[8], o1[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      fq[ks] = *(const bf16x8*)(qp + ks * 16);
+      o0[ks] = *(const f32x4*)(op + ks * 16);
+      o1[ks] = *(const f32x4*)(op + ks * 16 + 4);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const float x[8] = {o0[ks][0], o0[ks][1], o0[ks][2], o0[ks][3], o1[ks][0], o1[ks][1], o1[ks][2], o1[ks][3]};
+      split8(x, foh[ks], fol[ks]);
+      if (live) {
+        *(bf16x8*)(hl + ks * 16) = foh[ks];
+        *(bf16x8*)(hl + kD + ks * 16) = fol[ks];
+      }
+    }
+  }
+  TileAddr ad;
+  tile_addr(l, ad);
+  const float c = a.scale * kLog2e, lazy_raw = 8.0f / a.scale;
+  wait_loads<0>();
+  __syncthreads();
+
+  // S^T and dP^T (32 keys x this wave's queries) of half kt of the tile at K / K + kTile
+  auto products = [&](const unsigned char* K, int kt, f32x16& sc, f32x16& dp) {
+    const unsigned char* k0 = K + kt * 32 * 256;
+    sc = zero16();
+    dp = zero16();
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const bf16x8 fk = *(const bf16x8*)(k0 + ad.row[ks]), fv = *(const bf16x8*)(k0 + kTile + ad.row[ks]);
+      sc = mfma32(fk, fq[ks], sc);
+      dp = mfma32(fv, foh[ks], dp);
+      dp = mfma32(fv, fol[ks], dp);
+    }
+  };
+  // keys this lane's query does not see: score -inf
+  auto mask = [&](int t, int kt, f32x16& sc) {
+    const bool blk = t >= NTc;
+    const int row0 = (blk ? t - NTc : t) * 64 + kt * 32;
+    if (blk ? row0 + 31 > wq0 : row0 + 32 > s.m) {
+      const int lim = blk ? qrow : s.m - 1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (row0 + (i >> 2) * 8 + lh * 4 + (i & 3) > lim) sc[i] = -INFINITY;
+    }
+  };
+  auto visible = [&](int t, int kt) {       // uniform: some query of this wave sees a key of this half tile
+    if (t < NTc) return t * 64 + kt * 32 < s.m;
+    return (t - NTc) * 64 + kt * 32 < wq0 + 32;
+  };
+
+  // ---- first walk: reference m_run (lags the maximum by at most 8), row sum and sum of p dP
+  float m_run = -INFINITY, l_run = 0.f, d_run = 0.f;
+  for (int t = 0; t < NT; ++t) {
+    request(t + 1);
+    const unsigned char* K = smem + (t & 1) * 2 * kTile;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      if (!visible(t, kt)) continue;
+      f32x16 sc, dp;
+      products(K, kt, sc, dp);
+      mask(t, kt, sc);
+      float mx = sc[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sc[i]);
+      mx = max_halves(mx);
+      if (mx > m_run + lazy_raw) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c);
+        l_run *= alpha;
+        d_run *= alpha;
+        m_run = mx;
+      }
+      const float mc = m_run * c;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mc));
+        l_run += p;
+        d_run = fmaf(p, dp[i], d_run);
+      }
+    }
+    wait_loads<0>();
+    __syncthreads();
+  }
+  const float inv = 1.0f / sum_halves(l_run), D = sum_halves(d_run) * inv, mc = m_run * c;
+  if (live && lh == 0) {
+    float* st = g.stats + ((int64_t)b * a.Hq + hq) * a.L + s.start + qrow;
+    const int64_t plane = (int64_t)a.batch * a.Hq * a.L;
+    st[0] = mc;
+    st[plane] = inv;
+    st[2 * plane] = D;
+  }
+  // ---- second walk: dq^T += Yk^T dS^T
+  f32x16 acc[4];
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) acc[ct] = zero16();
+  const float ps = inv * a.scale;
+  for (int t = 0; t < NT; ++t) {
+    request(NT + t + 1);
+    const unsigned char* K = smem + ((NT + t) & 1) * 2 * kTile;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      if (!visible(t, kt)) continue;
+      f32x16 sc, dp;
+      products(K, kt, sc, dp);
+      mask(t, kt, sc);
+      float ds[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mc)) * ps * (dp[i] - D);
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        bf16x8 hi, lo;
+        split8(ds + 8 * s2, hi, lo);
+        const unsigned char* k0 = K + (kt * 32 + s2 * 16) * 256;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+          const bf16x8 fk = frag_tr(k0 + ad.tr[ct][0], k0 + ad.tr[ct][1]);
+          acc[ct] = mfma32(fk, hi, acc[ct]);
+          acc[ct] = mfma32(fk, lo, acc[ct]);
+        }
+      }
+    }
+    wait_loads<0>();
+    __syncthreads();
+  }
+  if (live) {
+    float* out = g.d_q + b * g.q_sb + hq * g.q_sh + (s.start + qrow) * kD + lh * 4;
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi)
+        *(f32x4*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
+  }
+}
+
+// Eight waves, two per group of 32 keys: waves 0..3 accumulate dYv (S, P^T dO), waves 4..7 dYk (S, dP, dS^T q).  One wave
+// with both would hold 384 registers of accumulators and key / value fragments; split, a wave needs under 256, each SIMD
+// has one of either kind to interleave, and the price is S computed twice (72 products instead of 64 per 32 x 32 tile).
+__global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
+  extern __shared__ __align__(16) unsigned char smem[];       // [2][q | dO hi | dO lo] tiles of 64 rows, [2][3][64] statistics
+  const AttnArgs& a = g.a;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
+  float* st_lds = (float*)(smem + 6 * kTile);
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  const int ktiles = (a.M + a.B + 127) / 128;
+  const int chain = (item / ktiles) % (a.batch * a.Hkv), n = item / ktiles / (a.batch * a.Hkv);
+  const int b = chain / a.Hkv, hkv = chain % a.Hkv, j0 = (item % ktiles) * 128;
+  const Seg s = segment(a, n, chain);
+  const int Tn = s.m + s.Bn;
+  if (j0 >= Tn) return;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
+  const bool for_v = w < 4;
+  const int wj = j0 + 32 * (w & 3), j = wj + l31;             // this lane's position in [cache ; block]
+  const int first = j0 >= s.m ? (j0 - s.m) / 64 : 0;          // tiles of rows before it see none of the keys
+  const int rtiles = (s.Bn + 63) / 64 - first, N = a.group * rtiles;
+  const int64_t plane = (int64_t)a.batch * a.Hq * a.L;
+
+  float stat = 0.f;
+  auto request = [&](int it) {
+    if (it >= N) return;
+    const int hq = hkv * a.group + it / rtiles, r0 = (first + it % rtiles) * 64;
+    const uint32_t lds = lds0 + (it & 1) * 3 * kTile;
+    const u32x4 rq = rows_rsrc((const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + s.start * a.q.st, s.Bn, a.q.st * 2);
+    const uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start) * (2 * kD);
+    const u32x4 ro = make_rsrc(hl, (uint32_t)s.Bn * 512u);
+    request_tile<8>(rq, (uint32_t)(a.q.st * 2), r0, lds, w, l);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4);
+        load_to_lds(ro, lds + (1 + h) * kTile + r4 * 1024, (r0 + r) * 512 + h * 256 + (((l & 15) ^ swz(r)) << 4));
+      }
+    if (tid < 192) {
+      const int r = r0 + (tid & 63);
+      stat = r < s.Bn ? g.stats[(tid >> 6) * plane + ((int64_t)b * a.Hq + hq) * a.L + s.start + r] : 0.f;
+    }
+  };
+  auto publish_stats = [&](int it) {
+    if (it < N && tid < 192) st_lds[(it & 1) * 192 + tid] = stat;
+  };
+  request(0);
+  // key (and value) fragments of this lane's position; positions past the end are computed from the last one and dropped
+  bf16x8 fk[8], fv[8];
+  {
+    const int jc = min(j, Tn - 1);
+    const uint16_t* kp = (jc < s.m ? s.ck + (int64_t)jc * kD
+                                   : (const uint16_t*)a.k.p + b * a.k.sb + hkv * a.k.sh + (s.start + jc - s.m) * a.k.st) + lh * 8;
+    const uint16_t* vp = (jc < s.m ? s.cv + (int64_t)jc * kD
+                                   : (const uint16_t*)a.v.p + b * a.v.sb + hkv * a.v.sh + (s.start + jc - s.m) * a.v.st) + lh * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) fk[ks] = *(const bf16x8*)(kp + ks * 16);
+    if (!for_v)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) fv[ks] = *(const bf16x8*)(vp + ks * 16);
+  }
+  TileAddr ad;
+  tile_addr(l, ad);
+  const float c = a.scale * kLog2e;
+  f32x16 acc[4];
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) acc[ct] = zero16();
+  wait_loads<0>();
+  publish_stats(0);
+  __syncthreads();
+
+  for (int it = 0; it < N; ++it) {
+    request(it + 1);
+    const int r0 = (first + it % rtiles) * 64;
+    const unsigned char* Q = smem + (it & 1) * 3 * kTile;
+    const float* st = st_lds + (it & 1) * 192 + lh * 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int rb = r0 + h * 32;
+      if (rb >= s.Bn || (wj >= s.m && rb + 31 < wj - s.m)) continue;      // no row of this half sees these keys
+      const unsigned char* q0 = Q + h * 32 * 256;
+      f32x16 sc = zero16();
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) sc = mfma32(*(const bf16x8*)(q0 + ad.row[ks]), fk[ks], sc);
+      f32x4 mcs[4], inv[4];
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi) {
+        mcs[gi] = *(const f32x4*)(st + h * 32 + gi * 8);
+        inv[gi] = *(const f32x4*)(st + 64 + h * 32 + gi * 8);
+      }
+      float p[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mcs[i >> 2][i & 3])) * inv[i >> 2][i & 3];
+      if (rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int r = rb + (i >> 2) * 8 + lh * 4 + (i & 3);
+          if (r >= s.Bn || j - s.m > r) p[i] = 0.f;
+        }
+      }
+      if (for_v) {
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          bf16x8 hi, lo;
+          split8(p + 8 * s2, hi, lo);
+          const unsigned char* o0 = q0 + kTile + s2 * 16 * 256;
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) {
+            const bf16x8 oh = frag_tr(o0 + ad.tr[ct][0], o0 + ad.tr[ct][1]);
+            const bf16x8 ol = frag_tr(o0 + kTile + ad.tr[ct][0], o0 + kTile + ad.tr[ct][1]);
+            acc[ct] = mfma32(oh, hi, acc[ct]);
+            acc[ct] = mfma32(oh, lo, acc[ct]);
+            acc[ct] = mfma32(ol, hi, acc[ct]);
+          }
+        }
+      } else {
+        f32x16 dp = zero16();
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          dp = mfma32(*(const bf16x8*)(q0 + kTile + ad.row[ks]), fv[ks], dp);
+          dp = mfma32(*(const bf16x8*)(q0 + 2 * kTile + ad.row[ks]), fv[ks], dp);
+        }
+#pragma unroll
+        for (int gi = 0; gi < 4; ++gi) {
+          const f32x4 dd = *(const f32x4*)(st + 128 + h * 32 + gi * 8);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) p[gi * 4 + e] *= (dp[gi * 4 + e] - dd[e]) * a.scale;
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          bf16x8 hi, lo;
+          split8(p + 8 * s2, hi, lo);
+          const unsigned char* t0 = q0 + s2 * 16 * 256;
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) {
+            const bf16x8 qf = frag_tr(t0 + ad.tr[ct][0], t0 + ad.tr[ct][1]);
+            acc[ct] = mfma32(qf, hi, acc[ct]);
+            acc[ct] = mfma32(qf, lo, acc[ct]);
+          }
+        }
+      }
+    }
+    wait_loads<0>();
+    publish_stats(it + 1);
+    __syncthreads();
+  }
+  if (j < Tn) {
+    float* dc = (for_v ? g.d_cv : g.d_ck) + ((int64_t)n * a.batch * a.Hkv + chain) * a.M * kD;
+    float* db = (for_v ? g.d_v : g.d_k) + b * g.k_sb + hkv * g.k_sh + s.start * kD;
+    float* out = (j < s.m ? dc + (int64_t)j * kD : db + (int64_t)(j - s.m) * kD) + lh * 4;
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi)
+        *(f32x4*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
+  }
+}
+
+}  // namespace
+
+hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
+  AttnArgs& a = g.a;
+  a.qtiles = (a.B + 127) / 128;
+  constexpr int lds_q = 4 * kTile, lds_kv = 6 * kTile + 2 * 3 * 64 * 4;
+  static bool attr_set = false;   // benign race: setting it twice is harmless
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)bwd_attn_kv_k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(bwd_attn_q_k, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
+  const int ktiles = (a.M + a.B + 127) / 128;
+  hipLaunchKernelGGL(bwd_attn_kv_k, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(512), lds_kv, s, g);
+  return hipGetLastError();
+}
+
+}  // namespace lococo

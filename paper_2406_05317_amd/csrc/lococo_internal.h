@@ -111,7 +111,8 @@ struct AttnArgs {
 
 // Arguments of the backward pass of one block step (backward_generic.hip).  `st` describes the
 // step as for the forward (cache = state before the step).  Gradients are fp32, contiguous:
-// d_o, d_q [batch, Hq, Bn, d]; d_k, d_v [batch, Hkv, Bn, d]; d_new_k/v, d_cache_k/v [chains, M, d];
+// d_o, d_q [batch, Hq, .., d] with q_chain elements between heads, d_k, d_v [batch, Hkv, .., d] with kv_chain (the block's
+// rows of longer arrays, or the block alone); d_new_k/v, d_cache_k/v [chains, M, d];
 // d_conv_w / d_conv_b laid out like conv_w / conv_b (added to).  Workspace: ws_p, ws_ds
 // [batch, Hq, Bn, T] (attention rows and their gradient), ws_w [chains, M, T] (raw logits on entry,
 // their gradient on exit), ws_n [chains, M, T] (normalised rows), ws_dw [chains, M, T] (gradient of the
@@ -134,6 +135,8 @@ struct BwdArgs {
   float* ws_n;
   float* ws_dw;
   void* ws_mfma;           // workspace of the MFMA form of the Eq. 5 contractions (see BwdMfmaLayout), or null
+  int64_t q_chain, kv_chain;
+  int32_t attn_done;       // the contributions of the attention are in d_q, d_k, d_v, d_cache_k, d_cache_v already
   int32_t banks;           // filter banks (1 = shared by the kv heads)
   int32_t gemms_mfma;      // the plain contractions may take their MFMA form (bf16 storage; see bwd_gemms_mfma_fit)
 };
@@ -220,6 +223,25 @@ hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s);
 // the block's queries (all heads of the group) put on it; reads the statistics the attention
 // launch with the same arguments left in a.stats.
 hipError_t launch_attn_colsum_mfma(const AttnArgs& a, float* colsum, hipStream_t s);
+
+// ---- backward of that attention, every block of a window at once (bwd_attn_mfma.hip).  `a`: the blocks and states as in
+// the forward (seg_first = 0; o not used).  Gradients fp32, rows of head_dim contiguous: d_o, d_q with the batch / head
+// strides q_sb, q_sh and d_k, d_v with k_sb, k_sh (elements; first row = first token of the window); d_ck, d_cv
+// [n_seg][chains][M][d], live rows only.  All outputs are assigned.  do_hl: scratch, 2 d bf16 per query row; stats: 3 fp32.
+struct BwdAttnArgs {
+  AttnArgs a;
+  const float* d_o;
+  float* d_q;
+  int64_t q_sb, q_sh;
+  float* d_k;
+  float* d_v;
+  int64_t k_sb, k_sh;
+  float* d_ck;
+  float* d_cv;
+  uint16_t* do_hl;
+  float* stats;
+};
+hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s);
 
 // ---- attention of one new token per sequence (attn_decode.hip): bf16, head_dim 128, Bn = 1
 bool attn_decode_supports(int dtype, int d, int Bn, int M, bool colsum);

@@ -178,7 +178,6 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
         for (int t = 0; t < nt; ++t) {
           const float* wb = Ws + ((st * L.taps + t) * C4 * 4 + lk) * 16 + l15;
           const float* xb = Xs + (p0 + l15 + t0 + t) * L.sx + lk;
-#pragma unroll 4
           for (int kk = k0; kk < k1; ++kk) {
             const float fb = wb[kk * 64];
 #pragma unroll

@@ -497,7 +497,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dx_mfma_k(BwdArgs g, const ui
       const int p = p0 + wy * 64 + pb * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
       if (p >= Tn) continue;
       float* row = p < a.m ? (c0 ? g.d_cache_v : g.d_cache_k) + ((int64_t)ch * a.M + p) * kD
-                           : (c0 ? g.d_v : g.d_k) + ((int64_t)ch * a.Bn + (p - a.m)) * kD;
+                           : (c0 ? g.d_v : g.d_k) + ch * g.kv_chain + (int64_t)(p - a.m) * kD;
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb) row[wx * 64 + cb * 32 + l31] += acc[pb][cb][i];
     }
@@ -902,7 +902,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_gemm_k(OpA A, OpB B, Out out,
 // `grouped`: z is a chain and the memory row runs over the rows of all query heads of its group,
 // head-major; otherwise z is (batch entry, query head).  Every width is a multiple of 4 and every base
 // 16-byte aligned (the launcher checks), so a group of four is inside or outside as a whole.
-struct Dims { int Bn, Tn, d, M, m, Hq, Hkv, group; };
+struct Dims { int Bn, Tn, d, M, m, Hq, Hkv, group; int64_t q_chain, kv_chain; };
 __device__ __forceinline__ void head_row(const Dims& s, bool grouped, int z, int r, int& b, int& hq, int& rr) {
   if (grouped) {
     b = z / s.Hkv;
@@ -940,15 +940,15 @@ struct OpQ {               // query rows, bf16
   }
 };
 template <bool KMAJOR>
-struct OpRowsF32 {         // fp32 [batch, Hq, Bn, width] rows: d_o (width d), ws_p / ws_ds (width Tn)
+struct OpRowsF32 {         // fp32 rows of a block, heads `chain` elements apart: d_o (width d), ws_p / ws_ds (width Tn)
   static constexpr bool kMajor = KMAJOR, kBf16 = false;
   static constexpr int kParts = 2;
-  Dims s; const float* p; int width; bool grouped;
+  Dims s; const float* p; int64_t chain; int width; bool grouped;
   __device__ int load4(u32x4& raw, int z, int r, int c) const {
     const bool ok = r < (grouped ? s.group * s.Bn : s.Bn) && c < width;
     int b, hq, rr;
     head_row(s, grouped, z, ok ? r : 0, b, hq, rr);
-    raw_f32x4(raw, p + (((int64_t)b * s.Hq + hq) * s.Bn + rr) * width + (ok ? c : 0));
+    raw_f32x4(raw, p + ((int64_t)b * s.Hq + hq) * chain + (int64_t)rr * width + (ok ? c : 0));
     return ok ? 4 : 0;
   }
 };
@@ -1025,10 +1025,10 @@ struct OutRows {           // fp32 [batch, Hq, Bn, Tn] rows, scaled; tiles wholl
   __device__ bool skip(int, int i0, int j0) const { return j0 > s.m + i0 + kTile - 1; }
   __device__ void store(int z, int i, int j, float v) const { p[((int64_t)z * s.Bn + i) * s.Tn + j] = v * scale; }
 };
-struct OutPlain {          // fp32 [z, rows, width]
-  float* p; int rows, width;
+struct OutPlain {          // fp32 rows of `width`, batch entries `chain` elements apart
+  float* p; int64_t chain; int width;
   __device__ bool skip(int, int, int) const { return false; }
-  __device__ void store(int z, int i, int j, float v) const { p[((int64_t)z * rows + i) * width + j] = v; }
+  __device__ void store(int z, int i, int j, float v) const { p[z * chain + (int64_t)i * width + j] = v; }
 };
 template <bool ADD>
 struct OutGrad {           // gradient rows of [cache ; block]: i = position, j = column of K (or of [K | V])
@@ -1039,7 +1039,7 @@ struct OutGrad {           // gradient rows of [cache ; block]: i = position, j 
     const int col = which == 2 && j >= s.d ? j - s.d : j;
     float* dc = val ? d_cache_v : d_cache_k;
     float* db = val ? d_blk_v : d_blk_k;
-    float* at = (i < s.m ? dc + ((int64_t)z * s.M + i) * s.d : db + ((int64_t)z * s.Bn + (i - s.m)) * s.d) + col;
+    float* at = (i < s.m ? dc + ((int64_t)z * s.M + i) * s.d : db + z * s.kv_chain + (int64_t)(i - s.m) * s.d) + col;
     if (ADD) *at += v;
     else *at = v;
   }
@@ -1061,7 +1061,13 @@ hipError_t launch_gemm(const OpA& A, const OpB& B, const Out& out, int I, int J,
   return hipGetLastError();
 }
 
-Dims dims_of(const StepArgs& a) { return Dims{a.Bn, a.m + a.Bn, a.d, a.M, a.m, a.Hq, a.Hkv, a.group}; }
+Dims dims_of(const StepArgs& a) { return Dims{a.Bn, a.m + a.Bn, a.d, a.M, a.m, a.Hq, a.Hkv, a.group, 0, 0}; }
+Dims dims_of(const BwdArgs& g) {
+  Dims s = dims_of(g.st);
+  s.q_chain = g.q_chain;
+  s.kv_chain = g.kv_chain;
+  return s;
+}
 
 __global__ void bwd_zero_k(float* p, int64_t n) {
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
@@ -1189,37 +1195,37 @@ bool bwd_gemms_mfma_fit(const BwdArgs& g) {
 // S = scale q Yk^T into ws_p and dP = dO Yv^T into ws_ds (the row kernel turns them into P and dS)
 hipError_t launch_bwd_attn_scores_mfma(const BwdArgs& g, hipStream_t s) {
   const StepArgs& a = g.st;
-  const Dims dm = dims_of(a);
+  const Dims dm = dims_of(g);
   const int Z = a.batch * a.Hq;
   hipError_t e = launch_gemm(OpQ<false>{dm, a.q, false}, OpY<false, 0>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
                              OutRows{dm, g.ws_p, a.scale}, a.Bn, dm.Tn, a.d, Z, s);
   if (e != hipSuccess) return e;
-  return launch_gemm(OpRowsF32<false>{dm, g.d_o, a.d, false}, OpY<false, 1>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
+  return launch_gemm(OpRowsF32<false>{dm, g.d_o, dm.q_chain, a.d, false}, OpY<false, 1>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
                      OutRows{dm, g.ws_ds, 1.0f}, a.Bn, dm.Tn, a.d, Z, s);
 }
 
 // dq = dS Yk; dYk = dS^T q and dYv = P^T dO over the heads of a group (assigned: first contributions)
 hipError_t launch_bwd_attn_grads_mfma(const BwdArgs& g, hipStream_t s) {
   const StepArgs& a = g.st;
-  const Dims dm = dims_of(a);
+  const Dims dm = dims_of(g);
   const int chains = a.batch * a.Hkv;
-  hipError_t e = launch_gemm(OpRowsF32<false>{dm, g.ws_ds, dm.Tn, false},
+  hipError_t e = launch_gemm(OpRowsF32<false>{dm, g.ws_ds, (int64_t)a.Bn * dm.Tn, dm.Tn, false},
                              OpY<true, 0>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
-                             OutPlain{g.d_q, a.Bn, a.d}, a.Bn, a.d, dm.Tn, a.batch * a.Hq, s);
+                             OutPlain{g.d_q, dm.q_chain, a.d}, a.Bn, a.d, dm.Tn, a.batch * a.Hq, s);
   if (e != hipSuccess) return e;
-  e = launch_gemm(OpRowsF32<true>{dm, g.ws_ds, dm.Tn, true}, OpQ<true>{dm, a.q, true},
+  e = launch_gemm(OpRowsF32<true>{dm, g.ws_ds, (int64_t)a.Bn * dm.Tn, dm.Tn, true}, OpQ<true>{dm, a.q, true},
                   OutGrad<false>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 0}, dm.Tn, a.d, a.group * a.Bn, chains, s);
   if (e != hipSuccess) return e;
-  return launch_gemm(OpRowsF32<true>{dm, g.ws_p, dm.Tn, true}, OpRowsF32<true>{dm, g.d_o, a.d, true},
+  return launch_gemm(OpRowsF32<true>{dm, g.ws_p, (int64_t)a.Bn * dm.Tn, dm.Tn, true}, OpRowsF32<true>{dm, g.d_o, dm.q_chain, a.d, true},
                      OutGrad<false>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 1}, dm.Tn, a.d, a.group * a.Bn, chains, s);
 }
 
 // dw[i, j] = g_k[i] . Yk[j] + g_v[i] . Yv[j] into ws_dw
 hipError_t launch_bwd_mix_dw_mfma(const BwdArgs& g, hipStream_t s) {
   const StepArgs& a = g.st;
-  const Dims dm = dims_of(a);
+  const Dims dm = dims_of(g);
   return launch_gemm(OpG<false>{dm, g.d_new_k, g.d_new_v, a.protect, a.protect_stride, false},
-                     OpY<false, 2>{dm, a.cache_k, a.cache_v, a.k, a.v, false}, OutPlain{g.ws_dw, a.M, dm.Tn}, a.M,
+                     OpY<false, 2>{dm, a.cache_k, a.cache_v, a.k, a.v, false}, OutPlain{g.ws_dw, (int64_t)a.M * dm.Tn, dm.Tn}, a.M,
                      dm.Tn, 2 * a.d, a.batch * a.Hkv, s);
 }
 
@@ -1263,7 +1269,7 @@ hipError_t launch_mixnorm_mfma(const StepArgs& a, const float* logits, hipStream
 // d[Yk | Yv][j] += sum over the unprotected slots of w[i, j] [g_k | g_v][i]
 hipError_t launch_bwd_mix_cols_mfma(const BwdArgs& g, hipStream_t s) {
   const StepArgs& a = g.st;
-  const Dims dm = dims_of(a);
+  const Dims dm = dims_of(g);
   return launch_gemm(OpWn{dm, g.ws_n, a.protect, a.protect_stride},
                      OpG<true>{dm, g.d_new_k, g.d_new_v, a.protect, a.protect_stride, true},
                      OutGrad<true>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 2}, dm.Tn, 2 * a.d, a.M,

@@ -420,3 +420,46 @@ def test_sequence_backward_refusals():
         lb.lococo_sequence_backward(cfg2, q, k, v, w.B, cw.cuda(), None, cache, g["d_o"], None, None, g["dq"], g["dk"],
                                     g["dv"], g["ck"], g["cv"], g["dW"], None, ws)
     assert e.value.status == lb.LOCOCO_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("case", [
+    dict(L=1, B=1, M=32, len0=32),                                               # one row, one tile
+    dict(L=33, B=33, M=64, len0=0, n_q_heads=6, n_kv_heads=2),                   # no cache rows
+    dict(L=129, B=129, M=96, len0=1),                                            # a row past the query tile, one cache row
+    dict(L=190, B=65, M=63, len0=63, n_q_heads=4, n_kv_heads=1),                 # a cache tile one row short, ragged tail
+    dict(L=40 * 64 - 7, B=64, M=512, len0=0, batch=2, n_q_heads=64, n_kv_heads=64),   # more blocks than one window of the walk holds
+], ids=str)
+def test_scan_backward_on_the_matrix_cores_against_fp32_arithmetic(case):
+    """impl = AUTO against the fp32 vector kernels (impl = GENERIC) from the same bf16 inputs.  The operands that enter a
+    matrix product as two bf16 halves keep 16 bits, and the two paths' recomputed states may differ by a bf16 step in an
+    entry: 2e-3 per tensor, as in the scans against the oracle above."""
+    c = dict(case)
+    len0 = c.pop("len0")
+    w = inputs.Workload(**{**dict(name="bwdvs", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=2, head_dim=128, conv_width=15,
+                                  seed=9, conv_gain=2.0), **c})
+    dev = "cuda"
+    g = torch.Generator(device=dev).manual_seed(4)
+    rnd = lambda *s, dt=torch.float32, sd=1.0: torch.empty(s, dtype=dt, device=dev).normal_(0, sd, generator=g)
+    bf = torch.bfloat16
+    q = rnd(w.batch, w.n_q_heads, w.L, 128, dt=bf, sd=0.3)
+    k, v = (rnd(w.batch, w.n_kv_heads, w.L, 128, dt=bf, sd=0.3) for _ in range(2))
+    cw = rnd(w.M, 128, w.conv_width, dt=bf, sd=0.05)
+    state = (w.batch, w.n_kv_heads, w.M, 128)
+    ck, cv = rnd(*state, dt=bf, sd=0.3), rnd(*state, dt=bf, sd=0.3)
+    d_o, d_fk, d_fv = rnd(*q.shape), rnd(*state), rnd(*state)
+    out = []
+    for impl in (0, 1):
+        cfg = lb.config_for(w, impl=impl)
+        cache = lb.Cache(cfg, dev)
+        cache.load(ck, cv, len0)
+        r = [torch.full(s, float("nan"), device=dev) for s in (q.shape, k.shape, k.shape, state, state)]
+        dW = torch.zeros(cw.shape, device=dev)
+        ws = torch.empty(lb.lococo_sequence_backward_workspace_bytes(cfg, w.L, w.B), dtype=torch.uint8, device=dev)
+        lb.lococo_sequence_backward(cfg, q, k, v, w.B, cw, None, cache, d_o, d_fk, d_fv, *r, dW, None, ws)
+        torch.cuda.synchronize()
+        out.append(r + [dW])
+    for name, x, y in zip(("dq", "dk", "dv", "d_cache0_k", "d_cache0_v", "d_conv_w"), *out):
+        assert torch.isfinite(x).all(), name
+        err = float((x.double() - y.double()).norm() / y.double().norm().clamp_min(1e-30))
+        print(name, f"{err:.1e}")
+        assert err < 2e-3, (name, err)
