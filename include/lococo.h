@@ -336,9 +336,8 @@ LOCOCO_API lococo_status lococo_mix_from_logits(const lococo_config* cfg, const 
  *   workspace: lococo_backward_workspace_bytes(cfg, B, cache_before->len) bytes, 256-byte aligned.
  * Any shape; fp32 vector arithmetic, except that with bf16 storage and cfg->impl !=
  * LOCOCO_IMPL_GENERIC the contractions run on the matrix cores, every fp32 operand entering as
- * the sum of two bf16 numbers (about 16 bits kept): the plain ones when block length + live
- * slots is a multiple of 4, the three convolution ones (Eq. 5 and its two gradients) with
- * head_dim 128 and a filter width up to 31 (the workspace is larger then).  Filter gradients are summed
+ * the sum of two bf16 numbers (about 16 bits kept): all of them with head_dim 128 and a filter width up to 31, the
+ * plain ones (attention and Eq. 4) of other shapes when block length + live slots is a multiple of 4.  Filter gradients are summed
  * with floating-point atomics, so their last bits depend on the order. */
 LOCOCO_API lococo_status lococo_backward_workspace_bytes(const lococo_config* cfg, int32_t B, int32_t len, size_t* out);
 LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococo_qkvo* blk, int32_t B,
@@ -352,11 +351,12 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
 /* Backward pass of a whole scan (lococo_sequence_forward's recurrence), for training the
  * convolution heads through Alg. 2's loop: the chain rule through every block step in reverse, the
  * gradient w.r.t. a block's starting state being handed to the block before it as the gradient
- * w.r.t. that block's resulting state.  The call runs the cache recurrence once more block by
- * block (the fill branch or steps 4-5), keeping the state every block starts from in the workspace, then walks the
- * blocks backwards through lococo_segment_step_backward; gradients therefore match that entry
- * point's composed by hand (on the MFMA kernels the attention of many blocks runs in one launch ahead of the walk, a
- * window of them at a time, so the workspace does not grow faster with L than the kept states).
+ * w.r.t. that block's resulting state.  The call runs the cache recurrence once more (the fill branch or steps 4-5, in
+ * one launch under the conditions of lococo_sequence_forward: lococo_scan_status takes this call's workspace too),
+ * keeping the state every block starts from in the workspace, then walks the blocks backwards; gradients match
+ * lococo_segment_step_backward's composed by hand.  On the MFMA kernels what does not depend on the walk (attention,
+ * logits, the gradients w.r.t. the blocks' own rows and the filters) runs in one launch for a window of many blocks, so
+ * the workspace does not grow faster with L than the kept states.
  *   seq: q, k, v of the L tokens as in the forward (o is not read); cache0: the state the scan
  *   starts from (not modified; its attn_colsum is neither read nor written).
  *   Gradients are fp32 device arrays, contiguous:
@@ -366,7 +366,7 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *          [batch, n_kv_heads, M, d] (rows that were not live in cache0 are zero); all overwritten;
  *     acc  d_conv_w, d_conv_b: ADDED to, as in the step (d_conv_b may be NULL).
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
- *   states per block (storage type), one step's worth of everything else and at most 1 GiB for the window.
+ *   states per block (storage type), one step's worth of everything else and about 2 GiB at most for the window.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */
 LOCOCO_API lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg, int64_t L, int32_t B,
                                                                   size_t* out);

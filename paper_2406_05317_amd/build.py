@@ -16,7 +16,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblococo.so")
 
 SOURCES = ["api.cpp", "generic_kernels.hip", "scan_small.hip", "compress_mfma.hip", "attn_mfma.hip", "attn_decode.hip",
-           "bwd_attn_mfma.hip",
+           "bwd_attn_mfma.hip", "bwd_conv_mfma.hip",
            "backward_generic.hip", "tiled_mfma.hip", "peaks.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -35,7 +35,8 @@ EXTRA = {"compress_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form",
                                 "-mllvm", "-pragma-unroll-threshold=200000"],
          # accumulators in ordinary registers: the softmax reads the scores where the MFMA left them
          "attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-         "bwd_attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+         "bwd_attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "bwd_conv_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src: str) -> str:

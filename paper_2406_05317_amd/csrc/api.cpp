@@ -538,6 +538,42 @@ lococo_status enqueue_update(const lococo_config* c, Path path, StepArgs a, loco
   return LOCOCO_OK;
 }
 
+// `n_steps` compress steps in one launch, the slot tiles of a chain handing the new cache to each other through the ring
+// of states at out_k / out_v (see ScanArgs); *taken = false, and nothing launched, while another persistent scan holds
+// compute units.  `clear`: the counters have been used since they were zeroed (the status word is kept).
+lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_steps, int32_t B, int64_t tokens_left, void* out_k,
+                           void* out_v, int64_t out_stride, int64_t slot0, int64_t ring, void* ws, bool clear, hipStream_t s,
+                           bool* taken) {
+  const bool capturing = stream_is_capturing(s);
+  std::unique_lock<std::mutex> lk(g_scan_mu);
+  *taken = capturing || !another_scan_in_flight(s);
+  if (!*taken) return LOCOCO_OK;
+  char* sync_ws = (char*)ws + filter_ws_bytes(c);
+  if (clear)
+    HIP_TRY(launch_scan_sync_clear(sync_ws, c->batch, c->n_kv_heads, c->M, true, s), "clearing the scan counters");
+  ScanArgs sa;
+  sa.st = a;
+  sa.n_steps = (int32_t)n_steps;
+  sa.B = B;
+  sa.tokens_left = tokens_left;
+  sa.out_k = out_k;
+  sa.out_v = out_v;
+  sa.out_stride = out_stride;
+  sa.slot0 = (int32_t)slot0;
+  sa.ring = (int32_t)ring;
+  sa.sync = nullptr;
+  sa.status = nullptr;
+  sa.spin_limit = spin_limit();
+  sa.same_l2_allowed = chain_sync_through_l2() ? 1 : 0;
+  {
+    KTimer t(K_COMPRESS_MFMA, s);
+    HIP_TRY(launch_compress_scan(sa, ws, filter_banks(c), cu_count(), sync_ws, partials_of(c, ws, B), prelogits_of(c, ws, B), s),
+            "compress scan launch");
+  }
+  if (!capturing) note_scan_launched(s);
+  return LOCOCO_OK;
+}
+
 lococo_status segment_step_impl(const lococo_config* cfg, const lococo_qkvo* blk, int32_t B,
                                 const void* conv_w, const void* conv_b, lococo_cache* cache,
                                 void* workspace, size_t ws_bytes, void* stream) {
@@ -885,7 +921,6 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
     hipStream_t s = (hipStream_t)stream;
     const size_t slot = align_up(state_bytes(cfg), 256);
     const int64_t window_rows = std::min<int64_t>(L, window * (int64_t)B);
-    char* sync_ws = (char*)workspace + filter_ws_bytes(cfg);      // fused path only
     float* win_stats = (float*)((char*)workspace + step_ws_bytes(cfg, path, B));
     char* hist_k = (char*)win_stats + stats_bytes(cfg, window_rows);
     char* hist_v = hist_k + (size_t)ring * slot;
@@ -924,37 +959,14 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
         if (one_launch) {
           // every later block of the window compresses too (the cache stays full): one launch runs
           // them all, the slot tiles of a chain handing the new cache to each other through the ring
-          const bool capturing = stream_is_capturing(s);
-          std::unique_lock<std::mutex> lk(g_scan_mu);
-          if (!capturing && another_scan_in_flight(s)) {
-            one_launch = false;          // another persistent scan holds compute units: one launch per step
-          } else {
-            if (c_done > 0)              // the counters start every launch at zero; the status word is kept
-              HIP_TRY(launch_scan_sync_clear(sync_ws, cfg->batch, cfg->n_kv_heads, cfg->M, true, s), "clearing the scan counters");
-            ScanArgs sa;
-            sa.st = a;
-            sa.n_steps = (int32_t)(w1 - bi);
-            sa.B = B;
-            sa.tokens_left = L - sg.start;
-            sa.out_k = hist_k;
-            sa.out_v = hist_v;
-            sa.out_stride = hist_stride;
-            sa.slot0 = (int32_t)(c_done % ring);
-            sa.ring = (int32_t)ring;
-            sa.sync = nullptr;
-            sa.status = nullptr;
-            sa.spin_limit = spin_limit();
-            sa.same_l2_allowed = chain_sync_through_l2() ? 1 : 0;
-            {
-              KTimer t(K_COMPRESS_MFMA, s);
-              HIP_TRY(launch_compress_scan(sa, workspace, filter_banks(cfg), cu_count(), sync_ws,
-                                           partials_of(cfg, workspace, B), prelogits_of(cfg, workspace, B), s),
-                      "compress scan launch");
-            }
-            if (!capturing) note_scan_launched(s);
+          // (the counters start every launch at zero)
+          if ((st = enqueue_scan(cfg, a, w1 - bi, B, L - sg.start, hist_k, hist_v, hist_stride, c_done % ring, ring, workspace,
+                                 c_done > 0, s, &one_launch)))
+            return st;
+          if (one_launch) {
             c_done += w1 - bi;
             break;
-          }
+          }                              // another persistent scan holds compute units: one launch per step
         }
         if (small_scan) {                // one workgroup per chain walks the rest of the window
           KTimer t(K_COMPRESS_SMALL, s);
@@ -1044,7 +1056,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
 }
 
 namespace {
-// the Eq. 5 contractions of the backward pass run on MFMA unless the shape-agnostic kernels are asked for
+// Eq. 4 - 6 of the backward pass run on MFMA (bwd_conv_mfma.hip) unless the shape-agnostic kernels are asked for
 bool bwd_on_mfma(const lococo_config* c) {
   return c->impl != LOCOCO_IMPL_GENERIC && bwd_mfma_supports(c->dtype, c->head_dim, c->conv_in, c->conv_width);
 }
@@ -1068,22 +1080,23 @@ size_t bwd_attn_hl_bytes(const lococo_config* c, int64_t rows) {
 size_t bwd_attn_stat_bytes(const lococo_config* c, int64_t rows) {
   return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * 3 * sizeof(float), 256);
 }
-struct BwdLayout { size_t p, ds, w, n, dw, mf, total; };
+struct BwdLayout { size_t p, ds, w, n, dw, conv, total; };
+BwdConvLayout conv_layout(const lococo_config* c, int32_t T, int64_t n_blk) {
+  return bwd_conv_layout(c->batch, c->n_kv_heads, c->M, T, c->conv_width, c->conv_in, filter_banks(c), n_blk);
+}
 BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   const size_t T = (size_t)len + B;
   const size_t rows = (size_t)c->batch * c->n_q_heads * B * T * sizeof(float);
-  const bool compress = len + B > c->M;
-  const size_t mat = compress ? (size_t)c->batch * c->n_kv_heads * c->M * T * sizeof(float) : 0;
+  const bool compress = len + B > c->M, conv = compress && bwd_on_mfma(c);
+  const size_t mat = compress && !conv ? align_up((size_t)c->batch * c->n_kv_heads * c->M * T * sizeof(float), 256) : 0;
   BwdLayout l;
   l.p = 0;                                     // attention rows, or dO as two halves; then their gradient, or the statistics
   l.ds = std::max(align_up(rows, 256), bwd_attn_hl_bytes(c, B));
   l.w = l.ds + std::max(align_up(rows, 256), bwd_attn_stat_bytes(c, B));
-  l.n = l.w + align_up(mat, 256);
-  l.dw = l.n + align_up(mat, 256);
-  l.mf = l.dw + align_up(mat, 256);
-  l.total = l.mf;
-  if (compress && bwd_on_mfma(c))
-    l.total += bwd_mfma_layout(c->batch, c->n_kv_heads, c->M, (int)T, c->conv_width, c->conv_in, filter_banks(c)).total;
+  l.n = l.w + mat;
+  l.dw = l.n + mat;
+  l.conv = l.dw + mat;
+  l.total = l.conv + (conv ? conv_layout(c, (int32_t)T, 1).total : 0);
   return l;
 }
 // The attention of the blocks of `t` (see BwdAttnArgs; the gradient arrays hold `rows` query / block rows per head from
@@ -1105,23 +1118,41 @@ lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool co
   g.ws_w = (float*)(ws + l.w);
   g.ws_n = (float*)(ws + l.n);
   g.ws_dw = (float*)(ws + l.dw);
-  g.ws_mfma = compress && bwd_on_mfma(cfg) ? ws + l.mf : nullptr;
-  g.banks = filter_banks(cfg);
+  g.conv_elsewhere = compress && bwd_on_mfma(cfg) ? 1 : 0;
   g.gemms_mfma = cfg->impl != LOCOCO_IMPL_GENERIC && cfg->dtype == LOCOCO_BF16 ? 1 : 0;
-  if (compress) {
+  if (compress && !g.conv_elsewhere) {
     // recompute Eq. 5 and Eq. 6 of the forward step: raw logits and normalised rows
-    if (g.ws_mfma) {
-      HIP_TRY(launch_pack_filters_per_tap(g.st, g.banks, g.ws_mfma, s), "filter packing launch");
-      HIP_TRY(launch_conv_logits_mfma(g.st, g.ws_mfma, g.ws_w, s), "conv launch");
-    } else {
-      HIP_TRY(launch_conv_logits_generic(cfg->dtype, g.st, g.ws_w, s), "conv launch");
-    }
+    HIP_TRY(launch_conv_logits_generic(cfg->dtype, g.st, g.ws_w, s), "conv launch");
     if (g.st.protect) HIP_TRY(launch_protect_logits_generic(g.st, g.ws_w, s), "protect launch");
     const size_t mat = (size_t)cfg->batch * cfg->n_kv_heads * cfg->M * ((size_t)g.st.m + g.st.Bn) * sizeof(float);
     HIP_TRY(hipMemcpyAsync(g.ws_n, g.ws_w, mat, hipMemcpyDeviceToDevice, s), "copying the logits");
     HIP_TRY(launch_normalise_generic(g.st, g.ws_n, s), "normalise launch");
   }
   HIP_TRY(launch_step_backward_generic(cfg->dtype, g, compress, s), "backward launches");
+  if (!g.conv_elsewhere) return LOCOCO_OK;
+  const int32_t T = g.st.m + g.st.Bn;
+  BwdConvArgs c{};
+  c.st = g.st;
+  c.n_blk = 1;
+  c.B = g.st.Bn;
+  c.banks = filter_banks(cfg);
+  c.tokens = g.st.Bn;
+  c.d_cache_k = g.d_cache_k;
+  c.d_cache_v = g.d_cache_v;
+  c.d_new_k = g.d_new_k;
+  c.d_new_v = g.d_new_v;
+  c.d_k = g.d_k;
+  c.d_v = g.d_v;
+  c.kv_chain = g.kv_chain;
+  c.d_conv_w = g.d_conv_w;
+  c.d_conv_b = g.d_conv_b;
+  bwd_conv_place(&c, conv_layout(cfg, T, 1), ws + l.conv);
+  HIP_TRY(launch_bwd_conv_begin(c, s), "filter packing launches");
+  HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
+  HIP_TRY(launch_bwd_conv_rows(c, 0, T, s), "row gradient launch");
+  HIP_TRY(launch_bwd_conv_dx(c, 0, 1, 2, T, s), "input gradient launch");
+  HIP_TRY(launch_bwd_conv_dw(c, s), "filter gradient launch");
+  HIP_TRY(launch_bwd_conv_end(c, s), "filter gradient launch");
   return LOCOCO_OK;
 }
 }  // namespace
@@ -1224,22 +1255,22 @@ lococo_status lococo_mix_from_logits(const lococo_config* cfg, const lococo_qkvo
 }  // extern "C"
 
 // ---- backward of a whole scan: the forward recurrence is run once more to keep the state every block
-// started from, then the blocks are walked in reverse, each through lococo_segment_step_backward
+// started from, then the blocks are walked in reverse
 namespace {
 struct SeqBwdLayout {
-  size_t cache[4];        // ping-pong buffers of the recomputed forward: k0, k1, v0, v1 (storage type)
+  size_t fwd_ws, fwd_ws_bytes;        // step workspace of the recomputed forward (first: see lococo_scan_status)
   size_t states_k, states_v, state;   // the state BEFORE every block: n_blocks slots of `state` bytes each
-  size_t fwd_ws, fwd_ws_bytes;        // step workspace of the recomputed forward
-  int64_t window;         // blocks whose attention runs in one launch (see lococo_sequence_backward)
+  int64_t window;         // blocks whose attention, logits and filter gradient run in one launch (see lococo_sequence_backward)
   size_t d_ck, d_cv, slot;            // gradients w.r.t. the state before each of them, fp32, `slot` bytes each
-  size_t hl, stats;       // scratch of those launches
+  size_t hl, stats;       // scratch of the attention launches
+  BwdConvLayout conv;     // of Eq. 4 - 6 (inside step_ws)
   size_t g[2][2];         // gradient w.r.t. the cache state, ping-pong: [which][k, v], fp32 [chains, M, d]
-  size_t step_ws;         // workspace of one backward step
+  size_t step_ws;         // the window's Eq. 4 - 6, or the workspace of one backward step where there are no windows
   size_t total;
 };
-// What the window of the attention may take: enough blocks to fill the device many times over at any shape, whatever the
-// length of the sequence.
-constexpr size_t kBwdWindowBytes = (size_t)1 << 30;
+// What a window may take: enough blocks to fill the device many times over at any shape, whatever the length of the
+// sequence.
+constexpr size_t kBwdWindowBytes = (size_t)2 << 30;
 
 lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBwdLayout* out) {
   SeqBwdLayout l{};
@@ -1248,27 +1279,36 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBw
   const size_t chains = (size_t)c->batch * c->n_kv_heads, es = esize(c->dtype);
   l.state = align_up(chains * c->M * c->head_dim * es, 256);
   const int64_t n = (L + B - 1) / B;
-  for (int i = 0; i < 4; ++i) l.cache[i] = take(l.state);
-  l.states_k = take((size_t)n * l.state);
-  l.states_v = take((size_t)n * l.state);
   Path path;
   lococo_status st = resolve_path(c, B, &path);
   if (st) return st;
   l.fwd_ws_bytes = step_ws_bytes(c, path, B);
   l.fwd_ws = take(l.fwd_ws_bytes);
+  l.states_k = take((size_t)n * l.state);
+  l.states_v = take((size_t)n * l.state);
   l.slot = align_up(chains * c->M * c->head_dim * sizeof(float), 256);
+  size_t step = 0;                    // a step's workspace grows with the occupancy: the full cache bounds all
+  if ((st = lococo_backward_workspace_bytes(c, B, c->M, &step))) return st;
   if (bwd_attn_has_mfma(c)) {
-    const size_t per_block = 2 * l.slot + bwd_attn_hl_bytes(c, B) + bwd_attn_stat_bytes(c, B);
-    l.window = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(kBwdWindowBytes / per_block)));
+    size_t per_block = 2 * l.slot + bwd_attn_hl_bytes(c, B) + bwd_attn_stat_bytes(c, B);
+    if (bwd_on_mfma(c)) {
+      const BwdConvLayout one = conv_layout(c, c->M + B, 1);
+      per_block += one.total - one.per_call;
+    }
+    // (blocks x chains and 2 x blocks are grid dimensions)
+    const int64_t most = std::min<int64_t>((int64_t)(kBwdWindowBytes / per_block), (int64_t)(16384 / chains));
+    l.window = std::max<int64_t>(1, std::min<int64_t>(n, most));
     l.d_ck = take((size_t)l.window * l.slot);
     l.d_cv = take((size_t)l.window * l.slot);
     l.hl = take(bwd_attn_hl_bytes(c, l.window * (int64_t)B));
     l.stats = take(bwd_attn_stat_bytes(c, l.window * (int64_t)B));
+    if (bwd_on_mfma(c)) {
+      l.conv = conv_layout(c, c->M + B, l.window);
+      step = std::max(step, l.conv.total);
+    }
   }
   for (int w = 0; w < 2; ++w)
     for (int kv = 0; kv < 2; ++kv) l.g[w][kv] = take(l.slot);
-  size_t step = 0;                    // a step's workspace grows with the occupancy: the full cache bounds all
-  if ((st = lococo_backward_workspace_bytes(c, B, c->M, &step))) return st;
   l.step_ws = take(step);
   l.total = at;
   *out = l;
@@ -1326,42 +1366,51 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   const size_t es = esize(cfg->dtype), d = (size_t)cfg->head_dim;
   const size_t chains = (size_t)cfg->batch * cfg->n_kv_heads, state = chains * cfg->M * d * es;
 
-  // ---- the recurrence once more, block by block, keeping the state every block starts from: the fill
-  // branch or steps 4-5 only (the same kernels as in lococo_segment_step, so the same states); nobody reads
-  // the attention outputs of step 3 here
+  // ---- the recurrence once more, keeping the state every block starts from: the fill branch or steps 4-5 only (the
+  // same kernels as in the forward schedules, so the same states); nobody reads the attention outputs of step 3 here.
+  // A fill appends in place: the states before the fill blocks are prefixes of one array, the slot of the first block
+  // that compresses (of the last block, if none before it does).
   Path path;
   if ((st = resolve_path(cfg, B, &path))) return st;
   if ((st = check_mfma_strides(cfg, path, seq, B, false))) return st;
-  bool filters_ready = false;
+  int64_t n_fill = 0;
+  while (n_fill < n - 1 && plan[(size_t)n_fill].branch == 0) ++n_fill;
+  auto state_k = [&](int64_t i) { return ws + l.states_k + (size_t)std::max(i, n_fill) * l.state; };
+  auto state_v = [&](int64_t i) { return ws + l.states_v + (size_t)std::max(i, n_fill) * l.state; };
   lococo_cache fc = *cache0;
-  fc.k[0] = ws + l.cache[0]; fc.k[1] = ws + l.cache[1];
-  fc.v[0] = ws + l.cache[2]; fc.v[1] = ws + l.cache[3];
   fc.cur = 0;
   fc.attn_colsum = nullptr;
-  HIP_TRY(hipMemcpyAsync(fc.k[0], cache0->k[cache0->cur], state, hipMemcpyDeviceToDevice, s), "copying the first state");
-  HIP_TRY(hipMemcpyAsync(fc.v[0], cache0->v[cache0->cur], state, hipMemcpyDeviceToDevice, s), "copying the first state");
-  for (int64_t i = 0; i < n; ++i) {
+  HIP_TRY(launch_copy_pair(state_k(0), cache0->k[cache0->cur], state_v(0), cache0->v[cache0->cur], state, s),
+          "copying the first state");
+  if (path == PATH_MFMA)
+    HIP_TRY(launch_scan_sync_clear(ws + l.fwd_ws + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false, s),
+            "clearing the scan counters");
+  for (int64_t i = 0; i + 1 < n; ++i) {                      // (the last block's own update is not needed)
     const lococo_seg& sg = plan[(size_t)i];
-    HIP_TRY(hipMemcpyAsync(ws + l.states_k + (size_t)i * l.state, fc.k[fc.cur], state, hipMemcpyDeviceToDevice, s), "keeping a state");
-    HIP_TRY(hipMemcpyAsync(ws + l.states_v + (size_t)i * l.state, fc.v[fc.cur], state, hipMemcpyDeviceToDevice, s), "keeping a state");
-    if (i + 1 == n) break;                                   // the last block's own update is not needed
+    fc.k[0] = state_k(i); fc.k[1] = state_k(i + 1);
+    fc.v[0] = state_v(i); fc.v[1] = state_v(i + 1);
+    fc.cur = 0;
     lococo_qkvo blk = *seq;
-    for (lococo_tensor* t : {&blk.q, &blk.k, &blk.v}) t->p = (char*)t->p + (size_t)(sg.start * t->stride_t) * es;
     blk.o = blk.q;                                           // (never written)
-    const StepArgs a = make_args(cfg, &blk, 0, sg.len, &fc, conv_w, conv_b, true);
-    if (sg.branch == 1 && path != PATH_GENERIC && !filters_ready) {
+    const StepArgs a = make_args(cfg, &blk, sg.start, sg.len, &fc, conv_w, conv_b, true);
+    if (i == n_fill && path != PATH_GENERIC) {               // the first block that compresses
       if ((st = enqueue_repack(cfg, path, a, ws + l.fwd_ws, s))) return st;
-      filters_ready = true;
+      bool taken = path == PATH_MFMA && scan_fits_one_launch(cfg, a);
+      if (taken && (st = enqueue_scan(cfg, a, n - 1 - i, B, L - sg.start, ws + l.states_k, ws + l.states_v,
+                                      (int64_t)(l.state / es), i + 1, n, ws + l.fwd_ws, false, s, &taken)))
+        return st;
+      if (taken) break;
     }
     lococo_cache next = fc;
     if ((st = enqueue_update(cfg, path, a, &next, ws + l.fwd_ws, B, s))) return st;
-    fc = next;
+    fc.len = next.len;
   }
 
   // ---- reverse walk.  (gk, gv) = gradient w.r.t. the state AFTER the block at hand.  Step 3 of a block needs nothing
   // of the walk, only the states: on the MFMA kernels the attention of a window of blocks runs in one launch ahead of
   // the walk through it and leaves its share of the gradient w.r.t. each block's starting state in a slot of its own,
-  // to which the step then adds.
+  // to which the step then adds.  The same goes for the logits of Eq. 5; and what nobody in the walk waits for, the
+  // gradients w.r.t. the blocks' own rows and the filters, follows it for the whole window.
   const size_t gbytes = chains * cfg->M * d * sizeof(float);
   const float* gk = d_final_k;
   const float* gv = d_final_v;
@@ -1369,6 +1418,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   if (!gv) { gv = (const float*)(ws + l.g[0][1]); HIP_TRY(launch_zero_fill(ws + l.g[0][1], gbytes, s), "clearing the final gradient"); }
   const bool batched = l.window > 0 && bwd_attn_on_mfma(cfg, seq, B);
   const int64_t G = batched ? l.window : n;
+  bool conv_begun = false;
   int w = 1;
   for (int64_t w1 = n; w1 > 0;) {
     const int64_t w0 = std::max<int64_t>(0, w1 - G);
@@ -1377,8 +1427,8 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
       int64_t fills = 0;                       // fill blocks at the head of the window: their states are prefixes of the last one's
       while (w0 + fills < w1 - 1 && plan[(size_t)(w0 + fills)].branch == 0) ++fills;
       lococo_cache at = fc;
-      at.k[0] = ws + l.states_k + (size_t)(w0 + fills) * l.state;
-      at.v[0] = ws + l.states_v + (size_t)(w0 + fills) * l.state;
+      at.k[0] = state_k(w0 + fills);
+      at.v[0] = state_v(w0 + fills);
       at.cur = 0;
       at.len = first.len_before;
       lococo_qkvo blk = *seq;
@@ -1400,11 +1450,64 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
       t.d_cv = (float*)(ws + l.d_cv);
       if ((st = enqueue_bwd_attn(cfg, t, L, ws + l.hl, ws + l.stats, s))) return st;
     }
-    for (int64_t i = w1 - 1; i >= w0; --i) {
+    int64_t w_steps = w1;                      // blocks w0 .. w_steps - 1 are left to the walk step by step
+    if (batched && bwd_on_mfma(cfg)) {
+      while (w_steps > w0 && plan[(size_t)(w_steps - 1)].branch == 1) --w_steps;   // (fills come first)
+      if (w_steps < w1) {
+        const lococo_seg& first = plan[(size_t)w_steps];
+        lococo_cache at = fc;
+        at.k[0] = state_k(w_steps);
+        at.v[0] = state_v(w_steps);
+        at.cur = 0;
+        at.len = first.len_before;
+        lococo_qkvo blk = *seq;
+        blk.o = blk.q;
+        BwdConvArgs c{};
+        c.st = make_args(cfg, &blk, first.start, first.len, &at, conv_w, conv_b, true);
+        c.n_blk = (int32_t)(w1 - w_steps);
+        c.B = B;
+        c.banks = filter_banks(cfg);
+        c.tokens = std::min<int64_t>(L - first.start, c.n_blk * (int64_t)B);
+        c.state_stride = (int64_t)(l.state / es);
+        c.d_cache_k = (float*)(ws + l.d_ck + (size_t)(w_steps - w0) * l.slot);
+        c.d_cache_v = (float*)(ws + l.d_cv + (size_t)(w_steps - w0) * l.slot);
+        c.d_stride = (int64_t)(l.slot / sizeof(float));
+        c.d_new_k = gk;
+        c.d_new_v = gv;
+        c.d_k = d_k + first.start * (int64_t)d;
+        c.d_v = d_v + first.start * (int64_t)d;
+        c.kv_chain = L * (int64_t)d;
+        c.d_conv_w = d_conv_w;
+        c.d_conv_b = d_conv_b;
+        bwd_conv_place(&c, l.conv, ws + l.step_ws);
+        if (!conv_begun) HIP_TRY(launch_bwd_conv_begin(c, s), "filter packing launches");
+        conv_begun = true;
+        if (first.len_before < cfg->M) {       // the rows no entry was live in: zero
+          BwdArgs g{};
+          g.st = c.st;
+          g.d_cache_k = c.d_cache_k;
+          g.d_cache_v = c.d_cache_v;
+          g.attn_done = g.conv_elsewhere = 1;
+          HIP_TRY(launch_step_backward_generic(cfg->dtype, g, true, s), "clearing the rows of empty slots");
+        }
+        HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
+        for (int i = c.n_blk - 1; i >= 0; --i) {
+          const lococo_seg& sg = plan[(size_t)(w_steps + i)];
+          HIP_TRY(launch_bwd_conv_rows(c, i, sg.len_before + sg.len, s), "row gradient launch");
+          HIP_TRY(launch_bwd_conv_dx(c, i, 1, 0, sg.len_before, s), "input gradient launch");
+        }
+        HIP_TRY(launch_bwd_conv_dx(c, 0, c.n_blk, 1, B, s), "input gradient launch");
+        HIP_TRY(launch_bwd_conv_dw(c, s), "filter gradient launch");
+        if (w_steps == 0 || plan[(size_t)(w_steps - 1)].branch == 0) HIP_TRY(launch_bwd_conv_end(c, s), "filter gradient launch");
+        gk = c.d_cache_k;
+        gv = c.d_cache_v;
+      }
+    }
+    for (int64_t i = w_steps - 1; i >= w0; --i) {
       const lococo_seg& sg = plan[(size_t)i];
       lococo_cache before = fc;
-      before.k[0] = ws + l.states_k + (size_t)i * l.state;
-      before.v[0] = ws + l.states_v + (size_t)i * l.state;
+      before.k[0] = state_k(i);
+      before.v[0] = state_v(i);
       before.cur = 0;
       before.len = sg.len_before;
       lococo_qkvo blk = *seq;

@@ -612,8 +612,6 @@ template <typename T>
 hipError_t run(const BwdArgs& g, bool compress, hipStream_t s) {
   const StepArgs& a = g.st;
   const int Tn = a.m + a.Bn, chains = a.batch * a.Hkv;
-  // with g.ws_mfma set every contraction below has a matrix-core form (tiled_mfma.hip)
-  const bool conv_mfma = g.ws_mfma != nullptr;
   const bool mfma = g.gemms_mfma && bwd_gemms_mfma_fit(g);
   hipError_t e = hipSuccess;
   if (!g.attn_done) {
@@ -637,6 +635,7 @@ hipError_t run(const BwdArgs& g, bool compress, hipStream_t s) {
     hipLaunchKernelGGL(bwd_fill_k, dim3(64, chains), dim3(kThreads), 0, s, g);
     return hipGetLastError();
   }
+  if (g.conv_elsewhere) return hipGetLastError();
   if (mfma) e = launch_bwd_mix_dw_mfma(g, s);
   else
     hipLaunchKernelGGL(bwd_mix_dw_k<T>, dim3((Tn + kMT - 1) / kMT, (a.M + kMT - 1) / kMT, chains), dim3(kThreads), 0,
@@ -648,7 +647,6 @@ hipError_t run(const BwdArgs& g, bool compress, hipStream_t s) {
     hipLaunchKernelGGL(bwd_mix_cols_k, dim3((2 * a.d + kMT - 1) / kMT, (Tn + kMT - 1) / kMT, chains), dim3(kThreads), 0,
                        s, g);
   if (e != hipSuccess) return e;
-  if (conv_mfma) return launch_bwd_conv_mfma(g, g.banks, g.ws_mfma, s);   // the two Eq. 5 gradients
   const int C = a.conv_in ? 2 * a.d : a.d;
   hipLaunchKernelGGL(bwd_conv_x_k<T>, dim3((Tn + kTI - 1) / kTI, (C + kTI - 1) / kTI, chains), dim3(kThreads), 0, s, g);
   hipLaunchKernelGGL(bwd_conv_w_k<T>,

@@ -1,0 +1,753 @@
+// Backward of Eq. 5, 6 and 4 of the compress steps of a window of blocks, bf16 storage, head_dim 128, filters over the
+// keys or over [K | V], any odd width up to 31.  With X = [cache ; block], g = the gradient w.r.t. the new cache:
+//
+//   G[i, j]      = g_k[i] . Xk[j] + g_v[i] . Xv[j]                                  (Eq. 4 w.r.t. the weights)
+//   dl[i, j]     = n[i, j] (G[i, j] - sum_j n G)                                    (Eq. 6; n: the normalised row i)
+//   dX[j, :]    += sum_i n[i, j] g[i, :] + sum_t sum_i dl[i, j - t + p] W[i, :, t]  (Eq. 4 and Eq. 5 w.r.t. the entries)
+//   dW[i, c, t] += sum_j dl[i, j] X[j + t - p, c]                                   (Eq. 5 w.r.t. the filters)
+//
+// Only g has to wait for the walk, and of dX only the rows of the cache are what the walk hands on.  So the logits of all
+// blocks come from one launch ahead of the walk (tiled_mfma.hip), a step of the walk is two launches (bwd_rows_k, bwd_dx_k
+// over the cache rows), and the rows of the blocks and the filter gradient follow in one launch each for the whole window.
+//
+// g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  dl
+// and n are kept as "planes" [chain][32 slots][position][32 high halves | 32 low halves]: 128 bytes per position, read row
+// by row where the slots are contracted (bwd_dx_k) and down the rows where the positions are (bwd_dw_k).
+#include <algorithm>
+
+#include "lococo_internal.h"
+#include "mfma_util.h"
+
+namespace lococo {
+namespace {
+
+constexpr int kD = 128;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;      // the caller's gradients: any float address
+
+// 64 lanes x 16 bytes, lane l from its own address p into cell l of the 1 KB of LDS at lds_addr (see load_to_lds)
+__device__ __forceinline__ void gather_to_lds(const unsigned char* p, uint32_t lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(lds_addr), "v"(p) : "memory");
+}
+// every wave has finished reading and its awaited loads have landed (waited for by hand)
+__device__ __forceinline__ void barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Rows of 128 bytes in LDS (8 cells): chunk c of row r sits in cell c ^ pswz(r).  Sixteen consecutive rows put one chunk on
+// sixteen different cells of 256 bytes; four rows from a multiple of four put four consecutive chunks there.
+__device__ __forceinline__ int pswz(int r) { return (((r >> 1) & 1) << 2) | ((r >> 2) & 3); }
+
+struct Block { int m, Bn, T; const uint16_t* ck; const uint16_t* cv; const uint16_t* k; const uint16_t* v; };
+__device__ __forceinline__ Block block_of(const BwdConvArgs& g, int blk) {
+  const StepArgs& a = g.st;
+  Block b;
+  const int64_t left = g.tokens - (int64_t)blk * g.B;
+  b.m = blk ? a.M : a.m;
+  b.Bn = (int)(left < g.B ? left : g.B);
+  b.T = b.m + b.Bn;
+  b.ck = (const uint16_t*)a.cache_k + blk * g.state_stride;
+  b.cv = (const uint16_t*)a.cache_v + blk * g.state_stride;
+  b.k = (const uint16_t*)a.k.p + (int64_t)blk * g.B * a.k.st;
+  b.v = (const uint16_t*)a.v.p + (int64_t)blk * g.B * a.v.st;
+  return b;
+}
+// row j of [cache ; block] of a chain, keys or values
+__device__ __forceinline__ const uint16_t* x_row(const StepArgs& a, const Block& x, int ch, int j, bool val) {
+  if (j < x.m) return (val ? x.cv : x.ck) + ((int64_t)ch * a.M + j) * kD;
+  const View& s = val ? a.v : a.k;
+  return (val ? x.v : x.k) + (ch / a.Hkv) * s.sb + (ch % a.Hkv) * s.sh + (int64_t)(j - x.m) * s.st;
+}
+__device__ __forceinline__ const float* grad_new(const BwdConvArgs& g, int blk, bool val) {
+  if (blk + 1 < g.n_blk) return (val ? g.d_cache_v : g.d_cache_k) + (blk + 1) * g.d_stride;
+  return val ? g.d_new_v : g.d_new_k;
+}
+
+// a value reduced over the 32 lanes of a half-wave
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <bool MAX>
+__device__ __forceinline__ float over32(float v) {
+  auto op = [](float x, float y) { return MAX ? fmaxf(x, y) : x + y; };
+  v = op(v, dpp<0xB1>(v));              // quad_perm [1,0,3,2]
+  v = op(v, dpp<0x4E>(v));              // quad_perm [2,3,0,1]
+  v = op(v, dpp<0x141>(v));             // row_half_mirror
+  v = op(v, dpp<0x140>(v));             // row_mirror
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+// exp(x), x <= 0: the product with log2 e carried to twice the working precision (v_exp_f32 is exact to one unit)
+__device__ __forceinline__ float exp_neg(float x) {
+  constexpr float lo2e = 1.9259629911e-8f;                 // log2(e) - (float)log2(e)
+  const float t = x * kLog2e, r = fmaf(x, lo2e, fmaf(x, kLog2e, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return x < -104.f ? 0.f : fmaf(e, r * 0.69314718f, e);   // (below: zero, and -inf has no remainder)
+}
+
+// ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
+// each; the rows of a step stay in registers from the logits to dl.  MULTI: more positions than that: they are walked
+// twice in chunks, first for the row sums alone.
+template <int NT, bool MULTI>
+__global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
+  const StepArgs& a = g.st;
+  __shared__ __align__(16) unsigned char Gs[2][2][32 * 256];     // [half][keys, values]: tiles of 32 rows (see swz)
+  __shared__ __align__(16) float red[2][8][32];
+  __shared__ __align__(16) float row_s[3][32];                   // reference, 1 / sum, sum n G
+  const Block x = block_of(g, blk);
+  const int tiles = (a.M + 31) / 32, item = xcd_item(blockIdx.x, gridDim.x);
+  const int sb = item % tiles, ch = item / tiles, s0 = sb * 32, hkv = ch % a.Hkv;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
+  const float* gk = grad_new(g, blk, false) + (int64_t)ch * a.M * kD;
+  const float* gv = grad_new(g, blk, true) + (int64_t)ch * a.M * kD;
+  uint16_t* gsp = g.gsplit + (int64_t)blk * g.gsplit_stride;
+  // slots that mix: all live ones but the protected
+  uint32_t mixing = a.M - s0 >= 32 ? 0xffffffffu : (1u << (a.M - s0)) - 1u;
+  const uint32_t* prot = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
+  if (prot && s0 < x.m) {
+    uint32_t p = prot[sb];
+    if (x.m - s0 < 32) p &= (1u << (x.m - s0)) - 1u;
+    if (p) {                                // a protected slot hands its gradient to the old row
+      float* dk = g.d_cache_k + blk * g.d_stride + (int64_t)ch * a.M * kD;
+      float* dv = g.d_cache_v + blk * g.d_stride + (int64_t)ch * a.M * kD;
+      for (int e = tid; e < 32 * kD; e += 512) {
+        const int64_t o = (int64_t)s0 * kD + e;
+        if ((p >> (e >> 7)) & 1u & (mixing >> (e >> 7))) { dk[o] += gk[o]; dv[o] += gv[o]; }
+      }
+    }
+    mixing &= ~p;
+  }
+  mixing = __builtin_amdgcn_readfirstlane(mixing);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {             // eight columns of a row of [g_k | g_v] per item
+    const int it = tid + i * 512, r = it >> 5, c8 = it & 31, val = c8 >> 4;
+    const bool in = s0 + r < a.M;
+    const float* p = (val ? gv : gk) + (int64_t)(in ? s0 + r : 0) * kD + (c8 & 15) * 8;
+    const f32x4_any v0 = *(const f32x4_any*)p, v1 = *(const f32x4_any*)(p + 4);
+    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+    bf16x8 hi, lo;
+    split8(v, hi, lo);
+    const int at = r * 256 + (((c8 & 15) ^ swz(r)) << 4);
+    *(bf16x8*)(Gs[0][val] + at) = hi;
+    *(bf16x8*)(Gs[1][val] + at) = lo;
+    if (in) {                               // for bwd_dx_k: [half][chain][slot][K | V]
+      uint16_t* o = gsp + ((int64_t)ch * a.M + s0 + r) * (2 * kD) + c8 * 8;
+      *(bf16x8*)o = hi;
+      *(bf16x8*)(o + (int64_t)a.batch * a.Hkv * a.M * (2 * kD)) = lo;
+    }
+  }
+  int ga[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) ga[ks] = l31 * 256 + (((2 * ks + lh) ^ swz(l31)) << 4);
+  const float* lg = g.logits + blk * g.logits_stride + (int64_t)ch * a.M * g.ld;
+  __syncthreads();
+
+  f32x16 acc[NT], xl[NT];
+  // the logits (row i of the tile: slot s0 + 8 (i / 4) + 4 lh + i % 4; this lane: position) and G of tile n of a chunk;
+  // a position that does not count has the logit -inf
+  auto fetch = [&](int pc) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = pc + (w + 8 * n) * 32, pos = p0 + l31;
+      const bool out = pos >= x.T || (prot && pos < x.m && ((prot[pos >> 5] >> (pos & 31)) & 1u));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = s0 + (i >> 2) * 8 + lh * 4 + (i & 3);
+        const float v = p0 < x.T ? lg[(int64_t)(r < a.M ? r : a.M - 1) * g.ld + (pos < x.T ? pos : 0)] : 0.f;
+        xl[n][i] = out ? -INFINITY : v;
+      }
+    }
+  };
+  auto contract = [&](int pc) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = pc + (w + 8 * n) * 32;
+      acc[n] = zero16();
+      if (p0 >= x.T) continue;
+      const int j = p0 + l31 < x.T ? p0 + l31 : x.T - 1;
+#pragma unroll
+      for (int val = 0; val < 2; ++val) {
+        const uint16_t* row = x_row(a, x, ch, j, val) + lh * 8;
+        bf16x8 fx[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) fx[ks] = *(const bf16x8*)(row + ks * 16);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          acc[n] = mfma32(*(const bf16x8*)(Gs[0][val] + ga[ks]), fx[ks], acc[n]);
+          acc[n] = mfma32(*(const bf16x8*)(Gs[1][val] + ga[ks]), fx[ks], acc[n]);
+        }
+      }
+    }
+  };
+  // the 16 rows' values of a lane, combined over the lanes and the waves; the result of row r lands with thread r
+  auto over_waves = [&](const f32x16& v, int which, bool mx) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float t = mx ? over32<true>(v[i]) : over32<false>(v[i]);
+      if (l31 == 0) red[which][w][(i >> 2) * 8 + lh * 4 + (i & 3)] = t;
+    }
+  };
+  auto collect = [&](int which, bool mx) {
+    float t = red[which][0][tid];
+    for (int k = 1; k < 8; ++k) t = mx ? fmaxf(t, red[which][k][tid]) : t + red[which][k][tid];
+    return t;
+  };
+  f32x16 rv;
+  auto rows = [&](int which) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 t = *(const f32x4*)&row_s[which][q * 8 + lh * 4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rv[q * 4 + e] = t[e];
+    }
+  };
+  // logits -> unnormalised weights, and the sums of a chunk on top of (sum, dot) of thread r < 32
+  float ref = -INFINITY, sum = 0.f, dot = 0.f;
+  auto weigh = [&]() {
+    if (a.norm == 0) {
+      f32x16 mx = xl[0];
+#pragma unroll
+      for (int n = 1; n < NT; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], xl[n][i]);
+      over_waves(mx, 0, true);
+      __syncthreads();
+      if (tid < 32) {
+        const float t = fmaxf(ref, collect(0, true));
+        if (MULTI && ref > -INFINITY) {
+          const float f = exp_neg(ref - t);
+          sum *= f;
+          dot *= f;
+        }
+        ref = row_s[0][tid] = t;
+      }
+      __syncthreads();
+      rows(0);
+    }
+    f32x16 ps = zero16(), pd = zero16();
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float e = a.norm == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
+        xl[n][i] = e;
+        ps[i] += e;
+        pd[i] = fmaf(e, acc[n][i], pd[i]);
+      }
+    over_waves(ps, 0, false);
+    over_waves(pd, 1, false);
+    __syncthreads();
+    if (tid < 32) {
+      sum += collect(0, false);
+      dot += collect(1, false);
+    }
+  };
+  auto publish = [&]() {
+    if (tid < 32) {
+      const float inv = 1.0f / (a.norm == 0 ? sum : sum + a.eps);
+      row_s[1][tid] = inv;
+      row_s[2][tid] = dot * inv;
+    }
+    __syncthreads();
+  };
+  f32x16 bsum = zero16();
+  auto finish = [&](int pc) {               // xl: unnormalised weights
+    f32x16 inv, r;
+    rows(1); inv = rv;
+    rows(2); r = rv;
+    uint16_t* pn = g.wn + blk * g.plane_stride;
+    uint16_t* pl = g.dl + blk * g.plane_stride;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = pc + (w + 8 * n) * 32, pos = p0 + l31;
+      if (p0 >= x.T) continue;
+      const int64_t o = (((int64_t)ch * tiles + sb) * g.P + pos) * 64 + lh * 8;
+#pragma unroll
+      for (int qp = 0; qp < 2; ++qp) {      // slots 16 qp .. + 15: two groups of four of this lane
+        uint32_t nh[2][2], nl[2][2], dh[2][2], dlo[2][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          float vn[4], vd[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int i = (qp * 2 + q) * 4 + e, slot = (qp * 2 + q) * 8 + lh * 4 + e;
+            const bool on = (mixing >> slot) & 1u;
+            const float nn = xl[n][i] * inv[i], dG = acc[n][i] - r[i];
+            const float d = a.norm == 0 ? (xl[n][i] > 0.f ? nn * dG : 0.f) : (xl[n][i] > 0.f ? dG * inv[i] : 0.f);
+            vn[e] = on ? nn : 0.f;
+            vd[e] = on ? d : 0.f;
+            bsum[i] += pos < x.T ? vd[e] : 0.f;
+          }
+          split2(vn[0], vn[1], nh[q][0], nl[q][0]);
+          split2(vn[2], vn[3], nh[q][1], nl[q][1]);
+          split2(vd[0], vd[1], dh[q][0], dlo[q][0]);
+          split2(vd[2], vd[3], dh[q][1], dlo[q][1]);
+        }
+        // the halves of the wave trade groups, so that a lane has eight consecutive slots: 16 qp + 8 lh ..
+        auto put = [&](uint16_t* at, const uint32_t (&v)[2][2]) {
+          const auto t0 = __builtin_amdgcn_permlane32_swap(v[0][0], v[1][0], false, false);
+          const auto t1 = __builtin_amdgcn_permlane32_swap(v[0][1], v[1][1], false, false);
+          const u32x4 out = {t0[0], t1[0], t0[1], t1[1]};
+          if (pos < x.T) *(u32x4*)at = out;
+        };
+        put(pn + o + qp * 16, nh);
+        put(pn + o + qp * 16 + 32, nl);
+        put(pl + o + qp * 16, dh);
+        put(pl + o + qp * 16 + 32, dlo);
+      }
+    }
+  };
+  if (!MULTI) {
+    fetch(0);
+    contract(0);
+    weigh();
+    publish();
+    finish(0);
+  } else {
+    for (int pc = 0; pc < x.T; pc += 256 * NT) {
+      fetch(pc);
+      contract(pc);
+      weigh();
+      __syncthreads();
+    }
+    publish();
+    for (int pc = 0; pc < x.T; pc += 256 * NT) {
+      fetch(pc);
+      contract(pc);
+      if (a.norm == 0) rows(0);
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xl[n][i] = a.norm == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
+      finish(pc);
+    }
+  }
+  if (g.d_conv_b) {
+    __syncthreads();
+    over_waves(bsum, 0, false);
+    __syncthreads();
+    if (tid < 32 && ((mixing >> tid) & 1u)) atomicAdd(g.d_conv_b + hkv * a.b_head_stride + s0 + tid, collect(0, false));
+  }
+}
+
+// ---- dX: a workgroup per (PT positions, 128 key or value columns) of a chain and block, contraction over the slots in
+// chunks of 64: for each chunk a stage per tap (dl, row-shifted, times that tap's filters) and two with n (times the two
+// halves of g).  The eight waves split each chunk four ways (16 slots each) and the outputs two ways; the four partial
+// sums meet in LDS at the end.  Everything arrives by loads that write LDS directly: the 64 x 128 right-hand matrices two
+// stages ahead in a ring of three, the plane rows of the next chunk (with their halo) while one is worked on.  Rows
+// outside come from a page of zeros.
+// part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
+template <int PT>
+__global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : 2;     // 32 x 32 output blocks of a wave
+  constexpr int DR = PT + 32, ND = DR / 32;                        // rows of a plane tile; its requests per wave
+  constexpr int WB = 64 * 256, DB = 2 * DR * 128;
+  const StepArgs& a = g.st;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
+  unsigned char* Ds = smem + 3 * WB;
+  const int blk = blk0 + blockIdx.z / 2, val = blockIdx.z % 2, ch = blockIdx.y, hkv = ch % a.Hkv;
+  const Block x = block_of(g, blk);
+  const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
+  if (p0 >= pend) return;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
+  const int kq = w & 3, wo = w >> 2;
+  const int KW = a.k_width, pad = (KW - 1) / 2, C = a.conv_in ? 2 * kD : kD, tiles = (a.M + 31) / 32;
+  const bool taps = val == 0 || a.conv_in;
+  const int nsc = (a.M + 63) / 64;
+  const unsigned char* zero = (const unsigned char*)g.zero_page + (l & 15) * 16;
+  const unsigned char* wt = (const unsigned char*)(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + (val ? kD : 0));
+  const unsigned char* gs = (const unsigned char*)(g.gsplit + blk * g.gsplit_stride + (int64_t)ch * a.M * (2 * kD) + (val ? kD : 0));
+  const int64_t gs_lo = (int64_t)a.batch * a.Hkv * a.M * (2 * kD) * 2;
+  const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+  const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+
+  // a stage: tap t of dl of chunk sc (ph 0), or half t of g with n (ph 1)
+  struct Stage { int sc, ph, t; };
+  auto next = [&](Stage s) {
+    if (++s.t == (s.ph ? 2 : KW)) {
+      s.t = 0;
+      if (s.ph) { ++s.sc; s.ph = taps ? 0 : 1; }
+      else s.ph = 1;
+    }
+    return s;
+  };
+  auto request_w = [&](const Stage& s, int buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4), slot = s.sc * 64 + r, chunk = (l & 15) ^ swz(r);
+      const unsigned char* p = s.ph == 0 ? wt + ((int64_t)s.t * a.M + slot) * (C * 2) + chunk * 16
+                                         : gs + (s.t ? gs_lo : 0) + (int64_t)slot * 512 + chunk * 16;
+      gather_to_lds(slot < a.M ? p : zero, lds0 + buf * WB + r4 * 1024);
+    }
+  };
+  auto request_d = [&](int sc, int ph, int buf) {
+    const unsigned char* base = ph ? pn : pl;
+    const int q0 = ph ? p0 : p0 - (KW - 1) + pad;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int idx = w * ND + i, ra = idx * 8, sbi = ra >= DR ? 1 : 0, r = ra - sbi * DR + (l >> 3), q = q0 + r;
+      const int sb = sc * 2 + sbi, chunk = (l & 7) ^ pswz(r);
+      const bool in = q >= 0 && q < x.T && sb < tiles;
+      gather_to_lds(in ? base + ((int64_t)sb * g.P + q) * 128 + chunk * 16 : zero, lds0 + 3 * WB + buf * DB + idx * 1024);
+    }
+  };
+  const int row0 = (PT == 128 ? wo * 64 : 0) + l31, col0 = PT == 128 ? 0 : wo * 64;
+  const int dchunk = (kq & 1) * 2 + lh;
+  const unsigned char* dbase = Ds + (kq >> 1) * DR * 128;
+  int wa[CB][2];
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int s16 = l & 15, g2 = (l >> 4) & 1, r = kq * 16 + lh * 8 + (s16 >> 2) + 4 * h;
+      const int chunk = (col0 >> 3) + 4 * cb + 2 * g2 + ((s16 & 3) >> 1);
+      wa[cb][h] = r * 256 + ((chunk ^ swz(r)) << 4) + (s16 & 1) * 8;
+    }
+  f32x16 acc[PB][CB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = zero16();
+
+  Stage s = {0, taps ? 0 : 1, 0}, s2 = next(s);
+  request_d(s.sc, s.ph, 0);
+  request_w(s, 0);
+  request_w(s2, 1);                       // (every phase has a successor or two stages: stage 1 exists)
+  s2 = next(s2);
+  wait_loads<0>();
+  barrier();
+  int wb = 0, db = 0;
+  while (s.sc < nsc) {
+    if (s.t == 0) {                       // the plane rows of the next phase
+      const int sc1 = s.ph ? s.sc + 1 : s.sc, ph1 = s.ph ? (taps ? 0 : 1) : 1;
+      if (sc1 < nsc) request_d(sc1, ph1, db ^ 1);
+    }
+    const bool more = s2.sc < nsc;
+    if (more) request_w(s2, wb == 0 ? 2 : wb - 1);
+    const int r = row0 + (s.ph ? 0 : KW - 1 - s.t);
+    const unsigned char* dp = dbase + db * DB + r * 128 + ((dchunk ^ pswz(r)) << 4);
+    const unsigned char* dpl = dbase + db * DB + r * 128 + (((dchunk + 4) ^ pswz(r)) << 4);
+    const unsigned char* wp = smem + wb * WB;
+    bf16x8 fw[CB], fh[PB], fl[PB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) fw[cb] = frag_tr(wp + wa[cb][0], wp + wa[cb][1]);
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      fh[pb] = *(const bf16x8*)(dp + pb * 32 * 128);
+      fl[pb] = *(const bf16x8*)(dpl + pb * 32 * 128);
+    }
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fh[pb], fw[cb], acc[pb][cb]);
+    if (!(s.ph && s.t)) {                 // low half x low half: below the 16 bits kept
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fl[pb], fw[cb], acc[pb][cb]);
+    }
+    // the next stage's matrix (and plane rows, requested before this stage's matrix) have landed
+    if (more) wait_loads<2>(); else wait_loads<0>();
+    barrier();
+    if (s.t == (s.ph ? 1 : KW - 1)) db ^= 1;
+    wb = wb == 2 ? 0 : wb + 1;
+    s = next(s);
+    s2 = next(s2);
+  }
+  // ---- the four partial sums of each output: column block cb is collected by the wave kq = cb of its half, two column
+  // blocks at a time (a wave's block: 16 registers x 256 bytes)
+  float* red = (float*)smem;
+#pragma unroll
+  for (int c0 = 0; c0 < CB; c0 += 2) {
+    if (c0) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (kq != c0 + c)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) red[((((wo * 2 + c) * 4 + kq) * PB + pb) * 16 + i) * 64 + l] = acc[pb][c0 + c][i];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (kq == c0 + c)
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+          const int pr = p0 + (PT == 128 ? wo * 64 : 0) + pb * 32 + lh * 4;
+          const int col = col0 + (c0 + c) * 32 + l31;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            float v = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              v += k == c0 + c ? acc[pb][c0 + c][i] : red[((((wo * 2 + c) * 4 + k) * PB + pb) * 16 + i) * 64 + l];
+            const int p = pr + (i >> 2) * 8 + (i & 3);
+            if (p >= pend) continue;
+            float* row = p < x.m ? (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + ((int64_t)ch * a.M + p) * kD
+                                 : (val ? g.d_v : g.d_k) + ch * g.kv_chain + ((int64_t)blk * g.B + p - x.m) * kD;
+            row[col] += v;
+          }
+        }
+  }
+}
+
+// ---- dW: a workgroup per (128 slots, 128 columns, two taps) and share of the contraction over (block, chain, position),
+// in stages of 32 positions.  The plane rows and the entries' rows (33 of them: the two taps are one row apart) come two
+// stages ahead into a ring of three; both operands are read down their rows, and the fragments of dl serve both taps.
+// Sums go to dwt [bank][tap][slot][channel] with atomics, once per workgroup.
+constexpr int kDwDl = 4 * 32 * 128, kDwX = 36 * 256, kDwStage = kDwDl + kDwX;
+__global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, int n_units, int spu) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const StepArgs& a = g.st;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
+  const int KW = a.k_width, pad = (KW - 1) / 2, C = a.conv_in ? 2 * kD : kD, tiles = (a.M + 31) / 32;
+  const int tg = (KW + 1) / 2, stiles = (a.M + 127) / 128;
+  const int gi = blockIdx.x % groups, tile = blockIdx.x / groups;
+  const int t0 = (tile % tg) * 2, st = (tile / tg) % stiles, val = tile / tg / stiles, sb0 = st * 4;
+  const bool two = t0 + 1 < KW, per_head = a.w_head_stride != 0;
+  const int hkv = per_head ? blockIdx.y : 0;
+  // unit u: (block, chain), or (block, batch entry) of this kv head where the filters are per head
+  const int per_blk = per_head ? a.batch : a.batch * a.Hkv;
+  const int64_t total = (int64_t)n_units * spu;
+  int64_t n = total * gi / groups;
+  const int64_t n_end = total * (gi + 1) / groups;
+  if (n >= n_end) return;
+  const unsigned char* zero = (const unsigned char*)g.zero_page + (l & 15) * 16;
+
+  struct Cursor { int u, st; };
+  auto request = [&](Cursor c, int buf) {
+    const int blk = c.u / per_blk, e = c.u % per_blk, ch = per_head ? e * a.Hkv + hkv : e, pc = c.st * 32;
+    const Block x = block_of(g, blk);
+    const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+    const uint32_t lds = lds0 + buf * kDwStage;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {          // 32 rows of slot block sb0 + w
+      const int r = i * 8 + (l >> 3), q = pc + r, chunk = (l & 7) ^ pswz(r);
+      gather_to_lds(q < x.T && sb0 + w < tiles ? pl + ((int64_t)(sb0 + w) * g.P + q) * 128 + chunk * 16 : zero,
+                    lds + (w * 4 + i) * 1024);
+    }
+    auto entry = [&](int r4) {
+      const int r = r4 * 4 + (l >> 4), q = pc + r + t0 - pad, chunk = (l & 15) ^ swz(r);
+      const bool in = q >= 0 && q < x.T;
+      gather_to_lds(in ? (const unsigned char*)x_row(a, x, ch, in ? q : 0, val) + chunk * 16 : zero, lds + kDwDl + r4 * 1024);
+    };
+    entry(w * 2);
+    entry(w * 2 + 1);
+    if (w == 0) entry(8);                  // rows 32 .. 35
+  };
+  auto advance = [&](Cursor& c) { if (++c.st == spu) { c.st = 0; ++c.u; } };
+  const int wy = w >> 1, wx = w & 1, s16 = l & 15, g2 = (l >> 4) & 1;
+  int da[2];                               // [4-row half] of k step 0, slot block wy * 2 (high halves; low: ^ 64)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = lh * 8 + (s16 >> 2) + 4 * h, chunk = 2 * g2 + ((s16 & 3) >> 1);
+    da[h] = wy * 2 * 32 * 128 + r * 128 + ((chunk ^ pswz(r)) << 4) + (s16 & 1) * 8;
+  }
+  int xa[2][2][2];                         // [tap][column block][4-row half]
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = lh * 8 + (s16 >> 2) + 4 * h + t, chunk = 8 * wx + 4 * cb + 2 * g2 + ((s16 & 3) >> 1);
+        xa[t][cb][h] = kDwDl + r * 256 + ((chunk ^ swz(r)) << 4) + (s16 & 1) * 8;
+      }
+  f32x16 acc[2][2][2];                     // [tap][slot block][column block]
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[t][y][c] = zero16();
+  Cursor ahead = {(int)(n / spu), (int)(n % spu)};
+  request(ahead, 0);
+  advance(ahead);
+  if (n + 1 < n_end) request(ahead, 1);
+  advance(ahead);
+  wait_loads<0>();
+  barrier();
+  int buf = 0;
+  for (; n < n_end; ++n) {
+    const bool more = n + 2 < n_end;
+    if (more) request(ahead, buf == 0 ? 2 : buf - 1);
+    advance(ahead);
+    const unsigned char* base = smem + buf * kDwStage;
+#pragma unroll
+    for (int kc = 0; kc < 2; ++kc) {       // (16 rows on: swz and pswz repeat)
+      bf16x8 fh[2], fl[2], fx[2][2];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        const unsigned char* p = base + y * 32 * 128 + kc * 16 * 128;
+        fh[y] = frag_tr(p + da[0], p + da[1]);
+        fl[y] = frag_tr(p + (da[0] ^ 64), p + (da[1] ^ 64));
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) fx[t][c] = frag_tr(base + kc * 16 * 256 + xa[t][c][0], base + kc * 16 * 256 + xa[t][c][1]);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (t && !two) break;
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            acc[t][y][c] = mfma32(fh[y], fx[t][c], acc[t][y][c]);
+            acc[t][y][c] = mfma32(fl[y], fx[t][c], acc[t][y][c]);
+          }
+      }
+    }
+    if (!more) wait_loads<0>();            // the next stage has landed; this one's requests may be on their way
+    else if (w == 0) wait_loads<7>();
+    else wait_loads<6>();
+    barrier();
+    buf = buf == 2 ? 0 : buf + 1;
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    if (t && !two) break;
+    float* o = g.dwt + (((int64_t)hkv * KW + t0 + t) * a.M) * C + val * kD;
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int s = st * 128 + wy * 64 + y * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
+        if (s >= a.M) continue;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) atomicAdd(o + (int64_t)s * C + wx * 64 + c * 32 + l31, acc[t][y][c][i]);
+      }
+  }
+}
+
+// d_conv_w[bank][slot][channel][tap] += dwt[bank][tap][slot][channel]
+__global__ void bwd_add_dw_k(const float* dwt, float* d_conv_w, int M, int C, int KW, int banks, int64_t w_head_stride) {
+  const int64_t n = (int64_t)banks * M * C * KW;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+    const int t = (int)(e % KW);
+    const int c = (int)((e / KW) % C);
+    const int s = (int)((e / ((int64_t)KW * C)) % M);
+    const int bank = (int)(e / ((int64_t)KW * C * M));
+    d_conv_w[bank * w_head_stride + ((int64_t)s * C + c) * KW + t] += dwt[(((int64_t)bank * KW + t) * M + s) * C + c];
+  }
+}
+
+template <typename F>
+hipError_t allow_lds(F* k, int bytes) {
+  return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+template <int PT>
+hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
+  constexpr int rings = 3 * 64 * 256 + 2 * 2 * (PT + 32) * 128, sums = 2 * 2 * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
+  constexpr int lds = rings > sums ? rings : sums;
+  static const hipError_t e = allow_lds(bwd_dx_k<PT>, lds);
+  if (e != hipSuccess) return e;
+  const StepArgs& a = g.st;
+  hipLaunchKernelGGL(bwd_dx_k<PT>, dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 2 * n_blk), dim3(512), lds, s, g, blk0, part);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk) {
+  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
+  const size_t chains = (size_t)batch * Hkv, C = conv_in ? 2 * kD : kD;
+  BwdConvLayout l;
+  l.ld = (T + 31) / 32 * 32;
+  l.logits_stride = up(chains * M * l.ld * 4) / 4;
+  l.plane_stride = up(chains * ((M + 31) / 32) * T * 128) / 2;
+  l.gsplit_stride = up(chains * M * 2 * kD * 2 * 2) / 2;
+  size_t at = 0;
+  auto take = [&](size_t bytes) { const size_t here = at; at += up(bytes); return here; };
+  l.wt = take((size_t)banks * conv_width * M * C * 2);
+  l.zero_page = take(256);
+  l.dwt = take((size_t)banks * conv_width * M * C * 4);
+  l.per_call = at;
+  l.logits = take((size_t)n_blk * l.logits_stride * 4);
+  l.dl = take((size_t)n_blk * l.plane_stride * 2);
+  l.wn = take((size_t)n_blk * l.plane_stride * 2);
+  l.gsplit = take((size_t)n_blk * l.gsplit_stride * 2);
+  l.total = at;
+  l.P = T;
+  return l;
+}
+
+void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
+  char* p = (char*)ws;
+  g->wt = (uint16_t*)(p + l.wt);
+  g->zero_page = p + l.zero_page;
+  g->dwt = (float*)(p + l.dwt);
+  g->logits = (float*)(p + l.logits);
+  g->dl = (uint16_t*)(p + l.dl);
+  g->wn = (uint16_t*)(p + l.wn);
+  g->gsplit = (uint16_t*)(p + l.gsplit);
+  g->logits_stride = (int64_t)l.logits_stride;
+  g->plane_stride = (int64_t)l.plane_stride;
+  g->gsplit_stride = (int64_t)l.gsplit_stride;
+  g->ld = l.ld;
+  g->P = l.P;
+}
+
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, hipStream_t s) {
+  const StepArgs& a = g.st;
+  const size_t n = (size_t)g.banks * a.k_width * a.M * (a.conv_in ? 2 * kD : kD);
+  hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
+  if (e != hipSuccess) return e;
+  // the page of zeros lies right before the sums
+  return launch_zero_fill(g.zero_page, (size_t)((char*)(g.dwt + n) - (char*)g.zero_page), s);
+}
+
+hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
+  StepArgs a = g.st;
+  a.ldw = g.ld;
+  LogitsWindow win = {g.n_blk, g.B, g.tokens, g.state_stride, g.logits_stride};
+  return launch_conv_logits_mfma(a, g.wt, g.logits, s, &win);
+}
+
+hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s) {
+  const StepArgs& a = g.st;
+  const dim3 grid((a.M + 31) / 32 * a.batch * a.Hkv), block(512);
+  if (T <= 256) hipLaunchKernelGGL((bwd_rows_k<1, false>), grid, block, 0, s, g, blk);
+  else if (T <= 512) hipLaunchKernelGGL((bwd_rows_k<2, false>), grid, block, 0, s, g, blk);
+  else if (T <= 1024) hipLaunchKernelGGL((bwd_rows_k<4, false>), grid, block, 0, s, g, blk);
+  else hipLaunchKernelGGL((bwd_rows_k<2, true>), grid, block, 0, s, g, blk);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  // the largest tile of which there is one for every compute unit
+  const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
+  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64>(g, blk0, n_blk, part, rows, s);
+  return launch_dx<32>(g, blk0, n_blk, part, rows, s);
+}
+
+hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s) {
+  static const hipError_t e = allow_lds(bwd_dw_k, 3 * kDwStage);
+  if (e != hipSuccess) return e;
+  const StepArgs& a = g.st;
+  const bool per_head = a.w_head_stride != 0;
+  const int units = g.n_blk * (per_head ? a.batch : a.batch * a.Hkv), spu = (g.P + 31) / 32;
+  const int tiles = (a.k_width + 1) / 2 * ((a.M + 127) / 128) * (a.conv_in ? 2 : 1);
+  // two workgroups per compute unit, the workgroups of a share (all tiles read the same rows) on one XCD
+  const int64_t want = std::max<int64_t>(1, 2 * cu_count() / ((int64_t)tiles * (per_head ? a.Hkv : 1)));
+  int64_t groups = std::min<int64_t>(want >= 8 ? want / 8 * 8 : want, (int64_t)units * spu);
+  hipLaunchKernelGGL(bwd_dw_k, dim3((unsigned)(tiles * groups), per_head ? a.Hkv : 1), dim3(256), 3 * kDwStage, s, g,
+                     (int)groups, units, spu);
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s) {
+  const StepArgs& a = g.st;
+  const int C = a.conv_in ? 2 * kD : kD;
+  const int64_t n = (int64_t)g.banks * a.k_width * a.M * C;
+  hipLaunchKernelGGL(bwd_add_dw_k, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256), 0, s, g.dwt, g.d_conv_w,
+                     a.M, C, a.k_width, g.banks, a.w_head_stride);
+  return hipGetLastError();
+}
+
+}  // namespace lococo

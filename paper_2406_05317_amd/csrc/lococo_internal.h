@@ -134,10 +134,9 @@ struct BwdArgs {
   float* ws_w;
   float* ws_n;
   float* ws_dw;
-  void* ws_mfma;           // workspace of the MFMA form of the Eq. 5 contractions (see BwdMfmaLayout), or null
   int64_t q_chain, kv_chain;
   int32_t attn_done;       // the contributions of the attention are in d_q, d_k, d_v, d_cache_k, d_cache_v already
-  int32_t banks;           // filter banks (1 = shared by the kv heads)
+  int32_t conv_elsewhere;  // a compress step's Eq. 4 - 6 are the caller's (bwd_conv_mfma.hip): attention and dead rows only
   int32_t gemms_mfma;      // the plain contractions may take their MFMA form (bf16 storage; see bwd_gemms_mfma_fit)
 };
 hipError_t launch_step_backward_generic(int dtype, const BwdArgs& g, bool compress, hipStream_t s);
@@ -247,16 +246,15 @@ hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s);
 bool attn_decode_supports(int dtype, int d, int Bn, int M, bool colsum);
 hipError_t launch_attn_decode(const StepArgs& a, hipStream_t s);
 
-// ---- Eq. 5 of the backward pass on MFMA (tiled_mfma.hip): bf16, head_dim 128, keys-only or [K | V] filters
-bool bwd_mfma_supports(int dtype, int d, int conv_in, int conv_width);
-// byte offsets inside its workspace: filters per tap, dW split into two bf16 halves (transposed, then as it is),
-// filter gradient per tap
-struct BwdMfmaLayout { size_t wt, dhi, dlo, dhi_s, dlo_s, dwt, total; };
-BwdMfmaLayout bwd_mfma_layout(int batch, int Hkv, int M, int Tn, int conv_width, int conv_in, int banks);
-// conv_w -> [bank][tap][slot][channel] at the layout's wt
+// ---- Eq. 5 as a kernel of its own on MFMA (tiled_mfma.hip): bf16, head_dim 128, keys-only or [K | V] filters
+// conv_w -> [bank][tap][slot][channel]
 hipError_t launch_pack_filters_per_tap(const StepArgs& a, int banks, void* wt, hipStream_t s);
-// raw logits fp32 [chains, M, T] (bias added), from the packed filters; keys-only or [K | V] input (a.conv_in)
-hipError_t launch_conv_logits_mfma(const StepArgs& a, const void* wt, float* logits, hipStream_t s);
+// n consecutive blocks of B tokens each (`tokens` in all: the last one may be shorter), the first one described by a
+// StepArgs, the others with a full cache; states state_stride elements apart, outputs out_stride floats apart
+struct LogitsWindow { int32_t n, B; int64_t tokens, state_stride, out_stride; };
+// raw logits fp32 [chains, M, ldw] (bias added), from the packed filters; keys-only or [K | V] input (a.conv_in)
+hipError_t launch_conv_logits_mfma(const StepArgs& a, const void* wt, float* logits, hipStream_t s,
+                                   const LogitsWindow* window = nullptr);
 bool conv_logits_mfma_supports(int dtype, int d, int conv_width);
 // bytes of the filters packed per tap [bank][tap][slot][channel]
 size_t packed_filter_bytes(int M, int conv_width, int conv_in, int banks);
@@ -266,8 +264,6 @@ hipError_t launch_mix_mfma(const StepArgs& a, const float* w, hipStream_t s);
 // Eq. 6 and Eq. 4a / 4b in one kernel, from raw logits [chains, M, ldw] into a.new_k / a.new_v (bf16)
 bool mixnorm_mfma_fits(const StepArgs& a, const float* logits);
 hipError_t launch_mixnorm_mfma(const StepArgs& a, const float* logits, hipStream_t s);
-// dX into d_k / d_cache_k (added) and dWc into d_conv_w (added), from the logit gradient in g.ws_w
-hipError_t launch_bwd_conv_mfma(const BwdArgs& g, int banks, void* ws, hipStream_t s);
 // the plain contractions of the pass (fp32 operands enter as two bf16 halves): same inputs,
 // outputs and workspace arrays as the fp32 kernels of backward_generic.hip they stand in for
 bool bwd_gemms_mfma_fit(const BwdArgs& g);                                 // widths multiples of 4, arrays 16-byte aligned
@@ -275,6 +271,54 @@ hipError_t launch_bwd_attn_scores_mfma(const BwdArgs& g, hipStream_t s);   // ws
 hipError_t launch_bwd_attn_grads_mfma(const BwdArgs& g, hipStream_t s);    // d_q; first contributions to dYk, dYv
 hipError_t launch_bwd_mix_dw_mfma(const BwdArgs& g, hipStream_t s);        // ws_dw
 hipError_t launch_bwd_mix_cols_mfma(const BwdArgs& g, hipStream_t s);      // Eq. 4 w.r.t. [K | V], added
+
+// ---- backward of Eq. 5, 6 and 4 on MFMA (bwd_conv_mfma.hip): bf16, head_dim 128, keys-only or [K | V] filters, odd
+// widths up to 31.  A window of n_blk consecutive compress blocks: `st` describes the first one (views at its first token,
+// the state before it, m, Bn), the others have a full cache.
+bool bwd_mfma_supports(int dtype, int d, int conv_in, int conv_width);
+struct BwdConvArgs {
+  StepArgs st;
+  int32_t n_blk, B, banks;
+  int64_t tokens;            // of all blocks: the last one may be shorter than B
+  int64_t state_stride;      // elements between the states
+  float* d_cache_k;          // gradient w.r.t. the state before the first block (added to), d_stride floats to the next
+  float* d_cache_v;          // block's, which is the gradient w.r.t. the state after this one
+  int64_t d_stride;
+  const float* d_new_k;      // gradient w.r.t. the state after the last block
+  const float* d_new_v;
+  float* d_k;                // added to, rows of the first block on, kv_chain floats between the heads
+  float* d_v;
+  int64_t kv_chain;
+  float* d_conv_w;           // added to
+  float* d_conv_b;
+  // workspace (bwd_conv_place)
+  uint16_t* wt;              // filters per tap
+  void* zero_page;           // 256 bytes of zeros
+  float* dwt;                // filter gradient per tap
+  float* logits;             // [block][chain][slot][ld]
+  uint16_t* dl;              // planes of the logit gradients and of the normalised rows, [block][chain][32 slots][P][64]
+  uint16_t* wn;
+  uint16_t* gsplit;          // gradient w.r.t. the new cache, [block][half][chain][slot][K | V]
+  int64_t logits_stride, plane_stride, gsplit_stride;     // between blocks, in elements of each
+  int32_t ld, P;
+};
+struct BwdConvLayout {       // byte offsets; the first three are per call, the rest per window
+  size_t wt, zero_page, dwt, per_call, logits, dl, wn, gsplit, total;
+  size_t logits_stride, plane_stride, gsplit_stride;
+  int ld, P;
+};
+// T: the most positions of a block (m + Bn); n_blk: blocks of a window
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk);
+void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws);
+// once per call: filters packed, sums and zeros cleared; at its end: the sums added to d_conv_w
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, hipStream_t s);
+hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s);
+// the logits of all blocks; then, from the last block to the first, rows and dx (part 0: cache rows; 1: the rows of the
+// blocks themselves, blocks blk0 .. blk0 + n_blk - 1; 2: both; `rows`: the most rows of one of them); then dw of all blocks
+hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s);
+hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s);
+hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s);
+hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s);
 
 // ---- measurement aid (peaks.hip): sustained bf16 MFMA rate of a bare loop and bandwidth of a plain
 // copy inside `scratch` (device, overwritten); synchronises the stream

@@ -2,18 +2,13 @@
 //  * Eq. 5 as a kernel of its own (keys-only or [K | V] filters, any odd width up to 31), used by the
 //    forward path for compressors the fused kernel is not built for and by the backward pass to
 //    recompute the logits;
-//  * the two gradients of Eq. 5 in the backward pass (head_dim = channels = 128, keys-only filters);
 //  * one batched GEMM kernel (bwd_gemm_k) whose instances are the seven plain contractions of the
 //    backward pass (attention and Eq. 4) and Eq. 4 of the unfused forward path.
 //
 //   logits[i, j]  = b[i] + sum_t sum_c Wc[i, c, t] X[j + t - p, c]
-//   dX[j, c]     += sum_t sum_i dW[i, j - t + p] Wc[i, c, t]
-//   dWc[i, c, t] += sum_j dW[i, j] X[j + t - p, c]
 //
-// Keys and filters are bf16 already, so the first contraction is exact up to the order of the
-// fp32 sums.  The gradient of the logits dW is fp32: it enters the other two as the sum of two
-// bf16 numbers (dW = hi + lo, lo = the rounding error of hi), two MFMAs per operand pair, which
-// keeps about 16 bits of it: the results agree with the fp32 kernels to the usual 1e-4.
+// Keys and filters are bf16 already, so the contraction is exact up to the order of the fp32 sums.
+// (The gradients of Eq. 5 are in bwd_conv_mfma.hip.)
 //
 // The Eq. 5 kernels: 256 threads, 128 x 128 outputs per workgroup (64 x 64 per wave, 2 x 2 MFMA
 // tiles of 32 x 32 x 16), operands staged through LDS in rows padded by 16 bytes; a tap is a
@@ -46,7 +41,7 @@ constexpr int kRow = 320;        // bytes of a 128-element row in LDS read by tr
                                  // that the four rows x 64 bytes half a wave touches fall on different banks
 constexpr int kRow64 = 144;      // bytes of a 64-element row in LDS
 constexpr int kTile = 128;       // outputs per workgroup, both ways
-constexpr int kChunk = 64;       // contraction chunk of the two gradient kernels
+constexpr int kChunk = 64;       // contraction chunk of the plain products and of Eq. 4
 
 __device__ __forceinline__ bf16x8 frag(const unsigned char* p) { return *(const bf16x8*)p; }
 // Fragment (lane: column c0 + l % 32; 8 contraction rows r0 + 8 (l / 32) ..) out of a row-major
@@ -107,58 +102,40 @@ __global__ void pack_filters_per_tap_k(const uint16_t* w, uint16_t* wt, int M, i
   }
 }
 
-// ---- dW fp32 [chain][slot][position] -> two bf16 halves, dW = hi + lo (lo = the rounding error of
-// hi), in both orientations: [chain][position][Mp] for dX, which contracts over the slots, and
-// [chain][slot][Tp] for dWc, which contracts over the positions (Mp, Tp = M, T rounded up to 64,
-// the tails zero, so that 16-byte loads of whole chunks stay inside)
-__global__ __launch_bounds__(kThreads) void bwd_split_dl_k(const float* dl, uint16_t* hi, uint16_t* lo,
-                                                           uint16_t* hi_s, uint16_t* lo_s, int M, int Mp, int Tn,
-                                                           int Tp) {
-  __shared__ float tile[64][65];
-  const int p0 = blockIdx.x * 64, s0 = blockIdx.y * 64, ch = blockIdx.z;
-  for (int e = threadIdx.x; e < 64 * 64; e += kThreads) {
-    const int s = e >> 6, p = e & 63;
-    const float v = (s0 + s < M && p0 + p < Tn) ? dl[((int64_t)ch * M + s0 + s) * Tn + p0 + p] : 0.f;
-    tile[s][p] = v;
-    if (s0 + s < M) {
-      const uint32_t h = bf16_rne(v), l = bf16_rne(v - bf16_val(h));
-      const int64_t o = ((int64_t)ch * M + s0 + s) * Tp + p0 + p;
-      hi_s[o] = (uint16_t)h;
-      lo_s[o] = (uint16_t)l;
-    }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 64 * 64; e += kThreads) {
-    const int p = e >> 6, s = e & 63;
-    if (p0 + p >= Tn) continue;
-    const float v = tile[s][p];
-    const uint32_t h = bf16_rne(v), l = bf16_rne(v - bf16_val(h));
-    const int64_t o = ((int64_t)ch * Tn + p0 + p) * Mp + s0 + s;
-    hi[o] = (uint16_t)h;
-    lo[o] = (uint16_t)l;
-  }
-}
-
 // ---- logits[i, j] (slots x positions, contraction over channels and taps)
 // LDS: X rows p0 - pad .. p0 + 127 + (KW - 1 - pad) once; per tap the (slot x channel) matrix of
 // 128 slots.  A = filters (rows: slots), B = keys (lane: position): a lane stores 32 consecutive
 // positions of one slot per instruction.  KV = 1: the convolution reads [K | V], 256 channels.
 // ST: 128 slots per workgroup, or 64 (a wave then has one block of 32 slots instead of two) where
 // 128 would leave compute units without a workgroup.
+// Block `blk` of a window of blocks (see LogitsWindow): its state, tokens and output
+__device__ __forceinline__ void window_block(StepArgs& a, const LogitsWindow& win, int blk, float*& out) {
+  if (blk > 0) a.m = a.M;
+  a.cache_k = (const uint16_t*)a.cache_k + blk * win.state_stride;
+  a.cache_v = (const uint16_t*)a.cache_v + blk * win.state_stride;
+  a.k.p = (const uint16_t*)a.k.p + (int64_t)blk * win.B * a.k.st;
+  a.v.p = (const uint16_t*)a.v.p + (int64_t)blk * win.B * a.v.st;
+  const int64_t left = win.tokens - (int64_t)blk * win.B;
+  a.Bn = (int)(left < win.B ? left : win.B);
+  out += blk * win.out_stride;
+}
 template <int KV, int ST>
 __global__ __launch_bounds__(KV ? 512 : 256, KV ? 1 : 2) void conv_logits_mfma_k(StepArgs a, const uint16_t* wt,
-                                                                                 float* out) {
+                                                                                 float* out, LogitsWindow win) {
   extern __shared__ __align__(16) unsigned char smem[];
   // 8 waves per compute unit either way: two workgroups of 4 (each wave 64 slots x 64 positions), or,
   // where the tiles of 256 channels leave LDS for one workgroup only, one of 8 (64 slots x 32 positions
   // per wave), so that every SIMD has a second wave to run while one waits for its fragments
   constexpr int NT = KV ? 512 : 256, PB = KV ? 1 : 2, SBW = ST / 64;
   constexpr int C = KV ? 2 * kD : kD, ROW = C * 2 + 16, CH16 = C / 8;   // channels, LDS row bytes, 16-byte chunks per row
+  const int ch = blockIdx.z % (a.batch * a.Hkv), b = ch / a.Hkv, hkv = ch % a.Hkv;
+  window_block(a, win, blockIdx.z / (a.batch * a.Hkv), out);
   const int KW = a.k_width, pad = (KW - 1) / 2, Tn = a.m + a.Bn;
   const int xrows = kTile + KW - 1;
   unsigned char* Xs = smem;
   unsigned char* Ws = smem + xrows * ROW;
-  const int p0 = blockIdx.x * kTile, s0 = blockIdx.y * ST, ch = blockIdx.z, b = ch / a.Hkv, hkv = ch % a.Hkv;
+  const int p0 = blockIdx.x * kTile, s0 = blockIdx.y * ST;
+  if (p0 >= Tn) return;                   // (a block of the window that is shorter than the others)
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int wy = w / (NT / 128), wx = w % (NT / 128);     // wave: slots 32 SBW wy .., positions 32 PB wx ..
   const uint16_t* wtb = wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0);
@@ -275,13 +252,16 @@ __device__ __forceinline__ void wait_loads_but() {
 }
 
 template <int NQ>
-__global__ __launch_bounds__(512, 1) void conv_logits_wide_k(StepArgs a, const uint16_t* wt, float* out) {
+__global__ __launch_bounds__(512, 1) void conv_logits_wide_k(StepArgs a, const uint16_t* wt, float* out, LogitsWindow win) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NT = 512, C = NQ * 64, SL = 256, PT = 256, WBUF = SL * 128;
+  const int ch = blockIdx.z % (a.batch * a.Hkv), b = ch / a.Hkv, hkv = ch % a.Hkv;
+  window_block(a, win, blockIdx.z / (a.batch * a.Hkv), out);
   const int KW = a.k_width, pad = (KW - 1) / 2, Tn = a.m + a.Bn, xrows = PT + KW - 1;
   unsigned char* Xs = smem + 3 * WBUF;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
-  const int p0 = blockIdx.x * PT, s0 = blockIdx.y * SL, ch = blockIdx.z, b = ch / a.Hkv, hkv = ch % a.Hkv;
+  const int p0 = blockIdx.x * PT, s0 = blockIdx.y * SL;
+  if (p0 >= Tn) return;                   // (a block of the window that is shorter than the others)
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int wy = w >> 1, wx = w & 1;                       // wave: slots 64 wy .., positions 128 wx ..
   const int w_uniform = __builtin_amdgcn_readfirstlane(w);
@@ -401,204 +381,6 @@ __global__ __launch_bounds__(512, 1) void conv_logits_wide_k(StepArgs a, const u
       }
     }
 }
-
-// ---- dX[j, c] (positions x channels, contraction over slots and taps)
-// LDS: per chunk of 64 slots the rows j0 + pad - (KW - 1) .. of dW^T (hi and lo), read row-shifted
-// per tap; per (chunk, tap) the 64 x 128 (slot x channel) filter matrix, read down its rows.
-// A = dW^T (rows: positions), B = filters (lane: channel).
-__global__ __launch_bounds__(kThreads, 2) void bwd_dx_mfma_k(BwdArgs g, const uint16_t* wt, const uint16_t* dhi,
-                                                             const uint16_t* dlo, int Mp) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const StepArgs& a = g.st;
-  const int KW = a.k_width, pad = (KW - 1) / 2, Tn = a.m + a.Bn;
-  const int drows = kTile + KW - 1;
-  unsigned char* Dh = smem;
-  unsigned char* Dl = Dh + drows * kRow64;
-  unsigned char* Ws = Dl + drows * kRow64;
-  const int p0 = blockIdx.x * kTile, ch = blockIdx.y, hkv = ch % a.Hkv;
-  // channel tile: 0 = the key channels; 1 = the value channels of [K | V] filters, whose gradient
-  // belongs to the value rows
-  const int c0 = blockIdx.z * kTile, C = a.conv_in ? 2 * kD : kD;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l31 = l & 31, lh = l >> 5, wy = w >> 1, wx = w & 1;
-  const uint16_t* wtb = wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + c0;
-  const int nsc = Mp / kChunk, nsteps = nsc * KW;
-
-  u32x4 wreg[4];
-  auto load_w = [&](int n) {
-    const int sc = n / KW, t = n % KW;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, row = item >> 4, c16 = item & 15, s = sc * kChunk + row;
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      wreg[i] = s < a.M ? *(const u32x4*)(wtb + ((int64_t)t * a.M + s) * C + c16 * 8) : z;
-    }
-  };
-  auto store_w = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, row = item >> 4, c16 = item & 15;
-      *(u32x4*)(Ws + row * kRow + c16 * 16) = wreg[i];
-    }
-  };
-  auto stage_d = [&](int sc) {            // all loads before the first store: one memory latency per tile
-    constexpr int DPER = ((kTile + 30) * 8 + kThreads - 1) / kThreads;
-    u32x4 vh[DPER], vl[DPER];
-#pragma unroll
-    for (int i = 0; i < DPER; ++i) {
-      const int item = tid + i * kThreads, row = item >> 3, c16 = item & 7, q = p0 + row - (KW - 1) + pad;
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      const bool in = item < drows * 8 && q >= 0 && q < Tn;
-      const int64_t o = ((int64_t)ch * Tn + (in ? q : 0)) * Mp + sc * kChunk + c16 * 8;
-      vh[i] = in ? *(const u32x4*)(dhi + o) : z;
-      vl[i] = in ? *(const u32x4*)(dlo + o) : z;
-    }
-#pragma unroll
-    for (int i = 0; i < DPER; ++i) {
-      const int item = tid + i * kThreads, row = item >> 3, c16 = item & 7;
-      if (item < drows * 8) {
-        *(u32x4*)(Dh + row * kRow64 + c16 * 16) = vh[i];
-        *(u32x4*)(Dl + row * kRow64 + c16 * 16) = vl[i];
-      }
-    }
-  };
-  f32x16 acc[2][2];                       // [position block][channel block]
-  zero_acc(acc);
-  load_w(0);
-  const int tro = tr_lane_offset(l, kRow);
-  for (int n = 0; n < nsteps; ++n) {
-    const int sc = n / KW, t = n % KW;
-    __syncthreads();
-    if (t == 0) stage_d(sc);
-    store_w();
-    if (n + 1 < nsteps) load_w(n + 1);
-    __syncthreads();
-    const int arow = wy * 64 + l31 - t + (KW - 1);
-    const unsigned char* dh = Dh + arow * kRow64 + lh * 16;
-    const unsigned char* dl = Dl + arow * kRow64 + lh * 16;
-    const unsigned char* wl = Ws + tro + (wx * 64) * 2;
-#pragma unroll
-    for (int kc = 0; kc < kChunk / 16; ++kc) {
-      const bf16x8 b0 = frag_tr(wl + kc * 16 * kRow, kRow), b1 = frag_tr(wl + kc * 16 * kRow + 64, kRow);
-#pragma unroll
-      for (int pb = 0; pb < 2; ++pb) {
-        const bf16x8 ah = frag(dh + pb * 32 * kRow64 + kc * 32), al = frag(dl + pb * 32 * kRow64 + kc * 32);
-        acc[pb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b0, acc[pb][0], 0, 0, 0);
-        acc[pb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b1, acc[pb][1], 0, 0, 0);
-        acc[pb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b0, acc[pb][0], 0, 0, 0);
-        acc[pb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b1, acc[pb][1], 0, 0, 0);
-      }
-    }
-  }
-  // every (position, channel) belongs to one lane: plain read-modify-write
-#pragma unroll
-  for (int pb = 0; pb < 2; ++pb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int p = p0 + wy * 64 + pb * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-      if (p >= Tn) continue;
-      float* row = p < a.m ? (c0 ? g.d_cache_v : g.d_cache_k) + ((int64_t)ch * a.M + p) * kD
-                           : (c0 ? g.d_v : g.d_k) + ch * g.kv_chain + (int64_t)(p - a.m) * kD;
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) row[wx * 64 + cb * 32 + l31] += acc[pb][cb][i];
-    }
-}
-
-// ---- dWc[i, c, t] for one tap (slots x channels, contraction over the positions of the
-// workgroup's chains).  LDS per chunk of 64 positions: the key rows shifted by the tap (read down
-// the rows) and the 128 x 64 tiles of the two halves of dW.
-// A = dW (rows: slots), B = keys (lane: channel).  Sums go to dwt [bank][tap][slot][channel] with
-// atomics (several workgroups, one per group of chains, share an output tile).
-__global__ __launch_bounds__(kThreads, 2) void bwd_dw_mfma_k(BwdArgs g, const uint16_t* dhi, const uint16_t* dlo,
-                                                             int Tp, float* dwt, int per_group) {
-  __shared__ __align__(16) unsigned char Xs[kChunk * kRow];
-  __shared__ __align__(16) unsigned char Dh[kTile * kRow64];
-  __shared__ __align__(16) unsigned char Dl[kTile * kRow64];
-  const StepArgs& a = g.st;
-  const int KW = a.k_width, pad = (KW - 1) / 2, Tn = a.m + a.Bn;
-  const int C = a.conv_in ? 2 * kD : kD, ctiles = C / kTile;
-  const int t = blockIdx.x, s0 = (blockIdx.y / ctiles) * kTile, c0 = (blockIdx.y % ctiles) * kTile;   // c0 = 128: value channels
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l31 = l & 31, lh = l >> 5, wy = w >> 1, wx = w & 1;
-  const bool per_head = a.w_head_stride != 0;
-  // the chains of this workgroup share a filter bank: consecutive chains when the bank is shared,
-  // consecutive batch entries of one kv head otherwise
-  const int hkv_fixed = per_head ? blockIdx.z % a.Hkv : 0;
-  const int first = (per_head ? blockIdx.z / a.Hkv : blockIdx.z) * per_group;
-  const int limit = per_head ? a.batch : a.batch * a.Hkv;
-  const int count = first + per_group <= limit ? per_group : limit - first;
-  const int nchunk = (Tn + kChunk - 1) / kChunk, nsteps = count * nchunk;
-
-  u32x4 xreg[4], hreg[4], lreg[4];
-  auto chain_of = [&](int n) {
-    const int e = first + n / nchunk;
-    return per_head ? e * a.Hkv + hkv_fixed : e;
-  };
-  auto load = [&](int n) {
-    const int ch = chain_of(n), b = ch / a.Hkv, hkv = ch % a.Hkv, pc = (n % nchunk) * kChunk;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, row = item >> 4, c16 = item & 15, q = pc + row + t - pad;
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      xreg[i] = (q >= 0 && q < Tn) ? *(const u32x4*)((c0 ? v_row(a, b, hkv, q) : x_row(a, b, hkv, q)) + c16 * 8) : z;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, s = s0 + (item >> 3), c16 = item & 7;
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      const int64_t o = ((int64_t)ch * a.M + s) * Tp + pc + c16 * 8;
-      hreg[i] = s < a.M ? *(const u32x4*)(dhi + o) : z;
-      lreg[i] = s < a.M ? *(const u32x4*)(dlo + o) : z;
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, row = item >> 4, c16 = item & 15;
-      *(u32x4*)(Xs + row * kRow + c16 * 16) = xreg[i];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int item = tid + i * kThreads, row = item >> 3, c16 = item & 7;
-      *(u32x4*)(Dh + row * kRow64 + c16 * 16) = hreg[i];
-      *(u32x4*)(Dl + row * kRow64 + c16 * 16) = lreg[i];
-    }
-  };
-  f32x16 acc[2][2];                       // [slot block][channel block]
-  zero_acc(acc);
-  if (nsteps > 0) load(0);
-  const int tro = tr_lane_offset(l, kRow);
-  for (int n = 0; n < nsteps; ++n) {
-    __syncthreads();
-    store();
-    if (n + 1 < nsteps) load(n + 1);
-    __syncthreads();
-    const unsigned char* xl = Xs + tro + (wx * 64) * 2;
-    const unsigned char* dh = Dh + (wy * 64 + l31) * kRow64 + lh * 16;
-    const unsigned char* dl = Dl + (wy * 64 + l31) * kRow64 + lh * 16;
-#pragma unroll
-    for (int kc = 0; kc < kChunk / 16; ++kc) {
-      const bf16x8 b0 = frag_tr(xl + kc * 16 * kRow, kRow), b1 = frag_tr(xl + kc * 16 * kRow + 64, kRow);
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        const bf16x8 ah = frag(dh + sb * 32 * kRow64 + kc * 32), al = frag(dl + sb * 32 * kRow64 + kc * 32);
-        acc[sb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b0, acc[sb][0], 0, 0, 0);
-        acc[sb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b1, acc[sb][1], 0, 0, 0);
-        acc[sb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b0, acc[sb][0], 0, 0, 0);
-        acc[sb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b1, acc[sb][1], 0, 0, 0);
-      }
-    }
-  }
-  float* o = dwt + ((int64_t)(per_head ? hkv_fixed : 0) * KW + t) * a.M * C + c0;
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int s = s0 + wy * 64 + sb * 32 + (i >> 2) * 8 + lh * 4 + (i & 3);
-      if (s >= a.M) continue;
-#pragma unroll
-      for (int cb = 0; cb < 2; ++cb) atomicAdd(o + (int64_t)s * C + wx * 64 + cb * 32 + l31, acc[sb][cb][i]);
-    }
-}
-
 
 // ---- Eq. 6 and Eq. 4a / 4b of the unfused forward path in one kernel: from raw logits fp32
 // [chain, M, ld] to the bf16 rows of the next cache, [new_K | new_V][i] = sum_j w[i, j] [Yk | Yv][j]
@@ -1069,24 +851,6 @@ Dims dims_of(const BwdArgs& g) {
   return s;
 }
 
-__global__ void bwd_zero_k(float* p, int64_t n) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-    p[e] = 0.f;
-}
-// d_conv_w[bank][slot][channel][tap] += dwt[bank][tap][slot][channel]
-__global__ void bwd_add_dw_k(const float* dwt, float* d_conv_w, int M, int C, int KW, int banks,
-                             int64_t w_head_stride) {
-  const int64_t n = (int64_t)banks * M * C * KW;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const int t = (int)(e % KW);
-    const int c = (int)((e / KW) % C);
-    const int s = (int)((e / ((int64_t)KW * C)) % M);
-    const int bank = (int)(e / ((int64_t)KW * C * M));
-    d_conv_w[bank * w_head_stride + ((int64_t)s * C + c) * KW + t] +=
-        dwt[(((int64_t)bank * KW + t) * M + s) * C + c];
-  }
-}
-
 int grid_for(int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 4096); }
 
 }  // namespace
@@ -1102,24 +866,6 @@ size_t packed_filter_bytes(int M, int conv_width, int conv_in, int banks) {
   return (size_t)banks * conv_width * M * (conv_in ? 2 * kD : kD) * 2;
 }
 
-static int padded_slots(int n) { return (n + kChunk - 1) / kChunk * kChunk; }   // also for positions
-
-BwdMfmaLayout bwd_mfma_layout(int batch, int Hkv, int M, int Tn, int conv_width, int conv_in, int banks) {
-  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const int C = conv_in ? 2 * kD : kD;
-  BwdMfmaLayout l;
-  l.wt = 0;
-  l.dhi = up((size_t)banks * conv_width * M * C * 2);
-  const size_t half = up((size_t)batch * Hkv * Tn * padded_slots(M) * 2);
-  l.dlo = l.dhi + half;
-  const size_t half_s = up((size_t)batch * Hkv * M * padded_slots(Tn) * 2);
-  l.dhi_s = l.dlo + half;
-  l.dlo_s = l.dhi_s + half_s;
-  l.dwt = l.dlo_s + half_s;
-  l.total = l.dwt + up((size_t)banks * conv_width * M * C * 4);
-  return l;
-}
-
 hipError_t launch_pack_filters_per_tap(const StepArgs& a, int banks, void* wt, hipStream_t s) {
   const int C = a.conv_in ? 2 * kD : kD;
   const int64_t n = (int64_t)banks * a.k_width * a.M * C;
@@ -1129,9 +875,8 @@ hipError_t launch_pack_filters_per_tap(const StepArgs& a, int banks, void* wt, h
 }
 
 template <int KV, int ST>
-static hipError_t launch_logits(const StepArgs& a, const void* wt, float* logits, hipStream_t s) {
+static hipError_t launch_logits(const StepArgs& a, const void* wt, float* logits, const LogitsWindow& win, int Tn, hipStream_t s) {
   constexpr int ROW = (KV ? 2 * kD : kD) * 2 + 16;
-  const int Tn = a.m + a.Bn;
   const int lds = (kTile + a.k_width - 1) * ROW + ST * ROW;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
@@ -1140,14 +885,13 @@ static hipError_t launch_logits(const StepArgs& a, const void* wt, float* logits
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((conv_logits_mfma_k<KV, ST>), dim3((Tn + kTile - 1) / kTile, (a.M + ST - 1) / ST, a.batch * a.Hkv),
-                     dim3(KV ? 512 : 256), lds, s, a, (const uint16_t*)wt, logits);
+  hipLaunchKernelGGL((conv_logits_mfma_k<KV, ST>), dim3((Tn + kTile - 1) / kTile, (a.M + ST - 1) / ST, a.batch * a.Hkv * win.n),
+                     dim3(KV ? 512 : 256), lds, s, a, (const uint16_t*)wt, logits, win);
   return hipGetLastError();
 }
 template <int NQ>
-static hipError_t launch_logits_wide(const StepArgs& a, const void* wt, float* logits, hipStream_t s) {
+static hipError_t launch_logits_wide(const StepArgs& a, const void* wt, float* logits, const LogitsWindow& win, int Tn, hipStream_t s) {
   constexpr int WBUFS = 3 * 256 * 128;    // the ring of filter tiles; behind it the rows of one channel quarter
-  const int Tn = a.m + a.Bn;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)conv_logits_wide_k<NQ>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1155,8 +899,8 @@ static hipError_t launch_logits_wide(const StepArgs& a, const void* wt, float* l
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL(conv_logits_wide_k<NQ>, dim3((Tn + 255) / 256, (a.M + 255) / 256, a.batch * a.Hkv), dim3(512),
-                     WBUFS + (256 + a.k_width - 1) * kRow64, s, a, (const uint16_t*)wt, logits);
+  hipLaunchKernelGGL(conv_logits_wide_k<NQ>, dim3((Tn + 255) / 256, (a.M + 255) / 256, a.batch * a.Hkv * win.n), dim3(512),
+                     WBUFS + (256 + a.k_width - 1) * kRow64, s, a, (const uint16_t*)wt, logits, win);
   return hipGetLastError();
 }
 // Three tile shapes.  64 and 128 slots give the same bits (every output element is the same sum in
@@ -1164,8 +908,9 @@ static hipError_t launch_logits_wide(const StepArgs& a, const void* wt, float* l
 // fp32 sums differ from theirs in rounding.  The debug option LOCOCO_OPT_LOGITS_TILES (64 | 128 | 256)
 // overrides the choice by grid size, for tests and measurements; 256 is ignored where there are at most
 // 128 slots.
-hipError_t launch_conv_logits_mfma(const StepArgs& a, const void* wt, float* logits, hipStream_t s) {
-  const int Tn = a.m + a.Bn, chains = a.batch * a.Hkv;
+hipError_t launch_conv_logits_mfma(const StepArgs& a, const void* wt, float* logits, hipStream_t s, const LogitsWindow* window) {
+  const LogitsWindow win = window ? *window : LogitsWindow{1, a.Bn, a.Bn, 0, 0};
+  const int Tn = win.n > 1 ? a.M + win.B : a.m + a.Bn, chains = a.batch * a.Hkv * win.n;
   const int64_t tiles256 = (int64_t)((Tn + 255) / 256) * ((a.M + 255) / 256) * chains;
   const int64_t tiles128 = (int64_t)((Tn + kTile - 1) / kTile) * ((a.M + kTile - 1) / kTile) * chains;
   // 256 x 256 where there are enough of those tiles for three quarters of the compute units;
@@ -1176,9 +921,11 @@ hipError_t launch_conv_logits_mfma(const StepArgs& a, const void* wt, float* log
     const int v = (int)debug_options().logits_tiles;
     if (v == 64 || v == 128 || (v == 256 && a.M > kTile)) shape = v;
   }
-  if (shape == 256) return a.conv_in ? launch_logits_wide<4>(a, wt, logits, s) : launch_logits_wide<2>(a, wt, logits, s);
-  if (shape == 64) return a.conv_in ? launch_logits<1, 64>(a, wt, logits, s) : launch_logits<0, 64>(a, wt, logits, s);
-  return a.conv_in ? launch_logits<1, 128>(a, wt, logits, s) : launch_logits<0, 128>(a, wt, logits, s);
+  if (shape == 256)
+    return a.conv_in ? launch_logits_wide<4>(a, wt, logits, win, Tn, s) : launch_logits_wide<2>(a, wt, logits, win, Tn, s);
+  if (shape == 64)
+    return a.conv_in ? launch_logits<1, 64>(a, wt, logits, win, Tn, s) : launch_logits<0, 64>(a, wt, logits, win, Tn, s);
+  return a.conv_in ? launch_logits<1, 128>(a, wt, logits, win, Tn, s) : launch_logits<0, 128>(a, wt, logits, win, Tn, s);
 }
 
 // The plain contractions take whole groups of four: every row width (d, 2 d, T) a multiple of 4
@@ -1274,50 +1021,6 @@ hipError_t launch_bwd_mix_cols_mfma(const BwdArgs& g, hipStream_t s) {
                      OpG<true>{dm, g.d_new_k, g.d_new_v, a.protect, a.protect_stride, true},
                      OutGrad<true>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 2}, dm.Tn, 2 * a.d, a.M,
                      a.batch * a.Hkv, s);
-}
-
-hipError_t launch_bwd_conv_mfma(const BwdArgs& g, int banks, void* ws, hipStream_t s) {
-  const StepArgs& a = g.st;
-  const int Tn = a.m + a.Bn, chains = a.batch * a.Hkv, Mp = padded_slots(a.M);
-  const BwdMfmaLayout l = bwd_mfma_layout(a.batch, a.Hkv, a.M, Tn, a.k_width, a.conv_in, banks);
-  const int C = a.conv_in ? 2 * kD : kD, ctiles = C / kTile;
-  const uint16_t* wt = (const uint16_t*)((char*)ws + l.wt);
-  uint16_t* dhi = (uint16_t*)((char*)ws + l.dhi);
-  uint16_t* dlo = (uint16_t*)((char*)ws + l.dlo);
-  uint16_t* dhi_s = (uint16_t*)((char*)ws + l.dhi_s);
-  uint16_t* dlo_s = (uint16_t*)((char*)ws + l.dlo_s);
-  const int Tp = padded_slots(Tn);
-  float* dwt = (float*)((char*)ws + l.dwt);
-  // (the split also writes the zero tail, slots M .. Mp, which the 16-byte loads of the dX kernel read)
-  hipLaunchKernelGGL(bwd_split_dl_k, dim3((Tn + 63) / 64, Mp / 64, chains), dim3(kThreads), 0, s, g.ws_w, dhi, dlo,
-                     dhi_s, dlo_s, a.M, Mp, Tn, Tp);
-  {
-    const int lds = 2 * (kTile + a.k_width - 1) * kRow64 + kChunk * kRow;
-    static bool attr_set = false;
-    if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute((const void*)bwd_dx_mfma_k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         2 * (kTile + 30) * kRow64 + kChunk * kRow);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(bwd_dx_mfma_k, dim3((Tn + kTile - 1) / kTile, chains, ctiles), dim3(kThreads), lds, s, g, wt,
-                       dhi, dlo, Mp);
-  }
-  const int64_t nw = (int64_t)banks * a.k_width * a.M * C;
-  hipLaunchKernelGGL(bwd_zero_k, dim3(grid_for(nw)), dim3(256), 0, s, dwt, nw);
-  {
-    // chains per workgroup: enough workgroups to fill the chip several times over, as few atomics as that allows
-    const int entries = banks > 1 ? a.batch : chains;
-    const int tiles = a.k_width * ((a.M + kTile - 1) / kTile) * ctiles * (banks > 1 ? a.Hkv : 1);
-    int per_group = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)tiles * entries / 1024));
-    const int groups = (entries + per_group - 1) / per_group;
-    hipLaunchKernelGGL(bwd_dw_mfma_k,
-                       dim3(a.k_width, ((a.M + kTile - 1) / kTile) * ctiles, groups * (banks > 1 ? a.Hkv : 1)),
-                       dim3(kThreads), 0, s, g, dhi_s, dlo_s, Tp, dwt, per_group);
-  }
-  hipLaunchKernelGGL(bwd_add_dw_k, dim3(grid_for(nw)), dim3(256), 0, s, dwt, g.d_conv_w, a.M, C, a.k_width, banks,
-                     a.w_head_stride);
-  return hipGetLastError();
 }
 
 }  // namespace lococo

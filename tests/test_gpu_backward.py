@@ -463,3 +463,34 @@ def test_scan_backward_on_the_matrix_cores_against_fp32_arithmetic(case):
         err = float((x.double() - y.double()).norm() / y.double().norm().clamp_min(1e-30))
         print(name, f"{err:.1e}")
         assert err < 2e-3, (name, err)
+
+
+@pytest.mark.parametrize("case", [
+    dict(B=128, M=128, conv_width=31),                                           # T = 256: one tile of positions a wave
+    dict(B=129, M=128, conv_width=1, norm=1),                                    # 257: two
+    dict(B=256, M=256, conv_width=5, conv_in=1),                                 # 512
+    dict(B=257, M=256, conv_width=15, n_kv_heads=1),                             # 513: four
+    dict(B=512, M=513, conv_width=3),                                            # 1025: the positions are walked twice
+    dict(B=1030, M=1020, conv_width=3, norm=1),                                  # 2050, slots that are no multiple of 32
+], ids=str)
+def test_step_backward_at_the_edges_of_the_row_kernel(case):
+    """One compress step, the matrix cores (impl = AUTO) against the fp32 vector kernels (impl = GENERIC) on the same
+    inputs, at the numbers of positions where the kernel that holds a row in registers changes its form.  Both sides see
+    the same operands; what enters a product as two bf16 halves keeps 16 bits: the 2e-4 of the sweep above."""
+    w = inputs.Workload(**{**dict(name="bwdrows", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=2, head_dim=128, L=case["B"],
+                                  seed=41, conv_gain=3.0), **case})
+    rng = np.random.default_rng(12)
+    q, k, v = inputs.qkv(w)
+    cw, _ = inputs.conv_filters(w)
+    chains = (w.batch, w.n_kv_heads, w.M, w.head_dim)
+    ck = torch.as_tensor(rng.standard_normal(chains) * 0.5).to(w.torch_dtype)
+    cv = torch.as_tensor(rng.standard_normal(chains) * 0.5).to(w.torch_dtype)
+    d_o, gk, gv = rng.standard_normal(q.shape), rng.standard_normal(chains), rng.standard_normal(chains)
+    out = []
+    for impl in (0, 1):
+        dW = torch.zeros(cw.shape, dtype=torch.float32, device="cuda")
+        r = _gpu_step_backward(w, lb.config_for(w, impl=impl), q, k, v, cw, None, ck, cv, w.M, d_o, gk, gv, dW, None)
+        out.append({**r, "d_conv_w": dW.cpu().numpy()})
+    for n in out[0]:
+        assert np.isfinite(out[0][n]).all(), n
+        assert _rel(out[0][n], out[1][n]) < 2e-4, (n, _rel(out[0][n], out[1][n]))
