@@ -1491,12 +1491,13 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
           HIP_TRY(launch_step_backward_generic(cfg->dtype, g, true, s), "clearing the rows of empty slots");
         }
         HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
+        const bool defer = bwd_conv_defers_blocks(c);
         for (int i = c.n_blk - 1; i >= 0; --i) {
           const lococo_seg& sg = plan[(size_t)(w_steps + i)];
           HIP_TRY(launch_bwd_conv_rows(c, i, sg.len_before + sg.len, s), "row gradient launch");
-          HIP_TRY(launch_bwd_conv_dx(c, i, 1, 0, sg.len_before, s), "input gradient launch");
+          HIP_TRY(launch_bwd_conv_dx(c, i, 1, defer ? 0 : 2, sg.len_before + (defer ? 0 : sg.len), s), "input gradient launch");
         }
-        HIP_TRY(launch_bwd_conv_dx(c, 0, c.n_blk, 1, B, s), "input gradient launch");
+        if (defer) HIP_TRY(launch_bwd_conv_dx(c, 0, c.n_blk, 1, B, s), "input gradient launch");
         HIP_TRY(launch_bwd_conv_dw(c, s), "filter gradient launch");
         if (w_steps == 0 || plan[(size_t)(w_steps - 1)].branch == 0) HIP_TRY(launch_bwd_conv_end(c, s), "filter gradient launch");
         gk = c.d_cache_k;

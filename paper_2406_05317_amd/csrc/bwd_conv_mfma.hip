@@ -28,6 +28,14 @@ typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;      //
 __device__ __forceinline__ void gather_to_lds(const unsigned char* p, uint32_t lds_addr) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "{m0}"(lds_addr), "v"(p) : "memory");
 }
+// the same from a uniform address and a 32-bit offset per lane
+__device__ __forceinline__ void gather_to_lds(const unsigned char* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds_addr), "v"(voff), "s"(base) : "memory");
+}
+// and from a buffer: offset `voff` per lane and `soff` for all
+__device__ __forceinline__ void load_to_lds_at(const u32x4& rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "{m0}"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
 // every wave has finished reading and its awaited loads have landed (waited for by hand)
 __device__ __forceinline__ void barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -36,6 +44,9 @@ __device__ __forceinline__ void barrier() {
 // Rows of 128 bytes in LDS (8 cells): chunk c of row r sits in cell c ^ pswz(r).  Sixteen consecutive rows put one chunk on
 // sixteen different cells of 256 bytes; four rows from a multiple of four put four consecutive chunks there.
 __device__ __forceinline__ int pswz(int r) { return (((r >> 1) & 1) << 2) | ((r >> 2) & 3); }
+
+struct Yes { static constexpr bool value = true; };
+struct No { static constexpr bool value = false; };
 
 struct Block { int m, Bn, T; const uint16_t* ck; const uint16_t* cv; const uint16_t* k; const uint16_t* v; };
 __device__ __forceinline__ Block block_of(const BwdConvArgs& g, int blk) {
@@ -51,31 +62,42 @@ __device__ __forceinline__ Block block_of(const BwdConvArgs& g, int blk) {
   b.v = (const uint16_t*)a.v.p + (int64_t)blk * g.B * a.v.st;
   return b;
 }
-// row j of [cache ; block] of a chain, keys or values
-__device__ __forceinline__ const uint16_t* x_row(const StepArgs& a, const Block& x, int ch, int j, bool val) {
-  if (j < x.m) return (val ? x.cv : x.ck) + ((int64_t)ch * a.M + j) * kD;
-  const View& s = val ? a.v : a.k;
-  return (val ? x.v : x.k) + (ch / a.Hkv) * s.sb + (ch % a.Hkv) * s.sh + (int64_t)(j - x.m) * s.st;
-}
+// gradient w.r.t. the state after a block: that of the next block's state
 __device__ __forceinline__ const float* grad_new(const BwdConvArgs& g, int blk, bool val) {
   if (blk + 1 < g.n_blk) return (val ? g.d_cache_v : g.d_cache_k) + (blk + 1) * g.d_stride;
   return val ? g.d_new_v : g.d_new_k;
 }
 
-// a value reduced over the 32 lanes of a half-wave
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
+// v[i] (i < 16) reduced over the 32 lanes of each half of a wave: every step halves the values a lane still carries, so
+// that lane l31 ends with the result of i = l31 / 2.
 template <bool MAX>
-__device__ __forceinline__ float over32(float v) {
+__device__ __forceinline__ float over32(const f32x16& v, int l31) {
   auto op = [](float x, float y) { return MAX ? fmaxf(x, y) : x + y; };
-  v = op(v, dpp<0xB1>(v));              // quad_perm [1,0,3,2]
-  v = op(v, dpp<0x4E>(v));              // quad_perm [2,3,0,1]
-  v = op(v, dpp<0x141>(v));             // row_half_mirror
-  v = op(v, dpp<0x140>(v));             // row_mirror
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  float a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {            // lanes 16 .. 31 keep i + 8
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    a[i] = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  const bool b3 = l31 & 8, b2 = l31 & 4, b1 = l31 & 2;
+  float b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {            // row_ror:8, the lane 8 away
+    const float keep = b3 ? a[i + 4] : a[i], give = b3 ? a[i] : a[i + 4];
+    b[i] = op(keep, dpp<0x128>(give));
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {            // row_half_mirror: the other four of eight lanes
+    const float keep = b2 ? b[i + 2] : b[i], give = b2 ? b[i] : b[i + 2];
+    c[i] = op(keep, dpp<0x141>(give));
+  }
+  const float keep = b1 ? c[1] : c[0], give = b1 ? c[0] : c[1];
+  const float d = op(keep, dpp<0x4E>(give));   // quad_perm [2,3,0,1]
+  return op(d, dpp<0xB1>(d));                  // quad_perm [1,0,3,2]
 }
 // exp(x), x <= 0: the product with log2 e carried to twice the working precision (v_exp_f32 is exact to one unit)
 __device__ __forceinline__ float exp_neg(float x) {
@@ -88,7 +110,7 @@ __device__ __forceinline__ float exp_neg(float x) {
 // ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
 // each; the rows of a step stay in registers from the logits to dl.  MULTI: more positions than that: they are walked
 // twice in chunks, first for the row sums alone.
-template <int NT, bool MULTI>
+template <int NT, bool MULTI, int NORM>
 __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   const StepArgs& a = g.st;
   __shared__ __align__(16) unsigned char Gs[2][2][32 * 256];     // [half][keys, values]: tiles of 32 rows (see swz)
@@ -100,10 +122,39 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const float* gk = grad_new(g, blk, false) + (int64_t)ch * a.M * kD;
   const float* gv = grad_new(g, blk, true) + (int64_t)ch * a.M * kD;
+  const uint32_t* prot = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
   uint16_t* gsp = g.gsplit + (int64_t)blk * g.gsplit_stride;
+  // the logits (row i of the tile: slot s0 + 8 (i / 4) + 4 lh + i % 4; this lane: a position) of a chunk; a position that
+  // does not count has the logit -inf.  (Rows of a slot past M hold whatever follows: they end as zeros below.)
+  const float* lg = g.logits + blk * g.logits_stride + ((int64_t)ch * a.M + s0) * g.ld;
+  f32x16 acc[NT], xl[NT];
+  auto fetch = [&](int pc) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = pc + (w + 8 * n) * 32;
+      if (p0 < x.T) {
+        const float* p = lg + (int64_t)(lh * 4) * g.ld + p0 + l31;         // (rows are padded to whole tiles)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xl[n][i] = p[(int64_t)((i >> 2) * 8 + (i & 3)) * g.ld];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xl[n][i] = -INFINITY;
+      }
+    }
+  };
+  auto mask = [&](int pc) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int pos = pc + (w + 8 * n) * 32 + l31;
+      bool out = pos >= x.T;
+      if (prot && pos < x.m) out = (prot[pos >> 5] >> (pos & 31)) & 1u;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) xl[n][i] = out ? -INFINITY : xl[n][i];
+    }
+  };
+  fetch(0);
   // slots that mix: all live ones but the protected
   uint32_t mixing = a.M - s0 >= 32 ? 0xffffffffu : (1u << (a.M - s0)) - 1u;
-  const uint32_t* prot = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
   if (prot && s0 < x.m) {
     uint32_t p = prot[sb];
     if (x.m - s0 < 32) p &= (1u << (x.m - s0)) - 1u;
@@ -139,38 +190,39 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   int ga[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) ga[ks] = l31 * 256 + (((2 * ks + lh) ^ swz(l31)) << 4);
-  const float* lg = g.logits + blk * g.logits_stride + (int64_t)ch * a.M * g.ld;
+  auto entry = [&](int p0, int val) {
+    const int j = p0 + l31 < x.T ? p0 + l31 : x.T - 1;
+    const uint16_t* c = (val ? x.cv : x.ck) + ((int64_t)ch * a.M + j) * kD;
+    const View& st = val ? a.v : a.k;
+    const uint16_t* q = (val ? x.v : x.k) + (ch / a.Hkv) * st.sb + hkv * st.sh + (int64_t)(j - x.m) * st.st;
+    return (j < x.m ? c : q) + lh * 8;
+  };
+  bf16x8 f0[2][8];                          // the first tile's, in flight while g is staged
+#pragma unroll
+  for (int val = 0; val < 2; ++val) {
+    const uint16_t* row = entry(w * 32, val);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) f0[val][ks] = *(const bf16x8*)(row + ks * 16);
+  }
   __syncthreads();
 
-  f32x16 acc[NT], xl[NT];
-  // the logits (row i of the tile: slot s0 + 8 (i / 4) + 4 lh + i % 4; this lane: position) and G of tile n of a chunk;
-  // a position that does not count has the logit -inf
-  auto fetch = [&](int pc) {
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      const int p0 = pc + (w + 8 * n) * 32, pos = p0 + l31;
-      const bool out = pos >= x.T || (prot && pos < x.m && ((prot[pos >> 5] >> (pos & 31)) & 1u));
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int r = s0 + (i >> 2) * 8 + lh * 4 + (i & 3);
-        const float v = p0 < x.T ? lg[(int64_t)(r < a.M ? r : a.M - 1) * g.ld + (pos < x.T ? pos : 0)] : 0.f;
-        xl[n][i] = out ? -INFINITY : v;
-      }
-    }
-  };
-  auto contract = [&](int pc) {
+  auto contract = [&](int pc, bool have_first) {
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const int p0 = pc + (w + 8 * n) * 32;
       acc[n] = zero16();
       if (p0 >= x.T) continue;
-      const int j = p0 + l31 < x.T ? p0 + l31 : x.T - 1;
 #pragma unroll
       for (int val = 0; val < 2; ++val) {
-        const uint16_t* row = x_row(a, x, ch, j, val) + lh * 8;
         bf16x8 fx[8];
+        if (n == 0 && have_first) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) fx[ks] = *(const bf16x8*)(row + ks * 16);
+          for (int ks = 0; ks < 8; ++ks) fx[ks] = f0[val][ks];
+        } else {
+          const uint16_t* row = entry(p0, val);
+#pragma unroll
+          for (int ks = 0; ks < 8; ++ks) fx[ks] = *(const bf16x8*)(row + ks * 16);
+        }
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
           acc[n] = mfma32(*(const bf16x8*)(Gs[0][val] + ga[ks]), fx[ks], acc[n]);
@@ -180,12 +232,10 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     }
   };
   // the 16 rows' values of a lane, combined over the lanes and the waves; the result of row r lands with thread r
-  auto over_waves = [&](const f32x16& v, int which, bool mx) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float t = mx ? over32<true>(v[i]) : over32<false>(v[i]);
-      if (l31 == 0) red[which][w][(i >> 2) * 8 + lh * 4 + (i & 3)] = t;
-    }
+  auto over_waves = [&](const f32x16& v, int which, auto mx) {
+    const float t = over32<decltype(mx)::value>(v, l31);
+    const int i = l31 >> 1;
+    red[which][w][(i >> 2) * 8 + lh * 4 + (i & 3)] = t;          // (two lanes hold the same)
   };
   auto collect = [&](int which, bool mx) {
     float t = red[which][0][tid];
@@ -204,13 +254,13 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   // logits -> unnormalised weights, and the sums of a chunk on top of (sum, dot) of thread r < 32
   float ref = -INFINITY, sum = 0.f, dot = 0.f;
   auto weigh = [&]() {
-    if (a.norm == 0) {
+    if (NORM == 0) {
       f32x16 mx = xl[0];
 #pragma unroll
       for (int n = 1; n < NT; ++n)
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx[i] = fmaxf(mx[i], xl[n][i]);
-      over_waves(mx, 0, true);
+      over_waves(mx, 0, Yes{});
       __syncthreads();
       if (tid < 32) {
         const float t = fmaxf(ref, collect(0, true));
@@ -229,13 +279,13 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float e = a.norm == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
+        const float e = NORM == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
         xl[n][i] = e;
         ps[i] += e;
         pd[i] = fmaf(e, acc[n][i], pd[i]);
       }
-    over_waves(ps, 0, false);
-    over_waves(pd, 1, false);
+    over_waves(ps, 0, No{});
+    over_waves(pd, 1, No{});
     __syncthreads();
     if (tid < 32) {
       sum += collect(0, false);
@@ -244,7 +294,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   };
   auto publish = [&]() {
     if (tid < 32) {
-      const float inv = 1.0f / (a.norm == 0 ? sum : sum + a.eps);
+      const float inv = 1.0f / (NORM == 0 ? sum : sum + a.eps);
       row_s[1][tid] = inv;
       row_s[2][tid] = dot * inv;
     }
@@ -273,10 +323,10 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
             const int i = (qp * 2 + q) * 4 + e, slot = (qp * 2 + q) * 8 + lh * 4 + e;
             const bool on = (mixing >> slot) & 1u;
             const float nn = xl[n][i] * inv[i], dG = acc[n][i] - r[i];
-            const float d = a.norm == 0 ? (xl[n][i] > 0.f ? nn * dG : 0.f) : (xl[n][i] > 0.f ? dG * inv[i] : 0.f);
+            const float d = NORM == 0 ? nn * dG : (xl[n][i] > 0.f ? dG * inv[i] : 0.f);
             vn[e] = on ? nn : 0.f;
             vd[e] = on ? d : 0.f;
-            bsum[i] += pos < x.T ? vd[e] : 0.f;
+            bsum[i] += vd[e];                // (zero where the position does not count)
           }
           split2(vn[0], vn[1], nh[q][0], nl[q][0]);
           split2(vn[2], vn[3], nh[q][1], nl[q][1]);
@@ -288,7 +338,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
           const auto t0 = __builtin_amdgcn_permlane32_swap(v[0][0], v[1][0], false, false);
           const auto t1 = __builtin_amdgcn_permlane32_swap(v[0][1], v[1][1], false, false);
           const u32x4 out = {t0[0], t1[0], t0[1], t1[1]};
-          if (pos < x.T) *(u32x4*)at = out;
+          *(u32x4*)at = out;                // (positions T .. of the last tile: zeros, which bwd_dw_k reads)
         };
         put(pn + o + qp * 16, nh);
         put(pn + o + qp * 16 + 32, nl);
@@ -298,54 +348,55 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     }
   };
   if (!MULTI) {
-    fetch(0);
-    contract(0);
+    contract(0, true);
+    mask(0);
     weigh();
     publish();
     finish(0);
   } else {
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
-      fetch(pc);
-      contract(pc);
+      if (pc) fetch(pc);
+      contract(pc, false);
+      mask(pc);
       weigh();
       __syncthreads();
     }
     publish();
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
       fetch(pc);
-      contract(pc);
-      if (a.norm == 0) rows(0);
+      contract(pc, false);
+      mask(pc);
+      if (NORM == 0) rows(0);
 #pragma unroll
       for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) xl[n][i] = a.norm == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
+        for (int i = 0; i < 16; ++i) xl[n][i] = NORM == 0 ? exp_neg(xl[n][i] - rv[i]) : fmaxf(xl[n][i], 0.f);
       finish(pc);
     }
   }
   if (g.d_conv_b) {
     __syncthreads();
-    over_waves(bsum, 0, false);
+    over_waves(bsum, 0, No{});
     __syncthreads();
     if (tid < 32 && ((mixing >> tid) & 1u)) atomicAdd(g.d_conv_b + hkv * a.b_head_stride + s0 + tid, collect(0, false));
   }
 }
 
 // ---- dX: a workgroup per (PT positions, 128 key or value columns) of a chain and block, contraction over the slots in
-// chunks of 64: for each chunk a stage per tap (dl, row-shifted, times that tap's filters) and two with n (times the two
-// halves of g).  The eight waves split each chunk four ways (16 slots each) and the outputs two ways; the four partial
-// sums meet in LDS at the end.  Everything arrives by loads that write LDS directly: the 64 x 128 right-hand matrices two
-// stages ahead in a ring of three, the plane rows of the next chunk (with their halo) while one is worked on.  Rows
-// outside come from a page of zeros.
+// chunks of 64.  A chunk is a phase with dl (one product per tap: its rows, shifted, times that tap's filters) and one with
+// n (times the two halves of g), worked through in pairs of products with one barrier each.  The eight waves split each
+// chunk four ways (16 slots each) and the outputs two ways; the four partial sums meet in LDS at the end.  Everything
+// arrives by loads that write LDS directly: the next pair's 64 x 128 right-hand matrices and the next phase's plane rows
+// (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
+constexpr int kDxW = 2 * 64 * 256;                                 // two right-hand matrices
 template <int PT>
 __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : 2;     // 32 x 32 output blocks of a wave
-  constexpr int DR = PT + 32, ND = DR / 32;                        // rows of a plane tile; its requests per wave
-  constexpr int WB = 64 * 256, DB = 2 * DR * 128;
+  constexpr int DR = PT + 32, ND = DR / 32, DB = 2 * DR * 128;     // rows of a plane tile; its requests per wave; bytes
   const StepArgs& a = g.st;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
-  unsigned char* Ds = smem + 3 * WB;
   const int blk = blk0 + blockIdx.z / 2, val = blockIdx.z % 2, ch = blockIdx.y, hkv = ch % a.Hkv;
   const Block x = block_of(g, blk);
   const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
@@ -354,47 +405,53 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   const int kq = w & 3, wo = w >> 2;
   const int KW = a.k_width, pad = (KW - 1) / 2, C = a.conv_in ? 2 * kD : kD, tiles = (a.M + 31) / 32;
   const bool taps = val == 0 || a.conv_in;
-  const int nsc = (a.M + 63) / 64;
-  const unsigned char* zero = (const unsigned char*)g.zero_page + (l & 15) * 16;
-  const unsigned char* wt = (const unsigned char*)(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + (val ? kD : 0));
-  const unsigned char* gs = (const unsigned char*)(g.gsplit + blk * g.gsplit_stride + (int64_t)ch * a.M * (2 * kD) + (val ? kD : 0));
-  const int64_t gs_lo = (int64_t)a.batch * a.Hkv * a.M * (2 * kD) * 2;
-  const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
-  const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+  const int nsc = (a.M + 63) / 64, npair = (KW + 1) / 2;
 
-  // a stage: tap t of dl of chunk sc (ph 0), or half t of g with n (ph 1)
-  struct Stage { int sc, ph, t; };
-  auto next = [&](Stage s) {
-    if (++s.t == (s.ph ? 2 : KW)) {
-      s.t = 0;
-      if (s.ph) { ++s.sc; s.ph = taps ? 0 : 1; }
-      else s.ph = 1;
-    }
-    return s;
-  };
-  auto request_w = [&](const Stage& s, int buf) {
+  // right-hand matrices of a pair: waves 0 .. 3 request the first, 4 .. 7 the second; a row past M is the last one again
+  // (its partner in the planes is zero)
+  const u32x4 rw = make_rsrc(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + (val ? kD : 0),
+                             (uint32_t)((int64_t)KW * a.M * C * 2) - (val ? 256 : 0));
+  const u32x4 rg = make_rsrc(g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) +
+                                 (val ? kD : 0), (uint32_t)(a.M * 512) - (val ? 256 : 0));
+  // offsets of this lane's cells of a chunk: row r times the row stride plus the cell's chunk
+  uint32_t wvo[4], gvo[4];
+  auto enter_chunk = [&](int sc) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4), slot = s.sc * 64 + r, chunk = (l & 15) ^ swz(r);
-      const unsigned char* p = s.ph == 0 ? wt + ((int64_t)s.t * a.M + slot) * (C * 2) + chunk * 16
-                                         : gs + (s.t ? gs_lo : 0) + (int64_t)slot * 512 + chunk * 16;
-      gather_to_lds(slot < a.M ? p : zero, lds0 + buf * WB + r4 * 1024);
+    for (int i = 0; i < 4; ++i) {
+      const int r4 = (kq * 4 + i) * 4 + (l >> 4), r = min(r4, a.M - 1 - sc * 64), c = ((l & 15) ^ swz(r4)) << 4;
+      wvo[i] = r * (C * 2) + c;
+      gvo[i] = r * 512 + c;
     }
   };
-  auto request_d = [&](int sc, int ph, int buf) {
-    const unsigned char* base = ph ? pn : pl;
-    const int q0 = ph ? p0 : p0 - (KW - 1) + pad;
+  const uint32_t wdst = __builtin_amdgcn_readfirstlane(lds0 + wo * (64 * 256) + kq * 4096);
+  auto request_taps = [&](uint32_t soff, int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_to_lds_at(rw, wdst + buf * kDxW + i * 1024, wvo[i], soff);
+  };
+  auto request_g = [&](uint32_t soff, int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_to_lds_at(rg, wdst + buf * kDxW + i * 1024, gvo[i], soff);
+  };
+  // plane rows: offsets inside the two 32-slot planes of a chunk, of dl (with the halo) and of n
+  uint32_t dvo[2][ND];
+#pragma unroll
+  for (int ph = 0; ph < 2; ++ph)
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
-      const int idx = w * ND + i, ra = idx * 8, sbi = ra >= DR ? 1 : 0, r = ra - sbi * DR + (l >> 3), q = q0 + r;
-      const int sb = sc * 2 + sbi, chunk = (l & 7) ^ pswz(r);
-      const bool in = q >= 0 && q < x.T && sb < tiles;
-      gather_to_lds(in ? base + ((int64_t)sb * g.P + q) * 128 + chunk * 16 : zero, lds0 + 3 * WB + buf * DB + idx * 1024);
+      const int ra = (w * ND + i) * 8, sbi = ra >= DR ? 1 : 0, r = ra - sbi * DR + (l >> 3);
+      const int q = (ph ? p0 : p0 - (KW - 1) + pad) + r;
+      dvo[ph][i] = q >= 0 && q < x.T ? (uint32_t)((sbi * g.P + q) * 128 + (((l & 7) ^ pswz(r)) << 4)) : 0x80000000u;
     }
+  const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+  const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
+  const uint32_t ddst = __builtin_amdgcn_readfirstlane(lds0 + 2 * kDxW + w * ND * 1024);
+  auto request_d = [&](int sc, const unsigned char* plane, const uint32_t (&vo)[ND], int buf) {
+    const u32x4 r = make_rsrc(plane + (int64_t)sc * 2 * g.P * 128, (uint32_t)(min(2, tiles - sc * 2) * g.P * 128));
+#pragma unroll
+    for (int i = 0; i < ND; ++i) load_to_lds_at(r, ddst + buf * DB + i * 1024, vo[i], 0u);
   };
   const int row0 = (PT == 128 ? wo * 64 : 0) + l31, col0 = PT == 128 ? 0 : wo * 64;
   const int dchunk = (kq & 1) * 2 + lh;
-  const unsigned char* dbase = Ds + (kq >> 1) * DR * 128;
   int wa[CB][2];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
@@ -410,50 +467,85 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = zero16();
 
-  Stage s = {0, taps ? 0 : 1, 0}, s2 = next(s);
-  request_d(s.sc, s.ph, 0);
-  request_w(s, 0);
-  request_w(s2, 1);                       // (every phase has a successor or two stages: stage 1 exists)
-  s2 = next(s2);
-  wait_loads<0>();
-  barrier();
-  int wb = 0, db = 0;
-  while (s.sc < nsc) {
-    if (s.t == 0) {                       // the plane rows of the next phase
-      const int sc1 = s.ph ? s.sc + 1 : s.sc, ph1 = s.ph ? (taps ? 0 : 1) : 1;
-      if (sc1 < nsc) request_d(sc1, ph1, db ^ 1);
+  // the two products of a pair: right-hand matrices in buffer wb, plane rows in buffer db from rows ra and rb on; the low
+  // halves of the planes count in the second product where lo1, and that product where `two`
+  auto pair = [&](int wb, int db, int ra, int rb, bool two, bool lo1, auto request) {
+    const unsigned char* dp = smem + 2 * kDxW + db * DB + (kq >> 1) * DR * 128;
+    const unsigned char* wp = smem + wb * kDxW;
+    // (where a pair is long, behind the fragment reads all eight waves start with; where it is short, as early as can be:
+    // 128 rows 166 -> 165 us a step of 512 slots, but 32 rows 18.9 -> 20.6 us a step of 128)
+    if (PT != 128) request();
+    bf16x8 fw[2][CB], fh[2][PB], fl[2][PB];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = row0 + (h ? rb : ra);
+      const unsigned char* p = dp + r * 128;
+      const int c = (dchunk ^ pswz(r)) << 4;
+#pragma unroll
+      for (int pb = 0; pb < PB; ++pb) {
+        fh[h][pb] = *(const bf16x8*)(p + c + pb * 32 * 128);
+        fl[h][pb] = *(const bf16x8*)(p + (c ^ 64) + pb * 32 * 128);
+      }
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) fw[h][cb] = frag_tr(wp + h * (64 * 256) + wa[cb][0], wp + h * (64 * 256) + wa[cb][1]);
     }
-    const bool more = s2.sc < nsc;
-    if (more) request_w(s2, wb == 0 ? 2 : wb - 1);
-    const int r = row0 + (s.ph ? 0 : KW - 1 - s.t);
-    const unsigned char* dp = dbase + db * DB + r * 128 + ((dchunk ^ pswz(r)) << 4);
-    const unsigned char* dpl = dbase + db * DB + r * 128 + (((dchunk + 4) ^ pswz(r)) << 4);
-    const unsigned char* wp = smem + wb * WB;
-    bf16x8 fw[CB], fh[PB], fl[PB];
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) fw[cb] = frag_tr(wp + wa[cb][0], wp + wa[cb][1]);
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      fh[pb] = *(const bf16x8*)(dp + pb * 32 * 128);
-      fl[pb] = *(const bf16x8*)(dpl + pb * 32 * 128);
-    }
-#pragma unroll
-    for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fh[pb], fw[cb], acc[pb][cb]);
-    if (!(s.ph && s.t)) {                 // low half x low half: below the 16 bits kept
+    auto multiply = [&](const bf16x8 (&fd)[PB], const bf16x8 (&fr)[CB]) {
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fl[pb], fw[cb], acc[pb][cb]);
+        for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fd[pb], fr[cb], acc[pb][cb]);
+    };
+    if (PT == 128) request();
+    multiply(fh[0], fw[0]);
+    multiply(fl[0], fw[0]);
+    if (two) multiply(fh[1], fw[1]);
+    if (lo1) multiply(fl[1], fw[1]);
+  };
+  const uint32_t tap_bytes = (uint32_t)(a.M * C * 2), chunk_w = (uint32_t)(64 * C * 2);
+  enter_chunk(0);
+  if (taps) {
+    request_d(0, pl, dvo[0], 0);
+    request_taps((uint32_t)min(wo, KW - 1) * tap_bytes, 0);
+  } else {
+    request_d(0, pn, dvo[1], 0);
+    request_g(0u, 0);
+  }
+  wait_loads<0>();
+  barrier();
+  int wb = 0, db = 0;
+  for (int sc = 0; sc < nsc; ++sc) {
+    if (taps) {
+      uint32_t soff = (uint32_t)sc * chunk_w + wo * tap_bytes;
+      for (int tp = 0; tp < npair; ++tp) {
+        const bool two = tp * 2 + 1 < KW;
+        pair(wb, db, KW - 1 - 2 * tp, two ? KW - 2 - 2 * tp : 0, two, two, [&]() {
+          // the next pair's matrices (a second tap that is not there: the first again, not used), and once the rows of n
+          if (tp + 1 < npair) request_taps((soff += 2 * tap_bytes) - (2 * tp + 2 + wo < KW ? 0u : tap_bytes), wb ^ 1);
+          else request_g((uint32_t)sc * (64 * 512), wb ^ 1);
+          if (tp == 0) request_d(sc, pn, dvo[1], db ^ 1);
+        });
+        if (tp == 0 && npair > 1) wait_loads<ND>(); else wait_loads<0>();
+        barrier();
+        wb ^= 1;
+      }
+      db ^= 1;
     }
-    // the next stage's matrix (and plane rows, requested before this stage's matrix) have landed
-    if (more) wait_loads<2>(); else wait_loads<0>();
+    // (low half x low half is below the 16 bits kept)
+    pair(wb, db, 0, 0, true, false, [&]() {
+      if (sc + 1 == nsc) return;
+      enter_chunk(sc + 1);
+      if (taps) {
+        request_d(sc + 1, pl, dvo[0], db ^ 1);
+        request_taps((uint32_t)(sc + 1) * chunk_w + (uint32_t)min(wo, KW - 1) * tap_bytes, wb ^ 1);
+      } else {
+        request_d(sc + 1, pn, dvo[1], db ^ 1);
+        request_g((uint32_t)(sc + 1) * (64 * 512), wb ^ 1);
+      }
+    });
+    wait_loads<0>();
     barrier();
-    if (s.t == (s.ph ? 1 : KW - 1)) db ^= 1;
-    wb = wb == 2 ? 0 : wb + 1;
-    s = next(s);
-    s2 = next(s2);
+    wb ^= 1;
+    db ^= 1;
   }
   // ---- the four partial sums of each output: column block cb is collected by the wave kq = cb of its half, two column
   // blocks at a time (a wave's block: 16 registers x 256 bytes)
@@ -476,17 +568,23 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
         for (int pb = 0; pb < PB; ++pb) {
           const int pr = p0 + (PT == 128 ? wo * 64 : 0) + pb * 32 + lh * 4;
           const int col = col0 + (c0 + c) * 32 + l31;
+          float* at[16];
+          float old[16];
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {       // every load before the first store
+            const int p = min(pr + (i >> 2) * 8 + (i & 3), pend - 1);
+            float* cr = (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + ((int64_t)ch * a.M + p) * kD;
+            float* br = (val ? g.d_v : g.d_k) + ch * g.kv_chain + ((int64_t)blk * g.B + p - x.m) * kD;
+            at[i] = (p < x.m ? cr : br) + col;
+            old[i] = *at[i];
+          }
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             float v = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
               v += k == c0 + c ? acc[pb][c0 + c][i] : red[((((wo * 2 + c) * 4 + k) * PB + pb) * 16 + i) * 64 + l];
-            const int p = pr + (i >> 2) * 8 + (i & 3);
-            if (p >= pend) continue;
-            float* row = p < x.m ? (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + ((int64_t)ch * a.M + p) * kD
-                                 : (val ? g.d_v : g.d_k) + ch * g.kv_chain + ((int64_t)blk * g.B + p - x.m) * kD;
-            row[col] += v;
+            if (pr + (i >> 2) * 8 + (i & 3) < pend) *at[i] = old[i] + v;
           }
         }
   }
@@ -505,7 +603,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, in
   const int KW = a.k_width, pad = (KW - 1) / 2, C = a.conv_in ? 2 * kD : kD, tiles = (a.M + 31) / 32;
   const int tg = (KW + 1) / 2, stiles = (a.M + 127) / 128;
   const int gi = blockIdx.x % groups, tile = blockIdx.x / groups;
-  const int t0 = (tile % tg) * 2, st = (tile / tg) % stiles, val = tile / tg / stiles, sb0 = st * 4;
+  const int t0 = (tile % tg) * 2, st = (tile / tg) % stiles, val = tile / tg / stiles, sbw = st * 4 + w;
   const bool two = t0 + 1 < KW, per_head = a.w_head_stride != 0;
   const int hkv = per_head ? blockIdx.y : 0;
   // unit u: (block, chain), or (block, batch entry) of this kv head where the filters are per head
@@ -514,30 +612,75 @@ __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, in
   int64_t n = total * gi / groups;
   const int64_t n_end = total * (gi + 1) / groups;
   if (n >= n_end) return;
-  const unsigned char* zero = (const unsigned char*)g.zero_page + (l & 15) * 16;
+  const unsigned char* zero = (const unsigned char*)g.zero_page;
 
-  struct Cursor { int u, st; };
-  auto request = [&](Cursor c, int buf) {
-    const int blk = c.u / per_blk, e = c.u % per_blk, ch = per_head ? e * a.Hkv + hkv : e, pc = c.st * 32;
-    const Block x = block_of(g, blk);
-    const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
-    const uint32_t lds = lds0 + buf * kDwStage;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {          // 32 rows of slot block sb0 + w
-      const int r = i * 8 + (l >> 3), q = pc + r, chunk = (l & 7) ^ pswz(r);
-      gather_to_lds(q < x.T && sb0 + w < tiles ? pl + ((int64_t)(sb0 + w) * g.P + q) * 128 + chunk * 16 : zero,
-                    lds + (w * 4 + i) * 1024);
-    }
-    auto entry = [&](int r4) {
-      const int r = r4 * 4 + (l >> 4), q = pc + r + t0 - pad, chunk = (l & 15) ^ swz(r);
-      const bool in = q >= 0 && q < x.T;
-      gather_to_lds(in ? (const unsigned char*)x_row(a, x, ch, in ? q : 0, val) + chunk * 16 : zero, lds + kDwDl + r4 * 1024);
-    };
-    entry(w * 2);
-    entry(w * 2 + 1);
-    if (w == 0) entry(8);                  // rows 32 .. 35
+  // where the stage requested next stands, and its unit's rows
+  int blk = (int)(n / spu) / per_blk, e = (int)(n / spu) % per_blk, stage = (int)(n % spu);
+  const View& sv = val ? a.v : a.k;
+  const int64_t st_bytes = sv.st * 2;
+  const bool near_rows = st_bytes * 36 < 0x7fffffff;                // a stage's rows of a block have 32-bit offsets
+  int m = 0, T = 0;
+  const unsigned char* plane = nullptr;
+  const unsigned char* crow = nullptr;
+  const unsigned char* brow = nullptr;
+  auto enter_unit = [&]() {
+    const int ch = per_head ? e * a.Hkv + hkv : e;
+    const Block x = block_of(g, blk < g.n_blk ? blk : 0);
+    m = x.m;
+    T = x.T;
+    plane = (const unsigned char*)(g.dl + blk * g.plane_stride) + ((int64_t)ch * tiles + sbw) * g.P * 128;
+    crow = (const unsigned char*)((val ? x.cv : x.ck) + (int64_t)ch * a.M * kD);
+    brow = (const unsigned char*)((val ? x.v : x.k) + (ch / a.Hkv) * sv.sb + (ch % a.Hkv) * sv.sh);
   };
-  auto advance = [&](Cursor& c) { if (++c.st == spu) { c.st = 0; ++c.u; } };
+  uint32_t dvo[4], cvo[3], bvo[3];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {            // 32 rows of slot block sbw
+    const int r = i * 8 + (l >> 3);
+    dvo[i] = r * 128 + (((l & 7) ^ pswz(r)) << 4);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {            // entry rows 8 w .. + 7, and 32 .. 35 (wave 0)
+    const int r = (i < 2 ? w * 2 + i : 8) * 4 + (l >> 4), c = ((l & 15) ^ swz(r)) << 4;
+    cvo[i] = r * 256 + c;
+    bvo[i] = (uint32_t)(r * st_bytes) + c;
+  }
+  auto request = [&](int buf) {
+    const int pc = stage * 32, q0 = pc + t0 - pad;
+    const uint32_t lds = lds0 + buf * kDwStage, ldx = lds + kDwDl;
+    if (pc < T && sbw < tiles) {           // (the planes are padded with zeros to whole stages)
+      const unsigned char* p = plane + (int64_t)pc * 128;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gather_to_lds(p, dvo[i], lds + (w * 4 + i) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gather_to_lds(zero, (uint32_t)(l & 15) * 16, lds + (w * 4 + i) * 1024);
+    }
+    const uint32_t at[3] = {ldx + w * 2048, ldx + w * 2048 + 1024, ldx + 8192};
+    if (q0 >= 0 && q0 + 36 <= m) {         // all rows in the cache
+      const unsigned char* p = crow + (int64_t)q0 * 256;
+      gather_to_lds(p, cvo[0], at[0]);
+      gather_to_lds(p, cvo[1], at[1]);
+      if (w == 0) gather_to_lds(p, cvo[2], at[2]);
+    } else if (q0 >= m && q0 + 36 <= T && near_rows) {   // all in the block
+      const unsigned char* p = brow + (q0 - m) * st_bytes;
+      gather_to_lds(p, bvo[0], at[0]);
+      gather_to_lds(p, bvo[1], at[1]);
+      if (w == 0) gather_to_lds(p, bvo[2], at[2]);
+    } else {                               // across the seam or an end: row by row, zeros outside
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const int r = (i < 2 ? w * 2 + i : 8) * 4 + (l >> 4), q = q0 + r, c = ((l & 15) ^ swz(r)) << 4;
+        const unsigned char* p = q < m ? crow + (int64_t)q * 256 : brow + (q - m) * st_bytes;
+        p = q >= 0 && q < T ? p + c : zero + (l & 15) * 16;
+        if (i < 2 || w == 0) gather_to_lds(p, at[i]);
+      }
+    }
+    if (++stage == spu) {
+      stage = 0;
+      if (++e == per_blk) { e = 0; ++blk; }
+      enter_unit();
+    }
+  };
   const int wy = w >> 1, wx = w & 1, s16 = l & 15, g2 = (l >> 4) & 1;
   int da[2];                               // [4-row half] of k step 0, slot block wy * 2 (high halves; low: ^ 64)
 #pragma unroll
@@ -562,18 +705,15 @@ __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, in
     for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int c = 0; c < 2; ++c) acc[t][y][c] = zero16();
-  Cursor ahead = {(int)(n / spu), (int)(n % spu)};
-  request(ahead, 0);
-  advance(ahead);
-  if (n + 1 < n_end) request(ahead, 1);
-  advance(ahead);
+  enter_unit();
+  request(0);
+  if (n + 1 < n_end) request(1);
   wait_loads<0>();
   barrier();
   int buf = 0;
   for (; n < n_end; ++n) {
     const bool more = n + 2 < n_end;
-    if (more) request(ahead, buf == 0 ? 2 : buf - 1);
-    advance(ahead);
+    if (more) request(buf == 0 ? 2 : buf - 1);
     const unsigned char* base = smem + buf * kDwStage;
 #pragma unroll
     for (int kc = 0; kc < 2; ++kc) {       // (16 rows on: swz and pswz repeat)
@@ -594,10 +734,11 @@ __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, in
 #pragma unroll
         for (int y = 0; y < 2; ++y)
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            acc[t][y][c] = mfma32(fh[y], fx[t][c], acc[t][y][c]);
-            acc[t][y][c] = mfma32(fl[y], fx[t][c], acc[t][y][c]);
-          }
+          for (int c = 0; c < 2; ++c) acc[t][y][c] = mfma32(fh[y], fx[t][c], acc[t][y][c]);
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) acc[t][y][c] = mfma32(fl[y], fx[t][c], acc[t][y][c]);
       }
     }
     if (!more) wait_loads<0>();            // the next stage has landed; this one's requests may be on their way
@@ -639,9 +780,15 @@ hipError_t allow_lds(F* k, int bytes) {
   return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
+template <int NT, bool MULTI>
+void launch_rows(const BwdConvArgs& g, int blk, int grid, hipStream_t s) {
+  if (g.st.norm == 0) hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, 0>), dim3(grid), dim3(512), 0, s, g, blk);
+  else hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, 1>), dim3(grid), dim3(512), 0, s, g, blk);
+}
+
 template <int PT>
 hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  constexpr int rings = 3 * 64 * 256 + 2 * 2 * (PT + 32) * 128, sums = 2 * 2 * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
+  constexpr int rings = 2 * kDxW + 2 * 2 * (PT + 32) * 128, sums = 2 * 2 * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
   constexpr int lds = rings > sums ? rings : sums;
   static const hipError_t e = allow_lds(bwd_dx_k<PT>, lds);
   if (e != hipSuccess) return e;
@@ -656,9 +803,9 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   const size_t chains = (size_t)batch * Hkv, C = conv_in ? 2 * kD : kD;
   BwdConvLayout l;
-  l.ld = (T + 31) / 32 * 32;
-  l.logits_stride = up(chains * M * l.ld * 4) / 4;
-  l.plane_stride = up(chains * ((M + 31) / 32) * T * 128) / 2;
+  l.ld = l.P = (T + 31) / 32 * 32;
+  l.logits_stride = up((chains * M + 31) * l.ld * 4) / 4;        // (whole tiles of 32 slots are read)
+  l.plane_stride = up(chains * ((M + 31) / 32) * l.P * 128) / 2;
   l.gsplit_stride = up(chains * M * 2 * kD * 2 * 2) / 2;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += up(bytes); return here; };
@@ -671,7 +818,6 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.wn = take((size_t)n_blk * l.plane_stride * 2);
   l.gsplit = take((size_t)n_blk * l.gsplit_stride * 2);
   l.total = at;
-  l.P = T;
   return l;
 }
 
@@ -709,11 +855,11 @@ hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
 
 hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s) {
   const StepArgs& a = g.st;
-  const dim3 grid((a.M + 31) / 32 * a.batch * a.Hkv), block(512);
-  if (T <= 256) hipLaunchKernelGGL((bwd_rows_k<1, false>), grid, block, 0, s, g, blk);
-  else if (T <= 512) hipLaunchKernelGGL((bwd_rows_k<2, false>), grid, block, 0, s, g, blk);
-  else if (T <= 1024) hipLaunchKernelGGL((bwd_rows_k<4, false>), grid, block, 0, s, g, blk);
-  else hipLaunchKernelGGL((bwd_rows_k<2, true>), grid, block, 0, s, g, blk);
+  const int grid = (a.M + 31) / 32 * a.batch * a.Hkv;
+  if (T <= 256) launch_rows<1, false>(g, blk, grid, s);
+  else if (T <= 512) launch_rows<2, false>(g, blk, grid, s);
+  else if (T <= 1024) launch_rows<4, false>(g, blk, grid, s);
+  else launch_rows<2, true>(g, blk, grid, s);
   return hipGetLastError();
 }
 
@@ -726,12 +872,17 @@ hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int par
   return launch_dx<32>(g, blk0, n_blk, part, rows, s);
 }
 
+// A step alone fills the device with 128-row tiles: nothing is gained by leaving its block's rows for later.
+bool bwd_conv_defers_blocks(const BwdConvArgs& g) {
+  return (int64_t)g.st.batch * g.st.Hkv * ((g.st.M + g.B + 127) / 128) < cu_count();
+}
+
 hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s) {
   static const hipError_t e = allow_lds(bwd_dw_k, 3 * kDwStage);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
   const bool per_head = a.w_head_stride != 0;
-  const int units = g.n_blk * (per_head ? a.batch : a.batch * a.Hkv), spu = (g.P + 31) / 32;
+  const int units = g.n_blk * (per_head ? a.batch : a.batch * a.Hkv), spu = g.P / 32;
   const int tiles = (a.k_width + 1) / 2 * ((a.M + 127) / 128) * (a.conv_in ? 2 : 1);
   // two workgroups per compute unit, the workgroups of a share (all tiles read the same rows) on one XCD
   const int64_t want = std::max<int64_t>(1, 2 * cu_count() / ((int64_t)tiles * (per_head ? a.Hkv : 1)));

@@ -318,6 +318,8 @@ hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s);
 hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s);
 hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s);
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s);
+// whether the rows of the blocks themselves are better taken together, after the walk
+bool bwd_conv_defers_blocks(const BwdConvArgs& g);
 hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s);
 
 // ---- measurement aid (peaks.hip): sustained bf16 MFMA rate of a bare loop and bandwidth of a plain
