@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblococo.so")
 
-SOURCES = ["api.cpp", "generic_kernels.hip", "scan_small.hip", "compress_mfma.hip", "attn_mfma.hip", "attn_decode.hip",
+SOURCES = ["api.cpp", "generic_kernels.hip", "scan_small.hip", "compress_mfma.hip", "compress_step.hip", "attn_mfma.hip", "attn_decode.hip",
            "bwd_attn_mfma.hip", "bwd_conv_mfma.hip",
            "backward_generic.hip", "tiled_mfma.hip", "peaks.hip"]
 
@@ -28,11 +28,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 # Per-file extras.  The compression kernel pins its filter slice to the accumulation registers;
 # with the VGPR form of the MFMA (accumulators in ordinary registers) nothing is copied between
 # the two register halves inside the loop.
-EXTRA = {"compress_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form",
-                                # the pipeline stages must be unrolled completely (the slices are
-                                # selected by compile-time slot numbers); the default size limit of
-                                # "#pragma unroll" is too small for the width-21 instantiation
-                                "-mllvm", "-pragma-unroll-threshold=200000"],
+COMPRESS = ["-mllvm", "-amdgpu-mfma-vgpr-form",
+            # the pipeline stages must be unrolled completely (the slices are selected by
+            # compile-time slot numbers); the default size limit of "#pragma unroll" is too
+            # small for the width-21 instantiation
+            "-mllvm", "-pragma-unroll-threshold=200000"]
+EXTRA = {"compress_mfma.hip": COMPRESS, "compress_step.hip": COMPRESS,
          # accumulators in ordinary registers: the softmax reads the scores where the MFMA left them
          "attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
          "bwd_attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],

@@ -598,6 +598,22 @@ lococo_status segment_step_impl(const lococo_config* cfg, const lococo_qkvo* blk
   if (compress && path != PATH_GENERIC &&
       (st = enqueue_repack(cfg, path, a, workspace, (hipStream_t)stream)))
     return st;
+  if (compress && path == PATH_MFMA && compress_step_fits(a, cu_count())) {
+    // both halves side by side in one launch, counted as the compression's
+    a.new_k = tmp.k[tmp.cur ^ 1];
+    a.new_v = tmp.v[tmp.cur ^ 1];
+    const AttnArgs t = attn_args_one_block(a);
+    {
+      KTimer kt(K_COMPRESS_MFMA, (hipStream_t)stream);
+      HIP_TRY(launch_compress_mfma(a, workspace, filter_banks(cfg), cu_count(), (char*)workspace + filter_ws_bytes(cfg),
+                                   partials_of(cfg, workspace, B), prelogits_of(cfg, workspace, B), B, (hipStream_t)stream, &t),
+              "step launch");
+    }
+    tmp.cur ^= 1;
+    tmp.len = cfg->M;
+    *cache = tmp;
+    return LOCOCO_OK;
+  }
   if ((st = enqueue_attn(cfg, path, a, step_stats(cfg, path, B, workspace, ws_bytes), (hipStream_t)stream)))
     return st;
   if ((st = enqueue_update(cfg, path, a, &tmp, workspace, B, (hipStream_t)stream))) return st;

@@ -187,8 +187,13 @@ hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, hipStre
 // Eq. 5 + Eq. 6 + Eq. 4a/4b in one kernel; writes a.new_k / a.new_v
 // sync_ws / partials: compress_scan_sync_bytes() / compress_partials_bytes() of device memory
 // prelogits: compress_prelogits_bytes(.., B, ..) of device memory, B >= a.Bn
-hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, int n_cu, void* sync_ws,
-                                void* partials, void* prelogits, int B, hipStream_t s);
+// attn: the block's attention in the same launch (only where compress_step_fits)
+struct AttnArgs;
+hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, int n_cu, void* sync_ws, void* partials,
+                                void* prelogits, int B, hipStream_t s, const AttnArgs* attn = nullptr);
+// ---- attention and compression of one block in one launch (compress_step.hip)
+bool compress_step_fits(const StepArgs& a, int n_cu);
+hipError_t launch_compress_step(const ScanArgs& sa, const AttnArgs& at, const void* wp, int64_t wp_head_stride, hipStream_t s);
 // workgroups per (chain, slot tile) that share out the positions of a step (1: no split)
 int compress_position_split(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu);
 // workgroups per (chain, slot tile) that take the steps of a scan in turn: 2, or 1 where the shape does not
