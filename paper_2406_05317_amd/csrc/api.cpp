@@ -1311,8 +1311,8 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBw
       const BwdConvLayout one = conv_layout(c, c->M + B, 1);
       per_block += one.total - one.per_call;
     }
-    // (blocks x chains and 2 x blocks are grid dimensions)
-    const int64_t most = std::min<int64_t>((int64_t)(kBwdWindowBytes / per_block), (int64_t)(16384 / chains));
+    // (blocks x chains and 4 x blocks are grid dimensions)
+    const int64_t most = std::min<int64_t>((int64_t)(kBwdWindowBytes / per_block), (int64_t)(8192 / chains));
     l.window = std::max<int64_t>(1, std::min<int64_t>(n, most));
     l.d_ck = take((size_t)l.window * l.slot);
     l.d_cv = take((size_t)l.window * l.slot);

@@ -197,16 +197,19 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     const uint16_t* q = (val ? x.v : x.k) + (ch / a.Hkv) * st.sb + hkv * st.sh + (int64_t)(j - x.m) * st.st;
     return (j < x.m ? c : q) + lh * 8;
   };
-  bf16x8 f0[2][8];                          // the first tile's, in flight while g is staged
+  // operand fragments of a tile's keys and values; each half is requested again for the next tile behind the products that
+  // read it (the first one here, in flight while g is staged)
+  bf16x8 fx[2][8];
+  auto request_entries = [&](int p0, int val) {
+    const uint16_t* row = entry(p0, val);
 #pragma unroll
-  for (int val = 0; val < 2; ++val) {
-    const uint16_t* row = entry(w * 32, val);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) f0[val][ks] = *(const bf16x8*)(row + ks * 16);
-  }
+    for (int ks = 0; ks < 8; ++ks) fx[val][ks] = *(const bf16x8*)(row + ks * 16);
+  };
+  request_entries(w * 32, 0);
+  request_entries(w * 32, 1);
   __syncthreads();
 
-  auto contract = [&](int pc, bool have_first) {
+  auto contract = [&](int pc) {
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const int p0 = pc + (w + 8 * n) * 32;
@@ -214,20 +217,12 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
       if (p0 >= x.T) continue;
 #pragma unroll
       for (int val = 0; val < 2; ++val) {
-        bf16x8 fx[8];
-        if (n == 0 && have_first) {
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) fx[ks] = f0[val][ks];
-        } else {
-          const uint16_t* row = entry(p0, val);
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) fx[ks] = *(const bf16x8*)(row + ks * 16);
-        }
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          acc[n] = mfma32(*(const bf16x8*)(Gs[0][val] + ga[ks]), fx[ks], acc[n]);
-          acc[n] = mfma32(*(const bf16x8*)(Gs[1][val] + ga[ks]), fx[ks], acc[n]);
+          acc[n] = mfma32(*(const bf16x8*)(Gs[0][val] + ga[ks]), fx[val][ks], acc[n]);
+          acc[n] = mfma32(*(const bf16x8*)(Gs[1][val] + ga[ks]), fx[val][ks], acc[n]);
         }
+        if (n + 1 < NT) request_entries(p0 + 256, val);        // (rows past the end: the last one again)
       }
     }
   };
@@ -348,15 +343,19 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     }
   };
   if (!MULTI) {
-    contract(0, true);
+    contract(0);
     mask(0);
     weigh();
     publish();
     finish(0);
   } else {
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
-      if (pc) fetch(pc);
-      contract(pc, false);
+      if (pc) {
+        fetch(pc);
+        request_entries(pc + w * 32, 0);
+        request_entries(pc + w * 32, 1);
+      }
+      contract(pc);
       mask(pc);
       weigh();
       __syncthreads();
@@ -364,7 +363,9 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     publish();
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
       fetch(pc);
-      contract(pc, false);
+      request_entries(pc + w * 32, 0);
+      request_entries(pc + w * 32, 1);
+      contract(pc);
       mask(pc);
       if (NORM == 0) rows(0);
 #pragma unroll
@@ -382,22 +383,24 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   }
 }
 
-// ---- dX: a workgroup per (PT positions, 128 key or value columns) of a chain and block, contraction over the slots in
+// ---- dX: a workgroup per (PT positions, NC key or value columns) of a chain and block, contraction over the slots in
 // chunks of 64.  A chunk is a phase with dl (one product per tap: its rows, shifted, times that tap's filters) and one with
 // n (times the two halves of g), worked through in pairs of products with one barrier each.  The eight waves split each
 // chunk four ways (16 slots each) and the outputs two ways; the four partial sums meet in LDS at the end.  Everything
-// arrives by loads that write LDS directly: the next pair's 64 x 128 right-hand matrices and the next phase's plane rows
+// arrives by loads that write LDS directly: the next pair's 64 x NC right-hand matrices and the next phase's plane rows
 // (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
-constexpr int kDxW = 2 * 64 * 256;                                 // two right-hand matrices
-template <int PT>
+template <int PT, int NC>
 __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : 2;     // 32 x 32 output blocks of a wave
+  constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : NC / 64;   // 32 x 32 output blocks of a wave
+  constexpr int WROW = NC * 2, WMAT = 64 * WROW, kDxW = 2 * WMAT;  // a row and a matrix of a pair in LDS; the pair
+  constexpr int NW = WMAT / 4096, RPI = 1024 / WROW;               // requests of a wave for its matrix; rows of one
   constexpr int DR = PT + 32, ND = DR / 32, DB = 2 * DR * 128;     // rows of a plane tile; its requests per wave; bytes
   const StepArgs& a = g.st;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
-  const int blk = blk0 + blockIdx.z / 2, val = blockIdx.z % 2, ch = blockIdx.y, hkv = ch % a.Hkv;
+  constexpr int ZC = 256 / NC;
+  const int blk = blk0 + blockIdx.z / ZC, val = blockIdx.z % ZC * NC / kD, cbase = blockIdx.z % ZC * NC % kD, ch = blockIdx.y, hkv = ch % a.Hkv;
   const Block x = block_of(g, blk);
   const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
   if (p0 >= pend) return;
@@ -409,28 +412,30 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 
   // right-hand matrices of a pair: waves 0 .. 3 request the first, 4 .. 7 the second; a row past M is the last one again
   // (its partner in the planes is zero)
-  const u32x4 rw = make_rsrc(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + (val ? kD : 0),
-                             (uint32_t)((int64_t)KW * a.M * C * 2) - (val ? 256 : 0));
+  const int coff = (val ? kD : 0) + cbase;
+  const u32x4 rw = make_rsrc(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + coff,
+                             (uint32_t)((int64_t)KW * a.M * C * 2) - coff * 2);
   const u32x4 rg = make_rsrc(g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) +
-                                 (val ? kD : 0), (uint32_t)(a.M * 512) - (val ? 256 : 0));
+                                 coff, (uint32_t)(a.M * 512) - coff * 2);
   // offsets of this lane's cells of a chunk: row r times the row stride plus the cell's chunk
-  uint32_t wvo[4], gvo[4];
+  auto cell = [&](int r, int chunk) { return NC == 128 ? chunk ^ swz(r) : chunk ^ pswz(r); };
+  uint32_t wvo[NW], gvo[NW];
   auto enter_chunk = [&](int sc) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r4 = (kq * 4 + i) * 4 + (l >> 4), r = min(r4, a.M - 1 - sc * 64), c = ((l & 15) ^ swz(r4)) << 4;
+    for (int i = 0; i < NW; ++i) {
+      const int rt = (kq * NW + i) * RPI + l / (WROW / 16), r = min(rt, a.M - 1 - sc * 64), c = cell(rt, l % (WROW / 16)) << 4;
       wvo[i] = r * (C * 2) + c;
       gvo[i] = r * 512 + c;
     }
   };
-  const uint32_t wdst = __builtin_amdgcn_readfirstlane(lds0 + wo * (64 * 256) + kq * 4096);
+  const uint32_t wdst = __builtin_amdgcn_readfirstlane(lds0 + wo * WMAT + kq * (NW * 1024));
   auto request_taps = [&](uint32_t soff, int buf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_to_lds_at(rw, wdst + buf * kDxW + i * 1024, wvo[i], soff);
+    for (int i = 0; i < NW; ++i) load_to_lds_at(rw, wdst + buf * kDxW + i * 1024, wvo[i], soff);
   };
   auto request_g = [&](uint32_t soff, int buf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_to_lds_at(rg, wdst + buf * kDxW + i * 1024, gvo[i], soff);
+    for (int i = 0; i < NW; ++i) load_to_lds_at(rg, wdst + buf * kDxW + i * 1024, gvo[i], soff);
   };
   // plane rows: offsets inside the two 32-slot planes of a chunk, of dl (with the halo) and of n
   uint32_t dvo[2][ND];
@@ -450,7 +455,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 #pragma unroll
     for (int i = 0; i < ND; ++i) load_to_lds_at(r, ddst + buf * DB + i * 1024, vo[i], 0u);
   };
-  const int row0 = (PT == 128 ? wo * 64 : 0) + l31, col0 = PT == 128 ? 0 : wo * 64;
+  const int row0 = (PT == 128 ? wo * 64 : 0) + l31, col0 = PT == 128 ? 0 : wo * (NC / 2);
   const int dchunk = (kq & 1) * 2 + lh;
   int wa[CB][2];
 #pragma unroll
@@ -459,7 +464,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
     for (int h = 0; h < 2; ++h) {
       const int s16 = l & 15, g2 = (l >> 4) & 1, r = kq * 16 + lh * 8 + (s16 >> 2) + 4 * h;
       const int chunk = (col0 >> 3) + 4 * cb + 2 * g2 + ((s16 & 3) >> 1);
-      wa[cb][h] = r * 256 + ((chunk ^ swz(r)) << 4) + (s16 & 1) * 8;
+      wa[cb][h] = r * WROW + (cell(r, chunk) << 4) + (s16 & 1) * 8;
     }
   f32x16 acc[PB][CB];
 #pragma unroll
@@ -487,7 +492,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
         fl[h][pb] = *(const bf16x8*)(p + (c ^ 64) + pb * 32 * 128);
       }
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb) fw[h][cb] = frag_tr(wp + h * (64 * 256) + wa[cb][0], wp + h * (64 * 256) + wa[cb][1]);
+      for (int cb = 0; cb < CB; ++cb) fw[h][cb] = frag_tr(wp + h * WMAT + wa[cb][0], wp + h * WMAT + wa[cb][1]);
     }
     auto multiply = [&](const bf16x8 (&fd)[PB], const bf16x8 (&fr)[CB]) {
 #pragma unroll
@@ -550,24 +555,25 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   // ---- the four partial sums of each output: column block cb is collected by the wave kq = cb of its half, two column
   // blocks at a time (a wave's block: 16 registers x 256 bytes)
   float* red = (float*)smem;
+  constexpr int C2 = CB < 2 ? 1 : 2;
 #pragma unroll
   for (int c0 = 0; c0 < CB; c0 += 2) {
     if (c0) __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < C2; ++c)
       if (kq != c0 + c)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) red[((((wo * 2 + c) * 4 + kq) * PB + pb) * 16 + i) * 64 + l] = acc[pb][c0 + c][i];
+          for (int i = 0; i < 16; ++i) red[((((wo * C2 + c) * 4 + kq) * PB + pb) * 16 + i) * 64 + l] = acc[pb][c0 + c][i];
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < C2; ++c)
       if (kq == c0 + c)
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) {
           const int pr = p0 + (PT == 128 ? wo * 64 : 0) + pb * 32 + lh * 4;
-          const int col = col0 + (c0 + c) * 32 + l31;
+          const int col = cbase + col0 + (c0 + c) * 32 + l31;
           float* at[16];
           float old[16];
 #pragma unroll
@@ -583,7 +589,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
             float v = 0.f;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-              v += k == c0 + c ? acc[pb][c0 + c][i] : red[((((wo * 2 + c) * 4 + k) * PB + pb) * 16 + i) * 64 + l];
+              v += k == c0 + c ? acc[pb][c0 + c][i] : red[((((wo * C2 + c) * 4 + k) * PB + pb) * 16 + i) * 64 + l];
             if (pr + (i >> 2) * 8 + (i & 3) < pend) *at[i] = old[i] + v;
           }
         }
@@ -786,14 +792,16 @@ void launch_rows(const BwdConvArgs& g, int blk, int grid, hipStream_t s) {
   else hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, 1>), dim3(grid), dim3(512), 0, s, g, blk);
 }
 
-template <int PT>
+template <int PT, int NC>
 hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  constexpr int rings = 2 * kDxW + 2 * 2 * (PT + 32) * 128, sums = 2 * 2 * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
+  constexpr int rings = 2 * 2 * 64 * NC * 2 + 2 * 2 * (PT + 32) * 128;
+  constexpr int sums = 2 * (NC == 64 ? 1 : 2) * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
   constexpr int lds = rings > sums ? rings : sums;
-  static const hipError_t e = allow_lds(bwd_dx_k<PT>, lds);
+  static const hipError_t e = allow_lds(bwd_dx_k<PT, NC>, lds);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
-  hipLaunchKernelGGL(bwd_dx_k<PT>, dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 2 * n_blk), dim3(512), lds, s, g, blk0, part);
+  hipLaunchKernelGGL((bwd_dx_k<PT, NC>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
+                     part);
   return hipGetLastError();
 }
 
@@ -865,11 +873,13 @@ hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_
 
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  // the largest tile of which there is one for every compute unit
+  // the largest tile of which there is one for every compute unit; the smallest one halved across the columns, two on a
+  // compute unit, where even those are too few (a step of 32 chains and 128 slots: 16.2 us, whole 18.9 us)
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
-  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64>(g, blk0, n_blk, part, rows, s);
-  return launch_dx<32>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128>(g, blk0, n_blk, part, rows, s);
+  return launch_dx<32, 64>(g, blk0, n_blk, part, rows, s);
 }
 
 // A step alone fills the device with 128-row tiles: nothing is gained by leaving its block's rows for later.
