@@ -366,7 +366,7 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *          [batch, n_kv_heads, M, d] (rows that were not live in cache0 are zero); all overwritten;
  *     acc  d_conv_w, d_conv_b: ADDED to, as in the step (d_conv_b may be NULL).
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
- *   states per block (storage type), one step's worth of everything else and about 2 GiB at most for the window.
+ *   states per block (storage type), one step's worth of everything else and about 3 GiB at most for the window.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */
 LOCOCO_API lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg, int64_t L, int32_t B,
                                                                   size_t* out);

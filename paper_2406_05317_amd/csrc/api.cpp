@@ -1089,9 +1089,9 @@ bool bwd_attn_on_mfma(const lococo_config* c, const lococo_qkvo* x, int32_t B) {
     if (((int64_t)B * t->stride_t + c->head_dim) * 2 >= lim) return false;
   return (int64_t)c->M * c->head_dim * 2 < lim && (int64_t)B * c->head_dim * 4 < lim;
 }
-// scratch of those kernels for `rows` query rows per head: dO as two bf16 halves, three floats of row statistics
+// scratch of those kernels for `rows` query rows per head: dO as up to three bf16 parts, three floats of row statistics
 size_t bwd_attn_hl_bytes(const lococo_config* c, int64_t rows) {
-  return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * c->head_dim * 4, 256);
+  return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * c->head_dim * 6, 256);
 }
 size_t bwd_attn_stat_bytes(const lococo_config* c, int64_t rows) {
   return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * 3 * sizeof(float), 256);
@@ -1286,7 +1286,7 @@ struct SeqBwdLayout {
 };
 // What a window may take: enough blocks to fill the device many times over at any shape, whatever the length of the
 // sequence.
-constexpr size_t kBwdWindowBytes = (size_t)2 << 30;
+constexpr size_t kBwdWindowBytes = (size_t)3 << 30;
 
 lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBwdLayout* out) {
   SeqBwdLayout l{};

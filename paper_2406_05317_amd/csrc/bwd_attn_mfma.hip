@@ -7,7 +7,9 @@
 //   bwd_attn_kv_k   a workgroup per 128 keys of [cache ; block]: dYk = dS^T q and dYv = P^T dO over the rows of all
 //                   heads of the group.
 // The fp32 operands (dO, P, dS) enter the matrix products as two bf16 halves (16 bits kept): S 1, dP 2, dq 2, dYk 2,
-// dYv 3 products; with the recomputation 15 products per (query, key) pair of 128 columns.
+// dYv 3 products; with the recomputation 15 products per (query, key) pair of 128 columns.  A block whose number of
+// positions is no multiple of 4 enters with three parts (24 bits, nothing lost; dP, dq, dYk 3, dYv 6 products): such blocks
+// have always been computed in fp32, and errors stay at that level (3e-7 against 3.5e-6 with two).
 // Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.0 ms for the whole sequence (1.7 + 3.2) against 20.0 ms as
 // seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.28 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
@@ -21,6 +23,11 @@ namespace {
 
 constexpr int kD = 128;
 constexpr int kTile = 64 * kD * 2;            // bytes of a tile of 64 rows
+constexpr int kOrow = 3 * kD;                 // elements of a row of dO's parts in memory
+
+// How many bf16 parts the fp32 operands of a block enter with: see BwdAttnArgs.  The two forms are launches of their own;
+// a workgroup of a block that is the other's leaves at once.
+__device__ __forceinline__ int parts_of(int T) { return T % 4 ? 3 : 2; }
 
 struct Seg {
   const uint16_t* ck; const uint16_t* cv;     // the chain's cache rows
@@ -53,7 +60,8 @@ __device__ __forceinline__ void request_tile(const u32x4& rsrc, uint32_t st, uin
   }
 }
 
-__global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
+template <int PARTS>
+__global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   const AttnArgs& a = g.a;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
@@ -61,7 +69,7 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
   const int qt = item % a.qtiles, hq = (item / a.qtiles) % a.Hq, b = (item / a.qtiles / a.Hq) % a.batch;
   const int n = item / a.qtiles / a.Hq / a.batch, hkv = hq / a.group, chain = b * a.Hkv + hkv, q0 = qt * 128;
   const Seg s = segment(a, n, chain);
-  if (q0 >= s.Bn) return;
+  if (q0 >= s.Bn || parts_of(s.m + s.Bn) != PARTS) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int wq0 = q0 + 32 * w, qrow = wq0 + l31;
   const u32x4 rck = rows_rsrc(s.ck, s.m, 256), rcv = rows_rsrc(s.cv, s.m, 256);
@@ -86,11 +94,11 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
   // ---- this lane's query and output-gradient row as operand fragments; dO also goes to memory as two halves
   const int row = min(qrow, s.Bn - 1);
   const bool live = qrow < s.Bn;
-  bf16x8 fq[8], foh[8], fol[8];
+  bf16x8 fq[8], fo[8][PARTS];
   {
     const uint16_t* qp = (const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + (s.start + row) * a.q.st + lh * 8;
     const float* op = g.d_o + b * g.q_sb + hq * g.q_sh + (s.start + row) * kD + lh * 8;
-    uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start + row) * (2 * kD) + lh * 8;
+    uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start + row) * kOrow + lh * 8;
     f32x4 o0[8], o1[8];
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
@@ -101,11 +109,10 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       const float x[8] = {o0[ks][0], o0[ks][1], o0[ks][2], o0[ks][3], o1[ks][0], o1[ks][1], o1[ks][2], o1[ks][3]};
-      split8(x, foh[ks], fol[ks]);
-      if (live) {
-        *(bf16x8*)(hl + ks * 16) = foh[ks];
-        *(bf16x8*)(hl + kD + ks * 16) = fol[ks];
-      }
+      split_parts<PARTS>(x, fo[ks]);
+      if (live)
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) *(bf16x8*)(hl + p * kD + ks * 16) = fo[ks][p];
     }
   }
   TileAddr ad;
@@ -123,8 +130,8 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
     for (int ks = 0; ks < 8; ++ks) {
       const bf16x8 fk = *(const bf16x8*)(k0 + ad.row[ks]), fv = *(const bf16x8*)(k0 + kTile + ad.row[ks]);
       sc = mfma32(fk, fq[ks], sc);
-      dp = mfma32(fv, foh[ks], dp);
-      dp = mfma32(fv, fol[ks], dp);
+#pragma unroll
+      for (int p = 0; p < PARTS; ++p) dp = mfma32(fv, fo[ks][p], dp);
     }
   };
   // keys this lane's query does not see: score -inf
@@ -202,14 +209,14 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
       for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mc)) * ps * (dp[i] - D);
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) {
-        bf16x8 hi, lo;
-        split8(ds + 8 * s2, hi, lo);
+        bf16x8 fd[PARTS];
+        split_parts<PARTS>(ds + 8 * s2, fd);
         const unsigned char* k0 = K + (kt * 32 + s2 * 16) * 256;
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) {
           const bf16x8 fk = frag_tr(k0 + ad.tr[ct][0], k0 + ad.tr[ct][1]);
-          acc[ct] = mfma32(fk, hi, acc[ct]);
-          acc[ct] = mfma32(fk, lo, acc[ct]);
+#pragma unroll
+          for (int p = 0; p < PARTS; ++p) acc[ct] = mfma32(fk, fd[p], acc[ct]);
         }
       }
     }
@@ -229,18 +236,20 @@ __global__ __launch_bounds__(256, 2) void bwd_attn_q_k(BwdAttnArgs g) {
 // Eight waves, two per group of 32 keys: waves 0..3 accumulate dYv (S, P^T dO), waves 4..7 dYk (S, dP, dS^T q).  One wave
 // with both would hold 384 registers of accumulators and key / value fragments; split, a wave needs under 256, each SIMD
 // has one of either kind to interleave, and the price is S computed twice (72 products instead of 64 per 32 x 32 tile).
+template <int PARTS>
 __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
-  extern __shared__ __align__(16) unsigned char smem[];       // [2][q | dO hi | dO lo] tiles of 64 rows, [2][3][64] statistics
+  constexpr int kSet = 1 + PARTS;
+  extern __shared__ __align__(16) unsigned char smem[];       // [2][q | parts of dO] tiles of 64 rows, [2][3][64] statistics
   const AttnArgs& a = g.a;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
-  float* st_lds = (float*)(smem + 6 * kTile);
+  float* st_lds = (float*)(smem + 2 * kSet * kTile);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int ktiles = (a.M + a.B + 127) / 128;
   const int chain = (item / ktiles) % (a.batch * a.Hkv), n = item / ktiles / (a.batch * a.Hkv);
   const int b = chain / a.Hkv, hkv = chain % a.Hkv, j0 = (item % ktiles) * 128;
   const Seg s = segment(a, n, chain);
   const int Tn = s.m + s.Bn;
-  if (j0 >= Tn) return;
+  if (j0 >= Tn || parts_of(Tn) != PARTS) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const bool for_v = w < 4;
   const int wj = j0 + 32 * (w & 3), j = wj + l31;             // this lane's position in [cache ; block]
@@ -252,17 +261,17 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   auto request = [&](int it) {
     if (it >= N) return;
     const int hq = hkv * a.group + it / rtiles, r0 = (first + it % rtiles) * 64;
-    const uint32_t lds = lds0 + (it & 1) * 3 * kTile;
+    const uint32_t lds = lds0 + (it & 1) * kSet * kTile;
     const u32x4 rq = rows_rsrc((const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + s.start * a.q.st, s.Bn, a.q.st * 2);
-    const uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start) * (2 * kD);
-    const u32x4 ro = make_rsrc(hl, (uint32_t)s.Bn * 512u);
+    const uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start) * kOrow;
+    const u32x4 ro = make_rsrc(hl, (uint32_t)s.Bn * (kOrow * 2u));
     request_tile<8>(rq, (uint32_t)(a.q.st * 2), r0, lds, w, l);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < PARTS; ++h)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4);
-        load_to_lds(ro, lds + (1 + h) * kTile + r4 * 1024, (r0 + r) * 512 + h * 256 + (((l & 15) ^ swz(r)) << 4));
+        load_to_lds(ro, lds + (1 + h) * kTile + r4 * 1024, (r0 + r) * (kOrow * 2) + h * 256 + (((l & 15) ^ swz(r)) << 4));
       }
     if (tid < 192) {
       const int r = r0 + (tid & 63);
@@ -300,7 +309,7 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   for (int it = 0; it < N; ++it) {
     request(it + 1);
     const int r0 = (first + it % rtiles) * 64;
-    const unsigned char* Q = smem + (it & 1) * 3 * kTile;
+    const unsigned char* Q = smem + (it & 1) * kSet * kTile;
     const float* st = st_lds + (it & 1) * 192 + lh * 4;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -329,24 +338,24 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
       if (for_v) {
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-          bf16x8 hi, lo;
-          split8(p + 8 * s2, hi, lo);
+          bf16x8 fp[PARTS];
+          split_parts<PARTS>(p + 8 * s2, fp);
           const unsigned char* o0 = q0 + kTile + s2 * 16 * 256;
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct) {
-            const bf16x8 oh = frag_tr(o0 + ad.tr[ct][0], o0 + ad.tr[ct][1]);
-            const bf16x8 ol = frag_tr(o0 + kTile + ad.tr[ct][0], o0 + kTile + ad.tr[ct][1]);
-            acc[ct] = mfma32(oh, hi, acc[ct]);
-            acc[ct] = mfma32(oh, lo, acc[ct]);
-            acc[ct] = mfma32(ol, hi, acc[ct]);
-          }
+          for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+            for (int u = 0; u < PARTS; ++u) {
+              const bf16x8 fo = frag_tr(o0 + u * kTile + ad.tr[ct][0], o0 + u * kTile + ad.tr[ct][1]);
+#pragma unroll
+              for (int v = 0; u + v < PARTS; ++v) acc[ct] = mfma32(fo, fp[v], acc[ct]);
+            }
         }
       } else {
         f32x16 dp = zero16();
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          dp = mfma32(*(const bf16x8*)(q0 + kTile + ad.row[ks]), fv[ks], dp);
-          dp = mfma32(*(const bf16x8*)(q0 + 2 * kTile + ad.row[ks]), fv[ks], dp);
+#pragma unroll
+          for (int u = 0; u < PARTS; ++u) dp = mfma32(*(const bf16x8*)(q0 + (1 + u) * kTile + ad.row[ks]), fv[ks], dp);
         }
 #pragma unroll
         for (int gi = 0; gi < 4; ++gi) {
@@ -356,14 +365,14 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
         }
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-          bf16x8 hi, lo;
-          split8(p + 8 * s2, hi, lo);
+          bf16x8 fd[PARTS];
+          split_parts<PARTS>(p + 8 * s2, fd);
           const unsigned char* t0 = q0 + s2 * 16 * 256;
 #pragma unroll
           for (int ct = 0; ct < 4; ++ct) {
             const bf16x8 qf = frag_tr(t0 + ad.tr[ct][0], t0 + ad.tr[ct][1]);
-            acc[ct] = mfma32(qf, hi, acc[ct]);
-            acc[ct] = mfma32(qf, lo, acc[ct]);
+#pragma unroll
+            for (int u = 0; u < PARTS; ++u) acc[ct] = mfma32(qf, fd[u], acc[ct]);
           }
         }
       }
@@ -386,21 +395,36 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
 
 }  // namespace
 
-hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
-  AttnArgs& a = g.a;
-  a.qtiles = (a.B + 127) / 128;
-  constexpr int lds_q = 4 * kTile, lds_kv = 6 * kTile + 2 * 3 * 64 * 4;
+template <int PARTS>
+static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
+  const AttnArgs& a = g.a;
+  constexpr int lds_q = 4 * kTile, lds_kv = 2 * (1 + PARTS) * kTile + 2 * 3 * 64 * 4;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)bwd_attn_kv_k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
+    hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)bwd_attn_kv_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL(bwd_attn_q_k, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
+  hipLaunchKernelGGL(bwd_attn_q_k<PARTS>, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
   const int ktiles = (a.M + a.B + 127) / 128;
-  hipLaunchKernelGGL(bwd_attn_kv_k, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(512), lds_kv, s, g);
+  hipLaunchKernelGGL(bwd_attn_kv_k<PARTS>, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(512), lds_kv, s, g);
   return hipGetLastError();
+}
+
+hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
+  AttnArgs& a = g.a;
+  a.qtiles = (a.B + 127) / 128;
+  bool two = false, three = false;          // which forms the window's blocks need
+  for (int n = 0; n < a.n_seg; ++n) {
+    const int64_t left = a.L - (int64_t)n * a.B;
+    const int T = (n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B);
+    (T % 4 ? three : two) = true;
+  }
+  hipError_t e = hipSuccess;
+  if (two) e = launch_parts<2>(g, s);
+  if (three && e == hipSuccess) e = launch_parts<3>(g, s);
+  return e;
 }
 
 }  // namespace lococo

@@ -10,7 +10,9 @@
 // blocks come from one launch ahead of the walk (tiled_mfma.hip), a step of the walk is two launches (bwd_rows_k, bwd_dx_k
 // over the cache rows), and the rows of the blocks and the filter gradient follow in one launch each for the whole window.
 //
-// g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  dl
+// g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  In a
+// block whose number of positions is no multiple of 4, n and g enter as three parts (G 3 products, n g 6): Eq. 4 of such
+// blocks has always been computed in fp32, and its error stays at that level.  dl
 // and n are kept as "planes" [chain][32 slots][position][32 high halves | 32 low halves]: 128 bytes per position, read row
 // by row where the slots are contracted (bwd_dx_k) and down the rows where the positions are (bwd_dw_k).
 #include <algorithm>
@@ -110,10 +112,10 @@ __device__ __forceinline__ float exp_neg(float x) {
 // ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
 // each; the rows of a step stay in registers from the logits to dl.  MULTI: more positions than that: they are walked
 // twice in chunks, first for the row sums alone.
-template <int NT, bool MULTI, int NORM>
+template <int NT, bool MULTI, int NORM, int PARTS>
 __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   const StepArgs& a = g.st;
-  __shared__ __align__(16) unsigned char Gs[2][2][32 * 256];     // [half][keys, values]: tiles of 32 rows (see swz)
+  __shared__ __align__(16) unsigned char Gs[PARTS][2][32 * 256];     // [part][keys, values]: tiles of 32 rows (see swz)
   __shared__ __align__(16) float red[2][8][32];
   __shared__ __align__(16) float row_s[3][32];                   // reference, 1 / sum, sum n G
   const Block x = block_of(g, blk);
@@ -176,15 +178,14 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     const float* p = (val ? gv : gk) + (int64_t)(in ? s0 + r : 0) * kD + (c8 & 15) * 8;
     const f32x4_any v0 = *(const f32x4_any*)p, v1 = *(const f32x4_any*)(p + 4);
     const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-    bf16x8 hi, lo;
-    split8(v, hi, lo);
+    bf16x8 part[PARTS];
+    split_parts<PARTS>(v, part);
     const int at = r * 256 + (((c8 & 15) ^ swz(r)) << 4);
-    *(bf16x8*)(Gs[0][val] + at) = hi;
-    *(bf16x8*)(Gs[1][val] + at) = lo;
-    if (in) {                               // for bwd_dx_k: [half][chain][slot][K | V]
-      uint16_t* o = gsp + ((int64_t)ch * a.M + s0 + r) * (2 * kD) + c8 * 8;
-      *(bf16x8*)o = hi;
-      *(bf16x8*)(o + (int64_t)a.batch * a.Hkv * a.M * (2 * kD)) = lo;
+#pragma unroll
+    for (int u = 0; u < PARTS; ++u) {
+      *(bf16x8*)(Gs[u][val] + at) = part[u];
+      if (in)                               // for bwd_dx_k: [part][chain][slot][K | V]
+        *(bf16x8*)(gsp + (((int64_t)u * a.batch * a.Hkv + ch) * a.M + s0 + r) * (2 * kD) + c8 * 8) = part[u];
     }
   }
   int ga[8];
@@ -219,8 +220,8 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
       for (int val = 0; val < 2; ++val) {
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-          acc[n] = mfma32(*(const bf16x8*)(Gs[0][val] + ga[ks]), fx[val][ks], acc[n]);
-          acc[n] = mfma32(*(const bf16x8*)(Gs[1][val] + ga[ks]), fx[val][ks], acc[n]);
+#pragma unroll
+          for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs[u][val] + ga[ks]), fx[val][ks], acc[n]);
         }
         if (n + 1 < NT) request_entries(p0 + 256, val);        // (rows past the end: the last one again)
       }
@@ -302,6 +303,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     rows(2); r = rv;
     uint16_t* pn = g.wn + blk * g.plane_stride;
     uint16_t* pl = g.dl + blk * g.plane_stride;
+    uint16_t* pw = g.wn_low + blk * g.plane_stride;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
       const int p0 = pc + (w + 8 * n) * 32, pos = p0 + l31;
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
       const int64_t o = (((int64_t)ch * tiles + sb) * g.P + pos) * 64 + lh * 8;
 #pragma unroll
       for (int qp = 0; qp < 2; ++qp) {      // slots 16 qp .. + 15: two groups of four of this lane
-        uint32_t nh[2][2], nl[2][2], dh[2][2], dlo[2][2];
+        uint32_t nh[2][2], nl[2][2], n3[2][2], dh[2][2], dlo[2][2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           float vn[4], vd[4];
@@ -323,8 +325,15 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
             vd[e] = on ? d : 0.f;
             bsum[i] += vd[e];                // (zero where the position does not count)
           }
-          split2(vn[0], vn[1], nh[q][0], nl[q][0]);
-          split2(vn[2], vn[3], nh[q][1], nl[q][1]);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            split2(vn[2 * e], vn[2 * e + 1], nh[q][e], nl[q][e]);
+            if (PARTS == 3) {
+              const f32x2 left = {vn[2 * e] - __uint_as_float(nh[q][e] << 16) - __uint_as_float(nl[q][e] << 16),
+                                  vn[2 * e + 1] - __uint_as_float(nh[q][e] & 0xffff0000u) - __uint_as_float(nl[q][e] & 0xffff0000u)};
+              n3[q][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(left, bf16x2));
+            }
+          }
           split2(vd[0], vd[1], dh[q][0], dlo[q][0]);
           split2(vd[2], vd[3], dh[q][1], dlo[q][1]);
         }
@@ -337,6 +346,10 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
         };
         put(pn + o + qp * 16, nh);
         put(pn + o + qp * 16 + 32, nl);
+        if (PARTS == 3) {
+          put(pw + o + qp * 16, n3);
+          put(pw + o + qp * 16 + 32, nh);
+        }
         put(pl + o + qp * 16, dh);
         put(pl + o + qp * 16 + 32, dlo);
       }
@@ -390,7 +403,8 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // arrives by loads that write LDS directly: the next pair's 64 x NC right-hand matrices and the next phase's plane rows
 // (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
-template <int PT, int NC>
+// FINE: the blocks whose n and g enter in three parts (m + Bn no multiple of 4); the others are another launch's.
+template <int PT, int NC, bool FINE>
 __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : NC / 64;   // 32 x 32 output blocks of a wave
@@ -402,6 +416,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   constexpr int ZC = 256 / NC;
   const int blk = blk0 + blockIdx.z / ZC, val = blockIdx.z % ZC * NC / kD, cbase = blockIdx.z % ZC * NC % kD, ch = blockIdx.y, hkv = ch % a.Hkv;
   const Block x = block_of(g, blk);
+  if ((x.T % 4 != 0) != FINE) return;
   const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
   if (p0 >= pend) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
@@ -415,6 +430,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   const int coff = (val ? kD : 0) + cbase;
   const u32x4 rw = make_rsrc(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + coff,
                              (uint32_t)((int64_t)KW * a.M * C * 2) - coff * 2);
+  const uint16_t* g2 = g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? 2 * a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) + coff;
+  const u32x4 rg2 = make_rsrc(g2, (uint32_t)(a.M * 512) - coff * 2);
   const u32x4 rg = make_rsrc(g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) +
                                  coff, (uint32_t)(a.M * 512) - coff * 2);
   // offsets of this lane's cells of a chunk: row r times the row stride plus the cell's chunk
@@ -433,9 +450,9 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 #pragma unroll
     for (int i = 0; i < NW; ++i) load_to_lds_at(rw, wdst + buf * kDxW + i * 1024, wvo[i], soff);
   };
-  auto request_g = [&](uint32_t soff, int buf) {
+  auto request_g = [&](const u32x4& r, uint32_t soff, int buf) {
 #pragma unroll
-    for (int i = 0; i < NW; ++i) load_to_lds_at(rg, wdst + buf * kDxW + i * 1024, gvo[i], soff);
+    for (int i = 0; i < NW; ++i) load_to_lds_at(r, wdst + buf * kDxW + i * 1024, gvo[i], soff);
   };
   // plane rows: offsets inside the two 32-slot planes of a chunk, of dl (with the halo) and of n
   uint32_t dvo[2][ND];
@@ -450,6 +467,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
   const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
   const uint32_t ddst = __builtin_amdgcn_readfirstlane(lds0 + 2 * kDxW + w * ND * 1024);
+  const unsigned char* pw = (const unsigned char*)(g.wn_low + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
   auto request_d = [&](int sc, const unsigned char* plane, const uint32_t (&vo)[ND], int buf) {
     const u32x4 r = make_rsrc(plane + (int64_t)sc * 2 * g.P * 128, (uint32_t)(min(2, tiles - sc * 2) * g.P * 128));
 #pragma unroll
@@ -473,8 +491,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
     for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = zero16();
 
   // the two products of a pair: right-hand matrices in buffer wb, plane rows in buffer db from rows ra and rb on; the low
-  // halves of the planes count in the second product where lo1, and that product where `two`
-  auto pair = [&](int wb, int db, int ra, int rb, bool two, bool lo1, auto request) {
+  // halves of the planes count in the two products where lo0 and lo1, the high ones in the second where `two`
+  auto pair = [&](int wb, int db, int ra, int rb, bool lo0, bool two, bool lo1, auto request) {
     const unsigned char* dp = smem + 2 * kDxW + db * DB + (kq >> 1) * DR * 128;
     const unsigned char* wp = smem + wb * kDxW;
     // (where a pair is long, behind the fragment reads all eight waves start with; where it is short, as early as can be:
@@ -502,7 +520,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
     };
     if (PT == 128) request();
     multiply(fh[0], fw[0]);
-    multiply(fl[0], fw[0]);
+    if (lo0) multiply(fl[0], fw[0]);
     if (two) multiply(fh[1], fw[1]);
     if (lo1) multiply(fl[1], fw[1]);
   };
@@ -513,7 +531,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
     request_taps((uint32_t)min(wo, KW - 1) * tap_bytes, 0);
   } else {
     request_d(0, pn, dvo[1], 0);
-    request_g(0u, 0);
+    request_g(rg, 0u, 0);
   }
   wait_loads<0>();
   barrier();
@@ -523,10 +541,10 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
       uint32_t soff = (uint32_t)sc * chunk_w + wo * tap_bytes;
       for (int tp = 0; tp < npair; ++tp) {
         const bool two = tp * 2 + 1 < KW;
-        pair(wb, db, KW - 1 - 2 * tp, two ? KW - 2 - 2 * tp : 0, two, two, [&]() {
+        pair(wb, db, KW - 1 - 2 * tp, two ? KW - 2 - 2 * tp : 0, true, two, two, [&]() {
           // the next pair's matrices (a second tap that is not there: the first again, not used), and once the rows of n
           if (tp + 1 < npair) request_taps((soff += 2 * tap_bytes) - (2 * tp + 2 + wo < KW ? 0u : tap_bytes), wb ^ 1);
-          else request_g((uint32_t)sc * (64 * 512), wb ^ 1);
+          else request_g(rg, (uint32_t)sc * (64 * 512), wb ^ 1);
           if (tp == 0) request_d(sc, pn, dvo[1], db ^ 1);
         });
         if (tp == 0 && npair > 1) wait_loads<ND>(); else wait_loads<0>();
@@ -535,8 +553,7 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
       }
       db ^= 1;
     }
-    // (low half x low half is below the 16 bits kept)
-    pair(wb, db, 0, 0, true, false, [&]() {
+    auto next_chunk = [&]() {
       if (sc + 1 == nsc) return;
       enter_chunk(sc + 1);
       if (taps) {
@@ -544,13 +561,29 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
         request_taps((uint32_t)(sc + 1) * chunk_w + (uint32_t)min(wo, KW - 1) * tap_bytes, wb ^ 1);
       } else {
         request_d(sc + 1, pn, dvo[1], db ^ 1);
-        request_g((uint32_t)(sc + 1) * (64 * 512), wb ^ 1);
+        request_g(rg, (uint32_t)(sc + 1) * (64 * 512), wb ^ 1);
+      }
+    };
+    // (low half x low half is below the 16 bits kept of two parts, not below the 24 of three)
+    pair(wb, db, 0, 0, true, true, FINE, [&]() {
+      if (FINE) {
+        request_d(sc, pw, dvo[1], db ^ 1);
+        request_g(rg2, (uint32_t)sc * (64 * 512), wb ^ 1);
+      } else {
+        next_chunk();
       }
     });
     wait_loads<0>();
     barrier();
     wb ^= 1;
     db ^= 1;
+    if (FINE) {                            // third part of n x first of g, first of n x third of g
+      pair(wb, db, 0, 0, false, false, true, next_chunk);
+      wait_loads<0>();
+      barrier();
+      wb ^= 1;
+      db ^= 1;
+    }
   }
   // ---- the four partial sums of each output: column block cb is collected by the wave kq = cb of its half, two column
   // blocks at a time (a wave's block: 16 registers x 256 bytes)
@@ -786,21 +819,26 @@ hipError_t allow_lds(F* k, int bytes) {
   return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
+template <int NT, bool MULTI, int NORM>
+void launch_rows_norm(const BwdConvArgs& g, int blk, int T, int grid, hipStream_t s) {
+  if (T % 4 == 0) hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, NORM, 2>), dim3(grid), dim3(512), 0, s, g, blk);
+  else hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, NORM, 3>), dim3(grid), dim3(512), 0, s, g, blk);
+}
 template <int NT, bool MULTI>
-void launch_rows(const BwdConvArgs& g, int blk, int grid, hipStream_t s) {
-  if (g.st.norm == 0) hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, 0>), dim3(grid), dim3(512), 0, s, g, blk);
-  else hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, 1>), dim3(grid), dim3(512), 0, s, g, blk);
+void launch_rows(const BwdConvArgs& g, int blk, int T, int grid, hipStream_t s) {
+  if (g.st.norm == 0) launch_rows_norm<NT, MULTI, 0>(g, blk, T, grid, s);
+  else launch_rows_norm<NT, MULTI, 1>(g, blk, T, grid, s);
 }
 
-template <int PT, int NC>
+template <int PT, int NC, bool FINE>
 hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   constexpr int rings = 2 * 2 * 64 * NC * 2 + 2 * 2 * (PT + 32) * 128;
   constexpr int sums = 2 * (NC == 64 ? 1 : 2) * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
   constexpr int lds = rings > sums ? rings : sums;
-  static const hipError_t e = allow_lds(bwd_dx_k<PT, NC>, lds);
+  static const hipError_t e = allow_lds(bwd_dx_k<PT, NC, FINE>, lds);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
-  hipLaunchKernelGGL((bwd_dx_k<PT, NC>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
+  hipLaunchKernelGGL((bwd_dx_k<PT, NC, FINE>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
                      part);
   return hipGetLastError();
 }
@@ -814,7 +852,7 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.ld = l.P = (T + 31) / 32 * 32;
   l.logits_stride = up((chains * M + 31) * l.ld * 4) / 4;        // (whole tiles of 32 slots are read)
   l.plane_stride = up(chains * ((M + 31) / 32) * l.P * 128) / 2;
-  l.gsplit_stride = up(chains * M * 2 * kD * 2 * 2) / 2;
+  l.gsplit_stride = up(chains * M * 2 * kD * 2 * 3) / 2;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += up(bytes); return here; };
   l.wt = take((size_t)banks * conv_width * M * C * 2);
@@ -824,6 +862,7 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.logits = take((size_t)n_blk * l.logits_stride * 4);
   l.dl = take((size_t)n_blk * l.plane_stride * 2);
   l.wn = take((size_t)n_blk * l.plane_stride * 2);
+  l.wn_low = take((size_t)n_blk * l.plane_stride * 2);
   l.gsplit = take((size_t)n_blk * l.gsplit_stride * 2);
   l.total = at;
   return l;
@@ -837,6 +876,7 @@ void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
   g->logits = (float*)(p + l.logits);
   g->dl = (uint16_t*)(p + l.dl);
   g->wn = (uint16_t*)(p + l.wn);
+  g->wn_low = (uint16_t*)(p + l.wn_low);
   g->gsplit = (uint16_t*)(p + l.gsplit);
   g->logits_stride = (int64_t)l.logits_stride;
   g->plane_stride = (int64_t)l.plane_stride;
@@ -864,22 +904,35 @@ hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
 hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s) {
   const StepArgs& a = g.st;
   const int grid = (a.M + 31) / 32 * a.batch * a.Hkv;
-  if (T <= 256) launch_rows<1, false>(g, blk, grid, s);
-  else if (T <= 512) launch_rows<2, false>(g, blk, grid, s);
-  else if (T <= 1024) launch_rows<4, false>(g, blk, grid, s);
-  else launch_rows<2, true>(g, blk, grid, s);
+  if (T <= 256) launch_rows<1, false>(g, blk, T, grid, s);
+  else if (T <= 512) launch_rows<2, false>(g, blk, T, grid, s);
+  else if (T <= 1024) launch_rows<4, false>(g, blk, T, grid, s);
+  else launch_rows<2, true>(g, blk, T, grid, s);
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
+template <bool FINE>
+static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   // the largest tile of which there is one for every compute unit; the smallest one halved across the columns, two on a
   // compute unit, where even those are too few (a step of 32 chains and 128 slots: 16.2 us, whole 18.9 us)
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
-  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128>(g, blk0, n_blk, part, rows, s);
-  return launch_dx<32, 64>(g, blk0, n_blk, part, rows, s);
+  if constexpr (!FINE)                     // (with the third parts the largest tile spills)
+    if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, FINE>(g, blk0, n_blk, part, rows, s);
+  return launch_dx<32, 64, FINE>(g, blk0, n_blk, part, rows, s);
+}
+hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  bool plain = false, fine = false;        // which forms the blocks need
+  for (int i = blk0; i < blk0 + n_blk; ++i) {
+    const int64_t left = g.tokens - (int64_t)i * g.B;
+    ((((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4) ? fine : plain) = true;
+  }
+  hipError_t e = hipSuccess;
+  if (plain) e = launch_dx_tiles<false>(g, blk0, n_blk, part, rows, s);
+  if (fine && e == hipSuccess) e = launch_dx_tiles<true>(g, blk0, n_blk, part, rows, s);
+  return e;
 }
 
 // A step alone fills the device with 128-row tiles: nothing is gained by leaving its block's rows for later.

@@ -231,7 +231,8 @@ hipError_t launch_attn_colsum_mfma(const AttnArgs& a, float* colsum, hipStream_t
 // ---- backward of that attention, every block of a window at once (bwd_attn_mfma.hip).  `a`: the blocks and states as in
 // the forward (seg_first = 0; o not used).  Gradients fp32, rows of head_dim contiguous: d_o, d_q with the batch / head
 // strides q_sb, q_sh and d_k, d_v with k_sb, k_sh (elements; first row = first token of the window); d_ck, d_cv
-// [n_seg][chains][M][d], live rows only.  All outputs are assigned.  do_hl: scratch, 2 d bf16 per query row; stats: 3 fp32.
+// [n_seg][chains][M][d], live rows only.  All outputs are assigned.  do_hl: scratch, 3 d bf16 per query row; stats: 3 fp32.
+// fp32 operands enter as two bf16 halves where a block's m + Bn is a multiple of 4, as three parts where it is not.
 struct BwdAttnArgs {
   AttnArgs a;
   const float* d_o;
@@ -303,12 +304,13 @@ struct BwdConvArgs {
   float* logits;             // [block][chain][slot][ld]
   uint16_t* dl;              // planes of the logit gradients and of the normalised rows, [block][chain][32 slots][P][64]
   uint16_t* wn;
-  uint16_t* gsplit;          // gradient w.r.t. the new cache, [block][half][chain][slot][K | V]
+  uint16_t* wn_low;          // third parts of the normalised rows, with the first ones: [third 32 | first 32] (blocks in three parts)
+  uint16_t* gsplit;          // gradient w.r.t. the new cache, [block][part][chain][slot][K | V]
   int64_t logits_stride, plane_stride, gsplit_stride;     // between blocks, in elements of each
   int32_t ld, P;
 };
 struct BwdConvLayout {       // byte offsets; the first three are per call, the rest per window
-  size_t wt, zero_page, dwt, per_call, logits, dl, wn, gsplit, total;
+  size_t wt, zero_page, dwt, per_call, logits, dl, wn, wn_low, gsplit, total;
   size_t logits_stride, plane_stride, gsplit_stride;
   int ld, P;
 };

@@ -34,19 +34,25 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& hi, uint32_
   const f32x2 e = {x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xffff0000u)};
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(e, bf16x2));
 }
-__device__ __forceinline__ void split8(const float* x, bf16x8& hi, bf16x8& lo) {
-  u32x4 h, l;
+// PARTS = 2: the same for eight values, as operands.  PARTS = 3: what those two leave over as well, 24 bits in all: nothing is lost.
+template <int PARTS>
+__device__ __forceinline__ void split_parts(const float* x, bf16x8 (&part)[PARTS]) {
+  float r[8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    uint32_t a, b;
-    split2(x[2 * i], x[2 * i + 1], a, b);
-    h[i] = a;
-    l[i] = b;
+  for (int i = 0; i < 8; ++i) r[i] = x[i];
+#pragma unroll
+  for (int p = 0; p < PARTS; ++p) {
+    u32x4 h;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x2 v = {r[2 * i], r[2 * i + 1]};
+      h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+      r[2 * i] -= __uint_as_float(h[i] << 16);
+      r[2 * i + 1] -= __uint_as_float(h[i] & 0xffff0000u);
+    }
+    part[p] = __builtin_bit_cast(bf16x8, h);
   }
-  hi = __builtin_bit_cast(bf16x8, h);
-  lo = __builtin_bit_cast(bf16x8, l);
 }
-
 // a value combined with the one the lane 32 away holds (v_permlane32_swap: no trip through the LDS crossbar)
 __device__ __forceinline__ float max_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
