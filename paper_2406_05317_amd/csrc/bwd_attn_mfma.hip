@@ -25,10 +25,6 @@ constexpr int kD = 128;
 constexpr int kTile = 64 * kD * 2;            // bytes of a tile of 64 rows
 constexpr int kOrow = 3 * kD;                 // elements of a row of dO's parts in memory
 
-// How many bf16 parts the fp32 operands of a block enter with: see BwdAttnArgs.  The two forms are launches of their own;
-// a workgroup of a block that is the other's leaves at once.
-__device__ __forceinline__ int parts_of(int T) { return T % 4 ? 3 : 2; }
-
 struct Seg {
   const uint16_t* ck; const uint16_t* cv;     // the chain's cache rows
   int64_t start;                              // first token of the block (in the window)
@@ -67,9 +63,9 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int qt = item % a.qtiles, hq = (item / a.qtiles) % a.Hq, b = (item / a.qtiles / a.Hq) % a.batch;
-  const int n = item / a.qtiles / a.Hq / a.batch, hkv = hq / a.group, chain = b * a.Hkv + hkv, q0 = qt * 128;
+  const int n = a.seg_first + item / a.qtiles / a.Hq / a.batch, hkv = hq / a.group, chain = b * a.Hkv + hkv, q0 = qt * 128;
   const Seg s = segment(a, n, chain);
-  if (q0 >= s.Bn || parts_of(s.m + s.Bn) != PARTS) return;
+  if (q0 >= s.Bn) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int wq0 = q0 + 32 * w, qrow = wq0 + l31;
   const u32x4 rck = rows_rsrc(s.ck, s.m, 256), rcv = rows_rsrc(s.cv, s.m, 256);
@@ -245,11 +241,11 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   float* st_lds = (float*)(smem + 2 * kSet * kTile);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int ktiles = (a.M + a.B + 127) / 128;
-  const int chain = (item / ktiles) % (a.batch * a.Hkv), n = item / ktiles / (a.batch * a.Hkv);
+  const int chain = (item / ktiles) % (a.batch * a.Hkv), n = a.seg_first + item / ktiles / (a.batch * a.Hkv);
   const int b = chain / a.Hkv, hkv = chain % a.Hkv, j0 = (item % ktiles) * 128;
   const Seg s = segment(a, n, chain);
   const int Tn = s.m + s.Bn;
-  if (j0 >= Tn || parts_of(Tn) != PARTS) return;
+  if (j0 >= Tn) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const bool for_v = w < 4;
   const int wj = j0 + 32 * (w & 3), j = wj + l31;             // this lane's position in [cache ; block]
@@ -415,15 +411,18 @@ static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
 hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
   AttnArgs& a = g.a;
   a.qtiles = (a.B + 127) / 128;
-  bool two = false, three = false;          // which forms the window's blocks need
-  for (int n = 0; n < a.n_seg; ++n) {
+  // runs of blocks of one form: all of them as a rule, or all but a ragged last one
+  auto parts = [&](int n) {
     const int64_t left = a.L - (int64_t)n * a.B;
-    const int T = (n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B);
-    (T % 4 ? three : two) = true;
-  }
+    return ((n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B)) % 4 ? 3 : 2;
+  };
+  const int n_all = a.n_seg;
   hipError_t e = hipSuccess;
-  if (two) e = launch_parts<2>(g, s);
-  if (three && e == hipSuccess) e = launch_parts<3>(g, s);
+  for (int n = 0; n < n_all && e == hipSuccess; n += a.n_seg) {
+    a.seg_first = n;
+    for (a.n_seg = 1; n + a.n_seg < n_all && parts(n + a.n_seg) == parts(n);) ++a.n_seg;
+    e = parts(n) == 2 ? launch_parts<2>(g, s) : launch_parts<3>(g, s);
+  }
   return e;
 }
 

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // arrives by loads that write LDS directly: the next pair's 64 x NC right-hand matrices and the next phase's plane rows
 // (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
-// FINE: the blocks whose n and g enter in three parts (m + Bn no multiple of 4); the others are another launch's.
+// FINE: the blocks whose n and g enter in three parts (m + Bn no multiple of 4).
 template <int PT, int NC, bool FINE>
 __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -416,7 +416,6 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   constexpr int ZC = 256 / NC;
   const int blk = blk0 + blockIdx.z / ZC, val = blockIdx.z % ZC * NC / kD, cbase = blockIdx.z % ZC * NC % kD, ch = blockIdx.y, hkv = ch % a.Hkv;
   const Block x = block_of(g, blk);
-  if ((x.T % 4 != 0) != FINE) return;
   const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
   if (p0 >= pend) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
@@ -924,14 +923,15 @@ static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int
 }
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  bool plain = false, fine = false;        // which forms the blocks need
-  for (int i = blk0; i < blk0 + n_blk; ++i) {
+  auto fine = [&](int i) {
     const int64_t left = g.tokens - (int64_t)i * g.B;
-    ((((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4) ? fine : plain) = true;
-  }
+    return ((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4 != 0;
+  };
   hipError_t e = hipSuccess;
-  if (plain) e = launch_dx_tiles<false>(g, blk0, n_blk, part, rows, s);
-  if (fine && e == hipSuccess) e = launch_dx_tiles<true>(g, blk0, n_blk, part, rows, s);
+  for (int i = blk0, n = 0; i < blk0 + n_blk && e == hipSuccess; i += n) {      // runs of blocks of one form
+    for (n = 1; i + n < blk0 + n_blk && fine(i + n) == fine(i);) ++n;
+    e = fine(i) ? launch_dx_tiles<true>(g, i, n, part, rows, s) : launch_dx_tiles<false>(g, i, n, part, rows, s);
+  }
   return e;
 }
 

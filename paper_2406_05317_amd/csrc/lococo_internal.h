@@ -229,7 +229,7 @@ hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_colsum_mfma(const AttnArgs& a, float* colsum, hipStream_t s);
 
 // ---- backward of that attention, every block of a window at once (bwd_attn_mfma.hip).  `a`: the blocks and states as in
-// the forward (seg_first = 0; o not used).  Gradients fp32, rows of head_dim contiguous: d_o, d_q with the batch / head
+// the forward (seg_first is set inside; o not used).  Gradients fp32, rows of head_dim contiguous: d_o, d_q with the batch / head
 // strides q_sb, q_sh and d_k, d_v with k_sb, k_sh (elements; first row = first token of the window); d_ck, d_cv
 // [n_seg][chains][M][d], live rows only.  All outputs are assigned.  do_hl: scratch, 3 d bf16 per query row; stats: 3 fp32.
 // fp32 operands enter as two bf16 halves where a block's m + Bn is a multiple of 4, as three parts where it is not.
