@@ -110,7 +110,9 @@ __device__ __forceinline__ float exp_neg(float x) {
 }
 
 // ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
-// each; the rows of a step stay in registers from the logits to dl.  MULTI: more positions than that: they are walked
+// each; the rows of a step stay in registers from the logits to dl.  Bound by its stores (134 MB a step of 32 chains, 512 slots,
+// 1024 positions) and by the latencies before them, one workgroup filling a compute unit: 83 us a step, 69 without the
+// stores, 55 without the products; as five kernels with fp32 arrays in memory between them 250 us.  MULTI: more positions than that: they are walked
 // twice in chunks, first for the row sums alone.
 template <int NT, bool MULTI, int NORM, int PARTS>
 __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
@@ -401,7 +403,9 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // n (times the two halves of g), worked through in pairs of products with one barrier each.  The eight waves split each
 // chunk four ways (16 slots each) and the outputs two ways; the four partial sums meet in LDS at the end.  Everything
 // arrives by loads that write LDS directly: the next pair's 64 x NC right-hand matrices and the next phase's plane rows
-// (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).
+// (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).  161 us a step of 32
+// chains, 512 slots and 1024 positions (155 GFLOP; 246 us as two kernels); without the matrix requests 140, with half of the
+// products 143: requests, fragment reads and products of a pair are a chain the two waves of a SIMD overlap in part.
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
 // FINE: the blocks whose n and g enter in three parts (m + Bn no multiple of 4).
 template <int PT, int NC, bool FINE>
@@ -631,7 +635,8 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 // ---- dW: a workgroup per (128 slots, 128 columns, two taps) and share of the contraction over (block, chain, position),
 // in stages of 32 positions.  The plane rows and the entries' rows (33 of them: the two taps are one row apart) come two
 // stages ahead into a ring of three; both operands are read down their rows, and the fragments of dl serve both taps.
-// Sums go to dwt [bank][tap][slot][channel] with atomics, once per workgroup.
+// Sums go to dwt [bank][tap][slot][channel] with atomics, once per workgroup.  Bound by the products: 127 us a block of 32
+// chains, 512 slots and 1024 positions, 1.0 PFLOP/s (210 us with a tap per workgroup and the atomics once per block).
 constexpr int kDwDl = 4 * 32 * 128, kDwX = 36 * 256, kDwStage = kDwDl + kDwX;
 __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, int n_units, int spu) {
   extern __shared__ __align__(16) unsigned char smem[];
