@@ -819,8 +819,11 @@ __global__ void bwd_add_dw_k(const float* dwt, float* d_conv_w, int M, int C, in
 }
 
 template <typename F>
-hipError_t allow_lds(F* k, int bytes) {
-  return hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+hipError_t allow_lds(F* k, int bytes, bool& done) {      // benign race: setting it twice is harmless
+  if (done) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  done = e == hipSuccess;
+  return e;
 }
 
 template <int NT, bool MULTI, int NORM>
@@ -839,7 +842,8 @@ hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int ro
   constexpr int rings = 2 * 2 * 64 * NC * 2 + 2 * 2 * (PT + 32) * 128;
   constexpr int sums = 2 * (NC == 64 ? 1 : 2) * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
   constexpr int lds = rings > sums ? rings : sums;
-  static const hipError_t e = allow_lds(bwd_dx_k<PT, NC, FINE>, lds);
+  static bool lds_set = false;
+  const hipError_t e = allow_lds(bwd_dx_k<PT, NC, FINE>, lds, lds_set);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
   hipLaunchKernelGGL((bwd_dx_k<PT, NC, FINE>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
@@ -946,7 +950,8 @@ bool bwd_conv_defers_blocks(const BwdConvArgs& g) {
 }
 
 hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s) {
-  static const hipError_t e = allow_lds(bwd_dw_k, 3 * kDwStage);
+  static bool lds_set = false;
+  const hipError_t e = allow_lds(bwd_dw_k, 3 * kDwStage, lds_set);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
   const bool per_head = a.w_head_stride != 0;

@@ -39,9 +39,12 @@ template <int KW, int NORM, int CIN>
 hipError_t launch(const ScanArgs& sa, const uint16_t* wp, int64_t wp_head_stride, const AttnArgs& at, int n_attn, hipStream_t s) {
   constexpr int lds = Geo<32, KW>::LDS;
   static_assert(lds >= attn_tile_detail::LDS_BYTES && lds >= (int)sizeof(attn_decode_detail::Parts), "one LDS area for all");
-  static const hipError_t e = hipFuncSetAttribute((const void*)compress_step_k<KW, NORM, CIN>,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  if (e != hipSuccess) return e;
+  static bool attr_set = false;   // benign race: setting it twice is harmless
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)compress_step_k<KW, NORM, CIN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
   const int n = sa.st.batch * sa.st.Hkv * (sa.st.M / 32);
   hipLaunchKernelGGL((compress_step_k<KW, NORM, CIN>), dim3(n + n_attn), dim3(kThreads), lds, s, sa, wp, wp_head_stride, n, at);
   return hipGetLastError();
