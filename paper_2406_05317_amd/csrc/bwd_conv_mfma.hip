@@ -267,7 +267,9 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
           sum *= f;
           dot *= f;
         }
-        ref = row_s[0][tid] = t;
+        ref = t;
+        // (a chunk whose positions are all protected: nothing to refer to yet, and -inf - -inf is no number)
+        row_s[0][tid] = MULTI && t == -INFINITY ? 0.f : t;
       }
       __syncthreads();
       rows(0);

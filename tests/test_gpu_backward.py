@@ -494,3 +494,36 @@ def test_step_backward_at_the_edges_of_the_row_kernel(case):
     for n in out[0]:
         assert np.isfinite(out[0][n]).all(), n
         assert _rel(out[0][n], out[1][n]) < 2e-4, (n, _rel(out[0][n], out[1][n]))
+
+
+@pytest.mark.parametrize("case", [
+    dict(B=512, M=1024, protected=512),                    # the first 512 of 1536 positions: the first of three chunks
+    dict(B=130, M=1024, protected=1023),                   # 1154 positions, three parts: one entry left in the first two chunks
+    dict(B=128, M=1024, protected=1000, norm=1),           # a rectified sum has no reference
+], ids=str)
+def test_step_backward_with_a_chunk_of_protected_slots(case):
+    """More positions than the row kernel holds at once are walked in chunks of 512; one whose positions are all protected
+    has no logit to refer the others to.  Against the fp32 vector kernels, with the bound of the test above."""
+    c = dict(case)
+    n = c.pop("protected")
+    w = inputs.Workload(name="bwdprot", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=1, head_dim=128, L=c["B"], seed=43,
+                        conv_gain=3.0, conv_width=3, **c)
+    rng = np.random.default_rng(13)
+    q, k, v = inputs.qkv(w)
+    cw, _ = inputs.conv_filters(w)
+    chains = (w.batch, w.n_kv_heads, w.M, w.head_dim)
+    ck = torch.as_tensor(rng.standard_normal(chains) * 0.5).to(w.torch_dtype)
+    cv = torch.as_tensor(rng.standard_normal(chains) * 0.5).to(w.torch_dtype)
+    d_o, gk, gv = rng.standard_normal(q.shape), rng.standard_normal(chains), rng.standard_normal(chains)
+    protect = np.broadcast_to(np.arange(w.M) < n, chains[:3]).copy()
+    out = []
+    for impl in (0, 1):
+        dW = torch.zeros(cw.shape, dtype=torch.float32, device="cuda")
+        r = _gpu_step_backward(w, lb.config_for(w, impl=impl), q, k, v, cw, None, ck, cv, w.M, d_o, gk, gv, dW, None, protect)
+        out.append({**r, "d_conv_w": dW.cpu().numpy()})
+    for name in out[0]:
+        assert np.isfinite(out[0][name]).all(), name
+        if not out[1][name].any():                         # (filters of slots that are all protected)
+            assert not out[0][name].any(), name
+        else:
+            assert _rel(out[0][name], out[1][name]) < 2e-4, (name, _rel(out[0][name], out[1][name]))
