@@ -422,7 +422,8 @@ hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_step
 bool attn_rows_fits(int T) { return T <= kRowsMaxT; }
 
 hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s) {
-  const int ld = a.M + a.B;
+  // the most positions a row can see: of a single block, its own (a large cache may have few live slots yet)
+  const int ld = (a.n_seg == 1 ? a.len0 : a.M) + a.B;
   const size_t lds = (size_t)4 * (d + ld) * sizeof(float);
   const dim3 grid((unsigned)(a.n_seg * ((a.B + 3) / 4)), a.Hq, a.batch);
   if (dtype == LOCOCO_F32) hipLaunchKernelGGL(attn_rows_k<float>, grid, dim3(256), lds, s, a, d, colsum, ld);

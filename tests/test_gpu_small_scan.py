@@ -44,3 +44,22 @@ def test_small_scans(case):
         assert a[3:] == other[3:]
         for x, y in zip(a[:3], other[:3]):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("case", [
+    dict(M=12000, B=16, L=40),                             # the LDS of a compute unit would not hold a row of M + B scores
+    dict(M=5000, B=16, L=40, dtype="bf16", n_q_heads=2),   # nor 64 KB four of them
+    dict(M=5000, B=700, L=2150, head_dim=16),              # past the 2048 positions a row may have: another kernel
+], ids=str)
+def test_first_blocks_of_a_large_cache(case):
+    """Few live slots in a cache far larger than the row attention's limit: what a block needs goes by what it sees."""
+    w = inputs.Workload(**{**dict(name="large", dtype="f32", batch=1, n_q_heads=1, n_kv_heads=1, head_dim=64, seed=37,
+                                  conv_width=3), **case})
+    q, k, v = inputs.qkv(w)
+    cw, cb = inputs.conv_filters(w)
+    want = oracle_forward(w, q, k, v, cw, cb)
+    a = gpu_forward(w, q, k, v, cw, cb, impl=1)
+    compare_scan(w, a, want, what="scan")
+    b = gpu_forward(w, q, k, v, cw, cb, impl=1, step_by_step=True)
+    for x, y in zip(a[:3], b[:3]):
+        assert torch.equal(x, y)
