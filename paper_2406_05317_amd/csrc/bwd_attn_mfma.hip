@@ -99,8 +99,8 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
       fq[ks] = *(const bf16x8*)(qp + ks * 16);
-      o0[ks] = *(const f32x4*)(op + ks * 16);
-      o1[ks] = *(const f32x4*)(op + ks * 16 + 4);
+      o0[ks] = *(const f32x4_any*)(op + ks * 16);
+      o1[ks] = *(const f32x4_any*)(op + ks * 16 + 4);
     }
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi)
-        *(f32x4*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
+        *(f32x4_any*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
   }
 }
 
@@ -385,7 +385,7 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
     for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi)
-        *(f32x4*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
+        *(f32x4_any*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
   }
 }
 

@@ -24,7 +24,6 @@ namespace lococo {
 namespace {
 
 constexpr int kD = 128;
-typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;      // the caller's gradients: any float address
 
 // 64 lanes x 16 bytes, lane l from its own address p into cell l of the 1 KB of LDS at lds_addr (see load_to_lds)
 __device__ __forceinline__ void gather_to_lds(const unsigned char* p, uint32_t lds_addr) {

@@ -527,3 +527,70 @@ def test_step_backward_with_a_chunk_of_protected_slots(case):
             assert not out[0][name].any(), name
         else:
             assert _rel(out[0][name], out[1][name]) < 2e-4, (name, _rel(out[0][name], out[1][name]))
+
+
+def _off_by_one_float(x):
+    """A copy of x that starts one float past a 16-byte boundary, and the buffer around it (NaN outside)."""
+    room = torch.full((x.numel() + 8,), float("nan"), device=x.device)
+    view = room[1:1 + x.numel()].view(x.shape)
+    view.copy_(x)
+    assert view.data_ptr() % 16 == 4
+    return view, room
+
+
+def _backward_of(w, entry, impl, off, len0=None):
+    """All gradients of one step (entry = "step") or scan with seeded inputs; `off`: every gradient array off by a float."""
+    dev, bf = "cuda", w.torch_dtype
+    g = torch.Generator(device=dev).manual_seed(6)
+    rnd = lambda *s, dt=torch.float32, sd=1.0: torch.empty(s, dtype=dt, device=dev).normal_(0, sd, generator=g)
+    d = w.head_dim
+    q = rnd(w.batch, w.n_q_heads, w.L, d, dt=bf, sd=0.3)
+    k, v = (rnd(w.batch, w.n_kv_heads, w.L, d, dt=bf, sd=0.3) for _ in range(2))
+    cw = rnd(w.M, d, w.conv_width, dt=bf, sd=0.05)
+    state = (w.batch, w.n_kv_heads, w.M, d)
+    cfg = lb.config_for(w, impl=impl)
+    cache = lb.Cache(cfg, dev)
+    cache.load(rnd(*state, dt=bf, sd=0.3), rnd(*state, dt=bf, sd=0.3), w.M if len0 is None else len0)
+    rooms = []
+    def place(x):
+        if not off:
+            return x
+        view, room = _off_by_one_float(x)
+        rooms.append((room, x.numel()))
+        return view
+    up = [place(rnd(*s)) for s in (q.shape, state, state)]
+    out = [place(torch.full(s, float("nan"), device=dev)) for s in (q.shape, k.shape, k.shape, state, state)]
+    dW = place(torch.zeros(cw.shape, device=dev))
+    if entry == "step":
+        ws = torch.empty(lb.lococo_backward_workspace_bytes(cfg, w.L, cache.len), dtype=torch.uint8, device=dev)
+        lb.lococo_segment_step_backward(cfg, q, k, v, cw, None, cache, *up, *out, dW, None, ws)
+    else:
+        ws = torch.empty(lb.lococo_sequence_backward_workspace_bytes(cfg, w.L, w.B), dtype=torch.uint8, device=dev)
+        lb.lococo_sequence_backward(cfg, q, k, v, w.B, cw, None, cache, *up, *out, dW, None, ws)
+    torch.cuda.synchronize()
+    for room, n in rooms:                                  # nothing was written around the arrays
+        assert torch.isnan(room[0]) and torch.isnan(room[n + 1:]).all()
+    return dict(zip(("dq", "dk", "dv", "d_cache_k", "d_cache_v", "d_conv_w"), out + [dW]))
+
+
+def _norm_err(x, y):
+    return float((x.double() - y.double()).norm() / y.double().norm().clamp_min(1e-30))
+
+
+@pytest.mark.parametrize("case", [
+    dict(entry="step", B=72, M=64, L=72),
+    dict(entry="step", B=70, M=160, L=70, n_q_heads=4),
+    dict(entry="scan", B=64, M=64, L=200),
+    dict(entry="step", B=72, M=64, L=72, head_dim=64),     # the plain contractions and the vector kernels
+    dict(entry="scan", B=64, M=64, L=200, head_dim=64),
+], ids=str)
+def test_gradients_at_any_float_address(case):
+    """Gradient arrays are asked to be contiguous floats, no more: views that start in the middle of sixteen bytes, against
+    the fp32 vector kernels with aligned ones."""
+    c = dict(case)
+    entry = c.pop("entry")
+    w = inputs.Workload(**{**dict(name="bwdoff", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=2, head_dim=128, conv_width=15,
+                                  seed=1), **c})
+    got, want = _backward_of(w, entry, 0, True), _backward_of(w, entry, 1, False)
+    for n in want:
+        assert _norm_err(got[n], want[n]) < (2e-4 if entry == "step" else 2e-3), (n, _norm_err(got[n], want[n]))
