@@ -1152,6 +1152,7 @@ lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool co
   c.n_blk = 1;
   c.B = g.st.Bn;
   c.banks = filter_banks(cfg);
+  c.three_parts = g.three_parts;
   c.tokens = g.st.Bn;
   c.d_cache_k = g.d_cache_k;
   c.d_cache_v = g.d_cache_v;
@@ -1223,6 +1224,8 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
   g.d_conv_w = d_conv_w;
   g.d_conv_b = d_conv_b;
   g.q_chain = g.kv_chain = (int64_t)B * cfg->head_dim;
+  // (with such arrays the plain contractions of a step do not take two halves: see bwd_gemms_mfma_fit)
+  g.three_parts = (((uintptr_t)d_o | (uintptr_t)d_new_k | (uintptr_t)d_new_v) & 15) != 0;
   if (bwd_attn_on_mfma(cfg, blk, B)) {
     BwdAttnArgs t{};
     t.a = attn_args_one_block(g.st);
@@ -1232,6 +1235,7 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
     t.d_v = d_v;
     t.d_ck = d_cache_k;
     t.d_cv = d_cache_v;
+    t.three_parts = g.three_parts;
     if ((st = enqueue_bwd_attn(cfg, t, B, (char*)workspace + l.p, (char*)workspace + l.ds, s))) return st;
     g.attn_done = 1;
   }

@@ -8,8 +8,9 @@
 //                   heads of the group.
 // The fp32 operands (dO, P, dS) enter the matrix products as two bf16 halves (16 bits kept): S 1, dP 2, dq 2, dYk 2,
 // dYv 3 products; with the recomputation 15 products per (query, key) pair of 128 columns.  A block whose number of
-// positions is no multiple of 4 enters with three parts (24 bits, nothing lost; dP, dq, dYk 3, dYv 6 products): such blocks
-// have always been computed in fp32, and errors stay at that level (3e-7 against 3.5e-6 with two).
+// positions is no multiple of 4, or a step whose gradients are not 16-byte aligned, enters with three parts (24 bits, nothing
+// lost; dP, dq, dYk 3, dYv 6 products): those have always been computed in fp32, and errors stay at that level (3e-7 against
+// 3.5e-6 with two).
 // Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.0 ms for the whole sequence (1.7 + 3.2) against 20.0 ms as
 // seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.28 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
@@ -414,7 +415,7 @@ hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
   // runs of blocks of one form: all of them as a rule, or all but a ragged last one
   auto parts = [&](int n) {
     const int64_t left = a.L - (int64_t)n * a.B;
-    return ((n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B)) % 4 ? 3 : 2;
+    return g.three_parts || ((n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B)) % 4 ? 3 : 2;
   };
   const int n_all = a.n_seg;
   hipError_t e = hipSuccess;

@@ -11,8 +11,8 @@
 // over the cache rows), and the rows of the blocks and the filter gradient follow in one launch each for the whole window.
 //
 // g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  In a
-// block whose number of positions is no multiple of 4, n and g enter as three parts (G 3 products, n g 6): Eq. 4 of such
-// blocks has always been computed in fp32, and its error stays at that level.  dl
+// block whose number of positions is no multiple of 4, and in a step whose gradients are not 16-byte aligned, n and g enter as
+// three parts (G 3 products, n g 6): Eq. 4 of those has always been computed in fp32, and its error stays at that level.  dl
 // and n are kept as "planes" [chain][32 slots][position][32 high halves | 32 low halves]: 128 bytes per position, read row
 // by row where the slots are contracted (bwd_dx_k) and down the rows where the positions are (bwd_dw_k).
 #include <algorithm>
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // chains, 512 slots and 1024 positions (155 GFLOP; 246 us as two kernels); without the matrix requests 140, with half of the
 // products 143: requests, fragment reads and products of a pair are a chain the two waves of a SIMD overlap in part.
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
-// FINE: the blocks whose n and g enter in three parts (m + Bn no multiple of 4).
+// FINE: the blocks whose n and g enter in three parts.
 template <int PT, int NC, bool FINE>
 __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -829,7 +829,7 @@ hipError_t allow_lds(F* k, int bytes, bool& done) {      // benign race: setting
 
 template <int NT, bool MULTI, int NORM>
 void launch_rows_norm(const BwdConvArgs& g, int blk, int T, int grid, hipStream_t s) {
-  if (T % 4 == 0) hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, NORM, 2>), dim3(grid), dim3(512), 0, s, g, blk);
+  if (T % 4 == 0 && !g.three_parts) hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, NORM, 2>), dim3(grid), dim3(512), 0, s, g, blk);
   else hipLaunchKernelGGL((bwd_rows_k<NT, MULTI, NORM, 3>), dim3(grid), dim3(512), 0, s, g, blk);
 }
 template <int NT, bool MULTI>
@@ -935,7 +935,7 @@ hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int par
   if (rows <= 0) return hipSuccess;
   auto fine = [&](int i) {
     const int64_t left = g.tokens - (int64_t)i * g.B;
-    return ((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4 != 0;
+    return g.three_parts || ((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4 != 0;
   };
   hipError_t e = hipSuccess;
   for (int i = blk0, n = 0; i < blk0 + n_blk && e == hipSuccess; i += n) {      // runs of blocks of one form

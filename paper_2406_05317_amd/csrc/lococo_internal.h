@@ -137,6 +137,7 @@ struct BwdArgs {
   int64_t q_chain, kv_chain;
   int32_t attn_done;       // the contributions of the attention are in d_q, d_k, d_v, d_cache_k, d_cache_v already
   int32_t conv_elsewhere;  // a compress step's Eq. 4 - 6 are the caller's (bwd_conv_mfma.hip): attention and dead rows only
+  int32_t three_parts;     // see BwdAttnArgs, BwdConvArgs
   int32_t gemms_mfma;      // the plain contractions may take their MFMA form (bf16 storage; see bwd_gemms_mfma_fit)
 };
 hipError_t launch_step_backward_generic(int dtype, const BwdArgs& g, bool compress, hipStream_t s);
@@ -232,7 +233,8 @@ hipError_t launch_attn_colsum_mfma(const AttnArgs& a, float* colsum, hipStream_t
 // the forward (seg_first is set inside; o not used).  Gradients fp32, rows of head_dim contiguous: d_o, d_q with the batch / head
 // strides q_sb, q_sh and d_k, d_v with k_sb, k_sh (elements; first row = first token of the window); d_ck, d_cv
 // [n_seg][chains][M][d], live rows only.  All outputs are assigned.  do_hl: scratch, 3 d bf16 per query row; stats: 3 fp32.
-// fp32 operands enter as two bf16 halves where a block's m + Bn is a multiple of 4, as three parts where it is not.
+// fp32 operands enter as two bf16 halves where a block's m + Bn is a multiple of 4, as three parts where it is not or where
+// three_parts is set.
 struct BwdAttnArgs {
   AttnArgs a;
   const float* d_o;
@@ -245,6 +247,7 @@ struct BwdAttnArgs {
   float* d_cv;
   uint16_t* do_hl;
   float* stats;
+  int32_t three_parts;
 };
 hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s);
 
@@ -285,6 +288,7 @@ bool bwd_mfma_supports(int dtype, int d, int conv_in, int conv_width);
 struct BwdConvArgs {
   StepArgs st;
   int32_t n_blk, B, banks;
+  int32_t three_parts;       // all blocks in three parts, whatever their positions
   int64_t tokens;            // of all blocks: the last one may be shorter than B
   int64_t state_stride;      // elements between the states
   float* d_cache_k;          // gradient w.r.t. the state before the first block (added to), d_stride floats to the next
