@@ -270,7 +270,7 @@ size_t history_ws_bytes(const lococo_config* c, Path path, int32_t B, int64_t n_
 
 // Whether the schedules that run the attention of many blocks in one launch exist for this shape
 bool batched_attention(const lococo_config* c, Path path, int32_t B) {
-  return path != PATH_GENERIC || attn_rows_fits(c->M + B);
+  return path != PATH_GENERIC || attn_rows_fits(c->M + B, c->head_dim);
 }
 
 // Polls a waiting workgroup makes before it gives up on its chain (each poll sleeps ~128 cycles and
@@ -446,7 +446,7 @@ lococo_status enqueue_attn(const lococo_config* c, Path path, const StepArgs& a,
     return LOCOCO_OK;
   }
   KTimer t(K_ATTN_GENERIC, s);
-  if (attn_rows_fits(a.m + a.Bn)) HIP_TRY(launch_attn_rows(c->dtype, attn_args_one_block(a), c->head_dim, a.colsum, s), "attention launch");
+  if (attn_rows_fits(a.m + a.Bn, a.d)) HIP_TRY(launch_attn_rows(c->dtype, attn_args_one_block(a), c->head_dim, a.colsum, s), "attention launch");
   else HIP_TRY(launch_attn_generic(c->dtype, a, s), "attention launch");
   return LOCOCO_OK;
 }

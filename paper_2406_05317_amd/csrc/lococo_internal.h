@@ -166,8 +166,8 @@ bool small_scan_one_launch(int T, int M, int d, int k, int conv_in);
 // taking the block s*B tokens further on (fewer where tokens_left runs out) and writing state (slot0 + s) % ring
 hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_steps, int B, int64_t tokens_left, void* out_k,
                                  void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s);
-// attention of the blocks of a window, a wave per query row; T: M + B
-bool attn_rows_fits(int T);
+// attention of the blocks of a window, a wave per query row; T: the most positions of a block
+bool attn_rows_fits(int T, int d);
 hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s);
 
 // largest T = m + Bn the generic attention kernel can hold in LDS

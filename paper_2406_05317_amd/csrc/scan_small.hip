@@ -10,6 +10,7 @@
 // Measured on that smallest scan (15 compressions): 1209 us with three kernels per step and one attention launch per
 // block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 105 us here (94 us the scan, 7 us the attention).
 #include <algorithm>
+#include <type_traits>
 
 #include "lococo_internal.h"
 
@@ -289,8 +290,8 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
 }
 
 // ---- attention of every block of a window in one launch (Alg. 2 step 3): one wave per query row, four rows of
-// a (block, head) per workgroup.  Scores: a lane per key; output: a lane per column.
-template <typename T>
+// a (block, head) per workgroup.  Scores: a lane per key; output: a lane per NC columns.
+template <typename T, int NC>
 __global__ __launch_bounds__(256) void attn_rows_k(AttnArgs a, int d, float* colsum, int ld) {
   extern __shared__ __align__(16) float sm[];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -341,25 +342,39 @@ __global__ __launch_bounds__(256) void attn_rows_k(AttnArgs a, int d, float* col
   if (colsum)                                        // accumulated attention per live cache slot
     for (int j = l; j < m; j += 64) atomicAdd(colsum + (int64_t)ch * a.M + j, sc[j] / z);
   T* o = (T*)a.o.p + b * a.o.sb + hq * a.o.sh + (tok0 + r) * a.o.st;
-  for (int c = l; c < d; c += 64) {
-    float s0 = 0.f, s1 = 0.f;
-    int j = 0;
-    const int mc = min(m, n_vis);
-    for (; j + 4 <= mc; j += 4) {
-      const float4 p = {sc[j], sc[j + 1], sc[j + 2], sc[j + 3]};
-      s0 = fmaf(p.x, to_f(cv[(int64_t)j * d + c]), s0);
-      s1 = fmaf(p.y, to_f(cv[(int64_t)(j + 1) * d + c]), s1);
-      s0 = fmaf(p.z, to_f(cv[(int64_t)(j + 2) * d + c]), s0);
-      s1 = fmaf(p.w, to_f(cv[(int64_t)(j + 3) * d + c]), s1);
-    }
-    for (; j < mc; ++j) s0 = fmaf(sc[j], to_f(cv[(int64_t)j * d + c]), s0);
-#pragma unroll 4
-    for (; j < n_vis; ++j) s1 = fmaf(sc[j], to_f(vb[(int64_t)(j - m) * a.v.st + c]), s1);
-    (void)store_f((s0 + s1) / z, o + c);
+  const int mc = min(m, n_vis);
+  int c[NC];
+  float s0[NC], s1[NC];
+#pragma unroll
+  for (int n = 0; n < NC; ++n) {
+    c[n] = min(64 * n + l, d - 1);                   // (a column past d is not stored)
+    s0[n] = s1[n] = 0.f;
   }
+  int j = 0;
+  for (; j + 4 <= mc; j += 4) {
+    const float4 p = {sc[j], sc[j + 1], sc[j + 2], sc[j + 3]};
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+      const T* vc = cv + (int64_t)j * d + c[n];
+      s0[n] = fmaf(p.x, to_f(vc[0]), s0[n]);
+      s1[n] = fmaf(p.y, to_f(vc[d]), s1[n]);
+      s0[n] = fmaf(p.z, to_f(vc[2 * d]), s0[n]);
+      s1[n] = fmaf(p.w, to_f(vc[3 * d]), s1[n]);
+    }
+  }
+  for (; j < mc; ++j)
+#pragma unroll
+    for (int n = 0; n < NC; ++n) s0[n] = fmaf(sc[j], to_f(cv[(int64_t)j * d + c[n]]), s0[n]);
+#pragma unroll 4
+  for (; j < n_vis; ++j)
+#pragma unroll
+    for (int n = 0; n < NC; ++n) s1[n] = fmaf(sc[j], to_f(vb[(int64_t)(j - m) * a.v.st + c[n]]), s1[n]);
+#pragma unroll
+  for (int n = 0; n < NC; ++n)
+    if (64 * n + l < d) (void)store_f((s0[n] + s1[n]) / z, o + c[n]);
 }
 
-constexpr int kRowsMaxT = 2048;
+constexpr int kRowsMaxT = 2048, kRowsMaxD = 128;
 
 // taps resident at once with one slot tile per workgroup (0: the positions do not fit, or too many units to keep
 // their sums in registers across the tap chunks)
@@ -419,15 +434,23 @@ hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_step
   return f32 ? launch<float, kMaxMix>(g, grid_x, s) : launch<bf16_t, kMaxMix>(g, grid_x, s);
 }
 
-bool attn_rows_fits(int T) { return T <= kRowsMaxT; }
+// The walk over the values is a chain of latencies, one wave's alone, so it is made once, for at most two columns a lane.  One
+// workgroup per row (attn_generic_k) is the better kernel for wider heads: 128 slots, one head, 16 tokens in fp32, with 64
+// columns 11.7 us against 16.1, with 128 16.6 against 17.4 (21.3 in two walks), with 256 39.3 (four walks) against 20.1.
+bool attn_rows_fits(int T, int d) { return T <= kRowsMaxT && d <= kRowsMaxD; }
 
 hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s) {
   // the most positions a row can see: of a single block, its own (a large cache may have few live slots yet)
   const int ld = (a.n_seg == 1 ? a.len0 : a.M) + a.B;
   const size_t lds = (size_t)4 * (d + ld) * sizeof(float);
   const dim3 grid((unsigned)(a.n_seg * ((a.B + 3) / 4)), a.Hq, a.batch);
-  if (dtype == LOCOCO_F32) hipLaunchKernelGGL(attn_rows_k<float>, grid, dim3(256), lds, s, a, d, colsum, ld);
-  else hipLaunchKernelGGL(attn_rows_k<bf16_t>, grid, dim3(256), lds, s, a, d, colsum, ld);
+  auto go = [&](auto nc) {
+    constexpr int NC = decltype(nc)::value;
+    if (dtype == LOCOCO_F32) hipLaunchKernelGGL((attn_rows_k<float, NC>), grid, dim3(256), lds, s, a, d, colsum, ld);
+    else hipLaunchKernelGGL((attn_rows_k<bf16_t, NC>), grid, dim3(256), lds, s, a, d, colsum, ld);
+  };
+  if (d <= 64) go(std::integral_constant<int, 1>{});
+  else go(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

@@ -63,3 +63,20 @@ def test_first_blocks_of_a_large_cache(case):
     b = gpu_forward(w, q, k, v, cw, cb, impl=1, step_by_step=True)
     for x, y in zip(a[:3], b[:3]):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d", [64, 65, 100, 128, 129])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_widths_around_the_columns_of_a_lane(d, dtype):
+    """Row attention with one column a lane, with two, the second one cut, and the first width that goes to a workgroup per row
+    (bf16 rows are 16-byte aligned: widths rounded up to a multiple of 8)."""
+    if dtype == "bf16":
+        d = (d + 7) // 8 * 8
+    w = inputs.Workload(name="width", dtype=dtype, batch=2, n_q_heads=2, n_kv_heads=1, head_dim=d, M=20, B=12, L=100, seed=41,
+                        conv_width=3)
+    q, k, v = inputs.qkv(w)
+    cw, cb = inputs.conv_filters(w)
+    a = gpu_forward(w, q, k, v, cw, cb, impl=1, history=True)
+    compare_scan(w, a, oracle_forward(w, q, k, v, cw, cb), what=f"d = {d}")
+    for x, y in zip(a[:3], gpu_forward(w, q, k, v, cw, cb, impl=1, history=False)[:3]):
+        assert torch.equal(x, y)
