@@ -268,9 +268,13 @@ size_t history_ws_bytes(const lococo_config* c, Path path, int32_t B, int64_t n_
   return step_ws_bytes(c, path, B) + stats_bytes(c, L) + 2 * (size_t)n_compress * align_up(state_bytes(c), 256);
 }
 
-// Whether the schedules that run the attention of many blocks in one launch exist for this shape
+// Whether the schedules that run the attention of many blocks in one launch exist for this shape.  On the shape-agnostic path
+// where the compression has its one kernel too: with the separate ones, step by step is the better schedule, each block's
+// attention bringing in the rows its compression reads (fp32, 8 heads of 128 on 2, ten blocks of 100 on 128 slots: 2.03 ms;
+// with the states apart and the attention behind them 2.25 ms).
 bool batched_attention(const lococo_config* c, Path path, int32_t B) {
-  return path != PATH_GENERIC || attn_rows_fits(c->M + B, c->head_dim);
+  if (path != PATH_GENERIC) return true;
+  return attn_rows_fits(c->M + B, c->head_dim) && small_step_fits(c->M + B, c->M, c->head_dim, c->conv_width, c->conv_in);
 }
 
 // Polls a waiting workgroup makes before it gives up on its chain (each poll sleeps ~128 cycles and
@@ -948,7 +952,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       StepArgs probe = make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true);
       one_launch = scan_fits_one_launch(cfg, probe);
     }
-    const bool small_scan = path == PATH_GENERIC && small_step_fits(cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in) &&
+    const bool small_scan = path == PATH_GENERIC &&
                             small_scan_one_launch(cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
     for (int64_t w0 = 0; w0 < n; w0 += window) {
