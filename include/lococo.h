@@ -365,6 +365,7 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *     out  d_q [batch, n_q_heads, L, d]; d_k, d_v [batch, n_kv_heads, L, d]; d_cache0_k, d_cache0_v
  *          [batch, n_kv_heads, M, d] (rows that were not live in cache0 are zero); all overwritten;
  *     acc  d_conv_w, d_conv_b: ADDED to, as in the step (d_conv_b may be NULL).
+ *     d_q may be the array d_o came in, d_cache0_k / d_cache0_v those of d_final_k / d_final_v.
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
  *   states per block (storage type), one step's worth of everything else and about 3 GiB at most for the window.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */

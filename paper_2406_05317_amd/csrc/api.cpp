@@ -1227,7 +1227,7 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
   g.d_cache_v = d_cache_v;
   g.d_conv_w = d_conv_w;
   g.d_conv_b = d_conv_b;
-  g.q_chain = g.kv_chain = (int64_t)B * cfg->head_dim;
+  g.o_chain = g.q_chain = g.kv_chain = (int64_t)B * cfg->head_dim;
   // (with such arrays the plain contractions of a step do not take two halves: see bwd_gemms_mfma_fit)
   g.three_parts = (((uintptr_t)d_o | (uintptr_t)d_new_k | (uintptr_t)d_new_v) & 15) != 0;
   if (bwd_attn_on_mfma(cfg, blk, B)) {
@@ -1288,6 +1288,7 @@ struct SeqBwdLayout {
   size_t d_ck, d_cv, slot;            // gradients w.r.t. the state before each of them, fp32, `slot` bytes each
   size_t hl, stats;       // scratch of the attention launches
   BwdConvLayout conv;     // of Eq. 4 - 6 (inside step_ws)
+  size_t d_o;             // a block's upstream gradient where the walk needs a copy of it (no windows)
   size_t g[2][2];         // gradient w.r.t. the cache state, ping-pong: [which][k, v], fp32 [chains, M, d]
   size_t step_ws;         // the window's Eq. 4 - 6, or the workspace of one backward step where there are no windows
   size_t total;
@@ -1331,6 +1332,8 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBw
       step = std::max(step, l.conv.total);
     }
   }
+  // (where the windows are not run after all, their scratch is idle)
+  l.d_o = l.window ? l.hl : take((size_t)c->batch * c->n_q_heads * B * c->head_dim * sizeof(float));
   for (int w = 0; w < 2; ++w)
     for (int kv = 0; kv < 2; ++kv) l.g[w][kv] = take(l.slot);
   l.step_ws = take(step);
@@ -1441,6 +1444,26 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   if (!gk) { gk = (const float*)(ws + l.g[0][0]); HIP_TRY(launch_zero_fill(ws + l.g[0][0], gbytes, s), "clearing the final gradient"); }
   if (!gv) { gv = (const float*)(ws + l.g[0][1]); HIP_TRY(launch_zero_fill(ws + l.g[0][1], gbytes, s), "clearing the final gradient"); }
   const bool batched = l.window > 0 && bwd_attn_on_mfma(cfg, seq, B);
+  // The step's kernels write d_q, d_k and d_v before the last of them has read d_o, and d_cache0 before d_final: where these
+  // share memory, what comes in is read from a copy.  So is what the plain contractions on the matrix cores could not read
+  // where it is (see bwd_gemms_mfma_fit).
+  const size_t q_bytes = (size_t)cfg->batch * cfg->n_q_heads * (size_t)L * d * sizeof(float), kv_bytes = chains * (size_t)L * d * sizeof(float);
+  auto shared = [](const void* a, size_t na, const void* b, size_t nb) {
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+  };
+  auto unaligned = [&](const void* p) { return cfg->dtype == LOCOCO_BF16 && ((uintptr_t)p & 15); };
+  const bool copy_d_o = !batched && (unaligned(d_o) || shared(d_o, q_bytes, d_q, q_bytes) || shared(d_o, q_bytes, d_k, kv_bytes) ||
+                                     shared(d_o, q_bytes, d_v, kv_bytes));
+  if (!batched) {
+    const float** from[2] = {&gk, &gv};
+    for (int x = 0; x < 2; ++x) {
+      const float* p = *from[x];
+      float* own = (float*)(ws + l.g[0][x]);
+      if (p == own || !(unaligned(p) || shared(p, gbytes, d_cache0_k, gbytes) || shared(p, gbytes, d_cache0_v, gbytes))) continue;
+      HIP_TRY(hipMemcpyAsync(own, p, gbytes, hipMemcpyDeviceToDevice, s), "copying the final gradient");
+      *from[x] = own;
+    }
+  }
   const int64_t G = batched ? l.window : n;
   bool conv_begun = false;
   int w = 1;
@@ -1540,6 +1563,14 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
       BwdArgs g{};
       g.st = make_args(cfg, &blk, sg.start, sg.len, &before, conv_w, conv_b, true);
       g.d_o = d_o + sg.start * (int64_t)d;
+      g.o_chain = L * (int64_t)d;
+      if (copy_d_o) {
+        const size_t row = (size_t)sg.len * d * sizeof(float);
+        HIP_TRY(hipMemcpy2DAsync(ws + l.d_o, row, g.d_o, (size_t)L * d * sizeof(float), row, (size_t)cfg->batch * cfg->n_q_heads,
+                                 hipMemcpyDeviceToDevice, s), "copying a block's upstream gradient");
+        g.d_o = (const float*)(ws + l.d_o);
+        g.o_chain = sg.len * (int64_t)d;
+      }
       g.d_new_k = gk;
       g.d_new_v = gv;
       g.d_q = d_q + sg.start * (int64_t)d;

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_scores_k(BwdArgs g) {
   const int hq = blockIdx.z % a.Hq, b = blockIdx.z / a.Hq, hkv = hq / a.group;
   if (j0 > a.m + r0 + kAT - 1) return;             // the whole tile lies after its queries
   const int tr = threadIdx.x / 16, tj = threadIdx.x % 16;
-  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, q0 = ((int64_t)b * a.Hq + hq) * g.q_chain;
+  const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, o0 = ((int64_t)b * a.Hq + hq) * g.o_chain;
   float accs[4][4], accp[4][4];
 #pragma unroll
   for (int ii = 0; ii < 4; ++ii)
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_scores_k(BwdArgs g) {
       if (cc < d) {
         if (r0 + x < a.Bn) {
           qv = to_f(((const T*)a.q.p + b * a.q.sb + hq * a.q.sh + (int64_t)(r0 + x) * a.q.st)[cc]);
-          ov = g.d_o[q0 + (int64_t)(r0 + x) * d + cc];
+          ov = g.d_o[o0 + (int64_t)(r0 + x) * d + cc];
         }
         if (j0 + x < Tn) {
           kv = to_f(cat_row<T>(a.cache_k, a.k, a.M, d, a.m, b, hkv, a.Hkv, j0 + x)[cc]);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_cols_k(BwdArgs g) {
     for (int q = 0; q < 4; ++q) acck[jj][q] = accv[jj][q] = 0.f;
   for (int hh = 0; hh < a.group; ++hh) {
     const int hq = hkv * a.group + hh;
-    const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, q0 = ((int64_t)b * a.Hq + hq) * g.q_chain;
+    const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.Bn, o0 = ((int64_t)b * a.Hq + hq) * g.o_chain;
     for (int rc = rbeg; rc < a.Bn; rc += kAK) {
       __syncthreads();
       for (int e = threadIdx.x; e < kAK * kAT; e += kThreads) {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void bwd_attn_cols_k(BwdArgs g) {
         Ps[rr][x] = in ? g.ws_p[(row0 + r) * Tn + j0 + x] : 0.f;
         const bool inc = r < a.Bn && c0 + x < d;
         Qs[rr][x] = inc ? to_f(((const T*)a.q.p + b * a.q.sb + hq * a.q.sh + (int64_t)r * a.q.st)[c0 + x]) : 0.f;
-        Os[rr][x] = inc ? g.d_o[q0 + (int64_t)r * d + c0 + x] : 0.f;
+        Os[rr][x] = inc ? g.d_o[o0 + (int64_t)r * d + c0 + x] : 0.f;
       }
       __syncthreads();
 #pragma unroll

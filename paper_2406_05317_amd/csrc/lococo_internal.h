@@ -111,7 +111,7 @@ struct AttnArgs {
 
 // Arguments of the backward pass of one block step (backward_generic.hip).  `st` describes the
 // step as for the forward (cache = state before the step).  Gradients are fp32, contiguous:
-// d_o, d_q [batch, Hq, .., d] with q_chain elements between heads, d_k, d_v [batch, Hkv, .., d] with kv_chain (the block's
+// d_o [batch, Hq, .., d] with o_chain elements between heads, d_q with q_chain, d_k, d_v [batch, Hkv, .., d] with kv_chain (the block's
 // rows of longer arrays, or the block alone); d_new_k/v, d_cache_k/v [chains, M, d];
 // d_conv_w / d_conv_b laid out like conv_w / conv_b (added to).  Workspace: ws_p, ws_ds
 // [batch, Hq, Bn, T] (attention rows and their gradient), ws_w [chains, M, T] (raw logits on entry,
@@ -134,7 +134,7 @@ struct BwdArgs {
   float* ws_w;
   float* ws_n;
   float* ws_dw;
-  int64_t q_chain, kv_chain;
+  int64_t o_chain, q_chain, kv_chain;
   int32_t attn_done;       // the contributions of the attention are in d_q, d_k, d_v, d_cache_k, d_cache_v already
   int32_t conv_elsewhere;  // a compress step's Eq. 4 - 6 are the caller's (bwd_conv_mfma.hip): attention and dead rows only
   int32_t three_parts;     // see BwdAttnArgs, BwdConvArgs

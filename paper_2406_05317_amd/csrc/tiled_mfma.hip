@@ -684,7 +684,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_gemm_k(OpA A, OpB B, Out out,
 // `grouped`: z is a chain and the memory row runs over the rows of all query heads of its group,
 // head-major; otherwise z is (batch entry, query head).  Every width is a multiple of 4 and every base
 // 16-byte aligned (the launcher checks), so a group of four is inside or outside as a whole.
-struct Dims { int Bn, Tn, d, M, m, Hq, Hkv, group; int64_t q_chain, kv_chain; };
+struct Dims { int Bn, Tn, d, M, m, Hq, Hkv, group; int64_t o_chain, q_chain, kv_chain; };
 __device__ __forceinline__ void head_row(const Dims& s, bool grouped, int z, int r, int& b, int& hq, int& rr) {
   if (grouped) {
     b = z / s.Hkv;
@@ -843,9 +843,10 @@ hipError_t launch_gemm(const OpA& A, const OpB& B, const Out& out, int I, int J,
   return hipGetLastError();
 }
 
-Dims dims_of(const StepArgs& a) { return Dims{a.Bn, a.m + a.Bn, a.d, a.M, a.m, a.Hq, a.Hkv, a.group, 0, 0}; }
+Dims dims_of(const StepArgs& a) { return Dims{a.Bn, a.m + a.Bn, a.d, a.M, a.m, a.Hq, a.Hkv, a.group, 0, 0, 0}; }
 Dims dims_of(const BwdArgs& g) {
   Dims s = dims_of(g.st);
+  s.o_chain = g.o_chain;
   s.q_chain = g.q_chain;
   s.kv_chain = g.kv_chain;
   return s;
@@ -947,7 +948,7 @@ hipError_t launch_bwd_attn_scores_mfma(const BwdArgs& g, hipStream_t s) {
   hipError_t e = launch_gemm(OpQ<false>{dm, a.q, false}, OpY<false, 0>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
                              OutRows{dm, g.ws_p, a.scale}, a.Bn, dm.Tn, a.d, Z, s);
   if (e != hipSuccess) return e;
-  return launch_gemm(OpRowsF32<false>{dm, g.d_o, dm.q_chain, a.d, false}, OpY<false, 1>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
+  return launch_gemm(OpRowsF32<false>{dm, g.d_o, dm.o_chain, a.d, false}, OpY<false, 1>{dm, a.cache_k, a.cache_v, a.k, a.v, true},
                      OutRows{dm, g.ws_ds, 1.0f}, a.Bn, dm.Tn, a.d, Z, s);
 }
 
@@ -963,7 +964,7 @@ hipError_t launch_bwd_attn_grads_mfma(const BwdArgs& g, hipStream_t s) {
   e = launch_gemm(OpRowsF32<true>{dm, g.ws_ds, (int64_t)a.Bn * dm.Tn, dm.Tn, true}, OpQ<true>{dm, a.q, true},
                   OutGrad<false>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 0}, dm.Tn, a.d, a.group * a.Bn, chains, s);
   if (e != hipSuccess) return e;
-  return launch_gemm(OpRowsF32<true>{dm, g.ws_p, (int64_t)a.Bn * dm.Tn, dm.Tn, true}, OpRowsF32<true>{dm, g.d_o, dm.q_chain, a.d, true},
+  return launch_gemm(OpRowsF32<true>{dm, g.ws_p, (int64_t)a.Bn * dm.Tn, dm.Tn, true}, OpRowsF32<true>{dm, g.d_o, dm.o_chain, a.d, true},
                      OutGrad<false>{dm, g.d_cache_k, g.d_k, g.d_cache_v, g.d_v, 1}, dm.Tn, a.d, a.group * a.Bn, chains, s);
 }
 

@@ -620,3 +620,42 @@ def test_steps_whose_operands_enter_in_three_parts(case):
     print({n: f"{e:.1e}" for n, e in errs.items()})
     for n in want:
         assert errs[n] < bound[n], (n, errs[n])
+
+
+@pytest.mark.parametrize("case", [
+    dict(dtype="f32", head_dim=32, L=77, B=12, M=30, conv_width=5, len0=0),
+    dict(dtype="f32", head_dim=32, L=12, B=12, M=16, conv_width=5, len0=16),       # one block: it is the last and the first
+    dict(dtype="bf16", head_dim=64, L=96, B=32, M=48, conv_width=5, len0=40),      # the plain contractions
+    dict(dtype="bf16", head_dim=128, L=200, B=64, M=64, conv_width=15, len0=64),
+    dict(dtype="bf16", head_dim=128, L=64, B=64, M=64, conv_width=15, len0=64),
+], ids=str)
+def test_scan_backward_in_place(case):
+    """d_q may be the array d_o came in, and d_cache0_k / v those of d_final_k / v: same results as with arrays apart."""
+    c = dict(case)
+    len0 = c.pop("len0")
+    w = inputs.Workload(**{**dict(name="inplace", batch=2, n_q_heads=2, n_kv_heads=2, seed=3), **c})
+    dev = "cuda"
+    g = torch.Generator(device=dev).manual_seed(2)
+    rnd = lambda *s, dt=w.torch_dtype: torch.empty(s, dtype=dt, device=dev).normal_(0, 0.3, generator=g)
+    d, state = w.head_dim, (w.batch, w.n_kv_heads, w.M, w.head_dim)
+    q, k, v = rnd(w.batch, w.n_q_heads, w.L, d), rnd(w.batch, w.n_kv_heads, w.L, d), rnd(w.batch, w.n_kv_heads, w.L, d)
+    cw, ck, cv = rnd(w.M, d, w.conv_width), rnd(*state), rnd(*state)
+    d_o, d_fk, d_fv = (rnd(*s, dt=torch.float32) for s in (q.shape, state, state))
+    cfg = lb.config_for(w)
+    cache = lb.Cache(cfg, dev)
+    cache.load(ck, cv, len0)
+    ws = torch.empty(lb.lococo_sequence_backward_workspace_bytes(cfg, w.L, w.B), dtype=torch.uint8, device=dev)
+    out = []
+    for same in (False, True):
+        up = [t.clone() for t in (d_o, d_fk, d_fv)]
+        dq, dck, dcv = up if same else [torch.full_like(t, float("nan")) for t in up]
+        dk, dv = torch.full(k.shape, float("nan"), device=dev), torch.full(k.shape, float("nan"), device=dev)
+        dW = torch.zeros(cw.shape, device=dev)
+        lb.lococo_sequence_backward(cfg, q, k, v, w.B, cw, None, cache, *up, dq, dk, dv, dck, dcv, dW, None, ws)
+        torch.cuda.synchronize()
+        out.append(dict(dq=dq, dk=dk, dv=dv, d_cache0_k=dck, d_cache0_v=dcv, d_conv_w=dW))
+    for n in out[0]:
+        if n == "d_conv_w":                      # (atomic sums)
+            assert _norm_err(out[1][n], out[0][n]) < 1e-5, n
+        else:
+            assert torch.equal(out[1][n], out[0][n]), (n, _norm_err(out[1][n], out[0][n]))
