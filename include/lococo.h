@@ -368,6 +368,8 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *     d_q may be the array d_o came in, d_cache0_k / d_cache0_v those of d_final_k / d_final_v.
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
  *   states per block (storage type), one step's worth of everything else and about 3 GiB at most for the window.
+ *   With less the window is as many blocks as fit; LOCOCO_EWORKSPACE, and the least there has to be in
+ *   lococo_last_error(), where one does not.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */
 LOCOCO_API lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg, int64_t L, int32_t B,
                                                                   size_t* out);

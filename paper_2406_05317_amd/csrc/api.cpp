@@ -1297,7 +1297,8 @@ struct SeqBwdLayout {
 // sequence.
 constexpr size_t kBwdWindowBytes = (size_t)3 << 30;
 
-lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBwdLayout* out) {
+// largest_window: blocks a window may have at most
+lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64_t largest_window, SeqBwdLayout* out) {
   SeqBwdLayout l{};
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
@@ -1322,7 +1323,7 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, SeqBw
     }
     // (blocks x chains and 4 x blocks are grid dimensions)
     const int64_t most = std::min<int64_t>((int64_t)(kBwdWindowBytes / per_block), (int64_t)(8192 / chains));
-    l.window = std::max<int64_t>(1, std::min<int64_t>(n, most));
+    l.window = std::max<int64_t>(1, std::min<int64_t>({n, most, largest_window}));
     l.d_ck = take((size_t)l.window * l.slot);
     l.d_cv = take((size_t)l.window * l.slot);
     l.hl = take(bwd_attn_hl_bytes(c, l.window * (int64_t)B));
@@ -1351,7 +1352,7 @@ lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg,
   if (!out) return fail(LOCOCO_EINVAL, "out is NULL");
   if (L < 0 || B <= 0) return fail(LOCOCO_EINVAL, "need L >= 0 and B > 0");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, &l))) return st;
   *out = l.total;
   return LOCOCO_OK;
 }
@@ -1384,7 +1385,16 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   for (const auto& sg : plan) any_compress |= sg.branch == 1;
   if (any_compress && (!conv_w || !d_conv_w)) return fail(LOCOCO_EINVAL, "conv_w or d_conv_w is NULL but the scan compresses");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, &l))) return st;
+  if (ws_bytes < l.total && l.window > 1) {    // the largest window that fits (a layout's size grows with its window)
+    int64_t fits = 1, not_fits = l.window;
+    while (not_fits - fits > 1) {
+      const int64_t mid = (fits + not_fits) / 2;
+      if ((st = seq_bwd_layout(cfg, L, B, mid, &l))) return st;
+      (l.total <= ws_bytes ? fits : not_fits) = mid;
+    }
+    if ((st = seq_bwd_layout(cfg, L, B, fits, &l))) return st;
+  }
   if (!workspace || ws_bytes < l.total || ((uintptr_t)workspace & 255))
     return fail(LOCOCO_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)", l.total,
                 workspace ? ws_bytes : (size_t)0);

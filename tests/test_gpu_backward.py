@@ -659,3 +659,48 @@ def test_scan_backward_in_place(case):
             assert _norm_err(out[1][n], out[0][n]) < 1e-5, n
         else:
             assert torch.equal(out[1][n], out[0][n]), (n, _norm_err(out[1][n], out[0][n]))
+
+
+@pytest.mark.parametrize("case", [
+    dict(L=10 * 64 + 30, B=64, M=64, len0=0),                                # a fill block, compress blocks, a ragged one
+    dict(L=600, B=24, M=96, len0=50, batch=2, n_q_heads=4, conv_width=21, conv_in=1, norm=1),
+], ids=str)
+def test_scan_backward_takes_a_smaller_workspace(case):
+    """As many blocks to a window as the workspace holds, down to one: the same gradients up to the order of the sums over
+    blocks; less than that is refused."""
+    c = dict(case)
+    len0 = c.pop("len0")
+    w = inputs.Workload(**{**dict(name="smaller", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=2, head_dim=128, conv_width=15,
+                                  seed=8), **c})
+    dev = "cuda"
+    g = torch.Generator(device=dev).manual_seed(5)
+    rnd = lambda *s, dt=torch.bfloat16, sd=0.3: torch.empty(s, dtype=dt, device=dev).normal_(0, sd, generator=g)
+    state = (w.batch, w.n_kv_heads, w.M, 128)
+    q, k, v = rnd(w.batch, w.n_q_heads, w.L, 128), rnd(w.batch, w.n_kv_heads, w.L, 128), rnd(w.batch, w.n_kv_heads, w.L, 128)
+    cw, ck, cv = rnd(w.M, 256 if w.conv_in else 128, w.conv_width, sd=0.05), rnd(*state), rnd(*state)
+    up = [rnd(*s, dt=torch.float32) for s in (q.shape, state, state)]
+    cfg = lb.config_for(w)
+    cache = lb.Cache(cfg, dev)
+    cache.load(ck, cv, len0)
+
+    def run(n_bytes):
+        out = [torch.full(s, float("nan"), device=dev) for s in (q.shape, k.shape, k.shape, state, state)]
+        dW = torch.zeros(cw.shape, device=dev)
+        room = torch.full((n_bytes + 4096,), 77, dtype=torch.uint8, device=dev)
+        lb.lococo_sequence_backward(cfg, q, k, v, w.B, cw, None, cache, *up, *out, dW, None, room[:n_bytes])
+        torch.cuda.synchronize()
+        assert (room[n_bytes:] == 77).all()                # nothing past the workspace
+        return out + [dW]
+
+    full = lb.lococo_sequence_backward_workspace_bytes(cfg, w.L, w.B)
+    with pytest.raises(lb.LococoError, match="workspace needs") as e:
+        run(256)
+    assert e.value.status == lb.LOCOCO_EWORKSPACE
+    least = int(str(e.value).split("workspace needs ")[1].split()[0])
+    assert least < full / 3
+    with pytest.raises(lb.LococoError):
+        run(least - 256)
+    want = run(full)
+    for n_bytes in (full - 256, (full + 2 * least) // 3 // 256 * 256, least):
+        for name, x, y in zip(("dq", "dk", "dv", "d_cache0_k", "d_cache0_v", "d_conv_w"), run(n_bytes), want):
+            assert _norm_err(x, y) < 1e-5, (n_bytes, name, _norm_err(x, y))
