@@ -1115,8 +1115,8 @@ BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   l.w = l.ds + std::max(align_up(rows, 256), bwd_attn_stat_bytes(c, B));
   l.n = l.w + mat;
   l.dw = l.n + mat;
-  l.conv = l.dw + mat;
-  l.total = l.conv + (conv ? conv_layout(c, (int32_t)T, 1).total : 0);
+  l.conv = 0;                                  // Eq. 4 - 6 on MFMA come when the attention is done with its arrays
+  l.total = std::max(l.dw + mat, conv ? conv_layout(c, (int32_t)T, 1).total : (size_t)0);
   return l;
 }
 // The attention of the blocks of `t` (see BwdAttnArgs; the gradient arrays hold `rows` query / block rows per head from
