@@ -53,7 +53,7 @@ KERNEL_PARTS = {
     "attn_generic": ("attn",), "attn_mfma": ("attn",),
     "conv_logits_generic": ("conv",), "mix_generic": ("mix",),
     "conv_logits_mfma": ("conv",), "mix_mfma": ("mix",),
-    "compress_mfma": ("conv", "mix"),
+    "compress_mfma": ("conv", "mix"), "compress_small": ("conv", "mix"),
 }
 KERNEL_BOUND = {  # roofline that bounds each kernel, peak, unit
     "attn_generic": ("mfma", PEAK_BF16_MFMA_TFLOPS, "TFLOP/s"),
@@ -274,7 +274,9 @@ def decode_bench(args, w, lb, inputs, torch):
     flops = step_flops(w, w.M, 1)
     name = max(kt, key=lambda n: kt[n][1])
     launches, total_ms = kt[name]
-    part = sum(flops[p] for p in KERNEL_PARTS.get(name, ())) * args.steps
+    # (with no attention kernel of its own, the step's attention ran in the compression's launch)
+    parts = KERNEL_PARTS.get(name, ()) + (("attn",) if name == "compress_mfma" and not any(n.startswith("attn") for n in kt) else ())
+    part = sum(flops[p] for p in parts) * args.steps
     achieved = part / (total_ms * 1e-3) / 1e12 if total_ms > 0 else 0.0
     out = {"metric": "generation-stage tokens/sec per layer (segment step with B = 1: attention, conv logits, "
                      "normalisation, fusion per token)",
@@ -321,6 +323,10 @@ def backward_scan_bench(args, w, lb, inputs, torch):
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) * 1e3 / args.steps
     kt = lb.lococo_timing_end()
+    # the recomputed recurrence may run as the one-launch scan, whose waits can give up
+    if lb.lococo_scan_status(cfg, ws) != 0:
+        print("bench.py: a chain wait inside the one-launch scan gave up; the run is invalid", file=sys.stderr)
+        sys.exit(3)
     print(json.dumps({"metric": "backward of the whole scan, tokens/sec per layer", "value": w.batch * w.L / (ms * 1e-3),
                       "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
                       "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
@@ -334,7 +340,7 @@ def backward_scan_bench(args, w, lb, inputs, torch):
 
 def backward_bench(args, w, lb, inputs, torch):
     """Backward of one compress step (full cache, one block).  --impl 1: every kernel shape-agnostic,
-    fp32 vector arithmetic; default: the three Eq. 5 contractions on the matrix cores."""
+    fp32 vector arithmetic; default: every contraction, and Eq. 6 with its gradient between them, on the matrix cores."""
     dev = "cuda"
     w = w.replace(name=w.name + "-backward-step", L=w.B)
     cfg = lb.config_for(w, impl=args.impl)
@@ -368,7 +374,8 @@ def backward_bench(args, w, lb, inputs, torch):
     peak = PEAK_FP32_VALU_TFLOPS if generic else PEAK_BF16_MFMA_TFLOPS
     print(json.dumps({"metric": "backward of one compress step, tokens/sec per layer (%s)" %
                                 ("shape-agnostic fp32 kernels" if generic else
-                                 "contractions on bf16 MFMA with fp32 operands as two bf16 halves, row reductions fp32 vector"),
+                                 "contractions on bf16 MFMA with fp32 operands as two bf16 halves (three where m + B is no multiple of 4), "
+                                 "row reductions fp32 vector"),
                       "value": w.batch * w.B / (ms * 1e-3), "unit": "tokens/s", "n_gpus": 1, "steps": args.steps,
                       "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
                       "vs_baseline": None, "dtype": "f32" if generic else "bf16", "data": "synthetic",
