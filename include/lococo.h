@@ -174,7 +174,8 @@ LOCOCO_API lococo_status lococo_plan(int64_t L, int32_t B, int32_t M, int32_t le
  *   history = 0: the step-by-step schedule (one block's scratch);
  *   history = 1: room for the cache state after every block, with which
  *                lococo_sequence_forward runs the whole compression scan first and then
- *                all blocks' attention as one batched launch;
+ *                all blocks' attention as one batched launch (on the shape-agnostic path
+ *                where a block's whole compression is one kernel; else as history = 0);
  *   history = G >= 2: room for a window of G blocks (G + 1 cache states): the same
  *                schedule window by window, memory independent of L.
  * The three schedules return the same bits: which kernel a block's attention runs on depends
@@ -239,21 +240,21 @@ LOCOCO_API lococo_status lococo_sequence_forward(const lococo_config* cfg, const
                                       lococo_cache* cache, void* workspace, size_t ws_bytes,
                                       void* stream);
 
-/* When lococo_sequence_forward runs a whole scan's compression steps in one launch, the
- * workgroups that share a chain wait for each other between steps with a bounded number of
+/* When lococo_sequence_forward, or lococo_sequence_backward for the states it walks back through, runs a whole scan's
+ * compression steps in one launch, the workgroups that share a chain wait for each other between steps with a bounded number of
  * polls (a few seconds).  That form is chosen only when the whole grid can be resident at once
  * (the runtime's occupancy figure for the kernel) and no other such launch of this process is
  * still running on another stream of the device; otherwise every step gets a launch of its own.
  * Work from elsewhere that keeps compute units busy for longer than the bound (another process, a
  * long kernel on another stream) can still make a wait run out: the kernel then leaves early, a
- * status word in the workspace is set, and THE OUTPUTS AND THE CACHE OF THAT CALL ARE INVALID
- * although it returned LOCOCO_OK at enqueue time.  A caller that shares the GPU must therefore
- * check lococo_scan_status() == 0 before it uses the results of a lococo_sequence_forward call
- * made with the larger (history) workspace; a caller that has the GPU to itself need not.
+ * status word in the workspace is set, and THE OUTPUTS AND THE CACHE (or the gradients, those added to d_conv_w and d_conv_b
+ * among them) OF THAT CALL ARE INVALID although it returned LOCOCO_OK at enqueue time.  A caller that shares the GPU must
+ * therefore check lococo_scan_status() == 0 before it uses the results of a lococo_sequence_forward call made with the larger
+ * (history) workspace or of a lococo_sequence_backward call; a caller that has the GPU to itself need not.
  *
  * This call SYNCHRONISES with the device and returns that word in *out: 0 = fine, 1 = a wait
  * gave up.  `workspace` is the one passed to lococo_sequence_forward (at least
- * lococo_workspace_bytes(history = 0) bytes); the word is cleared at the start of every such call
+ * lococo_workspace_bytes(history = 0) bytes) or to lococo_sequence_backward; the word is cleared at the start of every such call
  * and means nothing before the first one.  Configurations the MFMA kernels do not serve never
  * wait: *out is 0.  Under stream capture the in-flight check is skipped: replays of graphs that
  * hold such a scan must not overlap each other on one device. */
@@ -335,10 +336,12 @@ LOCOCO_API lococo_status lococo_mix_from_logits(const lococo_config* cfg, const 
  *          NULL) are ADDED to, so one buffer collects the whole scan; untouched by a fill step.
  *   workspace: lococo_backward_workspace_bytes(cfg, B, cache_before->len) bytes, 256-byte aligned.
  * Any shape; fp32 vector arithmetic, except that with bf16 storage and cfg->impl !=
- * LOCOCO_IMPL_GENERIC the contractions run on the matrix cores, every fp32 operand entering as
- * the sum of two bf16 numbers (about 16 bits kept): all of them with head_dim 128 and a filter width up to 31, the
- * plain ones (attention and Eq. 4) of other shapes when block length + live slots is a multiple of 4.  Filter gradients are summed
- * with floating-point atomics, so their last bits depend on the order. */
+ * LOCOCO_IMPL_GENERIC the contractions run on the matrix cores: the attention's with head_dim 128, the others with a filter
+ * width up to 31 as well.  Every fp32 operand enters as the sum of two bf16 numbers (about 16 bits kept) where block length +
+ * live slots is a multiple of 4 and d_o, d_new_k and d_new_v are 16-byte aligned, otherwise of three (all 24), but for the
+ * gradient of the logits: always two.  Of other shapes the plain contractions (attention and Eq. 4) do, in two, under the
+ * same condition and with head_dim a multiple of 4.  Filter gradients are summed with floating-point atomics, so their last
+ * bits depend on the order. */
 LOCOCO_API lococo_status lococo_backward_workspace_bytes(const lococo_config* cfg, int32_t B, int32_t len, size_t* out);
 LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococo_qkvo* blk, int32_t B,
                                            const void* conv_w, const void* conv_b,
@@ -387,7 +390,8 @@ LOCOCO_API lococo_status lococo_sequence_backward(const lococo_config* cfg, cons
  * lococo_timing_end() waits for those events and returns one row per kernel
  * that ran: its name (static storage), the number of launches and the summed
  * device time in milliseconds.  *n_inout: capacity of `out` on entry, rows
- * available on return.  Host pointers.  Meant for benchmarks; not thread safe
+ * available on return.  A lococo_segment_step whose attention shares the compression's launch is one
+ * row, "compress_mfma"; the backward's own kernels have none.  Host pointers.  Meant for benchmarks; not thread safe
  * against concurrent begin/end. */
 typedef struct lococo_kernel_time {
   const char* name;

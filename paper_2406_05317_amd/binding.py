@@ -335,7 +335,8 @@ def lococo_sequence_backward(cfg, q, k, v, B: int, conv_w, conv_b, cache: Cache,
 
 
 def lococo_scan_status(cfg, workspace) -> int:
-    """Synchronises; 0 = fine, 1 = a chain wait inside a one-launch scan gave up."""
+    """Synchronises; 0 = fine, 1 = a chain wait inside the one-launch scan of the lococo_sequence_forward or
+    lococo_sequence_backward call that had this workspace gave up: its results are invalid."""
     out = C.c_int32(0)
     _check(lib().lococo_scan_status(C.byref(cfg), _ptr(workspace), C.byref(out)))
     return out.value

@@ -11,8 +11,8 @@
 // positions is no multiple of 4, or a step whose gradients are not 16-byte aligned, enters with three parts (24 bits, nothing
 // lost; dP, dq, dYk 3, dYv 6 products): those have always been computed in fp32, and errors stay at that level (3e-7 against
 // 3.5e-6 with two).
-// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.0 ms for the whole sequence (1.7 + 3.2) against 20.0 ms as
-// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.28 against
+// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.3 ms for the whole sequence (2.1 + 3.3) against 20.0 ms as
+// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.27 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
 // between the products (matrix pipe 45 % busy in the first kernel, 27 % in the second).
 // D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.

@@ -636,8 +636,9 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
 // ---- dW: a workgroup per (128 slots, 128 columns, two taps) and share of the contraction over (block, chain, position),
 // in stages of 32 positions.  The plane rows and the entries' rows (33 of them: the two taps are one row apart) come two
 // stages ahead into a ring of three; both operands are read down their rows, and the fragments of dl serve both taps.
-// Sums go to dwt [bank][tap][slot][channel] with atomics, once per workgroup.  Bound by the products: 127 us a block of 32
-// chains, 512 slots and 1024 positions, 1.0 PFLOP/s (210 us with a tap per workgroup and the atomics once per block).
+// Sums go to dwt [bank][tap][slot][channel] with atomics, once per workgroup.  Bound by the products: 99 us a block of 32
+// chains, 512 slots and 1024 positions in windows of nine, 1.3 PFLOP/s (210 us with a tap per workgroup and the atomics once
+// per block).
 constexpr int kDwDl = 4 * 32 * 128, kDwX = 36 * 256, kDwStage = kDwDl + kDwX;
 __global__ __launch_bounds__(256, 2) void bwd_dw_k(BwdConvArgs g, int groups, int n_units, int spu) {
   extern __shared__ __align__(16) unsigned char smem[];

@@ -376,8 +376,8 @@ __global__ __launch_bounds__(256) void attn_rows_k(AttnArgs a, int d, float* col
 
 constexpr int kRowsMaxT = 2048, kRowsMaxD = 128;
 
-// taps resident at once with one slot tile per workgroup (0: the positions do not fit, or too many units to keep
-// their sums in registers across the tap chunks)
+// taps resident at once with one slot tile per workgroup (0: the positions do not fit, or with the taps in chunks a wave
+// would have more than one unit, whose sums it leaves in LDS between the chunks)
 int taps_that_fit(int T, int d, int k, int conv_in) {
   if (2 * ((d + 15) / 16) > kNW * kMaxMix) return 0;
   for (int taps = k; taps >= 1; --taps) {
@@ -436,7 +436,7 @@ hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_step
 
 // The walk over the values is a chain of latencies, one wave's alone, so it is made once, for at most two columns a lane.  One
 // workgroup per row (attn_generic_k) is the better kernel for wider heads: 128 slots, one head, 16 tokens in fp32, with 64
-// columns 11.7 us against 16.1, with 128 16.6 against 17.4 (21.3 in two walks), with 256 39.3 (four walks) against 20.1.
+// columns 11.5 us against 16.4, with 128 16.3 against 17.3 (21.2 in two walks), with 256 39.1 (four walks) against 19.9.
 bool attn_rows_fits(int T, int d) { return T <= kRowsMaxT && d <= kRowsMaxD; }
 
 hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s) {

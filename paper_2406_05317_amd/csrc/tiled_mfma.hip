@@ -1,9 +1,10 @@
 // LDS-tiled bf16 MFMA kernels for the contractions outside the two fused forward kernels:
 //  * Eq. 5 as a kernel of its own (keys-only or [K | V] filters, any odd width up to 31), used by the
 //    forward path for compressors the fused kernel is not built for and by the backward pass to
-//    recompute the logits;
-//  * one batched GEMM kernel (bwd_gemm_k) whose instances are the seven plain contractions of the
-//    backward pass (attention and Eq. 4) and Eq. 4 of the unfused forward path.
+//    recompute the logits of the blocks of a window;
+//  * one batched GEMM kernel (bwd_gemm_k) whose instances are Eq. 4 of the unfused forward path and the
+//    seven plain contractions of a step's backward (attention and Eq. 4) where bwd_attn_mfma.hip and
+//    bwd_conv_mfma.hip do not take them: head_dim other than 128, wider filters, rows too far apart.
 //
 //   logits[i, j]  = b[i] + sum_t sum_c Wc[i, c, t] X[j + t - p, c]
 //
