@@ -131,15 +131,15 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
       for (int p = 0; p < PARTS; ++p) dp = mfma32(fv, fo[ks][p], dp);
     }
   };
-  // keys this lane's query does not see: score -inf
-  auto mask = [&](int t, int kt, f32x16& sc) {
+  // keys this lane's query does not see: score -inf, and no part in anything however bad their values are
+  auto mask = [&](int t, int kt, f32x16& sc, f32x16& dp) {
     const bool blk = t >= NTc;
     const int row0 = (blk ? t - NTc : t) * 64 + kt * 32;
     if (blk ? row0 + 31 > wq0 : row0 + 32 > s.m) {
       const int lim = blk ? qrow : s.m - 1;
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        if (row0 + (i >> 2) * 8 + lh * 4 + (i & 3) > lim) sc[i] = -INFINITY;
+        if (row0 + (i >> 2) * 8 + lh * 4 + (i & 3) > lim) { sc[i] = -INFINITY; dp[i] = 0.f; }
     }
   };
   auto visible = [&](int t, int kt) {       // uniform: some query of this wave sees a key of this half tile
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
       if (!visible(t, kt)) continue;
       f32x16 sc, dp;
       products(K, kt, sc, dp);
-      mask(t, kt, sc);
+      mask(t, kt, sc, dp);
       float mx = sc[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, sc[i]);
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
       if (!visible(t, kt)) continue;
       f32x16 sc, dp;
       products(K, kt, sc, dp);
-      mask(t, kt, sc);
+      mask(t, kt, sc, dp);
       float ds[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) ds[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mc)) * ps * (dp[i] - D);
@@ -325,13 +325,16 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
       float p[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mcs[i >> 2][i & 3])) * inv[i >> 2][i & 3];
-      if (rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m)) {
+      auto hide = [&]() {                   // pairs of a key and a query that does not see it
+        if (rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m)) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int r = rb + (i >> 2) * 8 + lh * 4 + (i & 3);
-          if (r >= s.Bn || j - s.m > r) p[i] = 0.f;
+          for (int i = 0; i < 16; ++i) {
+            const int r = rb + (i >> 2) * 8 + lh * 4 + (i & 3);
+            if (r >= s.Bn || j - s.m > r) p[i] = 0.f;
+          }
         }
-      }
+      };
+      if (for_v) hide();
       if (for_v) {
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
@@ -360,6 +363,7 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) p[gi * 4 + e] *= (dp[gi * 4 + e] - dd[e]) * a.scale;
         }
+        hide();                             // (here, so that a query that is no number stays out of later keys' gradients)
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
           bf16x8 fd[PARTS];

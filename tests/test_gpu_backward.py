@@ -704,3 +704,38 @@ def test_scan_backward_takes_a_smaller_workspace(case):
     for n_bytes in (full - 256, (full + 2 * least) // 3 // 256 * 256, least):
         for name, x, y in zip(("dq", "dk", "dv", "d_cache0_k", "d_cache0_v", "d_conv_w"), run(n_bytes), want):
             assert _norm_err(x, y) < 1e-5, (n_bytes, name, _norm_err(x, y))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("B", [100, 200])
+def test_a_bad_token_stays_out_of_what_does_not_see_it(B, bad):
+    """A fill step (no compression, which mixes everything) with one entry of a query, or of a value row, that is no number:
+    the gradients of keys and values behind the query's token, and of queries before the value's, do not depend on it."""
+    w = inputs.Workload(name="bad", dtype="bf16", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=128, L=B, B=B, M=256, conv_width=15)
+    dev, r0, col, m = "cuda", 41, 7, 37
+    g = torch.Generator(device=dev).manual_seed(9)
+    rnd = lambda *s, dt=torch.float32: torch.empty(s, dtype=dt, device=dev).normal_(0, 0.5, generator=g)
+    state = (1, 2, w.M, 128)
+    cw, ck, cv = (rnd(*s, dt=torch.bfloat16) for s in ((w.M, 128, 15), state, state))
+    up = [rnd(*s) for s in ((1, 4, B, 128), state, state)]
+    for which in ("q", "v"):
+        for impl in (0, 1):
+            q, k, v = (rnd(1, h, B, 128, dt=torch.bfloat16) for h in (4, 2, 2))
+            (q if which == "q" else v)[0, 1, r0, col] = bad
+            cfg = lb.config_for(w, impl=impl)
+            cache = lb.Cache(cfg, dev)
+            cache.load(ck, cv, m)
+            dq, dk, dv = (torch.full(t.shape, float("nan"), device=dev) for t in (q, k, v))
+            dck, dcv = torch.empty(state, device=dev), torch.empty(state, device=dev)
+            ws = torch.empty(lb.lococo_backward_workspace_bytes(cfg, B, m), dtype=torch.uint8, device=dev)
+            lb.lococo_segment_step_backward(cfg, q, k, v, cw, None, cache, *up, dq, dk, dv, dck, dcv,
+                                            torch.zeros(cw.shape, device=dev), None, ws)
+            torch.cuda.synchronize()
+            if which == "q":                     # head 1 reads the keys of kv head 0; 0 x bad in its own column
+                others = torch.arange(128, device=dev) != col
+                assert torch.isfinite(dk[0, 0, r0 + 1:][:, others]).all() and torch.isfinite(dk[0, 1]).all(), impl
+                assert torch.isfinite(dv[0, :, r0 + 1:]).all() and torch.isfinite(dv[0, 1]).all(), impl
+                assert torch.isfinite(dq[0, [0, 2, 3]]).all() and torch.isfinite(dq[0, 1, torch.arange(B) != r0]).all(), impl
+            else:                                # the values of kv head 1 are those of heads 2 and 3
+                assert torch.isfinite(dq[0, :2]).all() and torch.isfinite(dq[0, 2:, :r0]).all(), impl
+                assert torch.isfinite(dv).all(), impl
