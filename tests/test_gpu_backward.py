@@ -318,8 +318,8 @@ def test_sequence_backward_matches_the_oracle_walked_in_reverse(case):
 
 def test_sequence_backward_equals_the_steps_composed_by_hand_on_the_matrix_cores():
     """bf16, head_dim 128: the one-call scan backward against lococo_segment_step (forward, keeping the
-    states) and lococo_segment_step_backward (reverse) called block by block: the same launches, so equal
-    up to the order of the filter gradients' atomic sums.  Also: the filter gradient against a central
+    states) and lococo_segment_step_backward (reverse) called block by block: the same products, a window of
+    blocks to a launch or one, so equal up to the order of sums.  Also: the filter gradient against a central
     difference of the ORACLE forward (bf16 inputs, exact arithmetic) along a random direction."""
     w = inputs.Workload(name="bwdseq_mfma", dtype="bf16", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=128, L=4 * 48 + 16,
                         B=48, M=64, conv_width=15, seed=5, conv_gain=3.0)
