@@ -8,7 +8,10 @@
 // whole chain fits one workgroup (filters included) the steps of a scan therefore run in ONE launch, the cache
 // rows staying in LDS from step to step; otherwise each step is one launch of a workgroup per 16 slots.
 // Measured on that smallest scan (15 compressions): 1209 us with three kernels per step and one attention launch per
-// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 105 us here (94 us the scan, 7 us the attention).
+// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 81 us here, of which the scan 70: 9 900 cycles a
+// step, 2 800 of them Eq. 5 and 2 000 Eq. 6 (12 900 before operand reads were issued in groups ahead of their products,
+// reductions left the LDS crossbar and divisions the index arithmetic; 104 us in all).  Drawn scans of one to four heads of
+// 64, 12 - 96 slots: 1.13 - 1.39 times as fast as before that.
 #include <algorithm>
 #include <type_traits>
 
@@ -39,6 +42,26 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// v combined over the 32 lanes of each half of a wave, on the vector unit alone
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <typename Op>
+__device__ __forceinline__ float over32(float v, Op op) {
+  v = op(v, dpp<0xB1>(v));                   // quad_perm [1,0,3,2]
+  v = op(v, dpp<0x4E>(v));                   // quad_perm [2,3,0,1]
+  v = op(v, dpp<0x141>(v));                  // row_half_mirror
+  v = op(v, dpp<0x140>(v));                  // row_mirror
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// u / n for small numbers (exact below two million): the integer division is a chain of some forty instructions
+__device__ __forceinline__ int small_div(int u, int n) {       // (both uniform)
+  return __builtin_amdgcn_readfirstlane((int)(((float)u + 0.5f) * __builtin_amdgcn_rcpf((float)n)));
+}
+
 constexpr int kNT = 512, kNW = kNT / 64;     // threads, waves
 constexpr int kPG = 2;                       // position tiles of 16 per unit of Eq. 5
 constexpr int kMaxMix = 8;                   // 16 x 16 tiles of Eq. 4 a wave holds at once
@@ -54,7 +77,9 @@ __host__ __device__ inline int odd4(int n) {
 
 // Parts the inner dimension of Eq. 5 is shared out in where a slot tile has fewer units than there are waves.  A
 // function of the positions alone, so that every form of the launch adds up in the same order.
-__host__ __device__ inline int planes_of(int pg) { return pg >= kNW ? 1 : kNW / pg; }
+static_assert(kNW == 8, "eight waves over the parts");
+__host__ __device__ inline int log_planes_of(int pg) { return pg == 1 ? 3 : pg == 2 ? 2 : pg <= 4 ? 1 : 0; }
+__host__ __device__ inline int planes_of(int pg) { return 1 << log_planes_of(pg); }
 
 struct SmallLayout {
   int tiles;          // slot tiles of 16 per workgroup
@@ -95,7 +120,8 @@ struct SmallArgs {
 };
 
 // One workgroup: 16 l.tiles slots of one chain.  n_steps > 1 only where those are all slots of the chain.
-template <typename T, int MIX>     // MIX: 16 x 16 tiles of Eq. 4 per wave
+// MIX: 16 x 16 tiles of Eq. 4 per wave.  D: head_dim where it is a constant (0: any).
+template <typename T, int MIX, int D>
 __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   extern __shared__ __align__(16) float sm[];
   const StepArgs& a = g.st;
@@ -104,9 +130,9 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   float* Vs = sm + L.off_v;
   float* Ls = sm + L.off_l;
   float* Ws = sm + L.off_w;
-  int tid = threadIdx.x, w = tid >> 6, l = tid & 63, l15 = l & 15, lk = l >> 4;
+  int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l15 = l & 15, lk = l >> 4;
   const int ch = blockIdx.y, b = ch / a.Hkv, hkv = ch % a.Hkv, i0 = blockIdx.x * 16 * L.tiles;
-  const int d = a.d, C = a.conv_in ? 2 * d : d, C4 = (C + 3) / 4, k = a.k_width, pad = (k - 1) / 2, M = a.M;
+  const int d = D ? D : a.d, C = a.conv_in ? 2 * d : d, C4 = (C + 3) / 4, k = a.k_width, pad = (k - 1) / 2, M = a.M;
   const T* wbase = (const T*)a.conv_w + hkv * a.w_head_stride;
   const T* bias = a.conv_b ? (const T*)a.conv_b + hkv * a.b_head_stride : nullptr;
   const uint32_t* protect = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
@@ -141,22 +167,27 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   const bool resident = L.taps == k;
   if (resident) load_filters(0, k);
 
+  int slot = g.slot0 % g.ring;
   for (int step = 0;; ++step) {
-    asm volatile("" : "+v"(tid), "+v"(w), "+v"(l15), "+v"(lk));   // addresses belong to the step: hoisted, they all spill
+    asm volatile("" : "+v"(tid), "+s"(w), "+v"(l15), "+v"(lk));   // addresses belong to the step: hoisted, they all spill
     const int Tn = m + Bn, pg = (Tn + 16 * kPG - 1) / (16 * kPG), units = L.tiles * pg;
-    const int planes = planes_of(pg), sl = odd4(32 * pg), plane = L.tiles * 16 * sl;
+    const int log_planes = log_planes_of(pg), planes = 1 << log_planes, sl = odd4(32 * pg), plane = L.tiles * 16 * sl;
     const int64_t next_tok = (int64_t)(step + 1) * g.B;
     const bool more = step + 1 < g.n_steps;
     const int Bnext = more ? (int)min((int64_t)g.B, g.tokens_left - next_tok) : 0;
     // the next block's first values, in flight under this step
     float pk[kPF], pv[kPF];
+    {
+      const T* kp = kb + next_tok * a.k.st;
+      const T* vp = vb + next_tok * a.v.st;
 #pragma unroll
-    for (int n = 0; n < kPF; ++n) {
-      const int e = tid + n * kNT;
-      if (e < Bnext * d) {
-        const int64_t tok = next_tok + e / d;
-        pk[n] = to_f(kb[tok * a.k.st + e % d]);
-        pv[n] = to_f(vb[tok * a.v.st + e % d]);
+      for (int n = 0; n < kPF; ++n) {
+        if (n * kNT >= Bnext * d) break;
+        const int e = tid + n * kNT;
+        if (e < Bnext * d) {
+          pk[n] = to_f(kp[(int64_t)(e / d) * a.k.st + e % d]);
+          pv[n] = to_f(vp[(int64_t)(e / d) * a.v.st + e % d]);
+        }
       }
     }
     __syncthreads();
@@ -169,26 +200,57 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
         __syncthreads();
       }
       for (int u = w; u < units * planes; u += kNW) {
-        const int part = u / units, uu = u % units, st = uu / pg, p0 = (uu % pg) * 16 * kPG;
+        const int part = small_div(u, units), uu = u - part * units, st = small_div(uu, pg), p0 = (uu - st * pg) * 16 * kPG;
         f32x4 acc[kPG];
         float* out = Ls + part * plane + (st * 16 + l15) * sl + p0 + 4 * lk;
 #pragma unroll
         for (int x = 0; x < kPG; ++x) acc[x] = t0 ? *(const f32x4*)(out + 16 * x) : f32x4{0.f, 0.f, 0.f, 0.f};
         // this part's channels, tap by tap: the order of the sum does not depend on how the taps are brought in
-        const int k0 = C4 * part / planes, k1 = C4 * (part + 1) / planes;
-        for (int t = 0; t < nt; ++t) {
-          const float* wb = Ws + ((st * L.taps + t) * C4 * 4 + lk) * 16 + l15;
-          const float* xb = Xs + (p0 + l15 + t0 + t) * L.sx + lk;
-          for (int kk = k0; kk < k1; ++kk) {
-            const float fb = wb[kk * 64];
+        const int k0 = C4 * part >> log_planes, k1 = C4 * (part + 1) >> log_planes;
+        const float* wb = Ws + (st * L.taps * C4 * 4 + lk) * 16 + l15 + k0 * 64;
+        const float* xb = Xs + (p0 + l15 + t0) * L.sx + lk + 4 * k0;
+        // KN channel groups at a time, TN taps of them in flight together: a wave's operand reads are what it waits for
+        auto taps = [&](auto kn, auto tn, auto rect) {
+          constexpr int KN = decltype(kn)::value, TN = decltype(tn)::value;
+          auto some = [&](auto n_t, int kc) {
+            constexpr int N = decltype(n_t)::value;
+            float fb[N][KN], fa[N][KN][kPG];
 #pragma unroll
-            for (int x = 0; x < kPG; ++x) {
-              float fa = xb[16 * x * L.sx + 4 * kk];
-              if (a.norm == 2) fa = fmaxf(fa, 0.f);        // the rectifier in front of the convolution
-              acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa, fb, acc[x], 0, 0, 0);
-            }
-          }
-        }
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+              for (int q = 0; q < KN; ++q) {
+                fb[t][q] = wb[(t * C4 + kc + q) * 64];
+#pragma unroll
+                for (int x = 0; x < kPG; ++x) fa[t][q][x] = xb[(16 * x + t) * L.sx + 4 * (kc + q)];
+              }
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+              for (int q = 0; q < KN; ++q)
+#pragma unroll
+                for (int x = 0; x < kPG; ++x) {
+                  if (decltype(rect)::value) fa[t][q][x] = fmaxf(fa[t][q][x], 0.f);   // the rectifier in front of the convolution
+                  acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[t][q][x], fb[t][q], acc[x], 0, 0, 0);
+                }
+          };
+          int t = 0;
+          if (TN > 1)
+#pragma clang loop unroll(disable)
+            for (; t + TN <= nt; t += TN, wb += TN * C4 * 64, xb += TN * L.sx) some(tn, 0);
+#pragma clang loop unroll(disable)
+          for (; t < nt; ++t, wb += C4 * 64, xb += L.sx)
+#pragma clang loop unroll(disable)
+            for (int kc = 0; kc < k1 - k0; kc += KN) some(std::integral_constant<int, 1>{}, kc);
+        };
+        auto widths = [&](auto rect) {
+          const int kn = k1 - k0;
+          if (kn == 2) taps(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{}, rect);
+          else if (kn == 4) taps(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{}, rect);
+          else if (kn % 8 == 0) taps(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{}, rect);
+          else taps(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}, rect);
+        };
+        if (a.norm == 2) widths(std::true_type{});
+        else widths(std::false_type{});
 #pragma unroll
         for (int x = 0; x < kPG; ++x) *(f32x4*)(out + 16 * x) = acc[x];
       }
@@ -203,22 +265,27 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
       float mx = -INFINITY;
       for (int j = c; j < Tn; j += 32) {
         float x = r[j] + bi;
-        for (int p = 1; p < planes; ++p) x += r[p * plane + j];
+        if (planes == kNW) {
+          float more_x[kNW - 1];
+#pragma unroll
+          for (int p = 1; p < kNW; ++p) more_x[p - 1] = r[p * plane + j];
+#pragma unroll
+          for (int p = 1; p < kNW; ++p) x += more_x[p - 1];
+        } else {
+          for (int p = 1; p < planes; ++p) x += r[p * plane + j];
+        }
         if (protect && j < m && ((protect[j >> 5] >> (j & 31)) & 1u)) x = soft ? -INFINITY : 0.f;
         r[j] = x;
         mx = fmaxf(mx, x);
       }
-      if (soft)
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 32));
+      if (soft) mx = over32(mx, [](float x, float y) { return fmaxf(x, y); });
       float z = 0.f;
       for (int j = c; j < Tn; j += 32) {
         const float x = r[j], e = soft ? expf(x - mx) : a.norm == 1 ? fmaxf(x, 0.f) : (isfinite(x) ? x : 0.f);
         r[j] = e;
         z += e;
       }
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) z += __shfl_xor(z, o, 32);
+      z = over32(z, [](float x, float y) { return x + y; });
       if (a.norm == 1) z += a.eps;
       if (a.norm == 2 && fabsf(z) < a.eps) z = z < 0.f ? -a.eps : a.eps;
       for (int j = c; j < Tn; j += 32) r[j] /= z;
@@ -233,26 +300,41 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
       const int u = w + n * kNW;
       acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (u < mix_units) {
-        const int st = u / (2 * ct), cu = u % (2 * ct), c = (cu % ct) * 16 + l15;
+        const int st = small_div(u, 2 * ct), cu = u - st * 2 * ct;
         const bool val = cu >= ct;
+        const int c = (val ? cu - ct : cu) * 16 + l15;
         const int stride = val && L.sv ? L.sv : L.sx;
         const float* wr = Ls + (st * 16 + l15) * sl + lk;
         const float* yr = (val ? yv(0) : Xs + pad * L.sx) + lk * stride + (c < d ? c : 0);   // a column past d is dropped
+        int kk = 0;
 #pragma clang loop unroll(disable)
-        for (int kk = 0; kk < k4; ++kk, wr += 4, yr += 4 * stride)
+        for (; kk + 8 <= k4; kk += 8, wr += 32, yr += 32 * stride) {    // eight groups of operands in flight
+          float fw[8], fy[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            fw[q] = wr[4 * q];
+            fy[q] = yr[4 * q * stride];
+          }
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[q], fy[q], acc[n], 0, 0, 0);
+        }
+#pragma clang loop unroll(disable)
+        for (; kk < k4; ++kk, wr += 4, yr += 4 * stride)
           acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(*wr, *yr, acc[n], 0, 0, 0);
       }
     }
     __syncthreads();                                       // every read of the old rows is done
-    const int64_t state = ((int64_t)((g.slot0 + step) % g.ring)) * g.out_stride + (int64_t)ch * M * d;
+    const int64_t state = (int64_t)slot * g.out_stride + (int64_t)ch * M * d;
+    if (++slot == g.ring) slot = 0;
     T* ok = (T*)g.out_k + state;
     T* ov = (T*)g.out_v + state;
 #pragma unroll
     for (int n = 0; n < MIX; ++n) {
       const int u = w + n * kNW;
       if (u >= mix_units) continue;
-      const int st = u / (2 * ct), cu = u % (2 * ct), c = (cu % ct) * 16 + l15;
+      const int st = small_div(u, 2 * ct), cu = u - st * 2 * ct;
       const bool val = cu >= ct;
+      const int c = (val ? cu - ct : cu) * 16 + l15;
       if (c >= d) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -269,6 +351,7 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
     // ---- the next block behind the new cache; zeros up to the end of what this step's rows used
 #pragma unroll
     for (int n = 0; n < kPF; ++n) {
+      if (n * kNT >= Bnext * d) break;
       const int e = tid + n * kNT;
       if (e < Bnext * d) {
         Xs[(pad + M + e / d) * L.sx + e % d] = pk[n];
@@ -387,16 +470,22 @@ int taps_that_fit(int T, int d, int k, int conv_in) {
   return 0;
 }
 
-template <typename T, int MIX>
-hipError_t launch(const SmallArgs& g, int grid_x, hipStream_t s) {
+template <typename T, int MIX, int D>
+hipError_t launch_d(const SmallArgs& g, int grid_x, hipStream_t s) {
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)compress_small_k<T, MIX>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    hipError_t e = hipFuncSetAttribute((const void*)compress_small_k<T, MIX, D>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((compress_small_k<T, MIX>), dim3(grid_x, g.st.batch * g.st.Hkv), dim3(kNT), g.l.bytes, s, g);
+  hipLaunchKernelGGL((compress_small_k<T, MIX, D>), dim3(grid_x, g.st.batch * g.st.Hkv), dim3(kNT), g.l.bytes, s, g);
   return hipGetLastError();
+}
+// A step of the smallest scans is a few hundred cycles of dependent work in each of its passes: indices that need a division by
+// the head_dim are a good part of it, so the one these scans are used with has a build of its own.
+template <typename T, int MIX>
+hipError_t launch(const SmallArgs& g, int grid_x, hipStream_t s) {
+  return g.st.d == 64 ? launch_d<T, MIX, 64>(g, grid_x, s) : launch_d<T, MIX, 0>(g, grid_x, s);
 }
 
 }  // namespace
