@@ -175,19 +175,17 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {             // eight columns of a row of [g_k | g_v] per item
     const int it = tid + i * 512, r = it >> 5, c8 = it & 31, val = c8 >> 4;
-    const bool in = s0 + r < a.M;
-    const float* p = (val ? gv : gk) + (int64_t)(in ? s0 + r : 0) * kD + (c8 & 15) * 8;
+    const float* p = (val ? gv : gk) + (int64_t)min(s0 + r, a.M - 1) * kD + (c8 & 15) * 8;
     const f32x4_any v0 = *(const f32x4_any*)p, v1 = *(const f32x4_any*)(p + 4);
-    const float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+    float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+    if (s0 + r >= a.M)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = 0.f;
     bf16x8 part[PARTS];
     split_parts<PARTS>(v, part);
     const int at = r * 256 + (((c8 & 15) ^ swz(r)) << 4);
 #pragma unroll
-    for (int u = 0; u < PARTS; ++u) {
-      *(bf16x8*)(Gs[u][val] + at) = part[u];
-      if (in)                               // for bwd_dx_k: [part][chain][slot][K | V]
-        *(bf16x8*)(gsp + (((int64_t)u * a.batch * a.Hkv + ch) * a.M + s0 + r) * (2 * kD) + c8 * 8) = part[u];
-    }
+    for (int u = 0; u < PARTS; ++u) *(bf16x8*)(Gs[u][val] + at) = part[u];
   }
   int ga[8];
 #pragma unroll
@@ -210,6 +208,18 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   request_entries(w * 32, 0);
   request_entries(w * 32, 1);
   __syncthreads();
+  {                                         // g for bwd_dx_k, as operand fragments: wave w the columns 32 w .. of [K | V]
+    const int s16 = l & 15, g2 = (l >> 4) & 1, chunk = (w & 3) * 4 + 2 * g2 + ((s16 & 3) >> 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = h * 16 + lh * 8 + (s16 >> 2), r4 = r + 4;
+      const int at = r * 256 + ((chunk ^ swz(r)) << 4) + (s16 & 1) * 8, at4 = r4 * 256 + ((chunk ^ swz(r4)) << 4) + (s16 & 1) * 8;
+#pragma unroll
+      for (int u = 0; u < PARTS; ++u)
+        *(bf16x8*)(gsp + ((((int64_t)u * a.batch * a.Hkv + ch) * tiles * 2 + sb * 2 + h) * 8 + w) * 512 + l * 8) =
+            frag_tr(Gs[u][w >> 2] + at, Gs[u][w >> 2] + at4);
+    }
+  }
 
   auto contract = [&](int pc) {
 #pragma unroll
@@ -400,22 +410,31 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 }
 
 // ---- dX: a workgroup per (PT positions, NC key or value columns) of a chain and block, contraction over the slots in
-// chunks of 64.  A chunk is a phase with dl (one product per tap: its rows, shifted, times that tap's filters) and one with
-// n (times the two halves of g), worked through in pairs of products with one barrier each.  The eight waves split each
-// chunk four ways (16 slots each) and the outputs two ways; the four partial sums meet in LDS at the end.  Everything
-// arrives by loads that write LDS directly: the next pair's 64 x NC right-hand matrices and the next phase's plane rows
-// (with their halo) while a pair is worked on.  Rows outside the sequence read as zero (buffer bounds).  161 us a step of 32
-// chains, 512 slots and 1024 positions (155 GFLOP; 246 us as two kernels); without the matrix requests 140, with half of the
-// products 143: requests, fragment reads and products of a pair are a chain the two waves of a SIMD overlap in part.
+// chunks of 16 KS.  A chunk is a phase with dl (one product per tap: its rows, shifted, times that tap's filters) and one
+// with n (times the parts of g).  Eight waves split a chunk KS ways (16 slots each) and the columns 8 / KS ways; the partial
+// sums meet in LDS at the end.  No two waves want the same filters, so these come from memory straight into the registers,
+// packed in fragment order, D taps ahead: within a phase there is nothing to meet for, and only the plane rows (which the
+// taps read at shifted rows) pass through LDS, by loads that write it directly, a phase or more ahead.  Rows outside the
+// sequence read as zero (buffer bounds).  (Filters through LDS, two taps a barrier: requests, fragment reads and products
+// were a chain that the two waves of a SIMD overlapped in part.)
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
 // FINE: the blocks whose n and g enter in three parts.
-template <int PT, int NC, bool FINE>
-__global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
+template <int PT, int NC, int KS, bool FINE>
+struct Dx {
+  static constexpr int CW = 8 / KS, PB = PT / 32, CB = NC / 32 / CW;     // column groups; 32 x 32 output blocks of a wave
+  static constexpr int PL = KS / 2, DR = PT + 32;                        // 32-slot planes of a chunk; rows with the halo
+  static constexpr int DB = PL * DR * 128, NB = PL * PT * 128;           // bytes of a chunk's rows of dl, of n
+  static constexpr int ND = DB / 8192, NN = NB / 8192;                   // requests of a wave for them
+  static constexpr int D = 3;                                            // taps of filters in flight (a divisor of 15 and 21)
+  static constexpr int rings = 2 * DB + (FINE ? 2 : 1) * NB, sums = 8 * 32 * 256;
+  static constexpr int lds = rings > sums ? rings : sums;
+  static_assert(DB % 8192 == 0 && NB % 8192 == 0, "whole requests");
+};
+template <int PT, int NC, int KS, bool FINE>
+__global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int PB = PT == 32 ? 1 : 2, CB = PT == 128 ? 4 : NC / 64;   // 32 x 32 output blocks of a wave
-  constexpr int WROW = NC * 2, WMAT = 64 * WROW, kDxW = 2 * WMAT;  // a row and a matrix of a pair in LDS; the pair
-  constexpr int NW = WMAT / 4096, RPI = 1024 / WROW;               // requests of a wave for its matrix; rows of one
-  constexpr int DR = PT + 32, ND = DR / 32, DB = 2 * DR * 128;     // rows of a plane tile; its requests per wave; bytes
+  using G = Dx<PT, NC, KS, FINE>;
+  constexpr int PB = G::PB, CB = G::CB, D = G::D, GP = FINE ? 3 : 2;
   const StepArgs& a = g.st;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
   constexpr int ZC = 256 / NC;
@@ -424,213 +443,214 @@ __global__ __launch_bounds__(512, 2) void bwd_dx_k(BwdConvArgs g, int blk0, int 
   const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
   if (p0 >= pend) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
-  const int kq = w & 3, wo = w >> 2;
+  const int kq = w % KS, wo = w / KS;
   const int KW = a.k_width, pad = (KW - 1) / 2, C = a.conv_in ? 2 * kD : kD, tiles = (a.M + 31) / 32;
   const bool taps = val == 0 || a.conv_in;
-  const int nsc = (a.M + 63) / 64, npair = (KW + 1) / 2;
+  const int n16 = (a.M + 15) / 16, nsc = (n16 + KS - 1) / KS;
 
-  // right-hand matrices of a pair: waves 0 .. 3 request the first, 4 .. 7 the second; a row past M is the last one again
-  // (its partner in the planes is zero)
-  const int coff = (val ? kD : 0) + cbase;
-  const u32x4 rw = make_rsrc(g.wt + (a.w_head_stride ? (int64_t)hkv * KW * a.M * C : 0) + coff,
-                             (uint32_t)((int64_t)KW * a.M * C * 2) - coff * 2);
-  const uint16_t* g2 = g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? 2 * a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) + coff;
-  const u32x4 rg2 = make_rsrc(g2, (uint32_t)(a.M * 512) - coff * 2);
-  const u32x4 rg = make_rsrc(g.gsplit + blk * g.gsplit_stride + ((int64_t)(wo ? a.batch * a.Hkv : 0) + ch) * a.M * (2 * kD) +
-                                 coff, (uint32_t)(a.M * 512) - coff * 2);
-  // offsets of this lane's cells of a chunk: row r times the row stride plus the cell's chunk
-  auto cell = [&](int r, int chunk) { return NC == 128 ? chunk ^ swz(r) : chunk ^ pswz(r); };
-  uint32_t wvo[NW], gvo[NW];
-  auto enter_chunk = [&](int sc) {
+  // right-hand fragments, 1 KB each: the filters [bank][32 channels][16 slots][tap], and g [part][chain][16 slots][32 columns].
+  // (16 slots past M: the last ones again, their partners in the planes are zero)
+  const uint32_t lane16 = l * 16;
+  const unsigned char* wf = (const unsigned char*)g.wf +
+      (int64_t)((a.w_head_stride ? hkv * (C / 32) : 0) + ((val ? kD : 0) + cbase) / 32 + wo * CB) * n16 * KW * 1024;
+  const unsigned char* gf = (const unsigned char*)(g.gsplit + blk * g.gsplit_stride) +
+      ((int64_t)ch * tiles * 16 + (val * kD + cbase) / 32 + wo * CB) * 1024;
+  const int64_t gpart = (int64_t)a.batch * a.Hkv * tiles * (16 * 1024);
+  bf16x8 fw[D][CB];
+  auto tap0 = [&](int sc) { return wf + (int64_t)min(min(sc, nsc - 1) * KS + kq, n16 - 1) * KW * 1024; };   // of this wave's 16 slots
+  auto load_tap = [&](bf16x8 (&f)[CB], const unsigned char* p) {
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int rt = (kq * NW + i) * RPI + l / (WROW / 16), r = min(rt, a.M - 1 - sc * 64), c = cell(rt, l % (WROW / 16)) << 4;
-      wvo[i] = r * (C * 2) + c;
-      gvo[i] = r * 512 + c;
+    for (int c = 0; c < CB; ++c) f[c] = *(const bf16x8*)(p + (int64_t)c * n16 * KW * 1024 + lane16);
+  };
+  const bool whole = KW % D == 0;            // the taps of a chunk end where those of the next one begin
+  auto first_taps = [&](int sc) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_tap(fw[i], tap0(sc) + min(i, KW - 1) * 1024);
+  };
+
+  // plane rows: offsets inside the 32-slot planes of a chunk, of dl (with the halo) and of n
+  uint32_t dvo[G::ND], nvo[G::NN];
+  auto plane_cell = [&](int ra, int rows, int first) -> uint32_t {
+    const int pl = ra / rows, r = ra - pl * rows + (l >> 3), q = first + r;
+    return q >= 0 && q < x.T ? (uint32_t)((pl * g.P + q) * 128 + (((l & 7) ^ pswz(r)) << 4)) : 0x80000000u;
+  };
+#pragma unroll
+  for (int i = 0; i < G::ND; ++i) dvo[i] = plane_cell((w * G::ND + i) * 8, G::DR, p0 - (KW - 1) + pad);
+#pragma unroll
+  for (int i = 0; i < G::NN; ++i) nvo[i] = plane_cell((w * G::NN + i) * 8, PT, p0);
+  const int64_t chain_planes = (int64_t)ch * tiles * g.P * 128;
+  const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + chain_planes;
+  const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + chain_planes;
+  const unsigned char* pw = (const unsigned char*)(g.wn_low + blk * g.plane_stride) + chain_planes;
+  auto planes_rsrc = [&](const unsigned char* p, int sc) {
+    return make_rsrc(p + (int64_t)sc * G::PL * g.P * 128, (uint32_t)(min(G::PL, tiles - sc * G::PL) * g.P * 128));
+  };
+  const uint32_t ddst = __builtin_amdgcn_readfirstlane(lds0 + w * G::ND * 1024), ndst = __builtin_amdgcn_readfirstlane(lds0 + w * G::NN * 1024);
+  auto request_d = [&](int sc) {
+    const u32x4 r = planes_rsrc(pl, sc);
+#pragma unroll
+    for (int i = 0; i < G::ND; ++i) load_to_lds_at(r, ddst + (sc & 1) * G::DB + i * 1024, dvo[i], 0u);
+  };
+  // the rows of n have one place behind the two of dl; without taps they take turns in those
+  const bool turns = !taps && !FINE;
+  auto n_at = [&](int sc) { return turns ? (sc & 1) * G::DB : 2 * G::DB; };
+  auto request_n = [&](int sc) {
+    const u32x4 r = planes_rsrc(pn, sc);
+#pragma unroll
+    for (int i = 0; i < G::NN; ++i) load_to_lds_at(r, ndst + n_at(sc) + i * 1024, nvo[i], 0u);
+    if (FINE) {
+      const u32x4 r3 = planes_rsrc(pw, sc);
+#pragma unroll
+      for (int i = 0; i < G::NN; ++i) load_to_lds_at(r3, ndst + n_at(sc) + G::NB + i * 1024, nvo[i], 0u);
     }
   };
-  const uint32_t wdst = __builtin_amdgcn_readfirstlane(lds0 + wo * WMAT + kq * (NW * 1024));
-  auto request_taps = [&](uint32_t soff, int buf) {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) load_to_lds_at(rw, wdst + buf * kDxW + i * 1024, wvo[i], soff);
-  };
-  auto request_g = [&](const u32x4& r, uint32_t soff, int buf) {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) load_to_lds_at(r, wdst + buf * kDxW + i * 1024, gvo[i], soff);
-  };
-  // plane rows: offsets inside the two 32-slot planes of a chunk, of dl (with the halo) and of n
-  uint32_t dvo[2][ND];
-#pragma unroll
-  for (int ph = 0; ph < 2; ++ph)
-#pragma unroll
-    for (int i = 0; i < ND; ++i) {
-      const int ra = (w * ND + i) * 8, sbi = ra >= DR ? 1 : 0, r = ra - sbi * DR + (l >> 3);
-      const int q = (ph ? p0 : p0 - (KW - 1) + pad) + r;
-      dvo[ph][i] = q >= 0 && q < x.T ? (uint32_t)((sbi * g.P + q) * 128 + (((l & 7) ^ pswz(r)) << 4)) : 0x80000000u;
-    }
-  const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
-  const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
-  const uint32_t ddst = __builtin_amdgcn_readfirstlane(lds0 + 2 * kDxW + w * ND * 1024);
-  const unsigned char* pw = (const unsigned char*)(g.wn_low + blk * g.plane_stride) + (int64_t)ch * tiles * g.P * 128;
-  auto request_d = [&](int sc, const unsigned char* plane, const uint32_t (&vo)[ND], int buf) {
-    const u32x4 r = make_rsrc(plane + (int64_t)sc * 2 * g.P * 128, (uint32_t)(min(2, tiles - sc * 2) * g.P * 128));
-#pragma unroll
-    for (int i = 0; i < ND; ++i) load_to_lds_at(r, ddst + buf * DB + i * 1024, vo[i], 0u);
-  };
-  const int row0 = (PT == 128 ? wo * 64 : 0) + l31, col0 = PT == 128 ? 0 : wo * (NC / 2);
-  const int dchunk = (kq & 1) * 2 + lh;
-  int wa[CB][2];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int s16 = l & 15, g2 = (l >> 4) & 1, r = kq * 16 + lh * 8 + (s16 >> 2) + 4 * h;
-      const int chunk = (col0 >> 3) + 4 * cb + 2 * g2 + ((s16 & 3) >> 1);
-      wa[cb][h] = r * WROW + (cell(r, chunk) << 4) + (s16 & 1) * 8;
-    }
   f32x16 acc[PB][CB];
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = zero16();
-
-  // the two products of a pair: right-hand matrices in buffer wb, plane rows in buffer db from rows ra and rb on; the low
-  // halves of the planes count in the two products where lo0 and lo1, the high ones in the second where `two`
-  auto pair = [&](int wb, int db, int ra, int rb, bool lo0, bool two, bool lo1, auto request) {
-    const unsigned char* dp = smem + 2 * kDxW + db * DB + (kq >> 1) * DR * 128;
-    const unsigned char* wp = smem + wb * kDxW;
-    // (where a pair is long, behind the fragment reads all eight waves start with; where it is short, as early as can be:
-    // 128 rows 166 -> 165 us a step of 512 slots, but 32 rows 18.9 -> 20.6 us a step of 128)
-    if (PT != 128) request();
-    bf16x8 fw[2][CB], fh[2][PB], fl[2][PB];
+  auto multiply = [&](const bf16x8 (&fd)[PB], const bf16x8 (&fr)[CB]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = row0 + (h ? rb : ra);
-      const unsigned char* p = dp + r * 128;
-      const int c = (dchunk ^ pswz(r)) << 4;
+    for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
-      for (int pb = 0; pb < PB; ++pb) {
-        fh[h][pb] = *(const bf16x8*)(p + c + pb * 32 * 128);
-        fl[h][pb] = *(const bf16x8*)(p + (c ^ 64) + pb * 32 * 128);
-      }
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) fw[h][cb] = frag_tr(wp + h * WMAT + wa[cb][0], wp + h * WMAT + wa[cb][1]);
-    }
-    auto multiply = [&](const bf16x8 (&fd)[PB], const bf16x8 (&fr)[CB]) {
-#pragma unroll
-      for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fd[pb], fr[cb], acc[pb][cb]);
-    };
-    if (PT == 128) request();
-    multiply(fh[0], fw[0]);
-    if (lo0) multiply(fl[0], fw[0]);
-    if (two) multiply(fh[1], fw[1]);
-    if (lo1) multiply(fl[1], fw[1]);
+      for (int cb = 0; cb < CB; ++cb) acc[pb][cb] = mfma32(fd[pb], fr[cb], acc[pb][cb]);
   };
-  const uint32_t tap_bytes = (uint32_t)(a.M * C * 2), chunk_w = (uint32_t)(64 * C * 2);
-  enter_chunk(0);
+  const int dchunk = (kq & 1) * 2 + lh;
+  // high or low halves of this wave's slots in 32 PB rows from row r on
+  auto rows_at = [&](const unsigned char* p, int r, int low, bf16x8 (&f)[PB]) {
+    p += r * 128 + (((dchunk ^ pswz(r)) << 4) ^ low * 64);
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) f[pb] = *(const bf16x8*)(p + pb * 32 * 128);
+  };
+
   if (taps) {
-    request_d(0, pl, dvo[0], 0);
-    request_taps((uint32_t)min(wo, KW - 1) * tap_bytes, 0);
-  } else {
-    request_d(0, pn, dvo[1], 0);
-    request_g(rg, 0u, 0);
+    request_d(0);
+    first_taps(0);
+    if (nsc > 1) request_d(1);
   }
+  request_n(0);
+  if (turns && nsc > 1) request_n(1);
   wait_loads<0>();
   barrier();
-  int wb = 0, db = 0;
   for (int sc = 0; sc < nsc; ++sc) {
-    if (taps) {
-      uint32_t soff = (uint32_t)sc * chunk_w + wo * tap_bytes;
-      for (int tp = 0; tp < npair; ++tp) {
-        const bool two = tp * 2 + 1 < KW;
-        pair(wb, db, KW - 1 - 2 * tp, two ? KW - 2 - 2 * tp : 0, true, two, two, [&]() {
-          // the next pair's matrices (a second tap that is not there: the first again, not used), and once the rows of n
-          if (tp + 1 < npair) request_taps((soff += 2 * tap_bytes) - (2 * tp + 2 + wo < KW ? 0u : tap_bytes), wb ^ 1);
-          else request_g(rg, (uint32_t)sc * (64 * 512), wb ^ 1);
-          if (tp == 0) request_d(sc, pn, dvo[1], db ^ 1);
-        });
-        if (tp == 0 && npair > 1) wait_loads<ND>(); else wait_loads<0>();
-        barrier();
-        wb ^= 1;
-      }
-      db ^= 1;
+    bf16x8 fg[GP][CB];
+    {
+      const unsigned char* p = gf + (int64_t)min(sc * KS + kq, n16 - 1) * (8 * 1024);
+#pragma unroll
+      for (int u = 0; u < GP; ++u)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) fg[u][c] = *(const bf16x8*)(p + u * gpart + c * 1024 + lane16);
     }
-    auto next_chunk = [&]() {
-      if (sc + 1 == nsc) return;
-      enter_chunk(sc + 1);
-      if (taps) {
-        request_d(sc + 1, pl, dvo[0], db ^ 1);
-        request_taps((uint32_t)(sc + 1) * chunk_w + (uint32_t)min(wo, KW - 1) * tap_bytes, wb ^ 1);
-      } else {
-        request_d(sc + 1, pn, dvo[1], db ^ 1);
-        request_g(rg, (uint32_t)(sc + 1) * (64 * 512), wb ^ 1);
-      }
-    };
-    // (low half x low half is below the 16 bits kept of two parts, not below the 24 of three)
-    pair(wb, db, 0, 0, true, true, FINE, [&]() {
-      if (FINE) {
-        request_d(sc, pw, dvo[1], db ^ 1);
-        request_g(rg2, (uint32_t)sc * (64 * 512), wb ^ 1);
-      } else {
-        next_chunk();
-      }
-    });
-    wait_loads<0>();
-    barrier();
-    wb ^= 1;
-    db ^= 1;
-    if (FINE) {                            // third part of n x first of g, first of n x third of g
-      pair(wb, db, 0, 0, false, false, true, next_chunk);
+    if (taps) {
+      const unsigned char* dp = smem + (sc & 1) * G::DB + (kq >> 1) * G::DR * 128;
+      // a tap's low halves are read ahead of the products with the high ones, the next tap's high ones ahead of those with the
+      // low ones; its filters are replaced by those D taps on, which at the end of a chunk are the next one's first
+      bf16x8 fh[PB], fl[PB];
+      auto tap = [&](int t, bf16x8 (&f)[CB]) {
+        rows_at(dp, l31 + KW - 1 - t, 1, fl);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(fh, f);
+        __builtin_amdgcn_sched_barrier(0);
+        rows_at(dp, l31 + max(KW - 2 - t, 0), 0, fh);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(fl, f);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      rows_at(dp, l31 + KW - 1, 0, fh);
+      const unsigned char* here = tap0(sc);
+      const unsigned char* there = whole ? tap0(sc + 1) : here;
+      int t0 = 0;
+      for (; t0 + D <= KW; t0 += D)
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+          tap(t0 + i, fw[i]);
+          const int t = t0 + i + D;
+          load_tap(fw[i], t < KW ? here + t * 1024 : there + (t - KW) * 1024);
+        }
+#pragma unroll
+      for (int i = 0; i < D - 1; ++i)
+        if (t0 + i < KW) tap(t0 + i, fw[i]);
       wait_loads<0>();
       barrier();
-      wb ^= 1;
-      db ^= 1;
+      if (sc + 2 < nsc) request_d(sc + 2);
+      if (!whole && sc + 1 < nsc) first_taps(sc + 1);
+    }
+    {
+      const unsigned char* np = smem + n_at(sc) + (kq >> 1) * PT * 128;
+      bf16x8 fh[PB], fl[PB];
+      rows_at(np, l31, 0, fh);
+      rows_at(np, l31, 1, fl);
+      multiply(fh, fg[0]);
+      multiply(fl, fg[0]);
+      multiply(fh, fg[1]);
+      // (low half x low half is below the 16 bits kept of two parts, not below the 24 of three)
+      if constexpr (FINE) {
+        multiply(fl, fg[1]);
+        multiply(fh, fg[2]);
+        rows_at(np + G::NB, l31, 0, fh);       // the third part, [third | first]
+        multiply(fh, fg[0]);
+      }
+    }
+    if (sc + 1 == nsc) break;
+    if (turns) wait_loads<0>();
+    barrier();
+    if (!turns) request_n(sc + 1);
+    else if (sc + 2 < nsc) request_n(sc + 2);
+    if (!taps && !turns) {
+      wait_loads<0>();
+      barrier();
     }
   }
-  // ---- the four partial sums of each output: column block cb is collected by the wave kq = cb of its half, two column
-  // blocks at a time (a wave's block: 16 registers x 256 bytes)
-  float* red = (float*)smem;
-  constexpr int C2 = CB < 2 ? 1 : 2;
+  // ---- the KS partial sums of each output, 32 registers of every wave at a time: a wave adds up 32 / KS of them
+  float* red = (float*)smem + wo * KS * 32 * 64 + l;
+  constexpr int X = 32 / KS;
 #pragma unroll
-  for (int c0 = 0; c0 < CB; c0 += 2) {
-    if (c0) __syncthreads();
-#pragma unroll
-    for (int c = 0; c < C2; ++c)
-      if (kq != c0 + c)
-#pragma unroll
-        for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) red[((((wo * C2 + c) * 4 + kq) * PB + pb) * 16 + i) * 64 + l] = acc[pb][c0 + c][i];
+  for (int rd = 0; rd < PB * CB / 2; ++rd) {
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < C2; ++c)
-      if (kq == c0 + c)
+    for (int q = 0; q < 32; ++q) red[(kq * 32 + q) * 64] = acc[(rd * 2 + q / 16) / CB][(rd * 2 + q / 16) % CB][q % 16];
+    const int b = rd * 2 + kq * X / 16, i0 = kq * X % 16;      // what this wave adds up: registers i0 .. of block b
+    float* at[X];
+    float old[X];
 #pragma unroll
-        for (int pb = 0; pb < PB; ++pb) {
-          const int pr = p0 + (PT == 128 ? wo * 64 : 0) + pb * 32 + lh * 4;
-          const int col = cbase + col0 + (c0 + c) * 32 + l31;
-          float* at[16];
-          float old[16];
+    for (int i = 0; i < X; ++i) {          // every load before the first store
+      const int p = min(p0 + b / CB * 32 + ((i0 + i) >> 2) * 8 + lh * 4 + (i & 3), pend - 1);
+      float* cr = (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + ((int64_t)ch * a.M + p) * kD;
+      float* br = (val ? g.d_v : g.d_k) + ch * g.kv_chain + ((int64_t)blk * g.B + p - x.m) * kD;
+      at[i] = (p < x.m ? cr : br) + cbase + (wo * CB + b % CB) * 32 + l31;
+      old[i] = *at[i];
+    }
+    __syncthreads();
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {       // every load before the first store
-            const int p = min(pr + (i >> 2) * 8 + (i & 3), pend - 1);
-            float* cr = (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + ((int64_t)ch * a.M + p) * kD;
-            float* br = (val ? g.d_v : g.d_k) + ch * g.kv_chain + ((int64_t)blk * g.B + p - x.m) * kD;
-            at[i] = (p < x.m ? cr : br) + col;
-            old[i] = *at[i];
-          }
+    for (int i = 0; i < X; ++i) {
+      float v = 0.f;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            float v = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-              v += k == c0 + c ? acc[pb][c0 + c][i] : red[((((wo * C2 + c) * 4 + k) * PB + pb) * 16 + i) * 64 + l];
-            if (pr + (i >> 2) * 8 + (i & 3) < pend) *at[i] = old[i] + v;
-          }
-        }
+      for (int k = 0; k < KS; ++k) v += red[(k * 32 + kq * X + i) * 64];
+      if (p0 + b / CB * 32 + ((i0 + i) >> 2) * 8 + lh * 4 + (i & 3) < pend) *at[i] = old[i] + v;
+    }
   }
+}
+
+// What a call starts with: the filters in the order bwd_dx_k's waves read them, and zeros from `zero` on
+__global__ void bwd_begin_k(StepArgs a, uint16_t* wf, int banks, u32x4* zero, int64_t zeros) {
+  const int C = a.conv_in ? 2 * kD : kD, KW = a.k_width, n16 = (a.M + 15) / 16;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, n = (int64_t)banks * (C / 32) * n16 * KW * 64;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += step) {
+    const int l = (int)(e & 63);
+    int64_t r = e >> 6;
+    const int t = (int)(r % KW); r /= KW;
+    const int s = (int)(r % n16) * 16 + (l >> 5) * 8; r /= n16;
+    const int c = (int)(r % (C / 32)) * 32 + (l & 31), bank = (int)(r / (C / 32));
+    const uint16_t* w = (const uint16_t*)a.conv_w + bank * a.w_head_stride + ((int64_t)s * C + c) * KW + t;
+    uint16_t v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = s + q < a.M ? w[(int64_t)q * C * KW] : (uint16_t)0;
+    u32x4 out;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q] = v[2 * q] | (uint32_t)v[2 * q + 1] << 16;
+    *(u32x4*)(wf + e * 8) = out;
+  }
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < zeros; e += step) zero[e] = u32x4{0u, 0u, 0u, 0u};
 }
 
 // ---- dW: a workgroup per (128 slots, 128 columns, two taps) and share of the contraction over (block, chain, position),
@@ -839,16 +859,14 @@ void launch_rows(const BwdConvArgs& g, int blk, int T, int grid, hipStream_t s) 
   else launch_rows_norm<NT, MULTI, 1>(g, blk, T, grid, s);
 }
 
-template <int PT, int NC, bool FINE>
+template <int PT, int NC, int KS, bool FINE>
 hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  constexpr int rings = 2 * 2 * 64 * NC * 2 + 2 * 2 * (PT + 32) * 128;
-  constexpr int sums = 2 * (NC == 64 ? 1 : 2) * 4 * (PT == 32 ? 1 : 2) * 16 * 256;
-  constexpr int lds = rings > sums ? rings : sums;
+  constexpr int lds = Dx<PT, NC, KS, FINE>::lds;
   static bool lds_set = false;
-  const hipError_t e = allow_lds(bwd_dx_k<PT, NC, FINE>, lds, lds_set);
+  const hipError_t e = allow_lds(bwd_dx_k<PT, NC, KS, FINE>, lds, lds_set);
   if (e != hipSuccess) return e;
   const StepArgs& a = g.st;
-  hipLaunchKernelGGL((bwd_dx_k<PT, NC, FINE>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
+  hipLaunchKernelGGL((bwd_dx_k<PT, NC, KS, FINE>), dim3((rows + PT - 1) / PT, a.batch * a.Hkv, 256 / NC * n_blk), dim3(512), lds, s, g, blk0,
                      part);
   return hipGetLastError();
 }
@@ -862,10 +880,11 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.ld = l.P = (T + 31) / 32 * 32;
   l.logits_stride = up((chains * M + 31) * l.ld * 4) / 4;        // (whole tiles of 32 slots are read)
   l.plane_stride = up(chains * ((M + 31) / 32) * l.P * 128) / 2;
-  l.gsplit_stride = up(chains * M * 2 * kD * 2 * 3) / 2;
+  l.gsplit_stride = up(chains * ((M + 31) / 32 * 32) * 2 * kD * 2 * 3) / 2;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += up(bytes); return here; };
   l.wt = take((size_t)banks * conv_width * M * C * 2);
+  l.wf = take((size_t)banks * conv_width * ((M + 15) / 16 * 16) * C * 2);
   l.zero_page = take(256);
   l.dwt = take((size_t)banks * conv_width * M * C * 4);
   l.per_call = at;
@@ -881,6 +900,7 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
 void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
   char* p = (char*)ws;
   g->wt = (uint16_t*)(p + l.wt);
+  g->wf = (uint16_t*)(p + l.wf);
   g->zero_page = p + l.zero_page;
   g->dwt = (float*)(p + l.dwt);
   g->logits = (float*)(p + l.logits);
@@ -900,8 +920,11 @@ hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, hipStream_t s) {
   const size_t n = (size_t)g.banks * a.k_width * a.M * (a.conv_in ? 2 * kD : kD);
   hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
   if (e != hipSuccess) return e;
-  // the page of zeros lies right before the sums
-  return launch_zero_fill(g.zero_page, (size_t)((char*)(g.dwt + n) - (char*)g.zero_page), s);
+  // the page of zeros lies right before the sums (n is a multiple of 4)
+  const int64_t zeros = ((char*)(g.dwt + n) - (char*)g.zero_page) / 16;
+  hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((zeros + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf, g.banks,
+                     (u32x4*)g.zero_page, zeros);
+  return hipGetLastError();
 }
 
 hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
@@ -923,14 +946,12 @@ hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_
 
 template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  // the largest tile of which there is one for every compute unit; the smallest one halved across the columns, two on a
-  // compute unit, where even those are too few (a step of 32 chains and 128 slots: 16.2 us, whole 18.9 us)
+  // the largest tile of which there is one for every compute unit
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
-  if constexpr (!FINE)                     // (with the third parts the largest tile spills)
-    if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, FINE>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, FINE>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, FINE>(g, blk0, n_blk, part, rows, s);
-  return launch_dx<32, 64, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, 8, FINE>(g, blk0, n_blk, part, rows, s);
+  return launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
 }
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;

@@ -303,18 +303,19 @@ struct BwdConvArgs {
   float* d_conv_b;
   // workspace (bwd_conv_place)
   uint16_t* wt;              // filters per tap
+  uint16_t* wf;              // filters as operand fragments of 16 slots x 32 channels: [bank][channels / 32][slots / 16][tap]
   void* zero_page;           // 256 bytes of zeros
   float* dwt;                // filter gradient per tap
   float* logits;             // [block][chain][slot][ld]
   uint16_t* dl;              // planes of the logit gradients and of the normalised rows, [block][chain][32 slots][P][64]
   uint16_t* wn;
   uint16_t* wn_low;          // third parts of the normalised rows, with the first ones: [third 32 | first 32] (blocks in three parts)
-  uint16_t* gsplit;          // gradient w.r.t. the new cache, [block][part][chain][slot][K | V]
+  uint16_t* gsplit;          // gradient w.r.t. the new cache, as such fragments: [block][part][chain][slots / 16][columns / 32]
   int64_t logits_stride, plane_stride, gsplit_stride;     // between blocks, in elements of each
   int32_t ld, P;
 };
-struct BwdConvLayout {       // byte offsets; the first three are per call, the rest per window
-  size_t wt, zero_page, dwt, per_call, logits, dl, wn, wn_low, gsplit, total;
+struct BwdConvLayout {       // byte offsets; the first four are per call, the rest per window
+  size_t wt, wf, zero_page, dwt, per_call, logits, dl, wn, wn_low, gsplit, total;
   size_t logits_stride, plane_stride, gsplit_stride;
   int ld, P;
 };
