@@ -426,7 +426,8 @@ struct Dx {
   static constexpr int DB = PL * DR * 128, NB = PL * PT * 128;           // bytes of a chunk's rows of dl, of n
   static constexpr int ND = DB / 8192, NN = NB / 8192;                   // requests of a wave for them
   static constexpr int D = 3;                                            // taps of filters in flight (a divisor of 15 and 21)
-  static constexpr int rings = 2 * DB + (FINE ? 2 : 1) * NB, sums = 8 * 32 * 256;
+  static constexpr int RR = PB * CB >= 8 ? 64 : 32;                      // registers of a wave summed up at a time
+  static constexpr int rings = 2 * DB + (FINE ? 2 : 1) * NB, sums = 8 * RR * 256;
   static constexpr int lds = rings > sums ? rings : sums;
   static_assert(DB % 8192 == 0 && NB % 8192 == 0, "whole requests");
 };
@@ -532,15 +533,16 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
   if (turns && nsc > 1) request_n(1);
   wait_loads<0>();
   barrier();
+  bf16x8 fg[GP][CB];
+  auto load_g = [&](int sc, bf16x8 (&f)[GP][CB]) {
+    const unsigned char* p = gf + (int64_t)min(min(sc, nsc - 1) * KS + kq, n16 - 1) * (8 * 1024);
+#pragma unroll
+    for (int u = 0; u < GP; ++u)
+#pragma unroll
+      for (int c = 0; c < CB; ++c) f[u][c] = *(const bf16x8*)(p + u * gpart + c * 1024 + lane16);
+  };
+  load_g(0, fg);
   for (int sc = 0; sc < nsc; ++sc) {
-    bf16x8 fg[GP][CB];
-    {
-      const unsigned char* p = gf + (int64_t)min(sc * KS + kq, n16 - 1) * (8 * 1024);
-#pragma unroll
-      for (int u = 0; u < GP; ++u)
-#pragma unroll
-        for (int c = 0; c < CB; ++c) fg[u][c] = *(const bf16x8*)(p + u * gpart + c * 1024 + lane16);
-    }
     if (taps) {
       const unsigned char* dp = smem + (sc & 1) * G::DB + (kq >> 1) * G::DR * 128;
       // a tap's low halves are read ahead of the products with the high ones, the next tap's high ones ahead of those with the
@@ -577,7 +579,8 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
     }
     {
       const unsigned char* np = smem + n_at(sc) + (kq >> 1) * PT * 128;
-      bf16x8 fh[PB], fl[PB];
+      bf16x8 fh[PB], fl[PB], next[GP][CB];
+      load_g(sc + 1, next);
       rows_at(np, l31, 0, fh);
       rows_at(np, l31, 1, fl);
       multiply(fh, fg[0]);
@@ -590,6 +593,10 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
         rows_at(np + G::NB, l31, 0, fh);       // the third part, [third | first]
         multiply(fh, fg[0]);
       }
+#pragma unroll
+      for (int u = 0; u < GP; ++u)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) fg[u][c] = next[u][c];
     }
     if (sc + 1 == nsc) break;
     if (turns) wait_loads<0>();
@@ -601,15 +608,15 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
       barrier();
     }
   }
-  // ---- the KS partial sums of each output, 32 registers of every wave at a time: a wave adds up 32 / KS of them
-  float* red = (float*)smem + wo * KS * 32 * 64 + l;
-  constexpr int X = 32 / KS;
+  // ---- the KS partial sums of each output, RR registers of every wave at a time: a wave adds up RR / KS of them
+  constexpr int RR = G::RR, X = RR / KS;
+  float* red = (float*)smem + wo * KS * RR * 64 + l;
 #pragma unroll
-  for (int rd = 0; rd < PB * CB / 2; ++rd) {
+  for (int rd = 0; rd < PB * CB * 16 / RR; ++rd) {
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 32; ++q) red[(kq * 32 + q) * 64] = acc[(rd * 2 + q / 16) / CB][(rd * 2 + q / 16) % CB][q % 16];
-    const int b = rd * 2 + kq * X / 16, i0 = kq * X % 16;      // what this wave adds up: registers i0 .. of block b
+    for (int q = 0; q < RR; ++q) red[(kq * RR + q) * 64] = acc[(rd * RR + q) / 16 / CB][(rd * RR + q) / 16 % CB][q % 16];
+    const int b = (rd * RR + kq * X) / 16, i0 = kq * X % 16;      // what this wave adds up: registers i0 .. of block b
     float* at[X];
     float old[X];
 #pragma unroll
@@ -625,7 +632,7 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
     for (int i = 0; i < X; ++i) {
       float v = 0.f;
 #pragma unroll
-      for (int k = 0; k < KS; ++k) v += red[(k * 32 + kq * X + i) * 64];
+      for (int k = 0; k < KS; ++k) v += red[(k * RR + kq * X + i) * 64];
       if (p0 + b / CB * 32 + ((i0 + i) >> 2) * 8 + lh * 4 + (i & 3) < pend) *at[i] = old[i] + v;
     }
   }
@@ -873,7 +880,7 @@ hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int ro
 
 }  // namespace
 
-BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk) {
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits) {
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   const size_t chains = (size_t)batch * Hkv, C = conv_in ? 2 * kD : kD;
   BwdConvLayout l;
@@ -888,7 +895,7 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.zero_page = take(256);
   l.dwt = take((size_t)banks * conv_width * M * C * 4);
   l.per_call = at;
-  l.logits = take((size_t)n_blk * l.logits_stride * 4);
+  l.logits = take(with_logits ? (size_t)n_blk * l.logits_stride * 4 : 0);
   l.dl = take((size_t)n_blk * l.plane_stride * 2);
   l.wn = take((size_t)n_blk * l.plane_stride * 2);
   l.wn_low = take((size_t)n_blk * l.plane_stride * 2);
@@ -915,11 +922,13 @@ void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
   g->P = l.P;
 }
 
-hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, hipStream_t s) {
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s) {
   const StepArgs& a = g.st;
   const size_t n = (size_t)g.banks * a.k_width * a.M * (a.conv_in ? 2 * kD : kD);
-  hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
-  if (e != hipSuccess) return e;
+  if (for_logits) {
+    const hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
+    if (e != hipSuccess) return e;
+  }
   // the page of zeros lies right before the sums (n is a multiple of 4)
   const int64_t zeros = ((char*)(g.dwt + n) - (char*)g.zero_page) / 16;
   hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((zeros + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf, g.banks,
