@@ -547,7 +547,7 @@ lococo_status enqueue_update(const lococo_config* c, Path path, StepArgs a, loco
 // compute units.  `clear`: the counters have been used since they were zeroed (the status word is kept).
 lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_steps, int32_t B, int64_t tokens_left, void* out_k,
                            void* out_v, int64_t out_stride, int64_t slot0, int64_t ring, void* ws, bool clear, hipStream_t s,
-                           bool* taken) {
+                           bool* taken, float* logits = nullptr, int64_t logits_stride = 0, int32_t logits_ld = 0) {
   const bool capturing = stream_is_capturing(s);
   std::unique_lock<std::mutex> lk(g_scan_mu);
   *taken = capturing || !another_scan_in_flight(s);
@@ -567,6 +567,9 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
   sa.ring = (int32_t)ring;
   sa.sync = nullptr;
   sa.status = nullptr;
+  sa.logits = logits;
+  sa.logits_stride = logits_stride;
+  sa.logits_ld = logits_ld;
   sa.spin_limit = spin_limit();
   sa.same_l2_allowed = chain_sync_through_l2() ? 1 : 0;
   {
@@ -1101,8 +1104,8 @@ size_t bwd_attn_stat_bytes(const lococo_config* c, int64_t rows) {
   return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * 3 * sizeof(float), 256);
 }
 struct BwdLayout { size_t p, ds, w, n, dw, conv, total; };
-BwdConvLayout conv_layout(const lococo_config* c, int32_t T, int64_t n_blk) {
-  return bwd_conv_layout(c->batch, c->n_kv_heads, c->M, T, c->conv_width, c->conv_in, filter_banks(c), n_blk);
+BwdConvLayout conv_layout(const lococo_config* c, int32_t T, int64_t n_blk, bool with_logits = true) {
+  return bwd_conv_layout(c->batch, c->n_kv_heads, c->M, T, c->conv_width, c->conv_in, filter_banks(c), n_blk, with_logits);
 }
 BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   const size_t T = (size_t)len + B;
@@ -1168,7 +1171,7 @@ lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool co
   c.d_conv_w = g.d_conv_w;
   c.d_conv_b = g.d_conv_b;
   bwd_conv_place(&c, conv_layout(cfg, T, 1), ws + l.conv);
-  HIP_TRY(launch_bwd_conv_begin(c, s), "filter packing launches");
+  HIP_TRY(launch_bwd_conv_begin(c, true, s), "filter packing launches");
   HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
   HIP_TRY(launch_bwd_conv_rows(c, 0, T, s), "row gradient launch");
   HIP_TRY(launch_bwd_conv_dx(c, 0, 1, 2, T, s), "input gradient launch");
@@ -1288,6 +1291,8 @@ struct SeqBwdLayout {
   size_t d_ck, d_cv, slot;            // gradients w.r.t. the state before each of them, fp32, `slot` bytes each
   size_t hl, stats;       // scratch of the attention launches
   BwdConvLayout conv;     // of Eq. 4 - 6 (inside step_ws)
+  bool keep_logits;       // the logits of all blocks have a place, `logits`: the recomputed scan leaves them there
+  size_t logits;
   size_t d_o;             // a block's upstream gradient where the walk needs a copy of it (no windows)
   size_t g[2][2];         // gradient w.r.t. the cache state, ping-pong: [which][k, v], fp32 [chains, M, d]
   size_t step_ws;         // the window's Eq. 4 - 6, or the workspace of one backward step where there are no windows
@@ -1296,9 +1301,12 @@ struct SeqBwdLayout {
 // What a window may take: enough blocks to fill the device many times over at any shape, whatever the length of the
 // sequence.
 constexpr size_t kBwdWindowBytes = (size_t)3 << 30;
+// The logits of Eq. 5 of every block may take this much (64 blocks of 32 chains, 512 slots and 1024 positions: 4.3 GB); what is
+// longer computes them window by window.  Keeping them takes Eq. 5 out of the pass once: 3.75 of 32.5 ms on that sequence.
+constexpr size_t kBwdLogitsBytes = (size_t)8 << 30;
 
-// largest_window: blocks a window may have at most
-lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64_t largest_window, SeqBwdLayout* out) {
+// largest_window: blocks a window may have at most; keep: whether the logits of all blocks may have a place
+lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64_t largest_window, bool keep, SeqBwdLayout* out) {
   SeqBwdLayout l{};
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
@@ -1310,15 +1318,21 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64
   if (st) return st;
   l.fwd_ws_bytes = step_ws_bytes(c, path, B);
   l.fwd_ws = take(l.fwd_ws_bytes);
-  l.states_k = take((size_t)n * l.state);
-  l.states_v = take((size_t)n * l.state);
+  if (path == PATH_MFMA && bwd_on_mfma(c) && bwd_attn_has_mfma(c) && n > 1) {
+    const int split = compress_position_split(c->batch, c->n_kv_heads, c->M, c->conv_width, c->conv_in, cu_count());
+    l.keep_logits = keep && compress_scan_leaves_logits(false, c->conv_in, split > 1) &&
+                    conv_layout(c, c->M + B, 1).logits_stride * 4 <= kBwdLogitsBytes / (size_t)n;
+  }
+  const size_t n_states = (size_t)n + (l.keep_logits ? 1 : 0);   // (then the last block's own update is made as well)
+  l.states_k = take(n_states * l.state);
+  l.states_v = take(n_states * l.state);
   l.slot = align_up(chains * c->M * c->head_dim * sizeof(float), 256);
   size_t step = 0;                    // a step's workspace grows with the occupancy: the full cache bounds all
   if ((st = lococo_backward_workspace_bytes(c, B, c->M, &step))) return st;
   if (bwd_attn_has_mfma(c)) {
     size_t per_block = 2 * l.slot + bwd_attn_hl_bytes(c, B) + bwd_attn_stat_bytes(c, B);
     if (bwd_on_mfma(c)) {
-      const BwdConvLayout one = conv_layout(c, c->M + B, 1);
+      const BwdConvLayout one = conv_layout(c, c->M + B, 1, !l.keep_logits);
       per_block += one.total - one.per_call;
     }
     // (blocks x chains and 4 x blocks are grid dimensions)
@@ -1329,7 +1343,8 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64
     l.hl = take(bwd_attn_hl_bytes(c, l.window * (int64_t)B));
     l.stats = take(bwd_attn_stat_bytes(c, l.window * (int64_t)B));
     if (bwd_on_mfma(c)) {
-      l.conv = conv_layout(c, c->M + B, l.window);
+      l.conv = conv_layout(c, c->M + B, l.window, !l.keep_logits);
+      if (l.keep_logits) l.logits = take((size_t)n * l.conv.logits_stride * 4);
       step = std::max(step, l.conv.total);
     }
   }
@@ -1352,7 +1367,7 @@ lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg,
   if (!out) return fail(LOCOCO_EINVAL, "out is NULL");
   if (L < 0 || B <= 0) return fail(LOCOCO_EINVAL, "need L >= 0 and B > 0");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, &l))) return st;
   *out = l.total;
   return LOCOCO_OK;
 }
@@ -1385,15 +1400,16 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   for (const auto& sg : plan) any_compress |= sg.branch == 1;
   if (any_compress && (!conv_w || !d_conv_w)) return fail(LOCOCO_EINVAL, "conv_w or d_conv_w is NULL but the scan compresses");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, &l))) return st;
+  if (ws_bytes < l.total && l.keep_logits && (st = seq_bwd_layout(cfg, L, B, INT64_MAX, false, &l))) return st;
   if (ws_bytes < l.total && l.window > 1) {    // the largest window that fits (a layout's size grows with its window)
     int64_t fits = 1, not_fits = l.window;
     while (not_fits - fits > 1) {
       const int64_t mid = (fits + not_fits) / 2;
-      if ((st = seq_bwd_layout(cfg, L, B, mid, &l))) return st;
+      if ((st = seq_bwd_layout(cfg, L, B, mid, false, &l))) return st;
       (l.total <= ws_bytes ? fits : not_fits) = mid;
     }
-    if ((st = seq_bwd_layout(cfg, L, B, fits, &l))) return st;
+    if ((st = seq_bwd_layout(cfg, L, B, fits, false, &l))) return st;
   }
   if (!workspace || ws_bytes < l.total || ((uintptr_t)workspace & 255))
     return fail(LOCOCO_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)", l.total,
@@ -1422,6 +1438,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   if (path == PATH_MFMA)
     HIP_TRY(launch_scan_sync_clear(ws + l.fwd_ws + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false, s),
             "clearing the scan counters");
+  bool have_logits = false;                                  // the scan leaves them
   for (int64_t i = 0; i + 1 < n; ++i) {                      // (the last block's own update is not needed)
     const lococo_seg& sg = plan[(size_t)i];
     fc.k[0] = state_k(i); fc.k[1] = state_k(i + 1);
@@ -1433,10 +1450,13 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
     if (i == n_fill && path != PATH_GENERIC) {               // the first block that compresses
       if ((st = enqueue_repack(cfg, path, a, ws + l.fwd_ws, s))) return st;
       bool taken = path == PATH_MFMA && scan_fits_one_launch(cfg, a);
-      if (taken && (st = enqueue_scan(cfg, a, n - 1 - i, B, L - sg.start, ws + l.states_k, ws + l.states_v,
-                                      (int64_t)(l.state / es), i + 1, n, ws + l.fwd_ws, false, s, &taken)))
+      const bool keep = l.keep_logits && compress_scan_leaves_logits(a.protect != nullptr, cfg->conv_in, false);
+      if (taken && (st = enqueue_scan(cfg, a, n - i - (keep ? 0 : 1), B, L - sg.start, ws + l.states_k, ws + l.states_v,
+                                      (int64_t)(l.state / es), i + 1, n + 1, ws + l.fwd_ws, false, s, &taken,
+                                      keep ? (float*)(ws + l.logits) + i * (int64_t)l.conv.logits_stride : nullptr,
+                                      (int64_t)l.conv.logits_stride, l.conv.ld)))
         return st;
-      if (taken) break;
+      if (taken) { have_logits = keep; break; }
     }
     lococo_cache next = fc;
     if ((st = enqueue_update(cfg, path, a, &next, ws + l.fwd_ws, B, s))) return st;
@@ -1537,7 +1557,8 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
         c.d_conv_w = d_conv_w;
         c.d_conv_b = d_conv_b;
         bwd_conv_place(&c, l.conv, ws + l.step_ws);
-        if (!conv_begun) HIP_TRY(launch_bwd_conv_begin(c, s), "filter packing launches");
+        if (l.keep_logits) c.logits = (float*)(ws + l.logits) + w_steps * c.logits_stride;
+        if (!conv_begun) HIP_TRY(launch_bwd_conv_begin(c, !have_logits, s), "filter packing launches");
         conv_begun = true;
         if (first.len_before < cfg->M) {       // the rows no entry was live in: zero
           BwdArgs g{};
@@ -1547,7 +1568,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
           g.attn_done = g.conv_elsewhere = 1;
           HIP_TRY(launch_step_backward_generic(cfg->dtype, g, true, s), "clearing the rows of empty slots");
         }
-        HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
+        if (!have_logits) HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
         const bool defer = bwd_conv_defers_blocks(c);
         for (int i = c.n_blk - 1; i >= 0; --i) {
           const lococo_seg& sg = plan[(size_t)(w_steps + i)];

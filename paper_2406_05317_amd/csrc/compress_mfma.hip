@@ -7,7 +7,7 @@ namespace {
 
 using namespace compress_detail;
 
-template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN>
+template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN, int LOG>
 __global__ __launch_bounds__(kThreads, 1) void compress_mfma_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t wg_id = blockIdx.x, wg_count = gridDim.x;
@@ -71,13 +71,16 @@ int position_split(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu
   return p;
 }
 template <class F>
-hipError_t with_instantiation(const StepArgs& t, bool multi, int split, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
+hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool logits, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
   const bool big = use_big_tiles(t.batch, t.Hkv, t.M, t.k_width, t.conv_in, n_cu);
   auto pick_cin = [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto spl) {
     if constexpr (decltype(bm)::value == 32) {
-      if (t.conv_in) return f(bm, kw, norm, prot, mu, spl, ic<1>{});
+      if (t.conv_in) return f(bm, kw, norm, prot, mu, spl, ic<1>{}, ic<0>{});
     }
-    return f(bm, kw, norm, prot, mu, spl, ic<0>{});
+    if constexpr (decltype(prot)::value == 0 && decltype(spl)::value != 1) {
+      if (logits) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<1>{});
+    }
+    return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<0>{});
   };
   auto pick_multi = [&](auto bm, auto kw, auto norm, auto prot) {
     if constexpr (decltype(bm)::value == 32) {
@@ -97,11 +100,11 @@ hipError_t with_instantiation(const StepArgs& t, bool multi, int split, int n_cu
   return hipErrorInvalidValue;   // compress_mfma_supports() keeps other shapes away
 }
 
-template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN>
+template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN, int LOG>
 hipError_t prepare_kernel() {
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN>,
+    hipError_t e = hipFuncSetAttribute((const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, Geo<BM, KW>::LDS);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -111,15 +114,15 @@ hipError_t prepare_kernel() {
 
 hipError_t dispatch(const ScanArgs& a, const uint16_t* wp, int64_t wp_head_stride, int n_cu, hipStream_t s) {
   const bool multi = a.groups < a.st.batch * a.st.Hkv;
-  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci) {
+  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), a.logits != nullptr, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
-    constexpr int CIN = decltype(ci)::value;
-    hipError_t e = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN>();
+    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value;
+    hipError_t e = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>();
     if (e != hipSuccess) return e;
     dim3 grid((a.st.M / BM) * a.groups * (SPLIT ? a.psplit : 1));
     constexpr int kLds = Geo<BM, KW>::LDS;
-    hipLaunchKernelGGL((compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN>), grid, dim3(kThreads), kLds, s, a, wp,
+    hipLaunchKernelGGL((compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>), grid, dim3(kThreads), kLds, s, a, wp,
                        wp_head_stride);
     return hipGetLastError();
   });
@@ -206,6 +209,8 @@ hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, in
   sa.ring = 1;
   sa.sync = nullptr;
   sa.status = nullptr;
+  sa.logits = nullptr;
+  sa.logits_stride = sa.logits_ld = 0;
   sa.spin_limit = 0;
   sa.same_l2_allowed = debug_options().chain_sync_device ? 0 : 1;   // (only the hand-off of a split step looks at it here)
   // more (chain, tile) pairs than compute units: one resident workgroup per compute unit, each
@@ -231,6 +236,8 @@ hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, in
   return dispatch(sa, (const uint16_t*)wp, wp_head_stride, n_cu, s);
 }
 
+bool compress_scan_leaves_logits(bool protect, int conv_in, bool position_split) { return !protect && !conv_in && !position_split; }
+
 int compress_tile_slots(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu) {
   return use_big_tiles(batch, Hkv, M, k_width, conv_in, n_cu) ? 64 : 32;
 }
@@ -242,14 +249,14 @@ int compress_scan_max_resident(const StepArgs& a, int n_cu) {
   const int split = multi ? 0 : step_pipeline(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) ? 2
                     : position_split(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) > 1 ? 1 : 0;
   int per_cu = 0;
-  hipError_t e = with_instantiation(a, multi, split, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci) {
+  hipError_t e = with_instantiation(a, multi, split, false, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
-    constexpr int CIN = decltype(ci)::value;
-    hipError_t e2 = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN>();
+    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value;
+    hipError_t e2 = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>();
     if (e2 != hipSuccess) return e2;
     constexpr int kLds = Geo<BM, KW>::LDS;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN>,
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>,
                                                         kThreads, kLds);
   });
   if (e != hipSuccess) { (void)hipGetLastError(); return 0; }

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kThreads, 1) void compress_step_k(ScanArgs sa, cons
   }
   // The build that has two workgroups per pair in a scan, of which the first has the one step: item 2 k of twice n_compress,
   // numbered so that the slot tiles of a chain are on one XCD here too
-  constexpr int BM = 32, PROT = 0, MULTI = 0, SPLIT = 2;
+  constexpr int BM = 32, PROT = 0, MULTI = 0, SPLIT = 2, LOG = 0;
   const uint32_t wg_count = 2 * n_compress, per = wg_count / 8;
   uint32_t k = blockIdx.x;
   if (k < n_compress / 8u * 8u) k = (k % 8) * (n_compress / 8u) + k / 8;

@@ -191,6 +191,8 @@ __device__ __forceinline__ Cat16 load_cat16(const CatRows& c, int p, int chunk) 
 // its partner finishes that step -- then, after the chain has been met, the tiles that touch the cache.
 // Only the second leg is on the chain's critical path.  (Single-step launches use the same build, one
 // workgroup of each pair idle, so that results do not depend on the kind of launch.)
+// LOG = 1: the logits of Eq. 5 also go to memory, step by step [chains, M, ld], for the backward pass of a scan (no protected
+// slots, filters over the keys).
 // CIN = 1: filters over [K | V] (two walks, see the head of the file); wp then holds the key half of
 // every bank's slices followed by the value half, each in the order above.
 

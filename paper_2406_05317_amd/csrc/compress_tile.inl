@@ -1,5 +1,5 @@
 // The work of one workgroup of the fused compression kernel, included as the body of the kernels that have it (template
-// parameters BM, KW, NORM, PROT, MULTI, SPLIT, CIN, as described in compress_tile.h).  In scope: ScanArgs sa, wp,
+// parameters BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG, as described in compress_tile.h).  In scope: ScanArgs sa, wp,
 // wp_head_stride, smem (Geo<BM, KW>::LDS bytes), and wg_id of wg_count.  It is text and not an inlined function because the
 // 64-slot builds use all 512 registers: as a function the same code spilled differently and the 32 K-token scan took 4 % longer.
   using G = Geo<BM, KW>;
@@ -71,6 +71,8 @@
   // key-side logits of one tile as this lane left them in the first walk (CIN only)
   f32x4 pre = {0.f, 0.f, 0.f, 0.f};
   __amdgpu_buffer_rsrc_t pre_rows = __builtin_amdgcn_make_buffer_rsrc((void*)sa.prelogits, 0, 0, 0x00020000);
+
+  __amdgpu_buffer_rsrc_t log_rows = __builtin_amdgcn_make_buffer_rsrc((void*)sa.logits, 0, 0, 0x00020000);
 
   // mixing accumulator, transposed: lane = slot rt*32 + l31, rows = columns 64w + ct*32 + (i/4)*8 + lh*4 + i%4
   f32x16 oacc[2][G::RT];
@@ -294,6 +296,13 @@
         }
         if (PH == 2 && slot == 8 * S + 2 * E4 + 1)     // the next tile's, a whole stage before they are added
           pre = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pre_rows, ((j0 / BN + 1) * (BM * BN) + tid * 4) * 4, 0, kDeviceScope));
+        if (LOG && slot == 8 * S + 2 * E4 + 1) {       // the logits as they are, for the backward pass
+#pragma unroll
+          for (int e4 = 0; e4 < E4; ++e4) {
+            const f32x4 v = {sv[e4 * 4], sv[e4 * 4 + 1], sv[e4 * 4 + 2], sv[e4 * 4 + 3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), log_rows, (srow * sa.logits_ld + sp0 + e4 * 4) * 4, j0 * 4, 0);
+          }
+        }
         if (PH != 1 && slot == 8 * S + 2 * E4 + 1) {
           if (j0 + BN > T) {                   // tail tile: positions past T carry no weight
 #pragma unroll
@@ -546,6 +555,9 @@
       jbase = lo * BN;
       NT = hi > lo ? hi - lo : 0;
     }
+    if (LOG)
+      log_rows = __builtin_amdgcn_make_buffer_rsrc((void*)(sa.logits + step * sa.logits_stride + ((int64_t)ch * a.M + i0) * sa.logits_ld), 0,
+                                                   BM * sa.logits_ld * 4, 0x00020000);
     const int64_t prev = (int64_t)((sa.slot0 + step - 1) % sa.ring) * sa.out_stride;   // (unused for step 0)
     const uint16_t* src_k = step == 0 ? (const uint16_t*)a.cache_k : (const uint16_t*)sa.out_k + prev;
     const uint16_t* src_v = step == 0 ? (const uint16_t*)a.cache_v : (const uint16_t*)sa.out_v + prev;

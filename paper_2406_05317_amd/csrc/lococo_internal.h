@@ -81,6 +81,9 @@ struct ScanArgs {
   uint32_t* psync;           // per (chain, 32-slot tile): parts that have handed in (launcher)
   float* prelogits;          // [K | V] filters: key-side logits between the two walks of a step (launcher)
   int64_t pre_stride;        // floats per (chain, 32-slot tile) there (launcher)
+  float* logits;             // not null: the logits of the steps are left there, rows of logits_ld floats [chains, M], steps
+  int64_t logits_stride;     // logits_stride floats apart (compress_scan_leaves_logits)
+  int32_t logits_ld;
 };
 
 // Arguments of the MFMA attention kernel: one block, or every block of a scan
@@ -215,6 +218,8 @@ size_t compress_scan_sync_bytes(int batch, int Hkv, int M);
 // zero them (a fill kernel, so the call may sit inside a captured graph); keep_status: only the chain
 // counters, not the status word (between the launches of one call)
 hipError_t launch_scan_sync_clear(void* sync_ws, int batch, int Hkv, int M, bool keep_status, hipStream_t s);
+// whether the scan kernel of this shape can leave its logits in memory
+bool compress_scan_leaves_logits(bool protect, int conv_in, bool position_split);
 // the same kernel over n_steps consecutive compress steps (see ScanArgs); `sync_ws` is
 // compress_scan_sync_bytes() of device memory, cleared beforehand
 hipError_t launch_compress_scan(const ScanArgs& a, const void* wp, int banks, int n_cu, void* sync_ws,
@@ -320,10 +325,11 @@ struct BwdConvLayout {       // byte offsets; the first four are per call, the r
   int ld, P;
 };
 // T: the most positions of a block (m + Bn); n_blk: blocks of a window
-BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk);
+// with_logits: false where the logits of all blocks are kept elsewhere
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits);
 void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws);
 // once per call: filters packed, sums and zeros cleared; at its end: the sums added to d_conv_w
-hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, hipStream_t s);
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s);    // (for launch_bwd_conv_logits, too)
 hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s);
 // the logits of all blocks; then, from the last block to the first, rows and dx (part 0: cache rows; 1: the rows of the
 // blocks themselves, blocks blk0 .. blk0 + n_blk - 1; 2: both; `rows`: the most rows of one of them); then dw of all blocks
