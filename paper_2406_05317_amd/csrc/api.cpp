@@ -464,10 +464,11 @@ float* step_stats(const lococo_config* c, Path path, int32_t B, void* workspace,
 
 // Repack the filter bank into the workspace (MFMA path; once per call unless the caller says
 // the workspace already holds it).
-lococo_status enqueue_repack(const lococo_config* c, Path path, const StepArgs& a, void* ws, hipStream_t s) {
+// sync_ws: see launch_repack_filters (fused MFMA path, filters not prepared).
+lococo_status enqueue_repack(const lococo_config* c, Path path, const StepArgs& a, void* ws, hipStream_t s, void* sync_ws = nullptr) {
   if (c->flags & LOCOCO_FLAG_FILTERS_PREPARED) return LOCOCO_OK;
   KTimer t(K_REPACK, s);
-  if (path == PATH_MFMA) HIP_TRY(launch_repack_filters(a, ws, filter_banks(c), s), "filter repack launch");
+  if (path == PATH_MFMA) HIP_TRY(launch_repack_filters(a, ws, filter_banks(c), sync_ws, s), "filter repack launch");
   else HIP_TRY(launch_pack_filters_per_tap(a, filter_banks(c), ws, s), "filter packing launch");
   return LOCOCO_OK;
 }
@@ -913,12 +914,16 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
                   workspace ? ws_bytes : (size_t)0);
   }
   lococo_cache tmp = *cache;
-  if (any_compress && path != PATH_GENERIC) {
+  // the scan status of this call starts at "no wait gave up", whichever schedule runs
+  const bool clear = path == PATH_MFMA && workspace && ws_bytes >= step_ws_bytes(cfg, path, B);
+  const bool repack = any_compress && path != PATH_GENERIC && !(cfg->flags & LOCOCO_FLAG_FILTERS_PREPARED);
+  if (repack) {
     StepArgs a0 = make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true);
-    if ((st = enqueue_repack(cfg, path, a0, workspace, (hipStream_t)stream))) return st;
+    if ((st = enqueue_repack(cfg, path, a0, workspace, (hipStream_t)stream,
+                             clear ? (char*)workspace + filter_ws_bytes(cfg) : nullptr)))
+      return st;
   }
-  if (path == PATH_MFMA && workspace && ws_bytes >= step_ws_bytes(cfg, path, B)) {
-    // the scan status of this call starts at "no wait gave up", whichever schedule runs
+  if (clear && !repack) {
     HIP_TRY(launch_scan_sync_clear((char*)workspace + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false,
                                    (hipStream_t)stream), "clearing the scan counters");
   }

@@ -1,5 +1,6 @@
 // Launches of the fused compression kernel (the work of a workgroup is in compress_tile.inl): which build a shape runs on,
 // how its workgroups are dealt out, and the repacking of the filters.
+#include "compress_roles.h"
 #include "compress_tile.h"
 
 namespace lococo {
@@ -7,18 +8,37 @@ namespace {
 
 using namespace compress_detail;
 
-template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN, int LOG>
+template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int LOG>
 __global__ __launch_bounds__(kThreads, 1) void compress_mfma_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t wg_id = blockIdx.x, wg_count = gridDim.x;
 #include "compress_tile.inl"
 }
+template <int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN>
+__global__ __launch_bounds__(kRoleThreads, 2) void compress_roles_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  compress_roles<KW, NORM, PROT, MULTI, SPLIT, CIN>(sa, wp, wp_head_stride, smem, blockIdx.x, gridDim.x);
+}
+// The kernel of an instantiation, its workgroups' threads and LDS.  ROLES: waves of two roles (compress_roles.h), which every
+// [K | V] bank runs on, and a single step on the builds with two workgroups per pair; both kernels of a shape give the same bits.
+template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN, int LOG, int ROLES>
+struct Build {
+  static constexpr int kWgThreads = ROLES ? kRoleThreads : kThreads;
+  static constexpr int kLds = ROLES ? Roles<KW>::LDS : Geo<BM, KW>::LDS;
+  static constexpr auto kernel() {
+    if constexpr (ROLES != 0) return &compress_roles_k<KW, NORM, PROT, MULTI, SPLIT, CIN>;
+    else return &compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, LOG>;
+  }
+};
 
 // [M][C][k] per bank -> register order (see compress_mfma_k); one thread per 16-byte chunk.  C = 128,
 // or 256 ([K | V] filters): then a bank is its key half (channels 0..127 of every slot) in that
 // order followed by its value half.
+// Also zeroes what a scan starts with, where the call wants both (one launch less: 3 us of a 300 us prefill).
 __global__ void repack_filters_k(const uint16_t* w, uint16_t* wp, int M, int C, int KW, int banks,
-                                 int64_t w_head_stride) {
+                                 int64_t w_head_stride, uint32_t* zero, int n_zero, uint32_t* zero2, int n_zero2) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0u;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero2; i += gridDim.x * blockDim.x) zero2[i] = 0u;
   const int64_t chunks_per_bank = (int64_t)M * KW * (C / 8);
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < chunks_per_bank * banks;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -71,16 +91,19 @@ int position_split(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu
   return p;
 }
 template <class F>
-hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool logits, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
+hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool logits, bool one_step, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
   const bool big = use_big_tiles(t.batch, t.Hkv, t.M, t.k_width, t.conv_in, n_cu);
   auto pick_cin = [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto spl) {
     if constexpr (decltype(bm)::value == 32) {
-      if (t.conv_in) return f(bm, kw, norm, prot, mu, spl, ic<1>{}, ic<0>{});
+      if (t.conv_in) return f(bm, kw, norm, prot, mu, spl, ic<1>{}, ic<0>{}, ic<1>{});
+      if constexpr (decltype(spl)::value == 2) {
+        if (one_step) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<0>{}, ic<1>{});
+      }
     }
     if constexpr (decltype(prot)::value == 0 && decltype(spl)::value != 1) {
-      if (logits) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<1>{});
+      if (logits) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<1>{}, ic<0>{});
     }
-    return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<0>{});
+    return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<0>{}, ic<0>{});
   };
   auto pick_multi = [&](auto bm, auto kw, auto norm, auto prot) {
     if constexpr (decltype(bm)::value == 32) {
@@ -100,12 +123,11 @@ hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool log
   return hipErrorInvalidValue;   // compress_mfma_supports() keeps other shapes away
 }
 
-template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN, int LOG>
+template <class B>
 hipError_t prepare_kernel() {
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, Geo<BM, KW>::LDS);
+    hipError_t e = hipFuncSetAttribute((const void*)B::kernel(), hipFuncAttributeMaxDynamicSharedMemorySize, B::kLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
@@ -114,16 +136,15 @@ hipError_t prepare_kernel() {
 
 hipError_t dispatch(const ScanArgs& a, const uint16_t* wp, int64_t wp_head_stride, int n_cu, hipStream_t s) {
   const bool multi = a.groups < a.st.batch * a.st.Hkv;
-  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), a.logits != nullptr, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo) {
+  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), a.logits != nullptr, a.n_steps == 1 && !a.logits, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
-    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value;
-    hipError_t e = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>();
+    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value, ROLES = decltype(ro)::value;
+    using B = Build<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG, ROLES>;
+    hipError_t e = prepare_kernel<B>();
     if (e != hipSuccess) return e;
     dim3 grid((a.st.M / BM) * a.groups * (SPLIT ? a.psplit : 1));
-    constexpr int kLds = Geo<BM, KW>::LDS;
-    hipLaunchKernelGGL((compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>), grid, dim3(kThreads), kLds, s, a, wp,
-                       wp_head_stride);
+    hipLaunchKernelGGL(B::kernel(), grid, dim3(B::kWgThreads), B::kLds, s, a, wp, wp_head_stride);
     return hipGetLastError();
   });
 }
@@ -157,13 +178,17 @@ size_t compress_prelogits_bytes(int batch, int Hkv, int M, int B, int conv_in, i
   return conv_in ? (size_t)pairs * areas * prelogits_stride(M, B) * sizeof(float) : 0;
 }
 
-hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, hipStream_t s) {
+static uint32_t* psync_of(void* sync_ws, int batch, int Hkv) { return (uint32_t*)sync_ws + 2 * batch * Hkv + 1; }
+
+hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s) {
   const int C = a.conv_in ? 2 * kD : kD;
   const int64_t n = (int64_t)banks * a.M * (C / 8) * a.k_width;   // 16-byte chunks
   int blocks = (int)((n + 255) / 256);
   if (blocks > 2048) blocks = 2048;
   hipLaunchKernelGGL(repack_filters_k, dim3(blocks), dim3(256), 0, s, (const uint16_t*)a.conv_w,
-                     (uint16_t*)wp, a.M, C, a.k_width, banks, a.w_head_stride);
+                     (uint16_t*)wp, a.M, C, a.k_width, banks, a.w_head_stride, (uint32_t*)sync_ws,
+                     sync_ws ? 2 * a.batch * a.Hkv + 1 : 0, sync_ws ? psync_of(sync_ws, a.batch, a.Hkv) : nullptr,
+                     sync_ws ? 2 * a.batch * a.Hkv * (a.M / 32) : 0);
   return hipGetLastError();
 }
 
@@ -173,7 +198,6 @@ hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, hipStre
 size_t compress_scan_sync_bytes(int batch, int Hkv, int M) {
   return ((size_t)batch * Hkv * (2 + 2 * (M / 32)) + 1) * sizeof(uint32_t);
 }
-static uint32_t* psync_of(void* sync_ws, int batch, int Hkv) { return (uint32_t*)sync_ws + 2 * batch * Hkv + 1; }
 
 int compress_position_split(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu) {
   return position_split(batch, Hkv, M, k_width, conv_in, n_cu);
@@ -249,15 +273,14 @@ int compress_scan_max_resident(const StepArgs& a, int n_cu) {
   const int split = multi ? 0 : step_pipeline(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) ? 2
                     : position_split(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) > 1 ? 1 : 0;
   int per_cu = 0;
-  hipError_t e = with_instantiation(a, multi, split, false, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo) {
+  hipError_t e = with_instantiation(a, multi, split, false, false, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
-    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value;
-    hipError_t e2 = prepare_kernel<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>();
+    constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value, ROLES = decltype(ro)::value;
+    using B = Build<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG, ROLES>;
+    hipError_t e2 = prepare_kernel<B>();
     if (e2 != hipSuccess) return e2;
-    constexpr int kLds = Geo<BM, KW>::LDS;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)compress_mfma_k<BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG>,
-                                                        kThreads, kLds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)B::kernel(), B::kWgThreads, B::kLds);
   });
   if (e != hipSuccess) { (void)hipGetLastError(); return 0; }
   return per_cu * n_cu;

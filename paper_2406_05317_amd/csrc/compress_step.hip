@@ -6,7 +6,7 @@
 // (18.5 + 10.5), 18.9 us.
 #include "attn_decode_row.h"
 #include "attn_tile.h"
-#include "compress_tile.h"
+#include "compress_roles.h"
 
 namespace lococo {
 namespace {
@@ -14,30 +14,29 @@ namespace {
 using namespace compress_detail;
 
 template <int KW, int NORM, int CIN>
-__global__ __launch_bounds__(kThreads, 1) void compress_step_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride,
+__global__ __launch_bounds__(kRoleThreads, 2) void compress_step_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride,
                                                                int n_compress, AttnArgs at) {
   extern __shared__ __align__(16) unsigned char smem[];
   if ((int)blockIdx.x >= n_compress) {
     const int id = blockIdx.x - n_compress;
     if (sa.st.Bn == 1)
-      attn_decode_detail::attn_decode_row<kThreads / 64, false>(sa.st, *(attn_decode_detail::Parts*)smem, nullptr, id);
-    else
+      attn_decode_detail::attn_decode_row<kRoleThreads / 64, false>(sa.st, *(attn_decode_detail::Parts*)smem, nullptr, id);
+    else if (threadIdx.x < 256)              // (its work is cut for four waves)
       attn_tile_detail::attn_tile(at, smem, id);
     return;
   }
   // The build that has two workgroups per pair in a scan, of which the first has the one step: item 2 k of twice n_compress,
   // numbered so that the slot tiles of a chain are on one XCD here too
-  constexpr int BM = 32, PROT = 0, MULTI = 0, SPLIT = 2, LOG = 0;
   const uint32_t wg_count = 2 * n_compress, per = wg_count / 8;
   uint32_t k = blockIdx.x;
   if (k < n_compress / 8u * 8u) k = (k % 8) * (n_compress / 8u) + k / 8;
   const uint32_t wg_id = 2 * k < per * 8 ? 2 * k % per * 8 + 2 * k / per : 2 * k;
-#include "compress_tile.inl"
+  compress_roles<KW, NORM, 0, 0, 2, CIN>(sa, wp, wp_head_stride, smem, wg_id, wg_count);
 }
 
 template <int KW, int NORM, int CIN>
 hipError_t launch(const ScanArgs& sa, const uint16_t* wp, int64_t wp_head_stride, const AttnArgs& at, int n_attn, hipStream_t s) {
-  constexpr int lds = Geo<32, KW>::LDS;
+  constexpr int lds = Roles<KW>::LDS;
   static_assert(lds >= attn_tile_detail::LDS_BYTES && lds >= (int)sizeof(attn_decode_detail::Parts), "one LDS area for all");
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
@@ -46,7 +45,7 @@ hipError_t launch(const ScanArgs& sa, const uint16_t* wp, int64_t wp_head_stride
     attr_set = true;
   }
   const int n = sa.st.batch * sa.st.Hkv * (sa.st.M / 32);
-  hipLaunchKernelGGL((compress_step_k<KW, NORM, CIN>), dim3(n + n_attn), dim3(kThreads), lds, s, sa, wp, wp_head_stride, n, at);
+  hipLaunchKernelGGL((compress_step_k<KW, NORM, CIN>), dim3(n + n_attn), dim3(kRoleThreads), lds, s, sa, wp, wp_head_stride, n, at);
   return hipGetLastError();
 }
 

@@ -1,11 +1,10 @@
 // The work of one workgroup of the fused compression kernel, included as the body of the kernels that have it (template
-// parameters BM, KW, NORM, PROT, MULTI, SPLIT, CIN, LOG, as described in compress_tile.h).  In scope: ScanArgs sa, wp,
+// parameters BM, KW, NORM, PROT, MULTI, SPLIT, LOG, as described in compress_tile.h).  In scope: ScanArgs sa, wp,
 // wp_head_stride, smem (Geo<BM, KW>::LDS bytes), and wg_id of wg_count.  It is text and not an inlined function because the
 // 64-slot builds use all 512 registers: as a function the same code spilled differently and the 32 K-token scan took 4 % longer.
   using G = Geo<BM, KW>;
   static_assert(!SPLIT || (BM == 32 && !MULTI), "the splits are built for 32-slot tiles, one chain per workgroup");
   constexpr bool PSPLIT = SPLIT == 1, PIPE = SPLIT == 2;
-  static_assert(!CIN || BM == 32, "[K | V] filters are built for 32-slot tiles");
   const StepArgs& a = sa.st;
   unsigned char* Xs0 = smem;                                    // NXBUF key tiles (with halo)
   unsigned char* Vs0 = Xs0 + G::NXBUF * G::XBYTES;              // NVBUF value tiles
@@ -45,11 +44,8 @@
   // ---- this wave's slice of the filter bank, resident in registers for the whole kernel:
   // lane (slot l31 of tile rt, channels 32w + 16h + 8*lh ..) for every tap
   bf16x8 wreg[G::RT][KW][2];
-  // (Requesting a [K | V] bank's next half as soon as the last logit MFMA of a pass has issued, so that it
-  // arrives while the pass drains, was tried: the allocator has nowhere to keep 168 registers in flight and
-  // spills them.)
-  auto load_filters = [&](int half_of_bank) {          // 0: the bank (or its key half), 1: its value half
-    const uint16_t* wb = wp + hkv0 * wp_head_stride + (CIN ? (int64_t)half_of_bank * a.M * (KW * kD) : 0);
+  {
+    const uint16_t* wb = wp + hkv0 * wp_head_stride;
 #pragma unroll
     for (int rt = 0; rt < G::RT; ++rt)
 #pragma unroll
@@ -66,12 +62,7 @@
       for (int t = 0; t < KW; ++t)
 #pragma unroll
         for (int h = 0; h < 2; ++h) asm volatile("" : "+a"(wreg[rt][t][h]));
-  };
-  if (!CIN) load_filters(0);
-  // key-side logits of one tile as this lane left them in the first walk (CIN only)
-  f32x4 pre = {0.f, 0.f, 0.f, 0.f};
-  __amdgpu_buffer_rsrc_t pre_rows = __builtin_amdgcn_make_buffer_rsrc((void*)sa.prelogits, 0, 0, 0x00020000);
-
+  }
   __amdgpu_buffer_rsrc_t log_rows = __builtin_amdgcn_make_buffer_rsrc((void*)sa.logits, 0, 0, 0x00020000);
 
   // mixing accumulator, transposed: lane = slot rt*32 + l31, rows = columns 64w + ct*32 + (i/4)*8 + lh*4 + i%4
@@ -152,15 +143,12 @@
   // consumed this tile's partial logits; the buffer is rewritten at the end of the stage.
   // Neither needs outstanding global loads to finish, so they are plain barriers preceded by a
   // wait on the LDS counter only.
-  // PH: 0 = the one walk of a bank over the keys; 1 = first walk of a [K | V] bank (logits of the key
-  // half only: DoSoftmax then means "sum the waves' partial logits and store them"); 2 = its second walk.
   // RI: the tile index modulo the period of the buffer rings (key tiles: NXBUF; values, probabilities,
   // rescale factors: 2) where the caller knows it at compile time, so that every buffer address of the
   // stage is a constant; -1: computed from i.
-  auto stage = [&](int i, auto do_conv, auto do_softmax, auto do_mix_t, auto ph_t, auto ring_t) {
+  auto stage = [&](int i, auto do_conv, auto do_softmax, auto do_mix_t, auto ring_t) {
     constexpr bool DoConv = decltype(do_conv)::value, DoSoftmax = decltype(do_softmax)::value;
     constexpr bool DoMix = decltype(do_mix_t)::value;
-    constexpr int PH = decltype(ph_t)::value;
     constexpr int RI = decltype(ring_t)::value;
     const int ib = RI >= 0 ? RI + 2 * G::NXBUF : i;      // (kept positive: ib - 1 enters a remainder)
     const int j0 = (SPLIT ? jbase : 0) + i * BN;
@@ -185,7 +173,7 @@
     };
     // protected positions of tile i (bits of live protected slots; BN = 32 = one mask word)
     uint32_t pmask = 0;
-    if (PROT && DoSoftmax && PH != 1 && j0 < m) {
+    if (PROT && DoSoftmax && j0 < m) {
       pmask = pwords[j0 >> 5];
       if (j0 + BN > m) pmask &= (1u << (m - j0)) - 1u;
     }
@@ -204,8 +192,7 @@
     auto sm_add = [&](int ww0, int e4) {      // 4 positions: + partials ww0 and ww0+1
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        sv[e4 * 4 + e] = ww0 == 0 ? (PH == 2 ? pre[e] : 0.f) + (NORM == 0 || PH == 1 ? part[0][e4][e] + part[1][e4][e]
-                                                                                        : bias + part[0][e4][e] + part[1][e4][e])
+        sv[e4 * 4 + e] = ww0 == 0 ? (NORM == 0 ? part[0][e4][e] + part[1][e4][e] : bias + part[0][e4][e] + part[1][e4][e])
                                   : sv[e4 * 4 + e] + part[ww0][e4][e] + part[ww0 + 1][e4][e];
     };
     auto sm_exp = [&](int e) {
@@ -259,7 +246,6 @@
         // store or one load fits the shadow of an MFMA, a store and two loads together do not.
         constexpr int kPieces = 3 * (G::XPER + G::VPER);
         constexpr bool kSpread = kSlots - kPieces - 1 >= kSlots * 3 / 5 + 8;   // behind the softmax and the mixing fetches
-        static_assert(!CIN || !kSpread, "[K | V] banks run on the 32-slot tiles' staging order");
         if (kSpread) {
           constexpr int Z0 = kSlots - kPieces - 1;
           if (slot >= Z0 && slot < Z0 + kPieces) {
@@ -275,11 +261,11 @@
             }
           }
         } else {
-          if ((PH != 1 || DoConv) && slot >= 5 * S && slot < 5 * S + G::XPER) {
+          if (slot >= 5 * S && slot < 5 * S + G::XPER) {
             store_x(slot - 5 * S, j0 + 3 * BN, Xstage);
             load_x(slot - 5 * S, j0 + 4 * BN);
           }
-          if (PH != 1 && slot >= 5 * S + G::XPER && slot < 5 * S + G::XPER + G::VPER) {
+          if (slot >= 5 * S + G::XPER && slot < 5 * S + G::XPER + G::VPER) {
             store_v(slot - 5 * S - G::XPER, j0, Vstage);
             load_v(slot - 5 * S - G::XPER, j0 + BN);
           }
@@ -287,15 +273,6 @@
         if (slot >= 8 * S && slot < 8 * S + E4) sm_add(0, slot - 8 * S);
         if (slot >= 8 * S + E4 && slot < 8 * S + 2 * E4) sm_add(2, slot - 8 * S - E4);
         if (slot == 8 * S + 2 * E4) __builtin_amdgcn_s_barrier();   // B2: the partial logits have been consumed
-        if (PH == 1 && slot == 8 * S + 2 * E4 + 1) {
-          // first walk: this lane's four sums go to the workspace; the second walk reads them back (same lane,
-          // at device scope: from the L2 the store went through to, whatever this CU's L1 holds from a step ago)
-          static_assert(!CIN || E4 == 1, "one 16-byte chunk of key-side logits per lane and tile");
-          const f32x4 v = {sv[0], sv[1], sv[2], sv[3]};
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), pre_rows, ((j0 / BN) * (BM * BN) + tid * 4) * 4, 0, 0);
-        }
-        if (PH == 2 && slot == 8 * S + 2 * E4 + 1)     // the next tile's, a whole stage before they are added
-          pre = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pre_rows, ((j0 / BN + 1) * (BM * BN) + tid * 4) * 4, 0, kDeviceScope));
         if (LOG && slot == 8 * S + 2 * E4 + 1) {       // the logits as they are, for the backward pass
 #pragma unroll
           for (int e4 = 0; e4 < E4; ++e4) {
@@ -303,7 +280,7 @@
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), log_rows, (srow * sa.logits_ld + sp0 + e4 * 4) * 4, j0 * 4, 0);
           }
         }
-        if (PH != 1 && slot == 8 * S + 2 * E4 + 1) {
+        if (slot == 8 * S + 2 * E4 + 1) {
           if (j0 + BN > T) {                   // tail tile: positions past T carry no weight
 #pragma unroll
             for (int e = 0; e < G::EPL; ++e)
@@ -320,8 +297,8 @@
             for (int e = 1; e < G::EPL; ++e) mx = fmaxf(mx, sv[e]);
           }
         }
-        if (PH != 1 && NORM == 0 && slot == 8 * S + 2 * E4 + 2) mx = group_max<G::LPR>(mx);
-        if (PH != 1 && NORM == 0 && slot == 8 * S + 2 * E4 + 3) {
+        if (NORM == 0 && slot == 8 * S + 2 * E4 + 2) mx = group_max<G::LPR>(mx);
+        if (NORM == 0 && slot == 8 * S + 2 * E4 + 3) {
           // The reference only moves when the row maximum outgrows it by kLazy, so exp(s - ref)
           // stays below e^kLazy and the accumulators are rescaled rarely.  Every tile has a
           // position < T, so mx is finite -- unless all 32 positions of the tile are protected
@@ -333,21 +310,21 @@
           mc = dead ? 0.f : m_new * kLog2e;
         }
         constexpr int X0 = 8 * S + 2 * E4 + 4;   // one exponential per slot
-        if (PH != 1 && slot >= X0 && slot < X0 + G::EPL) sm_exp(slot - X0);
-        if (PH != 1 && slot == X0 + G::EPL) {
+        if (slot >= X0 && slot < X0 + G::EPL) sm_exp(slot - X0);
+        if (slot == X0 + G::EPL) {
 #pragma unroll
           for (int e = 0; e < G::EPL; ++e) psum += sv[e];
         }
-        if (PH != 1 && slot == X0 + G::EPL + 1) {
+        if (slot == X0 + G::EPL + 1) {
           psum = group_sum<G::LPR>(psum);
           l_run = l_run * alpha + psum;
           m_run = m_new;
         }
-        if (PH != 1 && slot == X0 + G::EPL + 2) {
+        if (slot == X0 + G::EPL + 2) {
 #pragma unroll
           for (int e2 = 0; e2 < G::EPL / 2; ++e2) packed[e2] = pack_bf16(sv[2 * e2], sv[2 * e2 + 1]);
         }
-        if (PH != 1 && slot == X0 + G::EPL + 3) {
+        if (slot == X0 + G::EPL + 3) {
 #pragma unroll
           for (int e4 = 0; e4 < E4; ++e4) {
             const u32x2 pk = {packed[2 * e4], packed[2 * e4 + 1]};
@@ -521,19 +498,14 @@
   }
 
   const int n_mine = MULTI ? (n_chains - grp + groups - 1) / groups : 1;
-  // A bank over [K | V] makes two passes over the workgroup's chains per step -- every chain's first walk
-  // with the key half of the filters in the registers, then every chain's second walk with the value
-  // half -- so that a step costs two loads of a filter slice however many chains share it.
-  for (int step = 0; step < sa.n_steps; ++step)
-  for (int pass = 0; pass < (CIN ? 2 : 1); ++pass) {
+  for (int step = 0; step < sa.n_steps; ++step) {
   if (PIPE && (step & 1) != part) continue;            // the partner's step
-  if (CIN) load_filters(pass);
   for (int ci = 0; ci < n_mine; ++ci) {
   const int ch = grp + ci * groups;
   // ---- the step reads what every slot tile of this chain wrote in the step before
-  if (!PIPE && pass == 0 && step > 0 && !chain_wait(ch, step)) return;
+  if (!PIPE && step > 0 && !chain_wait(ch, step)) return;
   // PIPE: the chain is met between the two legs of the walk
-  const bool meet_between = PIPE && pass == 0 && step > 0;
+  const bool meet_between = PIPE && step > 0;
   int first_blk = 0, NT_all = 0;
   // ---- this step's inputs: source state, occupancy, block
   {
@@ -569,7 +541,7 @@
   // ---- prologue of a walk: key tiles 0, 1 and 2 staged; key tile 3 and value tile 0 on their way.  All
   // loads are issued before the first store (the accumulators' registers are free here), so the
   // walk starts after one memory latency, not three.
-  auto prologue = [&](bool with_v) {
+  auto prologue = [&]() {
     const int jb = SPLIT ? jbase : 0;
     Cat16 xpro[3][G::XPER];
 #pragma unroll
@@ -581,10 +553,8 @@
       }
 #pragma unroll
     for (int it = 0; it < G::XPER; ++it) load_x(it, jb + 3 * BN);
-    if (with_v) {
 #pragma unroll
-      for (int it = 0; it < G::VPER; ++it) load_v(it, jb);
-    }
+    for (int it = 0; it < G::VPER; ++it) load_v(it, jb);
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
@@ -606,12 +576,12 @@
   // the 64-slot builds answered with spills inside the copies and ran 1.6 times as long (two copies, with only the
   // parity of the index a constant, did not spill and gained 0.7 %, but the launch then fetched 18 % more from
   // HBM), so they and every other build keep the one copy.
-  constexpr bool RINGU = BM == 32 && KW == 15 && !CIN && SPLIT != 1 && !(PROT && SPLIT == 2);
-  auto steady_unrolled = [&](auto ph_t) {
+  constexpr bool RINGU = BM == 32 && KW == 15 && SPLIT != 1 && !(PROT && SPLIT == 2);
+  auto steady_unrolled = [&]() {
     int i = 1;
     auto one = [&](auto r_t) {
       if (!(i + 1 < NT)) return false;
-      stage(i, yes, yes, yes, ph_t, r_t);
+      stage(i, yes, yes, yes, r_t);
       ++i;
       return true;
     };
@@ -634,41 +604,30 @@
   // leg's range.  The two forms are kept apart on purpose: the one-walk builds' register allocation is
   // tight (all 512 registers in use) and has answered to small changes of this code with spills inside the
   // stage loop, so they keep their code as it was.
-  constexpr std::integral_constant<int, 1> first{};
-  constexpr std::integral_constant<int, CIN ? 2 : 0> ph{};
-  // first walk over a [K | V] bank: the key half of the filters, the key rows; summed logits to the workspace
-  auto walk_first = [&]() {
-    prologue(false);
-    stage(-1, yes, no, no, first, dyn);
-    for (int i = 0; i + 1 < NT; ++i) stage(i, yes, yes, no, first, dyn);
-    stage(NT - 1, no, yes, no, first, dyn);
-  };
   // the walk that mixes: pipeline fill, steady state, drain
   auto walk_main = [&]() {
-    if (CIN)
-      pre = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pre_rows, (((SPLIT ? jbase : 0) / BN) * (BM * BN) + tid * 4) * 4, 0, kDeviceScope));
-    prologue(true);
+    prologue();
     if constexpr (RINGU) {
-      stage(-1, yes, no, no, ph, std::integral_constant<int, 9>{});
+      stage(-1, yes, no, no, std::integral_constant<int, 9>{});
       if (NT > 1) {
-        stage(0, yes, yes, no, ph, std::integral_constant<int, 0>{});
-        steady_unrolled(ph);
-        stage(NT - 1, no, yes, yes, ph, dyn);
+        stage(0, yes, yes, no, std::integral_constant<int, 0>{});
+        steady_unrolled();
+        stage(NT - 1, no, yes, yes, dyn);
       } else {
-        stage(0, no, yes, no, ph, std::integral_constant<int, 0>{});
+        stage(0, no, yes, no, std::integral_constant<int, 0>{});
       }
-      stage(NT, no, no, yes, ph, dyn);
+      stage(NT, no, no, yes, dyn);
       return;
     }
-    stage(-1, yes, no, no, ph, dyn);                          // logits of tile 0 only
+    stage(-1, yes, no, no, dyn);                          // logits of tile 0 only
     if (NT > 1) {
-      stage(0, yes, yes, no, ph, dyn);
-      for (int i = 1; i + 1 < NT; ++i) stage(i, yes, yes, yes, ph, dyn);
-      stage(NT - 1, no, yes, yes, ph, dyn);
+      stage(0, yes, yes, no, dyn);
+      for (int i = 1; i + 1 < NT; ++i) stage(i, yes, yes, yes, dyn);
+      stage(NT - 1, no, yes, yes, dyn);
     } else {
-      stage(0, no, yes, no, ph, dyn);
+      stage(0, no, yes, no, dyn);
     }
-    stage(NT, no, no, yes, ph, dyn);
+    stage(NT, no, no, yes, dyn);
   };
   auto zero_state = [&]() {
 #pragma unroll
@@ -692,21 +651,6 @@
     }
     return true;
   };
-  if constexpr (CIN) {
-    // (the two workgroups of a pair work on different steps at the same time: an area each)
-    pre_rows = __builtin_amdgcn_make_buffer_rsrc((void*)(sa.prelogits + (int64_t)((ch * tiles + i0 / BM) * (PIPE ? 2 : 1) + (PIPE ? part : 0)) * sa.pre_stride), 0,
-                                                 (int)sa.pre_stride * 4, 0x00020000);
-    if (pass == 0) {
-      for (int leg = 0; leg < 2; ++leg) {
-        if (!set_leg(leg)) return;
-        if (NT > 0) walk_first();
-        __syncthreads();                 // the next leg's prologue writes the tiles this one read last
-      }
-      continue;
-    }
-    // ---- second walk: the value half, the value rows where the key rows were and the other way round
-    { const CatRows t = cat_k; cat_k = cat_v; cat_v = t; }
-  }
   zero_state();
   for (int leg = 0; leg < 2; ++leg) {
     if (!set_leg(leg)) return;
@@ -715,24 +659,6 @@
   }
 
   } else {
-  if constexpr (CIN) {
-    pre_rows = __builtin_amdgcn_make_buffer_rsrc((void*)(sa.prelogits + (int64_t)(ch * tiles + i0 / BM) * sa.pre_stride), 0,
-                                                 (int)sa.pre_stride * 4, 0x00020000);
-    if (pass == 0) {
-      // ---- first walk: the key half of the filters, the key rows; summed logits to the workspace
-      constexpr std::integral_constant<int, 1> first{};
-      if (!SPLIT || NT > 0) {
-        prologue(false);
-        stage(-1, yes, no, no, first, dyn);
-        for (int i = 0; i + 1 < NT; ++i) stage(i, yes, yes, no, first, dyn);
-        stage(NT - 1, no, yes, no, first, dyn);
-      }
-      continue;
-    }
-    // ---- second walk: the value half, the value rows where the key rows were and the other way round
-    { const CatRows t = cat_k; cat_k = cat_v; cat_v = t; }
-    pre = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(pre_rows, (((SPLIT ? jbase : 0) / BN) * (BM * BN) + tid * 4) * 4, 0, kDeviceScope));
-  }
   if (!SPLIT || NT > 0) {
 #pragma unroll
   for (int ct = 0; ct < 2; ++ct)
@@ -742,30 +668,29 @@
       for (int i = 0; i < 16; ++i) oacc[ct][rt][i] = 0.f;
   m_run = -INFINITY;
   l_run = 0.f;
-  constexpr std::integral_constant<int, CIN ? 2 : 0> ph{};
-  prologue(true);
+  prologue();
   if constexpr (RINGU) {
-  stage(-1, yes, no, no, ph, std::integral_constant<int, 9>{});
+  stage(-1, yes, no, no, std::integral_constant<int, 9>{});
   if (NT > 1) {
-    stage(0, yes, yes, no, ph, std::integral_constant<int, 0>{});
-    steady_unrolled(ph);
-    stage(NT - 1, no, yes, yes, ph, dyn);
+    stage(0, yes, yes, no, std::integral_constant<int, 0>{});
+    steady_unrolled();
+    stage(NT - 1, no, yes, yes, dyn);
   } else {
-    stage(0, no, yes, no, ph, std::integral_constant<int, 0>{});
+    stage(0, no, yes, no, std::integral_constant<int, 0>{});
   }
-  stage(NT, no, no, yes, ph, dyn);
+  stage(NT, no, no, yes, dyn);
   } else {
-  stage(-1, yes, no, no, ph, dyn);                          // logits of tile 0 only
+  stage(-1, yes, no, no, dyn);                          // logits of tile 0 only
 
   // ---- pipeline fill, steady state, drain
   if (NT > 1) {
-    stage(0, yes, yes, no, ph, dyn);
-    for (int i = 1; i + 1 < NT; ++i) stage(i, yes, yes, yes, ph, dyn);
-    stage(NT - 1, no, yes, yes, ph, dyn);
+    stage(0, yes, yes, no, dyn);
+    for (int i = 1; i + 1 < NT; ++i) stage(i, yes, yes, yes, dyn);
+    stage(NT - 1, no, yes, yes, dyn);
   } else {
-    stage(0, no, yes, no, ph, dyn);
+    stage(0, no, yes, no, dyn);
   }
-  stage(NT, no, no, yes, ph, dyn);
+  stage(NT, no, no, yes, dyn);
   }
   } else {                                 // a part without positions hands in an empty result
 #pragma unroll
@@ -784,9 +709,8 @@
   uint16_t* nv;
   {
     const int64_t out_at = (int64_t)((sa.slot0 + step) % sa.ring) * sa.out_stride + ((int64_t)ch * a.M + i0) * kD;
-    // (after the second walk of a [K | V] bank the accumulator's first d columns are the value rows)
-    nk = (uint16_t*)(CIN ? sa.out_v : sa.out_k) + out_at;
-    nv = (uint16_t*)(CIN ? sa.out_k : sa.out_v) + out_at;
+    nk = (uint16_t*)sa.out_k + out_at;
+    nv = (uint16_t*)sa.out_v + out_at;
   }
   if constexpr (PSPLIT) {
     // ---- this part's result goes to the workspace: accumulators [slot][2 d] as they are
@@ -953,4 +877,4 @@
   if (step + 1 < sa.n_steps) chain_signal(ch);
   else __syncthreads();
   }  // chains
-  }  // steps and passes
+  }  // steps

@@ -187,7 +187,8 @@ size_t compress_mfma_filter_bytes(int M, int conv_width, int conv_in, int banks)
 // B: the longest block of the call
 size_t compress_prelogits_bytes(int batch, int Hkv, int M, int B, int conv_in, int n_cu);
 // conv_w [M][C][k] (+ w_head_stride per bank) -> wp [bank][M][k][C]
-hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, hipStream_t s);
+// sync_ws: null, or the scan's counters and status word, which the same launch then zeroes (see launch_scan_sync_clear)
+hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s);
 // Eq. 5 + Eq. 6 + Eq. 4a/4b in one kernel; writes a.new_k / a.new_v
 // sync_ws / partials: compress_scan_sync_bytes() / compress_partials_bytes() of device memory
 // prelogits: compress_prelogits_bytes(.., B, ..) of device memory, B >= a.Bn

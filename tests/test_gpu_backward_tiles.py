@@ -1,0 +1,99 @@
+"""The backward kernels of Eq. 4 - 6 at the edges of their tiles, and the logits a recomputed scan leaves behind."""
+import pytest
+import torch
+
+from paper_2406_05317_amd import binding as lb
+from paper_2406_05317_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _rnd(g, *shape, sd=0.3, dtype=torch.bfloat16):
+    return torch.empty(shape, dtype=dtype, device=DEV).normal_(0, sd, generator=g)
+
+
+def _rel(a, b):
+    return float((a.double() - b.double()).norm() / b.double().norm().clamp_min(1e-30))
+
+
+@pytest.mark.parametrize("case", [
+    # (chains x row tiles decide the tile: 128, 64, 32 rows, and 32 rows in halves)
+    dict(batch=2, n_kv_heads=32, M=256, B=256),                                    # 128 rows, whole
+    dict(batch=2, n_kv_heads=32, M=253, B=254),                                    # 128 rows in three parts (507 positions)
+    dict(batch=2, n_kv_heads=32, M=100, B=100, conv_width=5),                      # 64 rows, slots past a chunk, KW % 3 = 2
+    dict(batch=2, n_kv_heads=32, M=97, B=101, conv_width=31),                      # the same in three parts, KW % 3 = 1
+    dict(batch=2, n_kv_heads=32, M=64, B=36, conv_width=21),                       # 32 rows
+    dict(batch=2, n_kv_heads=32, M=33, B=66, conv_width=3),                        # 32 rows in three parts, one slot past a tile
+    dict(batch=1, n_kv_heads=2, M=129, B=1),                                       # halves, a token
+    dict(batch=1, n_kv_heads=3, M=160, B=77, conv_width=7, per_head=True),         # halves in three parts, banks of their own
+    dict(batch=1, n_kv_heads=2, M=130, B=62, conv_in=1, conv_width=21),            # [K | V] filters: taps on both halves
+    dict(batch=2, n_kv_heads=32, M=128, B=384, conv_in=1),                         # the same with 128 rows
+    dict(batch=1, n_kv_heads=2, M=16, B=8, conv_width=1),                          # the smallest: sixteen slots, one tap
+], ids=str)
+def test_input_and_filter_gradients_at_tile_edges(case):
+    """Against the shape-agnostic fp32 kernels, which agree with the oracle to 3e-7.  g, n and dl keep 16 bits where they enter
+    a product: at most three such roundings of 2^-17 each on any path, 2.3e-5."""
+    c = dict(dict(conv_width=15, conv_in=0, per_head=False), **case)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    b, h, M, B, kw = c["batch"], c["n_kv_heads"], c["M"], c["B"], c["conv_width"]
+    C = 256 if c["conv_in"] else 128
+    q, k, v = (_rnd(g, b, h, B, 128) for _ in range(3))
+    ck, cv = _rnd(g, b, h, M, 128), _rnd(g, b, h, M, 128)
+    cw = _rnd(g, *([h] if c["per_head"] else []), M, C, kw, sd=0.05)
+    d_o, gk, gv = (_rnd(g, *s, sd=1.0, dtype=torch.float32) for s in (q.shape, ck.shape, ck.shape))
+    got = []
+    for impl in (lb.LOCOCO_IMPL_AUTO, lb.LOCOCO_IMPL_GENERIC):
+        cfg = lb.make_config(dtype=torch.bfloat16, batch=b, n_q_heads=h, n_kv_heads=h, head_dim=128, M=M, conv_width=kw,
+                             conv_in=c["conv_in"], impl=impl, **({"w_head_stride": M * C * kw} if c["per_head"] else {}))
+        cache = lb.Cache(cfg, DEV)
+        cache.load(ck, cv, M)
+        out = [torch.full_like(t, float("nan"), dtype=torch.float32) for t in (q, k, v, ck, cv)]
+        d_w = torch.zeros_like(cw, dtype=torch.float32)
+        ws = torch.full((lb.lococo_backward_workspace_bytes(cfg, B, M),), 0xff, dtype=torch.uint8, device=DEV)
+        lb.lococo_segment_step_backward(cfg, q, k, v, cw, None, cache, d_o, gk, gv, *out, d_w, None, ws)
+        got.append(out + [d_w])
+    for name, a, want in zip(("d_q", "d_k", "d_v", "d_cache_k", "d_cache_v", "d_w"), *got):
+        assert _rel(a, want) < 2.3e-5, (name, _rel(a, want))
+
+
+@pytest.mark.parametrize("case", [
+    dict(batch=1, n_kv_heads=2, M=64, B=48, L=300),                                # pairs of workgroups; a fill, a ragged block
+    dict(batch=1, n_kv_heads=2, M=96, B=96, L=481, conv_width=21, norm=1, bias=True),   # last block of one token
+    dict(batch=2, n_kv_heads=32, M=96, B=64, L=320),                               # a workgroup per chain and 32 slots
+    dict(batch=4, n_kv_heads=32, M=96, B=64, L=256, norm=1, bias=True),            # several chains per workgroup
+    dict(batch=4, n_kv_heads=32, M=128, B=70, L=333),                              # 64 slots
+    dict(batch=8, n_kv_heads=32, M=128, B=128, L=512, norm=1),                     # 64 slots, several chains per workgroup
+    dict(batch=1, n_kv_heads=2, M=64, B=64, L=256, protect=True),                  # computed window by window in either case
+    dict(batch=1, n_kv_heads=2, M=64, B=64, L=256, conv_in=1),
+], ids=str)
+def test_logits_left_by_the_scan_are_those_computed_again(case):
+    """With one byte less than the full workspace the logits are computed in a kernel of their own: the same products in
+    another order (1e-6 of a logit, which moves a softmax weight by as much; under the rectified sum one logit in 1e6 may
+    also change sides of zero, which takes its entry in or out)."""
+    c = dict(dict(conv_width=15, norm=0, conv_in=0, bias=False, protect=False), **case)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    b, h, M, B, L, kw = (c[n] for n in ("batch", "n_kv_heads", "M", "B", "L", "conv_width"))
+    C = 256 if c["conv_in"] else 128
+    cfg = lb.make_config(dtype=torch.bfloat16, batch=b, n_q_heads=h, n_kv_heads=h, head_dim=128, M=M, conv_width=kw,
+                         conv_in=c["conv_in"], norm=c["norm"])
+    q, k, v = (_rnd(g, b, h, L, 128) for _ in range(3))
+    cw = _rnd(g, M, C, kw, sd=0.05)
+    cb = _rnd(g, M, sd=0.5) if c["bias"] else None
+    d_o = _rnd(g, *q.shape, sd=1.0, dtype=torch.float32)
+    gk, gv = (_rnd(g, b, h, M, 128, sd=1.0, dtype=torch.float32) for _ in range(2))
+    full = lb.lococo_sequence_backward_workspace_bytes(cfg, L, B)
+    got = []
+    for n_bytes in (full, full - 1):
+        cache = lb.Cache(cfg, DEV)
+        if c["protect"]:
+            cache.set_protect((torch.arange(M) < 3).view(1, 1, -1).expand(b, h, -1).numpy())
+        out = [torch.full_like(t, float("nan"), dtype=torch.float32) for t in (q, k, v, gk, gv)]
+        d_w, d_b = torch.zeros_like(cw, dtype=torch.float32), torch.zeros(M, device=DEV) if c["bias"] else None
+        ws = torch.full((full,), 0xff, dtype=torch.uint8, device=DEV)[:n_bytes]
+        lb.lococo_sequence_backward(cfg, q, k, v, B, cw, cb, cache, d_o, gk, gv, *out, d_w, d_b, ws)
+        got.append(out + [d_w] + ([d_b] if c["bias"] else []))
+    for a, want in zip(*got):
+        assert torch.isfinite(a).all()
+        assert _rel(a, want) < (1e-3 if c["norm"] else 1e-5), _rel(a, want)
