@@ -14,8 +14,12 @@
 // Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.3 ms for the whole sequence (2.1 + 3.3) against 20.0 ms as
 // seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.27 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
-// between the products (matrix pipe 45 % busy in the first kernel, 27 % in the second).
+// between the products (matrix pipe 45 % busy in the first kernel, 30 % in the second).  Operands read ahead of their products,
+// fragments waited for before the loops and a loop of its own for either kind of wave (no spills, whose reloads waited for
+// the tiles just requested): 12 blocks of 256 queries on 512 keys, 2 x 32 heads on 8: 226 -> 216 and 339 -> 279 us.
 // D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.
+#include <type_traits>
+
 #include "lococo_internal.h"
 #include "mfma_util.h"
 
@@ -55,6 +59,13 @@ __device__ __forceinline__ void request_tile(const u32x4& rsrc, uint32_t st, uin
     const int r4 = w * (16 / W) + i, r = r4 * 4 + (l >> 4);
     load_to_lds(rsrc, lds + r4 * 1024, (row0 + r) * st + (((l & 15) ^ swz(r)) << 4));
   }
+}
+
+// Fragments loaded ahead of a loop have arrived here.  (Or the compiler counts them as possibly on their way in every pass of
+// the loop and waits for the tiles requested a moment ago instead: a trip to memory per tile.)
+__device__ __forceinline__ void landed(bf16x8 (&f)[8]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(f[i]));
 }
 
 template <int PARTS>
@@ -116,6 +127,7 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
   tile_addr(l, ad);
   const float c = a.scale * kLog2e, lazy_raw = 8.0f / a.scale;
   wait_loads<0>();
+  landed(fq);
   __syncthreads();
 
   // S^T and dP^T (32 keys x this wave's queries) of half kt of the tile at K / K + kTile
@@ -123,12 +135,23 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
     const unsigned char* k0 = K + kt * 32 * 256;
     sc = zero16();
     dp = zero16();
+    // (two steps' operands ahead of their products)
+    bf16x8 fk[3], fv[3];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      fk[ks] = *(const bf16x8*)(k0 + ad.row[ks]);
+      fv[ks] = *(const bf16x8*)(k0 + kTile + ad.row[ks]);
+    }
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const bf16x8 fk = *(const bf16x8*)(k0 + ad.row[ks]), fv = *(const bf16x8*)(k0 + kTile + ad.row[ks]);
-      sc = mfma32(fk, fq[ks], sc);
+      if (ks + 2 < 8) {
+        fk[(ks + 2) % 3] = *(const bf16x8*)(k0 + ad.row[ks + 2]);
+        fv[(ks + 2) % 3] = *(const bf16x8*)(k0 + kTile + ad.row[ks + 2]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      sc = mfma32(fk[ks % 3], fq[ks], sc);
 #pragma unroll
-      for (int p = 0; p < PARTS; ++p) dp = mfma32(fv, fo[ks][p], dp);
+      for (int p = 0; p < PARTS; ++p) dp = mfma32(fv[ks % 3], fo[ks][p], dp);
     }
   };
   // keys this lane's query does not see: score -inf, and no part in anything however bad their values are
@@ -209,12 +232,13 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
         bf16x8 fd[PARTS];
         split_parts<PARTS>(ds + 8 * s2, fd);
         const unsigned char* k0 = K + (kt * 32 + s2 * 16) * 256;
+        bf16x8 fk[4];
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          const bf16x8 fk = frag_tr(k0 + ad.tr[ct][0], k0 + ad.tr[ct][1]);
+        for (int ct = 0; ct < 4; ++ct) fk[ct] = frag_tr(k0 + ad.tr[ct][0], k0 + ad.tr[ct][1]);
 #pragma unroll
-          for (int p = 0; p < PARTS; ++p) acc[ct] = mfma32(fk, fd[p], acc[ct]);
-        }
+        for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma32(fk[ct], fd[p], acc[ct]);
       }
     }
     wait_loads<0>();
@@ -248,7 +272,6 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   const int Tn = s.m + s.Bn;
   if (j0 >= Tn) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
-  const bool for_v = w < 4;
   const int wj = j0 + 32 * (w & 3), j = wj + l31;             // this lane's position in [cache ; block]
   const int first = j0 >= s.m ? (j0 - s.m) / 64 : 0;          // tiles of rows before it see none of the keys
   const int rtiles = (s.Bn + 63) / 64 - first, N = a.group * rtiles;
@@ -279,6 +302,9 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
     if (it < N && tid < 192) st_lds[(it & 1) * 192 + tid] = stat;
   };
   request(0);
+  // either kind of wave has the loop to itself (the registers of one do not count against the other)
+  auto run = [&](auto for_v_t) {
+  constexpr bool for_v = decltype(for_v_t)::value;
   // key (and value) fragments of this lane's position; positions past the end are computed from the last one and dropped
   bf16x8 fk[8], fv[8];
   {
@@ -293,13 +319,22 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) fv[ks] = *(const bf16x8*)(vp + ks * 16);
   }
-  TileAddr ad;
-  tile_addr(l, ad);
+  // (operand addresses of the other k steps and column blocks are these, xor a constant: registers are short here)
+  int row0, tr0[2];
+  {
+    TileAddr ad;
+    tile_addr(l, ad);
+    row0 = ad.row[0];
+    tr0[0] = ad.tr[0][0];
+    tr0[1] = ad.tr[0][1];
+  }
   const float c = a.scale * kLog2e;
   f32x16 acc[4];
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) acc[ct] = zero16();
   wait_loads<0>();
+  landed(fk);
+  if (!for_v) landed(fv);
   publish_stats(0);
   __syncthreads();
 
@@ -313,18 +348,30 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
       const int rb = r0 + h * 32;
       if (rb >= s.Bn || (wj >= s.m && rb + 31 < wj - s.m)) continue;      // no row of this half sees these keys
       const unsigned char* q0 = Q + h * 32 * 256;
+      // N products of one accumulator, their operands read two ahead (left alone the compiler reads each right before its
+      // product and waits for it)
+      auto chain = [&](auto n_t, auto read, const bf16x8 (&f)[8], f32x16& to) {
+        constexpr int N = decltype(n_t)::value;
+        bf16x8 ring[3];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ring[i] = read(i);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          if (i + 2 < N) ring[(i + 2) % 3] = read(i + 2);
+          __builtin_amdgcn_sched_barrier(0);
+          to = mfma32(ring[i % 3], f[i % 8], to);
+        }
+      };
       f32x16 sc = zero16();
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) sc = mfma32(*(const bf16x8*)(q0 + ad.row[ks]), fk[ks], sc);
-      f32x4 mcs[4], inv[4];
-#pragma unroll
-      for (int gi = 0; gi < 4; ++gi) {
-        mcs[gi] = *(const f32x4*)(st + h * 32 + gi * 8);
-        inv[gi] = *(const f32x4*)(st + 64 + h * 32 + gi * 8);
-      }
+      chain(std::integral_constant<int, 8>{}, [&](int i) { return *(const bf16x8*)(q0 + (row0 ^ (i << 5))); }, fk, sc);
+      __builtin_amdgcn_sched_barrier(0);
       float p[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], c, -mcs[i >> 2][i & 3])) * inv[i >> 2][i & 3];
+      for (int gi = 0; gi < 4; ++gi) {
+        const f32x4 mcs = *(const f32x4*)(st + h * 32 + gi * 8), inv = *(const f32x4*)(st + 64 + h * 32 + gi * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[gi * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sc[gi * 4 + e], c, -mcs[e])) * inv[e];
+      }
       auto hide = [&]() {                   // pairs of a key and a query that does not see it
         if (rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m)) {
 #pragma unroll
@@ -342,21 +389,21 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
           split_parts<PARTS>(p + 8 * s2, fp);
           const unsigned char* o0 = q0 + kTile + s2 * 16 * 256;
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct)
+          for (int u = 0; u < PARTS; ++u) {
+            bf16x8 fo[4];
 #pragma unroll
-            for (int u = 0; u < PARTS; ++u) {
-              const bf16x8 fo = frag_tr(o0 + u * kTile + ad.tr[ct][0], o0 + u * kTile + ad.tr[ct][1]);
+            for (int ct = 0; ct < 4; ++ct) fo[ct] = frag_tr(o0 + u * kTile + (tr0[0] ^ (ct << 6)), o0 + u * kTile + (tr0[1] ^ (ct << 6)));
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-              for (int v = 0; u + v < PARTS; ++v) acc[ct] = mfma32(fo, fp[v], acc[ct]);
-            }
+            for (int v = 0; u + v < PARTS; ++v)
+#pragma unroll
+              for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma32(fo[ct], fp[v], acc[ct]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       } else {
         f32x16 dp = zero16();
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-#pragma unroll
-          for (int u = 0; u < PARTS; ++u) dp = mfma32(*(const bf16x8*)(q0 + (1 + u) * kTile + ad.row[ks]), fv[ks], dp);
-        }
+        chain(std::integral_constant<int, 8 * PARTS>{}, [&](int i) { return *(const bf16x8*)(q0 + (1 + i / 8) * kTile + (row0 ^ (i % 8 << 5))); }, fv, dp);
 #pragma unroll
         for (int gi = 0; gi < 4; ++gi) {
           const f32x4 dd = *(const f32x4*)(st + 128 + h * 32 + gi * 8);
@@ -369,12 +416,15 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
           bf16x8 fd[PARTS];
           split_parts<PARTS>(p + 8 * s2, fd);
           const unsigned char* t0 = q0 + s2 * 16 * 256;
+          bf16x8 qf[4];
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct) {
-            const bf16x8 qf = frag_tr(t0 + ad.tr[ct][0], t0 + ad.tr[ct][1]);
+          for (int ct = 0; ct < 4; ++ct) qf[ct] = frag_tr(t0 + (tr0[0] ^ (ct << 6)), t0 + (tr0[1] ^ (ct << 6)));
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < PARTS; ++u) acc[ct] = mfma32(qf, fd[u], acc[ct]);
-          }
+          for (int u = 0; u < PARTS; ++u)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma32(qf[ct], fd[u], acc[ct]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -392,6 +442,9 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
       for (int gi = 0; gi < 4; ++gi)
         *(f32x4_any*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
   }
+  };
+  if (w < 4) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 }  // namespace
