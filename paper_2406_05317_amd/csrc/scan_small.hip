@@ -8,10 +8,10 @@
 // whole chain fits one workgroup (filters included) the steps of a scan therefore run in ONE launch, the cache
 // rows staying in LDS from step to step; otherwise each step is one launch of a workgroup per 16 slots.
 // Measured on that smallest scan (15 compressions): 1209 us with three kernels per step and one attention launch per
-// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 81 us here, of which the scan 70: 9 900 cycles a
-// step, 2 800 of them Eq. 5 and 2 000 Eq. 6 (12 900 before operand reads were issued in groups ahead of their products,
-// reductions left the LDS crossbar and divisions the index arithmetic; 104 us in all).  Drawn scans of one to four heads of
-// 64, 12 - 96 slots: 1.13 - 1.39 times as fast as before that.
+// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 71 us here.  Before operand reads were issued in groups
+// ahead of their products, reductions left the LDS crossbar, divisions the index arithmetic and row strides became constants
+// for head_dim 64 it was 104 us, 12 900 cycles a step.  Drawn scans of one to four heads of 64, 12 - 96 slots: 1.24 - 1.55
+// times as fast as before that.
 #include <algorithm>
 #include <type_traits>
 
@@ -70,7 +70,7 @@ constexpr int kLds = 160 * 1024;
 
 // Row strides are a multiple of 4 floats that is an odd multiple of 4: the 16 rows x 4 columns one operand
 // read touches then fall on 64 different banks.
-__host__ __device__ inline int odd4(int n) {
+__host__ __device__ constexpr int odd4(int n) {
   const int q = (n + 3) / 4;
   return 4 * (q | 1);
 }
@@ -120,8 +120,8 @@ struct SmallArgs {
 };
 
 // One workgroup: 16 l.tiles slots of one chain.  n_steps > 1 only where those are all slots of the chain.
-// MIX: 16 x 16 tiles of Eq. 4 per wave.  D: head_dim where it is a constant (0: any).
-template <typename T, int MIX, int D>
+// MIX: 16 x 16 tiles of Eq. 4 per wave.  D: head_dim where it is a constant (0: any), and then CIN: filters over [K | V].
+template <typename T, int MIX, int D, int CIN>
 __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   extern __shared__ __align__(16) float sm[];
   const StepArgs& a = g.st;
@@ -132,13 +132,14 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   float* Ws = sm + L.off_w;
   int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l15 = l & 15, lk = l >> 4;
   const int ch = blockIdx.y, b = ch / a.Hkv, hkv = ch % a.Hkv, i0 = blockIdx.x * 16 * L.tiles;
-  const int d = D ? D : a.d, C = a.conv_in ? 2 * d : d, C4 = (C + 3) / 4, k = a.k_width, pad = (k - 1) / 2, M = a.M;
+  const int d = D ? D : a.d, C = (D ? CIN : a.conv_in) ? 2 * d : d, C4 = (C + 3) / 4, k = a.k_width, pad = (k - 1) / 2, M = a.M;
+  const int sx = D ? odd4(C) : L.sx, sv = D ? (CIN ? 0 : odd4(d)) : L.sv;
   const T* wbase = (const T*)a.conv_w + hkv * a.w_head_stride;
   const T* bias = a.conv_b ? (const T*)a.conv_b + hkv * a.b_head_stride : nullptr;
   const uint32_t* protect = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
 
   // where column c of the value row / key row of position j lives
-  auto yv = [&](int j) -> float* { return L.sv ? Vs + j * L.sv : Xs + (pad + j) * L.sx + d; };
+  auto yv = [&](int j) -> float* { return sv ? Vs + j * sv : Xs + (pad + j) * sx + d; };
   auto load_filters = [&](int t0, int nt) {       // [tile][tap][channel (padded to 4)][slot]
     for (int st = 0; st < L.tiles; ++st) {
       const int i = i0 + st * 16 + (tid & 15);
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
     const T* cv = (const T*)a.cache_v + (int64_t)ch * M * d;
     for (int e = tid; e < (m + Bn) * d; e += kNT) {
       const int j = e / d, c = e % d;
-      Xs[(pad + j) * L.sx + c] = to_f(j < m ? ck[e] : kb[(int64_t)(j - m) * a.k.st + c]);
+      Xs[(pad + j) * sx + c] = to_f(j < m ? ck[e] : kb[(int64_t)(j - m) * a.k.st + c]);
       yv(j)[c] = to_f(j < m ? cv[e] : vb[(int64_t)(j - m) * a.v.st + c]);
     }
   }
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
         // this part's channels, tap by tap: the order of the sum does not depend on how the taps are brought in
         const int k0 = C4 * part >> log_planes, k1 = C4 * (part + 1) >> log_planes;
         const float* wb = Ws + (st * L.taps * C4 * 4 + lk) * 16 + l15 + k0 * 64;
-        const float* xb = Xs + (p0 + l15 + t0) * L.sx + lk + 4 * k0;
+        const float* xb = Xs + (p0 + l15 + t0) * sx + lk + 4 * k0;
         // KN channel groups at a time, TN taps of them in flight together: a wave's operand reads are what it waits for
         auto taps = [&](auto kn, auto tn, auto rect) {
           constexpr int KN = decltype(kn)::value, TN = decltype(tn)::value;
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
               for (int q = 0; q < KN; ++q) {
                 fb[t][q] = wb[(t * C4 + kc + q) * 64];
 #pragma unroll
-                for (int x = 0; x < kPG; ++x) fa[t][q][x] = xb[(16 * x + t) * L.sx + 4 * (kc + q)];
+                for (int x = 0; x < kPG; ++x) fa[t][q][x] = xb[(16 * x + t) * sx + 4 * (kc + q)];
               }
 #pragma unroll
             for (int t = 0; t < N; ++t)
@@ -236,9 +237,9 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
           int t = 0;
           if (TN > 1)
 #pragma clang loop unroll(disable)
-            for (; t + TN <= nt; t += TN, wb += TN * C4 * 64, xb += TN * L.sx) some(tn, 0);
+            for (; t + TN <= nt; t += TN, wb += TN * C4 * 64, xb += TN * sx) some(tn, 0);
 #pragma clang loop unroll(disable)
-          for (; t < nt; ++t, wb += C4 * 64, xb += L.sx)
+          for (; t < nt; ++t, wb += C4 * 64, xb += sx)
 #pragma clang loop unroll(disable)
             for (int kc = 0; kc < k1 - k0; kc += KN) some(std::integral_constant<int, 1>{}, kc);
         };
@@ -303,9 +304,9 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
         const int st = small_div(u, 2 * ct), cu = u - st * 2 * ct;
         const bool val = cu >= ct;
         const int c = (val ? cu - ct : cu) * 16 + l15;
-        const int stride = val && L.sv ? L.sv : L.sx;
+        const int stride = val && sv ? sv : sx;
         const float* wr = Ls + (st * 16 + l15) * sl + lk;
-        const float* yr = (val ? yv(0) : Xs + pad * L.sx) + lk * stride + (c < d ? c : 0);   // a column past d is dropped
+        const float* yr = (val ? yv(0) : Xs + pad * sx) + lk * stride + (c < d ? c : 0);   // a column past d is dropped
         int kk = 0;
 #pragma clang loop unroll(disable)
         for (; kk + 8 <= k4; kk += 8, wr += 32, yr += 32 * stride) {    // eight groups of operands in flight
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
       for (int e = 0; e < 4; ++e) {
         const int i = i0 + st * 16 + lk * 4 + e;
         if (i >= M) continue;
-        float* row = val ? yv(i) : Xs + (pad + i) * L.sx;
+        float* row = val ? yv(i) : Xs + (pad + i) * sx;
         float v = acc[n][e];
         if (protect && i < m && ((protect[i >> 5] >> (i & 31)) & 1u)) v = row[c];   // carried over unchanged
         v = store_f(v, (val ? ov : ok) + (int64_t)i * d + c);
@@ -354,17 +355,17 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
       if (n * kNT >= Bnext * d) break;
       const int e = tid + n * kNT;
       if (e < Bnext * d) {
-        Xs[(pad + M + e / d) * L.sx + e % d] = pk[n];
+        Xs[(pad + M + e / d) * sx + e % d] = pk[n];
         yv(M + e / d)[e % d] = pv[n];
       }
     }
     for (int e = tid + kPF * kNT; e < Bnext * d; e += kNT) {
       const int64_t tok = next_tok + e / d;
-      Xs[(pad + M + e / d) * L.sx + e % d] = to_f(kb[tok * a.k.st + e % d]);
+      Xs[(pad + M + e / d) * sx + e % d] = to_f(kb[tok * a.k.st + e % d]);
       yv(M + e / d)[e % d] = to_f(vb[tok * a.v.st + e % d]);
     }
     for (int e = tid + (M + Bnext) * d; e < Tn * d; e += kNT) {
-      Xs[(pad + e / d) * L.sx + e % d] = 0.f;
+      Xs[(pad + e / d) * sx + e % d] = 0.f;
       yv(e / d)[e % d] = 0.f;
     }
     m = M;
@@ -470,22 +471,23 @@ int taps_that_fit(int T, int d, int k, int conv_in) {
   return 0;
 }
 
-template <typename T, int MIX, int D>
+template <typename T, int MIX, int D, int CIN>
 hipError_t launch_d(const SmallArgs& g, int grid_x, hipStream_t s) {
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)compress_small_k<T, MIX, D>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    hipError_t e = hipFuncSetAttribute((const void*)compress_small_k<T, MIX, D, CIN>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((compress_small_k<T, MIX, D>), dim3(grid_x, g.st.batch * g.st.Hkv), dim3(kNT), g.l.bytes, s, g);
+  hipLaunchKernelGGL((compress_small_k<T, MIX, D, CIN>), dim3(grid_x, g.st.batch * g.st.Hkv), dim3(kNT), g.l.bytes, s, g);
   return hipGetLastError();
 }
 // A step of the smallest scans is a few hundred cycles of dependent work in each of its passes: indices that need a division by
-// the head_dim are a good part of it, so the one these scans are used with has a build of its own.
+// the head_dim or a product with a row stride are a good part of it, so the one these scans are used with has builds of its own.
 template <typename T, int MIX>
 hipError_t launch(const SmallArgs& g, int grid_x, hipStream_t s) {
-  return g.st.d == 64 ? launch_d<T, MIX, 64>(g, grid_x, s) : launch_d<T, MIX, 0>(g, grid_x, s);
+  if (g.st.d != 64) return launch_d<T, MIX, 0, 0>(g, grid_x, s);
+  return g.st.conv_in ? launch_d<T, MIX, 64, 1>(g, grid_x, s) : launch_d<T, MIX, 64, 0>(g, grid_x, s);
 }
 
 }  // namespace
