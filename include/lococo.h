@@ -370,7 +370,8 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *     acc  d_conv_w, d_conv_b: ADDED to, as in the step (d_conv_b may be NULL).
  *     d_q may be the array d_o came in, d_cache0_k / d_cache0_v those of d_final_k / d_final_v.
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
- *   states per block (storage type), one step's worth of everything else and about 3 GiB at most for the window.
+ *   states per block (storage type), one step's worth of everything else, about 3 GiB at most for the window, and
+ *   the logits of all blocks where the recomputed scan can leave them and they take 8 GiB at most.
  *   With less the window is as many blocks as fit; LOCOCO_EWORKSPACE, and the least there has to be in
  *   lococo_last_error(), where one does not.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */

@@ -7,7 +7,7 @@
 //   dW[i, c, t] += sum_j dl[i, j] X[j + t - p, c]                                   (Eq. 5 w.r.t. the filters)
 //
 // Only g has to wait for the walk, and of dX only the rows of the cache are what the walk hands on.  So the logits of all
-// blocks come from one launch ahead of the walk (tiled_mfma.hip), a step of the walk is two launches (bwd_rows_k, bwd_dx_k
+// blocks come from the recomputed scan, or from one launch ahead of the walk (tiled_mfma.hip), a step of the walk is two launches (bwd_rows_k, bwd_dx_k
 // over the cache rows), and the rows of the blocks and the filter gradient follow in one launch each for the whole window.
 //
 // g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  In a
@@ -415,8 +415,10 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // sums meet in LDS at the end.  No two waves want the same filters, so these come from memory straight into the registers,
 // packed in fragment order, D taps ahead: within a phase there is nothing to meet for, and only the plane rows (which the
 // taps read at shifted rows) pass through LDS, by loads that write it directly, a phase or more ahead.  Rows outside the
-// sequence read as zero (buffer bounds).  (Filters through LDS, two taps a barrier: requests, fragment reads and products
-// were a chain that the two waves of a SIMD overlapped in part.)
+// sequence read as zero (buffer bounds).  145 us a step of 32 chains, 512 slots and 1024 positions (155 GFLOP), 11.5 us for the
+// cache rows at 128 slots (161 and 16.4 with the filters through LDS, two taps a barrier: requests, fragment reads and products
+// were a chain that the two waves of a SIMD overlapped in part).  Without the filter loads 131, without the LDS reads 133 us;
+// the value columns' workgroups, which follow the key columns', take 20 of it and the sums 6.
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
 // FINE: the blocks whose n and g enter in three parts.
 template <int PT, int NC, int KS, bool FINE>
@@ -955,7 +957,9 @@ hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_
 
 template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  // the largest tile of which there is one for every compute unit
+  // The largest tile of which there is one for every compute unit (32 chains, 512 slots on 1024 positions: 147 us with 128 rows,
+  // 164 with 64); 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole
+  // 15.0).
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
   if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
   if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
