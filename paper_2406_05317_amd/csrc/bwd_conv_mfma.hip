@@ -428,7 +428,7 @@ struct Dx {
   static constexpr int DB = PL * DR * 128, NB = PL * PT * 128;           // bytes of a chunk's rows of dl, of n
   static constexpr int ND = DB / 8192, NN = NB / 8192;                   // requests of a wave for them
   static constexpr int D = 3;                                            // taps of filters in flight (a divisor of 15 and 21)
-  static constexpr int RR = PB * CB >= 8 ? 64 : 32;                      // registers of a wave summed up at a time
+  static constexpr int RR = PB * CB >= 8 ? 64 : PB * CB >= 2 ? 32 : 16;  // registers of a wave summed up at a time
   static constexpr int rings = 2 * DB + (FINE ? 2 : 1) * NB, sums = 8 * RR * 256;
   static constexpr int lds = rings > sums ? rings : sums;
   static_assert(DB % 8192 == 0 && NB % 8192 == 0, "whole requests");
@@ -959,12 +959,15 @@ template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   // The largest tile of which there is one for every compute unit (32 chains, 512 slots on 1024 positions: 147 us with 128 rows,
   // 164 with 64); 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole
-  // 15.0).
+  // 15.0).  With 32 rows the slots go eight ways, but no more ways than there are slots for: up to 64 of them fill half of the
+  // waves or fewer, and the columns take the other factor of two (a step's pass, 64 chains of 64 slots and 64 tokens, 31 taps:
+  // 142.7 -> 133.5 us; from 80 slots on eight ways are up to 2 % faster at 4 - 32 chains, as often slower as faster at 64).
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
   if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
   if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, 8, FINE>(g, blk0, n_blk, part, rows, s);
-  return launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 31) / 32) >= cu_count())
+    return g.st.M <= 64 ? launch_dx<32, 128, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 128, 8, FINE>(g, blk0, n_blk, part, rows, s);
+  return g.st.M <= 64 ? launch_dx<32, 64, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
 }
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;

@@ -31,6 +31,11 @@ def _rel(a, b):
     dict(batch=1, n_kv_heads=2, M=130, B=62, conv_in=1, conv_width=21),            # [K | V] filters: taps on both halves
     dict(batch=2, n_kv_heads=32, M=128, B=384, conv_in=1),                         # the same with 128 rows
     dict(batch=1, n_kv_heads=2, M=16, B=8, conv_width=1),                          # the smallest: sixteen slots, one tap
+    # (32 rows: the slots in four parts up to 64 of them, in eight from there on)
+    dict(batch=1, n_kv_heads=2, M=64, B=1, conv_width=5),                          # halves in three parts, four parts of slots
+    dict(batch=1, n_kv_heads=3, M=64, B=60, conv_in=1, conv_width=31),             # halves
+    dict(batch=2, n_kv_heads=32, M=49, B=63, conv_width=15),                       # whole, a slot past 48
+    dict(batch=1, n_kv_heads=2, M=65, B=7, conv_width=21),                         # halves, the first with eight parts
 ], ids=str)
 def test_input_and_filter_gradients_at_tile_edges(case):
     """Against the shape-agnostic fp32 kernels, which agree with the oracle to 3e-7.  g, n and dl keep 16 bits where they enter
