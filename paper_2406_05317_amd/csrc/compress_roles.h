@@ -8,11 +8,17 @@
 //                           one tile after the other, leaving their partial sums in LDS;
 //   mixing waves (4 .. 7)   stage the tiles, add up the partial logits, run the softmax and mix, 64 columns of [K | V] each.
 // In stage i the logit waves work on tile i + 1 and the mixing waves on the softmax of tile i and the mixing of tile i - 1;
-// partial logits, probabilities and rescale factors are double-buffered, so one barrier ends a stage.  No wave needs more
-// than 256 registers.  What bounds a stage now is LDS, some 1 760 cycles of operand reads, partial logits and staging.
-// Measured: the compressor as printed, 3.5 K tokens of 32 heads, M = 128: 705 -> 522 us; 77 tokens on a cache of 256, 8 kv
-// heads: 18.9 -> 16.7 us; one token of 32 heads on 128 slots: 11.9 -> 11.2 us.  Scans with filters over the keys stay with
-// compress_mfma_k, whose stages take as long there (3.5 K tokens: 312 against 316 us) and whose prologue is shorter.
+// partial logits, probabilities and rescale factors are double-buffered, so one barrier ends a stage.  A wave has 256 registers;
+// builds without protected slots keep everything in them, but for those that share out the positions of a step.  What bounds a
+// stage now is LDS, some 1 760 cycles of operand reads, partial logits and staging.
+// Measured against one role, whole calls, width 21 over [K | V] with 32 heads: the compressor as printed, 3.5 K tokens, M = 128:
+// 723 -> 559 us.  Where every (chain, slot tile) has one workgroup to itself, 3.5 K tokens, M = 256: 664 -> 637 us, one token
+// 36.7 -> 33.5, 77 tokens 47.3 -> 43.7.  Several chains per workgroup: 4 x 2 K tokens, M = 128: 861 -> 825 us; 4 K tokens,
+// M = 512: 1322 -> 1269; 8 x 33 tokens, M = 128: 83.1 -> 80.4.  54 such shapes, widths 15 and 21, with and without protected
+// slots: 1.02 - 1.37 times as fast.
+// Filters over the keys, single steps: 77 tokens on a cache of 256, 8 kv heads: 18.9 -> 16.7 us; one token of 32
+// heads on 128 slots: 11.9 -> 11.2 us.  Scans with filters over the keys stay with compress_mfma_k, whose stages take as long there
+// (3.5 K tokens: 312 against 316 us) and whose prologue is shorter.
 #pragma once
 
 #include "compress_tile.h"
@@ -36,6 +42,11 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
   using G = Geo<BM, KW>;
   static_assert(!SPLIT || !MULTI, "the splits are built for one chain per workgroup");
   constexpr bool PSPLIT = SPLIT == 1, PIPE = SPLIT == 2;
+  // Who stages key tile 0 of a walk.  With the loops over passes and chains of a workgroup that has its tile to itself, the logit
+  // waves of width 21 (168 registers of filters) had no room for the tile's addresses: they came back from scratch memory in
+  // front of every walk.  The mixing waves have the room, and request it with tiles 1 - 3, under the logit waves' filter load.
+  // (one token of four sequences, M = 128, width 21: 42.2 -> 39.5 us; 4 x 2 K tokens: 864 -> 840; M = 512: 1278 -> 1274)
+  constexpr bool kMixersStageAll = SPLIT == 0;
   const StepArgs& a = sa.st;
   unsigned char* Xs0 = smem;                                    // NXBUF key tiles (with halo)
   unsigned char* Vs0 = Xs0 + G::NXBUF * G::XBYTES;              // NVBUF value tiles
@@ -382,12 +393,16 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
   // ends a stage: what was written to LDS is there (loads on their way stay on their way)
   auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-  // a walk over tiles 0 .. NT - 1 of the range at hand.  Key tiles 0 (by the logit waves), 1 and 2 are staged first, all loads
+  // a walk over tiles 0 .. NT - 1 of the range at hand.  Key tiles 0 (by either kind of wave), 1 and 2 are staged first, all loads
   // issued before the first store; key tile 3 and value tile 0 are on their way.
   auto walk = [&](auto ph_t) {
     constexpr int PH = decltype(ph_t)::value;
     if constexpr (MIX) {
-      Cat16 x1[G::XPER], x2[G::XPER];
+      Cat16 x0[kMixersStageAll ? G::XPER : 1], x1[G::XPER], x2[G::XPER];
+      if constexpr (kMixersStageAll) {
+#pragma unroll
+        for (int it = 0; it < G::XPER; ++it) x0[it] = x_chunk(it, jbase);
+      }
 #pragma unroll
       for (int it = 0; it < G::XPER; ++it) x1[it] = x_chunk(it, jbase + BN);
 #pragma unroll
@@ -399,11 +414,15 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
 #pragma unroll
         for (int it = 0; it < G::VPER; ++it) load_v(it, jbase);
       }
+      if constexpr (kMixersStageAll) {
+#pragma unroll
+        for (int it = 0; it < G::XPER; ++it) put_x(it, Xs0, x0[it]);
+      }
 #pragma unroll
       for (int it = 0; it < G::XPER; ++it) put_x(it, Xs0 + G::XBYTES, x1[it]);
 #pragma unroll
       for (int it = 0; it < G::XPER; ++it) put_x(it, Xs0 + 2 * G::XBYTES, x2[it]);
-    } else {
+    } else if constexpr (!kMixersStageAll) {
       Cat16 x0[G::XPER];
 #pragma unroll
       for (int it = 0; it < G::XPER; ++it) x0[it] = x_chunk(it, jbase);

@@ -1,0 +1,38 @@
+"""Registers of the two-role compression kernel, as the compiler reports them (CPU: nothing is run).  A SIMD holds a wave of
+either role, 256 registers each.  A build that wants more keeps the rest in scratch memory: the logit waves of width 21 then read
+addresses back in front of every walk, 1 % of a step of several chains."""
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2406_05317_amd import build as lib_build
+
+TEXT = """#include "compress_roles.h"
+using namespace lococo;
+using namespace lococo::compress_detail;
+template <int KW, int NORM, int PROT, int MULTI, int SPLIT, int CIN>
+__global__ __launch_bounds__(kRoleThreads, 2) void roles_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  compress_roles<KW, NORM, PROT, MULTI, SPLIT, CIN>(sa, wp, wp_head_stride, smem, blockIdx.x, gridDim.x);
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_builds_without_protected_slots_keep_everything_in_registers(tmp_path):
+    # one workgroup per (chain, slot tile); several chains per workgroup; pairs that take the steps in turn, filters over
+    # [K | V] and over the keys
+    builds = [(kw, 1, 0, *form) for kw in (15, 21) for form in ((0, 0, 1), (1, 0, 1), (0, 2, 1), (0, 2, 0))]
+    src = tmp_path / "roles.hip"
+    src.write_text(TEXT + "".join(f"template __global__ void roles_k<{', '.join(map(str, b))}>(ScanArgs, const uint16_t*, int64_t);\n"
+                                  for b in builds))
+    r = subprocess.run(["hipcc", "-x", "hip", *lib_build.FLAGS, *lib_build.COMPRESS, "--cuda-device-only", "-c", str(src), "-o",
+                        str(tmp_path / "roles.o"), "-Rpass-analysis=kernel-resource-usage"],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    names = re.findall(r"Function Name: (\S+)", r.stderr)
+    spilled = [int(n) for n in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
+    assert len(names) == len(spilled) == len(builds)
+    assert not any(spilled), dict(zip(names, spilled))
