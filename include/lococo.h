@@ -334,7 +334,9 @@ LOCOCO_API lococo_status lococo_mix_from_logits(const lococo_config* cfg, const 
  *          (rows that were not live are zero); all five are overwritten;
  *     acc  d_conv_w (laid out like conv_w, with w_head_stride) and d_conv_b (like conv_b, may be
  *          NULL) are ADDED to, so one buffer collects the whole scan; untouched by a fill step.
- *   workspace: lococo_backward_workspace_bytes(cfg, B, cache_before->len) bytes, 256-byte aligned.
+ *   workspace: lococo_backward_workspace_bytes(cfg, B, cache_before->len) bytes, 256-byte aligned.  With less, down to what
+ *   lococo_last_error() names when it is refused (LOCOCO_EWORKSPACE), the two orders the filters are packed in share one
+ *   place: the same gradients, a launch more.
  * Any shape; fp32 vector arithmetic, except that with bf16 storage and cfg->impl !=
  * LOCOCO_IMPL_GENERIC the contractions run on the matrix cores: the attention's with head_dim 128, the others with a filter
  * width up to 31 as well.  Every fp32 operand enters as the sum of two bf16 numbers (about 16 bits kept) where block length +
@@ -372,8 +374,8 @@ LOCOCO_API lococo_status lococo_segment_step_backward(const lococo_config* cfg, 
  *   workspace: lococo_sequence_backward_workspace_bytes(cfg, L, B) bytes, 256-byte aligned: two
  *   states per block (storage type), one step's worth of everything else, about 3 GiB at most for the window, and
  *   the logits of all blocks where the recomputed scan can leave them and they take 8 GiB at most.
- *   With less the window is as many blocks as fit; LOCOCO_EWORKSPACE, and the least there has to be in
- *   lococo_last_error(), where one does not.
+ *   With less the window is as many blocks as fit, at the last with one place for the filters as in the step;
+ *   LOCOCO_EWORKSPACE, and the least there has to be in lococo_last_error(), where one block does not.
  * LOCOCO_FLAG_FILTERS_PREPARED is refused (the call owns its workspaces); norm = 2 is forward only. */
 LOCOCO_API lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg, int64_t L, int32_t B,
                                                                   size_t* out);

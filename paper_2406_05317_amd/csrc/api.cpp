@@ -1108,11 +1108,13 @@ size_t bwd_attn_hl_bytes(const lococo_config* c, int64_t rows) {
 size_t bwd_attn_stat_bytes(const lococo_config* c, int64_t rows) {
   return align_up((size_t)c->batch * c->n_q_heads * (size_t)rows * 3 * sizeof(float), 256);
 }
-struct BwdLayout { size_t p, ds, w, n, dw, conv, total; };
-BwdConvLayout conv_layout(const lococo_config* c, int32_t T, int64_t n_blk, bool with_logits = true) {
-  return bwd_conv_layout(c->batch, c->n_kv_heads, c->M, T, c->conv_width, c->conv_in, filter_banks(c), n_blk, with_logits);
+struct BwdLayout { size_t p, ds, w, n, dw, conv, total; bool one_filters; };
+BwdConvLayout conv_layout(const lococo_config* c, int32_t T, int64_t n_blk, bool one_filters, bool with_logits = true) {
+  return bwd_conv_layout(c->batch, c->n_kv_heads, c->M, T, c->conv_width, c->conv_in, filter_banks(c), n_blk, with_logits, one_filters);
 }
-BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
+// one_filters: the least memory a step can do with.  The filters are packed in two orders, for Eq. 5 and for its input gradient;
+// with one place for both a step packs them in a launch more.
+BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len, bool one_filters) {
   const size_t T = (size_t)len + B;
   const size_t rows = (size_t)c->batch * c->n_q_heads * B * T * sizeof(float);
   const bool compress = len + B > c->M, conv = compress && bwd_on_mfma(c);
@@ -1124,7 +1126,8 @@ BwdLayout bwd_layout(const lococo_config* c, int32_t B, int32_t len) {
   l.n = l.w + mat;
   l.dw = l.n + mat;
   l.conv = 0;                                  // Eq. 4 - 6 on MFMA come when the attention is done with its arrays
-  l.total = std::max(l.dw + mat, conv ? conv_layout(c, (int32_t)T, 1).total : (size_t)0);
+  l.total = std::max(l.dw + mat, conv ? conv_layout(c, (int32_t)T, 1, one_filters).total : (size_t)0);
+  l.one_filters = one_filters;
   return l;
 }
 // The attention of the blocks of `t` (see BwdAttnArgs; the gradient arrays hold `rows` query / block rows per head from
@@ -1175,7 +1178,7 @@ lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool co
   c.kv_chain = g.kv_chain;
   c.d_conv_w = g.d_conv_w;
   c.d_conv_b = g.d_conv_b;
-  bwd_conv_place(&c, conv_layout(cfg, T, 1), ws + l.conv);
+  bwd_conv_place(&c, conv_layout(cfg, T, 1, l.one_filters), ws + l.conv);
   HIP_TRY(launch_bwd_conv_begin(c, true, s), "filter packing launches");
   HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
   HIP_TRY(launch_bwd_conv_rows(c, 0, T, s), "row gradient launch");
@@ -1191,7 +1194,7 @@ lococo_status lococo_backward_workspace_bytes(const lococo_config* cfg, int32_t 
   if ((st = check_config(cfg))) return st;
   if (!out) return fail(LOCOCO_EINVAL, "out is NULL");
   if (B <= 0 || len < 0 || len > cfg->M) return fail(LOCOCO_EINVAL, "B must be positive and len in [0, M]");
-  *out = bwd_layout(cfg, B, len).total;
+  *out = bwd_layout(cfg, B, len, false).total;
   return LOCOCO_OK;
 }
 
@@ -1216,7 +1219,8 @@ lococo_status lococo_segment_step_backward(const lococo_config* cfg, const lococ
   const bool compress = cache_before->len + B > cfg->M;
   if (compress && (!conv_w || !d_conv_w))
     return fail(LOCOCO_EINVAL, "conv_w or d_conv_w is NULL but the step compresses");
-  const BwdLayout l = bwd_layout(cfg, B, cache_before->len);
+  BwdLayout l = bwd_layout(cfg, B, cache_before->len, false);
+  if (ws_bytes < l.total) l = bwd_layout(cfg, B, cache_before->len, true);
   if (!workspace || ws_bytes < l.total || ((uintptr_t)workspace & 255))
     return fail(LOCOCO_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)", l.total,
                 workspace ? ws_bytes : (size_t)0);
@@ -1296,6 +1300,7 @@ struct SeqBwdLayout {
   size_t d_ck, d_cv, slot;            // gradients w.r.t. the state before each of them, fp32, `slot` bytes each
   size_t hl, stats;       // scratch of the attention launches
   BwdConvLayout conv;     // of Eq. 4 - 6 (inside step_ws)
+  bool one_filters;       // see bwd_layout
   bool keep_logits;       // the logits of all blocks have a place, `logits`: the recomputed scan leaves them there
   size_t logits;
   size_t d_o;             // a block's upstream gradient where the walk needs a copy of it (no windows)
@@ -1310,9 +1315,12 @@ constexpr size_t kBwdWindowBytes = (size_t)3 << 30;
 // longer computes them window by window.  Keeping them takes Eq. 5 out of the pass once: 3.75 of 32.5 ms on that sequence.
 constexpr size_t kBwdLogitsBytes = (size_t)8 << 30;
 
-// largest_window: blocks a window may have at most; keep: whether the logits of all blocks may have a place
-lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64_t largest_window, bool keep, SeqBwdLayout* out) {
+// largest_window: blocks a window may have at most; keep: whether the logits of all blocks may have a place; one_filters: see
+// bwd_layout
+lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64_t largest_window, bool keep, bool one_filters,
+                             SeqBwdLayout* out) {
   SeqBwdLayout l{};
+  l.one_filters = one_filters;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += align_up(bytes, 256); return here; };
   const size_t chains = (size_t)c->batch * c->n_kv_heads, es = esize(c->dtype);
@@ -1326,18 +1334,17 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64
   if (path == PATH_MFMA && bwd_on_mfma(c) && bwd_attn_has_mfma(c) && n > 1) {
     const int split = compress_position_split(c->batch, c->n_kv_heads, c->M, c->conv_width, c->conv_in, cu_count());
     l.keep_logits = keep && compress_scan_leaves_logits(false, c->conv_in, split > 1) &&
-                    conv_layout(c, c->M + B, 1).logits_stride * 4 <= kBwdLogitsBytes / (size_t)n;
+                    conv_layout(c, c->M + B, 1, one_filters).logits_stride * 4 <= kBwdLogitsBytes / (size_t)n;
   }
   const size_t n_states = (size_t)n + (l.keep_logits ? 1 : 0);   // (then the last block's own update is made as well)
   l.states_k = take(n_states * l.state);
   l.states_v = take(n_states * l.state);
   l.slot = align_up(chains * c->M * c->head_dim * sizeof(float), 256);
-  size_t step = 0;                    // a step's workspace grows with the occupancy: the full cache bounds all
-  if ((st = lococo_backward_workspace_bytes(c, B, c->M, &step))) return st;
+  size_t step = bwd_layout(c, B, c->M, one_filters).total;   // (grows with the occupancy: the full cache bounds all)
   if (bwd_attn_has_mfma(c)) {
     size_t per_block = 2 * l.slot + bwd_attn_hl_bytes(c, B) + bwd_attn_stat_bytes(c, B);
     if (bwd_on_mfma(c)) {
-      const BwdConvLayout one = conv_layout(c, c->M + B, 1, !l.keep_logits);
+      const BwdConvLayout one = conv_layout(c, c->M + B, 1, one_filters, !l.keep_logits);
       per_block += one.total - one.per_call;
     }
     // (blocks x chains and 4 x blocks are grid dimensions)
@@ -1348,7 +1355,7 @@ lococo_status seq_bwd_layout(const lococo_config* c, int64_t L, int32_t B, int64
     l.hl = take(bwd_attn_hl_bytes(c, l.window * (int64_t)B));
     l.stats = take(bwd_attn_stat_bytes(c, l.window * (int64_t)B));
     if (bwd_on_mfma(c)) {
-      l.conv = conv_layout(c, c->M + B, l.window, !l.keep_logits);
+      l.conv = conv_layout(c, c->M + B, l.window, one_filters, !l.keep_logits);
       if (l.keep_logits) l.logits = take((size_t)n * l.conv.logits_stride * 4);
       step = std::max(step, l.conv.total);
     }
@@ -1372,7 +1379,7 @@ lococo_status lococo_sequence_backward_workspace_bytes(const lococo_config* cfg,
   if (!out) return fail(LOCOCO_EINVAL, "out is NULL");
   if (L < 0 || B <= 0) return fail(LOCOCO_EINVAL, "need L >= 0 and B > 0");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, false, &l))) return st;
   *out = l.total;
   return LOCOCO_OK;
 }
@@ -1405,17 +1412,18 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   for (const auto& sg : plan) any_compress |= sg.branch == 1;
   if (any_compress && (!conv_w || !d_conv_w)) return fail(LOCOCO_EINVAL, "conv_w or d_conv_w is NULL but the scan compresses");
   SeqBwdLayout l;
-  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, &l))) return st;
-  if (ws_bytes < l.total && l.keep_logits && (st = seq_bwd_layout(cfg, L, B, INT64_MAX, false, &l))) return st;
+  if ((st = seq_bwd_layout(cfg, L, B, INT64_MAX, true, false, &l))) return st;
+  if (ws_bytes < l.total && l.keep_logits && (st = seq_bwd_layout(cfg, L, B, INT64_MAX, false, false, &l))) return st;
   if (ws_bytes < l.total && l.window > 1) {    // the largest window that fits (a layout's size grows with its window)
     int64_t fits = 1, not_fits = l.window;
     while (not_fits - fits > 1) {
       const int64_t mid = (fits + not_fits) / 2;
-      if ((st = seq_bwd_layout(cfg, L, B, mid, false, &l))) return st;
+      if ((st = seq_bwd_layout(cfg, L, B, mid, false, false, &l))) return st;
       (l.total <= ws_bytes ? fits : not_fits) = mid;
     }
-    if ((st = seq_bwd_layout(cfg, L, B, fits, false, &l))) return st;
+    if ((st = seq_bwd_layout(cfg, L, B, fits, false, false, &l))) return st;
   }
+  if (ws_bytes < l.total && (st = seq_bwd_layout(cfg, L, B, 1, false, true, &l))) return st;
   if (!workspace || ws_bytes < l.total || ((uintptr_t)workspace & 255))
     return fail(LOCOCO_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)", l.total,
                 workspace ? ws_bytes : (size_t)0);
@@ -1624,7 +1632,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
       }
       g.d_conv_w = d_conv_w;
       g.d_conv_b = d_conv_b;
-      if ((st = enqueue_step_backward(cfg, g, sg.branch == 1, bwd_layout(cfg, sg.len, sg.len_before), ws + l.step_ws, s))) return st;
+      if ((st = enqueue_step_backward(cfg, g, sg.branch == 1, bwd_layout(cfg, sg.len, sg.len_before, l.one_filters), ws + l.step_ws, s))) return st;
       gk = g.d_cache_k;
       gv = g.d_cache_v;
     }

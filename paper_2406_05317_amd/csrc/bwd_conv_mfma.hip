@@ -882,7 +882,8 @@ hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int ro
 
 }  // namespace
 
-BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits) {
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits,
+                              bool one_filters) {
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   const size_t chains = (size_t)batch * Hkv, C = conv_in ? 2 * kD : kD;
   BwdConvLayout l;
@@ -892,8 +893,9 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
   l.gsplit_stride = up(chains * ((M + 31) / 32 * 32) * 2 * kD * 2 * 3) / 2;
   size_t at = 0;
   auto take = [&](size_t bytes) { const size_t here = at; at += up(bytes); return here; };
-  l.wt = take((size_t)banks * conv_width * M * C * 2);
-  l.wf = take((size_t)banks * conv_width * ((M + 15) / 16 * 16) * C * 2);
+  const size_t wf_bytes = (size_t)banks * conv_width * ((M + 15) / 16 * 16) * C * 2;
+  l.wt = take(one_filters ? wf_bytes : (size_t)banks * conv_width * M * C * 2);
+  l.wf = one_filters ? l.wt : take(wf_bytes);
   l.zero_page = take(256);
   l.dwt = take((size_t)banks * conv_width * M * C * 4);
   l.per_call = at;
@@ -927,14 +929,15 @@ void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
 hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s) {
   const StepArgs& a = g.st;
   const size_t n = (size_t)g.banks * a.k_width * a.M * (a.conv_in ? 2 * kD : kD);
-  if (for_logits) {
+  const bool one_filters = g.wf == g.wt;     // (then launch_bwd_conv_logits packs them)
+  if (for_logits && !one_filters) {
     const hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
     if (e != hipSuccess) return e;
   }
   // the page of zeros lies right before the sums (n is a multiple of 4)
   const int64_t zeros = ((char*)(g.dwt + n) - (char*)g.zero_page) / 16;
-  hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((zeros + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf, g.banks,
-                     (u32x4*)g.zero_page, zeros);
+  hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((zeros + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf,
+                     one_filters ? 0 : g.banks, (u32x4*)g.zero_page, zeros);
   return hipGetLastError();
 }
 
@@ -942,7 +945,15 @@ hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
   StepArgs a = g.st;
   a.ldw = g.ld;
   LogitsWindow win = {g.n_blk, g.B, g.tokens, g.state_stride, g.logits_stride};
-  return launch_conv_logits_mfma(a, g.wt, g.logits, s, &win);
+  if (g.wf != g.wt) return launch_conv_logits_mfma(a, g.wt, g.logits, s, &win);
+  // one place for both packings: that per tap for this kernel, then the one the kernels of the walk read
+  hipError_t e = launch_pack_filters_per_tap(a, g.banks, g.wt, s);
+  if (e == hipSuccess) e = launch_conv_logits_mfma(a, g.wt, g.logits, s, &win);
+  if (e != hipSuccess) return e;
+  const int64_t n = (int64_t)g.banks * (a.conv_in ? 2 : 1) * (kD / 32) * ((a.M + 15) / 16) * a.k_width * 64;
+  hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf, g.banks,
+                     (u32x4*)g.zero_page, 0);
+  return hipGetLastError();
 }
 
 hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s) {

@@ -310,6 +310,7 @@ struct BwdConvArgs {
   // workspace (bwd_conv_place)
   uint16_t* wt;              // filters per tap
   uint16_t* wf;              // filters as operand fragments of 16 slots x 32 channels: [bank][channels / 32][slots / 16][tap]
+                             // (wf == wt: one place for both, the one the kernel at hand reads is packed ahead of it)
   void* zero_page;           // 256 bytes of zeros
   float* dwt;                // filter gradient per tap
   float* logits;             // [block][chain][slot][ld]
@@ -326,8 +327,9 @@ struct BwdConvLayout {       // byte offsets; the first four are per call, the r
   int ld, P;
 };
 // T: the most positions of a block (m + Bn); n_blk: blocks of a window
-// with_logits: false where the logits of all blocks are kept elsewhere
-BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits);
+// with_logits: false where the logits of all blocks are kept elsewhere; one_filters: one place for either packing of the filters
+BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits,
+                              bool one_filters);
 void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws);
 // once per call: filters packed, sums and zeros cleared; at its end: the sums added to d_conv_w
 hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s);    // (for launch_bwd_conv_logits, too)

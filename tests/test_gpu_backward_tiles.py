@@ -102,3 +102,49 @@ def test_logits_left_by_the_scan_are_those_computed_again(case):
     for a, want in zip(*got):
         assert torch.isfinite(a).all()
         assert _rel(a, want) < (1e-3 if c["norm"] else 1e-5), _rel(a, want)
+
+
+@pytest.mark.parametrize("entry", ["step", "scan"])
+@pytest.mark.parametrize("case", [
+    dict(M=128, B=128),
+    dict(M=96, B=33, conv_width=21, conv_in=1),            # three parts, filters over [K | V]
+    dict(M=64, B=64, n_kv_heads=4, per_head=True),
+], ids=str)
+def test_least_workspace_has_one_place_for_the_filters(entry, case):
+    """What a step and a scan of one block did with before the filters were packed in two orders still does: one place for both, a
+    launch more, the same gradients.  Nothing is written behind it, and less is refused."""
+    c = dict(dict(conv_width=15, conv_in=0, n_kv_heads=2, per_head=False), **case)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    h, M, B, kw = c["n_kv_heads"], c["M"], c["B"], c["conv_width"]
+    C = 256 if c["conv_in"] else 128
+    banks = h if c["per_head"] else 1
+    q, k, v = (_rnd(g, 1, h, B, 128) for _ in range(3))
+    ck, cv = _rnd(g, 1, h, M, 128), _rnd(g, 1, h, M, 128)
+    cw = _rnd(g, *([h] if c["per_head"] else []), M, C, kw, sd=0.05)
+    d_o, gk, gv = (_rnd(g, *s, sd=1.0, dtype=torch.float32) for s in (q.shape, ck.shape, ck.shape))
+    cfg = lb.make_config(dtype=torch.bfloat16, batch=1, n_q_heads=h, n_kv_heads=h, head_dim=128, M=M, conv_width=kw,
+                         conv_in=c["conv_in"], **({"w_head_stride": M * C * kw} if c["per_head"] else {}))
+    cache = lb.Cache(cfg, DEV)
+    cache.load(ck, cv, M)
+
+    def run(n_bytes):
+        out = [torch.full_like(t, float("nan"), dtype=torch.float32) for t in (q, k, v, ck, cv)]
+        d_w = torch.zeros_like(cw, dtype=torch.float32)
+        room = torch.full((n_bytes + 4096,), 0xff, dtype=torch.uint8, device=DEV)
+        if entry == "step":
+            lb.lococo_segment_step_backward(cfg, q, k, v, cw, None, cache, d_o, gk, gv, *out, d_w, None, room[:n_bytes])
+        else:
+            lb.lococo_sequence_backward(cfg, q, k, v, B, cw, None, cache, d_o, gk, gv, *out, d_w, None, room[:n_bytes])
+        assert (room[n_bytes:] == 0xff).all()
+        return out + [d_w]
+
+    up = lambda n: (n + 255) // 256 * 256
+    packed = up(banks * kw * M * C * 2)
+    full = lb.lococo_backward_workspace_bytes(cfg, B, M) if entry == "step" else lb.lococo_sequence_backward_workspace_bytes(cfg, B, B)
+    want, got = run(full), run(full - packed)
+    for name, a, b in zip(("d_q", "d_k", "d_v", "d_cache_k", "d_cache_v"), got, want):
+        assert torch.equal(a, b), name
+    assert _rel(got[5], want[5]) < 1e-6                    # (atomic sums)
+    with pytest.raises(lb.LococoError, match=f"workspace needs {full - packed} bytes") as e:
+        run(full - packed - 256)
+    assert e.value.status == lb.LOCOCO_EWORKSPACE
