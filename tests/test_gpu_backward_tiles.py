@@ -102,6 +102,9 @@ def test_logits_left_by_the_scan_are_those_computed_again(case):
     for a, want in zip(*got):
         assert torch.isfinite(a).all()
         assert _rel(a, want) < (1e-3 if c["norm"] else 1e-5), _rel(a, want)
+    # logits that were kept show in the last bits of the gradients (no atomics in these); computed both times, they are the same
+    kept = not (c["protect"] or c["conv_in"])
+    assert all(torch.equal(a, want) for a, want in zip(got[0][:5], got[1][:5])) != kept
 
 
 @pytest.mark.parametrize("entry", ["step", "scan"])
