@@ -5,6 +5,7 @@ import torch
 
 from paper_2406_05317_amd import binding as lb
 from paper_2406_05317_amd import inputs
+from parity_util import compare_scan, gpu_forward, oracle_forward
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +54,30 @@ def test_one_launch_or_two_give_the_same_bits(case):
         out.append((o, cache.k.clone(), cache.v.clone(), cache.len))
     for x, y in zip(*out):
         assert x == y if isinstance(x, int) else torch.equal(x, y)
+
+
+@pytest.mark.parametrize("case", [
+    dict(M=64, B=64, L=256, conv_width=21, norm=1),          # a block's own tiles and the cache's, two each
+    dict(M=32, B=16, L=96),                                  # no tile of the block's own
+    dict(M=32, B=1, L=34, conv_width=21),
+    dict(M=96, B=160, L=480),                                # an empty cache at the first step
+    dict(M=64, B=40, L=190, norm=1, n_kv_heads=1),           # a fill, a partly filled cache, a ragged block
+    dict(M=64, B=64, L=256, conv_width=21, protect=True),
+], ids=str)
+def test_steps_over_keys_and_values_that_wait_for_nobody(case):
+    """Filters over [K | V], pairs of workgroups: the first step of a launch walks all its tiles with the key half of the filters
+    before it takes the value half, later ones do either for the block's own tiles first.  The same bits, and the oracle's."""
+    c = dict(case)
+    protect = c.pop("protect", False)
+    w = inputs.Workload(**{**dict(name="kvstep", dtype="bf16", batch=1, n_q_heads=2, n_kv_heads=2, head_dim=128, conv_width=15,
+                                  conv_in=1, seed=5), **c})
+    cfg = lb.config_for(w)
+    assert lb.lococo_describe_path(cfg, w.B)["step_pipeline"] == 2
+    q, k, v = inputs.qkv(w)
+    cw, cb = inputs.conv_filters(w)
+    mask = (torch.arange(w.M) < 5).view(1, 1, -1).expand(1, w.n_kv_heads, -1).numpy() if protect else None
+    scan = gpu_forward(w, q, k, v, cw, cb, history=True, protect=mask)
+    steps = gpu_forward(w, q, k, v, cw, cb, step_by_step=True, protect=mask)
+    for x, y in zip(scan, steps):
+        assert x == y if isinstance(x, int) else torch.equal(x, y)
+    compare_scan(w, scan, oracle_forward(w, q, k, v, cw, cb, protect=mask), what=str(case))
