@@ -1311,8 +1311,11 @@ struct SeqBwdLayout {
 // What a window may take: enough blocks to fill the device many times over at any shape, whatever the length of the
 // sequence.
 constexpr size_t kBwdWindowBytes = (size_t)3 << 30;
-// The logits of Eq. 5 of every block may take this much (64 blocks of 32 chains, 512 slots and 1024 positions: 4.3 GB); what is
-// longer computes them window by window.  Keeping them takes Eq. 5 out of the pass once: 3.75 of 32.5 ms on that sequence.
+// The logits of Eq. 5 of every block may take this much (64 blocks of 32 chains, 512 slots and 1024 positions: 4.3 GB of the
+// 7.4 GiB a call on that sequence asks for, 3.2 without); what is longer computes them window by window.  Keeping them takes Eq. 5
+// out of the pass once, 34.2 -> 30.8 ms on that sequence, 16 K tokens of twice the chains 33.0 -> 29.9, 3.5 K tokens on 128 slots
+// 1.78 -> 1.67.  The limit bounds what a call asks for, it is not where keeping stops to pay; it is all blocks or none, and 64
+// blocks of 64 such chains miss it by 0.1 %.
 constexpr size_t kBwdLogitsBytes = (size_t)8 << 30;
 
 // largest_window: blocks a window may have at most; keep: whether the logits of all blocks may have a place; one_filters: see

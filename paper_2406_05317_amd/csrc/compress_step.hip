@@ -2,8 +2,9 @@
 // each other.  Where the compression of a single step leaves compute units without a workgroup (each workgroup of it fills
 // one: LDS and registers), the attention's workgroups take those.  The bodies are those of the separate launches, so are
 // the bits.  Bound by the compression (filter slice, walk, epilogue in series); measured, one token of 32 heads on 128
-// slots: 16.2 us as two launches (11.1 + 5), 11.9 us as one; 77 tokens of 32 heads on 8 kv heads, 256 slots: 29.2 us
-// (18.5 + 10.5), 18.9 us.
+// slots: 16.2 us as two launches (11.1 + 5), 11.9 us as one, 10.9 with the compression on waves of two roles; 77 tokens of 32
+// heads on 8 kv heads, 256 slots: 29.2 us (18.5 + 10.5), 18.9, 16.7 us (on inputs not in any cache 43.6 -> 41.3 us: there the first
+// reads of the filters and of the cache, one after the other, are most of it).
 #include "attn_decode_row.h"
 #include "attn_tile.h"
 #include "compress_roles.h"

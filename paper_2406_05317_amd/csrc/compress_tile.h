@@ -3,6 +3,10 @@
 // weights) in one pass, bf16 MFMA with fp32 accumulation.  The logits and the
 // normalised weights never leave the compute unit.
 //
+// Two kernels do this work: the one described next (compress_tile.inl), whose four waves all do the same, and one whose eight
+// waves have two roles (compress_roles.h), for filters over [K | V] and for single steps on the builds with two workgroups per
+// pair.  This file has what they share: the method, the layouts in LDS, the resources.
+//
 // Structure.  The step is "attention with a convolution for scores": for a
 // tile of BM cache slots the kernel walks the T = m + B positions of
 // [cache ; block] in tiles of 32, computes the logits as an implicit GEMM
@@ -38,8 +42,8 @@
 // and one over the values, so the walk is done twice: with the key half of the filters resident
 // the kernel leaves the summed key-side logits of every position tile in the workspace (4 KB per
 // tile, each lane writing the four values it will read back itself); then the value half takes the
-// registers' place and the ordinary pipeline runs with the value rows as the convolution's input,
-// the stored key-side logits added where the four waves' partial sums meet.  In that second walk
+// registers' place and the second walk runs with the value rows as the convolution's input,
+// the stored key-side logits added where the logit waves' partial sums meet.  In that walk
 // the two row tiles swap roles (values with halo, keys without), so the accumulator's first d
 // columns are the new value rows and the pointers are swapped where the rows are written.
 //
@@ -189,11 +193,11 @@ __device__ __forceinline__ Cat16 load_cat16(const CatRows& c, int p, int chunk) 
 // positions does not matter to either): first the tiles that lie wholly in the block, halo included --
 // they do not depend on the step before, so the workgroup whose turn is next works through them while
 // its partner finishes that step -- then, after the chain has been met, the tiles that touch the cache.
-// Only the second leg is on the chain's critical path.  (Single-step launches use the same build, one
+// Only the second leg is on the chain's critical path.  (Single-step launches walk the same two legs, one
 // workgroup of each pair idle, so that results do not depend on the kind of launch.)
-// LOG = 1: the logits of Eq. 5 also go to memory, step by step [chains, M, ld], for the backward pass of a scan (no protected
-// slots, filters over the keys).
-// CIN = 1: filters over [K | V] (two walks, see the head of the file); wp then holds the key half of
+// LOG = 1 (compress_tile.inl): the logits of Eq. 5 also go to memory, step by step [chains, M, ld], for the backward pass of a
+// scan (no protected slots, filters over the keys).
+// CIN = 1 (compress_roles.h): filters over [K | V] (two walks, see the head of the file); wp then holds the key half of
 // every bank's slices followed by the value half, each in the order above.
 
 }  // namespace compress_detail
