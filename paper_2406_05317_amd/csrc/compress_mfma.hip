@@ -8,9 +8,8 @@ namespace {
 
 using namespace compress_detail;
 
-// On page boundaries: the same code elsewhere in the library ran 0.5 - 1.5 % slower on 3.5 K tokens, M = 128.
 template <int BM, int KW, int NORM, int PROT, int MULTI, int SPLIT, int LOG>
-__attribute__((aligned(4096))) __global__ __launch_bounds__(kThreads, 1) void compress_mfma_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
+__global__ __launch_bounds__(kThreads, 1) void compress_mfma_k(ScanArgs sa, const uint16_t* wp, int64_t wp_head_stride) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t wg_id = blockIdx.x, wg_count = gridDim.x;
 #include "compress_tile.inl"
