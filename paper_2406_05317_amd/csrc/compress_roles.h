@@ -504,21 +504,20 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
   auto trade = [&]() { const CatRows t = cat_k; cat_k = cat_v; cat_v = t; };
   if constexpr (PIPE) {
     zero_state();
-    // first the tiles of the block alone, then, once the chain has been met, those that touch the cache.  Of a [K | V] bank each
-    // is walked twice, but a step that has nobody to wait for (the first of a launch) takes the first walk of all its tiles at
-    // once: two loads of a filter slice and three walks instead of four of either (a step of 64 tokens on 64 slots, 8 heads,
-    // width 21: 21.9 -> 18.7 us, 96 on 96: 25.4 -> 22.3; either way the same sums in the same order).
-    const bool alone = CIN && step == 0;
-    for (int leg = 0; leg < 2; ++leg) {
-      const bool both = CIN && !(alone && leg == 1);       // (both walks)
-      if (both) load_filters(0);
-      if (leg == 1) {
-        if (step > 0 && !chain_wait(ch, step)) return;
-      }
-      const int lo = leg == 0 ? first_blk * BN : 0, n = leg == 0 ? NT_all - first_blk : first_blk;
-      if constexpr (CIN) {
-        jbase = alone ? 0 : lo;
-        NT = alone ? NT_all : n;
+    // first the tiles of the block alone, then, once the chain has been met, those that touch the cache
+    if constexpr (CIN) {
+      // Each is walked twice.  But a step that has nobody to wait for (the first of a launch) takes the first walk of all its
+      // tiles at once: two loads of a filter slice and three walks instead of four of either (a step of 64 tokens on 64 slots,
+      // 8 heads, width 21: 21.9 -> 18.7 us, 96 on 96: 25.4 -> 22.3; either way the same sums in the same order).
+      const bool alone = step == 0;
+      for (int leg = 0; leg < 2; ++leg) {
+        const bool both = !(alone && leg == 1);
+        if (both) load_filters(0);
+        if (leg == 1) {
+          if (step > 0 && !chain_wait(ch, step)) return;
+        }
+        jbase = alone || leg == 1 ? 0 : first_blk * BN;
+        NT = alone ? NT_all : leg == 0 ? NT_all - first_blk : first_blk;
         if (both && NT > 0) {
           pin_filters();
           walk(first);
@@ -527,16 +526,26 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
           pin_filters();
           trade();
         }
+        jbase = leg == 0 ? first_blk * BN : 0;
+        NT = leg == 0 ? NT_all - first_blk : first_blk;
+        if (NT > 0) {
+          walk(main_walk);
+          if (!alone) trade();
+        }
+        if (leg == 0) __syncthreads();
       }
-      jbase = lo;
-      NT = n;
-      if (NT > 0) {
-        walk(main_walk);
-        if (CIN && !alone) trade();
+      if (!alone) trade();
+    } else {
+      for (int leg = 0; leg < 2; ++leg) {
+        if (leg == 1) {
+          if (step > 0 && !chain_wait(ch, step)) return;
+        }
+        jbase = leg == 0 ? first_blk * BN : 0;
+        NT = leg == 0 ? NT_all - first_blk : first_blk;
+        if (NT > 0) walk(main_walk);
+        if (leg == 0) __syncthreads();
       }
-      if (leg == 0) __syncthreads();
     }
-    if (CIN && !alone) trade();
   } else {
     if (CIN && pass == 0) {
       if (NT > 0) walk(first);
