@@ -109,14 +109,17 @@ __device__ __forceinline__ float exp_neg(float x) {
 }
 
 // ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
-// each; the rows of a step stay in registers from the logits to dl.  Bound by its stores (134 MB a step of 32 chains, 512 slots,
-// 1024 positions) and by the latencies before them, one workgroup filling a compute unit: 83 us a step, 69 without the
-// stores, 55 without the products; as five kernels with fp32 arrays in memory between them 250 us.  MULTI: more positions than that: they are walked
-// twice in chunks, first for the row sums alone.
+// each; the rows of a step stay in registers from the logits to dl.  Bound by memory in turns, one workgroup filling a compute
+// unit: the logits in (64 MB a step of 32 chains, 512 slots, 1024 positions), the entries from the L2 (512 KB a workgroup), the
+// planes out (134 MB): 66 us a step, 13.2 us with 128 slots on 256 positions; as five kernels with fp32 arrays in memory between
+// them 250 us.  Entries and planes go through LDS, 4 KB of a wave's own, so that an instruction covers whole lines: with
+// fragments straight from memory and 16 bytes a lane straight to it, 32 lines an instruction in quarters, 83 and 14.8 us.
+// MULTI: more positions than that: they are walked twice in chunks, first for the row sums alone.
 template <int NT, bool MULTI, int NORM, int PARTS>
 __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   const StepArgs& a = g.st;
   __shared__ __align__(16) unsigned char Gs[PARTS][2][32 * 256];     // [part][keys, values]: tiles of 32 rows (see swz)
+  __shared__ __align__(16) unsigned char Xs[8][32 * 128];        // a wave's own: 32 rows of 128 bytes (see pswz)
   __shared__ __align__(16) float red[2][8][32];
   __shared__ __align__(16) float row_s[3][32];                   // reference, 1 / sum, sum n G
   const Block x = block_of(g, blk);
@@ -131,18 +134,15 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   // does not count has the logit -inf.  (Rows of a slot past M hold whatever follows: they end as zeros below.)
   const float* lg = g.logits + blk * g.logits_stride + ((int64_t)ch * a.M + s0) * g.ld;
   f32x16 acc[NT], xl[NT];
-  auto fetch = [&](int pc) {
+  auto fetch = [&](int pc, int n) {
+    const int p0 = pc + (w + 8 * n) * 32;
+    if (p0 < x.T) {
+      const float* p = lg + (int64_t)(lh * 4) * g.ld + p0 + l31;           // (rows are padded to whole tiles)
 #pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      const int p0 = pc + (w + 8 * n) * 32;
-      if (p0 < x.T) {
-        const float* p = lg + (int64_t)(lh * 4) * g.ld + p0 + l31;         // (rows are padded to whole tiles)
+      for (int i = 0; i < 16; ++i) xl[n][i] = p[(int64_t)((i >> 2) * 8 + (i & 3)) * g.ld];
+    } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) xl[n][i] = p[(int64_t)((i >> 2) * 8 + (i & 3)) * g.ld];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) xl[n][i] = -INFINITY;
-      }
+      for (int i = 0; i < 16; ++i) xl[n][i] = -INFINITY;
     }
   };
   auto mask = [&](int pc) {
@@ -155,7 +155,6 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
       for (int i = 0; i < 16; ++i) xl[n][i] = out ? -INFINITY : xl[n][i];
     }
   };
-  fetch(0);
   // slots that mix: all live ones but the protected
   uint32_t mixing = a.M - s0 >= 32 ? 0xffffffffu : (1u << (a.M - s0)) - 1u;
   if (prot && s0 < x.m) {
@@ -172,12 +171,51 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     mixing &= ~p;
   }
   mixing = __builtin_amdgcn_readfirstlane(mixing);
+  // Rows of [g_k | g_v] first, then the entries' rows and the logits of the first tile: loads come back in the order they are
+  // asked for, and g is what the workgroup meets over.
+  f32x4 gr[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {             // eight columns of a row of [g_k | g_v] per item
+    const int it = tid + i * 512, r = it >> 5, c8 = it & 31;
+    const float* p = (c8 >> 4 ? gv : gk) + (int64_t)min(s0 + r, a.M - 1) * kD + (c8 & 15) * 8;
+    gr[i][0] = *(const f32x4_any*)p;
+    gr[i][1] = *(const f32x4_any*)(p + 4);
+  }
+  auto entry = [&](int j, int val) {
+    j = j < x.T ? j : x.T - 1;
+    const uint16_t* c = (val ? x.cv : x.ck) + ((int64_t)ch * a.M + j) * kD;
+    const View& st = val ? a.v : a.k;
+    const uint16_t* q = (val ? x.v : x.k) + (ch / a.Hkv) * st.sb + hkv * st.sh + (int64_t)(j - x.m) * st.st;
+    return j < x.m ? c : q;
+  };
+  // A tile's keys and values, whole rows of 128 bytes at a time (half h of row 8 i + l / 8: register 4 h + i), become operand
+  // fragments on the way through the wave's own LDS; each is requested again for the next tile when it is there.
+  bf16x8 fx[2][8];
+  auto request_entries = [&](int p0, int val) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint16_t* row = entry(p0 + 8 * i + (l >> 3), val) + (l & 7) * 8;
+      fx[val][i] = *(const bf16x8*)row;
+      fx[val][4 + i] = *(const bf16x8*)(row + 64);
+    }
+  };
+  auto request_tile0 = [&](int pc) {
+    request_entries(pc + w * 32, 0);
+    request_entries(pc + w * 32, 1);
+    fetch(pc, 0);
+  };
+  unsigned char* const xs = Xs[w];
+  const int by_row = (l >> 3) * 128 + (((l & 7) ^ pswz(l >> 3)) << 4);      // rows 8 i + l / 8: + 1024 i, ^ 32 where i is odd
+  const int by_pos = l31 * 128 + ((lh ^ pswz(l31)) << 4);                   // chunk 2 k + l / 32 of row l % 32: ^ 32 k
+  auto wave_sync = [&]() {                  // (LDS serves a wave in order: nothing to wait for)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  request_tile0(0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
     const int it = tid + i * 512, r = it >> 5, c8 = it & 31, val = c8 >> 4;
-    const float* p = (val ? gv : gk) + (int64_t)min(s0 + r, a.M - 1) * kD + (c8 & 15) * 8;
-    const f32x4_any v0 = *(const f32x4_any*)p, v1 = *(const f32x4_any*)(p + 4);
-    float v[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+    float v[8] = {gr[i][0][0], gr[i][0][1], gr[i][0][2], gr[i][0][3], gr[i][1][0], gr[i][1][1], gr[i][1][2], gr[i][1][3]};
     if (s0 + r >= a.M)
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] = 0.f;
@@ -190,23 +228,6 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   int ga[8];
 #pragma unroll
   for (int ks = 0; ks < 8; ++ks) ga[ks] = l31 * 256 + (((2 * ks + lh) ^ swz(l31)) << 4);
-  auto entry = [&](int p0, int val) {
-    const int j = p0 + l31 < x.T ? p0 + l31 : x.T - 1;
-    const uint16_t* c = (val ? x.cv : x.ck) + ((int64_t)ch * a.M + j) * kD;
-    const View& st = val ? a.v : a.k;
-    const uint16_t* q = (val ? x.v : x.k) + (ch / a.Hkv) * st.sb + hkv * st.sh + (int64_t)(j - x.m) * st.st;
-    return (j < x.m ? c : q) + lh * 8;
-  };
-  // operand fragments of a tile's keys and values; each half is requested again for the next tile behind the products that
-  // read it (the first one here, in flight while g is staged)
-  bf16x8 fx[2][8];
-  auto request_entries = [&](int p0, int val) {
-    const uint16_t* row = entry(p0, val);
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) fx[val][ks] = *(const bf16x8*)(row + ks * 16);
-  };
-  request_entries(w * 32, 0);
-  request_entries(w * 32, 1);
   __syncthreads();
   {                                         // g for bwd_dx_k, as operand fragments: wave w the columns 32 w .. of [K | V]
     const int s16 = l & 15, g2 = (l >> 4) & 1, chunk = (w & 3) * 4 + 2 * g2 + ((s16 & 3) >> 1);
@@ -226,16 +247,28 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     for (int n = 0; n < NT; ++n) {
       const int p0 = pc + (w + 8 * n) * 32;
       acc[n] = zero16();
-      if (p0 >= x.T) continue;
+      if (p0 >= x.T) {
+        if (n + 1 < NT) fetch(pc, n + 1);
+        continue;
+      }
 #pragma unroll
       for (int val = 0; val < 2; ++val) {
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-          for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs[u][val] + ga[ks]), fx[val][ks], acc[n]);
+          for (int i = 0; i < 4; ++i) *(bf16x8*)(xs + i * 1024 + (by_row ^ (i & 1) << 5)) = fx[val][4 * h + i];
+          if (h && n + 1 < NT) request_entries(p0 + 256, val);   // (rows past the end: the last one again)
+          wave_sync();
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const bf16x8 f = *(const bf16x8*)(xs + (by_pos ^ k << 5));
+#pragma unroll
+            for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs[u][val] + ga[4 * h + k]), f, acc[n]);
+          }
+          wave_sync();
         }
-        if (n + 1 < NT) request_entries(p0 + 256, val);        // (rows past the end: the last one again)
       }
+      if (n + 1 < NT) fetch(pc, n + 1);
     }
   };
   // the 16 rows' values of a lane, combined over the lanes and the waves; the result of row r lands with thread r
@@ -319,9 +352,9 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     uint16_t* pw = g.wn_low + blk * g.plane_stride;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
-      const int p0 = pc + (w + 8 * n) * 32, pos = p0 + l31;
+      const int p0 = pc + (w + 8 * n) * 32;
       if (p0 >= x.T) continue;
-      const int64_t o = (((int64_t)ch * tiles + sb) * g.P + pos) * 64 + lh * 8;
+      u32x4 out[3][2][2];                   // [plane][high, low halves][slots 16 qp + 8 lh ..]
 #pragma unroll
       for (int qp = 0; qp < 2; ++qp) {      // slots 16 qp .. + 15: two groups of four of this lane
         uint32_t nh[2][2], nl[2][2], n3[2][2], dh[2][2], dlo[2][2];
@@ -351,21 +384,37 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
           split2(vd[2], vd[3], dh[q][1], dlo[q][1]);
         }
         // the halves of the wave trade groups, so that a lane has eight consecutive slots: 16 qp + 8 lh ..
-        auto put = [&](uint16_t* at, const uint32_t (&v)[2][2]) {
+        auto trade = [&](const uint32_t (&v)[2][2]) {
           const auto t0 = __builtin_amdgcn_permlane32_swap(v[0][0], v[1][0], false, false);
           const auto t1 = __builtin_amdgcn_permlane32_swap(v[0][1], v[1][1], false, false);
-          const u32x4 out = {t0[0], t1[0], t0[1], t1[1]};
-          *(u32x4*)at = out;                // (positions T .. of the last tile: zeros, which bwd_dw_k reads)
+          return u32x4{t0[0], t1[0], t0[1], t1[1]};
         };
-        put(pn + o + qp * 16, nh);
-        put(pn + o + qp * 16 + 32, nl);
+        out[0][0][qp] = trade(nh);
+        out[0][1][qp] = trade(nl);
         if (PARTS == 3) {
-          put(pw + o + qp * 16, n3);
-          put(pw + o + qp * 16 + 32, nh);
+          out[2][0][qp] = trade(n3);
+          out[2][1][qp] = out[0][0][qp];
         }
-        put(pl + o + qp * 16, dh);
-        put(pl + o + qp * 16 + 32, dlo);
+        out[1][0][qp] = trade(dh);
+        out[1][1][qp] = trade(dlo);
       }
+      // a plane's 32 positions through the wave's LDS, so that every store covers whole lines: eight positions, 1 KB
+      // (positions T .. of the last tile: zeros, which bwd_dw_k reads)
+      const int64_t o = (((int64_t)ch * tiles + sb) * g.P + p0) * 64 + l * 8;
+      auto put = [&](uint16_t* at, const u32x4 (&v)[2][2]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *(u32x4*)(xs + (by_pos ^ k << 5)) = v[k >> 1][k & 1];
+        wave_sync();
+        u32x4 t[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = *(const u32x4*)(xs + i * 1024 + (by_row ^ (i & 1) << 5));
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *(u32x4*)(at + o + i * 512) = t[i];
+      };
+      put(pn, out[0]);
+      put(pl, out[1]);
+      if (PARTS == 3) put(pw, out[2]);
     }
   };
   if (!MULTI) {
@@ -376,11 +425,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     finish(0);
   } else {
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
-      if (pc) {
-        fetch(pc);
-        request_entries(pc + w * 32, 0);
-        request_entries(pc + w * 32, 1);
-      }
+      if (pc) request_tile0(pc);
       contract(pc);
       mask(pc);
       weigh();
@@ -388,9 +433,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     }
     publish();
     for (int pc = 0; pc < x.T; pc += 256 * NT) {
-      fetch(pc);
-      request_entries(pc + w * 32, 0);
-      request_entries(pc + w * 32, 1);
+      request_tile0(pc);
       contract(pc);
       mask(pc);
       if (NORM == 0) rows(0);
