@@ -7,16 +7,17 @@
 //   bwd_attn_kv_k   a workgroup per 128 keys of [cache ; block]: dYk = dS^T q and dYv = P^T dO over the rows of all
 //                   heads of the group.
 // The fp32 operands (dO, P, dS) enter the matrix products as two bf16 halves (16 bits kept): S 1, dP 2, dq 2, dYk 2,
-// dYv 3 products; with the recomputation 15 products per (query, key) pair of 128 columns.  A block whose number of
+// dYv 3 products; with the recomputation 14 products per (query, key) pair of 128 columns.  A block whose number of
 // positions is no multiple of 4, or a step whose gradients are not 16-byte aligned, enters with three parts (24 bits, nothing
 // lost; dP, dq, dYk 3, dYv 6 products): those have always been computed in fp32, and errors stay at that level (3e-7 against
 // 3.5e-6 with two).
-// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 5.3 ms for the whole sequence (2.1 + 3.3) against 20.0 ms as
-// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.27 against
+// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 4.2 ms for the whole sequence (1.9 + 2.3) against 20.0 ms as
+// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.22 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
-// between the products (matrix pipe 45 % busy in the first kernel, 30 % in the second).  Operands read ahead of their products,
-// fragments waited for before the loops and a loop of its own for either kind of wave (no spills, whose reloads waited for
-// the tiles just requested): 12 blocks of 256 queries on 512 keys, 2 x 32 heads on 8: 226 -> 216 and 339 -> 279 us.
+// between the products (matrix pipe 43 % busy in the first kernel, 33 % in the second).  The second kernel took 2.8 ms and 144 us
+// with one workgroup of eight waves to a compute unit, four for dYv and four for dYk with S computed twice: of a workgroup's
+// 90 000 cycles 14 000 went by before its first product and 20 000 in its stores, and the kinds waited for each other 1 800 of
+// 8 200 a tile.  One such workgroup with both sums in every wave still took 2.7 ms.
 // D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.
 #include <type_traits>
 
@@ -254,16 +255,27 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
   }
 }
 
-// Eight waves, two per group of 32 keys: waves 0..3 accumulate dYv (S, P^T dO), waves 4..7 dYk (S, dP, dS^T q).  One wave
-// with both would hold 384 registers of accumulators and key / value fragments; split, a wave needs under 256, each SIMD
-// has one of either kind to interleave, and the price is S computed twice (72 products instead of 64 per 32 x 32 tile).
+// A wave accumulates dYk and dYv of 32 keys: 128 of its 256 registers are sums, so key and value fragments lie in LDS in part,
+// in fragment order: as many as it takes to spill none (a reload waits for the tiles requested before it).
+// With two parts a workgroup is four waves that walk tiles of 32 rows, and two workgroups share a compute unit: one's first
+// loads and last stores, a third of its life, fall beside the other's products.  With three the tiles leave no room for two:
+// eight waves walk tiles of 64 rows, two per group of keys, one for either half of a tile, and add up at the end.
 template <int PARTS>
-__global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
-  constexpr int kSet = 1 + PARTS;
-  extern __shared__ __align__(16) unsigned char smem[];       // [2][q | parts of dO] tiles of 64 rows, [2][3][64] statistics
+struct Kv {
+  static constexpr int HV = PARTS == 2 ? 1 : 2, waves = 4 * HV, rows = 32 * HV;       // halves of a tile, rows of a tile
+  static constexpr int tile = rows * 256, set = (1 + PARTS) * tile;                   // tiles of q | parts of dO
+  static constexpr int VL = 4, KL = 3;                        // k steps whose value, key fragments are in LDS
+  static constexpr int f_at = 2 * set, st_at = f_at + (VL + KL) * 4 * 1024, lds = st_at + 2 * 3 * rows * 4;
+  static_assert(lds <= 80 * 1024 * HV && (HV == 1 || lds >= 8 * 64 * 64 * 4), "tiles, fragments, statistics; sums handed over");
+};
+template <int PARTS>
+__global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd_attn_kv_k(BwdAttnArgs g) {
+  using X = Kv<PARTS>;
+  constexpr int TR = X::rows, VL = X::VL, KL = X::KL, CG = PARTS == 2 ? 1 : 1;
+  extern __shared__ __align__(16) unsigned char smem[];       // [2][tiles], fragments, [2][3][rows] statistics
   const AttnArgs& a = g.a;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
-  float* st_lds = (float*)(smem + 2 * kSet * kTile);
+  float* st_lds = (float*)(smem + X::st_at);
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int ktiles = (a.M + a.B + 127) / 128;
   const int chain = (item / ktiles) % (a.batch * a.Hkv), n = a.seg_first + item / ktiles / (a.batch * a.Hkv);
@@ -272,41 +284,47 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   const int Tn = s.m + s.Bn;
   if (j0 >= Tn) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
-  const int wj = j0 + 32 * (w & 3), j = wj + l31;             // this lane's position in [cache ; block]
-  const int first = j0 >= s.m ? (j0 - s.m) / 64 : 0;          // tiles of rows before it see none of the keys
-  const int rtiles = (s.Bn + 63) / 64 - first, N = a.group * rtiles;
+  const int kg = w & 3, half = w >> 2;
+  const int wj = j0 + 32 * kg, j = wj + l31;                  // this lane's position in [cache ; block]
+  const int first = j0 >= s.m ? (j0 - s.m) / TR : 0;          // tiles of rows before it see none of the keys
+  const int rtiles = (s.Bn + TR - 1) / TR - first, N = a.group * rtiles;
   const int64_t plane = (int64_t)a.batch * a.Hq * a.L;
 
+  // requests tile u (q, then the parts of dO) of the rows that come next, behind the last of them the walk moves on
   float stat = 0.f;
-  auto request = [&](int it) {
-    if (it >= N) return;
-    const int hq = hkv * a.group + it / rtiles, r0 = (first + it % rtiles) * 64;
-    const uint32_t lds = lds0 + (it & 1) * kSet * kTile;
-    const u32x4 rq = rows_rsrc((const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + s.start * a.q.st, s.Bn, a.q.st * 2);
+  int rn = 0, hn = 0, buf = 0;
+  auto request = [&](int u) {
+    if (hn >= a.group) return;
+    int l = tid & 63;
+    asm volatile("" : "+v"(l));             // (offsets are worked out again every time, not kept in registers)
+    const int hq = hkv * a.group + hn, r0 = (first + rn) * TR;
+    const uint32_t lds = lds0 + buf * X::set + u * X::tile;
     const uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start) * kOrow;
-    const u32x4 ro = make_rsrc(hl, (uint32_t)s.Bn * (kOrow * 2u));
-    request_tile<8>(rq, (uint32_t)(a.q.st * 2), r0, lds, w, l);
+    const u32x4 rs = u == 0 ? rows_rsrc((const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + s.start * a.q.st, s.Bn, a.q.st * 2)
+                            : make_rsrc(hl, (uint32_t)s.Bn * (kOrow * 2u));
 #pragma unroll
-    for (int h = 0; h < PARTS; ++h)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4);
-        load_to_lds(ro, lds + (1 + h) * kTile + r4 * 1024, (r0 + r) * (kOrow * 2) + h * 256 + (((l & 15) ^ swz(r)) << 4));
-      }
-    if (tid < 192) {
-      const int r = r0 + (tid & 63);
-      stat = r < s.Bn ? g.stats[(tid >> 6) * plane + ((int64_t)b * a.Hq + hq) * a.L + s.start + r] : 0.f;
+    for (int i = 0; i < 2; ++i) {
+      const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4), c = ((l & 15) ^ swz(r)) << 4;
+      load_to_lds(rs, lds + r4 * 1024, u == 0 ? (r0 + r) * (uint32_t)(a.q.st * 2) + c : (r0 + r) * (kOrow * 2) + (u - 1) * 256 + c);
+    }
+    if (u == 0 && tid < 3 * TR) {
+      const int r = r0 + tid % TR;
+      stat = r < s.Bn ? g.stats[tid / TR * plane + ((int64_t)b * a.Hq + hq) * a.L + s.start + r] : 0.f;
+    }
+    if (u == PARTS) {
+      buf ^= 1;
+      if (++rn == rtiles) { rn = 0; ++hn; }
     }
   };
-  auto publish_stats = [&](int it) {
-    if (it < N && tid < 192) st_lds[(it & 1) * 192 + tid] = stat;
+  auto publish_stats = [&](int at) {
+    if (tid < 3 * TR) st_lds[at * 3 * TR + tid] = stat;
   };
-  request(0);
-  // either kind of wave has the loop to itself (the registers of one do not count against the other)
-  auto run = [&](auto for_v_t) {
-  constexpr bool for_v = decltype(for_v_t)::value;
-  // key (and value) fragments of this lane's position; positions past the end are computed from the last one and dropped
-  bf16x8 fk[8], fv[8];
+#pragma unroll
+  for (int u = 0; u <= PARTS; ++u) request(u);
+  // key and value fragments of this lane's position; positions past the end are computed from the last one and dropped
+  bf16x8 fk[8], fv[8];                      // [KL ..], [VL ..]: those that stay in registers
+  unsigned char* const vf = smem + X::f_at + kg * 1024 + l * 16;
+  unsigned char* const kf = vf + VL * 4096;
   {
     const int jc = min(j, Tn - 1);
     const uint16_t* kp = (jc < s.m ? s.ck + (int64_t)jc * kD
@@ -314,10 +332,15 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
     const uint16_t* vp = (jc < s.m ? s.cv + (int64_t)jc * kD
                                    : (const uint16_t*)a.v.p + b * a.v.sb + hkv * a.v.sh + (s.start + jc - s.m) * a.v.st) + lh * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) fk[ks] = *(const bf16x8*)(kp + ks * 16);
-    if (!for_v)
+    for (int ks = KL; ks < 8; ++ks) fk[ks] = *(const bf16x8*)(kp + ks * 16);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) fv[ks] = *(const bf16x8*)(vp + ks * 16);
+    for (int ks = VL; ks < 8; ++ks) fv[ks] = *(const bf16x8*)(vp + ks * 16);
+    if (X::HV == 1 || half == 0)
+#pragma unroll
+      for (int ks = 0; ks < VL; ++ks) *(bf16x8*)(vf + ks * 4096) = *(const bf16x8*)(vp + ks * 16);
+    if (X::HV == 1 || half == 1)
+#pragma unroll
+      for (int ks = 0; ks < KL; ++ks) *(bf16x8*)(kf + ks * 4096) = *(const bf16x8*)(kp + ks * 16);
   }
   // (operand addresses of the other k steps and column blocks are these, xor a constant: registers are short here)
   int row0, tr0[2];
@@ -329,51 +352,29 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
     tr0[1] = ad.tr[0][1];
   }
   const float c = a.scale * kLog2e;
-  f32x16 acc[4];
+  f32x16 av[4], ak[4];
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = zero16();
+  for (int ct = 0; ct < 4; ++ct) av[ct] = ak[ct] = zero16();
   wait_loads<0>();
-  landed(fk);
-  if (!for_v) landed(fv);
+#pragma unroll
+  for (int ks = KL; ks < 8; ++ks) asm volatile("" : "+v"(fk[ks]));     // (see landed)
+#pragma unroll
+  for (int ks = VL; ks < 8; ++ks) asm volatile("" : "+v"(fv[ks]));
   publish_stats(0);
   __syncthreads();
 
-  for (int it = 0; it < N; ++it) {
-    request(it + 1);
-    const int r0 = (first + it % rtiles) * 64;
-    const unsigned char* Q = smem + (it & 1) * kSet * kTile;
-    const float* st = st_lds + (it & 1) * 192 + lh * 4;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int rb = r0 + h * 32;
-      if (rb >= s.Bn || (wj >= s.m && rb + 31 < wj - s.m)) continue;      // no row of this half sees these keys
-      const unsigned char* q0 = Q + h * 32 * 256;
-      // N products of one accumulator, their operands read two ahead (left alone the compiler reads each right before its
-      // product and waits for it)
-      auto chain = [&](auto n_t, auto read, const bf16x8 (&f)[8], f32x16& to) {
-        constexpr int N = decltype(n_t)::value;
-        bf16x8 ring[3];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) ring[i] = read(i);
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-          if (i + 2 < N) ring[(i + 2) % 3] = read(i + 2);
-          __builtin_amdgcn_sched_barrier(0);
-          to = mfma32(ring[i % 3], f[i % 8], to);
-        }
-      };
-      f32x16 sc = zero16();
-      chain(std::integral_constant<int, 8>{}, [&](int i) { return *(const bf16x8*)(q0 + (row0 ^ (i << 5))); }, fk, sc);
-      __builtin_amdgcn_sched_barrier(0);
-      float p[16];
-#pragma unroll
-      for (int gi = 0; gi < 4; ++gi) {
-        const f32x4 mcs = *(const f32x4*)(st + h * 32 + gi * 8), inv = *(const f32x4*)(st + 64 + h * 32 + gi * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[gi * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sc[gi * 4 + e], c, -mcs[e])) * inv[e];
-      }
-      auto hide = [&]() {                   // pairs of a key and a query that does not see it
-        if (rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m)) {
+  for (int it = 0, rt = 0; it < N; ++it) {
+    request(0);
+    const int rb = (first + rt) * TR + half * 32;
+    if (++rt == rtiles) rt = 0;
+    const float* st = st_lds + (it & 1) * 3 * TR + half * 32 + lh * 4;
+    const bool seen = rb < s.Bn && !(wj >= s.m && rb + 31 < wj - s.m);      // else no row of this half sees these keys
+    if (seen) {
+      asm volatile("" : "+v"(row0), "+v"(tr0[0]), "+v"(tr0[1]));       // (or the xors are kept in registers of their own)
+      const unsigned char* q0 = smem + (it & 1) * X::set + half * 32 * 256;
+      const bool hidden = rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m);
+      auto hide = [&](float (&p)[16]) {     // pairs of a key and a query that does not see it
+        if (hidden) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
             const int r = rb + (i >> 2) * 8 + lh * 4 + (i & 3);
@@ -381,70 +382,148 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
           }
         }
       };
-      if (for_v) hide();
-      if (for_v) {
+      auto pin = [&]() { __builtin_amdgcn_sched_barrier(0); };
+      auto transposed = [&](const unsigned char* t, int ct) { return frag_tr(t + (tr0[0] ^ (ct << 6)), t + (tr0[1] ^ (ct << 6))); };
+      f32x16 sc, dp;
+      // S and dP, operands read two products ahead (left alone the compiler reads each right before its product and waits for it)
+      auto scores = [&]() {
+        bf16x8 ring[3], rk[3];
+        auto read = [&](int i) {
+          ring[i % 3] = *(const bf16x8*)(q0 + (row0 ^ (i << 5)));
+          rk[i % 3] = i < KL ? *(const bf16x8*)(kf + i * 4096) : fk[i];
+        };
+        sc = zero16();
+        read(0);
+        read(1);
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          bf16x8 fp[PARTS];
-          split_parts<PARTS>(p + 8 * s2, fp);
-          const unsigned char* o0 = q0 + kTile + s2 * 16 * 256;
-#pragma unroll
-          for (int u = 0; u < PARTS; ++u) {
-            bf16x8 fo[4];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) fo[ct] = frag_tr(o0 + u * kTile + (tr0[0] ^ (ct << 6)), o0 + u * kTile + (tr0[1] ^ (ct << 6)));
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int v = 0; u + v < PARTS; ++v)
-#pragma unroll
-              for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma32(fo[ct], fp[v], acc[ct]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+        for (int i = 0; i < 8; ++i) {
+          if (i + 2 < 8) read(i + 2);
+          pin();
+          sc = mfma32(ring[i % 3], rk[i % 3], sc);
         }
-      } else {
-        f32x16 dp = zero16();
-        chain(std::integral_constant<int, 8 * PARTS>{}, [&](int i) { return *(const bf16x8*)(q0 + (1 + i / 8) * kTile + (row0 ^ (i % 8 << 5))); }, fv, dp);
+        pin();
+      };
+      auto weights_grad = [&]() {
+        bf16x8 ring[3], rv[2];
+        auto read = [&](int i) {            // product i: part i % PARTS of k step i / PARTS
+          const int ks = i / PARTS;
+          ring[i % 3] = *(const bf16x8*)(q0 + (1 + i % PARTS) * X::tile + (row0 ^ (ks << 5)));
+          if (i % PARTS == 0) rv[ks % 2] = ks < VL ? *(const bf16x8*)(vf + ks * 4096) : fv[ks];
+        };
+        dp = zero16();
+        read(0);
+        read(1);
 #pragma unroll
-        for (int gi = 0; gi < 4; ++gi) {
-          const f32x4 dd = *(const f32x4*)(st + 128 + h * 32 + gi * 8);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) p[gi * 4 + e] *= (dp[gi * 4 + e] - dd[e]) * a.scale;
+        for (int i = 0; i < 8 * PARTS; ++i) {
+          if (i + 2 < 8 * PARTS) read(i + 2);
+          pin();
+          dp = mfma32(ring[i % 3], rv[i / PARTS % 2], dp);
         }
-        hide();                             // (here, so that a query that is no number stays out of later keys' gradients)
+        pin();
+      };
+      if (X::HV == 2 && half) weights_grad();             // (the two waves of a SIMD: one's products beside the other's exponentials)
+      scores();
+      request(1);
+      pin();
+      bf16x8 ring[2 * CG];
+      auto read_o = [&](int i) {            // fragment i: column block i % 4 of part i / 4 % PARTS, rows 16 (i / 4 / PARTS) ..
+        if (i < 8 * PARTS) ring[i % (2 * CG)] = transposed(q0 + (1 + i / 4 % PARTS) * X::tile + i / 4 / PARTS * 16 * 256, i % 4);
+      };
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          bf16x8 fd[PARTS];
-          split_parts<PARTS>(p + 8 * s2, fd);
-          const unsigned char* t0 = q0 + s2 * 16 * 256;
-          bf16x8 qf[4];
+      for (int i = 0; i < CG; ++i) read_o(i);
+      float p[16];
 #pragma unroll
-          for (int ct = 0; ct < 4; ++ct) qf[ct] = frag_tr(t0 + (tr0[0] ^ (ct << 6)), t0 + (tr0[1] ^ (ct << 6)));
-          __builtin_amdgcn_sched_barrier(0);
+      for (int gi = 0; gi < 4; ++gi) {
+        const f32x4 mcs = *(const f32x4*)(st + gi * 8), inv = *(const f32x4*)(st + TR + gi * 8);
 #pragma unroll
-          for (int u = 0; u < PARTS; ++u)
+        for (int e = 0; e < 4; ++e) p[gi * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sc[gi * 4 + e], c, -mcs[e])) * inv[e];
+        if (PARTS == 3 && gi == 1) pin();   // (registers)
+      }
+      hide(p);
+      bf16x8 part[PARTS];
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct) acc[ct] = mfma32(qf[ct], fd[u], acc[ct]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+      for (int i0 = 0; i0 < 8 * PARTS; i0 += CG) {
+        const int u = i0 / 4 % PARTS;
+        if (i0 % (4 * PARTS) == 0) split_parts<PARTS>(p + i0 / 4 / PARTS * 8, part);
+#pragma unroll
+        for (int i = i0; i < i0 + CG; ++i) read_o(i + CG);
+        pin();
+#pragma unroll
+        for (int v = 0; u + v < PARTS; ++v)
+#pragma unroll
+          for (int i = i0; i < i0 + CG; ++i) av[i % 4] = mfma32(ring[i % (2 * CG)], part[v], av[i % 4]);
+        pin();
+      }
+#pragma unroll
+      for (int u = 2; u <= PARTS; ++u) request(u);
+      pin();
+      if (X::HV == 1 || !half) weights_grad();
+      auto read_q = [&](int i) {
+        if (i < 8) ring[i % (2 * CG)] = transposed(q0 + i / 4 * 16 * 256, i % 4);
+      };
+#pragma unroll
+      for (int i = 0; i < CG; ++i) read_q(i);
+#pragma unroll
+      for (int gi = 0; gi < 4; ++gi) {
+        const f32x4 dd = *(const f32x4*)(st + 2 * TR + gi * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[gi * 4 + e] *= (dp[gi * 4 + e] - dd[e]) * a.scale;
+      }
+      hide(p);                              // (again, so that a query that is no number stays out of later keys' gradients)
+#pragma unroll
+      for (int i0 = 0; i0 < 8; i0 += CG) {
+        if (i0 % 4 == 0) split_parts<PARTS>(p + i0 / 4 * 8, part);
+#pragma unroll
+        for (int i = i0; i < i0 + CG; ++i) read_q(i + CG);
+        pin();
+#pragma unroll
+        for (int u = 0; u < PARTS; ++u)
+#pragma unroll
+          for (int i = i0; i < i0 + CG; ++i) ak[i % 4] = mfma32(ring[i % (2 * CG)], part[u], ak[i % 4]);
+        pin();
       }
     }
+    if (!seen)
+#pragma unroll
+      for (int u = 1; u <= PARTS; ++u) request(u);
     wait_loads<0>();
-    publish_stats(it + 1);
+    publish_stats(~it & 1);
     __syncthreads();
   }
-  if (j < Tn) {
-    float* dc = (for_v ? g.d_cv : g.d_ck) + ((int64_t)n * a.batch * a.Hkv + chain) * a.M * kD;
-    float* db = (for_v ? g.d_v : g.d_k) + b * g.k_sb + hkv * g.k_sh + s.start * kD;
-    float* out = (j < s.m ? dc + (int64_t)j * kD : db + (int64_t)(j - s.m) * kD) + lh * 4;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-      for (int gi = 0; gi < 4; ++gi)
-        *(f32x4_any*)(out + ct * 32 + gi * 8) = f32x4{acc[ct][gi * 4], acc[ct][gi * 4 + 1], acc[ct][gi * 4 + 2], acc[ct][gi * 4 + 3]};
-  }
+  float* const dc = (half ? g.d_ck : g.d_cv) + ((int64_t)n * a.batch * a.Hkv + chain) * a.M * kD;
+  float* const db = (half ? g.d_k : g.d_v) + b * g.k_sb + hkv * g.k_sh + s.start * kD;
+  float* const out = (j < s.m ? dc + (int64_t)j * kD : db + (int64_t)(j - s.m) * kD) + lh * 4;
+  auto quad = [](const f32x16 (&x)[4], int i) {
+    return f32x4{x[i >> 2][(i & 3) * 4], x[i >> 2][(i & 3) * 4 + 1], x[i >> 2][(i & 3) * 4 + 2], x[i >> 2][(i & 3) * 4 + 3]};
   };
-  if (w < 4) run(std::true_type{});
-  else run(std::false_type{});
+  if constexpr (X::HV == 1) {
+    float* const ko = (j < s.m ? g.d_ck + (((int64_t)n * a.batch * a.Hkv + chain) * a.M + j) * kD
+                               : g.d_k + b * g.k_sb + hkv * g.k_sh + (s.start + j - s.m) * kD) + lh * 4;
+    if (j < Tn)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        *(f32x4_any*)(out + (i >> 2) * 32 + (i & 3) * 8) = quad(av, i);
+        *(f32x4_any*)(ko + (i >> 2) * 32 + (i & 3) * 8) = quad(ak, i);
+      }
+  } else {                                  // the two halves trade: waves 0..3 finish dYv of their keys, waves 4..7 dYk
+    f32x4* const give = (f32x4*)smem + w * 1024 + l;
+    const f32x4* const take = (const f32x4*)smem + (w ^ 4) * 1024 + l;
+    auto hand_over = [&](const f32x16 (&x)[4]) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) give[i * 64] = quad(x, i);
+    };
+    if (half) hand_over(av);
+    else hand_over(ak);
+    __syncthreads();
+    auto finish = [&](const f32x16 (&x)[4]) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) *(f32x4_any*)(out + (i >> 2) * 32 + (i & 3) * 8) = quad(x, i) + take[i * 64];
+    };
+    if (j < Tn) {
+      if (half) finish(ak);
+      else finish(av);
+    }
+  }
 }
 
 }  // namespace
@@ -452,7 +531,7 @@ __global__ __launch_bounds__(512, 1) void bwd_attn_kv_k(BwdAttnArgs g) {
 template <int PARTS>
 static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
   const AttnArgs& a = g.a;
-  constexpr int lds_q = 4 * kTile, lds_kv = 2 * (1 + PARTS) * kTile + 2 * 3 * 64 * 4;
+  constexpr int lds_q = 4 * kTile, lds_kv = Kv<PARTS>::lds;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
@@ -462,7 +541,7 @@ static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
   }
   hipLaunchKernelGGL(bwd_attn_q_k<PARTS>, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
   const int ktiles = (a.M + a.B + 127) / 128;
-  hipLaunchKernelGGL(bwd_attn_kv_k<PARTS>, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(512), lds_kv, s, g);
+  hipLaunchKernelGGL(bwd_attn_kv_k<PARTS>, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(Kv<PARTS>::waves * 64), lds_kv, s, g);
   return hipGetLastError();
 }
 
