@@ -458,7 +458,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // sums meet in LDS at the end.  No two waves want the same filters, so these come from memory straight into the registers,
 // packed in fragment order, D taps ahead: within a phase there is nothing to meet for, and only the plane rows (which the
 // taps read at shifted rows) pass through LDS, by loads that write it directly, a phase or more ahead.  Rows outside the
-// sequence read as zero (buffer bounds).  145 us a step of 32 chains, 512 slots and 1024 positions (155 GFLOP), 11.5 us for the
+// sequence read as zero (buffer bounds).  139 us a step of 32 chains, 512 slots and 1024 positions (155 GFLOP), 11.5 us for the
 // cache rows at 128 slots (161 and 16.4 with the filters through LDS, two taps a barrier: requests, fragment reads and products
 // were a chain that the two waves of a SIMD overlapped in part).  Without the filter loads 131, without the LDS reads 133 us;
 // the value columns' workgroups, which follow the key columns', take 20 of it and the sums 6.
@@ -484,9 +484,12 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
   const StepArgs& a = g.st;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
   constexpr int ZC = 256 / NC;
-  const int blk = blk0 + blockIdx.z / ZC, val = blockIdx.z % ZC * NC / kD, cbase = blockIdx.z % ZC * NC % kD, ch = blockIdx.y, hkv = ch % a.Hkv;
+  // the tiles of a chain on one XCD: they read the same g, and their halos overlap (the cache rows of a step, 32 chains of 256
+  // slots, 32-row tiles, three parts: 44.1 -> 34.9 us; 128 slots, two parts: 11.6 -> 10.9; 512 slots, 128-row tiles: 141 -> 139)
+  const int item = xcd_item(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int blk = blk0 + blockIdx.z / ZC, val = blockIdx.z % ZC * NC / kD, cbase = blockIdx.z % ZC * NC % kD, ch = item / gridDim.x, hkv = ch % a.Hkv;
   const Block x = block_of(g, blk);
-  const int p0 = (part == 1 ? x.m : 0) + blockIdx.x * PT, pend = part == 0 ? x.m : x.T;
+  const int p0 = (part == 1 ? x.m : 0) + item % gridDim.x * PT, pend = part == 0 ? x.m : x.T;
   if (p0 >= pend) return;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int kq = w % KS, wo = w / KS;
