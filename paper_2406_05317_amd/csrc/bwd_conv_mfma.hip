@@ -470,6 +470,8 @@ struct Dx {
   static constexpr int PL = KS / 2, DR = PT + 32;                        // 32-slot planes of a chunk; rows with the halo
   static constexpr int DB = PL * DR * 128, NB = PL * PT * 128;           // bytes of a chunk's rows of dl, of n
   static constexpr int ND = DB / 8192, NN = NB / 8192;                   // requests of a wave for them
+  // two workgroups on a compute unit, 128 registers a wave: no room for g of the next chunk, whose wait the other one fills
+  static constexpr bool SHARED = PT == 64;
   static constexpr int D = 3;                                            // taps of filters in flight (a divisor of 15 and 21)
   static constexpr int RR = PB * CB >= 8 ? 64 : PB * CB >= 2 ? 32 : 16;  // registers of a wave summed up at a time
   static constexpr int rings = 2 * DB + (FINE ? 2 : 1) * NB, sums = 8 * RR * 256;
@@ -477,7 +479,7 @@ struct Dx {
   static_assert(DB % 8192 == 0 && NB % 8192 == 0, "whole requests");
 };
 template <int PT, int NC, int KS, bool FINE>
-__global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
+__global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g, int blk0, int part) {
   extern __shared__ __align__(16) unsigned char smem[];
   using G = Dx<PT, NC, KS, FINE>;
   constexpr int PB = G::PB, CB = G::CB, D = G::D, GP = FINE ? 3 : 2;
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
 #pragma unroll
       for (int c = 0; c < CB; ++c) f[u][c] = *(const bf16x8*)(p + u * gpart + c * 1024 + lane16);
   };
-  load_g(0, fg);
+  if (!G::SHARED) load_g(0, fg);
   for (int sc = 0; sc < nsc; ++sc) {
     if (taps) {
       const unsigned char* dp = smem + (sc & 1) * G::DB + (kq >> 1) * G::DR * 128;
@@ -628,7 +630,8 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
     {
       const unsigned char* np = smem + n_at(sc) + (kq >> 1) * PT * 128;
       bf16x8 fh[PB], fl[PB], next[GP][CB];
-      load_g(sc + 1, next);
+      if (G::SHARED) load_g(sc, fg);
+      else load_g(sc + 1, next);
       rows_at(np, l31, 0, fh);
       rows_at(np, l31, 1, fl);
       multiply(fh, fg[0]);
@@ -641,10 +644,11 @@ __global__ __launch_bounds__(512, NC == 64 ? 4 : 2) void bwd_dx_k(BwdConvArgs g,
         rows_at(np + G::NB, l31, 0, fh);       // the third part, [third | first]
         multiply(fh, fg[0]);
       }
+      if (!G::SHARED)
 #pragma unroll
-      for (int u = 0; u < GP; ++u)
+        for (int u = 0; u < GP; ++u)
 #pragma unroll
-        for (int c = 0; c < CB; ++c) fg[u][c] = next[u][c];
+          for (int c = 0; c < CB; ++c) fg[u][c] = next[u][c];
     }
     if (sc + 1 == nsc) break;
     if (turns) wait_loads<0>();
@@ -1014,17 +1018,20 @@ hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_
 
 template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
-  // The largest tile of which there is one for every compute unit (32 chains, 512 slots on 1024 positions: 147 us with 128 rows,
-  // 164 with 64); 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole
-  // 15.0).  With 32 rows the slots go eight ways, but no more ways than there are slots for: up to 64 of them fill half of the
-  // waves or fewer, and the columns take the other factor of two (a step's pass, 64 chains of 64 slots and 64 tokens, 31 taps:
-  // 142.7 -> 133.5 us; from 80 slots on eight ways are up to 2 % faster at 4 - 32 chains, as often slower as faster at 64).
+  // The largest tile of which there is one for every compute unit.  128 rows have one to themselves, 64 share it by two (32 chains,
+  // 512 slots on 1024 positions: 142 and 153 us, 128 slots, 27 blocks of 128 rows: 175 and 179), so 64 where they leave a tenth
+  // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 594 -> 581.
+  // 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole 15.0).  The
+  // slots of 32 rows go four ways, two workgroups on a compute unit: with eight, one (256 slots: 31.6 against 28.8 us; 160: 51 -
+  // 39; 384: 63 - 59; three parts 71 - 66).  Halves take eight (as often faster as slower at 80 and more slots), but four where
+  // that leaves an eighth less of the slots to pad (192 slots: 24.4 -> 22.1 us; 320: 30.8 -> 29.7).
   const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
-  if (per * ((rows + 127) / 128) >= cu_count()) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 63) / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
-  if (per * ((rows + 31) / 32) >= cu_count())
-    return g.st.M <= 64 ? launch_dx<32, 128, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 128, 8, FINE>(g, blk0, n_blk, part, rows, s);
-  return g.st.M <= 64 ? launch_dx<32, 64, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
+  const int64_t rows128 = ((int64_t)rows + 127) / 128 * 128, rows64 = ((int64_t)rows + 63) / 64 * 64;
+  const bool four_ways = (g.st.M + 63) / 64 * 64 * 9 <= (g.st.M + 127) / 128 * 128 * 8;
+  if (per * (rows128 / 128) >= cu_count() && rows128 * 10 <= rows64 * 11) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * (rows64 / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  return four_ways ? launch_dx<32, 64, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
 }
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;

@@ -64,6 +64,19 @@ def test_input_and_filter_gradients_at_tile_edges(case):
 
 
 @pytest.mark.parametrize("case", [
+    dict(batch=4, n_kv_heads=32, M=64, B=128),                                     # 64 rows: a third of two 128-row tiles is padding
+    dict(batch=4, n_kv_heads=32, M=65, B=122, conv_width=31),                      # the same in three parts, a row past a tile less
+    dict(batch=4, n_kv_heads=32, M=64, B=65, conv_in=1, conv_width=21),            # 129 rows, taps on both halves
+    dict(batch=2, n_kv_heads=32, M=160, B=32),                                     # 32 rows whole, four parts of more than 64 slots
+    dict(batch=2, n_kv_heads=32, M=129, B=30, conv_width=7),                       # the same in three parts, one slot past a chunk
+    dict(batch=1, n_kv_heads=3, M=192, B=64, conv_width=31),                       # halves, four parts
+    dict(batch=1, n_kv_heads=2, M=190, B=3, conv_in=1),                            # the same in three parts
+], ids=str)
+def test_gradients_on_the_tiles_that_pad_least(case):
+    test_input_and_filter_gradients_at_tile_edges(case)
+
+
+@pytest.mark.parametrize("case", [
     dict(batch=1, n_kv_heads=2, M=64, B=48, L=300),                                # pairs of workgroups; a fill, a ragged block
     dict(batch=1, n_kv_heads=2, M=96, B=96, L=481, conv_width=21, norm=1, bias=True),   # last block of one token
     dict(batch=2, n_kv_heads=32, M=96, B=64, L=320),                               # a workgroup per chain and 32 slots
