@@ -259,7 +259,8 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
 // in fragment order: as many as it takes to spill none (a reload waits for the tiles requested before it).
 // With two parts a workgroup is four waves that walk tiles of 32 rows, and two workgroups share a compute unit: one's first
 // loads and last stores, a third of its life, fall beside the other's products.  With three the tiles leave no room for two:
-// eight waves walk tiles of 64 rows, two per group of keys, one for either half of a tile, and add up at the end.
+// eight waves walk tiles of 64 rows, two per group of keys, one for either half of a tile, and add up at the end (as fast as with
+// a wave for either sum: 58 and 60 us on a block of 154 tokens).
 template <int PARTS>
 struct Kv {
   static constexpr int HV = PARTS == 2 ? 1 : 2, waves = 4 * HV, rows = 32 * HV;       // halves of a tile, rows of a tile
