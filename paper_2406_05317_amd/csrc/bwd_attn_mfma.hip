@@ -272,7 +272,7 @@ struct Kv {
 template <int PARTS>
 __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd_attn_kv_k(BwdAttnArgs g) {
   using X = Kv<PARTS>;
-  constexpr int TR = X::rows, VL = X::VL, KL = X::KL, CG = PARTS == 2 ? 1 : 1;
+  constexpr int TR = X::rows, VL = X::VL, KL = X::KL;
   extern __shared__ __align__(16) unsigned char smem[];       // [2][tiles], fragments, [2][3][rows] statistics
   const AttnArgs& a = g.a;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
@@ -426,12 +426,11 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
       scores();
       request(1);
       pin();
-      bf16x8 ring[2 * CG];
+      bf16x8 ring[2];
       auto read_o = [&](int i) {            // fragment i: column block i % 4 of part i / 4 % PARTS, rows 16 (i / 4 / PARTS) ..
-        if (i < 8 * PARTS) ring[i % (2 * CG)] = transposed(q0 + (1 + i / 4 % PARTS) * X::tile + i / 4 / PARTS * 16 * 256, i % 4);
+        if (i < 8 * PARTS) ring[i % 2] = transposed(q0 + (1 + i / 4 % PARTS) * X::tile + i / 4 / PARTS * 16 * 256, i % 4);
       };
-#pragma unroll
-      for (int i = 0; i < CG; ++i) read_o(i);
+      read_o(0);
       float p[16];
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
@@ -443,16 +442,12 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
       hide(p);
       bf16x8 part[PARTS];
 #pragma unroll
-      for (int i0 = 0; i0 < 8 * PARTS; i0 += CG) {
-        const int u = i0 / 4 % PARTS;
-        if (i0 % (4 * PARTS) == 0) split_parts<PARTS>(p + i0 / 4 / PARTS * 8, part);
-#pragma unroll
-        for (int i = i0; i < i0 + CG; ++i) read_o(i + CG);
+      for (int i = 0; i < 8 * PARTS; ++i) {
+        if (i % (4 * PARTS) == 0) split_parts<PARTS>(p + i / 4 / PARTS * 8, part);
+        read_o(i + 1);
         pin();
 #pragma unroll
-        for (int v = 0; u + v < PARTS; ++v)
-#pragma unroll
-          for (int i = i0; i < i0 + CG; ++i) av[i % 4] = mfma32(ring[i % (2 * CG)], part[v], av[i % 4]);
+        for (int v = 0; i / 4 % PARTS + v < PARTS; ++v) av[i % 4] = mfma32(ring[i % 2], part[v], av[i % 4]);
         pin();
       }
 #pragma unroll
@@ -460,10 +455,9 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
       pin();
       if (X::HV == 1 || !half) weights_grad();
       auto read_q = [&](int i) {
-        if (i < 8) ring[i % (2 * CG)] = transposed(q0 + i / 4 * 16 * 256, i % 4);
+        if (i < 8) ring[i % 2] = transposed(q0 + i / 4 * 16 * 256, i % 4);
       };
-#pragma unroll
-      for (int i = 0; i < CG; ++i) read_q(i);
+      read_q(0);
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
         const f32x4 dd = *(const f32x4*)(st + 2 * TR + gi * 8);
@@ -472,15 +466,12 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
       }
       hide(p);                              // (again, so that a query that is no number stays out of later keys' gradients)
 #pragma unroll
-      for (int i0 = 0; i0 < 8; i0 += CG) {
-        if (i0 % 4 == 0) split_parts<PARTS>(p + i0 / 4 * 8, part);
-#pragma unroll
-        for (int i = i0; i < i0 + CG; ++i) read_q(i + CG);
+      for (int i = 0; i < 8; ++i) {
+        if (i % 4 == 0) split_parts<PARTS>(p + i / 4 * 8, part);
+        read_q(i + 1);
         pin();
 #pragma unroll
-        for (int u = 0; u < PARTS; ++u)
-#pragma unroll
-          for (int i = i0; i < i0 + CG; ++i) ak[i % 4] = mfma32(ring[i % (2 * CG)], part[u], ak[i % 4]);
+        for (int u = 0; u < PARTS; ++u) ak[i % 4] = mfma32(ring[i % 2], part[u], ak[i % 4]);
         pin();
       }
     }
