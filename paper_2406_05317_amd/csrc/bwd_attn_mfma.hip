@@ -19,7 +19,7 @@
 // 90 000 cycles 14 000 went by before its first product and 20 000 in its stores, and the kinds waited for each other 1 800 of
 // 8 200 a tile.  One such workgroup with both sums in every wave still took 2.7 ms.
 // D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.
-#include <type_traits>
+#include <algorithm>
 
 #include "lococo_internal.h"
 #include "mfma_util.h"
@@ -256,24 +256,25 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
 }
 
 // A wave accumulates dYk and dYv of 32 keys: 128 of its 256 registers are sums, so key and value fragments lie in LDS in part,
-// in fragment order: as many as it takes to spill none (a reload waits for the tiles requested before it).
-// With two parts a workgroup is four waves that walk tiles of 32 rows, and two workgroups share a compute unit: one's first
-// loads and last stores, a third of its life, fall beside the other's products.  With three the tiles leave no room for two:
-// eight waves walk tiles of 64 rows, two per group of keys, one for either half of a tile, and add up at the end (as fast as with
-// a wave for either sum: 58 and 60 us on a block of 154 tokens).
-template <int PARTS>
+// in fragment order: as many as it takes to spill none (a reload waits for the tiles requested before it).  The rows of all heads
+// are walked in tiles of 32.
+// HV 1: a workgroup is four waves, one per 32 keys, and two share a compute unit: one's first loads and last stores, a third of
+// its life, fall beside the other's products.
+// HV 2: eight waves, two per 32 keys that take every second tile and add up at the end: half as many tiles in series, for launches
+// that leave compute units idle, and the form of three parts, whose tiles leave no room for two workgroups.
+template <int PARTS, int HV>
 struct Kv {
-  static constexpr int HV = PARTS == 2 ? 1 : 2, waves = 4 * HV, rows = 32 * HV;       // halves of a tile, rows of a tile
-  static constexpr int tile = rows * 256, set = (1 + PARTS) * tile;                   // tiles of q | parts of dO
-  static constexpr int VL = 4, KL = 3;                        // k steps whose value, key fragments are in LDS
-  static constexpr int f_at = 2 * set, st_at = f_at + (VL + KL) * 4 * 1024, lds = st_at + 2 * 3 * rows * 4;
-  static_assert(lds <= 80 * 1024 * HV && (HV == 1 || lds >= 8 * 64 * 64 * 4), "tiles, fragments, statistics; sums handed over");
+  static constexpr int tile = 32 * 256, set = HV * (1 + PARTS) * tile;                // [half] tiles of q | parts of dO
+  static constexpr int VL = PARTS == 2 && HV == 2 ? 5 : 4, KL = 3;       // k steps whose value, key fragments are in LDS
+  static constexpr int f_at = 2 * set, st_at = f_at + (VL + KL) * 4 * 1024, end = st_at + 2 * HV * 3 * 32 * 4;
+  static constexpr int sums = HV == 1 ? 0 : 8 * 64 * 64 * 4, lds = end > sums ? end : sums;   // (handed over behind the walk)
+  static_assert(lds <= 80 * 1024 * HV, "two workgroups of four waves, one of eight");
 };
-template <int PARTS>
-__global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd_attn_kv_k(BwdAttnArgs g) {
-  using X = Kv<PARTS>;
-  constexpr int TR = X::rows, VL = X::VL, KL = X::KL;
-  extern __shared__ __align__(16) unsigned char smem[];       // [2][tiles], fragments, [2][3][rows] statistics
+template <int PARTS, int HV>
+__global__ __launch_bounds__(256 * HV, 2) void bwd_attn_kv_k(BwdAttnArgs g) {
+  using X = Kv<PARTS, HV>;
+  constexpr int VL = X::VL, KL = X::KL;
+  extern __shared__ __align__(16) unsigned char smem[];       // [2][HV] tiles, fragments, [2][HV][3][32] statistics
   const AttnArgs& a = g.a;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
   float* st_lds = (float*)(smem + X::st_at);
@@ -287,38 +288,46 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l31 = l & 31, lh = l >> 5;
   const int kg = w & 3, half = w >> 2;
   const int wj = j0 + 32 * kg, j = wj + l31;                  // this lane's position in [cache ; block]
-  const int first = j0 >= s.m ? (j0 - s.m) / TR : 0;          // tiles of rows before it see none of the keys
-  const int rtiles = (s.Bn + TR - 1) / TR - first, N = a.group * rtiles;
+  const int first = j0 >= s.m ? (j0 - s.m) / 32 : 0;          // tiles of rows before it see none of the keys
+  const int rtiles = (s.Bn + 31) / 32 - first, N = (a.group * rtiles + HV - 1) / HV;
   const int64_t plane = (int64_t)a.batch * a.Hq * a.L;
 
-  // requests tile u (q, then the parts of dO) of the rows that come next, behind the last of them the walk moves on
+  // requests tile u (q, then the parts of dO) of this half's next rows, behind the last of them the walk moves on
   float stat = 0.f;
-  int rn = 0, hn = 0, buf = 0;
+  int rn = half, hn = 0, buf = 0;           // these rows: tile `first + rn` of head hn
+  auto wrap = [&](int& r, int& h) {
+#pragma unroll
+    for (int i = 0; i < HV; ++i)
+      if (r >= rtiles) { r -= rtiles; ++h; }
+  };
+  wrap(rn, hn);
+  int rt = rn, ht = hn;                     // the rows whose products come next
   auto request = [&](int u) {
     if (hn >= a.group) return;
     int l = tid & 63;
     asm volatile("" : "+v"(l));             // (offsets are worked out again every time, not kept in registers)
-    const int hq = hkv * a.group + hn, r0 = (first + rn) * TR;
-    const uint32_t lds = lds0 + buf * X::set + u * X::tile;
+    const int hq = hkv * a.group + hn, r0 = (first + rn) * 32;
+    const uint32_t lds = lds0 + buf * X::set + (half * (1 + PARTS) + u) * X::tile;
     const uint16_t* hl = g.do_hl + (((int64_t)b * a.Hq + hq) * a.L + s.start) * kOrow;
     const u32x4 rs = u == 0 ? rows_rsrc((const uint16_t*)a.q.p + b * a.q.sb + hq * a.q.sh + s.start * a.q.st, s.Bn, a.q.st * 2)
                             : make_rsrc(hl, (uint32_t)s.Bn * (kOrow * 2u));
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int r4 = w * 2 + i, r = r4 * 4 + (l >> 4), c = ((l & 15) ^ swz(r)) << 4;
+      const int r4 = kg * 2 + i, r = r4 * 4 + (l >> 4), c = ((l & 15) ^ swz(r)) << 4;
       load_to_lds(rs, lds + r4 * 1024, u == 0 ? (r0 + r) * (uint32_t)(a.q.st * 2) + c : (r0 + r) * (kOrow * 2) + (u - 1) * 256 + c);
     }
-    if (u == 0 && tid < 3 * TR) {
-      const int r = r0 + tid % TR;
-      stat = r < s.Bn ? g.stats[tid / TR * plane + ((int64_t)b * a.Hq + hq) * a.L + s.start + r] : 0.f;
+    if (u == 0 && (tid & 255) < 96) {
+      const int r = r0 + tid % 32;
+      stat = r < s.Bn ? g.stats[(tid & 255) / 32 * plane + ((int64_t)b * a.Hq + hq) * a.L + s.start + r] : 0.f;
     }
     if (u == PARTS) {
       buf ^= 1;
-      if (++rn == rtiles) { rn = 0; ++hn; }
+      rn += HV;
+      wrap(rn, hn);
     }
   };
   auto publish_stats = [&](int at) {
-    if (tid < 3 * TR) st_lds[at * 3 * TR + tid] = stat;
+    if ((tid & 255) < 96) st_lds[(at * HV + half) * 96 + (tid & 255)] = stat;
   };
 #pragma unroll
   for (int u = 0; u <= PARTS; ++u) request(u);
@@ -336,10 +345,10 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
     for (int ks = KL; ks < 8; ++ks) fk[ks] = *(const bf16x8*)(kp + ks * 16);
 #pragma unroll
     for (int ks = VL; ks < 8; ++ks) fv[ks] = *(const bf16x8*)(vp + ks * 16);
-    if (X::HV == 1 || half == 0)
+    if (HV == 1 || half == 0)
 #pragma unroll
       for (int ks = 0; ks < VL; ++ks) *(bf16x8*)(vf + ks * 4096) = *(const bf16x8*)(vp + ks * 16);
-    if (X::HV == 1 || half == 1)
+    if (HV == 1 || half == 1)
 #pragma unroll
       for (int ks = 0; ks < KL; ++ks) *(bf16x8*)(kf + ks * 4096) = *(const bf16x8*)(kp + ks * 16);
   }
@@ -364,15 +373,16 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
   publish_stats(0);
   __syncthreads();
 
-  for (int it = 0, rt = 0; it < N; ++it) {
+  for (int it = 0; it < N; ++it) {
     request(0);
-    const int rb = (first + rt) * TR + half * 32;
-    if (++rt == rtiles) rt = 0;
-    const float* st = st_lds + (it & 1) * 3 * TR + half * 32 + lh * 4;
-    const bool seen = rb < s.Bn && !(wj >= s.m && rb + 31 < wj - s.m);      // else no row of this half sees these keys
+    const int rb = (first + rt) * 32;
+    const float* st = st_lds + ((it & 1) * HV + half) * 96 + lh * 4;
+    const bool seen = ht < a.group && !(wj >= s.m && rb + 31 < wj - s.m);   // else there is no row that sees these keys
+    rt += HV;
+    wrap(rt, ht);
     if (seen) {
       asm volatile("" : "+v"(row0), "+v"(tr0[0]), "+v"(tr0[1]));       // (or the xors are kept in registers of their own)
-      const unsigned char* q0 = smem + (it & 1) * X::set + half * 32 * 256;
+      const unsigned char* q0 = smem + (it & 1) * X::set + half * (1 + PARTS) * X::tile;
       const bool hidden = rb + 31 >= s.Bn || (wj + 31 >= s.m && rb < wj + 31 - s.m);
       auto hide = [&](float (&p)[16]) {     // pairs of a key and a query that does not see it
         if (hidden) {
@@ -422,7 +432,7 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
         }
         pin();
       };
-      if (X::HV == 2 && half) weights_grad();             // (the two waves of a SIMD: one's products beside the other's exponentials)
+      if (HV == 2 && half) weights_grad();             // (the two waves of a SIMD: one's products beside the other's exponentials)
       scores();
       request(1);
       pin();
@@ -434,7 +444,7 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
       float p[16];
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
-        const f32x4 mcs = *(const f32x4*)(st + gi * 8), inv = *(const f32x4*)(st + TR + gi * 8);
+        const f32x4 mcs = *(const f32x4*)(st + gi * 8), inv = *(const f32x4*)(st + 32 + gi * 8);
 #pragma unroll
         for (int e = 0; e < 4; ++e) p[gi * 4 + e] = __builtin_amdgcn_exp2f(fmaf(sc[gi * 4 + e], c, -mcs[e])) * inv[e];
         if (PARTS == 3 && gi == 1) pin();   // (registers)
@@ -453,14 +463,14 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
 #pragma unroll
       for (int u = 2; u <= PARTS; ++u) request(u);
       pin();
-      if (X::HV == 1 || !half) weights_grad();
+      if (HV == 1 || !half) weights_grad();
       auto read_q = [&](int i) {
         if (i < 8) ring[i % 2] = transposed(q0 + i / 4 * 16 * 256, i % 4);
       };
       read_q(0);
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi) {
-        const f32x4 dd = *(const f32x4*)(st + 2 * TR + gi * 8);
+        const f32x4 dd = *(const f32x4*)(st + 64 + gi * 8);
 #pragma unroll
         for (int e = 0; e < 4; ++e) p[gi * 4 + e] *= (dp[gi * 4 + e] - dd[e]) * a.scale;
       }
@@ -488,7 +498,7 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
   auto quad = [](const f32x16 (&x)[4], int i) {
     return f32x4{x[i >> 2][(i & 3) * 4], x[i >> 2][(i & 3) * 4 + 1], x[i >> 2][(i & 3) * 4 + 2], x[i >> 2][(i & 3) * 4 + 3]};
   };
-  if constexpr (X::HV == 1) {
+  if constexpr (HV == 1) {
     float* const ko = (j < s.m ? g.d_ck + (((int64_t)n * a.batch * a.Hkv + chain) * a.M + j) * kD
                                : g.d_k + b * g.k_sb + hkv * g.k_sh + (s.start + j - s.m) * kD) + lh * 4;
     if (j < Tn)
@@ -520,21 +530,37 @@ __global__ __launch_bounds__(Kv<PARTS>::waves * 64, PARTS == 2 ? 2 : 1) void bwd
 
 }  // namespace
 
+template <int PARTS, int HV>
+static hipError_t launch_kv(const BwdAttnArgs& g, int64_t grid, hipStream_t s) {
+  constexpr int lds = Kv<PARTS, HV>::lds;
+  static bool attr_set = false;   // benign race: setting it twice is harmless
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_kv_k<PARTS, HV>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((bwd_attn_kv_k<PARTS, HV>), dim3((unsigned)grid), dim3(256 * HV), lds, s, g);
+  return hipGetLastError();
+}
+
 template <int PARTS>
 static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
   const AttnArgs& a = g.a;
-  constexpr int lds_q = 4 * kTile, lds_kv = Kv<PARTS>::lds;
+  constexpr int lds_q = 4 * kTile;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)bwd_attn_kv_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_kv);
+    const hipError_t e = hipFuncSetAttribute((const void*)bwd_attn_q_k<PARTS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_q);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
   hipLaunchKernelGGL(bwd_attn_q_k<PARTS>, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
-  const int ktiles = (a.M + a.B + 127) / 128;
-  hipLaunchKernelGGL(bwd_attn_kv_k<PARTS>, dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(Kv<PARTS>::waves * 64), lds_kv, s, g);
-  return hipGetLastError();
+  // Two waves per group of keys where the workgroups find a compute unit each and have four tiles or more to walk (one step, us,
+  // four waves and eight: 8 key heads of 32 query heads, 128 tokens on 256 keys 48.0 and 34.0, 16 on 144 18.2 and 16.3; 32 heads,
+  // 128 tokens 19.2 and 17.0, 96 15.7 and 15.7, 32 10.6 and 12.5; 64 chains, 512 tokens, two workgroups a compute unit 71 and 83).
+  const int64_t grid = (int64_t)((a.M + a.B + 127) / 128) * a.batch * a.Hkv * a.n_seg;
+  const int64_t rows = std::min<int64_t>(a.B, a.L - (int64_t)a.seg_first * a.B);
+  if (PARTS == 2 && (grid > cu_count() || a.group * ((rows + 31) / 32) < 4)) return launch_kv<2, 1>(g, grid, s);
+  return launch_kv<PARTS, 2>(g, grid, s);
 }
 
 hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {

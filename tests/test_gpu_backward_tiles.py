@@ -77,6 +77,44 @@ def test_gradients_on_the_tiles_that_pad_least(case):
 
 
 @pytest.mark.parametrize("case", [
+    # (tiles of 32 rows of all heads of a group; two waves per 32 keys from four of them on)
+    dict(kv=2, group=4, M=128, B=16),                      # four heads of a tile each
+    dict(kv=1, group=5, M=60, B=20),                       # five: one wave of the two ends a tile earlier
+    dict(kv=2, group=1, M=128, B=128),                     # keys of the block see four tiles, three, two, one
+    dict(kv=1, group=1, M=128, B=100),                     # a last tile of four rows
+    dict(kv=2, group=3, M=32, B=96),                       # nine tiles, all keys in one workgroup
+    dict(kv=1, group=2, M=500, B=260),                     # a last workgroup of keys that is mostly empty
+    dict(kv=1, group=3, M=96, B=32),                       # three tiles: one wave per 32 keys
+    dict(kv=2, group=1, M=128, B=1),                       # three parts, nothing for the second wave
+    dict(kv=1, group=5, M=61, B=20),                       # three parts, five tiles
+    dict(kv=1, group=3, M=33, B=65),                       # three parts, nine tiles
+], ids=str)
+def test_key_and_value_gradients_of_launches_that_leave_compute_units_idle(case):
+    """Against the shape-agnostic fp32 kernels.  Two parts: 16 bits kept of dO, P and dS, at most two such roundings of 2^-17 in a
+    product: 1.6e-5; three parts: nothing lost, fp32 sums of up to 1300 terms in another order."""
+    h, gr, M, B = (case[n] for n in ("kv", "group", "M", "B"))
+    g = torch.Generator(device=DEV).manual_seed(13)
+    q = _rnd(g, 1, h * gr, B, 128, sd=1.0)
+    k, v, ck, cv = (_rnd(g, 1, h, n, 128, sd=1.0) for n in (B, B, M, M))
+    cw = _rnd(g, M, 128, 3, sd=0.05)
+    d_o = _rnd(g, *q.shape, sd=1.0, dtype=torch.float32)
+    no_grad = torch.zeros(ck.shape, device=DEV)            # of the new state: only the attention's part is left
+    got = []
+    for impl in (lb.LOCOCO_IMPL_AUTO, lb.LOCOCO_IMPL_GENERIC):
+        cfg = lb.make_config(dtype=torch.bfloat16, batch=1, n_q_heads=h * gr, n_kv_heads=h, head_dim=128, M=M, conv_width=3, impl=impl)
+        cache = lb.Cache(cfg, DEV)
+        cache.load(ck, cv, M)
+        out = [torch.full_like(t, float("nan"), dtype=torch.float32) for t in (q, k, v, ck, cv)]
+        ws = torch.full((lb.lococo_backward_workspace_bytes(cfg, B, M),), 0xff, dtype=torch.uint8, device=DEV)
+        lb.lococo_segment_step_backward(cfg, q, k, v, cw, None, cache, d_o, no_grad, no_grad, *out, torch.zeros_like(cw, dtype=torch.float32),
+                                        None, ws)
+        got.append(out)
+    bound = 1.6e-5 if (M + B) % 4 == 0 else 1e-6
+    for name, a, want in zip(("d_q", "d_k", "d_v", "d_cache_k", "d_cache_v"), *got):
+        assert _rel(a, want) < bound, (name, _rel(a, want))
+
+
+@pytest.mark.parametrize("case", [
     dict(batch=1, n_kv_heads=2, M=64, B=48, L=300),                                # pairs of workgroups; a fill, a ragged block
     dict(batch=1, n_kv_heads=2, M=96, B=96, L=481, conv_width=21, norm=1, bias=True),   # last block of one token
     dict(batch=2, n_kv_heads=32, M=96, B=64, L=320),                               # a workgroup per chain and 32 slots
