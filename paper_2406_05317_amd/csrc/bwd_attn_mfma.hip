@@ -259,13 +259,16 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
 // in fragment order: as many as it takes to spill none (a reload waits for the tiles requested before it).  The rows of all heads
 // are walked in tiles of 32.
 // HV 1: a workgroup is four waves, one per 32 keys, and two share a compute unit: one's first loads and last stores, a third of
-// its life, fall beside the other's products.
+// its life, fall beside the other's products.  (Three parts: fewer fragments find room in LDS, and dP's operands are read one
+// product ahead instead of two for it.  4097 tokens in blocks of 303 on 687 keys, 32 heads: 371 us, with eight waves 440; 1528 in blocks
+// of 191 on 383, 128 heads: 282 and 358.)
 // HV 2: eight waves, two per 32 keys that take every second tile and add up at the end: half as many tiles in series, for launches
-// that leave compute units idle, and the form of three parts, whose tiles leave no room for two workgroups.
+// that leave compute units idle.
 template <int PARTS, int HV>
 struct Kv {
   static constexpr int tile = 32 * 256, set = HV * (1 + PARTS) * tile;                // [half] tiles of q | parts of dO
-  static constexpr int VL = PARTS == 2 && HV == 2 ? 5 : 4, KL = 3;       // k steps whose value, key fragments are in LDS
+  // k steps whose value, key fragments are in LDS
+  static constexpr int VL = HV == 1 ? (PARTS == 2 ? 4 : 0) : (PARTS == 2 ? 5 : 4), KL = 3;
   static constexpr int f_at = 2 * set, st_at = f_at + (VL + KL) * 4 * 1024, end = st_at + 2 * HV * 3 * 32 * 4;
   static constexpr int sums = HV == 1 ? 0 : 8 * 64 * 64 * 4, lds = end > sums ? end : sums;   // (handed over behind the walk)
   static_assert(lds <= 80 * 1024 * HV, "two workgroups of four waves, one of eight");
@@ -415,20 +418,21 @@ __global__ __launch_bounds__(256 * HV, 2) void bwd_attn_kv_k(BwdAttnArgs g) {
         pin();
       };
       auto weights_grad = [&]() {
-        bf16x8 ring[3], rv[2];
+        constexpr int R = PARTS == 3 && HV == 1 ? 2 : 3;
+        bf16x8 ring[R], rv[2];
         auto read = [&](int i) {            // product i: part i % PARTS of k step i / PARTS
           const int ks = i / PARTS;
-          ring[i % 3] = *(const bf16x8*)(q0 + (1 + i % PARTS) * X::tile + (row0 ^ (ks << 5)));
+          ring[i % R] = *(const bf16x8*)(q0 + (1 + i % PARTS) * X::tile + (row0 ^ (ks << 5)));
           if (i % PARTS == 0) rv[ks % 2] = ks < VL ? *(const bf16x8*)(vf + ks * 4096) : fv[ks];
         };
         dp = zero16();
-        read(0);
-        read(1);
+#pragma unroll
+        for (int i = 0; i < R - 1; ++i) read(i);
 #pragma unroll
         for (int i = 0; i < 8 * PARTS; ++i) {
-          if (i + 2 < 8 * PARTS) read(i + 2);
+          if (i + R - 1 < 8 * PARTS) read(i + R - 1);
           pin();
-          dp = mfma32(ring[i % 3], rv[i / PARTS % 2], dp);
+          dp = mfma32(ring[i % R], rv[i / PARTS % 2], dp);
         }
         pin();
       };
@@ -530,8 +534,35 @@ __global__ __launch_bounds__(256 * HV, 2) void bwd_attn_kv_k(BwdAttnArgs g) {
 
 }  // namespace
 
+// block n of a window: live slots before it, tokens
+static int live_before(const AttnArgs& a, int n) { return n <= a.n_fill ? a.len0 + n * a.B : a.M; }
+static int tokens_of(const AttnArgs& a, int n) { return (int)std::min<int64_t>(a.B, a.L - (int64_t)n * a.B); }
+
+// Two waves per 32 keys where the longest walk is four tiles or more, and the workgroups fill no more than a compute unit each.
+// They are counted by what they walk, three tiles on top for loads and stores, in units of the longest: most of a block's keys are
+// seen by few of its rows.  One step, us, one wave and two: 8 key heads of 32 query heads, 128 tokens on 256 keys 48.0 and 34.0, 16
+// on 144 18.2 and 16.3; 32 heads, 128 tokens 19.2 and 17.0, 96 15.7 and 15.7, 32 10.6 and 12.5; 64 chains, 512 tokens 71 and 83;
+// three parts, 8 of 32 heads, 127 tokens on 255 keys 59 and 45; 32 heads, one token 11.8 and 13.7; 64 chains, 77 on 589 keys 30 and 38;
+// 32 chains, 514 on 1026, 288 workgroups, 76 and 53.  Over 150 steps of 160 - 700 workgroups the form not taken is at best 6 % the
+// faster one, 0.1 % on average (their plain number on either side of the compute units: 31 and 0.9 %).
+static bool two_waves(const AttnArgs& a) {
+  const int longest = a.group * ((tokens_of(a, a.seg_first) + 31) / 32);
+  if (longest < 4) return false;
+  const int64_t room = (int64_t)cu_count() * (longest + 3), chains = (int64_t)a.batch * a.Hkv;
+  int64_t work = 0;
+  for (int n = a.seg_first; n < a.seg_first + a.n_seg; ++n) {
+    const int m = live_before(a, n), Bn = tokens_of(a, n);
+    for (int j = 0; j < m + Bn; j += 128) {
+      work += chains * (a.group * ((Bn + 31) / 32 - std::max(0, (j - m) / 32)) + 3);
+      if (work > room) return false;
+    }
+  }
+  return true;
+}
+
 template <int PARTS, int HV>
-static hipError_t launch_kv(const BwdAttnArgs& g, int64_t grid, hipStream_t s) {
+static hipError_t launch_kv(const BwdAttnArgs& g, hipStream_t s) {
+  const AttnArgs& a = g.a;
   constexpr int lds = Kv<PARTS, HV>::lds;
   static bool attr_set = false;   // benign race: setting it twice is harmless
   if (!attr_set) {
@@ -539,7 +570,8 @@ static hipError_t launch_kv(const BwdAttnArgs& g, int64_t grid, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL((bwd_attn_kv_k<PARTS, HV>), dim3((unsigned)grid), dim3(256 * HV), lds, s, g);
+  const int ktiles = (a.M + a.B + 127) / 128;
+  hipLaunchKernelGGL((bwd_attn_kv_k<PARTS, HV>), dim3((unsigned)(ktiles * a.batch * a.Hkv * a.n_seg)), dim3(256 * HV), lds, s, g);
   return hipGetLastError();
 }
 
@@ -554,23 +586,14 @@ static hipError_t launch_parts(const BwdAttnArgs& g, hipStream_t s) {
     attr_set = true;
   }
   hipLaunchKernelGGL(bwd_attn_q_k<PARTS>, dim3((unsigned)(a.qtiles * a.Hq * a.batch * a.n_seg)), dim3(256), lds_q, s, g);
-  // Two waves per group of keys where the workgroups find a compute unit each and have four tiles or more to walk (one step, us,
-  // four waves and eight: 8 key heads of 32 query heads, 128 tokens on 256 keys 48.0 and 34.0, 16 on 144 18.2 and 16.3; 32 heads,
-  // 128 tokens 19.2 and 17.0, 96 15.7 and 15.7, 32 10.6 and 12.5; 64 chains, 512 tokens, two workgroups a compute unit 71 and 83).
-  const int64_t grid = (int64_t)((a.M + a.B + 127) / 128) * a.batch * a.Hkv * a.n_seg;
-  const int64_t rows = std::min<int64_t>(a.B, a.L - (int64_t)a.seg_first * a.B);
-  if (PARTS == 2 && (grid > cu_count() || a.group * ((rows + 31) / 32) < 4)) return launch_kv<2, 1>(g, grid, s);
-  return launch_kv<PARTS, 2>(g, grid, s);
+  return two_waves(a) ? launch_kv<PARTS, 2>(g, s) : launch_kv<PARTS, 1>(g, s);
 }
 
 hipError_t launch_bwd_attn_mfma(BwdAttnArgs g, hipStream_t s) {
   AttnArgs& a = g.a;
   a.qtiles = (a.B + 127) / 128;
   // runs of blocks of one form: all of them as a rule, or all but a ragged last one
-  auto parts = [&](int n) {
-    const int64_t left = a.L - (int64_t)n * a.B;
-    return g.three_parts || ((n <= a.n_fill ? a.len0 + n * a.B : a.M) + (int)(left < a.B ? left : a.B)) % 4 ? 3 : 2;
-  };
+  auto parts = [&](int n) { return g.three_parts || (live_before(a, n) + tokens_of(a, n)) % 4 ? 3 : 2; };
   const int n_all = a.n_seg;
   hipError_t e = hipSuccess;
   for (int n = 0; n < n_all && e == hipSuccess; n += a.n_seg) {

@@ -77,7 +77,7 @@ def test_gradients_on_the_tiles_that_pad_least(case):
 
 
 @pytest.mark.parametrize("case", [
-    # (tiles of 32 rows of all heads of a group; two waves per 32 keys from four of them on)
+    # (tiles of 32 rows of all heads of a group; two waves per 32 keys from four of them on where the launch fills no more than the chip)
     dict(kv=2, group=4, M=128, B=16),                      # four heads of a tile each
     dict(kv=1, group=5, M=60, B=20),                       # five: one wave of the two ends a tile earlier
     dict(kv=2, group=1, M=128, B=128),                     # keys of the block see four tiles, three, two, one
@@ -88,8 +88,10 @@ def test_gradients_on_the_tiles_that_pad_least(case):
     dict(kv=2, group=1, M=128, B=1),                       # three parts, nothing for the second wave
     dict(kv=1, group=5, M=61, B=20),                       # three parts, five tiles
     dict(kv=1, group=3, M=33, B=65),                       # three parts, nine tiles
+    dict(kv=96, group=2, M=190, B=129),                    # three parts, more workgroups than compute units: one wave again
+    dict(kv=96, group=1, M=191, B=129),                    # the same in two parts
 ], ids=str)
-def test_key_and_value_gradients_of_launches_that_leave_compute_units_idle(case):
+def test_key_and_value_gradients_by_size_of_the_launch(case):
     """Against the shape-agnostic fp32 kernels.  Two parts: 16 bits kept of dO, P and dS, at most two such roundings of 2^-17 in a
     product: 1.6e-5; three parts: nothing lost, fp32 sums of up to 1300 terms in another order."""
     h, gr, M, B = (case[n] for n in ("kv", "group", "M", "B"))
