@@ -519,16 +519,24 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
     for (int i = 0; i < D; ++i) load_tap(fw[i], tap0(sc) + min(i, KW - 1) * 1024);
   };
 
-  // plane rows: offsets inside the 32-slot planes of a chunk, of dl (with the halo) and of n
+  // plane rows: offsets inside the 32-slot planes of a chunk, of dl (with the halo) and of n.  SHARED works them out again for
+  // every request: its 128 registers hold no more than sums and fragments, and a reload from scratch memory waits for the request
+  // before it and for the filters on their way.
   uint32_t dvo[G::ND], nvo[G::NN];
   auto plane_cell = [&](int ra, int rows, int first) -> uint32_t {
+    int l = tid & 63;
+    if (G::SHARED) asm volatile("" : "+v"(l));
     const int pl = ra / rows, r = ra - pl * rows + (l >> 3), q = first + r;
     return q >= 0 && q < x.T ? (uint32_t)((pl * g.P + q) * 128 + (((l & 7) ^ pswz(r)) << 4)) : 0x80000000u;
   };
+  auto d_cell = [&](int i) { return plane_cell((w * G::ND + i) * 8, G::DR, p0 - (KW - 1) + pad); };
+  auto n_cell = [&](int i) { return plane_cell((w * G::NN + i) * 8, PT, p0); };
+  if (!G::SHARED) {
 #pragma unroll
-  for (int i = 0; i < G::ND; ++i) dvo[i] = plane_cell((w * G::ND + i) * 8, G::DR, p0 - (KW - 1) + pad);
+    for (int i = 0; i < G::ND; ++i) dvo[i] = d_cell(i);
 #pragma unroll
-  for (int i = 0; i < G::NN; ++i) nvo[i] = plane_cell((w * G::NN + i) * 8, PT, p0);
+    for (int i = 0; i < G::NN; ++i) nvo[i] = n_cell(i);
+  }
   const int64_t chain_planes = (int64_t)ch * tiles * g.P * 128;
   const unsigned char* pl = (const unsigned char*)(g.dl + blk * g.plane_stride) + chain_planes;
   const unsigned char* pn = (const unsigned char*)(g.wn + blk * g.plane_stride) + chain_planes;
@@ -540,7 +548,7 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
   auto request_d = [&](int sc) {
     const u32x4 r = planes_rsrc(pl, sc);
 #pragma unroll
-    for (int i = 0; i < G::ND; ++i) load_to_lds_at(r, ddst + (sc & 1) * G::DB + i * 1024, dvo[i], 0u);
+    for (int i = 0; i < G::ND; ++i) load_to_lds_at(r, ddst + (sc & 1) * G::DB + i * 1024, G::SHARED ? d_cell(i) : dvo[i], 0u);
   };
   // the rows of n have one place behind the two of dl; without taps they take turns in those
   const bool turns = !taps && !FINE;
@@ -548,11 +556,11 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
   auto request_n = [&](int sc) {
     const u32x4 r = planes_rsrc(pn, sc);
 #pragma unroll
-    for (int i = 0; i < G::NN; ++i) load_to_lds_at(r, ndst + n_at(sc) + i * 1024, nvo[i], 0u);
+    for (int i = 0; i < G::NN; ++i) load_to_lds_at(r, ndst + n_at(sc) + i * 1024, G::SHARED ? n_cell(i) : nvo[i], 0u);
     if (FINE) {
       const u32x4 r3 = planes_rsrc(pw, sc);
 #pragma unroll
-      for (int i = 0; i < G::NN; ++i) load_to_lds_at(r3, ndst + n_at(sc) + G::NB + i * 1024, nvo[i], 0u);
+      for (int i = 0; i < G::NN; ++i) load_to_lds_at(r3, ndst + n_at(sc) + G::NB + i * 1024, G::SHARED ? n_cell(i) : nvo[i], 0u);
     }
   };
   f32x16 acc[PB][CB];
@@ -584,17 +592,21 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
   wait_loads<0>();
   barrier();
   bf16x8 fg[GP][CB];
+  auto load_part = [&](int sc, int u, bf16x8 (&f)[CB]) {
+    const unsigned char* p = gf + (int64_t)min(min(sc, nsc - 1) * KS + kq, n16 - 1) * (8 * 1024) + u * gpart;
+#pragma unroll
+    for (int c = 0; c < CB; ++c) f[c] = *(const bf16x8*)(p + c * 1024 + lane16);
+  };
   auto load_g = [&](int sc, bf16x8 (&f)[GP][CB]) {
-    const unsigned char* p = gf + (int64_t)min(min(sc, nsc - 1) * KS + kq, n16 - 1) * (8 * 1024);
 #pragma unroll
-    for (int u = 0; u < GP; ++u)
-#pragma unroll
-      for (int c = 0; c < CB; ++c) f[u][c] = *(const bf16x8*)(p + u * gpart + c * 1024 + lane16);
+    for (int u = 0; u < GP; ++u) load_part(sc, u, f[u]);
   };
   if (!G::SHARED) load_g(0, fg);
   for (int sc = 0; sc < nsc; ++sc) {
     if (taps) {
       const unsigned char* dp = smem + (sc & 1) * G::DB + (kq >> 1) * G::DR * 128;
+      int l31 = tid & 31;
+      if (G::SHARED) asm volatile("" : "+v"(l31));     // (nor are the walk's first rows kept)
       // a tap's low halves are read ahead of the products with the high ones, the next tap's high ones ahead of those with the
       // low ones; its filters are replaced by those D taps on, which at the end of a chunk are the next one's first
       bf16x8 fh[PB], fl[PB];
@@ -630,19 +642,29 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
     {
       const unsigned char* np = smem + n_at(sc) + (kq >> 1) * PT * 128;
       bf16x8 fh[PB], fl[PB], next[GP][CB];
-      if (G::SHARED) load_g(sc, fg);
-      else load_g(sc + 1, next);
+      if (G::SHARED) {
+        load_part(sc, 1, fg[1]);
+        load_part(sc, 0, fg[0]);
+      } else {
+        load_g(sc + 1, next);
+      }
       rows_at(np, l31, 0, fh);
       rows_at(np, l31, 1, fl);
-      multiply(fh, fg[0]);
-      multiply(fl, fg[0]);
       multiply(fh, fg[1]);
       // (low half x low half is below the 16 bits kept of two parts, not below the 24 of three)
       if constexpr (FINE) {
         multiply(fl, fg[1]);
+        if (G::SHARED) {                       // the third part in the place of the second
+          __builtin_amdgcn_sched_barrier(0);
+          load_part(sc, 2, fg[2]);
+        }
+      }
+      multiply(fh, fg[0]);
+      multiply(fl, fg[0]);
+      if constexpr (FINE) {
+        rows_at(np + G::NB, l31, 0, fl);       // the third part, [third | first]
+        multiply(fl, fg[0]);
         multiply(fh, fg[2]);
-        rows_at(np + G::NB, l31, 0, fh);       // the third part, [third | first]
-        multiply(fh, fg[0]);
       }
       if (!G::SHARED)
 #pragma unroll
@@ -1020,7 +1042,7 @@ template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   // The largest tile of which there is one for every compute unit.  128 rows have one to themselves, 64 share it by two (32 chains,
   // 512 slots on 1024 positions: 142 and 153 us, 128 slots, 27 blocks of 128 rows: 175 and 179), so 64 where they leave a tenth
-  // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 594 -> 581.
+  // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 708 -> 657.
   // 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole 15.0).  The
   // slots of 32 rows go four ways, two workgroups on a compute unit: with eight, one (256 slots: 31.6 against 28.8 us; 160: 51 -
   // 39; 384: 63 - 59; three parts 71 - 66).  Halves take eight (as often faster as slower at 80 and more slots), but four where

@@ -1,6 +1,7 @@
-"""Registers of the two-role compression kernel, as the compiler reports them (CPU: nothing is run).  A SIMD holds a wave of
-either role, 256 registers each.  A build that wants more keeps the rest in scratch memory: the logit waves of width 21 then read
-addresses back in front of every walk, 1 % of a step of several chains."""
+"""Registers of the two-role compression kernel and of the backward kernels, as the compiler reports them (CPU: nothing is run).
+In the former a SIMD holds a wave of either role, 256 registers each.  A build that wants more keeps the rest in scratch memory: the
+logit waves of width 21 then read addresses back in front of every walk, 1 % of a step of several chains."""
+import os
 import re
 import shutil
 import subprocess
@@ -36,3 +37,18 @@ def test_builds_without_protected_slots_keep_everything_in_registers(tmp_path):
     spilled = [int(n) for n in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
     assert len(names) == len(spilled) == len(builds)
     assert not any(spilled), dict(zip(names, spilled))
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("source", ["bwd_attn_mfma.hip", "bwd_conv_mfma.hip"])
+def test_backward_kernels_keep_everything_in_registers(tmp_path, source):
+    """A reload from scratch memory inside their loops waits for every load on its way: the tiles, rows and filters requested ahead."""
+    r = subprocess.run(["hipcc", "-x", "hip", *lib_build.FLAGS, *lib_build.EXTRA[source], "--cuda-device-only", "-c",
+                        os.path.join(lib_build.CSRC, source), "-o", str(tmp_path / "bwd.o"), "-Rpass-analysis=kernel-resource-usage"],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    names = re.findall(r"Function Name: (\S+)", r.stderr)
+    spilled = [int(n) for n in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
+    scratch = [int(n) for n in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
+    assert names and len(names) == len(spilled) == len(scratch)
+    assert not any(spilled) and not any(scratch), dict(zip(names, zip(spilled, scratch)))
