@@ -110,18 +110,22 @@ __device__ __forceinline__ float exp_neg(float x) {
 
 // ---- G, Eq. 6 and its gradient: a workgroup per (chain, 32 slots), all positions, eight waves of NT 32-position tiles
 // each; the rows of a step stay in registers from the logits to dl.  Bound by memory in turns, one workgroup filling a compute
-// unit: the logits in (64 MB a step of 32 chains, 512 slots, 1024 positions), the entries from the L2 (512 KB a workgroup), the
-// planes out (134 MB): 66 us a step, 13.2 us with 128 slots on 256 positions; as five kernels with fp32 arrays in memory between
-// them 250 us.  Entries and planes go through LDS, 4 KB of a wave's own, so that an instruction covers whole lines: with
+// unit from 257 positions on: the logits in (64 MB a step of 32 chains, 512 slots, 1024 positions), the entries from the L2 (512 KB a
+// workgroup), the planes out (134 MB): 66 us a step; as five kernels with fp32 arrays in memory between them 250 us.  Up to 256
+// positions two share it (128 slots on 256: 13.0 us for 128 workgroups, 22.8 for 512; three parts, 253 positions, 512: 25.6, alone on
+// a compute unit 32.0).  Entries and planes go through LDS, 4 KB of a wave's own, so that an instruction covers whole lines: with
 // fragments straight from memory and 16 bytes a lane straight to it, 32 lines an instruction in quarters, 83 and 14.8 us.
 // MULTI: more positions than that: they are walked twice in chunks, first for the row sums alone.
 template <int NT, bool MULTI, int NORM, int PARTS>
 __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   const StepArgs& a = g.st;
-  __shared__ __align__(16) unsigned char Gs[PARTS][2][32 * 256];     // [part][keys, values]: tiles of 32 rows (see swz)
+  // [part][keys, values]: tiles of 32 rows of g (see swz)
+  __shared__ __align__(16) unsigned char Gs[PARTS * 2 + (MULTI ? 1 : 0)][32 * 256];
   __shared__ __align__(16) unsigned char Xs[8][32 * 128];        // a wave's own: 32 rows of 128 bytes (see pswz)
-  __shared__ __align__(16) float red[2][8][32];
-  __shared__ __align__(16) float row_s[3][32];                   // reference, 1 / sum, sum n G
+  // Results of a row in what is idle then: a wave's own in its rows, between the products and the planes; those of all waves
+  // (reference, 1 / sum, sum n G) in place of g, behind the barrier after the products, or behind g where more products come.
+  // (Three parts, 80 KB: two workgroups to a compute unit with one tile a wave.)
+  float* const row_s = (float*)Gs[MULTI ? PARTS * 2 : 0];
   const Block x = block_of(g, blk);
   const int tiles = (a.M + 31) / 32, item = xcd_item(blockIdx.x, gridDim.x);
   const int sb = item % tiles, ch = item / tiles, s0 = sb * 32, hkv = ch % a.Hkv;
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
     split_parts<PARTS>(v, part);
     const int at = r * 256 + (((c8 & 15) ^ swz(r)) << 4);
 #pragma unroll
-    for (int u = 0; u < PARTS; ++u) *(bf16x8*)(Gs[u][val] + at) = part[u];
+    for (int u = 0; u < PARTS; ++u) *(bf16x8*)(Gs[u * 2 + val] + at) = part[u];
   }
   int ga[8];
 #pragma unroll
@@ -238,7 +242,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 #pragma unroll
       for (int u = 0; u < PARTS; ++u)
         *(bf16x8*)(gsp + ((((int64_t)u * a.batch * a.Hkv + ch) * tiles * 2 + sb * 2 + h) * 8 + w) * 512 + l * 8) =
-            frag_tr(Gs[u][w >> 2] + at, Gs[u][w >> 2] + at4);
+            frag_tr(Gs[u * 2 + (w >> 2)] + at, Gs[u * 2 + (w >> 2)] + at4);
     }
   }
 
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
           for (int k = 0; k < 4; ++k) {
             const bf16x8 f = *(const bf16x8*)(xs + (by_pos ^ k << 5));
 #pragma unroll
-            for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs[u][val] + ga[4 * h + k]), f, acc[n]);
+            for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs[u * 2 + val] + ga[4 * h + k]), f, acc[n]);
           }
           wave_sync();
         }
@@ -275,18 +279,21 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   auto over_waves = [&](const f32x16& v, int which, auto mx) {
     const float t = over32<decltype(mx)::value>(v, l31);
     const int i = l31 >> 1;
-    red[which][w][(i >> 2) * 8 + lh * 4 + (i & 3)] = t;          // (two lanes hold the same)
+    ((float*)xs)[which * 32 + (i >> 2) * 8 + lh * 4 + (i & 3)] = t;          // (two lanes hold the same)
   };
   auto collect = [&](int which, bool mx) {
-    float t = red[which][0][tid];
-    for (int k = 1; k < 8; ++k) t = mx ? fmaxf(t, red[which][k][tid]) : t + red[which][k][tid];
+    float t = ((const float*)Xs[0])[which * 32 + tid];
+    for (int k = 1; k < 8; ++k) {
+      const float o = ((const float*)Xs[k])[which * 32 + tid];
+      t = mx ? fmaxf(t, o) : t + o;
+    }
     return t;
   };
   f32x16 rv;
   auto rows = [&](int which) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const f32x4 t = *(const f32x4*)&row_s[which][q * 8 + lh * 4];
+      const f32x4 t = *(const f32x4*)(row_s + which * 32 + q * 8 + lh * 4);
 #pragma unroll
       for (int e = 0; e < 4; ++e) rv[q * 4 + e] = t[e];
     }
@@ -311,7 +318,7 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
         }
         ref = t;
         // (a chunk whose positions are all protected: nothing to refer to yet, and -inf - -inf is no number)
-        row_s[0][tid] = MULTI && t == -INFINITY ? 0.f : t;
+        row_s[tid] = MULTI && t == -INFINITY ? 0.f : t;
       }
       __syncthreads();
       rows(0);
@@ -337,8 +344,8 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
   auto publish = [&]() {
     if (tid < 32) {
       const float inv = 1.0f / (NORM == 0 ? sum : sum + a.eps);
-      row_s[1][tid] = inv;
-      row_s[2][tid] = dot * inv;
+      row_s[32 + tid] = inv;
+      row_s[64 + tid] = dot * inv;
     }
     __syncthreads();
   };

@@ -52,3 +52,7 @@ def test_backward_kernels_keep_everything_in_registers(tmp_path, source):
     scratch = [int(n) for n in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
     assert names and len(names) == len(spilled) == len(scratch)
     assert not any(spilled) and not any(scratch), dict(zip(names, zip(spilled, scratch)))
+    # one tile a wave: two workgroups of eight waves to a compute unit, registers and LDS allowing
+    waves = dict(zip(names, (int(n) for n in re.findall(r"Occupancy \[waves/SIMD\]: (\d+)", r.stderr))))
+    rows = {n: w for n, w in waves.items() if "bwd_rows_kILi1ELb0E" in n}
+    assert len(rows) == (4 if source == "bwd_conv_mfma.hip" else 0) and all(w >= 4 for w in rows.values()), rows
