@@ -1052,14 +1052,18 @@ static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int
   // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 708 -> 657.
   // 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole 15.0).  The
   // slots of 32 rows go four ways, two workgroups on a compute unit: with eight, one (256 slots: 31.6 against 28.8 us; 160: 51 -
-  // 39; 384: 63 - 59; three parts 71 - 66).  Halves take eight (as often faster as slower at 80 and more slots), but four where
-  // that leaves an eighth less of the slots to pad (192 slots: 24.4 -> 22.1 us; 320: 30.8 -> 29.7).
-  const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk;
-  const int64_t rows128 = ((int64_t)rows + 127) / 128 * 128, rows64 = ((int64_t)rows + 63) / 64 * 64;
-  const bool four_ways = (g.st.M + 63) / 64 * 64 * 9 <= (g.st.M + 127) / 128 * 128 * 8;
+  // 39; 384: 63 - 59; three parts 71 - 66).
+  const int64_t per = (int64_t)g.st.batch * g.st.Hkv * n_blk, slots = g.st.M;
+  const int64_t rows128 = ((int64_t)rows + 127) / 128 * 128, rows64 = ((int64_t)rows + 63) / 64 * 64, halves = per * ((rows + 31) / 32) * 4;
   if (per * (rows128 / 128) >= cu_count() && rows128 * 10 <= rows64 * 11) return launch_dx<128, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
   if (per * (rows64 / 64) >= cu_count()) return launch_dx<64, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
   if (per * ((rows + 31) / 32) >= cu_count()) return launch_dx<32, 128, 4, FINE>(g, blk0, n_blk, part, rows, s);
+  // Halves go eight ways, half as many phases in series, but four ways where that leaves an eighth less of the slots to pad and
+  // there are workgroups enough to fill each other's waits.  Four against eight ways, by workgroups: 192 slots 128 1.02, 256 0.99,
+  // 384 0.91 (three parts 0.99, 0.97, 0.91); 320 slots 192 1.08, 384 1.03, 576 0.96 (1.08, 1.04, 0.87); 448 slots 256 1.16, 384 1.09,
+  // 512 1.02, 768 0.98 (1.12, 1.10, 0.91, 0.91); 128 slots, nothing less to pad, 1.02 - 1.26.  Up to 64 slots half of eight have none.
+  const int64_t enough = slots <= 64 ? 0 : slots <= 192 ? cu_count() / 2 : 2 * cu_count();
+  const bool four_ways = (slots + 63) / 64 * 64 * 9 <= (slots + 127) / 128 * 128 * 8 && halves >= enough;
   return four_ways ? launch_dx<32, 64, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
 }
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {

@@ -77,6 +77,20 @@ def test_gradients_on_the_tiles_that_pad_least(case):
 
 
 @pytest.mark.parametrize("case", [
+    # (32 rows in halves; four parts where slots and workgroups are enough)
+    dict(batch=1, n_kv_heads=3, M=200, B=40, per_head=True, conv_width=7),         # eight parts, two chunks of slots
+    dict(batch=1, n_kv_heads=2, M=253, B=33, conv_in=1, conv_width=21),            # the same in three parts, taps on both halves
+    dict(batch=1, n_kv_heads=4, M=320, B=32, conv_width=3),                        # three chunks: too few workgroups for four parts
+    dict(batch=1, n_kv_heads=8, M=192, B=64),                                      # four parts
+    dict(batch=1, n_kv_heads=8, M=190, B=3, conv_in=1, conv_width=7),              # the same in three parts
+    dict(batch=2, n_kv_heads=8, M=320, B=33, conv_width=3),                        # four parts, five chunks, three parts of n and g
+    dict(batch=2, n_kv_heads=8, M=448, B=32, conv_width=3),                        # the same in two parts, seven chunks
+], ids=str)
+def test_gradients_of_launches_in_halves(case):
+    test_input_and_filter_gradients_at_tile_edges(case)
+
+
+@pytest.mark.parametrize("case", [
     # (tiles of 32 rows of all heads of a group; two waves per 32 keys from four of them on where the launch fills no more than the chip)
     dict(kv=2, group=4, M=128, B=16),                      # four heads of a tile each
     dict(kv=1, group=5, M=60, B=20),                       # five: one wave of the two ends a tile earlier
