@@ -31,7 +31,7 @@ def _rel(a, b):
     dict(batch=1, n_kv_heads=2, M=130, B=62, conv_in=1, conv_width=21),            # [K | V] filters: taps on both halves
     dict(batch=2, n_kv_heads=32, M=128, B=384, conv_in=1),                         # the same with 128 rows
     dict(batch=1, n_kv_heads=2, M=16, B=8, conv_width=1),                          # the smallest: sixteen slots, one tap
-    # (32 rows: the slots in four parts up to 64 of them, in eight from there on)
+    # (32 rows in halves: the slots in four parts up to 64 of them, in eight above with so few workgroups; whole: always in four)
     dict(batch=1, n_kv_heads=2, M=64, B=1, conv_width=5),                          # halves in three parts, four parts of slots
     dict(batch=1, n_kv_heads=3, M=64, B=60, conv_in=1, conv_width=31),             # halves
     dict(batch=2, n_kv_heads=32, M=49, B=63, conv_width=15),                       # whole, a slot past 48
@@ -64,16 +64,48 @@ def test_input_and_filter_gradients_at_tile_edges(case):
 
 
 @pytest.mark.parametrize("case", [
-    dict(batch=4, n_kv_heads=32, M=64, B=128),                                     # 64 rows: a third of two 128-row tiles is padding
+    dict(batch=4, n_kv_heads=32, M=64, B=128),                                     # 64 rows: a quarter of two 128-row tiles is padding
     dict(batch=4, n_kv_heads=32, M=65, B=122, conv_width=31),                      # the same in three parts, a row past a tile less
     dict(batch=4, n_kv_heads=32, M=64, B=65, conv_in=1, conv_width=21),            # 129 rows, taps on both halves
     dict(batch=2, n_kv_heads=32, M=160, B=32),                                     # 32 rows whole, four parts of more than 64 slots
     dict(batch=2, n_kv_heads=32, M=129, B=30, conv_width=7),                       # the same in three parts, one slot past a chunk
-    dict(batch=1, n_kv_heads=3, M=192, B=64, conv_width=31),                       # halves, four parts
+    dict(batch=1, n_kv_heads=3, M=192, B=64, conv_width=31),                       # halves, eight parts of two chunks
     dict(batch=1, n_kv_heads=2, M=190, B=3, conv_in=1),                            # the same in three parts
+    dict(batch=8, n_kv_heads=32, M=32, B=32),                                      # up to 64 rows of 256 chains: one 64-row tile each
+    dict(batch=8, n_kv_heads=32, M=33, B=22, conv_width=5),                        # the same in three parts
 ], ids=str)
 def test_gradients_on_the_tiles_that_pad_least(case):
     test_input_and_filter_gradients_at_tile_edges(case)
+
+
+@pytest.mark.parametrize("case", [
+    dict(M=64, B=48, conv_width=15),                                               # 16 chains, 20 blocks
+    dict(M=63, B=42, conv_width=7),                                                # the same in three parts
+], ids=str)
+def test_rows_of_many_short_blocks_at_once(case):
+    """The rows of all blocks of a window in one launch, 64-row tiles from 256 chains and blocks on, against windows of one block,
+    32-row tiles: the same products, fp32 sums of up to 2e3 terms in another order (3e-7 each at most, uncorrelated)."""
+    M, B, kw = case["M"], case["B"], case["conv_width"]
+    L, h = M + 20 * B, 16
+    g = torch.Generator(device=DEV).manual_seed(17)
+    q, k, v = (_rnd(g, 1, h, L, 128) for _ in range(3))
+    cw = _rnd(g, M, 128, kw, sd=0.05)
+    d_o, gk, gv = (_rnd(g, 1, h, n, 128, sd=1.0, dtype=torch.float32) for n in (L, M, M))
+    cfg = lb.make_config(dtype=torch.bfloat16, batch=1, n_q_heads=h, n_kv_heads=h, head_dim=128, M=M, conv_width=kw)
+    full = lb.lococo_sequence_backward_workspace_bytes(cfg, L, B)
+
+    def run(n_bytes):
+        out = [torch.full_like(t, float("nan"), dtype=torch.float32) for t in (q, k, v, gk, gv)]
+        d_w = torch.zeros_like(cw, dtype=torch.float32)
+        lb.lococo_sequence_backward(cfg, q, k, v, B, cw, None, lb.Cache(cfg, DEV), d_o, gk, gv, *out, d_w, None,
+                                    torch.full((n_bytes,), 0xff, dtype=torch.uint8, device=DEV))
+        return out + [d_w]
+
+    with pytest.raises(lb.LococoError, match="workspace needs") as e:
+        run(256)
+    least = int(str(e.value).split("workspace needs ")[1].split()[0])
+    for name, a, want in zip(("d_q", "d_k", "d_v", "d_cache0_k", "d_cache0_v", "d_w"), run(full), run(least)):
+        assert _rel(a, want) < 1e-5, (name, _rel(a, want))
 
 
 @pytest.mark.parametrize("case", [
