@@ -7,17 +7,18 @@
 //   bwd_attn_kv_k   a workgroup per 128 keys of [cache ; block]: dYk = dS^T q and dYv = P^T dO over the rows of all
 //                   heads of the group.
 // The fp32 operands (dO, P, dS) enter the matrix products as two bf16 halves (16 bits kept): S 1, dP 2, dq 2, dYk 2,
-// dYv 3 products; with the recomputation 14 products per (query, key) pair of 128 columns.  A block whose number of
-// positions is no multiple of 4, or a step whose gradients are not 16-byte aligned, enters with three parts (24 bits, nothing
-// lost; dP, dq, dYk 3, dYv 6 products): those have always been computed in fp32, and errors stay at that level (3e-7 against
-// 3.5e-6 with two).
-// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 4.2 ms for the whole sequence (1.9 + 2.3) against 20.0 ms as
-// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.22 against
+// dYv 3 products; with the recomputation (S and dP three times each) 16 products per (query, key) pair of 128 columns.  A block
+// whose number of positions is no multiple of 4, or a step whose gradients are not 16-byte aligned, enters with three parts (24
+// bits, nothing lost; dP, dq, dYk 3, dYv 6 products): those have always been computed in fp32, and errors stay at that level (3e-7
+// against 3.5e-6 with two).
+// Measured, 64 blocks of 512 queries on 1024 keys, 32 heads: 4.1 ms for the whole sequence (1.9 + 2.2) against 20.0 ms as
+// seven batched products and a row kernel per block with P, dS in fp32 in memory; 28 blocks of 128 on 256: 0.21 against
 // 3.0 ms (launches of 15 - 23 us each that did not fill the chip).  Bound by the issue of the vector and LDS instructions
 // between the products (matrix pipe 43 % busy in the first kernel, 33 % in the second).  The second kernel took 2.8 ms and 144 us
 // with one workgroup of eight waves to a compute unit, four for dYv and four for dYk with S computed twice: of a workgroup's
 // 90 000 cycles 14 000 went by before its first product and 20 000 in its stores, and the kinds waited for each other 1 800 of
-// 8 200 a tile.  One such workgroup with both sums in every wave still took 2.7 ms.
+// 8 200 a tile.  One such workgroup with both sums in every wave still took 2.7 ms, but is the faster form where there are no more
+// workgroups than compute units (see two_waves).
 // D is taken from P and dP, not from dO . O: the stored outputs are bf16 and would cost dS half its bits.
 #include <algorithm>
 
@@ -260,8 +261,8 @@ __global__ __launch_bounds__(256, PARTS == 2 ? 2 : 1) void bwd_attn_q_k(BwdAttnA
 // are walked in tiles of 32.
 // HV 1: a workgroup is four waves, one per 32 keys, and two share a compute unit: one's first loads and last stores, a third of
 // its life, fall beside the other's products.  (Three parts: fewer fragments find room in LDS, and dP's operands are read one
-// product ahead instead of two for it.  4097 tokens in blocks of 303 on 687 keys, 32 heads: 371 us, with eight waves 440; 1528 in blocks
-// of 191 on 383, 128 heads: 282 and 358.)
+// product ahead instead of two for it.  4097 tokens in blocks of 303 on 687 keys, 32 heads: 296 us, with eight waves 350; 1528
+// in blocks of 191 on 383, 128 heads: 255 and 321.)
 // HV 2: eight waves, two per 32 keys that take every second tile and add up at the end: half as many tiles in series, for launches
 // that leave compute units idle.
 template <int PARTS, int HV>

@@ -112,8 +112,8 @@ __device__ __forceinline__ float exp_neg(float x) {
 // each; the rows of a step stay in registers from the logits to dl.  Bound by memory in turns, one workgroup filling a compute
 // unit from 257 positions on: the logits in (64 MB a step of 32 chains, 512 slots, 1024 positions), the entries from the L2 (512 KB a
 // workgroup), the planes out (134 MB): 66 us a step; as five kernels with fp32 arrays in memory between them 250 us.  Up to 256
-// positions two share it (128 slots on 256: 13.0 us for 128 workgroups, 22.8 for 512; three parts, 253 positions, 512: 25.6, alone on
-// a compute unit 32.0).  Entries and planes go through LDS, 4 KB of a wave's own, so that an instruction covers whole lines: with
+// positions two share it (128 slots on 256: 13.0 us for 128 workgroups, 22.8 for 512; 96 on 177, three parts, 384 workgroups: 20.7,
+// one to a compute unit 26.1).  Entries and planes go through LDS, 4 KB of a wave's own, so that an instruction covers whole lines: with
 // fragments straight from memory and 16 bytes a lane straight to it, 32 lines an instruction in quarters, 83 and 14.8 us.
 // MULTI: more positions than that: they are walked twice in chunks, first for the row sums alone.
 template <int NT, bool MULTI, int NORM, int PARTS>
@@ -465,10 +465,11 @@ __global__ __launch_bounds__(512, 2) void bwd_rows_k(BwdConvArgs g, int blk) {
 // sums meet in LDS at the end.  No two waves want the same filters, so these come from memory straight into the registers,
 // packed in fragment order, D taps ahead: within a phase there is nothing to meet for, and only the plane rows (which the
 // taps read at shifted rows) pass through LDS, by loads that write it directly, a phase or more ahead.  Rows outside the
-// sequence read as zero (buffer bounds).  139 us a step of 32 chains, 512 slots and 1024 positions (155 GFLOP), 11.5 us for the
+// sequence read as zero (buffer bounds).  139 us a step of 32 chains, 512 slots and 1024 positions (155 GFLOP), 10.9 us for the
 // cache rows at 128 slots (161 and 16.4 with the filters through LDS, two taps a barrier: requests, fragment reads and products
-// were a chain that the two waves of a SIMD overlapped in part).  Without the filter loads 131, without the LDS reads 133 us;
-// the value columns' workgroups, which follow the key columns', take 20 of it and the sums 6.
+// were a chain that the two waves of a SIMD overlapped in part).  Of 145 us, before a chain's tiles shared an XCD, 131 were left
+// without the filter loads and 133 without the LDS reads; the value columns' workgroups, which follow the key columns', took 20 of
+// it and the sums 6.
 // part 0: the cache rows of block blk0; 1: the rows of blocks blk0, blk0 + 1, .. themselves (grid.z); 2: both, of blk0.
 // FINE: the blocks whose n and g enter in three parts.
 template <int PT, int NC, int KS, bool FINE>
@@ -1049,7 +1050,7 @@ template <bool FINE>
 static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   // The largest tile of which there is one for every compute unit.  128 rows have one to themselves, 64 share it by two (32 chains,
   // 512 slots on 1024 positions: 142 and 153 us, 128 slots, 27 blocks of 128 rows: 175 and 179), so 64 where they leave a tenth
-  // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 708 -> 657.
+  // less to pad: blocks of 134 rows 1000 -> 868 us, 192 rows 341 -> 273, 320 rows 256 -> 220, 303 rows (three parts) 565 -> 524.
   // 32 rows in halves, two workgroups on a compute unit, where even those are too few (128 slots: 11.9 us, whole 15.0).  The
   // slots of 32 rows go four ways, two workgroups on a compute unit: with eight, one (256 slots: 31.6 against 28.8 us; 160: 51 -
   // 39; 384: 63 - 59; three parts 71 - 66).
