@@ -961,7 +961,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       one_launch = scan_fits_one_launch(cfg, probe);
     }
     const bool small_scan = path == PATH_GENERIC &&
-                            small_scan_one_launch(cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
+                            small_scan_one_launch(cfg->dtype, cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
     for (int64_t w0 = 0; w0 < n; w0 += window) {
       const int64_t w1 = std::min<int64_t>(n, w0 + window);

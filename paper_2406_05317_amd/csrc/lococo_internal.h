@@ -164,7 +164,7 @@ hipError_t launch_protect_rows_generic(int dtype, const StepArgs& a, hipStream_t
 // T: the largest m + Bn of the call
 bool small_step_fits(int T, int M, int d, int k, int conv_in);
 // whether all steps of a scan fit one launch of one workgroup per chain
-bool small_scan_one_launch(int T, int M, int d, int k, int conv_in);
+bool small_scan_one_launch(int dtype, int T, int M, int d, int k, int conv_in);
 // n_steps consecutive compress steps (n_steps > 1 only where small_scan_one_launch), step 0 described by `a`, step s
 // taking the block s*B tokens further on (fewer where tokens_left runs out) and writing state (slot0 + s) % ring
 hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_steps, int B, int64_t tokens_left, void* out_k,

@@ -8,11 +8,8 @@
 // whole chain fits one workgroup (filters included) the steps of a scan therefore run in ONE launch, the cache
 // rows staying in LDS from step to step; otherwise each step is one launch of a workgroup per 16 slots.
 // Measured on that smallest scan (15 compressions): 1209 us with three kernels per step and one attention launch per
-// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 71 us here.  Before operand reads were issued in groups
-// ahead of their products, reductions left the LDS crossbar, divisions the index arithmetic and row strides became constants
-// for head_dim 64 it was 104 us, 12 900 cycles a step.  Two heads of other sizes gained as well, fp32 and bf16: 576 tokens of
-// 32, 96 slots, width 15: 182 -> 139 us; 144 of 56, 24 slots, width 5: 88 -> 75; 192 of 80, 32 slots: 110 -> 96; 96 of 128,
-// 16 slots, width 3: 63 -> 54 (bf16 64 -> 64); 384 of 64, 64 slots, width 9: 159 -> 127.
+// block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 104 us with compress_small_k at first, 71 us with its operand
+// reads issued in groups ahead of their products and its reductions on the vector unit, 38 us with compress64_k in its place.
 #include <algorithm>
 #include <type_traits>
 
@@ -117,6 +114,7 @@ struct SmallArgs {
   void* out_k; void* out_v;
   int64_t out_stride;     // elements between states
   int slot0, ring;
+  int T;                  // the most positions of a step
   SmallLayout l;
 };
 
@@ -374,6 +372,334 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
   }
 }
 
+// ---- the same for single precision, head_dim 64 and filters over the keys.  Bound by the number of instructions its waves issue
+// between the barriers of a step: one in some five cycles a wave, two waves to a SIMD.  So filters stay in registers in operand order
+// (read once, through LDS in whole lines: from memory each lane's own touch 64 lines an instruction), operands are read 16 bytes a lane
+// (four steps of the contraction, in an order both operands share), rows move four at a time, a row of Eq. 6 takes a lane as few
+// positions as it has, and the four barriers of a step wait for LDS alone.  A step of the smallest scan (M = B = 16, width 3):
+// 10 400 -> 4 500 cycles, 61 -> 28.5 us the 15 of them (970 Eq. 5, its products 770; 950 Eq. 6; 940 Eq. 4, its products 510).  A launch
+// per step (8 tokens on 60 slots, width 5): 15.9 -> 7.7 us, half of it before the first product; 22 on 95, width 9: 24.2 -> 11.8, four
+// of them products of Eq. 5.
+constexpr int k64 = 64, kSx = 68;            // head_dim; row stride of X and V: 16 rows x 4 columns on 64 banks
+constexpr int kPF64 = 6;                     // items of the next block a wave fetches ahead: 96 rows in all
+constexpr int kParts = 4, kPosGroups = 2;    // a wave: a quarter of the channels, every second tile of 16 positions
+static_assert(kParts * kPosGroups == kNW, "eight waves");
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
+
+struct Layout64 { int sl, off_v, off_l, bytes; };
+__host__ __device__ inline Layout64 layout64_of(int T, int k, int tiles) {
+  const int n16 = (T + 15) / 16;
+  Layout64 l;
+  l.sl = odd4(16 * n16);
+  l.off_v = (16 * n16 + k - 1) * kSx;
+  l.off_l = l.off_v + 16 * n16 * kSx;
+  // (a slot tile's filters pass through on their way into the registers: rows of 64 k + 4)
+  const int words = l.off_l + kParts * tiles * 16 * l.sl, filters = 16 * (k64 * k + 4);
+  l.bytes = (words > filters ? words : filters) * 4;
+  return l;
+}
+
+// every wave's LDS accesses are done (loads and stores of global memory may be on their way)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One workgroup: 16 TL slots of one chain.  n_steps > 1 only where those are all slots of the chain.  KW: filter width; SOFT: Eq. 6
+// as a softmax (norm 0).
+template <int KW, int TL, bool SOFT>
+__global__ __launch_bounds__(kNT) void compress64_k(SmallArgs g) {
+  extern __shared__ __align__(16) float sm[];
+  const StepArgs& a = g.st;
+  const int M = a.M, tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, l15 = l & 15, lk = l >> 4;
+  const Layout64 L = layout64_of(g.T, KW, TL);
+  float* Xs = sm;
+  float* Vs = sm + L.off_v;
+  float* Ls = sm + L.off_l;
+  constexpr int pad = (KW - 1) / 2;
+  const int sl = L.sl, plane = TL * 16 * sl, ch = blockIdx.y, b = ch / a.Hkv, hkv = ch % a.Hkv, i0 = blockIdx.x * 16 * TL;
+  const int part = w & 3, pg = w >> 2;
+  const uint32_t* protect = a.protect ? a.protect + (int64_t)ch * a.protect_stride : nullptr;
+
+  // Rows come four at a time, 16 bytes a lane: item u of a set of rows is rows 4 (u / 2) .. of the keys (u even) or the values.
+  // Of the first state and the first block, the first eight items of a wave are asked for ahead of the filters.
+  const float* kb = (const float*)a.k.p + b * a.k.sb + hkv * a.k.sh;
+  const float* vb = (const float*)a.v.p + b * a.v.sb + hkv * a.v.sh;
+  const int lr = l >> 4, lc = (l & 15) * 4;
+  int m = a.m, Tn = m + a.Bn, n16 = (Tn + 15) / 16;
+  f32x4 x8[8];
+  auto request = [&](int u0) {
+    const float* ck = (const float*)a.cache_k + (int64_t)ch * M * k64;
+    const float* cv = (const float*)a.cache_v + (int64_t)ch * M * k64;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int u = u0 + n * kNW, j = min((u >> 1) * 4 + lr, Tn - 1);
+      if ((u >> 1) * 4 >= Tn) break;
+      const float* in_cache = (u & 1 ? cv : ck) + j * k64;
+      const float* in_block = (u & 1 ? vb : kb) + (int64_t)(j - m) * (u & 1 ? a.v.st : a.k.st);
+      x8[n] = *(const f32x4_any*)((j < m ? in_cache : in_block) + lc);
+    }
+  };
+  auto place = [&](int u0) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      const int u = u0 + n * kNW, j = (u >> 1) * 4 + lr;
+      if (j < Tn) *(f32x4*)((u & 1 ? Vs : Xs + pad * kSx) + j * kSx + lc) = x8[n];
+    }
+  };
+  request(w);
+  // this lane's filters: slot l15 of each tile, channels 16 part + 4 lk ..: consecutive in memory, [slot][channel][tap].  They come
+  // in whole lines, through LDS (straight from memory a load touches 64 lines)
+  float fw[TL][KW][4];
+#pragma unroll
+  for (int st = 0; st < TL; ++st) {
+    const int s0 = i0 + st * 16, have = min(16, M - s0) * k64 * KW;      // floats of live slots (a multiple of 4)
+    const float* p = (const float*)a.conv_w + hkv * a.w_head_stride + (int64_t)s0 * k64 * KW;
+    constexpr int N = 16 * k64 * KW / 4, PER = (N + kNT - 1) / kNT;      // chunks of 16 bytes
+    f32x4 f[PER];
+#pragma unroll
+    for (int n = 0; n < PER; ++n) {
+      const int e = (tid + n * kNT) * 4;
+      f[n] = e < have ? *(const f32x4_any*)(p + e) : f32x4_any{0.f, 0.f, 0.f, 0.f};
+    }
+    if (st) lds_barrier();
+#pragma unroll
+    for (int n = 0; n < PER; ++n) {
+      const int e = (tid + n * kNT) * 4, row = e / (k64 * KW);
+      if (row < 16) *(f32x4*)(sm + e + row * 4) = f[n];
+    }
+    lds_barrier();
+    const float* q = sm + l15 * (k64 * KW + 4) + (part * 16 + lk * 4) * KW;
+#pragma unroll
+    for (int n = 0; n < KW; ++n) {
+      const f32x4 v = *(const f32x4*)(q + 4 * n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) fw[st][(4 * n + e) % KW][(4 * n + e) / KW] = v[e];
+    }
+  }
+  lds_barrier();
+  place(w);
+  for (int u0 = w + 8 * kNW; (u0 >> 1) * 4 < Tn; u0 += 8 * kNW) {
+    request(u0);
+    place(u0);
+  }
+  for (int r = w; r < pad; r += kNW) Xs[r * kSx + l] = 0.f;              // zeros around them
+  for (int r = Tn + w; r < 16 * n16 + KW - 1 - pad; r += kNW) {
+    Xs[(pad + r) * kSx + l] = 0.f;
+    if (r < 16 * n16) Vs[r * kSx + l] = 0.f;
+  }
+
+  const bool val = w >= 4;                   // Eq. 4: wave w the columns 16 w .. of [K | V]
+  const int col = (w & 3) * 16 + l15;
+  float* const rows = val ? Vs + col : Xs + pad * kSx + col;             // row j, this lane's column: + j * kSx
+  float* const states = (float*)(val ? g.out_v : g.out_k) + ((int64_t)ch * M + i0 + lk * 4) * k64 + col;
+  // where this lane's first rows of a block come from (items w, w + 8, ..: all of one array) and go to
+  const int64_t st = w & 1 ? a.v.st : a.k.st;
+  const float* from = (w & 1 ? vb : kb) + (g.B + (w >> 1) * 4 + lr) * st + lc;
+  float* const to = (w & 1 ? Vs : Xs + pad * kSx) + (M + (w >> 1) * 4 + lr) * kSx + lc;
+  const int Blast = (int)min((int64_t)g.B, g.tokens_left - (g.n_steps - 1) * (int64_t)g.B);
+  const bool whole = i0 + 16 * TL <= M;                                  // every slot is a live one
+  int slot = g.slot0;
+  for (int step = 0;; ++step) {
+    const bool more = step + 1 < g.n_steps;
+    const int Bnext = step + 2 < g.n_steps ? g.B : more ? Blast : 0;
+    // the next block's first rows, in flight under this step
+    f32x4 ahead[kPF64];
+    if (more) {
+      const int r0 = (w >> 1) * 4;
+#pragma unroll
+      for (int n = 0; n < kPF64; ++n) {
+        if (r0 + 16 * n >= Bnext) break;
+        ahead[n] = *(const f32x4_any*)(from + min(16 * n, Bnext - 1 - r0 - lr) * st);
+      }
+    }
+    lds_barrier();
+    // ---- Eq. 5: positions x slots (A: 16 positions x 16 channels at a tap's row shift, B: filters)
+    auto conv = [&](auto rect) {
+      for (int pt = pg; pt < n16; pt += kPosGroups) {
+        f32x4 acc[TL][2];                    // (two chains of products)
+#pragma unroll
+        for (int st = 0; st < TL; ++st) acc[st][0] = acc[st][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const float* xb = Xs + (pt * 16 + l15) * kSx + part * 16 + lk * 4;
+#pragma unroll
+        for (int t = 0; t < KW; ++t) {
+          f32x4 x = *(const f32x4*)(xb + t * kSx);
+          if (decltype(rect)::value)         // the rectifier in front of the convolution
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = fmaxf(x[q], 0.f);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int st = 0; st < TL; ++st)
+              acc[st][q & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q], fw[st][t][q], acc[st][q & 1], 0, 0, 0);
+        }
+        float* out = Ls + part * plane + l15 * sl + pt * 16 + 4 * lk;
+#pragma unroll
+        for (int st = 0; st < TL; ++st) *(f32x4*)(out + st * 16 * sl) = acc[st][0] + acc[st][1];
+      }
+    };
+    if (!SOFT && a.norm == 2) conv(std::true_type{});
+    else conv(std::false_type{});
+    lds_barrier();
+    // ---- Eq. 6: 32 lanes per slot, N positions a lane (and as many 128 positions on): a wave issues each instruction for all of
+    // its lanes, so short rows take no more of them than they have positions for
+    auto normalise = [&](auto width, auto halves) {
+      constexpr int N = decltype(width)::value, H = decltype(halves)::value;
+      typedef __attribute__((ext_vector_type(N))) float fx;
+      const int c = (tid & 31) * N, row = tid >> 5, last = 16 * n16 - N;
+      fx x[TL][H];
+      float mx[TL], z[TL];
+#pragma unroll
+      for (int st = 0; st < TL; ++st) {
+        const float* r = Ls + (st * 16 + row) * sl;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const float* p = r + min(c + 128 * h, last);
+          x[st][h] = (*(const fx*)p + *(const fx*)(p + plane)) + (*(const fx*)(p + 2 * plane) + *(const fx*)(p + 3 * plane));
+        }
+      }
+      if (a.conv_b)
+#pragma unroll
+        for (int st = 0; st < TL; ++st) {
+          const int i = i0 + st * 16 + row;
+          const float bi = i < M ? ((const float*)a.conv_b)[hkv * a.b_head_stride + i] : 0.f;
+#pragma unroll
+          for (int h = 0; h < H; ++h) x[st][h] += bi;
+        }
+      constexpr float none = SOFT ? -INFINITY : 0.f;       // a protected slot's position
+      if (protect)
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const int j0 = c + 128 * h;                      // (N divides 32: one word)
+          const uint32_t bits = j0 < m ? protect[j0 >> 5] >> (j0 & 31) : 0;
+#pragma unroll
+          for (int e = 0; e < N; ++e)
+#pragma unroll
+            for (int st = 0; st < TL; ++st) x[st][h][e] = j0 + e < m && ((bits >> e) & 1u) ? none : x[st][h][e];
+        }
+      bool in[H][N];                                       // past T: zero, whatever the sum
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int e = 0; e < N; ++e) in[h][e] = c + 128 * h + e < Tn;
+#pragma unroll
+      for (int st = 0; st < TL; ++st)
+        if (SOFT) {
+          mx[st] = -INFINITY;
+#pragma unroll
+          for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int e = 0; e < N; ++e) mx[st] = fmaxf(mx[st], in[h][e] ? x[st][h][e] : -INFINITY);
+          mx[st] = over32(mx[st], [](float p, float q) { return fmaxf(p, q); });
+        }
+#pragma unroll
+      for (int st = 0; st < TL; ++st) {
+        z[st] = 0.f;
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int e = 0; e < N; ++e) {
+            const float y = x[st][h][e];
+            const float v = SOFT ? expf(y - mx[st]) : a.norm == 1 ? fmaxf(y, 0.f) : (isfinite(y) ? y : 0.f);
+            x[st][h][e] = in[h][e] ? v : 0.f;
+            z[st] += x[st][h][e];
+          }
+      }
+#pragma unroll
+      for (int st = 0; st < TL; ++st) {
+        z[st] = over32(z[st], [](float p, float q) { return p + q; });
+        if (!SOFT && a.norm == 1) z[st] += a.eps;
+        if (!SOFT && a.norm == 2 && fabsf(z[st]) < a.eps) z[st] = z[st] < 0.f ? -a.eps : a.eps;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          fx v;
+#pragma unroll
+          for (int e = 0; e < N; ++e) v[e] = in[h][e] ? x[st][h][e] / z[st] : 0.f;
+          if (c + 128 * h <= last) *(fx*)(Ls + (st * 16 + row) * sl + c + 128 * h) = v;
+        }
+      }
+    };
+    using std::integral_constant;
+    if (n16 <= 2) normalise(integral_constant<int, 1>{}, integral_constant<int, 1>{});
+    else if (n16 <= 4) normalise(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    else if (n16 <= 8) normalise(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+    else normalise(integral_constant<int, 4>{}, integral_constant<int, 2>{});
+    lds_barrier();
+    // ---- Eq. 4a / 4b: slots x 16 columns (A: weights of 16 positions, B: their rows)
+    f32x4 acc[TL][2];
+    {
+#pragma unroll
+      for (int st = 0; st < TL; ++st) acc[st][0] = acc[st][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const float* wr = Ls + l15 * sl + 4 * lk;
+      const float* yr = rows + 4 * lk * kSx;
+      auto some = [&](auto count) {          // COUNT tiles of 16 positions in flight together
+        constexpr int COUNT = decltype(count)::value;
+        float y[COUNT][4];
+        f32x4 x[COUNT][TL];
+#pragma unroll
+        for (int n = 0; n < COUNT; ++n) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) y[n][q] = yr[(16 * n + q) * kSx];
+#pragma unroll
+          for (int st = 0; st < TL; ++st) x[n][st] = *(const f32x4*)(wr + 16 * n + st * 16 * sl);
+        }
+        wr += 16 * COUNT;
+        yr += 16 * COUNT * kSx;
+#pragma unroll
+        for (int n = 0; n < COUNT; ++n)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int st = 0; st < TL; ++st)
+              acc[st][q & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[n][st][q], y[n][q], acc[st][q & 1], 0, 0, 0);
+      };
+      int p = 0;
+#pragma clang loop unroll(disable)
+      for (; p + 2 <= n16; p += 2) some(std::integral_constant<int, 2>{});
+      if (p < n16) some(std::integral_constant<int, 1>{});
+    }
+    lds_barrier();                           // every read of the old rows is done
+    float* const out = states + (int64_t)slot * g.out_stride;
+    if (++slot == g.ring) slot = 0;
+#pragma unroll
+    for (int st = 0; st < TL; ++st) {
+      f32x4 v = acc[st][0] + acc[st][1];
+      const int i = i0 + st * 16 + lk * 4;   // rows i .. i + 3
+      if (protect)                           // a live protected slot is carried over unchanged
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i + e < m && ((protect[(i + e) >> 5] >> ((i + e) & 31)) & 1u)) v[e] = rows[(i + e) * kSx];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (whole || i + e < M) {
+          out[(st * 16 + e) * k64] = v[e];
+          rows[(i + e) * kSx] = v[e];
+        }
+    }
+    if (!more) break;
+    // ---- the next block behind the new cache; zeros up to the end of what this step's rows used
+    {
+      const int r0 = (w >> 1) * 4 + lr;
+#pragma unroll
+      for (int n = 0; n < kPF64; ++n) {
+        if ((w >> 1) * 4 + 16 * n >= Bnext) break;
+        if (r0 + 16 * n < Bnext) *(f32x4*)(to + 16 * n * kSx) = ahead[n];
+      }
+      for (int r = r0 + 16 * kPF64; r < Bnext; r += 16) *(f32x4*)(to + (r - r0) * kSx) = *(const f32x4_any*)(from + (r - r0) * st);
+    }
+    // (a first step of fewer live slots may be the shorter one: what a longer one reads beyond it is zeroed here as well)
+    const int Tnext = M + Bnext;
+    if (Tnext != Tn) {
+      const int end = 16 * max(n16, (Tnext + 15) / 16);
+      for (int r = Tnext + w; r < end + KW - 1 - pad; r += kNW) {
+        Xs[(pad + r) * kSx + l] = 0.f;
+        if (r < end) Vs[r * kSx + l] = 0.f;
+      }
+      Tn = Tnext;
+      n16 = (Tn + 15) / 16;
+    }
+    m = M;
+    from += g.B * st;
+  }
+}
+
 // ---- attention of every block of a window in one launch (Alg. 2 step 3): one wave per query row, four rows of
 // a (block, head) per workgroup.  Scores: a lane per key; output: a lane per NC columns.
 template <typename T, int NC>
@@ -491,16 +817,61 @@ hipError_t launch(const SmallArgs& g, int grid_x, hipStream_t s) {
   return g.st.conv_in ? launch_d<T, MIX, 64, 1>(g, grid_x, s) : launch_d<T, MIX, 64, 0>(g, grid_x, s);
 }
 
+// Slot tiles a workgroup of compress64_k holds the filters and sums of without spilling registers
+constexpr int tiles64(int k) { return k <= 5 ? 3 : k <= 11 ? 2 : 1; }
+// whether compress64_k has a build for this width and the positions fit with `tiles` slot tiles to a workgroup
+bool fits64(int dtype, int T, int d, int k, int conv_in, int tiles) {
+  return dtype == LOCOCO_F32 && d == k64 && !conv_in && k >= 3 && (k <= 15 || k == 21) && tiles <= tiles64(k) && T <= 256 &&
+         layout64_of(T, k, tiles).bytes <= kLds;
+}
+
+template <int KW, int TL, bool SOFT>
+hipError_t launch64_as(const SmallArgs& g, int grid_x, hipStream_t s) {
+  static bool attr_set = false;   // benign race: setting it twice is harmless
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void*)compress64_k<KW, TL, SOFT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((compress64_k<KW, TL, SOFT>), dim3(grid_x, g.st.batch * g.st.Hkv), dim3(kNT), layout64_of(g.T, KW, TL).bytes, s, g);
+  return hipGetLastError();
+}
+template <int KW, bool SOFT>
+hipError_t launch64_tiles(const SmallArgs& g, int tiles, int grid_x, hipStream_t s) {
+  if constexpr (tiles64(KW) >= 3) if (tiles == 3) return launch64_as<KW, 3, SOFT>(g, grid_x, s);
+  if constexpr (tiles64(KW) >= 2) if (tiles == 2) return launch64_as<KW, 2, SOFT>(g, grid_x, s);
+  return tiles == 1 ? launch64_as<KW, 1, SOFT>(g, grid_x, s) : hipErrorInvalidValue;
+}
+template <bool SOFT>
+hipError_t launch64(const SmallArgs& g, int tiles, int grid_x, hipStream_t s) {
+  switch (g.st.k_width) {
+    case 3: return launch64_tiles<3, SOFT>(g, tiles, grid_x, s);
+    case 5: return launch64_tiles<5, SOFT>(g, tiles, grid_x, s);
+    case 7: return launch64_tiles<7, SOFT>(g, tiles, grid_x, s);
+    case 9: return launch64_tiles<9, SOFT>(g, tiles, grid_x, s);
+    case 11: return launch64_tiles<11, SOFT>(g, tiles, grid_x, s);
+    case 13: return launch64_tiles<13, SOFT>(g, tiles, grid_x, s);
+    case 15: return launch64_tiles<15, SOFT>(g, tiles, grid_x, s);
+    case 21: return launch64_tiles<21, SOFT>(g, tiles, grid_x, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 }  // namespace
 
 // Decided for blocks of at least M tokens, so that a shorter (last) block runs on the same kernels as the others.
 bool small_step_fits(int T, int M, int d, int k, int conv_in) { return taps_that_fit(std::max(T, 2 * M), d, k, conv_in) > 0; }
 
-// All steps of a scan in one launch where one workgroup holds a whole chain: LDS, the registers of Eq. 4, and no more
-// matrix work put on one compute unit per step than the launch it saves costs (12 000 cycles, about 5 us: the
-// dispatch of a dependent kernel plus reading rows and filters back in).
-bool small_scan_one_launch(int T, int M, int d, int k, int conv_in) {
+// All steps of a scan in one launch where one workgroup holds a whole chain: LDS, the registers of Eq. 4 (or of the filters), and no
+// more matrix work put on one compute unit per step than the launch it saves costs (12 000 cycles, about 5 us: the
+// dispatch of a dependent kernel plus reading rows and filters back in; 8 tokens on 28 slots, width 5, 2 500 cycles more: 4.3 us
+// a step, in launches of their own 7.7).
+bool small_scan_one_launch(int dtype, int T, int M, int d, int k, int conv_in) {
   const int tiles = (M + 15) / 16, C4 = ((conv_in ? 2 * d : d) + 3) / 4;
+  if (fits64(dtype, std::max(T, 2 * M), d, k, conv_in, 1)) {     // (decided like small_step_fits: a step is the same bits in either form)
+    const int64_t cycles = (int64_t)tiles * ((T + 15) / 16) * 16 * k * 32 / 4;
+    return fits64(dtype, std::max(T, 2 * M), d, k, conv_in, tiles) && cycles - cycles / tiles <= 12000;
+  }
   if (tiles * 2 * ((d + 15) / 16) > kNW * kMaxMix || layout_of(T, d, k, conv_in, tiles, k).bytes > kLds) return false;
   const int64_t cycles = (int64_t)tiles * ((T + 15) / 16) * C4 * k * 32 / 4;    // one 32-cycle MFMA per 4 channels, four SIMDs
   return cycles - cycles / tiles <= 12000;
@@ -519,6 +890,11 @@ hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_step
   g.slot0 = slot0;
   g.ring = ring;
   const int tiles = n_steps > 1 ? (a.M + 15) / 16 : 1;
+  g.T = std::max(T, 2 * a.M);
+  if (fits64(dtype, g.T, a.d, a.k_width, a.conv_in, 1)) {
+    const int grid64 = ((a.M + 15) / 16 + tiles - 1) / tiles;
+    return a.norm == 0 ? launch64<true>(g, tiles, grid64, s) : launch64<false>(g, tiles, grid64, s);
+  }
   g.l = layout_of(T, a.d, a.k_width, a.conv_in, tiles, n_steps > 1 ? a.k_width : taps_that_fit(T, a.d, a.k_width, a.conv_in));
   const int grid_x = ((a.M + 15) / 16 + tiles - 1) / tiles;
   const bool f32 = dtype == LOCOCO_F32;
