@@ -241,8 +241,8 @@ LOCOCO_API lococo_status lococo_sequence_forward(const lococo_config* cfg, const
                                       void* stream);
 
 /* When lococo_sequence_forward, or lococo_sequence_backward for the states it walks back through, runs a whole scan's
- * compression steps in one launch, the workgroups that share a chain wait for each other between steps with a bounded number of
- * polls (a few seconds).  That form is chosen only when the whole grid can be resident at once
+ * compression steps in one launch, or lococo_sequence_backward its walk back through them, the workgroups that share a chain wait
+ * for each other between steps with a bounded number of polls (a few seconds).  That form is chosen only when the whole grid can be resident at once
  * (the runtime's occupancy figure for the kernel) and no other such launch of this process is
  * still running on another stream of the device; otherwise every step gets a launch of its own.
  * Work from elsewhere that keeps compute units busy for longer than the bound (another process, a
@@ -267,7 +267,7 @@ enum {
   LOCOCO_OPT_RESET = 0,             /* every option back to its default; value ignored                         */
   LOCOCO_OPT_SPIN_LIMIT = 1,        /* polls a waiting workgroup of the one-launch scan makes before it gives
                                        up (0 = default, 2^21); negative: give up at once                       */
-  LOCOCO_OPT_SCAN_PER_STEP = 2,     /* 1: one launch per compression step even where one per scan fits         */
+  LOCOCO_OPT_SCAN_PER_STEP = 2,     /* 1: launches per step even where one per scan, or per walk back, fits      */
   LOCOCO_OPT_CHAIN_SYNC_DEVICE = 3, /* 1: workgroups of a chain always meet with device-scope release and
                                        acquire (default: without the L2 write-back when they find themselves
                                        on one XCD)                                                             */

@@ -582,6 +582,22 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
   return LOCOCO_OK;
 }
 
+// Steps hi, hi - 1, .. hi - n + 1 of the backward walk through a window in one launch, on the counters the scan that recomputed its
+// states has finished with (the status word is kept); *taken = false, and nothing launched, where its workgroups could not all be
+// resident.
+lococo_status enqueue_bwd_walk(const lococo_config* c, const BwdConvArgs& g, int hi, int n, void* ws, hipStream_t s, bool* taken) {
+  *taken = false;
+  if (g_debug.scan_per_step) return LOCOCO_OK;
+  const bool capturing = stream_is_capturing(s);
+  std::unique_lock<std::mutex> lk(g_scan_mu);
+  if (!capturing && another_scan_in_flight(s)) return LOCOCO_OK;
+  char* sync_ws = (char*)ws + filter_ws_bytes(c);
+  HIP_TRY(launch_scan_sync_clear(sync_ws, c->batch, c->n_kv_heads, c->M, true, s), "clearing the scan counters");
+  HIP_TRY(launch_bwd_conv_walk(g, hi, n, sync_ws, spin_limit(), chain_sync_through_l2(), taken, s), "backward walk launch");
+  if (*taken && !capturing) note_scan_launched(s);
+  return LOCOCO_OK;
+}
+
 lococo_status segment_step_impl(const lococo_config* cfg, const lococo_qkvo* blk, int32_t B,
                                 const void* conv_w, const void* conv_b, lococo_cache* cache,
                                 void* workspace, size_t ws_bytes, void* stream) {
@@ -1587,6 +1603,15 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
         if (!have_logits) HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
         const bool defer = bwd_conv_defers_blocks(c);
         for (int i = c.n_blk - 1; i >= 0; --i) {
+          int run = 0;                         // blocks from here down whose steps one launch can take
+          if (path == PATH_MFMA && bwd_conv_walk_takes(c))
+            while (run <= i && bwd_conv_three_parts(c, i - run) == bwd_conv_three_parts(c, i)) ++run;
+          bool taken = false;
+          if (run > 1 && (st = enqueue_bwd_walk(cfg, c, i, run, ws + l.fwd_ws, s, &taken))) return st;
+          if (taken) {
+            i -= run - 1;
+            continue;
+          }
           const lococo_seg& sg = plan[(size_t)(w_steps + i)];
           HIP_TRY(launch_bwd_conv_rows(c, i, sg.len_before + sg.len, s), "row gradient launch");
           HIP_TRY(launch_bwd_conv_dx(c, i, 1, defer ? 0 : 2, sg.len_before + (defer ? 0 : sg.len), s), "input gradient launch");

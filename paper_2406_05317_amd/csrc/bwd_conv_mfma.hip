@@ -7,8 +7,9 @@
 //   dW[i, c, t] += sum_j dl[i, j] X[j + t - p, c]                                   (Eq. 5 w.r.t. the filters)
 //
 // Only g has to wait for the walk, and of dX only the rows of the cache are what the walk hands on.  So the logits of all
-// blocks come from the recomputed scan, or from one launch ahead of the walk (tiled_mfma.hip), a step of the walk is two launches (bwd_rows_k, bwd_dx_k
-// over the cache rows), and the rows of the blocks and the filter gradient follow in one launch each for the whole window.
+// blocks come from the recomputed scan, or from one launch ahead of the walk (tiled_mfma.hip), the walk is one launch for all blocks
+// (bwd_walk_k) or two for each (bwd_rows_k, bwd_dx_k over the cache rows), and the rows of the blocks and the filter gradient follow
+// in one launch each for the whole window.
 //
 // g, n and dl enter the matrix products as two bf16 halves (16 bits kept): n g in three products, the others in two.  In a
 // block whose number of positions is no multiple of 4, and in a step whose gradients are not 16-byte aligned, n and g enter as
@@ -16,6 +17,7 @@
 // and n are kept as "planes" [chain][32 slots][position][32 high halves | 32 low halves]: 128 bytes per position, read row
 // by row where the slots are contracted (bwd_dx_k) and down the rows where the positions are (bwd_dw_k).
 #include <algorithm>
+#include <type_traits>
 
 #include "lococo_internal.h"
 #include "mfma_util.h"
@@ -720,6 +722,557 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
   }
 }
 
+// ---- The walk over a run of blocks in one launch: what bwd_rows_k and bwd_dx_k over the cache rows do block by block.  A step is
+// bound by the chain of latencies from one block's g to the next one's, for 3 us of matrix work at the chip's rate on 32 chains of 128
+// slots and 256 positions: two launches a block 23.6 us, some 4 of either the launch, here 20.6 (256 slots, 512 positions, 16 chains:
+// 34.4 and 30).  Four workgroups to 64 slots of a chain stay for all blocks.  Each has one tile of 32 slots, whose rows it takes
+// in turn with another, every second block; and 64 cache rows by 32 key and 32 value columns of dX of every block.  What does not
+// wait for g is out of the way before it arrives: the normalised rows and their planes (made by the one workgroup while the other is at
+// work on the block before), the entries' first rows, the first filters.  The workgroups of a chain meet twice a block, over dl (all of
+// its tiles) and over the next g (the four of 64 rows), on counters and by rules that are those of the forward scan (compress_tile.inl):
+// through the L2 where they share one, with device-scope release and acquire where not; waits are bounded.  Planes and fragments of g
+// have places of their own in every block, so no compute unit can have read them before they were written; g itself it can, as what
+// its sums were added to, so that is read past its L1.
+// Clock stamps of the former (49 000 cycles a step): 4 000 from g to its halves in LDS, 2 400 G, 1 200 row sums, 3 800 dl, 4 700 until it
+// is known to have arrived, 3 000 to have it back, 9 500 taps and n g (4 600 of matrix work, the rest the forty instructions around a
+// tap's four products), 6 000 partial sums.
+struct WalkArgs {
+  BwdConvArgs c;
+  int32_t hi, n;             // blocks hi, hi - 1, .. hi - n + 1
+  uint32_t* sync;            // per chain
+  uint32_t* tsync;           // per (chain, tile): two words, the count of a tile's halves; the second of a chain's first: XCD mask
+  int32_t* status;
+  int32_t spin_limit, same_l2_allowed;
+};
+// loads of what other workgroups have written since this one began: from the L2, never from this compute unit's L1
+__device__ __forceinline__ f32x4 load_f4_shared(const void* base, uint32_t bytes, uint32_t off) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 1 << 4));
+}
+// 32-slot tiles whose rows of dl and n are in LDS at once: all of them in as few rounds as there is room for
+template <int PARTS>
+__host__ __device__ inline int walk_round(int tiles) {
+  constexpr int most = PARTS == 3 ? 5 : 8;
+  const int rounds = (tiles + most - 1) / most;
+  return (tiles + rounds - 1) / rounds;
+}
+__host__ __device__ inline int walk_rows(int KW) { return (64 + KW - 1 + 7) / 8 * 8; }
+template <int PARTS>
+int walk_lds(int tiles, int KW) {
+  const int rows = PARTS * 2 * 8192 + 8 * 4096, dx = walk_round<PARTS>(tiles) * (walk_rows(KW) * 128 + 8192 * (PARTS - 1)), sums = 8 * 64 * 256;
+  return std::max(rows, std::max(dx, sums));
+}
+
+// NT: 32-position tiles a wave holds of a row; PARTS: of n and g (see above)
+template <int NT, int PARTS>
+__global__ __launch_bounds__(512, 2) void bwd_walk_k(WalkArgs wa) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ __align__(16) float row_s[3 * 32];                  // of a row: reference, 1 / sum, sum n G
+  __shared__ int bail, same_l2;
+  const BwdConvArgs& g = wa.c;
+  const StepArgs& a = g.st;
+  unsigned char* const Gs = smem;                                // [part][keys, values]: tiles of 32 rows of g (see swz)
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int l = tid & 63, l31 = l & 31, lh = l >> 5;
+  // addresses belong to a phase of a step: hoisted out of the walk, they spill
+  auto phase = [&]() { asm volatile("" : "+v"(l), "+v"(l31), "+v"(lh)); };
+  unsigned char* const Xs0 = smem + PARTS * 2 * 8192;            // a wave's own 4 KB each: 32 rows of 128 bytes (see pswz)
+  unsigned char* const xs = Xs0 + w * 4096;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)smem);
+  const int tiles = a.M / 32, mine = (tiles + 1) / 2 * 4, item = xcd_item(blockIdx.x, gridDim.x);
+  const int ch = item / mine, r2 = item % mine >> 2, cg = item & 3, tile = r2 * 2 + (cg & 1), half = cg >> 1, s0 = tile * 32, hkv = ch % a.Hkv;
+  const int KW = a.k_width, pad = (KW - 1) / 2, n16 = tiles * 2, DR = walk_rows(KW);
+
+  // ---- meeting points
+  if (tid == 0) { bail = 0; same_l2 = 0; }
+  __syncthreads();
+  auto signal = [&](uint32_t* c) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+      if (same_l2) __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  };
+  auto await = [&](const uint32_t* c, uint32_t target) -> bool {
+    if (tid == 0) {
+      int polls = 0;
+      while (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        __builtin_amdgcn_s_sleep(1);
+        if (++polls > wa.spin_limit) {       // bounded: never spin forever on a workgroup that is not there
+          __hip_atomic_store(wa.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          bail = 1;
+          break;
+        }
+      }
+      if (!same_l2) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    return bail == 0;
+  };
+  uint32_t* const chain_count = wa.sync + ch;
+  uint32_t* const rows_count = wa.tsync + 2 * (ch * tiles + r2);
+  {                                          // the first meeting is a census of the XCDs a chain's workgroups run on
+    uint32_t* const mask = wa.tsync + 2 * ch * tiles + 1;
+    if (tid == 0) {
+      const uint32_t xcd = __builtin_amdgcn_s_getreg(20 | ((4 - 1) << 11));   // XCC_ID, bits [3:0]
+      __hip_atomic_fetch_or(mask, 1u << xcd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    signal(chain_count);
+    if (!await(chain_count, (uint32_t)mine)) return;
+    if (tid == 0) {
+      const uint32_t seen = __hip_atomic_load(mask, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      same_l2 = wa.same_l2_allowed && (seen & (seen - 1)) == 0;
+    }
+    __syncthreads();
+  }
+
+  // ---- rows: this workgroup's 32 slots, all positions; wave w has the position tiles w, w + 8, ..  (see bwd_rows_k)
+  auto wave_sync = [&]() {                   // (LDS serves a wave in order: nothing to wait for)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto by_row = [&]() { return (l >> 3) * 128 + (((l & 7) ^ pswz(l >> 3)) << 4); };   // rows 8 i + l / 8: + 1024 i, ^ 32 where i is odd
+  auto by_pos = [&]() { return l31 * 128 + ((lh ^ pswz(l31)) << 4); };                // chunk 2 k + l / 32 of row l % 32: ^ 32 k
+  auto over_waves = [&](const f32x16& v, auto mx) {
+    const float t = over32<decltype(mx)::value>(v, l31);
+    const int i = l31 >> 1;
+    ((float*)xs)[(i >> 2) * 8 + lh * 4 + (i & 3)] = t;           // (two lanes hold the same)
+  };
+  auto collect = [&](bool mx) {
+    float t = ((const float*)Xs0)[tid];
+    for (int k = 1; k < 8; ++k) {
+      const float o = ((const float*)(Xs0 + k * 4096))[tid];
+      t = mx ? fmaxf(t, o) : t + o;
+    }
+    return t;
+  };
+  auto rows = [&](int which) {
+    f32x16 r;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 t = *(const f32x4*)(row_s + which * 32 + q * 8 + lh * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[q * 4 + e] = t[e];
+    }
+    return r;
+  };
+  // 32 slots x 32 positions of a lane's values -> rows of a plane [position][32 high | 32 low halves], through the wave's LDS, whole
+  // lines a store; `third`: what the two halves leave over, with the high ones beside it, into a plane of its own
+  auto planes = [&](const f32x16& v, uint16_t* at, uint16_t* third) {
+    u32x4 out[2][2], out3[2];
+#pragma unroll
+    for (int qp = 0; qp < 2; ++qp) {         // slots 16 qp .. + 15: two groups of four of this lane
+      uint32_t hi[2][2], lo[2][2], th[2][2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float x0 = v[(qp * 2 + q) * 4 + 2 * e], x1 = v[(qp * 2 + q) * 4 + 2 * e + 1];
+          split2(x0, x1, hi[q][e], lo[q][e]);
+          if (third) {
+            const f32x2 left = {x0 - __uint_as_float(hi[q][e] << 16) - __uint_as_float(lo[q][e] << 16),
+                                x1 - __uint_as_float(hi[q][e] & 0xffff0000u) - __uint_as_float(lo[q][e] & 0xffff0000u)};
+            th[q][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(left, bf16x2));
+          }
+        }
+      // the halves of the wave trade groups, so that a lane has eight consecutive slots: 16 qp + 8 lh ..
+      auto trade = [&](const uint32_t (&p)[2][2]) {
+        const auto t0 = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+        const auto t1 = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+        return u32x4{t0[0], t1[0], t0[1], t1[1]};
+      };
+      out[0][qp] = trade(hi);
+      out[1][qp] = trade(lo);
+      if (third) out3[qp] = trade(th);
+    }
+    const int br = by_row(), bp = by_pos();
+    auto put = [&](uint16_t* to, const u32x4 (&x)[2], const u32x4 (&y)[2]) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) *(u32x4*)(xs + (bp ^ k << 5)) = k < 2 ? x[k & 1] : y[k & 1];
+      wave_sync();
+      u32x4 t[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = *(const u32x4*)(xs + i * 1024 + (br ^ (i & 1) << 5));
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *(u32x4*)(to + l * 8 + i * 512) = t[i];
+    };
+    put(at, out[0], out[1]);
+    if (third) put(third, out3, out[0]);
+  };
+  const int64_t plane0 = ((int64_t)ch * tiles + tile) * g.P * 64;
+  f32x16 xn[NT];                             // the normalised rows of the block this workgroup's rows are next
+  // What does not wait for g: the normalised rows of block blk and their planes.
+  auto prepare = [&](int blk) {
+    phase();
+    const Block x = block_of(g, blk);
+    const float* lg = g.logits + blk * g.logits_stride + ((int64_t)ch * a.M + s0) * g.ld + (int64_t)(lh * 4) * g.ld + l31;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = (w + 8 * n) * 32;
+      if (p0 < x.T) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xn[n][i] = lg[(int64_t)((i >> 2) * 8 + (i & 3)) * g.ld + p0];
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) xn[n][i] = -INFINITY;
+      }
+    }
+    f32x16 mx;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const bool out = (w + 8 * n) * 32 + l31 >= x.T;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        xn[n][i] = out ? -INFINITY : xn[n][i];
+        mx[i] = n ? fmaxf(mx[i], xn[n][i]) : xn[n][i];
+      }
+    }
+    over_waves(mx, Yes{});
+    barrier();
+    if (tid < 32) row_s[tid] = collect(true);
+    barrier();
+    {
+      const f32x16 ref = rows(0);
+      f32x16 ps = zero16();
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          xn[n][i] = exp_neg(xn[n][i] - ref[i]);
+          ps[i] += xn[n][i];
+        }
+      over_waves(ps, No{});
+    }
+    barrier();
+    if (tid < 32) row_s[32 + tid] = 1.0f / collect(false);
+    barrier();
+    const f32x16 inv = rows(1);
+    uint16_t* pn = g.wn + blk * g.plane_stride + plane0;
+    uint16_t* pw = PARTS == 3 ? g.wn_low + blk * g.plane_stride + plane0 : nullptr;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) xn[n][i] *= inv[i];
+      const int p0 = (w + 8 * n) * 32;
+      if (p0 < x.T) planes(xn[n], pn + (int64_t)p0 * 64, PARTS == 3 ? pw + (int64_t)p0 * 64 : nullptr);
+    }
+  };
+
+  // The entries' rows of a wave's first tile in block blk are asked for ahead, under the wait for g, the others a tile ahead.  (A row's
+  // offset in the cache or in the block: 32 bits.)
+  bf16x8 fx[2][8];
+  auto request_entries = [&](const Block& x, int p0, int val) {
+    const unsigned char* cache = (const unsigned char*)((val ? x.cv : x.ck) + (int64_t)ch * a.M * kD);
+    const View& st = val ? a.v : a.k;
+    const unsigned char* block = (const unsigned char*)((val ? x.v : x.k) + (ch / a.Hkv) * st.sb + hkv * st.sh);
+    const uint32_t stride = (uint32_t)st.st * 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = min(p0 + 8 * i + (l >> 3), x.T - 1);
+      const unsigned char* row = (j < x.m ? cache : block) + ((j < x.m ? j * 256u : (uint32_t)(j - x.m) * stride) + (l & 7) * 16);
+      fx[val][i] = *(const bf16x8*)row;
+      fx[val][4 + i] = *(const bf16x8*)(row + 128);
+    }
+  };
+  auto request_first = [&](int blk) {
+    if (blk < 0) {                           // (none: nothing of them is kept from here on)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) fx[0][i] = fx[1][i] = bf16x8{};
+      return;
+    }
+    phase();
+    const Block x = block_of(g, blk);
+    request_entries(x, w * 32, 0);
+    request_entries(x, w * 32, 1);
+  };
+
+  // G, its row sums and dl of block blk; target: of the count of this tile's halves (0: g is there)
+  auto differentiate = [&](int blk, uint32_t target) -> bool {
+    phase();
+    const Block x = block_of(g, blk);
+    {                                        // the first tile's entries have come: through the wave's LDS into operand order
+      const int br = by_row(), bp = by_pos();
+#pragma unroll
+      for (int val = 0; val < 2; ++val)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) *(bf16x8*)(xs + i * 1024 + (br ^ (i & 1) << 5)) = fx[val][4 * h + i];
+          wave_sync();
+#pragma unroll
+          for (int q = 0; q < 4; ++q) fx[val][4 * h + q] = *(const bf16x8*)(xs + (bp ^ q << 5));
+          wave_sync();
+        }
+    }
+    if (target && !await(rows_count, target)) return false;
+    const int by_chunk = tid >> 4, c8 = tid & 15;                // eight columns of a row of g_k, and of g_v
+    {
+      f32x4 gr[2][2];
+#pragma unroll
+      for (int val = 0; val < 2; ++val)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          gr[val][h] = load_f4_shared(grad_new(g, blk, val) + (int64_t)ch * a.M * kD, (uint32_t)a.M * kD * 4,
+                                      (uint32_t)((s0 + by_chunk) * kD + c8 * 8 + h * 4) * 4);
+#pragma unroll
+      for (int val = 0; val < 2; ++val) {
+        const float v[8] = {gr[val][0][0], gr[val][0][1], gr[val][0][2], gr[val][0][3], gr[val][1][0], gr[val][1][1], gr[val][1][2], gr[val][1][3]};
+        bf16x8 part[PARTS];
+        split_parts<PARTS>(v, part);
+#pragma unroll
+        for (int u = 0; u < PARTS; ++u) *(bf16x8*)(Gs + (u * 2 + val) * 8192 + by_chunk * 256 + ((c8 ^ swz(by_chunk)) << 4)) = part[u];
+      }
+    }
+    barrier();
+    {                                        // g for cache_rows, as operand fragments: wave w the columns 32 w .. of [K | V]
+      uint16_t* gsp = g.gsplit + (int64_t)blk * g.gsplit_stride;
+      const int s16 = l & 15, g2 = (l >> 4) & 1, chunk = (w & 3) * 4 + 2 * g2 + ((s16 & 3) >> 1);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int r = h * 16 + lh * 8 + (s16 >> 2), r4 = r + 4;
+        const int at = r * 256 + ((chunk ^ swz(r)) << 4) + (s16 & 1) * 8, at4 = r4 * 256 + ((chunk ^ swz(r4)) << 4) + (s16 & 1) * 8;
+#pragma unroll
+        for (int u = 0; u < PARTS; ++u) {
+          const unsigned char* p = Gs + (u * 2 + (w >> 2)) * 8192;
+          *(bf16x8*)(gsp + ((((int64_t)u * a.batch * a.Hkv + ch) * n16 + tile * 2 + h) * 8 + w) * 512 + l * 8) = frag_tr(p + at, p + at4);
+        }
+      }
+    }
+    f32x16 acc[NT];
+    {
+      const int br = by_row(), bp = by_pos();
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const int p0 = (w + 8 * n) * 32;
+        acc[n] = zero16();
+        if (p0 >= x.T) continue;
+#pragma unroll
+        for (int val = 0; val < 2; ++val)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            if (n) {
+#pragma unroll
+              for (int i = 0; i < 4; ++i) *(bf16x8*)(xs + i * 1024 + (br ^ (i & 1) << 5)) = fx[val][4 * h + i];
+              if (h && n + 1 < NT) request_entries(x, p0 + 256, val);    // (rows past the end: the last one again)
+              wave_sync();
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const bf16x8 f = n ? *(const bf16x8*)(xs + (bp ^ q << 5)) : fx[val][4 * h + q];
+              const int at = l31 * 256 + (((2 * (4 * h + q) + lh) ^ swz(l31)) << 4);
+#pragma unroll
+              for (int u = 0; u < PARTS; ++u) acc[n] = mfma32(*(const bf16x8*)(Gs + (u * 2 + val) * 8192 + at), f, acc[n]);
+            }
+            if (n) wave_sync();
+            else if (h && NT > 1) request_entries(x, p0 + 256, val);
+          }
+      }
+    }
+    {
+      f32x16 pd = zero16();
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pd[i] = fmaf(xn[n][i], acc[n][i], pd[i]);
+      over_waves(pd, No{});
+    }
+    barrier();
+    if (tid < 32) row_s[64 + tid] = collect(false);
+    barrier();
+    const f32x16 r = rows(2);
+    uint16_t* pl = g.dl + blk * g.plane_stride + plane0;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int p0 = (w + 8 * n) * 32;
+      if (p0 >= x.T) continue;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[n][i] = xn[n][i] * (acc[n][i] - r[i]);
+      planes(acc[n], pl + (int64_t)p0 * 64, nullptr);
+    }
+    return true;
+  };
+
+  // ---- dX over 64 rows of the cache, 32 key and 32 value columns: the contraction over (slot, tap) shared out evenly among the
+  // waves, that with n over the slots; partial sums meet in LDS.  Filters come straight into registers, a few taps ahead, rows of
+  // dl and n through LDS (see bwd_dx_k).  (32 rows and 64 columns each: twice the filters for the same products.)
+  constexpr int D = 6;                       // taps of filters in flight (even)
+  const int ct = walk_round<PARTS>(tiles), dl_bytes = ct * DR * 128, p0 = r2 * 64, units = n16 * KW;
+  const unsigned char* const f0 = (const unsigned char*)g.wf + ((int64_t)(a.w_head_stride ? hkv * 4 : 0) + cg) * units * 1024;
+  bf16x8 fw[D];
+  float old[2][4];
+  const int prow = p0 + w * 8;               // what this lane adds up: rows prow + 4 lh .. + 3 of column 32 cg + l31
+  auto load_unit = [&](int u, bf16x8& f) { f = *(const bf16x8*)(f0 + (int64_t)min(u, units - 1) * 1024 + l * 16); };
+  auto sums_of = [&](int blk, int val) { return (val ? g.d_cache_v : g.d_cache_k) + blk * g.d_stride + (int64_t)ch * a.M * kD + cg * 32; };
+  // what does not wait for the chain: the first filters, and what the sums are added to
+  auto look_ahead = [&](int blk) {
+    phase();
+    const int m = max(blk ? a.M : a.m, 1);
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_unit(ct * 2 * KW * w / 8 + i, fw[i]);
+#pragma unroll
+    for (int val = 0; val < 2; ++val)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) old[val][i] = sums_of(blk, val)[min(prow + lh * 4 + i, m - 1) * kD + l31];
+  };
+  auto cache_rows = [&](int blk, int next, uint32_t target) -> bool {
+    const Block x = block_of(g, blk);
+    if (!await(chain_count, target)) return false;
+    if (p0 >= x.m) {
+      request_first(next);
+      return true;
+    }
+    phase();
+    f32x16 acc[2][2];                        // [keys, values][32 rows]
+#pragma unroll
+    for (int val = 0; val < 2; ++val) acc[val][0] = acc[val][1] = zero16();
+    const int64_t chain_planes = (int64_t)ch * tiles * g.P * 128;
+    for (int c = 0; c * ct < tiles; ++c) {
+      const int here = min(ct, tiles - c * ct), s_first = c * ct * 2, groups = here * 2;
+      const int64_t off = chain_planes + (int64_t)c * ct * g.P * 128;
+      if (c) __syncthreads();                // the rows of the tiles before are read
+      // rows of a plane, eight a request; those outside 0 .. T - 1 lie outside the buffer and read as zero
+      const int lr = l >> 3;
+      const uint32_t cell0 = (uint32_t)(lr * 128 + (((l & 7) ^ pswz(lr)) << 4));       // (rows 8 i + lr: i even; odd: ^ 32)
+      auto request_rows = [&](const uint16_t* planes, int pl, int first, int i, int at) {
+        const u32x4 r = make_rsrc((const unsigned char*)(planes + blk * g.plane_stride) + off + (int64_t)pl * g.P * 128, (uint32_t)x.T * 128);
+        load_to_lds(r, lds0 + (uint32_t)(at + i * 1024), (cell0 ^ (uint32_t)(i & 1) << 5) + (uint32_t)((first + i * 8) * 128));
+      };
+      // dl first; n and g, which the products with the taps do not need, come under these
+      const int per = DR / 8;
+      for (int i = w, pl = 0; i < here * per; i += 8) {
+        while (i >= (pl + 1) * per) ++pl;
+        request_rows(g.dl, pl, p0 - (KW - 1) + pad, i - pl * per, pl * DR * 128);
+      }
+      wait_loads<0>();
+      barrier();
+      for (int pl = 0; pl < here; ++pl) {
+        request_rows(g.wn, pl, p0, w, dl_bytes + pl * 8192);
+        if (PARTS == 3) request_rows(g.wn_low, pl, p0, w, dl_bytes + (ct + pl) * 8192);
+      }
+      bf16x8 fg[PARTS][2];
+      auto load_g = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < PARTS; ++u)
+#pragma unroll
+          for (int val = 0; val < 2; ++val)
+            fg[u][val] = *(const bf16x8*)(g.gsplit + (int64_t)blk * g.gsplit_stride +
+                                          ((((int64_t)u * a.batch * a.Hkv + ch) * n16 + s) * 8 + val * 4 + cg) * 512 + l * 8);
+      };
+      load_g(s_first + min(w, groups - 1));
+      // dl, this wave's share of the (slots, tap)
+      phase();
+      const int all = groups * KW, u0 = all * w / 8, u1 = all * (w + 1) / 8, base = s_first * KW;
+      int s = u0 / KW, t = u0 - s * KW;
+      bf16x8 fd[2][2][2];                    // [this unit, the next][high, low halves][32 rows]
+      auto rows_of = [&](int s, int t, bf16x8 (&f)[2][2]) {
+        const int r = l31 + KW - 1 - t, cell = (((s & 1) * 2 + lh) ^ pswz(r)) << 4;
+        const unsigned char* q = smem + ((s >> 1) * DR + r) * 128;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) {
+          f[0][rb] = *(const bf16x8*)(q + rb * 4096 + cell);
+          f[1][rb] = *(const bf16x8*)(q + rb * 4096 + (cell ^ 64));
+        }
+      };
+      rows_of(s, t, fd[0]);
+      auto unit = [&](int i) {
+        if (++t == KW) { t = 0; ++s; }
+        rows_of(min(s, groups - 1), t, fd[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) acc[0][rb] = mfma32(fd[i & 1][h][rb], fw[i], acc[0][rb]);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      int u = u0;
+      for (; u + D < u1; u += D)
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+          unit(i);
+          load_unit(base + u + i + D, fw[i]);
+        }
+#pragma unroll
+      for (int i = 0; i < D; ++i)            // (nothing more is asked for: what is on its way keeps its registers)
+        if (u + i < u1) unit(i);
+      // n g of slots 16 (s_first + gi) ..
+      auto mix = [&](int gi) {
+        const unsigned char* np = smem + dl_bytes + (gi >> 1) * 8192 + l31 * 128;
+        const int cell = (((gi & 1) * 2 + lh) ^ pswz(l31)) << 4;
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb, np += 4096) {
+          const bf16x8 fh = *(const bf16x8*)(np + cell), fl = *(const bf16x8*)(np + (cell ^ 64));
+          auto multiply = [&](const bf16x8& f, const bf16x8 (&v)[2]) {
+#pragma unroll
+            for (int val = 0; val < 2; ++val) acc[val][rb] = mfma32(f, v[val], acc[val][rb]);
+          };
+          multiply(fh, fg[1]);
+          if constexpr (PARTS == 3) multiply(fl, fg[1]);
+          multiply(fh, fg[0]);
+          multiply(fl, fg[0]);
+          if constexpr (PARTS == 3) {
+            multiply(*(const bf16x8*)(np + ct * 8192 + cell), fg[0]);          // the third part, [third | first]
+            multiply(fh, fg[2]);
+          }
+        }
+      };
+      phase();
+      wait_loads<0>();
+      barrier();
+      for (int gi = w; gi < groups; gi += 8) {
+        if (gi != w) load_g(s_first + gi);
+        mix(gi);
+      }
+      if ((c + 1) * ct < tiles) {
+        const int then = base + all, n_all = min(ct, tiles - (c + 1) * ct) * 2 * KW;
+#pragma unroll
+        for (int i = 0; i < D; ++i) load_unit(then + n_all * w / 8 + i, fw[i]);
+      }
+    }
+    // the eight partial sums of each output: a wave adds up four registers of each
+    phase();
+    f32x4* red = (f32x4*)smem + l;
+    barrier();
+#pragma unroll
+    for (int val = 0; val < 2; ++val)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const f32x16& v = acc[val][q / 4];
+        const int e = q % 4 * 4;
+        red[((w * 2 + val) * 8 + q) * 64] = f32x4{v[e], v[e + 1], v[e + 2], v[e + 3]};
+      }
+    request_first(next);
+    barrier();
+#pragma unroll
+    for (int val = 0; val < 2; ++val) {
+      f32x4 v = red[(val * 8 + w) * 64];
+#pragma unroll
+      for (int k = 1; k < 8; ++k) v += red[((k * 2 + val) * 8 + w) * 64];
+      float* at = sums_of(blk, val) + (prow + lh * 4) * kD + l31;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (prow + lh * 4 + i < x.m) at[i * kD] = old[val][i] + v[i];
+    }
+    return true;
+  };
+
+  for (int k = -1; k < wa.n; ++k) {
+    const int blk = wa.hi - k;
+    const bool now = tile < tiles && (k & 1) == half, next = tile < tiles && (k & 1) != half && k + 1 < wa.n;   // whose rows are its own
+    if (k >= 0 && now && !differentiate(blk, 4u * k)) return;
+    if (next) prepare(blk - 1);
+    if (k < 0) {
+      request_first(next ? blk - 1 : -1);
+      continue;
+    }
+    look_ahead(blk);
+    if (now) signal(chain_count);
+    if (!cache_rows(blk, next ? blk - 1 : -1, (uint32_t)(mine + tiles * (k + 1)))) return;
+    signal(rows_count);
+  }
+}
+
 // What a call starts with: the filters in the order bwd_dx_k's waves read them, and zeros from `zero` on
 __global__ void bwd_begin_k(StepArgs a, uint16_t* wf, int banks, u32x4* zero, int64_t zeros) {
   const int C = a.conv_in ? 2 * kD : kD, KW = a.k_width, n16 = (a.M + 15) / 16;
@@ -960,6 +1513,22 @@ hipError_t launch_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int ro
   return hipGetLastError();
 }
 
+template <int NT, int PARTS>
+hipError_t walk_kernel(const WalkArgs& wa, int grid, int n_cu, bool* resident, hipStream_t s) {
+  static bool lds_set = false;
+  const int lds = walk_lds<PARTS>(wa.c.st.M / 32, wa.c.st.k_width);
+  hipError_t e = allow_lds(bwd_walk_k<NT, PARTS>, 160 * 1024 - 1024, lds_set);
+  if (e != hipSuccess) return e;
+  int per_cu = 0;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)bwd_walk_k<NT, PARTS>, 512, lds);
+  if (e != hipSuccess) return e;
+  const int64_t limit = debug_options().max_resident > 0 ? debug_options().max_resident : (int64_t)per_cu * n_cu;
+  *resident = grid <= limit;
+  if (!*resident) return hipSuccess;
+  hipLaunchKernelGGL((bwd_walk_k<NT, PARTS>), dim3(grid), dim3(512), lds, s, wa);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, int conv_in, int banks, int64_t n_blk, bool with_logits,
@@ -1067,18 +1636,50 @@ static hipError_t launch_dx_tiles(const BwdConvArgs& g, int blk0, int n_blk, int
   const bool four_ways = (slots + 63) / 64 * 64 * 9 <= (slots + 127) / 128 * 128 * 8 && halves >= enough;
   return four_ways ? launch_dx<32, 64, 4, FINE>(g, blk0, n_blk, part, rows, s) : launch_dx<32, 64, 8, FINE>(g, blk0, n_blk, part, rows, s);
 }
+bool bwd_conv_three_parts(const BwdConvArgs& g, int i) {
+  const int64_t left = g.tokens - (int64_t)i * g.B;
+  return g.three_parts || ((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4 != 0;
+}
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  auto fine = [&](int i) {
-    const int64_t left = g.tokens - (int64_t)i * g.B;
-    return g.three_parts || ((i ? g.st.M : g.st.m) + (int)(left < g.B ? left : g.B)) % 4 != 0;
-  };
+  auto fine = [&](int i) { return bwd_conv_three_parts(g, i); };
   hipError_t e = hipSuccess;
   for (int i = blk0, n = 0; i < blk0 + n_blk && e == hipSuccess; i += n) {      // runs of blocks of one form
     for (n = 1; i + n < blk0 + n_blk && fine(i + n) == fine(i);) ++n;
     e = fine(i) ? launch_dx_tiles<true>(g, i, n, part, rows, s) : launch_dx_tiles<false>(g, i, n, part, rows, s);
   }
   return e;
+}
+
+// Which blocks the walk takes in one launch: whole slot tiles, Eq. 6 as a softmax over the keys' logits, all slots mixing, its
+// workgroups one to a compute unit at most.  Up to 256 slots and 512 positions: the launches it saves are less of a longer step (a
+// pass over 29 blocks of 100 tokens on 128 slots, 8 chains, 1101 -> 1021 us, 19 of 101 on 160 1033 -> 958, 14 of 200 on 256, 16 chains,
+// 1722 -> 1611; 9 of 256 on 288, 8 chains, 907 -> 908, 15 of 331 on 384 2173 -> 2161, 9 of 400 on 512 1658 -> 1699).
+bool bwd_conv_walk_takes(const BwdConvArgs& g) {
+  const StepArgs& a = g.st;
+  return a.M % 32 == 0 && a.norm == 0 && !a.conv_in && !a.protect && !g.d_conv_b && a.k_width <= 25 && a.M <= 256 && a.M + g.B <= 512 &&
+         (int64_t)a.batch * a.Hkv * ((a.M + 63) / 64 * 4) <= cu_count() && bwd_conv_defers_blocks(g);
+}
+hipError_t launch_bwd_conv_walk(const BwdConvArgs& g, int hi, int n, void* sync_ws, int spin_limit, bool through_l2, bool* taken,
+                                hipStream_t s) {
+  const StepArgs& a = g.st;
+  const int chains = a.batch * a.Hkv, tiles = a.M / 32;
+  WalkArgs wa;
+  wa.c = g;
+  wa.hi = hi;
+  wa.n = n;
+  wa.sync = (uint32_t*)sync_ws;
+  wa.status = (int32_t*)sync_ws + chains;
+  wa.tsync = (uint32_t*)sync_ws + 2 * chains + 1;
+  wa.spin_limit = spin_limit;
+  wa.same_l2_allowed = through_l2 ? 1 : 0;
+  const int grid = chains * ((tiles + 1) / 2 * 4), T = a.M + g.B;
+  auto go = [&](auto parts) {
+    constexpr int P = decltype(parts)::value;
+    if (T <= 256) return walk_kernel<1, P>(wa, grid, cu_count(), taken, s);
+    return walk_kernel<2, P>(wa, grid, cu_count(), taken, s);
+  };
+  return bwd_conv_three_parts(g, hi) ? go(std::integral_constant<int, 3>{}) : go(std::integral_constant<int, 2>{});
 }
 
 // A step alone fills the device with 128-row tiles: nothing is gained by leaving its block's rows for later.

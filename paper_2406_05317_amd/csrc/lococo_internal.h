@@ -12,7 +12,7 @@ namespace lococo {
 // Process-wide test and measurement hooks (lococo_debug_option); every field 0 by default.
 struct DebugOptions {
   int64_t spin_limit;         // polls a waiting workgroup makes before it gives up (0: the default)
-  int64_t scan_per_step;      // 1: one launch per compression step even where one launch per scan fits
+  int64_t scan_per_step;      // 1: launches per step even where one launch per scan, or per walk back through it, fits
   int64_t chain_sync_device;  // 1: the slot tiles of a chain always meet with device-scope release / acquire
   int64_t logits_tiles;       // 64 | 128 | 256: slots per workgroup of the Eq. 5 kernel of the unfused MFMA path
   int64_t max_resident;       // > 0: pretend that only this many workgroups of the scan kernel fit the GPU at once
@@ -339,6 +339,13 @@ hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s);
 hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s);
 hipError_t launch_bwd_conv_rows(const BwdConvArgs& g, int blk, int T, hipStream_t s);
 hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int part, int rows, hipStream_t s);
+// rows and dx (part 0) of the blocks hi, hi - 1, .. hi - n + 1, all of one form (bwd_conv_three_parts), in one launch that needs its
+// whole grid resident; *taken: whether it is (and was launched).  sync_ws, spin_limit, through_l2: as for launch_compress_scan,
+// cleared beforehand.  What a wait that gave up leaves in the status word: 1.
+bool bwd_conv_three_parts(const BwdConvArgs& g, int blk);
+bool bwd_conv_walk_takes(const BwdConvArgs& g);
+hipError_t launch_bwd_conv_walk(const BwdConvArgs& g, int hi, int n, void* sync_ws, int spin_limit, bool through_l2, bool* taken,
+                                hipStream_t s);
 // whether the rows of the blocks themselves are better taken together, after the walk
 bool bwd_conv_defers_blocks(const BwdConvArgs& g);
 hipError_t launch_bwd_conv_dw(const BwdConvArgs& g, hipStream_t s);
