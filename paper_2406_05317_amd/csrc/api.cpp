@@ -464,11 +464,12 @@ float* step_stats(const lococo_config* c, Path path, int32_t B, void* workspace,
 
 // Repack the filter bank into the workspace (MFMA path; once per call unless the caller says
 // the workspace already holds it).
-// sync_ws: see launch_repack_filters (fused MFMA path, filters not prepared).
-lococo_status enqueue_repack(const lococo_config* c, Path path, const StepArgs& a, void* ws, hipStream_t s, void* sync_ws = nullptr) {
+// sync_ws, fill: see launch_repack_filters (fused MFMA path, filters not prepared).
+lococo_status enqueue_repack(const lococo_config* c, Path path, const StepArgs& a, void* ws, hipStream_t s, void* sync_ws = nullptr,
+                             const StepArgs* fill = nullptr) {
   if (c->flags & LOCOCO_FLAG_FILTERS_PREPARED) return LOCOCO_OK;
   KTimer t(K_REPACK, s);
-  if (path == PATH_MFMA) HIP_TRY(launch_repack_filters(a, ws, filter_banks(c), sync_ws, s), "filter repack launch");
+  if (path == PATH_MFMA) HIP_TRY(launch_repack_filters(a, ws, filter_banks(c), sync_ws, s, fill), "filter repack launch");
   else HIP_TRY(launch_pack_filters_per_tap(a, filter_banks(c), ws, s), "filter packing launch");
   return LOCOCO_OK;
 }
@@ -548,7 +549,8 @@ lococo_status enqueue_update(const lococo_config* c, Path path, StepArgs a, loco
 // compute units.  `clear`: the counters have been used since they were zeroed (the status word is kept).
 lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_steps, int32_t B, int64_t tokens_left, void* out_k,
                            void* out_v, int64_t out_stride, int64_t slot0, int64_t ring, void* ws, bool clear, hipStream_t s,
-                           bool* taken, float* logits = nullptr, int64_t logits_stride = 0, int32_t logits_ld = 0) {
+                           bool* taken, float* logits = nullptr, int64_t logits_stride = 0, int32_t logits_ld = 0, void* last_k = nullptr,
+                           void* last_v = nullptr) {
   const bool capturing = stream_is_capturing(s);
   std::unique_lock<std::mutex> lk(g_scan_mu);
   *taken = capturing || !another_scan_in_flight(s);
@@ -571,6 +573,8 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
   sa.logits = logits;
   sa.logits_stride = logits_stride;
   sa.logits_ld = logits_ld;
+  sa.last_k = last_k;
+  sa.last_v = last_v;
   sa.spin_limit = spin_limit();
   sa.same_l2_allowed = chain_sync_through_l2() ? 1 : 0;
   {
@@ -584,16 +588,19 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
 
 // Steps hi, hi - 1, .. hi - n + 1 of the backward walk through a window in one launch, on the counters the scan that recomputed its
 // states has finished with (the status word is kept); *taken = false, and nothing launched, where its workgroups could not all be
-// resident.
-lococo_status enqueue_bwd_walk(const lococo_config* c, const BwdConvArgs& g, int hi, int n, void* ws, hipStream_t s, bool* taken) {
+// resident.  `cleared`: whether the counters are at zero.
+lococo_status enqueue_bwd_walk(const lococo_config* c, const BwdConvArgs& g, int hi, int n, void* ws, hipStream_t s, bool* cleared,
+                               bool* taken) {
   *taken = false;
   if (g_debug.scan_per_step) return LOCOCO_OK;
   const bool capturing = stream_is_capturing(s);
   std::unique_lock<std::mutex> lk(g_scan_mu);
   if (!capturing && another_scan_in_flight(s)) return LOCOCO_OK;
   char* sync_ws = (char*)ws + filter_ws_bytes(c);
-  HIP_TRY(launch_scan_sync_clear(sync_ws, c->batch, c->n_kv_heads, c->M, true, s), "clearing the scan counters");
+  if (!*cleared)
+    HIP_TRY(launch_scan_sync_clear(sync_ws, c->batch, c->n_kv_heads, c->M, true, s), "clearing the scan counters");
   HIP_TRY(launch_bwd_conv_walk(g, hi, n, sync_ws, spin_limit(), chain_sync_through_l2(), taken, s), "backward walk launch");
+  *cleared = !*taken;
   if (*taken && !capturing) note_scan_launched(s);
   return LOCOCO_OK;
 }
@@ -929,20 +936,6 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       return fail(LOCOCO_EWORKSPACE, "workspace needs %zu bytes, 256-byte aligned (got %zu)", need,
                   workspace ? ws_bytes : (size_t)0);
   }
-  lococo_cache tmp = *cache;
-  // the scan status of this call starts at "no wait gave up", whichever schedule runs
-  const bool clear = path == PATH_MFMA && workspace && ws_bytes >= step_ws_bytes(cfg, path, B);
-  const bool repack = any_compress && path != PATH_GENERIC && !(cfg->flags & LOCOCO_FLAG_FILTERS_PREPARED);
-  if (repack) {
-    StepArgs a0 = make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true);
-    if ((st = enqueue_repack(cfg, path, a0, workspace, (hipStream_t)stream,
-                             clear ? (char*)workspace + filter_ws_bytes(cfg) : nullptr)))
-      return st;
-  }
-  if (clear && !repack) {
-    HIP_TRY(launch_scan_sync_clear((char*)workspace + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false,
-                                   (hipStream_t)stream), "clearing the scan counters");
-  }
   int64_t n_compress = 0;
   for (const auto& sg : plan) n_compress += sg.branch;
   // Batched-attention schedules: run the fill / compress recurrence of a window of blocks first,
@@ -960,6 +953,34 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       for (int64_t g = std::min<int64_t>(n, 4096); g >= 2; --g)
         if (ws_bytes >= history_ws_bytes(cfg, path, B, g + 1, g * (int64_t)B)) { window = g; ring = g + 1; break; }
     }
+  }
+  lococo_cache tmp = *cache;
+  // the scan status of this call starts at "no wait gave up", whichever schedule runs
+  const bool clear = path == PATH_MFMA && workspace && ws_bytes >= step_ws_bytes(cfg, path, B);
+  const bool repack = any_compress && path != PATH_GENERIC && !(cfg->flags & LOCOCO_FLAG_FILTERS_PREPARED);
+  // the blocks from lo to before hi, all fills, as one
+  auto fill_args = [&](int64_t lo, int64_t hi) {
+    const lococo_seg& sg = plan[(size_t)lo];
+    const int64_t tokens = plan[(size_t)(hi - 1)].start + plan[(size_t)(hi - 1)].len - sg.start;
+    StepArgs a = make_args(cfg, seq, sg.start, (int32_t)tokens, &tmp, conv_w, conv_b, true);
+    a.m = sg.len_before;
+    a.new_k = tmp.k[tmp.cur];
+    a.new_v = tmp.v[tmp.cur];
+    return a;
+  };
+  int64_t filled = 0;                         // leading fill blocks that are behind us
+  if (repack) {
+    StepArgs a0 = make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true), f;
+    if (path == PATH_MFMA)
+      while (filled < std::min(n, window) && plan[(size_t)filled].branch == 0) ++filled;
+    if (filled) f = fill_args(0, filled);
+    if ((st = enqueue_repack(cfg, path, a0, workspace, (hipStream_t)stream,
+                             clear ? (char*)workspace + filter_ws_bytes(cfg) : nullptr, filled ? &f : nullptr)))
+      return st;
+  }
+  if (clear && !repack) {
+    HIP_TRY(launch_scan_sync_clear((char*)workspace + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false,
+                                   (hipStream_t)stream), "clearing the scan counters");
   }
   if (window > 0) {
     hipStream_t s = (hipStream_t)stream;
@@ -979,6 +1000,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
     const bool small_scan = path == PATH_GENERIC &&
                             small_scan_one_launch(cfg->dtype, cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
+    const bool direct = n_compress > 0 && plan.back().buf_after != tmp.cur;
     for (int64_t w0 = 0; w0 < n; w0 += window) {
       const int64_t w1 = std::min<int64_t>(n, w0 + window);
       // the state the window starts from: the caller's live buffer until the first compression
@@ -991,13 +1013,17 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
         const lococo_seg& sg = plan[(size_t)bi];
         StepArgs a = make_args(cfg, seq, sg.start, sg.len, &tmp, conv_w, conv_b, true);
         a.m = sg.len_before;
-        if (sg.branch == 0) {
-          a.new_k = tmp.k[tmp.cur];
-          a.new_v = tmp.v[tmp.cur];
+        if (sg.branch == 0) {                 // the fill blocks at the head of the window in one launch
+          bi = w0 + fills - 1;
+          if (bi < filled) continue;
           KTimer t(K_FILL, s);
-          HIP_TRY(launch_fill_generic(cfg->dtype, a, s), "fill launch");
+          HIP_TRY(launch_fill_generic(cfg->dtype, fill_args(w0, w0 + fills), s), "fill launch");
           continue;
         }
+        // The last state of all is nobody's but the caller's, and goes there at once where the attention that follows does not
+        // read the buffer: where that is not the one the call found the cache in.
+        void* const last_k = direct ? tmp.k[plan.back().buf_after] : nullptr;
+        void* const last_v = direct ? tmp.v[plan.back().buf_after] : nullptr;
         a.cache_k = c_done == 0 ? tmp.k[tmp.cur] : slot_k(c_done - 1);
         a.cache_v = c_done == 0 ? tmp.v[tmp.cur] : slot_v(c_done - 1);
         if (one_launch) {
@@ -1005,7 +1031,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
           // them all, the slot tiles of a chain handing the new cache to each other through the ring
           // (the counters start every launch at zero)
           if ((st = enqueue_scan(cfg, a, w1 - bi, B, L - sg.start, hist_k, hist_v, hist_stride, c_done % ring, ring, workspace,
-                                 c_done > 0, s, &one_launch)))
+                                 c_done > 0, s, &one_launch, nullptr, 0, 0, w1 == n ? last_k : nullptr, w1 == n ? last_v : nullptr)))
             return st;
           if (one_launch) {
             c_done += w1 - bi;
@@ -1015,12 +1041,14 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
         if (small_scan) {                // one workgroup per chain walks the rest of the window
           KTimer t(K_COMPRESS_SMALL, s);
           HIP_TRY(launch_compress_small(cfg->dtype, a, cfg->M + B, (int)(w1 - bi), B, L - sg.start, hist_k, hist_v, hist_stride,
-                                        (int)(c_done % ring), (int)ring, s), "compress scan launch");
+                                        (int)(c_done % ring), (int)ring, s, w1 == n ? last_k : nullptr, w1 == n ? last_v : nullptr),
+                  "compress scan launch");
           c_done += w1 - bi;
           break;
         }
-        a.new_k = slot_k(c_done);
-        a.new_v = slot_v(c_done);
+        const bool to_caller = direct && c_done + 1 == n_compress;
+        a.new_k = to_caller ? last_k : slot_k(c_done);
+        a.new_v = to_caller ? last_v : slot_v(c_done);
         if ((st = enqueue_compress(cfg, path, a, workspace, B, s))) return st;
         ++c_done;
       }
@@ -1079,7 +1107,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
       }
     }
     const lococo_seg& last = plan.back();
-    if (c_done > 0) {
+    if (c_done > 0 && !direct) {
       HIP_TRY(launch_copy_pair(tmp.k[last.buf_after], slot_k(c_done - 1), tmp.v[last.buf_after], slot_v(c_done - 1),
                                state_bytes(cfg), s),
               "publishing the final cache");
@@ -1195,7 +1223,7 @@ lococo_status enqueue_step_backward(const lococo_config* cfg, BwdArgs g, bool co
   c.d_conv_w = g.d_conv_w;
   c.d_conv_b = g.d_conv_b;
   bwd_conv_place(&c, conv_layout(cfg, T, 1, l.one_filters), ws + l.conv);
-  HIP_TRY(launch_bwd_conv_begin(c, true, s), "filter packing launches");
+  HIP_TRY(launch_bwd_conv_begin(c, true, nullptr, s), "filter packing launches");
   HIP_TRY(launch_bwd_conv_logits(c, s), "conv launch");
   HIP_TRY(launch_bwd_conv_rows(c, 0, T, s), "row gradient launch");
   HIP_TRY(launch_bwd_conv_dx(c, 0, 1, 2, T, s), "input gradient launch");
@@ -1465,22 +1493,32 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
   lococo_cache fc = *cache0;
   fc.cur = 0;
   fc.attn_colsum = nullptr;
-  HIP_TRY(launch_copy_pair(state_k(0), cache0->k[cache0->cur], state_v(0), cache0->v[cache0->cur], state, s),
-          "copying the first state");
-  if (path == PATH_MFMA)
+  if (cache0->len > 0)
+    HIP_TRY(launch_copy_pair(state_k(0), cache0->k[cache0->cur], state_v(0), cache0->v[cache0->cur], state, s),
+            "copying the first state");
+  // (on the fused path the filters' launch clears the counters and appends the leading fill blocks, where there is one)
+  const bool folds = path == PATH_MFMA && n_fill + 1 < n;
+  if (path == PATH_MFMA && !folds)
     HIP_TRY(launch_scan_sync_clear(ws + l.fwd_ws + filter_ws_bytes(cfg), cfg->batch, cfg->n_kv_heads, cfg->M, false, s),
             "clearing the scan counters");
   bool have_logits = false;                                  // the scan leaves them
-  for (int64_t i = 0; i + 1 < n; ++i) {                      // (the last block's own update is not needed)
+  for (int64_t i = folds ? n_fill : 0; i + 1 < n; ++i) {                      // (the last block's own update is not needed)
     const lococo_seg& sg = plan[(size_t)i];
     fc.k[0] = state_k(i); fc.k[1] = state_k(i + 1);
     fc.v[0] = state_v(i); fc.v[1] = state_v(i + 1);
     fc.cur = 0;
+    if (folds && i == n_fill) fc.len = sg.len_before;
     lococo_qkvo blk = *seq;
     blk.o = blk.q;                                           // (never written)
     const StepArgs a = make_args(cfg, &blk, sg.start, sg.len, &fc, conv_w, conv_b, true);
     if (i == n_fill && path != PATH_GENERIC) {               // the first block that compresses
-      if ((st = enqueue_repack(cfg, path, a, ws + l.fwd_ws, s))) return st;
+      StepArgs f = make_args(cfg, &blk, 0, (int32_t)sg.start, &fc, conv_w, conv_b, true);
+      f.m = cache0->len;
+      f.new_k = state_k(0);
+      f.new_v = state_v(0);
+      if ((st = enqueue_repack(cfg, path, a, ws + l.fwd_ws, s, folds ? ws + l.fwd_ws + filter_ws_bytes(cfg) : nullptr,
+                               folds && i ? &f : nullptr)))
+        return st;
       bool taken = path == PATH_MFMA && scan_fits_one_launch(cfg, a);
       const bool keep = l.keep_logits && compress_scan_leaves_logits(a.protect != nullptr, cfg->conv_in, false);
       if (taken && (st = enqueue_scan(cfg, a, n - i - (keep ? 0 : 1), B, L - sg.start, ws + l.states_k, ws + l.states_v,
@@ -1527,7 +1565,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
     }
   }
   const int64_t G = batched ? l.window : n;
-  bool conv_begun = false;
+  bool conv_begun = false, walk_clear = false;       // the walk's counters are at zero
   int w = 1;
   for (int64_t w1 = n; w1 > 0;) {
     const int64_t w0 = std::max<int64_t>(0, w1 - G);
@@ -1590,7 +1628,11 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
         c.d_conv_b = d_conv_b;
         bwd_conv_place(&c, l.conv, ws + l.step_ws);
         if (l.keep_logits) c.logits = (float*)(ws + l.logits) + w_steps * c.logits_stride;
-        if (!conv_begun) HIP_TRY(launch_bwd_conv_begin(c, !have_logits, s), "filter packing launches");
+        if (!conv_begun) {
+          walk_clear = path == PATH_MFMA && bwd_conv_walk_takes(c);
+          HIP_TRY(launch_bwd_conv_begin(c, !have_logits, walk_clear ? ws + l.fwd_ws + filter_ws_bytes(cfg) : nullptr, s),
+                  "filter packing launches");
+        }
         conv_begun = true;
         if (first.len_before < cfg->M) {       // the rows no entry was live in: zero
           BwdArgs g{};
@@ -1607,7 +1649,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
           if (path == PATH_MFMA && bwd_conv_walk_takes(c))
             while (run <= i && bwd_conv_three_parts(c, i - run) == bwd_conv_three_parts(c, i)) ++run;
           bool taken = false;
-          if (run > 1 && (st = enqueue_bwd_walk(cfg, c, i, run, ws + l.fwd_ws, s, &taken))) return st;
+          if (run > 1 && (st = enqueue_bwd_walk(cfg, c, i, run, ws + l.fwd_ws, s, &walk_clear, &taken))) return st;
           if (taken) {
             i -= run - 1;
             continue;

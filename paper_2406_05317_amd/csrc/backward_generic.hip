@@ -304,16 +304,22 @@ __global__ __launch_bounds__(kThreads) void bwd_zero_dead_rows_k(BwdArgs g) {
   }
 }
 
-// ---- fill branch: new cache = [cache ; block], so its gradient goes straight through
+// ---- fill branch: new cache = [cache ; block], so its gradient goes straight through; rows that were not live before: zero
 __global__ __launch_bounds__(kThreads) void bwd_fill_k(BwdArgs g) {
   const StepArgs& a = g.st;
   const int ch = blockIdx.y, Tn = a.m + a.Bn;
-  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < (int64_t)Tn * a.d;
+  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < (int64_t)a.M * a.d;
        e += (int64_t)gridDim.x * kThreads) {
     const int j = (int)(e / a.d), c = (int)(e % a.d);
     const int64_t at = ((int64_t)ch * a.M + j) * a.d + c;
-    grad_row(g.d_cache_k, g.d_k, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_k[at];
-    grad_row(g.d_cache_v, g.d_v, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_v[at];
+    if (j < Tn) {
+      grad_row(g.d_cache_k, g.d_k, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_k[at];
+      grad_row(g.d_cache_v, g.d_v, a.M, a.d, a.m, g.kv_chain, ch, j)[c] += g.d_new_v[at];
+    }
+    if (j >= a.m) {
+      g.d_cache_k[at] = 0.f;
+      g.d_cache_v[at] = 0.f;
+    }
   }
 }
 
@@ -630,7 +636,7 @@ hipError_t run(const BwdArgs& g, bool compress, hipStream_t s) {
                          dim3(kThreads), 0, s, g);
     }
   }
-  if (a.m < a.M) hipLaunchKernelGGL(bwd_zero_dead_rows_k, dim3(64, chains), dim3(kThreads), 0, s, g);
+  if (compress && a.m < a.M) hipLaunchKernelGGL(bwd_zero_dead_rows_k, dim3(64, chains), dim3(kThreads), 0, s, g);
   if (!compress) {
     hipLaunchKernelGGL(bwd_fill_k, dim3(64, chains), dim3(kThreads), 0, s, g);
     return hipGetLastError();

@@ -1273,8 +1273,14 @@ __global__ __launch_bounds__(512, 2) void bwd_walk_k(WalkArgs wa) {
   }
 }
 
-// What a call starts with: the filters in the order bwd_dx_k's waves read them, and zeros from `zero` on
-__global__ void bwd_begin_k(StepArgs a, uint16_t* wf, int banks, u32x4* zero, int64_t zeros) {
+// What a call starts with: the filters in the order bwd_dx_k's waves read them, zeros from `zero` on, and the walk's counters (null:
+// not its business)
+__global__ void bwd_begin_k(StepArgs a, uint16_t* wf, int banks, u32x4* zero, int64_t zeros, uint32_t* sync) {
+  if (sync && blockIdx.x == 0) {             // (see WalkArgs: the status word and the masks of the scan in between are kept)
+    const int chains = a.batch * a.Hkv, words = 2 * chains * (a.M / 32);
+    for (int i = threadIdx.x; i < chains; i += blockDim.x) sync[i] = 0u;
+    for (int i = threadIdx.x; i < words; i += blockDim.x) sync[2 * chains + 1 + i] = 0u;
+  }
   const int C = a.conv_in ? 2 * kD : kD, KW = a.k_width, n16 = (a.M + 15) / 16;
   const int64_t step = (int64_t)gridDim.x * blockDim.x, n = (int64_t)banks * (C / 32) * n16 * KW * 64;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += step) {
@@ -1575,7 +1581,7 @@ void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws) {
   g->P = l.P;
 }
 
-hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s) {
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, void* walk_sync_ws, hipStream_t s) {
   const StepArgs& a = g.st;
   const size_t n = (size_t)g.banks * a.k_width * a.M * (a.conv_in ? 2 * kD : kD);
   const bool one_filters = g.wf == g.wt;     // (then launch_bwd_conv_logits packs them)
@@ -1586,7 +1592,7 @@ hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStrea
   // the page of zeros lies right before the sums (n is a multiple of 4)
   const int64_t zeros = ((char*)(g.dwt + n) - (char*)g.zero_page) / 16;
   hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((zeros + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf,
-                     one_filters ? 0 : g.banks, (u32x4*)g.zero_page, zeros);
+                     one_filters ? 0 : g.banks, (u32x4*)g.zero_page, zeros, (uint32_t*)walk_sync_ws);
   return hipGetLastError();
 }
 
@@ -1601,7 +1607,7 @@ hipError_t launch_bwd_conv_logits(const BwdConvArgs& g, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int64_t n = (int64_t)g.banks * (a.conv_in ? 2 : 1) * (kD / 32) * ((a.M + 15) / 16) * a.k_width * 64;
   hipLaunchKernelGGL(bwd_begin_k, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, s, a, g.wf, g.banks,
-                     (u32x4*)g.zero_page, 0);
+                     (u32x4*)g.zero_page, 0, (uint32_t*)nullptr);
   return hipGetLastError();
 }
 

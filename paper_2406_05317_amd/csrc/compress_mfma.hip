@@ -34,15 +34,27 @@ struct Build {
 // [M][C][k] per bank -> register order (see compress_mfma_k); one thread per 16-byte chunk.  C = 128,
 // or 256 ([K | V] filters): then a bank is its key half (channels 0..127 of every slot) in that
 // order followed by its value half.
-// Also zeroes what a scan starts with, where the call wants both: a launch less in front of the scan (in whole calls it does not
-// show: 3.5 K tokens, M = 128, take 318 us either way).
+// Also zeroes what a scan starts with, and appends the blocks the cache has room for (workgroups from `fill_from` on, whole 16
+// bytes at a time), where the call wants these: nothing of the three waits for the others, and a launch that does costs 3 - 4 us.
 __global__ void repack_filters_k(const uint16_t* w, uint16_t* wp, int M, int C, int KW, int banks,
-                                 int64_t w_head_stride, uint32_t* zero, int n_zero, uint32_t* zero2, int n_zero2) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += gridDim.x * blockDim.x) zero[i] = 0u;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero2; i += gridDim.x * blockDim.x) zero2[i] = 0u;
+                                 int64_t w_head_stride, uint32_t* zero, int n_zero, uint32_t* zero2, int n_zero2, StepArgs f, int fill_from) {
+  if ((int)blockIdx.x >= fill_from) {
+    const int64_t per = (int64_t)f.Bn * 16, n = per * f.batch * f.Hkv, step = (int64_t)(gridDim.x - fill_from) * blockDim.x;
+    for (int64_t e = (int64_t)(blockIdx.x - fill_from) * blockDim.x + threadIdx.x; e < n; e += step) {
+      const int ch = (int)(e / per), r = (int)(e % per), t = r >> 4, c = (r & 15) * 8, b = ch / f.Hkv, h = ch % f.Hkv;
+      const int64_t to = ((int64_t)ch * f.M + f.m + t) * kD + c;
+      const u32x4 k = *(const u32x4*)((const uint16_t*)f.k.p + b * f.k.sb + h * f.k.sh + t * f.k.st + c);
+      const u32x4 v = *(const u32x4*)((const uint16_t*)f.v.p + b * f.v.sb + h * f.v.sh + t * f.v.st + c);
+      *(u32x4*)((uint16_t*)f.new_k + to) = k;
+      *(u32x4*)((uint16_t*)f.new_v + to) = v;
+    }
+    return;
+  }
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += fill_from * blockDim.x) zero[i] = 0u;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_zero2; i += fill_from * blockDim.x) zero2[i] = 0u;
   const int64_t chunks_per_bank = (int64_t)M * KW * (C / 8);
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < chunks_per_bank * banks;
-       e += (int64_t)gridDim.x * blockDim.x) {
+       e += (int64_t)fill_from * blockDim.x) {
     const int bank = (int)(e / chunks_per_bank);
     int64_t r = e % chunks_per_bank;
     const int lane = (int)(r % 64); r /= 64;
@@ -181,15 +193,17 @@ size_t compress_prelogits_bytes(int batch, int Hkv, int M, int B, int conv_in, i
 
 static uint32_t* psync_of(void* sync_ws, int batch, int Hkv) { return (uint32_t*)sync_ws + 2 * batch * Hkv + 1; }
 
-hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s) {
+hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s, const StepArgs* fill) {
   const int C = a.conv_in ? 2 * kD : kD;
   const int64_t n = (int64_t)banks * a.M * (C / 8) * a.k_width;   // 16-byte chunks
   int blocks = (int)((n + 255) / 256);
   if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(repack_filters_k, dim3(blocks), dim3(256), 0, s, (const uint16_t*)a.conv_w,
+  const int64_t rows16 = fill ? (int64_t)fill->Bn * 16 * fill->batch * fill->Hkv : 0;
+  const int fills = (int)(rows16 < 256 * 4096 ? (rows16 + 255) / 256 : 4096);
+  hipLaunchKernelGGL(repack_filters_k, dim3(blocks + fills), dim3(256), 0, s, (const uint16_t*)a.conv_w,
                      (uint16_t*)wp, a.M, C, a.k_width, banks, a.w_head_stride, (uint32_t*)sync_ws,
                      sync_ws ? 2 * a.batch * a.Hkv + 1 : 0, sync_ws ? psync_of(sync_ws, a.batch, a.Hkv) : nullptr,
-                     sync_ws ? 2 * a.batch * a.Hkv * (a.M / 32) : 0);
+                     sync_ws ? 2 * a.batch * a.Hkv * (a.M / 32) : 0, fill ? *fill : a, blocks);
   return hipGetLastError();
 }
 
@@ -236,6 +250,7 @@ hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, in
   sa.status = nullptr;
   sa.logits = nullptr;
   sa.logits_stride = sa.logits_ld = 0;
+  sa.last_k = sa.last_v = nullptr;
   sa.spin_limit = 0;
   sa.same_l2_allowed = debug_options().chain_sync_device ? 0 : 1;   // (only the hand-off of a split step looks at it here)
   // more (chain, tile) pairs than compute units: one resident workgroup per compute unit, each

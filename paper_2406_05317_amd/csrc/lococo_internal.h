@@ -84,6 +84,8 @@ struct ScanArgs {
   float* logits;             // not null: the logits of the steps are left there, rows of logits_ld floats [chains, M], steps
   int64_t logits_stride;     // logits_stride floats apart (compress_scan_leaves_logits)
   int32_t logits_ld;
+  void* last_k;              // not null: where the last step writes its state, in place of its slot
+  void* last_v;
 };
 
 // Arguments of the MFMA attention kernel: one block, or every block of a scan
@@ -167,8 +169,10 @@ bool small_step_fits(int T, int M, int d, int k, int conv_in);
 bool small_scan_one_launch(int dtype, int T, int M, int d, int k, int conv_in);
 // n_steps consecutive compress steps (n_steps > 1 only where small_scan_one_launch), step 0 described by `a`, step s
 // taking the block s*B tokens further on (fewer where tokens_left runs out) and writing state (slot0 + s) % ring
+// last_k / last_v: null, or where the last step writes its state, in place of its slot
 hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_steps, int B, int64_t tokens_left, void* out_k,
-                                 void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s);
+                                 void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s, void* last_k = nullptr,
+                                 void* last_v = nullptr);
 // attention of the blocks of a window, a wave per query row; T: the most positions of a block
 bool attn_rows_fits(int T, int d);
 hipError_t launch_attn_rows(int dtype, const AttnArgs& a, int d, float* colsum, hipStream_t s);
@@ -188,7 +192,8 @@ size_t compress_mfma_filter_bytes(int M, int conv_width, int conv_in, int banks)
 size_t compress_prelogits_bytes(int batch, int Hkv, int M, int B, int conv_in, int n_cu);
 // conv_w [M][C][k] (+ w_head_stride per bank) -> wp [bank][M][k][C]
 // sync_ws: null, or the scan's counters and status word, which the same launch then zeroes (see launch_scan_sync_clear)
-hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s);
+// fill: null, or blocks to append to the cache in the same launch (k / v, new_k / new_v, m, Bn)
+hipError_t launch_repack_filters(const StepArgs& a, void* wp, int banks, void* sync_ws, hipStream_t s, const StepArgs* fill = nullptr);
 // Eq. 5 + Eq. 6 + Eq. 4a/4b in one kernel; writes a.new_k / a.new_v
 // sync_ws / partials: compress_scan_sync_bytes() / compress_partials_bytes() of device memory
 // prelogits: compress_prelogits_bytes(.., B, ..) of device memory, B >= a.Bn
@@ -332,7 +337,8 @@ BwdConvLayout bwd_conv_layout(int batch, int Hkv, int M, int T, int conv_width, 
                               bool one_filters);
 void bwd_conv_place(BwdConvArgs* g, const BwdConvLayout& l, void* ws);
 // once per call: filters packed, sums and zeros cleared; at its end: the sums added to d_conv_w
-hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, hipStream_t s);    // (for launch_bwd_conv_logits, too)
+// (for_logits: for launch_bwd_conv_logits, too; walk_sync_ws: null, or the counters launch_bwd_conv_walk finds cleared then)
+hipError_t launch_bwd_conv_begin(const BwdConvArgs& g, bool for_logits, void* walk_sync_ws, hipStream_t s);
 hipError_t launch_bwd_conv_end(const BwdConvArgs& g, hipStream_t s);
 // the logits of all blocks; then, from the last block to the first, rows and dx (part 0: cache rows; 1: the rows of the
 // blocks themselves, blocks blk0 .. blk0 + n_blk - 1; 2: both; `rows`: the most rows of one of them); then dw of all blocks

@@ -115,6 +115,7 @@ struct SmallArgs {
   int64_t out_stride;     // elements between states
   int slot0, ring;
   int T;                  // the most positions of a step
+  void* last_k; void* last_v;   // not null: where the last step writes its state, in place of its slot
   SmallLayout l;
 };
 
@@ -326,8 +327,9 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
     __syncthreads();                                       // every read of the old rows is done
     const int64_t state = (int64_t)slot * g.out_stride + (int64_t)ch * M * d;
     if (++slot == g.ring) slot = 0;
-    T* ok = (T*)g.out_k + state;
-    T* ov = (T*)g.out_v + state;
+    const bool last = !more && g.last_k;
+    T* ok = last ? (T*)g.last_k + (int64_t)ch * M * d : (T*)g.out_k + state;
+    T* ov = last ? (T*)g.last_v + (int64_t)ch * M * d : (T*)g.out_v + state;
 #pragma unroll
     for (int n = 0; n < MIX; ++n) {
       const int u = w + n * kNW;
@@ -489,7 +491,7 @@ __global__ __launch_bounds__(kNT) void compress64_k(SmallArgs g) {
   const bool val = w >= 4;                   // Eq. 4: wave w the columns 16 w .. of [K | V]
   const int col = (w & 3) * 16 + l15;
   float* const rows = val ? Vs + col : Xs + pad * kSx + col;             // row j, this lane's column: + j * kSx
-  float* const states = (float*)(val ? g.out_v : g.out_k) + ((int64_t)ch * M + i0 + lk * 4) * k64 + col;
+  const int64_t mine = ((int64_t)ch * M + i0 + lk * 4) * k64 + col;      // of a state: this lane's first element
   // where this lane's first rows of a block come from (items w, w + 8, ..: all of one array) and go to
   const int64_t st = w & 1 ? a.v.st : a.k.st;
   const float* from = (w & 1 ? vb : kb) + (g.B + (w >> 1) * 4 + lr) * st + lc;
@@ -656,7 +658,7 @@ __global__ __launch_bounds__(kNT) void compress64_k(SmallArgs g) {
       if (p < n16) some(std::integral_constant<int, 1>{});
     }
     lds_barrier();                           // every read of the old rows is done
-    float* const out = states + (int64_t)slot * g.out_stride;
+    float* const out = (!more && g.last_k ? (float*)(val ? g.last_v : g.last_k) : (float*)(val ? g.out_v : g.out_k) + (int64_t)slot * g.out_stride) + mine;
     if (++slot == g.ring) slot = 0;
 #pragma unroll
     for (int st = 0; st < TL; ++st) {
@@ -878,8 +880,10 @@ bool small_scan_one_launch(int dtype, int T, int M, int d, int k, int conv_in) {
 }
 
 hipError_t launch_compress_small(int dtype, const StepArgs& a, int T, int n_steps, int B, int64_t tokens_left, void* out_k,
-                                 void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s) {
+                                 void* out_v, int64_t out_stride, int slot0, int ring, hipStream_t s, void* last_k, void* last_v) {
   SmallArgs g;
+  g.last_k = last_k;
+  g.last_v = last_v;
   g.st = a;
   g.n_steps = n_steps;
   g.B = B;

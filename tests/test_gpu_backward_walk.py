@@ -77,6 +77,7 @@ CASES = [
     dict(M=224, B=224, L=1000, kv=4, heads=8),                                # one round of seven, a half-empty pair
     dict(M=256, B=256, L=1400, kv=8, heads=8, batch=2),                       # the largest; the last block in parts of its own
     dict(M=256, B=255, L=1300, len0=3, width=21),                             # three parts, three live slots
+    dict(M=96, B=20, L=330, kv=4, heads=4),                                   # four fill blocks in the filters' launch
     dict(M=64, B=200, L=900),                                                 # blocks longer than the cache, an empty first state
 ]
 

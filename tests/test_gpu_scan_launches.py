@@ -1,0 +1,47 @@
+"""What a scan no longer launches on its own: leading fill blocks go with the filters, the last state goes straight to the caller's
+buffer where the attention behind the scan does not read it.  Bit for bit against the step-by-step schedule."""
+import pytest
+import torch
+
+from paper_2406_05317_amd import binding as lb
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float32, 64)], ids=["bf16", "f32"])
+@pytest.mark.parametrize("cur", [0, 1])
+@pytest.mark.parametrize("case", [
+    dict(M=96, B=20, L=20 * 4),                  # fill blocks alone
+    dict(M=96, B=20, L=20 * 5),                  # one compression
+    dict(M=96, B=20, L=20 * 6),                  # two: the last state lands in the buffer the first one came from
+    dict(M=96, B=20, L=20 * 7 + 3),              # three and a short block
+    dict(M=32, B=7, L=60, len0=9),               # live slots ahead of the fills
+    dict(M=64, B=64, L=64 * 3, len0=64),         # none to fill
+    dict(M=64, B=16, L=16 * 9, history=3),       # windows of three blocks, fills across two of them
+    dict(M=64, B=16, L=16 * 10, history=3),
+], ids=str)
+def test_schedules_leave_the_same_bits(case, cur, dtype, d):
+    c = dict(dict(len0=0, history=1), **case)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    b, hq, hkv, M, L = 2, 4, 2, c["M"], c["L"]
+    rnd = lambda *s: torch.empty(s, dtype=dtype, device=DEV).normal_(0, 0.3, generator=g)
+    wide = rnd(b, L, hq + 2 * hkv, d)            # token-major, as a projection leaves them: heads d apart, tokens (hq + 2 hkv) d
+    q, k, v = (wide[:, :, i:j].transpose(1, 2) for i, j in ((0, hq), (hq, hq + hkv), (hq + hkv, hq + 2 * hkv)))
+    w, ck, cv = rnd(M, d, 15) * 0.2, rnd(b, hkv, M, d), rnd(b, hkv, M, d)
+    cfg = lb.make_config(dtype=dtype, batch=b, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, M=M, conv_width=15)
+    got = []
+    for history in (c["history"], 0):
+        cache = lb.Cache(cfg, DEV)
+        cache.c.cur = cur
+        cache.load(ck, cv, c["len0"])
+        assert cache.cur == cur
+        o = torch.full((b, hq, L, d), float("nan"), dtype=dtype, device=DEV)
+        ws = lb.workspace(cfg, L, c["B"], history, DEV)
+        lb.lococo_sequence_forward(cfg, q, k, v, o, w, None, cache, c["B"], ws)
+        torch.cuda.synchronize()
+        got.append((o, cache.k[:, :, :cache.len].clone(), cache.v[:, :, :cache.len].clone(), cache.len, cache.cur))
+    assert got[0][3:] == got[1][3:]
+    for x, y in zip(got[0][:3], got[1][:3]):
+        assert torch.isfinite(x.float()).all() and torch.equal(x, y)
