@@ -573,8 +573,13 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
   sa.logits = logits;
   sa.logits_stride = logits_stride;
   sa.logits_ld = logits_ld;
-  sa.last_k = last_k;
-  sa.last_v = last_v;
+  sa.last_k = n_steps > 1 ? last_k : nullptr;
+  sa.last_v = n_steps > 1 ? last_v : nullptr;
+  if (last_k && n_steps == 1) {
+    sa.out_k = last_k;
+    sa.out_v = last_v;
+    sa.slot0 = 0;
+  }
   sa.spin_limit = spin_limit();
   sa.same_l2_allowed = chain_sync_through_l2() ? 1 : 0;
   {
@@ -1000,7 +1005,9 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
     const bool small_scan = path == PATH_GENERIC &&
                             small_scan_one_launch(cfg->dtype, cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
-    const bool direct = n_compress > 0 && plan.back().buf_after != tmp.cur;
+    // (scans over [K | V] run on the kernel of two roles, which single steps of 17 us share: with the choice of where to write in
+    // it these took 0.4 us longer, so their last state is copied)
+    const bool direct = n_compress > 0 && plan.back().buf_after != tmp.cur && !(path == PATH_MFMA && cfg->conv_in);
     for (int64_t w0 = 0; w0 < n; w0 += window) {
       const int64_t w1 = std::min<int64_t>(n, w0 + window);
       // the state the window starts from: the caller's live buffer until the first compression

@@ -564,10 +564,6 @@ __device__ __forceinline__ void compress_roles(const ScanArgs& sa, const uint16_
     // (after the second walk of a [K | V] bank the accumulator's first d columns are the value rows)
     nk = (uint16_t*)(CIN ? sa.out_v : sa.out_k) + out_at;
     nv = (uint16_t*)(CIN ? sa.out_k : sa.out_v) + out_at;
-    if (sa.last_k && step + 1 == sa.n_steps) {
-      nk = (uint16_t*)(CIN ? sa.last_v : sa.last_k) + ((int64_t)ch * a.M + i0) * kD;
-      nv = (uint16_t*)(CIN ? sa.last_k : sa.last_v) + ((int64_t)ch * a.M + i0) * kD;
-    }
   }
   if constexpr (PSPLIT) {
     // ---- this part's result goes to the workspace: accumulators [slot][2 d] as they are

@@ -711,7 +711,7 @@
     const int64_t out_at = (int64_t)((sa.slot0 + step) % sa.ring) * sa.out_stride + ((int64_t)ch * a.M + i0) * kD;
     nk = (uint16_t*)sa.out_k + out_at;
     nv = (uint16_t*)sa.out_v + out_at;
-    if (sa.last_k && step + 1 == sa.n_steps) {
+    if (step > 0 && step + 1 == sa.n_steps && sa.last_k) {     // (a single step looks no further)
       nk = (uint16_t*)sa.last_k + ((int64_t)ch * a.M + i0) * kD;
       nv = (uint16_t*)sa.last_v + ((int64_t)ch * a.M + i0) * kD;
     }

@@ -84,7 +84,7 @@ struct ScanArgs {
   float* logits;             // not null: the logits of the steps are left there, rows of logits_ld floats [chains, M], steps
   int64_t logits_stride;     // logits_stride floats apart (compress_scan_leaves_logits)
   int32_t logits_ld;
-  void* last_k;              // not null: where the last step writes its state, in place of its slot
+  void* last_k;              // not null: where the last of several steps writes its state, in place of its slot
   void* last_v;
 };
 
