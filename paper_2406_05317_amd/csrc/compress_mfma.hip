@@ -250,15 +250,18 @@ hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, in
   sa.status = nullptr;
   sa.logits = nullptr;
   sa.logits_stride = sa.logits_ld = 0;
-  sa.last_k = sa.last_v = nullptr;
   sa.spin_limit = 0;
   sa.same_l2_allowed = debug_options().chain_sync_device ? 0 : 1;   // (only the hand-off of a split step looks at it here)
   // more (chain, tile) pairs than compute units: one resident workgroup per compute unit, each
   // taking several chains on one load of its filter slice (nothing to wait for within one step)
   sa.groups = compress_scan_groups(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, a.w_head_stride != 0 || a.b_head_stride != 0, n_cu);
   if (sa.groups <= 0) sa.groups = a.batch * a.Hkv;
-  sa.prelogits = (float*)prelogits;
-  sa.pre_stride = prelogits_stride(a.M, B > a.Bn ? B : a.Bn);
+  if (a.conv_in) {
+    sa.prelogits = (float*)prelogits;
+    sa.pre_stride = prelogits_stride(a.M, B > a.Bn ? B : a.Bn);
+  } else {
+    sa.last_k = sa.last_v = nullptr;
+  }
   // fewer than half as many: the positions of the step are shared out between several workgroups,
   // whose count per (chain, tile) starts at zero
   sa.psplit = sa.groups < a.batch * a.Hkv ? 1 : position_split(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu);
@@ -325,8 +328,10 @@ hipError_t launch_compress_scan(const ScanArgs& a_in, const void* wp, int banks,
   a.status = (int32_t*)sync_ws + chains;
   a.groups = compress_scan_groups(a.st.batch, a.st.Hkv, a.st.M, a.st.k_width, a.st.conv_in,
                                   a.st.w_head_stride != 0 || a.st.b_head_stride != 0, n_cu);
-  a.prelogits = (float*)prelogits;
-  a.pre_stride = prelogits_stride(a.st.M, a.B > a.st.Bn ? a.B : a.st.Bn);
+  if (a.st.conv_in) {
+    a.prelogits = (float*)prelogits;
+    a.pre_stride = prelogits_stride(a.st.M, a.B > a.st.Bn ? a.B : a.st.Bn);
+  }
   if (a.groups <= 0) return hipErrorInvalidValue;   // the caller keeps such shapes away
   a.psplit = a.groups < chains ? 1 : position_split(a.st.batch, a.st.Hkv, a.st.M, a.st.k_width, a.st.conv_in, n_cu);
   a.pipe = a.groups == chains && step_pipeline(a.st.batch, a.st.Hkv, a.st.M, a.st.k_width, a.st.conv_in, n_cu) ? 1 : 0;

@@ -45,3 +45,27 @@ def test_schedules_leave_the_same_bits(case, cur, dtype, d):
     assert got[0][3:] == got[1][3:]
     for x, y in zip(got[0][:3], got[1][:3]):
         assert torch.isfinite(x.float()).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 3])
+@pytest.mark.parametrize("cur", [0, 1])
+def test_scans_over_keys_and_values_leave_the_same_bits(cur, blocks):
+    """Their area for the key-side logits is where scans over the keys are told the place of the last state."""
+    g = torch.Generator(device=DEV).manual_seed(12)
+    b, h, M, B, d = 1, 4, 64, 50, 128
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0, 0.3, generator=g)
+    q, k, v = (rnd(b, h, B * blocks, d) for _ in range(3))
+    w, ck, cv = rnd(M, 2 * d, 15) * 0.2, rnd(b, h, M, d), rnd(b, h, M, d)
+    cfg = lb.make_config(dtype=torch.bfloat16, batch=b, n_q_heads=h, n_kv_heads=h, head_dim=d, M=M, conv_width=15, conv_in=1, norm=1)
+    got = []
+    for history in (1, 0):
+        cache = lb.Cache(cfg, DEV)
+        cache.c.cur = cur
+        cache.load(ck, cv, M)
+        o = torch.full_like(q, float("nan"))
+        lb.lococo_sequence_forward(cfg, q, k, v, o, w, None, cache, B, lb.workspace(cfg, B * blocks, B, history, DEV))
+        torch.cuda.synchronize()
+        got.append((o, cache.k.clone(), cache.v.clone(), cache.len, cache.cur))
+    assert got[0][3:] == got[1][3:]
+    for x, y in zip(got[0][:3], got[1][:3]):
+        assert torch.isfinite(x.float()).all() and torch.equal(x, y)

@@ -56,3 +56,18 @@ def test_backward_kernels_keep_everything_in_registers(tmp_path, source):
     waves = dict(zip(names, (int(n) for n in re.findall(r"Occupancy \[waves/SIMD\]: (\d+)", r.stderr))))
     rows = {n: w for n, w in waves.items() if "bwd_rows_kILi1ELb0E" in n}
     assert len(rows) == (4 if source == "bwd_conv_mfma.hip" else 0) and all(w >= 4 for w in rows.values()), rows
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_step_kernels_take_nothing_that_only_scans_use(tmp_path):
+    """Scan and step kernels share their arguments, and a single step waits for them: where a scan over the keys leaves its last state
+    has to share its place with the area of [K | V] filters (with room of its own a step of 77 tokens on 256 slots took 1 % longer)."""
+    src = tmp_path / "args.hip"
+    src.write_text("""#include "lococo_internal.h"
+using lococo::ScanArgs;
+static_assert(offsetof(ScanArgs, last_k) == offsetof(ScanArgs, prelogits) && offsetof(ScanArgs, last_v) == offsetof(ScanArgs, pre_stride), "");
+static_assert(sizeof(ScanArgs) - sizeof(lococo::StepArgs) == 144, "bytes a step kernel takes beside the step's own");
+""")
+    r = subprocess.run(["hipcc", "-x", "hip", *lib_build.FLAGS, "--cuda-host-only", "-include", "cstddef", "-c", str(src), "-o",
+                        str(tmp_path / "args.o")], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-2000:]
