@@ -267,7 +267,8 @@ enum {
   LOCOCO_OPT_RESET = 0,             /* every option back to its default; value ignored                         */
   LOCOCO_OPT_SPIN_LIMIT = 1,        /* polls a waiting workgroup of the one-launch scan makes before it gives
                                        up (0 = default, 2^21); negative: give up at once                       */
-  LOCOCO_OPT_SCAN_PER_STEP = 2,     /* 1: launches per step even where one per scan, or per walk back, fits      */
+  LOCOCO_OPT_SCAN_PER_STEP = 2,     /* 1: launches per step even where one per scan, or per walk back, fits;
+                                       2: the scan's alone, the walk back in one launch where that fits        */
   LOCOCO_OPT_CHAIN_SYNC_DEVICE = 3, /* 1: workgroups of a chain always meet with device-scope release and
                                        acquire (default: without the L2 write-back when they find themselves
                                        on one XCD)                                                             */
@@ -394,7 +395,7 @@ LOCOCO_API lococo_status lococo_sequence_backward(const lococo_config* cfg, cons
  * that ran: its name (static storage), the number of launches and the summed
  * device time in milliseconds.  *n_inout: capacity of `out` on entry, rows
  * available on return.  A lococo_segment_step whose attention shares the compression's launch is one
- * row, "compress_mfma"; the backward's own kernels have none.  Host pointers.  Meant for benchmarks; not thread safe
+ * row, "compress_mfma"; of the backward's own kernels the walk in one launch has a row, "bwd_walk", the others have none.  Host pointers.  Meant for benchmarks; not thread safe
  * against concurrent begin/end. */
 typedef struct lococo_kernel_time {
   const char* name;

@@ -62,11 +62,11 @@ lococo_status hip_fail(hipError_t e, const char* what) {
 // ---- optional per-kernel timing with HIP events (lococo_timing_begin / _end)
 enum KernelId { K_ATTN_GENERIC, K_FILL, K_CONV_GENERIC, K_NORM_GENERIC, K_MIX_GENERIC,
                 K_REPACK, K_COMPRESS_MFMA, K_ATTN_MFMA, K_ATTN_DECODE, K_ATTN_COLSUM, K_CONV_MFMA, K_MIX_MFMA,
-                K_COMPRESS_SMALL, K_COUNT };
+                K_COMPRESS_SMALL, K_BWD_WALK, K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"attn_generic", "fill", "conv_logits_generic",
                                            "normalise_generic", "mix_generic", "repack_filters",
                                            "compress_mfma", "attn_mfma", "attn_decode", "attn_colsum",
-                                           "conv_logits_mfma", "mix_mfma", "compress_small"};
+                                           "conv_logits_mfma", "mix_mfma", "compress_small", "bwd_walk"};
 struct TimedLaunch { int id; hipEvent_t start, stop; };
 std::mutex g_timing_mu;
 bool g_timing_on = false;
@@ -84,6 +84,12 @@ struct KTimer {
       return;
     }
     (void)hipEventRecord(start, s);
+  }
+  void drop() {                            // nothing was launched after all
+    if (!start) return;
+    (void)hipEventDestroy(start);
+    (void)hipEventDestroy(stop);
+    start = stop = nullptr;
   }
   ~KTimer() {
     if (!start) return;
@@ -597,14 +603,19 @@ lococo_status enqueue_scan(const lococo_config* c, const StepArgs& a, int64_t n_
 lococo_status enqueue_bwd_walk(const lococo_config* c, const BwdConvArgs& g, int hi, int n, void* ws, hipStream_t s, bool* cleared,
                                bool* taken) {
   *taken = false;
-  if (g_debug.scan_per_step) return LOCOCO_OK;
+  if (g_debug.scan_per_step == 1) return LOCOCO_OK;
   const bool capturing = stream_is_capturing(s);
   std::unique_lock<std::mutex> lk(g_scan_mu);
   if (!capturing && another_scan_in_flight(s)) return LOCOCO_OK;
   char* sync_ws = (char*)ws + filter_ws_bytes(c);
   if (!*cleared)
     HIP_TRY(launch_scan_sync_clear(sync_ws, c->batch, c->n_kv_heads, c->M, true, s), "clearing the scan counters");
-  HIP_TRY(launch_bwd_conv_walk(g, hi, n, sync_ws, spin_limit(), chain_sync_through_l2(), taken, s), "backward walk launch");
+  {
+    KTimer t(K_BWD_WALK, s);
+    const hipError_t e = launch_bwd_conv_walk(g, hi, n, sync_ws, spin_limit(), chain_sync_through_l2(), taken, s);
+    if (e != hipSuccess || !*taken) t.drop();
+    HIP_TRY(e, "backward walk launch");
+  }
   *cleared = !*taken;
   if (*taken && !capturing) note_scan_launched(s);
   return LOCOCO_OK;
@@ -690,7 +701,7 @@ lococo_status lococo_debug_option(int32_t option, int64_t value) {
   switch (option) {
     case LOCOCO_OPT_RESET: g_debug = DebugOptions{0, 0, 0, 0, 0, 0, 0}; return LOCOCO_OK;
     case LOCOCO_OPT_SPIN_LIMIT: g_debug.spin_limit = value; return LOCOCO_OK;
-    case LOCOCO_OPT_SCAN_PER_STEP: g_debug.scan_per_step = value != 0; return LOCOCO_OK;
+    case LOCOCO_OPT_SCAN_PER_STEP: g_debug.scan_per_step = value == 2 ? 2 : value != 0; return LOCOCO_OK;
     case LOCOCO_OPT_CHAIN_SYNC_DEVICE: g_debug.chain_sync_device = value != 0; return LOCOCO_OK;
     case LOCOCO_OPT_LOGITS_TILES:
       if (value != 0 && value != 64 && value != 128 && value != 256)

@@ -12,7 +12,7 @@ namespace lococo {
 // Process-wide test and measurement hooks (lococo_debug_option); every field 0 by default.
 struct DebugOptions {
   int64_t spin_limit;         // polls a waiting workgroup makes before it gives up (0: the default)
-  int64_t scan_per_step;      // 1: launches per step even where one launch per scan, or per walk back through it, fits
+  int64_t scan_per_step;      // 1: launches per step even where one launch per scan, or per walk back through it, fits; 2: the scan's alone
   int64_t chain_sync_device;  // 1: the slot tiles of a chain always meet with device-scope release / acquire
   int64_t logits_tiles;       // 64 | 128 | 256: slots per workgroup of the Eq. 5 kernel of the unfused MFMA path
   int64_t max_resident;       // > 0: pretend that only this many workgroups of the scan kernel fit the GPU at once

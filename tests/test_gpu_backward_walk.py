@@ -1,6 +1,9 @@
 """The backward walk over the blocks of a window in one launch, against the same walk with two launches a block (the two differ in
 the order of their sums alone): slot tiles of every number it takes, odd ones whose last pair of row tiles is half empty, blocks
-in two and in three parts, first blocks with fewer live slots, its meetings, and what it does where it cannot have the device."""
+in two and in three parts, first blocks with fewer live slots, its meetings, and what it does where it cannot have the device.
+How many walks a call launched is read from its timing rows, and asserted."""
+import itertools
+
 import pytest
 import torch
 
@@ -48,9 +51,16 @@ class Scan:
     def run(self):
         for t in self.out:
             t.fill_(float("nan"))
+        lb.lococo_timing_begin()
         self.enqueue()
+        self.walks = lb.lococo_timing_end().get("bwd_walk", (0, 0.0))[0]
         torch.cuda.synchronize()
         return [t.clone() for t in (*self.out, self.d_w)]
+
+    def runs(self):
+        """Walks the call takes: runs of two or more compressing blocks of one form (three parts: positions no multiple of 4)."""
+        forms = [(before + n) % 4 != 0 for _, n, branch, before, _, _ in lb.lococo_plan(self.L, self.B, self.cfg.M, self.cache.len) if branch]
+        return sum(len(list(run)) > 1 for _, run in itertools.groupby(forms))
 
     def status(self):
         return lb.lococo_scan_status(self.cfg, self.ws)
@@ -86,17 +96,19 @@ CASES = [
 def test_one_launch_against_two_a_block(case, options):
     s = Scan(**case)
     got = s.run()
-    assert s.status() == 0
+    assert s.status() == 0 and s.walks == s.runs() > 0
     options(lb.LOCOCO_OPT_SCAN_PER_STEP, 1)
     close(got, s.run())
+    assert s.walks == 0
 
 
 def test_meetings_with_device_scope(options):
     s = Scan(M=96, B=80, L=500, kv=8, heads=8)
     got = s.run()
+    assert s.walks == s.runs() > 0
     options(lb.LOCOCO_OPT_CHAIN_SYNC_DEVICE, 1)
     again = s.run()
-    assert s.status() == 0
+    assert s.status() == 0 and s.walks == s.runs()
     for a, b in zip(got[:5], again[:5]):
         assert torch.equal(a, b)
 
@@ -112,17 +124,44 @@ def test_a_wait_that_gives_up_is_reported(options):
     assert s.status() == 0
 
 
+def test_the_walk_reports_a_wait_of_its_own(options):
+    """The recomputed scan in launches per step, which wait for nobody: what is in the status word is the walk's."""
+    s = Scan(M=128, B=128, L=700)
+    options(lb.LOCOCO_OPT_SCAN_PER_STEP, 2)
+    want = s.run()
+    assert s.walks == s.runs() > 0 and s.status() == 0
+    options(lb.LOCOCO_OPT_SPIN_LIMIT, -1)
+    s.run()
+    assert s.walks > 0 and s.status() == 1
+    options(lb.LOCOCO_OPT_SCAN_PER_STEP, 1)                                   # (nobody waits: the word is cleared and stays so)
+    close(s.run(), want)
+    assert s.walks == 0 and s.status() == 0
+
+
+def test_gradients_of_the_last_state_that_are_4_byte_aligned_only():
+    s = Scan(M=96, B=80, L=500, kv=8, heads=8)
+    want = s.run()
+    s.d_f = [torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape) for t in s.d_f]
+    assert all(t.data_ptr() % 16 for t in s.d_f)
+    got = s.run()
+    assert s.walks == s.runs() > 0
+    for a, b in zip(got[:5], want[:5]):
+        assert torch.equal(a, b)
+
+
 def test_two_launches_a_block_where_the_grid_would_not_be_resident(options):
     s = Scan(M=128, B=128, L=700, kv=4, heads=4)
     want = s.run()
+    assert s.walks == s.runs() > 0
     options(lb.LOCOCO_OPT_MAX_RESIDENT, 15)                                   # four workgroups a chain and pair of tiles: 32
     close(s.run(), want)
-    assert s.status() == 0
+    assert s.status() == 0 and s.walks == 0
 
 
 def test_two_streams_and_a_captured_graph():
     s, t = Scan(M=128, B=100, L=600, kv=8, heads=8), Scan(M=128, B=100, L=600, kv=8, heads=8, seed=9)
     want = [x.run() for x in (s, t)]
+    assert s.walks == t.walks == s.runs() > 0
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     for _ in range(3):
         for x, st in zip((s, t), streams):
