@@ -1016,9 +1016,9 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
     const bool small_scan = path == PATH_GENERIC &&
                             small_scan_one_launch(cfg->dtype, cfg->M + B, cfg->M, cfg->head_dim, cfg->conv_width, cfg->conv_in);
     int64_t c_done = 0;                       // compress steps enqueued so far: state c_done - 1 is the newest
-    // (scans over [K | V] run on the kernel of two roles, which single steps of 17 us share: with the choice of where to write in
-    // it these took 0.4 us longer, so their last state is copied)
-    const bool direct = n_compress > 0 && plan.back().buf_after != tmp.cur && !(path == PATH_MFMA && cfg->conv_in);
+    const bool direct = n_compress > 0 && plan.back().buf_after != tmp.cur &&
+                        (path != PATH_MFMA || n_compress == 1 ||
+                         compress_scan_last_to_caller(make_args(cfg, seq, 0, B, &tmp, conv_w, conv_b, true), B, n_compress, cu_count()));
     for (int64_t w0 = 0; w0 < n; w0 += window) {
       const int64_t w1 = std::min<int64_t>(n, w0 + window);
       // the state the window starts from: the caller's live buffer until the first compression
@@ -1039,7 +1039,7 @@ lococo_status lococo_sequence_forward(const lococo_config* cfg, const lococo_qkv
           continue;
         }
         // The last state of all is nobody's but the caller's, and goes there at once where the attention that follows does not
-        // read the buffer: where that is not the one the call found the cache in.
+        // read the buffer (where that is not the one the call found the cache in) and the scan's kernel can tell its last step.
         void* const last_k = direct ? tmp.k[plan.back().buf_after] : nullptr;
         void* const last_v = direct ? tmp.v[plan.back().buf_after] : nullptr;
         a.cache_k = c_done == 0 ? tmp.k[tmp.cur] : slot_k(c_done - 1);

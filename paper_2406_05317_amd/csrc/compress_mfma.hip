@@ -103,8 +103,11 @@ int position_split(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu
   while (p < 4 && grid * (2 * p) <= n_cu && M / 32 >= 4 * (2 * p)) p *= 2;
   return p;
 }
+// builds whose last step can write to the caller beside those that always can (last_to_caller)
+template <int BM, int KW, int PROT, int SPLIT>
+constexpr bool kLastBuild = BM == 32 && KW == 15 && PROT == 0 && SPLIT == 2;
 template <class F>
-hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool logits, bool one_step, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
+hipError_t with_instantiation(const StepArgs& t, bool multi, int split, int log, bool one_step, int n_cu, F&& f) {   // split: 0, 1 positions, 2 steps
   const bool big = use_big_tiles(t.batch, t.Hkv, t.M, t.k_width, t.conv_in, n_cu);
   auto pick_cin = [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto spl) {
     if constexpr (decltype(bm)::value == 32) {
@@ -114,7 +117,10 @@ hipError_t with_instantiation(const StepArgs& t, bool multi, int split, bool log
       }
     }
     if constexpr (decltype(prot)::value == 0 && decltype(spl)::value != 1) {
-      if (logits) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<1>{}, ic<0>{});
+      if (log == 1) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<1>{}, ic<0>{});
+    }
+    if constexpr (kLastBuild<decltype(bm)::value, decltype(kw)::value, decltype(prot)::value, decltype(spl)::value>) {
+      if (log == 2) return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<2>{}, ic<0>{});
     }
     return f(bm, kw, norm, prot, mu, spl, ic<0>{}, ic<0>{}, ic<0>{});
   };
@@ -149,7 +155,7 @@ hipError_t prepare_kernel() {
 
 hipError_t dispatch(const ScanArgs& a, const uint16_t* wp, int64_t wp_head_stride, int n_cu, hipStream_t s) {
   const bool multi = a.groups < a.st.batch * a.st.Hkv;
-  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), a.logits != nullptr, a.n_steps == 1 && !a.logits, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
+  return with_instantiation(a.st, multi, a.pipe ? 2 : (a.psplit > 1 ? 1 : 0), a.logits ? 1 : !a.st.conv_in && a.last_k ? 2 : 0, a.n_steps == 1 && !a.logits, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
     constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value, ROLES = decltype(ro)::value;
@@ -279,6 +285,20 @@ hipError_t launch_compress_mfma(const StepArgs& a, const void* wp, int banks, in
   return dispatch(sa, (const uint16_t*)wp, wp_head_stride, n_cu, s);
 }
 
+bool compress_scan_last_to_caller(const StepArgs& a, int B, int64_t n_steps, int n_cu) {
+  // (scans over [K | V] run on the kernel of two roles, which single steps of 17 us share: with the choice in it these took 0.4 us
+  // longer)
+  if (a.conv_in) return false;
+  const bool per_head = a.w_head_stride != 0 || a.b_head_stride != 0;
+  const bool multi = compress_scan_groups(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, per_head, n_cu) < a.batch * a.Hkv;
+  if (last_to_caller(use_big_tiles(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) ? 64 : 32, a.k_width, multi)) return true;
+  // The build of pairs that can tell its last step costs as much more a step as its walk is long, the copy 2 - 3 us a call.  With it
+  // against without, us: 96 slots of 192 positions, 32 chains, 3 steps 57.6 and 60.2, 127 steps 1147 and 1163; 512 of 798, 8 chains, 3
+  // steps 114.3 and 116.1, 9 steps 258.1 and 256.2, 127 steps 3139 and 3096; 256 of 512, 9 steps 161.4 and 162.2, 63 steps 896 and 891.
+  const int T = a.M + B;
+  return !a.protect && (T <= 256 || n_steps * T <= 5000) && step_pipeline(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu);
+}
+
 bool compress_scan_leaves_logits(bool protect, int conv_in, bool position_split) { return !protect && !conv_in && !position_split; }
 
 int compress_tile_slots(int batch, int Hkv, int M, int k_width, int conv_in, int n_cu) {
@@ -292,7 +312,7 @@ int compress_scan_max_resident(const StepArgs& a, int n_cu) {
   const int split = multi ? 0 : step_pipeline(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) ? 2
                     : position_split(a.batch, a.Hkv, a.M, a.k_width, a.conv_in, n_cu) > 1 ? 1 : 0;
   int per_cu = 0;
-  hipError_t e = with_instantiation(a, multi, split, false, false, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
+  hipError_t e = with_instantiation(a, multi, split, 0, false, n_cu, [&](auto bm, auto kw, auto norm, auto prot, auto mu, auto sp, auto ci, auto lo, auto ro) {
     constexpr int BM = decltype(bm)::value, KW = decltype(kw)::value, NORM = decltype(norm)::value;
     constexpr int PROT = decltype(prot)::value, MULTI = decltype(mu)::value, SPLIT = decltype(sp)::value;
     constexpr int CIN = decltype(ci)::value, LOG = decltype(lo)::value, ROLES = decltype(ro)::value;

@@ -70,6 +70,13 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 constexpr int kD = 128;            // head_dim = conv channels
 constexpr int kThreads = 256;
 constexpr int BN = 32;             // positions per tile
+
+// Whether a build's last step always can write its state to the caller (ScanArgs::last_k) in place of its slot.  The choice costs
+// registers in the epilogue of every step and saves a copy a call.  In the 32-slot, one-chain builds of width 15 it puts six vector
+// registers (softmax, pairs) into scratch memory: 132 steps on 512 slots, 8 chains, 3147 us without it and 3193 with, 102 on 160, 32
+// chains, 1452 and 1463, 126 on 128, 64 chains, 1815 and 1833.  In the others it is free or better: width 21, 65 on 352, 8 chains, 1452
+// without and 1436 with; 64 slots a workgroup, 53 on 512, 32 chains, 2823 and 2795; several chains, 62 on 128, 1562 and 1553.
+constexpr bool last_to_caller(int bm, int kw, bool multi) { return bm == 64 || kw != 15 || multi; }
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.0f;      // the softmax reference lags the row maximum by at most this much
 
@@ -197,6 +204,7 @@ __device__ __forceinline__ Cat16 load_cat16(const CatRows& c, int p, int chunk) 
 // workgroup of each pair idle, so that results do not depend on the kind of launch.)
 // LOG = 1 (compress_tile.inl): the logits of Eq. 5 also go to memory, step by step [chains, M, ld], for the backward pass of a
 // scan (no protected slots, filters over the keys).
+// LOG = 2: no logits, but the last step can write to the caller, where the build without cannot (see last_to_caller).
 // CIN = 1 (compress_roles.h): filters over [K | V] (two walks, see the head of the file); wp then holds the key half of
 // every bank's slices followed by the value half, each in the order above.
 

@@ -273,7 +273,7 @@
         if (slot >= 8 * S && slot < 8 * S + E4) sm_add(0, slot - 8 * S);
         if (slot >= 8 * S + E4 && slot < 8 * S + 2 * E4) sm_add(2, slot - 8 * S - E4);
         if (slot == 8 * S + 2 * E4) __builtin_amdgcn_s_barrier();   // B2: the partial logits have been consumed
-        if (LOG && slot == 8 * S + 2 * E4 + 1) {       // the logits as they are, for the backward pass
+        if (LOG == 1 && slot == 8 * S + 2 * E4 + 1) {       // the logits as they are, for the backward pass
 #pragma unroll
           for (int e4 = 0; e4 < E4; ++e4) {
             const f32x4 v = {sv[e4 * 4], sv[e4 * 4 + 1], sv[e4 * 4 + 2], sv[e4 * 4 + 3]};
@@ -527,7 +527,7 @@
       jbase = lo * BN;
       NT = hi > lo ? hi - lo : 0;
     }
-    if (LOG)
+    if (LOG == 1)
       log_rows = __builtin_amdgcn_make_buffer_rsrc((void*)(sa.logits + step * sa.logits_stride + ((int64_t)ch * a.M + i0) * sa.logits_ld), 0,
                                                    BM * sa.logits_ld * 4, 0x00020000);
     const int64_t prev = (int64_t)((sa.slot0 + step - 1) % sa.ring) * sa.out_stride;   // (unused for step 0)
@@ -711,9 +711,11 @@
     const int64_t out_at = (int64_t)((sa.slot0 + step) % sa.ring) * sa.out_stride + ((int64_t)ch * a.M + i0) * kD;
     nk = (uint16_t*)sa.out_k + out_at;
     nv = (uint16_t*)sa.out_v + out_at;
-    if (step > 0 && step + 1 == sa.n_steps && sa.last_k) {     // (a single step looks no further)
-      nk = (uint16_t*)sa.last_k + ((int64_t)ch * a.M + i0) * kD;
-      nv = (uint16_t*)sa.last_v + ((int64_t)ch * a.M + i0) * kD;
+    if constexpr (LOG == 2 || last_to_caller(BM, KW, MULTI)) {
+      if (step > 0 && step + 1 == sa.n_steps && sa.last_k) {   // (a single step looks no further)
+        nk = (uint16_t*)sa.last_k + ((int64_t)ch * a.M + i0) * kD;
+        nv = (uint16_t*)sa.last_v + ((int64_t)ch * a.M + i0) * kD;
+      }
     }
   }
   if constexpr (PSPLIT) {

@@ -85,6 +85,7 @@ struct ScanArgs {
   union {
     float* prelogits;        // [K | V]: key-side logits between the two walks of a step (launcher)
     void* last_k;            // keys: not null: where the last of several steps writes its state, in place of its slot
+                             // (only where compress_scan_last_to_caller)
   };
   union {
     int64_t pre_stride;      // [K | V]: floats per (chain, 32-slot tile) there (launcher)
@@ -231,6 +232,8 @@ size_t compress_scan_sync_bytes(int batch, int Hkv, int M);
 // zero them (a fill kernel, so the call may sit inside a captured graph); keep_status: only the chain
 // counters, not the status word (between the launches of one call)
 hipError_t launch_scan_sync_clear(void* sync_ws, int batch, int Hkv, int M, bool keep_status, hipStream_t s);
+// whether the scan kernel of this shape (blocks of B tokens, n_steps of them) is to write the last of several states to the caller
+bool compress_scan_last_to_caller(const StepArgs& a, int B, int64_t n_steps, int n_cu);
 // whether the scan kernel of this shape can leave its logits in memory
 bool compress_scan_leaves_logits(bool protect, int conv_in, bool position_split);
 // the same kernel over n_steps consecutive compress steps (see ScanArgs); `sync_ws` is

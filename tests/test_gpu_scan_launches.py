@@ -69,3 +69,35 @@ def test_scans_over_keys_and_values_leave_the_same_bits(cur, blocks):
     assert got[0][3:] == got[1][3:]
     for x, y in zip(got[0][:3], got[1][:3]):
         assert torch.isfinite(x.float()).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("steps", [2, 3])
+@pytest.mark.parametrize("case", [
+    dict(M=64, heads=4, width=21),               # two workgroups a pair that take the steps in turn
+    dict(M=64, heads=4, width=15),               # so, few positions: the build that can tell its last step
+    dict(M=512, heads=4, width=15),              # more, but few steps
+    dict(M=512, heads=4, width=15, steps=11),    # and so many that the state is copied
+    dict(M=96, heads=64, width=21),              # one, a chain each
+    dict(M=96, heads=96, width=15),              # several chains a workgroup
+    dict(M=128, heads=128, width=15),            # 64 slots a workgroup
+    dict(M=128, heads=160, width=15),            # and several chains
+    dict(M=96, heads=64, width=15),              # one chain each, width 15: the state is copied
+], ids=str)
+def test_builds_whose_last_step_writes_to_the_caller(case, steps):
+    g = torch.Generator(device=DEV).manual_seed(13)
+    h, M, B, d, steps = case["heads"], case["M"], 40, 128, case.get("steps", steps)
+    rnd = lambda *s: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0, 0.3, generator=g)
+    q, k, v = (rnd(1, h, B * steps - 3, d) for _ in range(3))
+    w, ck, cv = rnd(M, d, case["width"]) * 0.2, rnd(1, h, M, d), rnd(1, h, M, d)
+    cfg = lb.make_config(dtype=torch.bfloat16, batch=1, n_q_heads=h, n_kv_heads=h, head_dim=d, M=M, conv_width=case["width"])
+    got = []
+    for history in (1, 0):
+        cache = lb.Cache(cfg, DEV)
+        cache.load(ck, cv, M)
+        o = torch.full_like(q, float("nan"))
+        lb.lococo_sequence_forward(cfg, q, k, v, o, w, None, cache, B, lb.workspace(cfg, q.shape[2], B, history, DEV))
+        torch.cuda.synchronize()
+        got.append((o, cache.k.clone(), cache.v.clone(), cache.len, cache.cur))
+    assert got[0][3:] == got[1][3:]
+    for x, y in zip(got[0][:3], got[1][:3]):
+        assert torch.isfinite(x.float()).all() and torch.equal(x, y)
