@@ -101,3 +101,35 @@ def test_builds_whose_last_step_writes_to_the_caller(case, steps):
     assert got[0][3:] == got[1][3:]
     for x, y in zip(got[0][:3], got[1][:3]):
         assert torch.isfinite(x.float()).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3])
+@pytest.mark.parametrize("case", [
+    dict(dtype=torch.float32, d=32, M=24, width=5),
+    dict(dtype=torch.float32, d=80, M=17, width=3),               # a second slot tile of one slot
+    dict(dtype=torch.float32, d=64, M=16, width=3, conv_in=1),    # values in the rows of the keys
+    dict(dtype=torch.bfloat16, d=64, M=20, width=9),
+    dict(dtype=torch.bfloat16, d=40, M=20, width=5, heads=3, protect=True),
+], ids=str)
+def test_small_scans_hand_over_their_rows(case, steps):
+    g = torch.Generator(device=DEV).manual_seed(14)
+    h, M, d, dtype, conv_in = case.get("heads", 2), case["M"], case["d"], case["dtype"], case.get("conv_in", 0)
+    B = M - 3
+    rnd = lambda *s: torch.empty(s, dtype=dtype, device=DEV).normal_(0, 0.3, generator=g)
+    q, k, v = (rnd(2, h, B * steps - 1, d) for _ in range(3))
+    w, ck, cv = rnd(M, d * (1 + conv_in), case["width"]) * 0.2, rnd(2, h, M, d), rnd(2, h, M, d)
+    cfg = lb.make_config(dtype=dtype, batch=2, n_q_heads=h, n_kv_heads=h, head_dim=d, M=M, conv_width=case["width"], conv_in=conv_in, impl=1)
+    got = []
+    for history in (1, 2, 0):
+        cache = lb.Cache(cfg, DEV)
+        cache.load(ck, cv, M)
+        if case.get("protect"):
+            cache.set_protect((torch.arange(M) % 5 == 0).view(1, 1, -1).expand(2, h, -1).numpy())
+        o = torch.full_like(q, float("nan"))
+        lb.lococo_sequence_forward(cfg, q, k, v, o, w, None, cache, B, lb.workspace(cfg, q.shape[2], B, history, DEV))
+        torch.cuda.synchronize()
+        got.append((o, cache.k.clone(), cache.v.clone(), cache.len, cache.cur))
+    for other in got[1:]:
+        assert got[0][3:] == other[3:]
+        for x, y in zip(got[0][:3], other[:3]):
+            assert torch.isfinite(x.float()).all() and torch.equal(x, y)
