@@ -1667,7 +1667,7 @@ lococo_status lococo_sequence_backward(const lococo_config* cfg, const lococo_qk
           if (path == PATH_MFMA && bwd_conv_walk_takes(c))
             while (run <= i && bwd_conv_three_parts(c, i - run) == bwd_conv_three_parts(c, i)) ++run;
           bool taken = false;
-          if (run > 1 && (st = enqueue_bwd_walk(cfg, c, i, run, ws + l.fwd_ws, s, &walk_clear, &taken))) return st;
+          if (run >= bwd_conv_walk_least(c, i) && (st = enqueue_bwd_walk(cfg, c, i, run, ws + l.fwd_ws, s, &walk_clear, &taken))) return st;
           if (taken) {
             i -= run - 1;
             continue;

@@ -1666,6 +1666,13 @@ bool bwd_conv_walk_takes(const BwdConvArgs& g) {
   return a.M % 32 == 0 && a.norm == 0 && !a.conv_in && !a.protect && !g.d_conv_b && a.k_width <= 25 && a.M <= 256 && a.M + g.B <= 512 &&
          (int64_t)a.batch * a.Hkv * ((a.M + 63) / 64 * 4) <= cu_count() && bwd_conv_defers_blocks(g);
 }
+// The fewest blocks (hi, hi - 1, ..) it is worth taking: its start, a census and a first block prepared with nothing to hide that, costs
+// 10 - 20 us (and clearing the counters 3 in every window but the first), and a block saves 2 - 4 in two parts, 8 in three.  A pass over
+// few blocks, from a full cache, in two launches a block and in one launch, us: 128 slots, 256 positions, 32 chains 237 / 246 (2 blocks),
+// 321 / 323 (4), 409 / 404 (6); 96 slots of width 21 199 / 212, 295 / 301, 373 / 372; 256 slots, 384 positions, 8 chains 248 / 261, 337 /
+// 345, 427 / 433, 517 / 515 (8); 128 slots, 229 positions, three parts 249 / 256, 342 / 339, 457 / 439; 64 slots, 8 chains 136 / 142, 187 /
+// 187, 234 / 229.
+int bwd_conv_walk_least(const BwdConvArgs& g, int hi) { return bwd_conv_three_parts(g, hi) || g.st.M <= 64 ? 4 : 6; }
 hipError_t launch_bwd_conv_walk(const BwdConvArgs& g, int hi, int n, void* sync_ws, int spin_limit, bool through_l2, bool* taken,
                                 hipStream_t s) {
   const StepArgs& a = g.st;

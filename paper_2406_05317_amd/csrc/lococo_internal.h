@@ -360,6 +360,7 @@ hipError_t launch_bwd_conv_dx(const BwdConvArgs& g, int blk0, int n_blk, int par
 // cleared beforehand.  What a wait that gave up leaves in the status word: 1.
 bool bwd_conv_three_parts(const BwdConvArgs& g, int blk);
 bool bwd_conv_walk_takes(const BwdConvArgs& g);
+int bwd_conv_walk_least(const BwdConvArgs& g, int hi);
 hipError_t launch_bwd_conv_walk(const BwdConvArgs& g, int hi, int n, void* sync_ws, int spin_limit, bool through_l2, bool* taken,
                                 hipStream_t s);
 // whether the rows of the blocks themselves are better taken together, after the walk

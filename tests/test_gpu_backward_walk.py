@@ -58,9 +58,10 @@ class Scan:
         return [t.clone() for t in (*self.out, self.d_w)]
 
     def runs(self):
-        """Walks the call takes: runs of two or more compressing blocks of one form (three parts: positions no multiple of 4)."""
+        """Walks the call takes: runs of compressing blocks of one form (three parts: positions no multiple of 4), of at least 6, or of
+        4 in three parts or on 64 slots and fewer."""
         forms = [(before + n) % 4 != 0 for _, n, branch, before, _, _ in lb.lococo_plan(self.L, self.B, self.cfg.M, self.cache.len) if branch]
-        return sum(len(list(run)) > 1 for _, run in itertools.groupby(forms))
+        return sum(len(list(run)) >= (4 if three or self.cfg.M <= 64 else 6) for three, run in itertools.groupby(forms))
 
     def status(self):
         return lb.lococo_scan_status(self.cfg, self.ws)
@@ -78,17 +79,20 @@ def close(got, want):
 CASES = [
     dict(M=32, B=32, L=170),                                                  # one slot tile: half a pair of row tiles
     dict(M=64, B=33, L=300, kv=3, heads=6),                                   # three parts, chains not all on one XCD
-    dict(M=96, B=96, L=500, width=21),                                        # an odd number of tiles
-    dict(M=128, B=128, L=700, kv=32, heads=32),                               # every compute unit
-    dict(M=128, B=128, L=650, len0=70),                                       # a first block that finds 70 live slots
+    dict(M=96, B=96, L=692, width=21),                                        # an odd number of tiles
+    dict(M=128, B=128, L=956, kv=32, heads=32),                               # every compute unit
+    dict(M=128, B=128, L=906, len0=70),                                       # a first block that finds 70 live slots
     dict(M=128, B=101, L=500, len0=128, width=21, per_head=True),             # three parts, banks of their own
     dict(M=160, B=97, L=600, kv=8, heads=8),                                  # 257 positions: two tiles a wave, one round of five
-    dict(M=192, B=191, L=900, batch=2),                                       # three parts, two rounds of three
-    dict(M=224, B=224, L=1000, kv=4, heads=8),                                # one round of seven, a half-empty pair
-    dict(M=256, B=256, L=1400, kv=8, heads=8, batch=2),                       # the largest; the last block in parts of its own
+    dict(M=192, B=191, L=1091, batch=2),                                       # three parts, two rounds of three
+    dict(M=224, B=224, L=1448, kv=4, heads=8),                                # one round of seven, a half-empty pair
+    dict(M=256, B=256, L=1913, kv=8, heads=8, batch=2),                       # the largest; the last block in parts of its own
     dict(M=256, B=255, L=1300, len0=3, width=21),                             # three parts, three live slots
     dict(M=96, B=20, L=330, kv=4, heads=4),                                   # four fill blocks in the filters' launch
     dict(M=64, B=200, L=900),                                                 # blocks longer than the cache, an empty first state
+    dict(M=128, B=100, L=700, len0=128),                                      # six blocks and a seventh
+    dict(M=64, B=33, L=132, len0=64),                                         # four in three parts: the fewest
+    dict(M=96, B=96, L=576, len0=96),                                         # six in two
 ]
 
 
@@ -102,8 +106,28 @@ def test_one_launch_against_two_a_block(case, options):
     assert s.walks == 0
 
 
+@pytest.mark.parametrize("case", [dict(M=96, B=96, L=480, len0=96), dict(M=64, B=33, L=99, len0=64), dict(M=128, B=128, L=256, len0=128)], ids=str)
+def test_few_blocks_are_walked_one_by_one(case):
+    s = Scan(**case)
+    s.run()
+    assert s.walks == s.runs() == 0 and s.status() == 0
+
+
+def test_windows_of_a_smaller_workspace(options):
+    """Counters cleared again for every window; windows too short for the walk."""
+    s = Scan(M=64, B=64, L=64 * 31)
+    want, whole = s.run(), s.ws
+    walks = []
+    for part in (0.6, 0.4, 0.25):
+        s.ws = torch.full((int(part * whole.numel()),), 0xff, dtype=torch.uint8, device=DEV)
+        close(s.run(), want)
+        assert s.status() == 0
+        walks.append(s.walks)
+    assert walks[0] > 1 and walks[-1] != walks[0], walks
+
+
 def test_meetings_with_device_scope(options):
-    s = Scan(M=96, B=80, L=500, kv=8, heads=8)
+    s = Scan(M=96, B=80, L=660, kv=8, heads=8)
     got = s.run()
     assert s.walks == s.runs() > 0
     options(lb.LOCOCO_OPT_CHAIN_SYNC_DEVICE, 1)
@@ -114,7 +138,7 @@ def test_meetings_with_device_scope(options):
 
 
 def test_a_wait_that_gives_up_is_reported(options):
-    s = Scan(M=128, B=128, L=700)
+    s = Scan(M=128, B=128, L=956)
     want = s.run()
     options(lb.LOCOCO_OPT_SPIN_LIMIT, -1)
     s.run()
@@ -126,7 +150,7 @@ def test_a_wait_that_gives_up_is_reported(options):
 
 def test_the_walk_reports_a_wait_of_its_own(options):
     """The recomputed scan in launches per step, which wait for nobody: what is in the status word is the walk's."""
-    s = Scan(M=128, B=128, L=700)
+    s = Scan(M=128, B=128, L=956)
     options(lb.LOCOCO_OPT_SCAN_PER_STEP, 2)
     want = s.run()
     assert s.walks == s.runs() > 0 and s.status() == 0
@@ -139,7 +163,7 @@ def test_the_walk_reports_a_wait_of_its_own(options):
 
 
 def test_gradients_of_the_last_state_that_are_4_byte_aligned_only():
-    s = Scan(M=96, B=80, L=500, kv=8, heads=8)
+    s = Scan(M=96, B=80, L=660, kv=8, heads=8)
     want = s.run()
     s.d_f = [torch.cat([t.new_zeros(1), t.flatten()])[1:].view(t.shape) for t in s.d_f]
     assert all(t.data_ptr() % 16 for t in s.d_f)
@@ -150,7 +174,7 @@ def test_gradients_of_the_last_state_that_are_4_byte_aligned_only():
 
 
 def test_two_launches_a_block_where_the_grid_would_not_be_resident(options):
-    s = Scan(M=128, B=128, L=700, kv=4, heads=4)
+    s = Scan(M=128, B=128, L=956, kv=4, heads=4)
     want = s.run()
     assert s.walks == s.runs() > 0
     options(lb.LOCOCO_OPT_MAX_RESIDENT, 15)                                   # four workgroups a chain and pair of tiles: 32
@@ -159,7 +183,7 @@ def test_two_launches_a_block_where_the_grid_would_not_be_resident(options):
 
 
 def test_two_streams_and_a_captured_graph():
-    s, t = Scan(M=128, B=100, L=600, kv=8, heads=8), Scan(M=128, B=100, L=600, kv=8, heads=8, seed=9)
+    s, t = Scan(M=128, B=100, L=800, kv=8, heads=8), Scan(M=128, B=100, L=800, kv=8, heads=8, seed=9)
     want = [x.run() for x in (s, t)]
     assert s.walks == t.walks == s.runs() > 0
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
