@@ -9,7 +9,7 @@
 // rows staying in LDS from step to step; otherwise each step is one launch of a workgroup per 16 slots.
 // Measured on that smallest scan (15 compressions): 1209 us with three kernels per step and one attention launch per
 // block (63 us of each step in the 64 x 64-tiled Eq. 5, one workgroup), 104 us with compress_small_k at first, 71 us with its operand
-// reads issued in groups ahead of their products and its reductions on the vector unit, 38 us with compress64_k in its place.
+// reads issued in groups ahead of their products and its reductions on the vector unit, 37 us with compress64_k in its place.
 #include <algorithm>
 #include <type_traits>
 
@@ -389,10 +389,10 @@ __global__ __launch_bounds__(kNT) void compress_small_k(SmallArgs g) {
 // between the barriers of a step: one in some five cycles a wave, two waves to a SIMD.  So filters stay in registers in operand order
 // (read once, through LDS in whole lines: from memory each lane's own touch 64 lines an instruction), operands are read 16 bytes a lane
 // (four steps of the contraction, in an order both operands share), rows move four at a time, a row of Eq. 6 takes a lane as few
-// positions as it has, and the four barriers of a step wait for LDS alone.  A step of the smallest scan (M = B = 16, width 3):
-// 10 400 -> 4 500 cycles, 61 -> 28.5 us the 15 of them (970 Eq. 5, its products 770; 950 Eq. 6; 940 Eq. 4, its products 510).  A launch
-// per step (8 tokens on 60 slots, width 5): 15.9 -> 7.7 us, half of it before the first product; 22 on 95, width 9: 24.2 -> 11.8, four
-// of them products of Eq. 5.
+// positions as it has, and the four barriers of a step wait for LDS alone.  The 15 steps of the smallest scan (M = B = 16, width 3),
+// in the general kernel and here: 61.3 and 29.3 us; by clock stamps 4 500 cycles a step here (970 Eq. 5, its products 770; 950 Eq. 6;
+// 940 Eq. 4, its products 510).  A launch per step (8 tokens on 60 slots, width 5): 15.5 and 7.2 us, half of it before the first product;
+// 22 on 95, width 9: 23.6 and 11.3, four of them products of Eq. 5.
 constexpr int k64 = 64, kSx = 68;            // head_dim; row stride of X and V: 16 rows x 4 columns on 64 banks
 constexpr int kPF64 = 6;                     // items of the next block a wave fetches ahead: 96 rows in all
 constexpr int kParts = 4, kPosGroups = 2;    // a wave: a quarter of the channels, every second tile of 16 positions
@@ -830,9 +830,11 @@ hipError_t launch(const SmallArgs& g, int grid_x, hipStream_t s) {
   return g.st.conv_in ? launch_d<T, MIX, 64, 1>(g, grid_x, s) : launch_d<T, MIX, 64, 0>(g, grid_x, s);
 }
 
-// Slot tiles a workgroup of compress64_k holds the filters and sums of without spilling registers
+// Slot tiles a workgroup of compress64_k holds the filters and sums of without vector registers in scratch memory (with three, or norms 1
+// and 2, up to 20 scalar ones lie in lanes of vector registers)
 constexpr int tiles64(int k) { return k <= 5 ? 3 : k <= 11 ? 2 : 1; }
-// whether compress64_k has a build for this width and the positions fit with `tiles` slot tiles to a workgroup
+// whether compress64_k has a build for this width (every odd one from 3 to 15, and 21, the widest a workload here has; others are
+// compress_small_k's) and the positions fit with `tiles` slot tiles to a workgroup
 bool fits64(int dtype, int T, int d, int k, int conv_in, int tiles) {
   return dtype == LOCOCO_F32 && d == k64 && !conv_in && k >= 3 && (k <= 15 || k == 21) && tiles <= tiles64(k) && T <= 256 &&
          layout64_of(T, k, tiles).bytes <= kLds;
@@ -877,8 +879,8 @@ bool small_step_fits(int T, int M, int d, int k, int conv_in) { return taps_that
 
 // All steps of a scan in one launch where one workgroup holds a whole chain: LDS, the registers of Eq. 4 (or of the filters), and no
 // more matrix work put on one compute unit per step than the launch it saves costs (12 000 cycles, about 5 us: the
-// dispatch of a dependent kernel plus reading rows and filters back in; 8 tokens on 28 slots, width 5, 2 500 cycles more: 4.3 us
-// a step, in launches of their own 7.7).
+// dispatch of a dependent kernel plus reading rows and filters back in; compress64_k, 8 tokens on 28 slots, width 5, 1 900 cycles more
+// by this count: 4.2 us a step, in a launch of its own 5.6 and the way from one to the next).
 bool small_scan_one_launch(int dtype, int T, int M, int d, int k, int conv_in) {
   const int tiles = (M + 15) / 16, C4 = ((conv_in ? 2 * d : d) + 3) / 4;
   if (fits64(dtype, std::max(T, 2 * M), d, k, conv_in, 1)) {     // (decided like small_step_fits: a step is the same bits in either form)

@@ -1,5 +1,6 @@
-"""Registers of the two-role compression kernel and of the backward kernels, as the compiler reports them (CPU: nothing is run).
-In the former a SIMD holds a wave of either role, 256 registers each.  A build that wants more keeps the rest in scratch memory: the
+"""Registers of the compression kernels, of the small fp32 scan and of the backward kernels, as the compiler reports them (CPU: nothing
+is run): vector registers and scratch memory.  Scalar registers a build has too many of lie in lanes of vector ones and are not looked at.
+In the two-role kernel a SIMD holds a wave of either role, 256 registers each.  A build that wants more keeps the rest in scratch memory: the
 logit waves of width 21 then read addresses back in front of every walk, 1 % of a step of several chains."""
 import os
 import re
@@ -86,6 +87,19 @@ def test_backward_kernels_keep_everything_in_registers(tmp_path, source):
     waves = dict(zip(names, (int(n) for n in re.findall(r"Occupancy \[waves/SIMD\]: (\d+)", r.stderr))))
     rows = {n: w for n, w in waves.items() if "bwd_rows_kILi1ELb0E" in n}
     assert len(rows) == (4 if source == "bwd_conv_mfma.hip" else 0) and all(w >= 4 for w in rows.values()), rows
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_small_scan_kernels_keep_everything_in_registers(tmp_path):
+    """compress64_k: 15 builds of a width and a number of slot tiles, each for either kind of Eq. 6."""
+    r = subprocess.run(["hipcc", "-x", "hip", *lib_build.FLAGS, "--cuda-device-only", "-c", os.path.join(lib_build.CSRC, "scan_small.hip"),
+                        "-o", str(tmp_path / "small.o"), "-Rpass-analysis=kernel-resource-usage"], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    names = re.findall(r"Function Name: (\S+)", r.stderr)
+    spilled = [int(n) for n in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
+    scratch = [int(n) for n in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
+    assert len(names) == len(spilled) == len(scratch) and sum("compress64_k" in n for n in names) == 30
+    assert not any(spilled) and not any(scratch), dict(zip(names, zip(spilled, scratch)))
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
