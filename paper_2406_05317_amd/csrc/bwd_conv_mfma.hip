@@ -735,7 +735,8 @@ __global__ __launch_bounds__(512, NC == 64 || PT == 64 ? 4 : 2) void bwd_dx_k(Bw
 // its sums were added to, so that is read past its L1.
 // Clock stamps of the former (49 000 cycles a step): 4 000 from g to its halves in LDS, 2 400 G, 1 200 row sums, 3 800 dl, 4 700 until it
 // is known to have arrived, 3 000 to have it back, 9 500 taps and n g (4 600 of matrix work, the rest the forty instructions around a
-// tap's four products), 6 000 partial sums.
+// tap's four products), 6 000 partial sums.  (143 to 168 scalar values of a build lie in lanes of vector registers; none of the
+// vector registers is in scratch memory.)
 struct WalkArgs {
   BwdConvArgs c;
   int32_t hi, n;             // blocks hi, hi - 1, .. hi - n + 1

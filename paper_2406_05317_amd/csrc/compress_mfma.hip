@@ -353,6 +353,7 @@ hipError_t launch_compress_scan(const ScanArgs& a_in, const void* wp, int banks,
     a.pre_stride = prelogits_stride(a.st.M, a.B > a.st.Bn ? a.B : a.st.Bn);
   }
   if (a.groups <= 0) return hipErrorInvalidValue;   // the caller keeps such shapes away
+  if (!a.st.conv_in && a.last_k && !compress_scan_last_to_caller(a.st, a.B, a.n_steps, n_cu)) return hipErrorInvalidValue;   // (and these)
   a.psplit = a.groups < chains ? 1 : position_split(a.st.batch, a.st.Hkv, a.st.M, a.st.k_width, a.st.conv_in, n_cu);
   a.pipe = a.groups == chains && step_pipeline(a.st.batch, a.st.Hkv, a.st.M, a.st.k_width, a.st.conv_in, n_cu) ? 1 : 0;
   if (a.pipe) a.psplit = 2;
